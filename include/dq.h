@@ -142,8 +142,10 @@ dq_status dq_mx_decompress(dq_codec fmt, const void *packed_in, const void *loca
 
 /* ---- Hop replay (Section 3.4 "Reduce-scatter", Appendix B): N simulated workers whose
  * reordered gradients all live in this GPU's HBM; a transfer between workers is a pointer
- * hand-off.  One kernel launch per schedule step covers every (worker, chunk) job of that
- * step.  DQ_RING / DQ_BUTTERFLY: worker_grads[w] holds worker w's n_buckets buckets back to
+ * hand-off.  Run step by step, one kernel launch per schedule step covers every (worker, chunk) job
+ * of that step; run whole, a DQ_DYNAMIQ schedule is a single launch in which every super-group is
+ * carried through all its hops on the chip (same results; of the messages of a ring or chain the last two
+ * steps' are written, the others never leave the chip).  DQ_RING / DQ_BUTTERFLY: worker_grads[w] holds worker w's n_buckets buckets back to
  * back, each n_sg_bucket SGs (a multiple of n_workers; butterfly needs a power of two);
  * bucket b uses widths n_sg_by_width[4*b..4*b+3] and global SG indices starting at
  * first_sg + b*n_sg_bucket; `out` receives the reduced buckets (the SUM over workers, fp32,
@@ -211,7 +213,8 @@ dq_status dq_replay_step_info(const dq_replay *plan, uint32_t step, uint32_t *ki
 /* DQ_RING / DQ_CHAIN: where the packed message that step `step` writes for chunk `chunk` of bucket
  * `bucket` sits inside scratch, and its size (dq_packed_bytes of that chunk) -- what the worker that ran
  * the step would hand to the transport (Section 3.4: the compressed partial sum sent to the next hop).
- * It stays intact until step + 2 has run (two message sets, written alternately).  DQ_EINVAL for the
+ * It stays intact until step + 2 has run (two message sets, written alternately); after a whole replay the
+ * last two steps' messages are there.  DQ_EINVAL for the
  * last step (it writes fp32 sums, not a message) or indices out of range; DQ_EUNSUPPORTED for a
  * butterfly plan. */
 dq_status dq_replay_message(const dq_replay *plan, uint32_t step, uint32_t bucket, uint32_t chunk, const void **ptr,

@@ -73,11 +73,11 @@ bool build_levels(int R, double g, std::vector<float> &T, std::vector<float> &D)
     D[r] = T[r + 1] - T[r];
     if (!(D[r] > 0.0f)) return false;
   }
-  D[R] = 0.0f;  // at the top level T + u*D = 1 is never below x'
+  D[R] = 0.0f;
   return true;
 }
 
-// Search table over q = round(x * 2^m): the closed bin [(q-1/2)/2^m, (q+1/2)/2^m] holds at
+// Search table over q = floor(round(x * 2^(m+3)) / 8): the closed bin [(q - 1/16)/2^m, (q + 15/16)/2^m] holds at
 // most one level boundary, so the level at or below x is rc(q) or rc(q)+1.
 bool build_search(const std::vector<float> &T, int R, int *m_out, std::vector<uint32_t> &lut) {
   float min_gap = 1.0f;
@@ -89,7 +89,7 @@ bool build_search(const std::vector<float> &T, int R, int *m_out, std::vector<ui
     lut.assign(2 * (size_t)n, 0u);
     bool ok = true;
     for (int q = 0; q < n && ok; ++q) {
-      const double lo = fmax(0.0, ((double)q - 0.5) * w), hi = fmin(1.0, ((double)q + 0.5) * w);
+      const double lo = fmax(0.0, ((double)q - 0.0625) * w), hi = fmin(1.0, ((double)q + 0.9375) * w);
       int rc = 0;
       while (rc < R && (double)T[rc + 1] <= lo) ++rc;
       if (rc > R - 1) ok = false;
@@ -180,6 +180,7 @@ dq_status dq_create(const dq_config *cfg, dq_ctx **out) {
   // ([reciprocals][2-bit decode][4-bit decode][4-bit {T,D}][8-bit decode][8-bit {T,D}]), then the
   // two search tables, whose size follows the level sets.
   std::vector<uint32_t> lut[3];
+  int bins_log[3] = {0, 0, 0};
   auto range = [&](int r, uint32_t lo, uint32_t width) {
     P.range_lo[r] = lo;
     P.range_hi[r] = (uint32_t)blob.size();
@@ -190,8 +191,8 @@ dq_status dq_create(const dq_config *cfg, dq_ctx **out) {
     for (int m = 0; m < 128; ++m) {
       const float sig = 1.0f + (float)m / 128.0f;
       const float a = sig / 255.0f, b = 255.0f / sig;
-      rec[2 * m] = fbits(a);
-      rec[2 * m + 1] = fbits(b);
+      rec[2 * m] = fbits(a) - (127u << 23);
+      rec[2 * m + 1] = fbits(b) + (127u << 23);
     }
     uint32_t off;
     append_aligned(blob, rec, &off);
@@ -218,19 +219,25 @@ dq_status dq_create(const dq_config *cfg, dq_ctx **out) {
     append_aligned(blob, dec, &off_dec);
     if (off_dec != want_dec[wi]) return DQ_EINVAL;
     if (wi > 0) {  // levels {0,1} need no search
-      std::vector<uint32_t> tab(2 * (size_t)(R + 1));
-      for (int r = 0; r <= R; ++r) {
-        tab[2 * r] = fbits(T[r]);
-        tab[2 * r + 1] = fbits(D[r]);
-      }
-      // at the top level nothing rounds up: T + u*D is held above every x' the kernels can form (they
-      // do not clamp x' to 1; it can exceed 1 by an ulp when the reciprocal of the group maximum is denormal)
-      tab[2 * R] = fbits(2.0f);
+      // pair r: the entries of levels r+1 and r, 16 bytes each; at the top level nothing rounds up: T + u*D is
+      // infinite, above every x' the kernels can form (they do not clamp x' to 1; it can exceed 1 by an ulp
+      // when the reciprocal of the group maximum is denormal)
+      std::vector<uint32_t> tab(8 * (size_t)R);
+      for (int r = 0; r < R; ++r)
+        for (int up = 0; up < 2; ++up) {
+          const int at = r + 1 - up;
+          uint32_t *e = &tab[8 * (size_t)r + 4 * (size_t)up];
+          e[0] = fbits(T[at]);
+          e[1] = at == R ? 0x7F800000u : fbits(D[at]);
+          e[2] = fbits(T[at == R ? R : at + 1]);
+          e[3] = (uint32_t)at << (32 - b);
+        }
       append_aligned(blob, tab, &off_tab);
       if (off_tab != want_tab[wi]) return DQ_EINVAL;
       int m = 0;
       if (!build_search(T, R, &m, lut[wi])) return DQ_EUNSUPPORTED;
-      P.magic[wi] = (float)ldexp(1.0, 23 - m);
+      for (size_t q = 1; q < lut[wi].size(); q += 2) lut[wi][q] = off_tab * 4 + 32 * lut[wi][q];  // LDS address of the pair
+      bins_log[wi] = m;
     }
     while (blob.size() % 4) blob.push_back(0);
     range(1 + wi, off_dec, (uint32_t)wi);
@@ -241,9 +248,15 @@ dq_status dq_create(const dq_config *cfg, dq_ctx **out) {
     if (off != dq::kOffLut4) return DQ_EINVAL;
     while (blob.size() % 4) blob.push_back(0);
     range(4, off, 1);
-    append_aligned(blob, lut[2], &P.off_lut8);
+    uint32_t off8;
+    append_aligned(blob, lut[2], &off8);
     while (blob.size() % 4) blob.push_back(0);
-    range(5, P.off_lut8, 2);
+    range(5, off8, 2);
+    const uint32_t lut_at[3] = {0, off * 4, off8 * 4};  // LDS byte addresses
+    for (int wi = 1; wi < 3; ++wi) {
+      const uint32_t bits = fbits((float)ldexp(1.0, 20 - bins_log[wi])) + lut_at[wi];
+      memcpy(&P.magic[wi], &bits, 4);
+    }
   }
   if (blob.size() * 4 > 60 * 1024) return DQ_EUNSUPPORTED;
 
@@ -288,13 +301,13 @@ dq_status dq_create(const dq_config *cfg, dq_ctx **out) {
   P.key1 = (uint32_t)(cfg->seed >> 32);
   P.round = cfg->round;
   P.n_workers = cfg->n_workers;
-  P.n_mask = (cfg->n_workers & (cfg->n_workers - 1)) == 0 ? cfg->n_workers - 1 : 0xFFFFFFFFu;
   while ((1u << P.perm_bits) < cfg->n_workers) ++P.perm_bits;  // the shared permutation mixes integers of this many bits
-  P.inv_n = 1.0f / (float)cfg->n_workers;
-  if (cfg->independent_rounding) {  // the case n = 1 of the same arithmetic: one interval, slot 0
-    P.inv_n = 1.0f;
-    P.n_mask = 0;
-  }
+  // independent rounding is the case n = 1 of the same arithmetic: one interval, slot 0
+  P.n_slots = cfg->independent_rounding ? 1u : cfg->n_workers;
+  P.slot_keep = cfg->independent_rounding ? 0u : 0xFFFFFFFFu;
+  for (uint32_t g = 0; g < 16; ++g) P.g_mod |= (uint64_t)(g % P.n_slots) << (4 * g);
+  P.inv_n = 1.0f / (float)P.n_slots;
+  P.inv_n512 = P.inv_n * (1.0f / 512.0f);
   P.s_n = P.inv_n * (1.0f / 256.0f);
   ctx->params = P;
   *out = ctx;

@@ -4,6 +4,8 @@
 #include <stdint.h>
 #include <stdlib.h>
 
+#include <vector>
+
 #include "dq.h"
 
 namespace dq {
@@ -47,13 +49,13 @@ inline Job make_job(const uint8_t *in, const void *local, const float *mu, void 
 // search tables, whose size follows the level sets, come last.  The kernels take LDS byte address
 // 0 for the start of the blob: they use dynamic LDS only, which starts at 0 when a kernel has no
 // static LDS (checked once per context, see static_lds_bytes).
-constexpr uint32_t kOffRec = 0;        // 128 pairs {bits((1+m/128)/255), bits(255/(1+m/128))}
+constexpr uint32_t kOffRec = 0;        // 128 pairs {bits((1+m/128)/255) - bias, bits(255/(1+m/128)) + bias}, bias = 127 << 23
 constexpr uint32_t kOffDec2 = 256;     // 2-bit decode: 256 bytes x 4 signed levels
 constexpr uint32_t kOffDec4 = 1280;    // 4-bit decode: 256 bytes x 2 signed levels
-constexpr uint32_t kOffTab4 = 1792;    // 8 pairs {T, D}
-constexpr uint32_t kOffDec8 = 1808;    // 8-bit decode: 256 signed levels
-constexpr uint32_t kOffTab8 = 2064;    // 128 pairs {T, D}
-constexpr uint32_t kOffLut4 = 2320;    // search table of the 4-bit set: (2^m + 1) pairs {next level, candidate index}
+constexpr uint32_t kOffTab4 = 1792;    // 4-bit levels: 7 pairs of entries {T[r], D[r], T[r+1], r << 28}, of r+1 and of r
+constexpr uint32_t kOffDec8 = 1848;    // 8-bit decode: 256 signed levels
+constexpr uint32_t kOffTab8 = 2104;    // 8-bit levels: 127 pairs of entries {T[r], D[r], T[r+1], r << 24}
+constexpr uint32_t kOffLut4 = 3120;    // search table of the 4-bit set: (2^m + 1) pairs {next level, address of the candidate's pair}
 constexpr int kRanges = 6;             // copy ranges: common, 2-bit, 4-bit fixed, 8-bit fixed, 4-bit search, 8-bit search
 
 // Everything the kernels need besides the job: PRNG key, worker count, table blob.
@@ -62,16 +64,45 @@ struct Params {
   uint32_t blob_dwords;  // multiple of 4
   uint32_t range_lo[kRanges], range_hi[kRanges];  // dword ranges a block copies into LDS (multiples of 4) ...
   uint32_t range_width[kRanges];                  // ... if it meets tiles of this width index (3: always)
-  uint32_t off_lut8;     // search table of the 8-bit set (dword offset; its size follows the set)
-  float magic[3];        // 2^(23-m): adding it leaves round(x * 2^m) in the low mantissa bits
+  float magic[3];        // 2^(20-m) plus the search table's LDS address in units of its last bit (see quantize_codes)
   uint32_t key0, key1, round;
   uint32_t n_workers;
-  uint32_t n_mask;       // n-1 if n is a power of two, else 0xFFFFFFFF (meaning: use %)
   uint32_t perm_bits;    // ceil(log2 n): width of the integers the rounding permutation mixes
-  float inv_n, s_n;
+  uint32_t n_slots;      // intervals the rounding divides [0,1) into: n, or 1 for independent rounding
+  uint32_t slot_keep;    // all ones, or 0 for independent rounding: every slot is 0
+  uint64_t g_mod;        // nibble g: g mod n_slots (g itself above 16)
+  float inv_n;           // 1 / n_slots
+  float inv_n512;        // inv_n / 512
+  float s_n;             // inv_n / 256: one step of an entry's random byte
 };
 
 enum Kind { kCompress = 0, kDar = 1, kDecompress = 2 };
+
+// One chunk of one bucket on its way through a whole schedule (dq_walk.hip).
+struct WalkPath {
+  Job job;          // `local` is the chunk's byte offset inside every worker's tensor; `in` and `rank` are not used
+  uint8_t *msg[2];  // ring, chain: where the packed messages of even and odd steps go (the last two are written)
+  uint32_t chunk;
+};
+struct Walk {
+  const void *const *grads;  // device: the workers' tensors
+  uint32_t n, log_n;         // workers (log_n: butterfly)
+  uint32_t encodes;          // how many leaves are followed by an encoding: n - 1, or n with the all-gather
+  uint32_t first_kept;       // ring, chain: first step whose message is written
+  uint32_t chain;            // 1: leaf i is worker i
+  uint32_t hops_log;         // log2 of the hops one call of the per-super-group draws covers
+  uint32_t stack_bytes;      // butterfly: LDS per wave for the pending messages
+  uint32_t n_paths;
+  uint32_t widths;           // which widths some chunk has (bit k: 2 << k bits)
+  uint32_t blocks, waves;    // grid, waves per block
+};
+struct WalkShare {
+  uint32_t path, tile;
+};
+constexpr uint32_t kStackCoded = 1280, kStackRaw = 2048;  // bytes of a pending message per wave: codes and scale, or raw bf16
+bool split_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths_host, Walk *W, std::vector<WalkShare> *shares);
+hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W,
+                       const Params &P, hipStream_t stream);
 
 // kernel launchers (dq_kernels.hip); grid_blocks = thread blocks the GPU keeps resident at once
 hipError_t launch_one(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &p, uint32_t grid_blocks,

@@ -55,6 +55,12 @@ struct Plan {
   uint8_t *ring_msg[2] = {nullptr, nullptr};
   uint32_t ring_chunks = 0;   // chunks per bucket (0: not a ring or chain)
   uint32_t ring_message_steps = 0;  // steps 0 .. this-1 write messages
+  // the whole schedule as one launch (dq_walk.hip): one path per (bucket, chunk), the workers' tensors
+  bool walk = false, tree = false;
+  dq::Walk w = {};
+  std::vector<dq::WalkPath> paths;  // freed once they are on the device
+  std::vector<dq::WalkShare> shares;
+  size_t paths_off = 0, shares_off = 0, grads_off = 0;
 };
 
 bool is_mx(dq_codec c) { return c == DQ_MXFP8_E4M3 || c == DQ_MXFP6_E3M2 || c == DQ_MXFP4_E2M1; }
@@ -77,6 +83,68 @@ void chunk_widths(const uint32_t by_width[4], uint64_t m, uint32_t c, uint32_t o
     const uint64_t a = lo > edges[w] ? lo : edges[w], b = hi < edges[w + 1] ? hi : edges[w + 1];
     out[w] = b > a ? (uint32_t)(b - a) : 0;
   }
+}
+
+struct ChunkInfo {
+  uint32_t n_sg[4];
+  uint64_t first_sg;
+  size_t bytes;
+};
+
+// The same schedule as one launch that carries every tile through all its hops (dq_walk.hip).
+void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, uint32_t n_chunks, uint64_t m, float *out, Plan *plan,
+               size_t *off) {
+  const uint32_t n = ctx->cfg.n_workers;
+  const size_t es = elt_size(d->dtype);
+  const uint64_t bucket_bytes = d->n_sg_bucket * 256 * es;
+  dq::Walk &w = plan->w;
+  w.n = n;
+  while ((1u << w.log_n) < n) ++w.log_n;
+  w.encodes = d->all_gather ? n : n - 1;
+  w.first_kept = n > 3 ? n - 3 : 0;
+  w.chain = d->topology == DQ_CHAIN;
+  while ((1u << w.hops_log) < w.encodes && w.hops_log < 4) ++w.hops_log;
+  plan->tree = d->topology == DQ_BUTTERFLY;
+  bool raw = false;
+  w.n_paths = d->n_buckets * n_chunks;
+  plan->paths.resize(w.n_paths);
+  for (uint32_t b = 0; b < d->n_buckets; ++b)
+    for (uint32_t c = 0; c < n_chunks; ++c) {
+      const size_t i = (size_t)b * n_chunks + c;
+      const ChunkInfo &x = ci[i];
+      dq::WalkPath &p = plan->paths[i];
+      const uint64_t sg = x.first_sg - d->first_sg;  // place in the reordered bucket set
+      const uint64_t local = (uint64_t)b * bucket_bytes + (d->inputs_in_original_order ? 0 : (uint64_t)c * m * 256 * es);
+      float *o = out + (uint64_t)b * d->n_sg_bucket * 256;
+      p.job = dq::make_job(nullptr, reinterpret_cast<const void *>((uintptr_t)local), d->mu ? d->mu + sg : nullptr,
+                           d->origin ? o : o + (uint64_t)c * m * 256, x.first_sg, x.n_sg, 0);
+      if (d->inputs_in_original_order) p.job.src = d->origin + sg;
+      if (d->origin) {
+        p.job.dest = d->origin + sg;
+        p.job.back = d->mu ? d->mu + sg : nullptr;
+      }
+      for (int k = 0; k < 2; ++k) p.msg[k] = plan->ring_chunks ? plan->ring_msg[k] + plan->ring_slot[i] : nullptr;
+      p.chunk = c;
+      raw = raw || x.n_sg[3] != 0;
+    }
+  // butterfly: a pending message for every level above the first; the area also stages half a tile's result
+  const uint32_t levels = w.log_n > 1 ? w.log_n - 1 : 1;
+  w.stack_bytes = levels * (raw ? dq::kStackRaw : dq::kStackCoded);
+  if (w.stack_bytes < 2048) w.stack_bytes = 2048;
+  plan->walk = dq::split_walk(ctx->params, plan->tree, ctx->n_cu, plan->paths.data(), &w, &plan->shares);
+  if (!plan->walk) {
+    plan->paths.clear();
+    return;
+  }
+  *off = align_up(*off, 256);
+  plan->paths_off = *off;
+  *off += plan->paths.size() * sizeof(dq::WalkPath);
+  *off = align_up(*off, 256);
+  plan->shares_off = *off;
+  *off += plan->shares.size() * sizeof(dq::WalkShare);
+  *off = align_up(*off, 256);
+  plan->grads_off = *off;
+  *off += (size_t)n * sizeof(void *);
 }
 
 // Builds the whole schedule.  With base == nullptr only sizes are computed (pointers are
@@ -110,11 +178,6 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
   const uint64_t chunk_entries = m * 256;
 
   // per (bucket, chunk): widths, packed size
-  struct ChunkInfo {
-    uint32_t n_sg[4];
-    uint64_t first_sg;
-    size_t bytes;
-  };
   std::vector<ChunkInfo> ci((size_t)d->n_buckets * n_chunks);
   for (uint32_t b = 0; b < d->n_buckets; ++b) {
     uint32_t bw[4] = {(uint32_t)d->n_sg_bucket, 0, 0, 0};
@@ -321,6 +384,8 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
     plan->steps.push_back(std::move(sd));
   }
 
+  if (!mx) plan_walk(ctx, d, ci.data(), n_chunks, m, out, plan, &off);
+
   // job tables
   for (Step &st : plan->steps)
     for (Launch &L : st.launches) {
@@ -350,6 +415,8 @@ struct dq_replay {
   Plan plan;
   uint8_t *scratch;
   std::vector<hipEvent_t> events;
+  dq_dtype dtype;
+  bool means;
 };
 
 extern "C" {
@@ -374,6 +441,8 @@ dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *
   if (!r) return DQ_EINVAL;
   r->ctx = ctx;
   r->codec = desc->codec;
+  r->dtype = desc->dtype;
+  r->means = desc->mu != nullptr;
   r->scratch = static_cast<uint8_t *>(scratch);
   dq_status st = build_plan(ctx, desc, worker_grads, r->scratch, out, &r->plan);
   if (st == DQ_OK && r->plan.scratch_bytes > scratch_bytes) st = DQ_EINVAL;
@@ -382,6 +451,21 @@ dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *
     return st;
   }
   const bool mx = desc->codec != DQ_DYNAMIQ;
+  if (r->plan.walk) {
+    Plan &p = r->plan;
+    hipError_t e = hipMemcpy(r->scratch + p.paths_off, p.paths.data(), p.paths.size() * sizeof(dq::WalkPath), hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+      e = hipMemcpy(r->scratch + p.shares_off, p.shares.data(), p.shares.size() * sizeof(dq::WalkShare), hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+      e = hipMemcpy(r->scratch + p.grads_off, worker_grads, (size_t)p.w.n * sizeof(void *), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      delete r;
+      return dq::hip_status(e);
+    }
+    p.w.grads = reinterpret_cast<const void *const *>(r->scratch + p.grads_off);
+    std::vector<dq::WalkPath>().swap(p.paths);
+    std::vector<dq::WalkShare>().swap(p.shares);
+  }
   for (Step &s : r->plan.steps)
     for (Launch &L : s.launches) {
       if (L.jobs.empty()) continue;
@@ -454,8 +538,16 @@ static dq_status run_step(dq_replay *plan, size_t i, hipStream_t s, int only = -
   return DQ_OK;
 }
 
+// The whole schedule in one launch.
+static dq_status run_walk(dq_replay *r, hipStream_t s) {
+  const Plan &p = r->plan;
+  return dq::hip_status(dq::launch_walk(r->dtype, p.tree, r->means, reinterpret_cast<const dq::WalkPath *>(r->scratch + p.paths_off),
+                                        reinterpret_cast<const dq::WalkShare *>(r->scratch + p.shares_off), p.w, r->ctx->params, s));
+}
+
 dq_status dq_replay_run_steps(dq_replay *plan, uint32_t first, uint32_t count, void *hip_stream) {
   if (!plan || (size_t)first + count > plan->plan.steps.size()) return DQ_EINVAL;
+  if (plan->plan.walk && count == plan->plan.steps.size()) return run_walk(plan, (hipStream_t)hip_stream);
   for (uint32_t i = first; i < first + count; ++i) {
     const dq_status st = run_step(plan, i, (hipStream_t)hip_stream);
     if (st != DQ_OK) return st;
@@ -472,6 +564,7 @@ dq_status dq_replay_run(dq_replay *plan, float *step_ms, void *hip_stream) {
   if (!plan) return DQ_EINVAL;
   hipStream_t s = (hipStream_t)hip_stream;
   const size_t ns = plan->plan.steps.size();
+  if (plan->plan.walk && !step_ms) return run_walk(plan, s);
   hipError_t he = hipSuccess;
   while (step_ms && he == hipSuccess && plan->events.size() < ns + 1) {
     hipEvent_t e;

@@ -1,0 +1,459 @@
+// A whole replay in one launch: every tile of a chunk is carried through ALL hops of its schedule (first
+// compress, every DAR hop, the last decompress-accumulate, optionally the all-gather's compress and
+// decompress) by one wave, with the partial sum in registers.
+//
+// Why: a super-group's hop depends on nothing but the same super-group's hop before it, so the steps of a
+// schedule need no synchronisation between waves.  Launched step by step, a replay reads and writes every
+// packed partial sum once per hop, reads the fp32 keep-buffers of a recursive halving twice and pays the fixed part
+// of a launch (5 us: descriptor, tables, the first tile's trip to memory, the tail) per step.  Here a tile's
+// memory traffic is its n local slices and one result.
+//   ring / chain : leaf i is worker chunk + i (mod n) / worker i; one message is pending at a time and stays
+//                  in registers as signed levels and scale.  The packed messages of the last two steps are
+//                  also written, where dq_replay_message finds them.
+//   butterfly    : recursive halving of one chunk is a binary tree over the workers; the leaves are visited
+//                  depth first, the sending child of a node before the keeping one, so that at most one
+//                  message per level is pending.  A message that the next leaf takes stays in registers, the
+//                  others wait as packed codes in LDS (20 bytes per lane and level).
+// Per hop and tile the random numbers are the same Philox counters as in the step kernels; the per-super-group
+// draws of up to 16 hops are made by one wave-wide call (lane = tile of the batch, hop, row).
+#include "dq_codec.h"
+
+namespace dq {
+namespace {
+
+constexpr int kWalkWaves = 8;           // waves per block: they share one copy of the tables
+constexpr int kWalkThreads = kWalkWaves * 64;
+constexpr uint32_t kParkBytes = 1280;   // per wave: 64 scale draws of 16 bytes, 64 permutation slots
+constexpr uint32_t kXposeBytes = 2048;  // per wave: half a tile of fp32 results
+
+__device__ __forceinline__ void lds_st1(uint32_t a, uint32_t v) {
+  *reinterpret_cast<__attribute__((address_space(3))) uint32_t *>(a) = v;
+}
+
+// The lane's number, opaque to the compiler: what is derived from it is computed where it is used, once in many hops,
+// and not held in registers around the loops (a spilled register's reload waits for the tile's loads in flight).
+__device__ __forceinline__ uint32_t lane_here() {
+  uint32_t lane = threadIdx.x & 63u;
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+// Worker whose entries are the i-th a chunk meets.
+template <bool TREE>
+__device__ __forceinline__ uint32_t leaf_of(const Walk &W, uint32_t chunk, uint32_t i) {
+  if constexpr (TREE) {
+    return chunk ^ (__brev(~i) >> (32u - W.log_n));
+  } else {
+    const uint32_t x = (W.chain ? 0u : chunk) + i;
+    return min(x, x - W.n);
+  }
+}
+
+// Per-super-group draws for 2^hops_log hops, starting at hop i, of 16 >> hops_log tiles, starting at `pos`.
+template <bool TREE>
+__device__ __forceinline__ void park_hops(const Job &job, const Params &P, const Walk &W, uint32_t chunk, const TilePos pos,
+                                          uint32_t i, uint32_t area) {
+  const uint32_t lane = lane_here();
+  const uint32_t idx = lane >> 2, h = idx & ((1u << W.hops_log) - 1u), sub = idx >> W.hops_log;
+  const uint32_t sgw = min(pos.tile_first + sub * kWaveSGs + (lane & 3u), pos.n_seg - 1);
+  const uint64_t G = job.first_sg + pos.seg_first + sgw;
+  const uint32_t rank = leaf_of<TREE>(W, chunk, min(i + h, W.n - 1));  // hops past the last are drawn for nothing
+  const U4 shared = philox4x32_10((uint32_t)G, (uint32_t)(G >> 32), P.round, (2u << 16) | 0xFFFFu, P.key0, P.key1);
+  const U4 scale = philox4x32_10((uint32_t)G, (uint32_t)(G >> 32), P.round, (1u << 16) | (rank & 0xFFFFu), P.key0, P.key1);
+  lds_st4(area + lane * 16, u32x4{scale.x, scale.y, scale.z, scale.w});
+  lds_st1(area + 1024 + lane * 4, perm_slot(shared, P, rank));
+}
+
+template <typename LT>
+struct Slice {
+  uint4 w[sizeof(LT) == 4 ? 4 : 2];  // a lane's 16 entries, raw
+};
+// The launch's tables (tensors, paths, shares) are read through the constant address space, as nothing in the kernel
+// writes to them: scalar loads into scalar registers.  As global loads they are vector loads, and the one of the next
+// tensor's address waits in every hop for everything the wave has in flight.
+template <typename T>
+__device__ __forceinline__ T table_entry(const T *table, uint32_t i) {
+  constexpr uint32_t kWords = sizeof(T) / 4;
+  typedef __attribute__((address_space(4))) const uint32_t constant_u32;
+  constant_u32 *p = (constant_u32 *)(uintptr_t)table + (uint64_t)i * kWords;
+  struct Words { uint32_t w[kWords]; } words;
+#pragma unroll
+  for (uint32_t k = 0; k < kWords; ++k) words.w[k] = p[k];
+  return __builtin_bit_cast(T, words);
+}
+template <typename LT>
+__device__ __forceinline__ Slice<LT> load_slice(const Walk &W, uint32_t leaf, uint64_t at) {
+  const uint8_t *p = reinterpret_cast<const uint8_t *>(table_entry(reinterpret_cast<const uint64_t *>(W.grads), leaf)) + at;
+  Slice<LT> s;
+#pragma unroll
+  for (int i = 0; i < (sizeof(LT) == 4 ? 4 : 2); ++i) s.w[i] = gld16(p + 16 * i);
+  return s;
+}
+// Byte offset of this lane's 16 entries of the tile at `pos` inside every worker's tensor, and the mean to take off.
+template <typename LT, bool MU>
+__device__ __forceinline__ uint64_t slice_at(const Job &job, const TilePos pos, float *mu) {
+  const uint32_t lane = lane_here();
+  const uint32_t sg0 = pos.seg_first + min(pos.tile_first + (lane >> 4), pos.n_seg - 1);
+  const uint64_t sg = job.src ? (uint64_t)gld<uint32_t>(job.src + sg0) : (uint64_t)sg0;
+  if constexpr (MU) *mu = gld<float>(job.mu + sg0);
+  return (uint64_t)reinterpret_cast<uintptr_t>(job.local) + sg * (kSG * sizeof(LT)) + (lane & 15u) * (16 * sizeof(LT));
+}
+
+// A tile's results, v[16] per lane, to out[...] like store_tile_f32, two super-groups at a time.
+__device__ __forceinline__ void store_result(const Job &job, const Params &P, float (&v)[16], uint32_t xpose, const TilePos pos) {
+  const uint32_t lane = lane_here(), l = lane & 31u;
+  const uint32_t last_row = min((uint32_t)kWaveSGs - 1, pos.n_seg - 1 - pos.tile_first);
+  const size_t sg0 = (size_t)pos.seg_first + pos.tile_first;
+  if (job.back) {
+    const float back = (float)P.n_workers * gld<float>(job.back + sg0 + min(lane >> 4, last_row));
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = v[k] + back;
+  }
+  float *out = static_cast<float *>(job.out);
+#pragma unroll
+  for (uint32_t half = 0; half < 2; ++half) {
+    __builtin_amdgcn_wave_barrier();
+    if ((lane >> 5) == half) {
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i)
+        lds_stf4(xpose + l * 64 + ((i ^ ((l >> 2) & 3u)) * 16), f32x4{v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]});
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (uint32_t q = 0; q < 2; ++q) {
+      const uint32_t r = 2 * half + q;
+      if (r > last_row) break;
+      const uint32_t slot = q * 64 + lane, w = slot >> 2, c = slot & 3u;
+      const f32x4 o = lds_ldf4(xpose + w * 64 + ((c ^ ((w >> 2) & 3u)) * 16));
+      const size_t sg = job.dest ? (size_t)gld<uint32_t>(job.dest + sg0 + r) : sg0 + r;
+      gst<f32x4>(reinterpret_cast<float4 *>(out + sg * kSG) + lane, o);
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Where the LDS areas of a wave sit.
+struct Areas {
+  uint32_t park, xpose, stack;
+};
+
+enum { kNone = 0, kLevels = 1, kCodes = 2, kBoth = 3 };
+template <int N>
+struct How { static constexpr int value = N; };
+
+// `len` consecutive tiles of width B from `pos` on.
+template <int B, typename LT, bool MU, bool TREE>
+__device__ __forceinline__ void walk_tiles(const WalkPath &path, const Params &P, const Vec &V, const Walk &W, const Areas A,
+                                           TilePos pos, uint32_t len) {
+  const Job &job = path.job;
+  const uint32_t lane = threadIdx.x & 63u, g = lane & 15u;
+  const uint32_t hops = 1u << W.hops_log, tiles = 16u >> W.hops_log;
+  float mu = 0.0f, mu_next = 0.0f;
+  uint64_t at = slice_at<LT, MU>(job, pos, &mu);
+  Slice<LT> s = load_slice<LT>(W, leaf_of<TREE>(W, path.chunk, 0u), at);
+  for (uint32_t t = 0; t < len; ++t) {
+    TilePos pos_next = pos;
+    pos_next.tile_first += kWaveSGs;
+    const bool more = t + 1 < len;
+    uint64_t at_next = at;
+    if (more) at_next = slice_at<LT, MU>(job, pos_next, &mu_next);
+    const uint32_t rowc = min(lane >> 4, pos.n_seg - 1 - pos.tile_first);
+    const uint64_t gi = (job.first_sg + pos.seg_first + pos.tile_first + rowc) * 16 + g;  // global group index
+    float v[16];       // this leaf's entries, then the partial sum, then the message's signed levels
+    float level[16];   // the pending message: signed levels ...
+    float sfg = 0.0f;  // ... times this
+    // One leaf: its entries, plus the pending message (has), plus (tree) `taken` messages of the stack; then the
+    // encoding (kNone: it is the last).  The loops below are written so that every encoding variant has a body of its
+    // own: behind a branch the compiler computes what the variants share for all 16 entries first and runs
+    // out of registers.
+    auto leaf = [&](uint32_t i, bool has, uint32_t taken, auto how) {
+      constexpr int kHow = decltype(how)::value;
+      const uint32_t rank = leaf_of<TREE>(W, path.chunk, i);
+      Draws d;
+      if constexpr (kHow != kNone) {
+        if ((i & (hops - 1u)) == 0 && (t & (tiles - 1u)) == 0) {
+          __builtin_amdgcn_wave_barrier();
+          park_hops<TREE>(job, P, W, path.chunk, pos, i, A.park);
+          __builtin_amdgcn_wave_barrier();
+        }
+        const uint32_t slot = ((((t & (tiles - 1u)) << W.hops_log) + (i & (hops - 1u))) * 4 + rowc);
+        uint64_t index = gi;
+        asm volatile("" : "+v"(index));  // the generator's first round is not worth four registers around the loop
+        d = draw_group(P, index, rank, lds_ld1(A.park + 1024 + slot * 4), lds_ld1(A.park + slot * 16 + (g >> 2) * 4), g);
+        asm volatile("" : "+v"(s.w[0].x) : "v"(d.gam.x), "v"(d.gam.y), "v"(d.gam.z), "v"(d.gam.w), "v"(d.o_pi), "v"(d.us));
+      }
+      widen_local<LT>(s.w, v);
+      if constexpr (MU) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = v[k] - mu;
+      }
+      // the next leaf's entries, or the next tile's first
+      if (i + 1 < W.n) s = load_slice<LT>(W, leaf_of<TREE>(W, path.chunk, i + 1), at);
+      else if (more) s = load_slice<LT>(W, leaf_of<TREE>(W, path.chunk, 0u), at_next);
+      if (has) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = __builtin_fmaf(level[k], sfg, v[k]);
+      }
+      uint32_t stack = A.stack;
+      if constexpr (TREE) {
+#pragma unroll 1
+        for (uint32_t q = 0; q < taken; ++q, stack += kStackCoded) {
+          const u32x4 m = lds_ld4(stack + lane * 16);
+          const uint32_t ms[4] = {m.x, m.y, m.z, m.w};
+          uint32_t cw[Width<B>::words];
+#pragma unroll
+          for (int k = 0; k < Width<B>::words; ++k) cw[k] = ms[k];
+          const float f = u2f(lds_ld1(stack + 1024 + lane * 4));
+          each_level<B, HopTables>(cw, [&](int k, float l) { v[k] = __builtin_fmaf(l, f, v[k]); });
+        }
+      }
+      if constexpr (kHow != kNone) {
+        const Scales sc = scale_group(v, d.us, kRec0);
+        sfg = sc.sfg;
+        uint32_t ow[Width<B>::words];
+        quantize<B, (kHow & kCodes) != 0, (kHow & kLevels) != 0>(v, sc.inv, d.gam, d.o_pi, V, ow);
+        if constexpr (kHow == kCodes) {  // tree: onto the stack
+          u32x4 m = {0, 0, 0, 0};
+          m.x = ow[0];
+          if constexpr (B >= 4) m.y = ow[1];
+          if constexpr (B == 8) { m.z = ow[2]; m.w = ow[3]; }
+          lds_st4(stack + lane * 16, m);
+          lds_st1(stack + 1024 + lane * 4, f2u(sc.sfg));
+        } else {
+          if constexpr (kHow == kBoth) store_codes<B>(path.msg[i & 1u], TileBase<B>(job, pos), rowc * 16 + g, rowc, ow, sc.rg, sc.sfb);
+#pragma unroll
+          for (int k = 0; k < 16; ++k) level[k] = v[k];
+        }
+      }
+    };
+    const uint32_t last = W.n - 1;
+    const bool gathered = W.encodes == W.n;
+    uint32_t taken = 0;
+    if constexpr (TREE) {
+#pragma unroll 1
+      for (uint32_t i = 0;; i += 2) {
+        leaf(i, false, 0, How<kLevels>());
+        taken = __builtin_ctz(~(i >> 1));  // trailing ones above the lowest bit: the messages this node takes
+        if (i + 1 == last) break;
+        leaf(i + 1, true, taken, How<kCodes>());
+      }
+    } else {
+      uint32_t i = 0;
+#pragma unroll 1
+      for (; i < W.first_kept; ++i) leaf(i, i > 0, 0, How<kLevels>());
+#pragma unroll 1
+      for (; i < last; ++i) leaf(i, i > 0, 0, How<kBoth>());
+    }
+    if (gathered) {  // what every worker decodes from the sink's message
+      leaf(last, true, taken, How<kLevels>());
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = level[k] * sfg;
+    } else {
+      leaf(last, true, taken, How<kNone>());
+    }
+    store_result(job, P, v, A.xpose, pos);
+    pos = pos_next;
+    at = at_next;
+    mu = mu_next;
+  }
+}
+
+// The same for raw 16-bit super-groups: the message is the partial sum rounded to bf16.
+template <typename LT, bool TREE>
+__device__ __forceinline__ void walk_tile16(const WalkPath &path, const Params &P, const Walk &W, const Areas A, const TilePos pos) {
+  const Job &job = path.job;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t rowc = min(lane >> 4, pos.n_seg - 1 - pos.tile_first), lg = rowc * 16 + (lane & 15u);
+  float mu = 0.0f;
+  const uint64_t at = job.mu ? slice_at<LT, true>(job, pos, &mu) : slice_at<LT, false>(job, pos, &mu);
+  Slice<LT> s = load_slice<LT>(W, leaf_of<TREE>(W, path.chunk, 0u), at);
+  float v[16];
+  uint32_t m[8];  // the pending message
+#pragma unroll
+  for (int k = 0; k < 8; ++k) m[k] = 0;
+  auto take = [&](const uint32_t (&w)[8]) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      v[2 * j] = u2f(w[j] << 16) + v[2 * j];
+      v[2 * j + 1] = u2f(w[j] & 0xFFFF0000u) + v[2 * j + 1];
+    }
+  };
+#pragma unroll 1
+  for (uint32_t i = 0; i < W.n; ++i) {
+    widen_local<LT>(s.w, v);
+    if (job.mu) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = v[k] - mu;
+    }
+    if (i + 1 < W.n) s = load_slice<LT>(W, leaf_of<TREE>(W, path.chunk, i + 1), at);
+    if (TREE ? (i & 1u) : i > 0) take(m);
+    uint32_t up = i >> 1, stack = A.stack;
+    if constexpr (TREE) {
+      if (i & 1u) {
+#pragma unroll 1
+        for (; up & 1u; up >>= 1, stack += kStackRaw) {
+          const u32x4 a = lds_ld4(stack + lane * 16), b = lds_ld4(stack + 1024 + lane * 16);
+          const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+          take(w);
+        }
+      }
+    }
+    if (i < W.encodes) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) m[k] = bf16_rne_pair(v[2 * k], v[2 * k + 1]);
+      if constexpr (TREE) {
+        if ((i & 1u) && i + 1 < W.n) {
+          lds_st4(stack + lane * 16, u32x4{m[0], m[1], m[2], m[3]});
+          lds_st4(stack + 1024 + lane * 16, u32x4{m[4], m[5], m[6], m[7]});
+        }
+      } else if (i >= W.first_kept && i + 1 < W.n) {
+        uint8_t *dst = path.msg[i & 1u] + TileBase<16>(job, pos).code_off + lg * 32;
+        gst<u32x4>(dst, u32x4{m[0], m[1], m[2], m[3]});
+        gst<u32x4>(dst + 16, u32x4{m[4], m[5], m[6], m[7]});
+      }
+    }
+  }
+  if (W.encodes == W.n) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = 0.0f;
+    take(m);
+  }
+  store_result(job, P, v, A.xpose, pos);
+}
+
+template <typename LT, bool MU, bool TREE>
+__device__ __forceinline__ void walk_range(const WalkPath &path, const Params &P, const Vec &V, const Walk &W, const Areas A,
+                                           uint32_t lo, uint32_t hi) {
+  while (lo < hi) {
+    const TilePos p = locate(path.job, lo);
+    const uint32_t left = (p.n_seg - p.tile_first + kWaveSGs - 1) / kWaveSGs;
+    const uint32_t len = min(hi - lo, left);
+    if (p.wi == 0) walk_tiles<2, LT, MU, TREE>(path, P, V, W, A, p, len);
+    else if (p.wi == 1) walk_tiles<4, LT, MU, TREE>(path, P, V, W, A, p, len);
+    else if (p.wi == 2) walk_tiles<8, LT, MU, TREE>(path, P, V, W, A, p, len);
+    else {
+      TilePos q = p;
+      for (uint32_t i = 0; i < len; ++i, q.tile_first += kWaveSGs) walk_tile16<LT, TREE>(path, P, W, A, q);
+    }
+    lo += len;
+  }
+}
+
+// Wave w takes the tiles from S.shares[w] up to S.shares[w + 1] of the paths laid end to end (split_walk).
+template <typename LT, bool MU, bool TREE>
+__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_walk(const WalkPath *paths, const WalkShare *shares,
+                                                                                           Walk W, Params P) {
+  extern __shared__ uint4 lds_raw[];
+  uint32_t *lds = reinterpret_cast<uint32_t *>(lds_raw);
+  const uint32_t waves = blockDim.x / 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+  for (int r = 0; r < kRanges; ++r)  // tables of widths no chunk has are left out; ring and chain never decode from codes
+    if (P.range_width[r] > 2 || (W.widths >> P.range_width[r] & 1u))
+      for (uint32_t i = P.range_lo[r] + threadIdx.x * 4; i < P.range_hi[r]; i += blockDim.x * 4)
+        *reinterpret_cast<uint4 *>(&lds[i]) = gld16(&P.blob[i]);
+  __syncthreads();
+  const uint32_t v = __builtin_amdgcn_readfirstlane(blockIdx.x * waves + wave);
+  const WalkShare from = table_entry(shares, v), to = table_entry(shares, v + 1);
+  Areas A;
+  const uint32_t end = P.blob_dwords * 4;
+  A.park = end + wave * kParkBytes;
+  A.stack = end + waves * kParkBytes + wave * (TREE ? W.stack_bytes : kXposeBytes);
+  A.xpose = A.stack;  // the stack is empty when a tile's result is stored
+  const Vec V(P);
+  for (uint32_t p = from.path, lo = from.tile; p < to.path || (p == to.path && lo < to.tile); ++p, lo = 0) {
+    const WalkPath path = table_entry(paths, p);
+    uint32_t hi = to.tile;
+    if (p < to.path) {
+      hi = 0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) hi += (path.job.n_sg[w] + kWaveSGs - 1) / kWaveSGs;
+    }
+    walk_range<LT, MU, TREE>(path, P, V, W, A, lo, hi);
+  }
+}
+
+uint32_t walk_lds(const Params &P, bool tree, uint32_t stack_bytes, uint32_t waves) {
+  return P.blob_dwords * 4 + waves * (kParkBytes + (tree ? stack_bytes : kXposeBytes));
+}
+
+template <typename LT, bool MU, bool TREE>
+hipError_t go_walk(const WalkPath *paths, const WalkShare *shares, const Walk &W, const Params &P, hipStream_t s) {
+  hipLaunchKernelGGL((k_walk<LT, MU, TREE>), dim3(W.blocks), dim3(W.waves * 64), walk_lds(P, TREE, W.stack_bytes, W.waves), s, paths,
+                     shares, W, P);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// The grid, and where every wave's share begins: equal shares of the tiles' cost in path order.  A tile's cost by
+// width was chosen by measurement (2-bit tiles need no search; 8-bit ones collide more in LDS): with equal costs the
+// chunks of one width finish early, 1150 us instead of 880 for eight 25 MB buckets through 16 workers' recursive
+// halving.  With less than two tiles per wave the count decides: a wave with one tile more takes twice as long whatever its width.
+bool split_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W, std::vector<WalkShare> *shares) {
+  static const uint32_t kCosts[2][4] = {{1, 1, 1, 1}, {6, 11, 12, 6}};
+  const uint32_t *kCost = kCosts[1];
+  uint64_t tiles = 0, cost = 0;
+  W->widths = 0;
+  for (uint32_t p = 0; p < W->n_paths; ++p)
+    for (int w = 0; w < 4; ++w) {
+      const uint64_t t = (paths[p].job.n_sg[w] + kWaveSGs - 1) / kWaveSGs;
+      tiles += t;
+      cost += t * kCost[w];
+      if (t) W->widths |= 1u << w;
+    }
+  if (tiles == 0) return false;
+  // blocks of eight waves share a copy of the tables; where there are fewer tiles than two waves for every SIMD, blocks of four
+  // reach all CUs
+  W->waves = tiles < (uint64_t)n_cu * 8 ? 4 : kWalkWaves;
+  const uint32_t lds = walk_lds(P, tree, W->stack_bytes, W->waves);
+  uint32_t per_cu = 160u * 1024 / lds;
+  if (per_cu == 0) return false;
+  if (per_cu > 16 / W->waves) per_cu = 16 / W->waves;
+  const uint64_t needed = (tiles + W->waves - 1) / W->waves;
+  W->blocks = n_cu * per_cu;
+  if (W->blocks > needed) W->blocks = (uint32_t)needed;
+  const uint32_t n = W->blocks * W->waves;
+  if (tiles < 2ull * n) {
+    kCost = kCosts[0];
+    cost = tiles;
+  }
+  shares->resize((size_t)n + 1);
+  // first tile of share v: the first whose cost before it reaches v * cost / n
+  uint32_t p = 0, t = 0, w = 0, left = 0;  // tile t of path p is in width w's run, which has `left` tiles more
+  uint64_t before = 0;
+  auto settle = [&] {  // on to the next run that has tiles
+    while (left == 0 && p < W->n_paths) {
+      if (w == 4) { ++p; w = 0; t = 0; continue; }
+      left = (paths[p].job.n_sg[w] + kWaveSGs - 1) / kWaveSGs;
+      if (left == 0) ++w;
+    }
+  };
+  settle();
+  for (uint32_t v = 0; v < n; ++v) {
+    const uint64_t want = (uint64_t)(((unsigned __int128)cost * v) / n);
+    while (before < want && p < W->n_paths) {
+      const uint64_t take = (want - before + kCost[w] - 1) / kCost[w];
+      const uint32_t k = take < left ? (uint32_t)take : left;
+      before += (uint64_t)k * kCost[w];
+      t += k;
+      left -= k;
+      if (left == 0) { ++w; settle(); }
+    }
+    (*shares)[v] = WalkShare{p, p < W->n_paths ? t : 0u};
+  }
+  (*shares)[n] = WalkShare{W->n_paths, 0};
+  return true;
+}
+
+hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths, const WalkShare *shares, const Walk &W,
+                       const Params &P, hipStream_t s) {
+  const bool f32 = dtype == DQ_F32;
+#define DQ_WALK(T, M) (tree ? go_walk<T, M, true>(paths, shares, W, P, s) : go_walk<T, M, false>(paths, shares, W, P, s))
+  if (means) return f32 ? DQ_WALK(float, true) : DQ_WALK(uint16_t, true);
+  return f32 ? DQ_WALK(float, false) : DQ_WALK(uint16_t, false);
+#undef DQ_WALK
+}
+
+}  // namespace dq
