@@ -137,6 +137,19 @@ hipError_t mx_launch_one(Kind kind, dq_codec fmt, dq_dtype dtype, bool has_local
 hipError_t mx_launch_batch(Kind kind, dq_codec fmt, dq_dtype dtype, bool has_local, const MxJob *jobs_dev,
                            uint32_t n_jobs, uint64_t max_entries_per_job, uint32_t n_cu, hipStream_t stream);
 
+// A whole replay of an MX codec in one launch: all chunks have the same size, so a path (bucket, chunk) is found by arithmetic.
+struct MxWalk {
+  const void *const *grads;  // device: the workers' tensors
+  float *out;
+  uint8_t *msg[2];           // ring, chain: messages of even and odd steps, one every msg_stride bytes
+  size_t msg_stride;
+  uint64_t chunk_blocks;     // blocks of 32 entries per chunk
+  uint32_t n_chunks, n_tiles, tiles_per_path;  // a tile: 64 blocks of one chunk
+  uint32_t n, log_n, encodes, first_kept, chain;  // as in Walk
+  uint32_t wave_bytes;       // set by the launcher: LDS per wave
+};
+hipError_t launch_mx_walk(dq_codec fmt, dq_dtype dtype, bool tree, const MxWalk &W, uint32_t n_cu, hipStream_t stream);
+
 }  // namespace dq
 
 // context internals shared between dq_api.cpp and dq_replay.cpp

@@ -59,7 +59,7 @@ __device__ __forceinline__ Fetch<B, KIND, LT> fetch(const Job &job, const TilePo
   return f;
 }
 
-// A tile's encoded output, kept in registers until the next tile's loads are about to be requested.
+// A tile's encoded output.
 template <int B>
 struct Encoded {
   uint32_t ow[Width<B>::words], rg, sfb;
@@ -234,26 +234,19 @@ __device__ __forceinline__ void run_tiles(const Job &job, const Params &P, const
                                           uint32_t len) {
   // The next tile of the run is requested from inside the current one (see compute's `ahead`): with five waves
   // per SIMD a wave's own wait for its tile is no longer covered by the others (measured: 3-7 % on the 25 MB
-  // and the 100-bucket configurations, nothing on the largest launches).  A tile's stores are issued there too, one
-  // tile late and before those loads: loads and stores of a wave count down in order, so stores issued after
-  // the loads would have to be acknowledged before the next tile's data may be touched.
+  // and the 100-bucket configurations, nothing on the largest launches).
   Fetch<B, KIND, LT> f = fetch<B, KIND, LT, MU>(job, pos);
-  Encoded<B> e;
-  TilePos pos_prev = pos;
   for (uint32_t i = 0; i < len; ++i) {
     Fetch<B, KIND, LT> next = f;
     TilePos pos_next = pos;
     pos_next.tile_first += kWaveSGs;
-    const Encoded<B> mine = compute<B, KIND, LT, MU>(job, P, V, stage + i * 128, pos, f, [&] {
-      if (i > 0) put<B>(job, pos_prev, e);
+    const Encoded<B> e = compute<B, KIND, LT, MU>(job, P, V, stage + i * 128, pos, f, [&] {
       if (i + 1 < len) next = fetch<B, KIND, LT, MU>(job, pos_next);
     });
-    e = mine;
+    put<B>(job, pos, e);
     f = next;
-    pos_prev = pos;
     pos = pos_next;
   }
-  put<B>(job, pos_prev, e);
 }
 
 // Per-SG draws of `nb` <= 8 consecutive tiles starting at tile `t_first`, made by one wave-wide
@@ -355,11 +348,6 @@ __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
   const uint32_t b_lo = bw * q + min(bw, r);
   const uint32_t b_hi = (bw + kBlockWaves) * q + min(bw + kBlockWaves, r);
   if (b_lo >= b_hi) return;
-  // With many tiles per wave every wave takes its share of EACH width's run: the widths' tiles differ in cost (a 2-bit
-  // tile takes two thirds of a 4- or 8-bit one), and with one contiguous range per wave the waves of the cheap
-  // run were done early (waves resident on average: 4.1 of 5; 125 M entries, 5 bits: 97 -> 89 us).  Below
-  // that the extra runs cost more than the balance gives.
-  const bool spread = q >= 8;
   constexpr uint32_t lds0 = kLds0;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t wv = bw + wave;
@@ -374,8 +362,7 @@ __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
 
   // copy the common tables and the table ranges of the widths this block meets; the first
   // 16 bytes per thread of every range are requested together (one round trip, not six)
-  const bool meets[4] = {spread ? t0 > 0 : b_lo < t0, spread ? t1 > 0 : b_lo < t0 + t1 && b_hi > t0,
-                         spread ? t2 > 0 : b_lo < t0 + t1 + t2 && b_hi > t0 + t1, true};
+  const bool meets[4] = {b_lo < t0, b_lo < t0 + t1 && b_hi > t0, b_lo < t0 + t1 + t2 && b_hi > t0 + t1, true};
   constexpr int kEarly = kRanges;
   uint4 first[kEarly];
   bool need[kRanges], has[kEarly];
@@ -405,31 +392,16 @@ __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
   [[maybe_unused]] const uint32_t area = park0 + wave * 1024;     // compress, DAR: this wave's parked draws
   [[maybe_unused]] const uint32_t xpose = park0 + wave * (64 * 64);  // decompress: its transpose area, 64 lanes x 64 bytes
   const Vec V(P);
-  auto range = [&](uint32_t lo, uint32_t hi) {
-    if constexpr (KIND == kDecompress) {
-      da_range<LT>(job, P, xpose, lo, hi);
-    } else {
-      for (uint32_t tb = lo; tb < hi; tb += kBatch) {
-        const uint32_t nb = min((uint32_t)kBatch, hi - tb);
-        if (!block_draws) park_draws(job, P, tb, nb, area);
-        __builtin_amdgcn_wave_barrier();
-        run_range<KIND, LT>(job, P, V, block_draws ? park0 + (tb - b_lo) * 128 : area, tb, nb);
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-  };
-  if (spread) {
-    const uint32_t runs[4] = {t0, t1, t2, t3};
-    uint32_t first = 0;
-#pragma unroll 1
-    for (int w = 0; w < 4; ++w) {
-      const uint32_t n = runs[w], qw = n / n_waves, rw = n - qw * n_waves;
-      const uint32_t v = w & 1 ? n_waves - 1 - wv : wv;  // the tiles left over go to the low waves, then to the high ones
-      range(first + v * qw + min(v, rw), first + (v + 1) * qw + min(v + 1, rw));
-      first += n;
-    }
+  if constexpr (KIND == kDecompress) {
+    da_range<LT>(job, P, xpose, w_lo, w_hi);
   } else {
-    range(w_lo, w_hi);
+    for (uint32_t tb = w_lo; tb < w_hi; tb += kBatch) {
+      const uint32_t nb = min((uint32_t)kBatch, w_hi - tb);
+      if (!block_draws) park_draws(job, P, tb, nb, area);
+      __builtin_amdgcn_wave_barrier();
+      run_range<KIND, LT>(job, P, V, block_draws ? park0 + (tb - b_lo) * 128 : area, tb, nb);
+      __builtin_amdgcn_wave_barrier();
+    }
   }
 }
 
@@ -504,7 +476,13 @@ uint32_t job_tiles(const Job &j) {
 // Grid shape: `grid_blocks` (what the GPU holds at once: CUs x blocks per CU, fixed when the
 // context is made) shared between the jobs of the launch (one block holds 4 waves; a wave
 // then walks its share of the job's tiles).
-uint32_t blocks_per_job(uint32_t max_tiles, uint32_t n_jobs, uint32_t grid_blocks) {
+// Compress and DAR launches with many tiles per wave take twice the grid: the second half's blocks start wherever a
+// first one ends, which evens out what the even split by tile count leaves uneven (2-bit tiles are cheaper).  A 125 M entry hop at
+// 5 bits: 100.5 -> 97 us; three and four times the grid gain no more, and below 12 tiles per wave the second copy
+// of the tables costs more than it gives.  Decompress launches are bound by memory alone: no gain.
+template <Kind KIND>
+uint32_t blocks_per_job(uint32_t max_tiles, uint64_t total_tiles, uint32_t n_jobs, uint32_t grid_blocks) {
+  if (KIND != kDecompress && total_tiles >= 12ull * kBlockWaves * grid_blocks) grid_blocks *= 2;
   uint32_t blocks = (grid_blocks + n_jobs - 1) / n_jobs;
   const uint32_t needed = (max_tiles + kBlockWaves - 1) / kBlockWaves;
   if (blocks > needed) blocks = needed;
@@ -520,7 +498,7 @@ template <Kind KIND, typename LT>
 hipError_t go_one(const Job &job, Params p, uint32_t grid_blocks, hipStream_t s) {
   const uint32_t tiles = job_tiles(job);
   if (tiles == 0) return hipSuccess;
-  const uint32_t blocks = blocks_per_job(tiles, 1, grid_blocks);
+  const uint32_t blocks = blocks_per_job<KIND>(tiles, tiles, 1, grid_blocks);
   hipLaunchKernelGGL((k_one<KIND, LT>), dim3(blocks), dim3(kBlockThreads), lds_bytes(p, KIND), s, job, p);
   return hipGetLastError();
 }
@@ -528,13 +506,12 @@ template <Kind KIND, typename LT>
 hipError_t go_batch(const Job *jobs, uint32_t n_jobs, uint32_t max_tiles, uint64_t total_tiles, Params p,
                     uint32_t grid_blocks, hipStream_t s) {
   if (n_jobs == 0 || max_tiles == 0) return hipSuccess;
-  (void)total_tiles;
   if (max_tiles <= (uint32_t)kBatch && n_jobs >= grid_blocks) {  // so many small jobs that a block per job would queue up
     hipLaunchKernelGGL((k_batch_small<KIND, LT>), dim3((n_jobs + kBlockWaves - 1) / kBlockWaves), dim3(kBlockThreads),
                        lds_bytes(p, KIND), s, jobs, n_jobs, p);
     return hipGetLastError();
   }
-  const uint32_t blocks = blocks_per_job(max_tiles, n_jobs, grid_blocks);
+  const uint32_t blocks = blocks_per_job<KIND>(max_tiles, total_tiles, n_jobs, grid_blocks);
   // the grid's y dimension (one row per job) holds at most 65,535 rows: more jobs take more launches
   for (uint32_t first = 0; first < n_jobs; first += kMaxGridRows) {
     const uint32_t rows = n_jobs - first < kMaxGridRows ? n_jobs - first : kMaxGridRows;

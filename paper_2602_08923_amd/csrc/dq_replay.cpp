@@ -58,6 +58,7 @@ struct Plan {
   // the whole schedule as one launch (dq_walk.hip): one path per (bucket, chunk), the workers' tensors
   bool walk = false, tree = false;
   dq::Walk w = {};
+  dq::MxWalk mx = {};
   std::vector<dq::WalkPath> paths;  // freed once they are on the device
   std::vector<dq::WalkShare> shares;
   size_t paths_off = 0, shares_off = 0, grads_off = 0;
@@ -142,6 +143,33 @@ void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, 
   *off = align_up(*off, 256);
   plan->shares_off = *off;
   *off += plan->shares.size() * sizeof(dq::WalkShare);
+  *off = align_up(*off, 256);
+  plan->grads_off = *off;
+  *off += (size_t)n * sizeof(void *);
+}
+
+void plan_mx_walk(const dq_ctx *ctx, const dq_replay_desc *d, uint32_t n_chunks, uint64_t m, float *out, Plan *plan, size_t *off) {
+  const uint32_t n = ctx->cfg.n_workers;
+  dq::MxWalk &w = plan->mx;
+  w.n = n;
+  while ((1u << w.log_n) < n) ++w.log_n;
+  w.encodes = d->all_gather ? n : n - 1;
+  w.first_kept = n > 3 ? n - 3 : 0;
+  w.chain = d->topology == DQ_CHAIN;
+  plan->tree = d->topology == DQ_BUTTERFLY;
+  w.out = out;
+  w.chunk_blocks = m * 8;
+  w.n_chunks = n_chunks;
+  const uint64_t per_path = (w.chunk_blocks + 63) / 64, tiles = per_path * d->n_buckets * n_chunks;
+  if (tiles >= (1ull << 31)) return;  // tile numbers are 32-bit: step by step
+  w.tiles_per_path = (uint32_t)per_path;
+  w.n_tiles = (uint32_t)tiles;
+  if (plan->ring_chunks) {
+    w.msg[0] = plan->ring_msg[0];
+    w.msg[1] = plan->ring_msg[1];
+    w.msg_stride = align_up(plan->ring_bytes[0], 256);  // equal chunks: slot i starts at i * msg_stride
+  }
+  plan->walk = true;
   *off = align_up(*off, 256);
   plan->grads_off = *off;
   *off += (size_t)n * sizeof(void *);
@@ -384,7 +412,8 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
     plan->steps.push_back(std::move(sd));
   }
 
-  if (!mx) plan_walk(ctx, d, ci.data(), n_chunks, m, out, plan, &off);
+  if (mx) plan_mx_walk(ctx, d, n_chunks, m, out, plan, &off);
+  else plan_walk(ctx, d, ci.data(), n_chunks, m, out, plan, &off);
 
   // job tables
   for (Step &st : plan->steps)
@@ -453,16 +482,17 @@ dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *
   const bool mx = desc->codec != DQ_DYNAMIQ;
   if (r->plan.walk) {
     Plan &p = r->plan;
-    hipError_t e = hipMemcpy(r->scratch + p.paths_off, p.paths.data(), p.paths.size() * sizeof(dq::WalkPath), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
+    const size_t n_workers = ctx->cfg.n_workers;
+    hipError_t e = hipMemcpy(r->scratch + p.grads_off, worker_grads, n_workers * sizeof(void *), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !mx)
+      e = hipMemcpy(r->scratch + p.paths_off, p.paths.data(), p.paths.size() * sizeof(dq::WalkPath), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !mx)
       e = hipMemcpy(r->scratch + p.shares_off, p.shares.data(), p.shares.size() * sizeof(dq::WalkShare), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-      e = hipMemcpy(r->scratch + p.grads_off, worker_grads, (size_t)p.w.n * sizeof(void *), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
       delete r;
       return dq::hip_status(e);
     }
-    p.w.grads = reinterpret_cast<const void *const *>(r->scratch + p.grads_off);
+    p.w.grads = p.mx.grads = reinterpret_cast<const void *const *>(r->scratch + p.grads_off);
     std::vector<dq::WalkPath>().swap(p.paths);
     std::vector<dq::WalkShare>().swap(p.shares);
   }
@@ -541,6 +571,7 @@ static dq_status run_step(dq_replay *plan, size_t i, hipStream_t s, int only = -
 // The whole schedule in one launch.
 static dq_status run_walk(dq_replay *r, hipStream_t s) {
   const Plan &p = r->plan;
+  if (r->codec != DQ_DYNAMIQ) return dq::hip_status(dq::launch_mx_walk(r->codec, r->dtype, p.tree, p.mx, r->ctx->n_cu, s));
   return dq::hip_status(dq::launch_walk(r->dtype, p.tree, r->means, reinterpret_cast<const dq::WalkPath *>(r->scratch + p.paths_off),
                                         reinterpret_cast<const dq::WalkShare *>(r->scratch + p.shares_off), p.w, r->ctx->params, s));
 }

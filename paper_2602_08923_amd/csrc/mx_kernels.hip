@@ -85,127 +85,152 @@ typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x32 __attribute__((ext_vector_type(32)));
 
+// A block's code words and scale byte.
+template <int FMT>
+struct MxMsg {
+  uint32_t w[Fmt<FMT>::cb], e;
+};
+template <int FMT>
+__device__ __forceinline__ MxMsg<FMT> mx_load(const uint8_t *packed, uint64_t n_blocks, uint64_t bl) {
+  constexpr int cw = Fmt<FMT>::cb;
+  MxMsg<FMT> m;
+  const uint8_t *src = packed + (size_t)bl * (cw * 4);
+  if constexpr (cw == 8) {
+    const u32x4 a = gld<u32x4>(src), b = gld<u32x4>(src + 16);
+    m.w[0] = a.x; m.w[1] = a.y; m.w[2] = a.z; m.w[3] = a.w; m.w[4] = b.x; m.w[5] = b.y; m.w[6] = b.z; m.w[7] = b.w;
+  } else if constexpr (cw == 6) {
+    const u32x2 a = gld<u32x2>(src), b = gld<u32x2>(src + 8), c = gld<u32x2>(src + 16);
+    m.w[0] = a.x; m.w[1] = a.y; m.w[2] = b.x; m.w[3] = b.y; m.w[4] = c.x; m.w[5] = c.y;
+  } else {
+    const u32x4 a = gld<u32x4>(src);
+    m.w[0] = a.x; m.w[1] = a.y; m.w[2] = a.z; m.w[3] = a.w;
+  }
+  m.e = gld<uint8_t>(packed + (size_t)n_blocks * (cw * 4) + bl);
+  return m;
+}
+template <int FMT>
+__device__ __forceinline__ void mx_store(uint8_t *packed, uint64_t n_blocks, uint64_t bl, const MxMsg<FMT> &m) {
+  constexpr int cw = Fmt<FMT>::cb;
+  uint8_t *dst = packed + (size_t)bl * (cw * 4);
+  if constexpr (cw == 8) {
+    gst<u32x4>(dst, u32x4{m.w[0], m.w[1], m.w[2], m.w[3]});
+    gst<u32x4>(dst + 16, u32x4{m.w[4], m.w[5], m.w[6], m.w[7]});
+  } else if constexpr (cw == 6) {
+    gst<u32x2>(dst, u32x2{m.w[0], m.w[1]});
+    gst<u32x2>(dst + 8, u32x2{m.w[2], m.w[3]});
+    gst<u32x2>(dst + 16, u32x2{m.w[4], m.w[5]});
+  } else {
+    gst<u32x4>(dst, u32x4{m.w[0], m.w[1], m.w[2], m.w[3]});
+  }
+  gst<uint8_t>(packed + (size_t)n_blocks * (cw * 4) + bl, (uint8_t)m.e);
+}
+// v = decoded block (ADD: + v)
+template <int FMT, bool ADD>
+__device__ __forceinline__ void mx_decode(const MxMsg<FMT> &m, float (&v)[32]) {
+  constexpr int cw = Fmt<FMT>::cb;
+  const float X = u2f(m.e << 23);  // the instruction reads the exponent field as the E8M0 scale
+  float d[32];
+  if constexpr (cw == 8) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const f32x2 lo = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(m.w[i], X, false);
+      const f32x2 hi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(m.w[i], X, true);
+      d[4 * i] = lo.x; d[4 * i + 1] = lo.y; d[4 * i + 2] = hi.x; d[4 * i + 3] = hi.y;
+    }
+  } else if constexpr (cw == 4) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const f32x2 b0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(m.w[i], X, 0);
+      const f32x2 b1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(m.w[i], X, 1);
+      const f32x2 b2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(m.w[i], X, 2);
+      const f32x2 b3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(m.w[i], X, 3);
+      d[8 * i] = b0.x; d[8 * i + 1] = b0.y; d[8 * i + 2] = b1.x; d[8 * i + 3] = b1.y;
+      d[8 * i + 4] = b2.x; d[8 * i + 5] = b2.y; d[8 * i + 6] = b3.x; d[8 * i + 7] = b3.y;
+    }
+  } else {
+    const f32x32 all = __builtin_amdgcn_cvt_scalef32_pk32_f32_bf6(u32x6{m.w[0], m.w[1], m.w[2], m.w[3], m.w[4], m.w[5]}, X);
+#pragma unroll
+    for (int k = 0; k < 32; ++k) d[k] = all[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 32; ++k) v[k] = ADD ? d[k] + v[k] : d[k];
+}
+template <int FMT>
+__device__ __forceinline__ MxMsg<FMT> mx_encode(float (&v)[32]) {
+  using F = Fmt<FMT>;
+  constexpr int cw = F::cb;
+  MxMsg<FMT> out;
+  float m = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 32; ++k) m = fmaxf(m, fabsf(v[k]));
+  int e = (int)(f2u(m) >> 23) - F::emax;
+  e = e < 0 ? 0 : (e > 254 ? 254 : e);
+  const float X = u2f((uint32_t)e << 23);
+  if constexpr (cw == 8) {
+    // the E4M3 conversion turns overflow into NaN; MX saturates: clamp to the largest normal first
+    const float top = 448.0f * X;
+#pragma unroll
+    for (int k = 0; k < 32; ++k) v[k] = __builtin_amdgcn_fmed3f(v[k], -top, top);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      s16x2 r = {0, 0};
+      r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, v[4 * i], v[4 * i + 1], X, false);
+      r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, v[4 * i + 2], v[4 * i + 3], X, true);
+      out.w[i] = __builtin_bit_cast(uint32_t, r);
+    }
+  } else if constexpr (cw == 4) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t r = 0;
+      r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * i], v[8 * i + 1], X, 0);
+      r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * i + 2], v[8 * i + 3], X, 1);
+      r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * i + 4], v[8 * i + 5], X, 2);
+      r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * i + 6], v[8 * i + 7], X, 3);
+      out.w[i] = r;
+    }
+  } else {
+    f32x16 a, b;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) { a[k] = v[2 * k]; b[k] = v[2 * k + 1]; }  // the two inputs interleave
+    const u32x6 r = __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(a, b, X);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) out.w[i] = r[i];
+  }
+  out.e = (uint32_t)e;
+  return out;
+}
+// The wave's 64 blocks, 8 KB of consecutive output from `out` on (n_valid of them exist).  Lane l parks its 8 float4
+// in the wave's LDS area (slot index xor-ed with l % 8 against bank conflicts); round r then stores float4
+// number 64 r + l of the tile, 1 KB of consecutive memory per instruction.
+__device__ __forceinline__ void mx_store_f32(float *out, uint64_t n_valid, const float (&v)[32], uint32_t xpose) {
+  const uint32_t lane = threadIdx.x & 63u;
+#pragma unroll
+  for (uint32_t c = 0; c < 8; ++c)
+    lds_put(xpose + lane * 128 + ((c ^ (lane & 7u)) * 16), f32x4{v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]});
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  float4 *o = reinterpret_cast<float4 *>(out);
+#pragma unroll
+  for (uint32_t r = 0; r < 8; ++r) {
+    const uint32_t L = r * 64 + lane, w = L >> 3, c = L & 7u;
+    if (w < n_valid) gst<f32x4>(o + L, lds_get(xpose + w * 128 + ((c ^ (w & 7u)) * 16)));
+  }
+  __builtin_amdgcn_wave_barrier();  // the area is reused by the wave's next tile
+}
+
 template <int FMT, Kind KIND, typename LT>
 __device__ __forceinline__ void mx_block(const MxJob &job, uint64_t bi, uint64_t n_blocks, bool active, uint32_t xpose) {
-  using F = Fmt<FMT>;
   constexpr bool kHasLocal = !__is_same(LT, NoLocal);
-  constexpr int cw = F::cb;
-  const size_t scale_off = (size_t)n_blocks * (cw * 4);
   const uint64_t bl = active ? bi : n_blocks - 1;  // block whose inputs this lane reads
   float v[32];
   if constexpr (kHasLocal) load_local32<LT>(job.local, (size_t)bl * 32, v);
-  if constexpr (KIND != kCompress) {
-    uint32_t w[cw];
-    const uint8_t *src = job.in + (size_t)bl * (cw * 4);
-    if constexpr (cw == 8) {
-      const u32x4 a = gld<u32x4>(src), b = gld<u32x4>(src + 16);
-      w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w; w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
-    } else if constexpr (cw == 6) {
-      const u32x2 a = gld<u32x2>(src), b = gld<u32x2>(src + 8), c = gld<u32x2>(src + 16);
-      w[0] = a.x; w[1] = a.y; w[2] = b.x; w[3] = b.y; w[4] = c.x; w[5] = c.y;
-    } else {
-      const u32x4 a = gld<u32x4>(src);
-      w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
-    }
-    const uint32_t e = gld<uint8_t>(job.in + scale_off + bl);
-    const float X = u2f(e << 23);  // the instruction reads the exponent field as the E8M0 scale
-    float d[32];
-    if constexpr (cw == 8) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const f32x2 lo = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[i], X, false);
-        const f32x2 hi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[i], X, true);
-        d[4 * i] = lo.x; d[4 * i + 1] = lo.y; d[4 * i + 2] = hi.x; d[4 * i + 3] = hi.y;
-      }
-    } else if constexpr (cw == 4) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const f32x2 b0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], X, 0);
-        const f32x2 b1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], X, 1);
-        const f32x2 b2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], X, 2);
-        const f32x2 b3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], X, 3);
-        d[8 * i] = b0.x; d[8 * i + 1] = b0.y; d[8 * i + 2] = b1.x; d[8 * i + 3] = b1.y;
-        d[8 * i + 4] = b2.x; d[8 * i + 5] = b2.y; d[8 * i + 6] = b3.x; d[8 * i + 7] = b3.y;
-      }
-    } else {
-      const f32x32 all = __builtin_amdgcn_cvt_scalef32_pk32_f32_bf6(u32x6{w[0], w[1], w[2], w[3], w[4], w[5]}, X);
-#pragma unroll
-      for (int k = 0; k < 32; ++k) d[k] = all[k];
-    }
-#pragma unroll
-    for (int k = 0; k < 32; ++k) v[k] = kHasLocal ? d[k] + v[k] : d[k];
-  }
+  if constexpr (KIND != kCompress) mx_decode<FMT, kHasLocal>(mx_load<FMT>(job.in, n_blocks, bl), v);
   if constexpr (KIND == kDecompress) {
-    // The wave's 64 blocks are 8 KB of consecutive output.  Lane l parks its 8 float4 in the
-    // wave's LDS area (slot index xor-ed with l % 8 against bank conflicts); round r then
-    // stores float4 number 64 r + l of the tile, 1 KB of consecutive memory per instruction.
-    const uint32_t lane = threadIdx.x & 63u;
-    if (active) {
-#pragma unroll
-      for (uint32_t c = 0; c < 8; ++c)
-        lds_put(xpose + lane * 128 + ((c ^ (lane & 7u)) * 16), f32x4{v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]});
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const uint64_t tile_first = bi - lane;  // first block of the wave's tile
-    float4 *o = reinterpret_cast<float4 *>(static_cast<float *>(job.out) + (size_t)tile_first * 32);
-#pragma unroll
-    for (uint32_t r = 0; r < 8; ++r) {
-      const uint32_t L = r * 64 + lane, w = L >> 3, c = L & 7u;
-      if (tile_first + w < n_blocks) gst<f32x4>(o + L, lds_get(xpose + w * 128 + ((c ^ (w & 7u)) * 16)));
-    }
-    __builtin_amdgcn_wave_barrier();  // the area is reused by the wave's next tile
+    const uint64_t first = bi - (threadIdx.x & 63u);  // first block of the wave's tile
+    mx_store_f32(static_cast<float *>(job.out) + (size_t)first * 32, n_blocks - first, v, xpose);
   } else {
-    float m = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) m = fmaxf(m, fabsf(v[k]));
-    int e = (int)(f2u(m) >> 23) - F::emax;
-    e = e < 0 ? 0 : (e > 254 ? 254 : e);
-    const float X = u2f((uint32_t)e << 23);
-    uint32_t ow[cw];
-    if constexpr (cw == 8) {
-      // the E4M3 conversion turns overflow into NaN; MX saturates: clamp to the largest normal first
-      const float top = 448.0f * X;
-#pragma unroll
-      for (int k = 0; k < 32; ++k) v[k] = __builtin_amdgcn_fmed3f(v[k], -top, top);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        s16x2 r = {0, 0};
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, v[4 * i], v[4 * i + 1], X, false);
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, v[4 * i + 2], v[4 * i + 3], X, true);
-        ow[i] = __builtin_bit_cast(uint32_t, r);
-      }
-    } else if constexpr (cw == 4) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        uint32_t r = 0;
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * i], v[8 * i + 1], X, 0);
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * i + 2], v[8 * i + 3], X, 1);
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * i + 4], v[8 * i + 5], X, 2);
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * i + 6], v[8 * i + 7], X, 3);
-        ow[i] = r;
-      }
-    } else {
-      f32x16 a, b;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) { a[k] = v[2 * k]; b[k] = v[2 * k + 1]; }  // the two inputs interleave
-      const u32x6 r = __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(a, b, X);
-#pragma unroll
-      for (int i = 0; i < 6; ++i) ow[i] = r[i];
-    }
-    uint8_t *dst = static_cast<uint8_t *>(job.out) + (size_t)bi * (cw * 4);
-    if constexpr (cw == 8) {
-      gst<u32x4>(dst, u32x4{ow[0], ow[1], ow[2], ow[3]});
-      gst<u32x4>(dst + 16, u32x4{ow[4], ow[5], ow[6], ow[7]});
-    } else if constexpr (cw == 6) {
-      gst<u32x2>(dst, u32x2{ow[0], ow[1]});
-      gst<u32x2>(dst + 8, u32x2{ow[2], ow[3]});
-      gst<u32x2>(dst + 16, u32x2{ow[4], ow[5]});
-    } else {
-      gst<u32x4>(dst, u32x4{ow[0], ow[1], ow[2], ow[3]});
-    }
-    gst<uint8_t>(static_cast<uint8_t *>(job.out) + scale_off + bi, (uint8_t)e);
+    mx_store<FMT>(static_cast<uint8_t *>(job.out), n_blocks, bi, mx_encode<FMT>(v));
   }
 }
 
@@ -237,6 +262,150 @@ template <int FMT, Kind KIND, typename LT>
 __global__ __launch_bounds__(kBlockThreads) void mx_batch(const MxJob *jobs) {
   const MxJob job = jobs[blockIdx.y];
   mx_run<FMT, KIND, LT>(job);
+}
+
+// A whole replay in one launch, as in dq_walk.hip: a wave carries 64 blocks of a chunk through all hops of the schedule,
+// the pending message in registers (a recursive halving's higher levels in LDS).  A replay of a ring of 8 over 25 MB: 57 us, 4.6 TB/s,
+// the rate of a large copy on this card; 94 us in eight launches, bound by the messages' way to memory and back and
+// by the launches' fixed parts.  Three waves per SIMD without spills beat four with (57 and 59 us); grids of 3 to 7 blocks
+// per CU are within 3 %.
+constexpr uint32_t kMxStackLevel = 36 * 64;  // eight code words and the scale per lane
+constexpr uint32_t kMxXpose = 8192;
+
+template <bool TREE>
+__device__ __forceinline__ uint32_t mx_leaf(const MxWalk &W, uint32_t chunk, uint32_t i) {
+  if constexpr (TREE) {
+    return chunk ^ (__brev(~i) >> (32u - W.log_n));
+  } else {
+    const uint32_t x = (W.chain ? 0u : chunk) + i;
+    return min(x, x - W.n);
+  }
+}
+template <typename LT>
+struct MxSlice {
+  u32x4 w[sizeof(LT) == 4 ? 8 : 4];
+};
+template <typename LT>
+__device__ __forceinline__ MxSlice<LT> mx_slice(const MxWalk &W, uint32_t leaf, uint64_t at) {
+  typedef __attribute__((address_space(4))) const uint64_t constant_u64;  // a scalar load: nothing here writes the table
+  const uint8_t *p = reinterpret_cast<const uint8_t *>(((constant_u64 *)(uintptr_t)W.grads)[leaf]) + at;
+  MxSlice<LT> s;
+#pragma unroll
+  for (int i = 0; i < (sizeof(LT) == 4 ? 8 : 4); ++i) s.w[i] = gld<u32x4>(p + 16 * i);
+  return s;
+}
+template <typename LT>
+__device__ __forceinline__ void mx_widen(const MxSlice<LT> &s, float (&v)[32]) {
+  if constexpr (sizeof(LT) == 4) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      v[4 * i] = u2f(s.w[i].x); v[4 * i + 1] = u2f(s.w[i].y); v[4 * i + 2] = u2f(s.w[i].z); v[4 * i + 3] = u2f(s.w[i].w);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t w[4] = {s.w[i].x, s.w[i].y, s.w[i].z, s.w[i].w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        v[8 * i + 2 * j] = u2f(w[j] << 16);
+        v[8 * i + 2 * j + 1] = u2f(w[j] & 0xFFFF0000u);
+      }
+    }
+  }
+}
+
+template <int FMT, typename LT, bool TREE>
+__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3))) void mx_walk(MxWalk W) {
+  extern __shared__ float4 mx_lds[];
+  constexpr int cw = Fmt<FMT>::cb;
+  const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t area = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float4 *)mx_lds + wave * W.wave_bytes;
+  const uint32_t n_waves = gridDim.x * kBlockWaves, last = W.n - 1;
+  typedef __attribute__((address_space(3))) uint32_t lds_u32;
+  // tile t: blocks [64 k, 64 k + 64) of path p's chunk
+  struct Tile {
+    uint32_t path, chunk;
+    uint64_t first;  // the wave's first block inside the chunk
+    uint64_t at;     // this lane's block inside every worker's tensor, in bytes
+  };
+  auto tile = [&](uint32_t t) {
+    Tile x;
+    x.path = t / W.tiles_per_path;
+    x.chunk = x.path % W.n_chunks;
+    x.first = (uint64_t)(t - x.path * W.tiles_per_path) * 64;
+    const uint64_t bl = min(x.first + lane, W.chunk_blocks - 1);  // lanes past the end redo the last block
+    x.at = ((uint64_t)x.path * W.chunk_blocks + bl) * (32 * sizeof(LT));
+    return x;
+  };
+  uint32_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * kBlockWaves + wave);
+  if (t >= W.n_tiles) return;
+  Tile x = tile(t);
+  MxSlice<LT> s = mx_slice<LT>(W, mx_leaf<TREE>(W, x.chunk, 0u), x.at);
+  for (;;) {
+    const bool more = W.n_tiles - t > n_waves;
+    const Tile next = more ? tile(t + n_waves) : x;
+    const uint64_t bl = min(x.first + lane, W.chunk_blocks - 1);
+    float v[32];
+    MxMsg<FMT> m;
+#pragma unroll 1
+    for (uint32_t i = 0;; ++i) {
+      mx_widen<LT>(s, v);
+      if (i < last) s = mx_slice<LT>(W, mx_leaf<TREE>(W, x.chunk, i + 1), x.at);
+      else if (more) s = mx_slice<LT>(W, mx_leaf<TREE>(W, next.chunk, 0u), next.at);
+      if (TREE ? (i & 1u) : i > 0) mx_decode<FMT, true>(m, v);
+      uint32_t stack = area;
+      if constexpr (TREE) {
+        if (i & 1u) {
+#pragma unroll 1
+          for (uint32_t q = i >> 1; q & 1u; q >>= 1, stack += kMxStackLevel) {
+            MxMsg<FMT> p;
+#pragma unroll
+            for (int k = 0; k < cw; ++k) p.w[k] = *reinterpret_cast<lds_u32 *>(stack + k * 256 + lane * 4);
+            p.e = *reinterpret_cast<lds_u32 *>(stack + 2048 + lane * 4);
+            mx_decode<FMT, true>(p, v);
+          }
+        }
+      }
+      if (i == W.encodes) break;
+      m = mx_encode<FMT>(v);
+      if (i == last) {  // all-gather: what every worker decodes from the sink's message
+        mx_decode<FMT, false>(m, v);
+        break;
+      }
+      if constexpr (TREE) {
+        if (i & 1u) {
+#pragma unroll
+          for (int k = 0; k < cw; ++k) *reinterpret_cast<lds_u32 *>(stack + k * 256 + lane * 4) = m.w[k];
+          *reinterpret_cast<lds_u32 *>(stack + 2048 + lane * 4) = m.e;
+        }
+      } else if (i >= W.first_kept) {
+        mx_store<FMT>(W.msg[i & 1u] + (size_t)x.path * W.msg_stride, W.chunk_blocks, bl, m);
+      }
+    }
+    mx_store_f32(W.out + ((uint64_t)x.path * W.chunk_blocks + x.first) * 32, W.chunk_blocks - x.first, v, area);
+    if (!more) break;
+    t += n_waves;
+    x = next;
+  }
+}
+
+template <int FMT, typename LT, bool TREE>
+hipError_t go_mx_walk(MxWalk W, uint32_t n_cu, hipStream_t s) {
+  const uint32_t levels = TREE && W.log_n > 1 ? W.log_n - 1 : 0;
+  W.wave_bytes = levels * kMxStackLevel > kMxXpose ? levels * kMxStackLevel : kMxXpose;
+  const uint32_t lds = W.wave_bytes * kBlockWaves;
+  uint32_t per_cu = 160u * 1024 / lds;
+  if (per_cu > 4) per_cu = 4;
+  if (per_cu < 1) per_cu = 1;
+  uint32_t blocks = (W.n_tiles + kBlockWaves - 1) / kBlockWaves;
+  if (blocks > n_cu * per_cu) blocks = n_cu * per_cu;
+  hipLaunchKernelGGL((mx_walk<FMT, LT, TREE>), dim3(blocks), dim3(kBlockThreads), lds, s, W);
+  return hipGetLastError();
+}
+template <int FMT>
+hipError_t mx_walk_fmt(dq_dtype dtype, bool tree, const MxWalk &W, uint32_t n_cu, hipStream_t s) {
+  if (dtype == DQ_F32) return tree ? go_mx_walk<FMT, float, true>(W, n_cu, s) : go_mx_walk<FMT, float, false>(W, n_cu, s);
+  return tree ? go_mx_walk<FMT, uint16_t, true>(W, n_cu, s) : go_mx_walk<FMT, uint16_t, false>(W, n_cu, s);
 }
 
 template <int FMT, Kind KIND, typename LT>
@@ -284,6 +453,15 @@ hipError_t dispatch_fmt(Kind kind, dq_codec fmt, dq_dtype dtype, bool has_local,
 }
 
 }  // namespace
+
+hipError_t launch_mx_walk(dq_codec fmt, dq_dtype dtype, bool tree, const MxWalk &W, uint32_t n_cu, hipStream_t s) {
+  switch (fmt) {
+    case DQ_MXFP8_E4M3: return mx_walk_fmt<DQ_MXFP8_E4M3>(dtype, tree, W, n_cu, s);
+    case DQ_MXFP6_E3M2: return mx_walk_fmt<DQ_MXFP6_E3M2>(dtype, tree, W, n_cu, s);
+    case DQ_MXFP4_E2M1: return mx_walk_fmt<DQ_MXFP4_E2M1>(dtype, tree, W, n_cu, s);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 hipError_t mx_launch_one(Kind kind, dq_codec fmt, dq_dtype dtype, bool has_local, const MxJob &job, uint32_t n_cu,
                          hipStream_t s) {
