@@ -1,8 +1,10 @@
-"""Thin ctypes binding of libdq.so: same names as include/dq.h, argument marshalling only.
+"""Thin binding of libdq.so: same names as include/dq.h, argument marshalling only.
 
 PyTorch is used for device memory and streams; every step of the path runs in the HIP
 kernels.  There is no fallback: if the library is not built, or no GPU is present when a
-compute call is made, the call raises.
+compute call is made, the call raises.  The calls that a program makes once per chunk or bucket do
+their checks and allocations in the extension module _dqpy (csrc/dq_python.cpp); contexts,
+schedules and whatever is set up once go through ctypes.
 """
 import ctypes as C
 import os
@@ -56,11 +58,18 @@ class Local(C.Structure):
 
 
 _lib = None
+_py = None      # the extension module, its entry points bound to _lib's
+
+
+def _native():
+    if _lib is None:
+        lib()
+    return _py
 
 
 def lib():
-    """Load libdq.so (built in-tree by build.py).  Raises if it is missing."""
-    global _lib
+    """Load libdq.so and _dqpy.so (built in-tree by build.py).  Raises if one is missing."""
+    global _lib, _py
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise DqError(f"{LIB_PATH} is not built: run `python -m paper_2602_08923_amd.build` "
@@ -110,7 +119,12 @@ def lib():
         L.dq_pipelined_stage_bytes.restype = C.c_size_t
         L.dq_dar_hop_pipelined.argtypes = [vp, vp, C.POINTER(Local), C.POINTER(Chunk), u32, u32, vp, vp, vp, vp]
         L.dq_dar_hop_pipelined_static.argtypes = [vp, vp, C.POINTER(Local), C.POINTER(Chunk), u32, u32, vp, vp, vp]
-        _lib = L
+        try:
+            from . import _dqpy
+        except ImportError as e:
+            raise DqError(f"_dqpy is not built: run `python -m paper_2602_08923_amd.build` ({e})") from e
+        _dqpy.init(LIB_PATH, DqError)
+        _lib, _py = L, _dqpy
     return _lib
 
 
@@ -124,7 +138,7 @@ def _check(st, detail=False):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
@@ -177,8 +191,7 @@ def _local(local, chunk, mu=None, sg_index=None):
     else:
         if sg_index.dtype != torch.int32 or sg_index.numel() != sum(chunk.n_sg) or local.numel() % 256:
             raise DqError("sg_index is int32, one per super-group of the chunk")
-        if sg_index.numel() and not 0 <= int(sg_index.min()) <= int(sg_index.max()) < local.numel() // 256:
-            raise DqError("sg_index points outside the tensor")
+        _native().check_index(sg_index, local.numel() // 256)
     d, m, x = _ptr(local), _ptr(_mean(mu, chunk)), _ptr(sg_index)
     return C.byref(Local(d, _dtype(local), m, x))
 
@@ -204,49 +217,18 @@ class Context:
         _check(lib().dq_set_round(self.h, r))
 
     def dq_compress(self, local, chunk, rank, packed_out=None, mu=None, sg_index=None):
-        loc = _local(local, chunk, mu, sg_index)
-        if packed_out is None:
-            packed_out = torch.zeros(dq_packed_bytes(chunk), dtype=torch.uint8, device=local.device)
-        if packed_out.numel() < dq_packed_bytes(chunk):
-            raise DqError("packed_out too small")
-        _check(lib().dq_compress(self.h, loc, C.byref(chunk), rank, _ptr(packed_out), _stream()))
-        return packed_out
+        return _py.compress(self.h, local, chunk, rank, packed_out, mu, sg_index)
 
     def dq_dar_hop(self, packed_in, local, chunk, rank, packed_out=None, mu=None, sg_index=None):
-        loc = _local(local, chunk, mu, sg_index)
-        if packed_in.numel() < dq_packed_bytes(chunk):
-            raise DqError("buffers do not match the chunk")
-        if packed_out is None:
-            packed_out = torch.zeros(dq_packed_bytes(chunk), dtype=torch.uint8, device=local.device)
-        if packed_out.numel() < dq_packed_bytes(chunk):
-            raise DqError("packed_out too small")
-        _check(lib().dq_dar_hop(self.h, _ptr(packed_in), loc, C.byref(chunk), rank, _ptr(packed_out), _stream()))
-        return packed_out
+        return _py.dar_hop(self.h, packed_in, local, chunk, rank, packed_out, mu, sg_index)
 
     def dq_decompress(self, packed_in, chunk, local=None, out=None, mu=None, sg_index=None):
-        loc = _local(local, chunk, mu, sg_index)
-        if packed_in.numel() < dq_packed_bytes(chunk):
-            raise DqError("buffers do not match the chunk")
-        if out is None:
-            out = torch.empty(_entries(chunk), dtype=torch.float32, device=packed_in.device)
-        if out.numel() != _entries(chunk) or out.dtype != torch.float32:
-            raise DqError("out must be float32 with one element per entry")
-        _check(lib().dq_decompress(self.h, _ptr(packed_in), loc, C.byref(chunk), _ptr(out), _stream()))
-        return out
+        return _py.decompress(self.h, packed_in, chunk, local, out, mu, sg_index)
 
     def dq_decompress_restore(self, packed_in, chunk, origin, out_base, local=None, mu=None, mu_back=None, sg_index=None):
         """Decompress (+ local - mu) with every super-group written to out_base[origin[j]] and
         n_workers * mu_back[j] added: the restore fused into the sink's kernel."""
-        loc = _local(local, chunk, mu, sg_index)
-        if packed_in.numel() < dq_packed_bytes(chunk):
-            raise DqError("buffers do not match the chunk")
-        if origin.dtype != torch.int32 or origin.numel() != sum(chunk.n_sg):
-            raise DqError("origin is int32, one per super-group of the chunk")
-        if out_base.dtype != torch.float32 or (origin.numel() and out_base.numel() < (int(origin.max()) + 1) * 256):
-            raise DqError("out_base is float32 and holds every destination super-group")
-        _check(lib().dq_decompress_restore(self.h, _ptr(packed_in), loc, C.byref(chunk), _ptr(origin),
-                                           _ptr(_mean(mu_back, chunk)), _ptr(out_base), _stream()))
-        return out_base
+        return _py.decompress_restore(self.h, packed_in, chunk, origin, out_base, local, mu, mu_back, sg_index)
 
 
 # ---- MX comparison codec -------------------------------------------------------------
@@ -256,31 +238,15 @@ def dq_mx_packed_bytes(fmt, n_entries):
 
 
 def dq_mx_compress(fmt, local, packed_out=None):
-    n = local.numel()
-    if packed_out is None:
-        packed_out = torch.zeros(dq_mx_packed_bytes(fmt, n), dtype=torch.uint8, device=local.device)
-    _check(lib().dq_mx_compress(fmt, _ptr(local), _dtype(local), n, _ptr(packed_out), _stream()))
-    return packed_out
+    return _native().mx_compress(fmt, local, packed_out)
 
 
 def dq_mx_dar_hop(fmt, packed_in, local, packed_out=None):
-    n = local.numel()
-    if packed_in.numel() < dq_mx_packed_bytes(fmt, n):
-        raise DqError("packed_in too small")
-    if packed_out is None:
-        packed_out = torch.zeros(dq_mx_packed_bytes(fmt, n), dtype=torch.uint8, device=local.device)
-    _check(lib().dq_mx_dar_hop(fmt, _ptr(packed_in), _ptr(local), _dtype(local), n, _ptr(packed_out), _stream()))
-    return packed_out
+    return _native().mx_dar_hop(fmt, packed_in, local, packed_out)
 
 
 def dq_mx_decompress(fmt, packed_in, n_entries, local=None, out=None):
-    if packed_in.numel() < dq_mx_packed_bytes(fmt, n_entries):
-        raise DqError("packed_in too small")
-    if out is None:
-        out = torch.empty(n_entries, dtype=torch.float32, device=packed_in.device)
-    _check(lib().dq_mx_decompress(fmt, _ptr(packed_in), _ptr(local), 0 if local is None else _dtype(local), n_entries,
-                                  _ptr(out), _stream()))
-    return out
+    return _native().mx_decompress(fmt, packed_in, n_entries, local, out)
 
 
 # ---- hop replay ------------------------------------------------------------------------
@@ -335,11 +301,10 @@ class Replay:
             ms = (C.c_float * self.n_steps)()
             _check(lib().dq_replay_run(self.h, ms, _stream()))
             return list(ms)
-        _check(lib().dq_replay_run(self.h, None, _stream()))
-        return None
+        return _py.replay_run(self.h)
 
     def run_steps(self, first, count):
-        _check(lib().dq_replay_run_steps(self.h, first, count, _stream()))
+        _py.replay_run_steps(self.h, first, count)
 
     def run_launch(self, step, launch):
         _check(lib().dq_replay_run_launch(self.h, step, launch, _stream()))
@@ -367,83 +332,33 @@ class Replay:
 # ------------------------------------------------------------------ before and after the main stage
 def dq_sg_stats(x, mu_out=None, F_out=None):
     """Per-super-group mean and sum of squares of one worker's tensor -> (mu, F) float32."""
-    n_sg = x.numel() // 256
-    if x.numel() % 256:
-        raise DqError("tensor length must be a multiple of 256")
-    if mu_out is None:
-        mu_out = torch.empty(n_sg, dtype=torch.float32, device=x.device)
-    if F_out is None:
-        F_out = torch.empty(n_sg, dtype=torch.float32, device=x.device)
-    _check(lib().dq_sg_stats(_ptr(x), _dtype(x), n_sg, _ptr(mu_out), _ptr(F_out), _stream()))
-    return mu_out, F_out
+    return _native().sg_stats(x, mu_out, F_out)
 
 
 def dq_stats_combine(mu_all, F_all):
     """mu_all, F_all: float32 [n_workers, n_sg] -> (mu, F) float32 [n_sg]."""
-    n, J = mu_all.shape
-    if F_all.shape != mu_all.shape or mu_all.dtype != torch.float32 or F_all.dtype != torch.float32:
-        raise DqError("statistics are two float32 tensors of the same [n_workers, n_sg] shape")
-    mu = torch.empty(J, dtype=torch.float32, device=mu_all.device)
-    F = torch.empty(J, dtype=torch.float32, device=mu_all.device)
-    _check(lib().dq_stats_combine(_ptr(mu_all), _ptr(F_all), n, J, _ptr(mu), _ptr(F), _stream()))
-    return mu, F
+    return _native().stats_combine(mu_all, F_all)
 
 
 def dq_allocate(F, n_sg_per_bucket, max_code_bits, max_width=8):
     """F: float32 [n_buckets * n_sg_per_bucket] -> (widths uint8, pos int32 (holds uint32),
     counts int32 [n_buckets, 5] = #2-bit, #4-bit, #8-bit, #16-bit, threshold pattern)."""
-    if F.dtype != torch.float32 or F.numel() % n_sg_per_bucket:
-        raise DqError("F is float32 with a whole number of buckets")
-    nb = F.numel() // n_sg_per_bucket
-    widths = torch.empty(F.numel(), dtype=torch.uint8, device=F.device)
-    pos = torch.empty(F.numel(), dtype=torch.int32, device=F.device)
-    counts = torch.empty((nb, 5), dtype=torch.int32, device=F.device)
-    _check(lib().dq_allocate(_ptr(F), n_sg_per_bucket, nb, int(max_code_bits), int(max_width), _ptr(widths), _ptr(pos),
-                             _ptr(counts), _stream()))
-    return widths, pos, counts
+    return _native().allocate(F, n_sg_per_bucket, int(max_code_bits), int(max_width))
 
 
 def dq_reorder(x, pos, n_sg_per_bucket, out=None):
-    nb = pos.numel() // n_sg_per_bucket
-    if x.numel() != pos.numel() * 256 or pos.numel() % n_sg_per_bucket or pos.dtype != torch.int32:
-        raise DqError("x holds 256 entries per position; positions are int32, a whole number of buckets")
-    if out is None:
-        out = torch.empty_like(x)
-    _check(lib().dq_reorder(_ptr(x), _dtype(x), _ptr(pos), n_sg_per_bucket, nb, _ptr(out), _stream()))
-    return out
+    return _native().reorder(x, pos, n_sg_per_bucket, out)
 
 
 def dq_reorder_mean(mu, pos, n_sg_per_bucket, counts=None, out=None, with_origin=False):
     """The means the main stage subtracts, in reordered order (zero for 16-bit super-groups).
     counts: what dq_allocate returned (int32 [n_buckets, 5]) or None (no 16-bit class).
     mu None: only the origins.  with_origin: also return origin (int32, origin[pos[j]] = j per bucket)."""
-    nb = pos.numel() // n_sg_per_bucket
-    if pos.numel() % n_sg_per_bucket or pos.dtype != torch.int32:
-        raise DqError("positions are int32, a whole number of buckets")
-    if mu is not None and (mu.dtype != torch.float32 or mu.numel() != pos.numel()):
-        raise DqError("mu is float32, one per position")
-    if counts is not None and (counts.dtype != torch.int32 or counts.numel() != 5 * nb):
-        raise DqError("counts is int32 [n_buckets, 5]")
-    if mu is None and not with_origin:
-        raise DqError("nothing to compute")
-    if out is None and mu is not None:
-        out = torch.empty_like(mu)
-    origin = torch.empty_like(pos) if with_origin else None
-    _check(lib().dq_reorder_mean(_ptr(mu), _ptr(pos), _ptr(counts), n_sg_per_bucket, nb,
-                                 _ptr(out) if mu is not None else None, _ptr(origin), _stream()))
-    return (out, origin) if with_origin else out
+    return _native().reorder_mean(mu, pos, n_sg_per_bucket, counts, out, with_origin)
 
 
 def dq_restore(total, pos, n_sg_per_bucket, n_workers, mu_main=None, out=None):
-    nb = pos.numel() // n_sg_per_bucket
-    if total.dtype != torch.float32 or total.numel() != pos.numel() * 256 or pos.dtype != torch.int32:
-        raise DqError("the main stage's result is float32, 256 entries per position")
-    if mu_main is not None and (mu_main.dtype != torch.float32 or mu_main.numel() != pos.numel()):
-        raise DqError("mu_main is float32, one per super-group")
-    if out is None:
-        out = torch.empty_like(total)
-    _check(lib().dq_restore(_ptr(total), _ptr(pos), _ptr(mu_main), n_workers, n_sg_per_bucket, nb, _ptr(out), _stream()))
-    return out
+    return _native().restore(total, pos, n_sg_per_bucket, n_workers, mu_main, out)
 
 
 # ------------------------------------------------------------------ block-wise pipelining

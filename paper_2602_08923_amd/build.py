@@ -1,4 +1,4 @@
-"""Compile libdq.so (the HIP kernels + C ABI) for gfx950, in-tree.
+"""Compile libdq.so (the HIP kernels + C ABI) for gfx950 and _dqpy.so (the binding's native half), in-tree.
 
 hipcc cross-compiles without a GPU.  Flags that matter for bit-exactness against the CPU
 oracle: -ffp-contract=off (fused multiply-adds only where the source writes them) and the
@@ -8,12 +8,15 @@ shifts and masks into SDWA operands (an SDWA instruction takes the issue slots o
 import os
 import subprocess
 import sys
+import sysconfig
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdq.so")
-SOURCES = ["dq_kernels.hip", "dq_walk.hip", "mx_kernels.hip", "pp_kernels.hip", "probe_kernels.hip", "dq_api.cpp", "dq_replay.cpp"]
+EXT = os.path.join(HERE, "_dqpy.so")
+SOURCES = ["dq_kernels.hip", "dq_walk.hip", "dq_bounds.hip", "mx_kernels.hip", "pp_kernels.hip", "probe_kernels.hip", "dq_api.cpp", "dq_replay.cpp"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-ffp-contract=off", "-fhip-fp32-correctly-rounded-divide-sqrt",
@@ -23,12 +26,42 @@ FLAGS = [
 ]
 
 
+def _run(cmds, verbose):
+    """Run the commands side by side; raise if one fails."""
+    procs = []
+    for cmd in cmds:
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        procs.append((cmd, subprocess.Popen(cmd)))
+    for cmd, p in procs:
+        if p.wait() != 0:
+            for _, other in procs:
+                other.wait()
+            raise subprocess.CalledProcessError(p.returncode, cmd)
+
+
+def _extension_command():
+    """The host compiler's command for _dqpy.so, against this interpreter's and PyTorch's headers."""
+    import torch
+    t = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+            "-I", sysconfig.get_path("include"), "-isystem", os.path.join(t, "include"),
+            "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
+            "-I", os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(CSRC, "dq_python.cpp"), "-o", EXT,
+            "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+
+
 def build(verbose=False, extra_flags=()):
-    srcs = [os.path.join(CSRC, s) for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
-    cmd = ["hipcc", "-x", "hip"] + FLAGS + list(extra_flags) + ["-I", os.path.join(ROOT, "include"), "-I", CSRC] + srcs + ["-o", LIB]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
+    with tempfile.TemporaryDirectory() as tmp:
+        cmds, objs = [_extension_command()], []
+        for s in SOURCES:
+            objs.append(os.path.join(tmp, s + ".o"))
+            cmds.append(["hipcc", "-x", "hip"] + [f for f in FLAGS if f != "-shared"] + list(extra_flags) +
+                        ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", os.path.join(CSRC, s), "-o", objs[-1]])
+        _run(cmds, verbose)
+        _run([["hipcc", "--offload-arch=gfx950", "-fPIC", "-shared"] + objs + ["-o", LIB]], verbose)
     return LIB
 
 

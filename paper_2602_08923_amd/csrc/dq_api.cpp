@@ -8,6 +8,7 @@
 #include <string>
 #include <vector>
 
+#include "dq_bounds.h"
 #include "dq_device.h"
 
 namespace {
@@ -310,6 +311,7 @@ dq_status dq_create(const dq_config *cfg, dq_ctx **out) {
   P.inv_n512 = P.inv_n * (1.0f / 512.0f);
   P.s_n = P.inv_n * (1.0f / 256.0f);
   ctx->params = P;
+  dq::bounds_context(1);
   *out = ctx;
   return DQ_OK;
 }
@@ -319,6 +321,7 @@ void dq_destroy(dq_ctx *ctx) {
   if (ctx->blob_dev) (void)hipFree(ctx->blob_dev);
   drop_events(ctx);
   delete ctx;
+  dq::bounds_context(-1);
 }
 
 dq_status dq_stream_probe(dq_ctx *ctx, const void *in, size_t in_bytes, void *out, size_t out_bytes, void *hip_stream) {

@@ -26,6 +26,7 @@
 // All arithmetic that decides a code is IEEE binary32 with explicit fused multiply-adds
 // only where written (this file is compiled with -ffp-contract=off and correctly rounded
 // division), so the results do not depend on the launch shape.
+#include "dq_bounds.h"
 #include "dq_codec.h"
 
 namespace dq {
@@ -409,6 +410,7 @@ __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
 // with fp32 locals use 82-88 since a tile's successor is requested from inside the tile, the others at most 80).
 template <Kind KIND, typename LT>
 __global__ __launch_bounds__(kBlockThreads) void k_one(Job job, Params P) {
+  if (P.guard && gld<uint32_t>(P.guard)) return;
   run_job<KIND, LT>(job, P);
 }
 template <Kind KIND, typename LT>
@@ -498,6 +500,7 @@ template <Kind KIND, typename LT>
 hipError_t go_one(const Job &job, Params p, uint32_t grid_blocks, hipStream_t s) {
   const uint32_t tiles = job_tiles(job);
   if (tiles == 0) return hipSuccess;
+  p.guard = armed_guard();
   const uint32_t blocks = blocks_per_job<KIND>(tiles, tiles, 1, grid_blocks);
   hipLaunchKernelGGL((k_one<KIND, LT>), dim3(blocks), dim3(kBlockThreads), lds_bytes(p, KIND), s, job, p);
   return hipGetLastError();

@@ -1,0 +1,412 @@
+// The binding's per-call work in native code: argument checks, output allocation, the current stream and the call into
+// libdq.  A call on a small chunk takes the GPU 4 to 5 us; through ctypes and Python the host took 9 to 10 us for it, here it
+// takes less than the launch itself.  binding.py documents the functions; errors are its DqError.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <ATen/ATen.h>
+#include <c10/hip/HIPStream.h>
+#include <dlfcn.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <string>
+
+#include "dq_bounds.h"
+
+namespace {
+
+PyObject *g_error = nullptr;  // binding.DqError
+
+// libdq's entry points, looked up in the library the binding names (init)
+#define DQ_SYMBOLS(X)                                                                                                    \
+  X(dq_packed_bytes) X(dq_compress) X(dq_dar_hop) X(dq_decompress) X(dq_decompress_restore) X(dq_mx_packed_bytes)       \
+  X(dq_mx_compress) X(dq_mx_dar_hop) X(dq_mx_decompress) X(dq_replay_run) X(dq_replay_run_steps) X(dq_sg_stats) X(dq_stats_combine) \
+  X(dq_allocate) X(dq_reorder) X(dq_reorder_mean) X(dq_restore) X(dq_status_str) X(dq_last_hip_error) X(dqx_bounds_begin) \
+  X(dqx_bounds_end)
+struct Lib {
+#define X(name) decltype(&::name) name = nullptr;
+  DQ_SYMBOLS(X)
+#undef X
+} L;
+
+struct Raised {};  // a Python exception is set
+[[noreturn]] void fail(const std::string &what) {
+  PyErr_SetString(g_error, what.c_str());
+  throw Raised();
+}
+void check(dq_status st) {
+  if (st == DQ_OK) return;
+  std::string msg = L.dq_status_str(st);
+  if (st == DQ_EHIP) msg += std::string(": ") + L.dq_last_hip_error();
+  fail(msg);
+}
+
+void *stream() { return (void *)c10::hip::getCurrentHIPStream().stream(); }
+
+const at::Tensor &tensor(PyObject *o) {
+  if (!THPVariable_Check(o)) {
+    PyErr_Format(PyExc_TypeError, "expected a tensor, got %.100s", Py_TYPE(o)->tp_name);
+    throw Raised();
+  }
+  return THPVariable_Unpack(o);
+}
+const at::Tensor *tensor_or_null(PyObject *o) { return o == Py_None ? nullptr : &tensor(o); }
+void *ptr(const at::Tensor &t) {
+  if (!t.is_cuda() || !t.is_contiguous()) fail("tensors must be contiguous CUDA tensors");
+  return t.data_ptr();
+}
+void *ptr(const at::Tensor *t) { return t ? ptr(*t) : nullptr; }
+template <typename T>
+T *as(void *p) { return static_cast<T *>(p); }
+
+dq_dtype local_dtype(const at::Tensor &t) {
+  const auto s = t.scalar_type();
+  if (s == at::kFloat) return DQ_F32;
+  if (s == at::kBFloat16) return DQ_BF16;
+  fail("local slices must be float32 or bfloat16");
+}
+unsigned long long number(PyObject *o) {
+  const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
+  if (PyErr_Occurred()) throw Raised();
+  return v;
+}
+
+// A handle kept in a ctypes.c_void_p (None: closed).
+void *handle(PyObject *o) {
+  if (o == Py_None) return nullptr;
+  Py_buffer b;
+  if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) throw Raised();
+  void *p = nullptr;
+  if (b.len == sizeof(p)) memcpy(&p, b.buf, sizeof(p));
+  PyBuffer_Release(&b);
+  return p;
+}
+dq_chunk chunk_of(PyObject *o) {
+  Py_buffer b;
+  if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) throw Raised();
+  dq_chunk c;
+  const bool ok = (size_t)b.len == sizeof(c);
+  if (ok) memcpy(&c, b.buf, sizeof(c));
+  PyBuffer_Release(&b);
+  if (!ok) {
+    PyErr_SetString(PyExc_TypeError, "expected a Chunk");
+    throw Raised();
+  }
+  return c;
+}
+int64_t sgs(const dq_chunk &c) { return (int64_t)c.n_sg[0] + c.n_sg[1] + c.n_sg[2] + c.n_sg[3]; }
+
+at::Tensor make(int64_t n, at::ScalarType t, const at::Tensor &like, bool zero = false) {
+  const auto o = like.options().dtype(t);
+  return zero ? at::zeros({n}, o) : at::empty({n}, o);
+}
+PyObject *wrap(const at::Tensor &t) { return THPVariable_Wrap(t); }
+PyObject *give(PyObject *given, const at::Tensor &made) {  // the caller's own object, or the new tensor
+  if (given == Py_None) return wrap(made);
+  Py_INCREF(given);
+  return given;
+}
+
+float *mean(const at::Tensor *mu, const dq_chunk &c) {
+  if (mu && (mu->scalar_type() != at::kFloat || mu->numel() != sgs(c))) fail("mu is float32, one per super-group of the chunk");
+  return as<float>(ptr(mu));
+}
+// dq_local of a chunk's entries, or of the original tensor that `index` picks from; the check of the indices goes to `b`.
+dq_local local_of(const at::Tensor &local, const dq_chunk &c, const at::Tensor *mu, const at::Tensor *index, dq::Bound *b, int *n) {
+  if (!index) {
+    if (local.numel() != sgs(c) * 256) fail("local slice does not match the chunk");
+  } else {
+    if (index->scalar_type() != at::kInt || index->numel() != sgs(c) || local.numel() % 256)
+      fail("sg_index is int32, one per super-group of the chunk");
+    const uint32_t *p = as<uint32_t>(ptr(*index));
+    const int64_t limit = local.numel() / 256;
+    if (index->numel()) b[(*n)++] = dq::Bound{p, (uint32_t)index->numel(), (uint32_t)(limit < INT32_MAX ? limit : INT32_MAX)};
+  }
+  dq_local l;
+  l.data = ptr(local);
+  l.mu = mean(mu, c);
+  l.sg_index = index ? as<uint32_t>(index->data_ptr()) : nullptr;
+  l.dtype = local_dtype(local);
+  return l;
+}
+
+constexpr const char *kOutside = "sg_index points outside the tensor";
+// Runs `call` behind the check of its indices (if it has any); the texts are the errors of its arrays.
+template <typename F>
+void checked(const dq::Bound *b, int n, F call, const char *first = kOutside, const char *second = nullptr) {
+  void *s = stream();
+  if (n == 0) return check(call(s));
+  check(L.dqx_bounds_begin(b, n, s));
+  const dq_status st = call(s);
+  int outside = 0;
+  dq_status end;
+  Py_BEGIN_ALLOW_THREADS
+  end = L.dqx_bounds_end(s, &outside);
+  Py_END_ALLOW_THREADS
+  check(st);
+  check(end);
+  if (outside) fail(outside & 1 ? first : second);
+}
+
+#define DQ_ARGS(n)                                                                     \
+  if (nargs != n) {                                                                    \
+    PyErr_Format(PyExc_TypeError, "expected %d arguments, got %zd", n, nargs);         \
+    throw Raised();                                                                    \
+  }
+
+PyObject *py_compress(PyObject *const *a, Py_ssize_t nargs) {  // ctx, local, chunk, rank, packed_out, mu, sg_index
+  DQ_ARGS(7)
+  const at::Tensor &local = tensor(a[1]);
+  const dq_chunk c = chunk_of(a[2]);
+  dq::Bound b[2];
+  int n = 0;
+  const dq_local l = local_of(local, c, tensor_or_null(a[5]), tensor_or_null(a[6]), b, &n);
+  const int64_t bytes = (int64_t)L.dq_packed_bytes(&c);
+  const at::Tensor out = a[4] == Py_None ? make(bytes, at::kByte, local, true) : tensor(a[4]);
+  if (out.numel() < bytes) fail("packed_out too small");
+  void *h = handle(a[0]), *o = ptr(out);
+  const uint32_t rank = (uint32_t)number(a[3]);
+  checked(b, n, [&](void *s) { return L.dq_compress(as<dq_ctx>(h), &l, &c, rank, o, s); });
+  return give(a[4], out);
+}
+PyObject *py_dar_hop(PyObject *const *a, Py_ssize_t nargs) {  // ctx, packed_in, local, chunk, rank, packed_out, mu, sg_index
+  DQ_ARGS(8)
+  const at::Tensor &in = tensor(a[1]), &local = tensor(a[2]);
+  const dq_chunk c = chunk_of(a[3]);
+  dq::Bound b[2];
+  int n = 0;
+  const dq_local l = local_of(local, c, tensor_or_null(a[6]), tensor_or_null(a[7]), b, &n);
+  const int64_t bytes = (int64_t)L.dq_packed_bytes(&c);
+  if (in.numel() < bytes) fail("buffers do not match the chunk");
+  const at::Tensor out = a[5] == Py_None ? make(bytes, at::kByte, local, true) : tensor(a[5]);
+  if (out.numel() < bytes) fail("packed_out too small");
+  void *h = handle(a[0]), *i = ptr(in), *o = ptr(out);
+  const uint32_t rank = (uint32_t)number(a[4]);
+  checked(b, n, [&](void *s) { return L.dq_dar_hop(as<dq_ctx>(h), i, &l, &c, rank, o, s); });
+  return give(a[5], out);
+}
+PyObject *py_decompress(PyObject *const *a, Py_ssize_t nargs) {  // ctx, packed_in, chunk, local, out, mu, sg_index
+  DQ_ARGS(7)
+  const at::Tensor &in = tensor(a[1]);
+  const at::Tensor *local = tensor_or_null(a[3]);
+  const dq_chunk c = chunk_of(a[2]);
+  dq::Bound b[2];
+  int n = 0;
+  dq_local l = {};
+  if (local) l = local_of(*local, c, tensor_or_null(a[5]), tensor_or_null(a[6]), b, &n);
+  if (in.numel() < (int64_t)L.dq_packed_bytes(&c)) fail("buffers do not match the chunk");
+  const at::Tensor out = a[4] == Py_None ? make(sgs(c) * 256, at::kFloat, in) : tensor(a[4]);
+  if (out.numel() != sgs(c) * 256 || out.scalar_type() != at::kFloat) fail("out must be float32 with one element per entry");
+  void *h = handle(a[0]), *i = ptr(in), *o = ptr(out);
+  checked(b, n, [&](void *s) { return L.dq_decompress(as<dq_ctx>(h), i, local ? &l : nullptr, &c, as<float>(o), s); });
+  return give(a[4], out);
+}
+PyObject *py_decompress_restore(PyObject *const *a, Py_ssize_t nargs) {
+  DQ_ARGS(9)  // ctx, packed_in, chunk, origin, out_base, local, mu, mu_back, sg_index
+  const at::Tensor &in = tensor(a[1]), &origin = tensor(a[3]), &out = tensor(a[4]);
+  const at::Tensor *local = tensor_or_null(a[5]);
+  const dq_chunk c = chunk_of(a[2]);
+  dq::Bound b[2];
+  int n = 0;
+  dq_local l = {};
+  if (local) l = local_of(*local, c, tensor_or_null(a[6]), tensor_or_null(a[8]), b, &n);
+  const bool index = n > 0;
+  if (in.numel() < (int64_t)L.dq_packed_bytes(&c)) fail("buffers do not match the chunk");
+  if (origin.scalar_type() != at::kInt || origin.numel() != sgs(c)) fail("origin is int32, one per super-group of the chunk");
+  constexpr const char *kSmall = "out_base is float32 and holds every destination super-group";
+  if (out.scalar_type() != at::kFloat) fail(kSmall);
+  void *h = handle(a[0]), *i = ptr(in), *g = ptr(origin), *o = ptr(out);
+  const int64_t limit = out.numel() / 256;
+  if (origin.numel()) b[n++] = dq::Bound{as<uint32_t>(g), (uint32_t)origin.numel(), (uint32_t)(limit < INT32_MAX ? limit : INT32_MAX)};
+  const float *back = mean(tensor_or_null(a[7]), c);
+  checked(b, n, [&](void *s) { return L.dq_decompress_restore(as<dq_ctx>(h), i, local ? &l : nullptr, &c, as<uint32_t>(g), back, as<float>(o), s); },
+          index ? kOutside : kSmall, kSmall);
+  return give(a[4], out);
+}
+
+PyObject *py_mx_compress(PyObject *const *a, Py_ssize_t nargs) {  // fmt, local, packed_out
+  DQ_ARGS(3)
+  const dq_codec fmt = (dq_codec)number(a[0]);
+  const at::Tensor &local = tensor(a[1]);
+  const int64_t n = local.numel();
+  const at::Tensor out = a[2] == Py_None ? make((int64_t)L.dq_mx_packed_bytes(fmt, n), at::kByte, local, true) : tensor(a[2]);
+  check(L.dq_mx_compress(fmt, ptr(local), local_dtype(local), n, ptr(out), stream()));
+  return give(a[2], out);
+}
+PyObject *py_mx_dar_hop(PyObject *const *a, Py_ssize_t nargs) {  // fmt, packed_in, local, packed_out
+  DQ_ARGS(4)
+  const dq_codec fmt = (dq_codec)number(a[0]);
+  const at::Tensor &in = tensor(a[1]), &local = tensor(a[2]);
+  const int64_t n = local.numel(), bytes = (int64_t)L.dq_mx_packed_bytes(fmt, n);
+  if (in.numel() < bytes) fail("packed_in too small");
+  const at::Tensor out = a[3] == Py_None ? make(bytes, at::kByte, local, true) : tensor(a[3]);
+  check(L.dq_mx_dar_hop(fmt, ptr(in), ptr(local), local_dtype(local), n, ptr(out), stream()));
+  return give(a[3], out);
+}
+PyObject *py_mx_decompress(PyObject *const *a, Py_ssize_t nargs) {  // fmt, packed_in, n_entries, local, out
+  DQ_ARGS(5)
+  const dq_codec fmt = (dq_codec)number(a[0]);
+  const at::Tensor &in = tensor(a[1]);
+  const int64_t n = (int64_t)number(a[2]);
+  const at::Tensor *local = tensor_or_null(a[3]);
+  if (in.numel() < (int64_t)L.dq_mx_packed_bytes(fmt, n)) fail("packed_in too small");
+  const at::Tensor out = a[4] == Py_None ? make(n, at::kFloat, in) : tensor(a[4]);
+  check(L.dq_mx_decompress(fmt, ptr(in), ptr(local), local ? local_dtype(*local) : DQ_F32, n, as<float>(ptr(out)), stream()));
+  return give(a[4], out);
+}
+
+PyObject *py_replay_run(PyObject *const *a, Py_ssize_t nargs) {  // replay
+  DQ_ARGS(1)
+  check(L.dq_replay_run(as<dq_replay>(handle(a[0])), nullptr, stream()));
+  Py_RETURN_NONE;
+}
+PyObject *py_replay_run_steps(PyObject *const *a, Py_ssize_t nargs) {  // replay, first, count
+  DQ_ARGS(3)
+  check(L.dq_replay_run_steps(as<dq_replay>(handle(a[0])), (uint32_t)number(a[1]), (uint32_t)number(a[2]), stream()));
+  Py_RETURN_NONE;
+}
+
+PyObject *pair(PyObject *x, PyObject *y) {
+  PyObject *t = PyTuple_New(2);
+  PyTuple_SET_ITEM(t, 0, x);
+  PyTuple_SET_ITEM(t, 1, y);
+  return t;
+}
+PyObject *py_sg_stats(PyObject *const *a, Py_ssize_t nargs) {  // x, mu_out, F_out
+  DQ_ARGS(3)
+  const at::Tensor &x = tensor(a[0]);
+  if (x.numel() % 256) fail("tensor length must be a multiple of 256");
+  const int64_t n = x.numel() / 256;
+  const at::Tensor mu = a[1] == Py_None ? make(n, at::kFloat, x) : tensor(a[1]), F = a[2] == Py_None ? make(n, at::kFloat, x) : tensor(a[2]);
+  void *p = ptr(x);
+  check(L.dq_sg_stats(p, local_dtype(x), n, as<float>(ptr(mu)), as<float>(ptr(F)), stream()));
+  return pair(give(a[1], mu), give(a[2], F));
+}
+PyObject *py_stats_combine(PyObject *const *a, Py_ssize_t nargs) {  // mu_all, F_all
+  DQ_ARGS(2)
+  const at::Tensor &mu_all = tensor(a[0]), &F_all = tensor(a[1]);
+  if (mu_all.dim() != 2 || F_all.sizes() != mu_all.sizes() || mu_all.scalar_type() != at::kFloat || F_all.scalar_type() != at::kFloat)
+    fail("statistics are two float32 tensors of the same [n_workers, n_sg] shape");
+  const int64_t n = mu_all.size(0), J = mu_all.size(1);
+  const at::Tensor mu = make(J, at::kFloat, mu_all), F = make(J, at::kFloat, mu_all);
+  check(L.dq_stats_combine(as<float>(ptr(mu_all)), as<float>(ptr(F_all)), (uint32_t)n, J, as<float>(ptr(mu)), as<float>(ptr(F)), stream()));
+  return pair(wrap(mu), wrap(F));
+}
+PyObject *py_allocate(PyObject *const *a, Py_ssize_t nargs) {  // F, n_sg_per_bucket, max_code_bits, max_width
+  DQ_ARGS(4)
+  const at::Tensor &F = tensor(a[0]);
+  const int64_t J = (int64_t)number(a[1]);
+  if (J == 0) {
+    PyErr_SetString(PyExc_ZeroDivisionError, "n_sg_per_bucket is zero");
+    throw Raised();
+  }
+  if (F.scalar_type() != at::kFloat || F.numel() % J) fail("F is float32 with a whole number of buckets");
+  const int64_t nb = F.numel() / J;
+  const at::Tensor widths = make(F.numel(), at::kByte, F), pos = make(F.numel(), at::kInt, F);
+  const at::Tensor counts = at::empty({nb, 5}, F.options().dtype(at::kInt));
+  check(L.dq_allocate(as<float>(ptr(F)), (uint32_t)J, (uint32_t)nb, number(a[2]), (uint32_t)number(a[3]), as<uint8_t>(ptr(widths)),
+                      as<uint32_t>(ptr(pos)), as<uint32_t>(ptr(counts)), stream()));
+  PyObject *t = PyTuple_New(3);
+  PyTuple_SET_ITEM(t, 0, wrap(widths));
+  PyTuple_SET_ITEM(t, 1, wrap(pos));
+  PyTuple_SET_ITEM(t, 2, wrap(counts));
+  return t;
+}
+PyObject *py_reorder(PyObject *const *a, Py_ssize_t nargs) {  // x, pos, n_sg_per_bucket, out
+  DQ_ARGS(4)
+  const at::Tensor &x = tensor(a[0]), &pos = tensor(a[1]);
+  const int64_t J = (int64_t)number(a[2]);
+  if (J == 0 || x.numel() != pos.numel() * 256 || pos.numel() % J || pos.scalar_type() != at::kInt)
+    fail("x holds 256 entries per position; positions are int32, a whole number of buckets");
+  const at::Tensor out = a[3] == Py_None ? at::empty_like(x) : tensor(a[3]);
+  void *p = ptr(x);
+  check(L.dq_reorder(p, local_dtype(x), as<uint32_t>(ptr(pos)), (uint32_t)J, (uint32_t)(pos.numel() / J), ptr(out), stream()));
+  return give(a[3], out);
+}
+PyObject *py_reorder_mean(PyObject *const *a, Py_ssize_t nargs) {  // mu, pos, n_sg_per_bucket, counts, out, with_origin
+  DQ_ARGS(6)
+  const at::Tensor *mu = tensor_or_null(a[0]), *counts = tensor_or_null(a[3]);
+  const at::Tensor &pos = tensor(a[1]);
+  const int64_t J = (int64_t)number(a[2]);
+  if (J == 0 || pos.numel() % J || pos.scalar_type() != at::kInt) fail("positions are int32, a whole number of buckets");
+  const int64_t nb = pos.numel() / J;
+  if (mu && (mu->scalar_type() != at::kFloat || mu->numel() != pos.numel())) fail("mu is float32, one per position");
+  if (counts && (counts->scalar_type() != at::kInt || counts->numel() != 5 * nb)) fail("counts is int32 [n_buckets, 5]");
+  const int with_origin = PyObject_IsTrue(a[5]);
+  if (with_origin < 0) throw Raised();
+  if (!mu && !with_origin) fail("nothing to compute");
+  at::Tensor out, origin;
+  if (a[4] != Py_None) out = tensor(a[4]);
+  else if (mu) out = at::empty_like(*mu);
+  if (with_origin) origin = at::empty_like(pos);
+  check(L.dq_reorder_mean(as<float>(ptr(mu)), as<uint32_t>(ptr(pos)), as<uint32_t>(ptr(counts)), (uint32_t)J, (uint32_t)nb,
+                          mu ? as<float>(ptr(out)) : nullptr, with_origin ? as<uint32_t>(ptr(origin)) : nullptr, stream()));
+  PyObject *o;
+  if (!out.defined()) {
+    Py_INCREF(Py_None);
+    o = Py_None;
+  } else {
+    o = give(a[4], out);
+  }
+  return with_origin ? pair(o, wrap(origin)) : o;
+}
+PyObject *py_restore(PyObject *const *a, Py_ssize_t nargs) {  // total, pos, n_sg_per_bucket, n_workers, mu_main, out
+  DQ_ARGS(6)
+  const at::Tensor &total = tensor(a[0]), &pos = tensor(a[1]);
+  const at::Tensor *mu = tensor_or_null(a[4]);
+  const int64_t J = (int64_t)number(a[2]);
+  if (J == 0 || total.scalar_type() != at::kFloat || total.numel() != pos.numel() * 256 || pos.scalar_type() != at::kInt)
+    fail("the main stage's result is float32, 256 entries per position");
+  if (mu && (mu->scalar_type() != at::kFloat || mu->numel() != pos.numel())) fail("mu_main is float32, one per super-group");
+  const at::Tensor out = a[5] == Py_None ? at::empty_like(total) : tensor(a[5]);
+  check(L.dq_restore(as<float>(ptr(total)), as<uint32_t>(ptr(pos)), as<float>(ptr(mu)), (uint32_t)number(a[3]), (uint32_t)J,
+                     (uint32_t)(pos.numel() / J), as<float>(ptr(out)), stream()));
+  return give(a[5], out);
+}
+// The check of sg_index alone, waited for: for calls that run on other streams than the current one.
+PyObject *py_check_index(PyObject *const *a, Py_ssize_t nargs) {  // sg_index, limit
+  DQ_ARGS(2)
+  const at::Tensor &index = tensor(a[0]);
+  if (index.numel()) {
+    const long long limit = (long long)number(a[1]);
+    const dq::Bound b{as<uint32_t>(ptr(index)), (uint32_t)index.numel(), (uint32_t)(limit < INT32_MAX ? limit : INT32_MAX)};
+    checked(&b, 1, [](void *) { return DQ_OK; });
+  }
+  Py_RETURN_NONE;
+}
+PyObject *py_init(PyObject *const *a, Py_ssize_t nargs) {  // path of libdq.so, DqError
+  DQ_ARGS(2)
+  const char *path = PyUnicode_AsUTF8(a[0]);
+  if (!path) throw Raised();
+  Py_INCREF(a[1]);
+  Py_XDECREF(g_error);
+  g_error = a[1];
+  void *h = dlopen(path, RTLD_NOW | RTLD_LOCAL);
+  if (!h) fail(std::string("cannot load ") + path + ": " + dlerror());
+#define X(name)                                                       \
+  L.name = reinterpret_cast<decltype(L.name)>(dlsym(h, #name));       \
+  if (!L.name) fail(std::string(path) + " has no " #name);
+  DQ_SYMBOLS(X)
+#undef X
+  Py_RETURN_NONE;
+}
+
+template <PyObject *(*F)(PyObject *const *, Py_ssize_t)>
+PyObject *guarded(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
+  try {
+    return F(args, nargs);
+  } catch (const Raised &) {
+  } catch (const std::exception &e) {
+    PyErr_SetString(PyExc_RuntimeError, e.what());
+  }
+  return nullptr;
+}
+#define M(name) {#name, (PyCFunction)(void (*)(void))guarded<py_##name>, METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {M(init), M(compress), M(dar_hop), M(decompress), M(decompress_restore), M(mx_compress), M(mx_dar_hop),
+                         M(mx_decompress), M(replay_run), M(replay_run_steps), M(sg_stats), M(stats_combine), M(allocate),
+                         M(reorder), M(reorder_mean), M(restore), M(check_index), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_dqpy", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__dqpy(void) { return PyModule_Create(&module); }

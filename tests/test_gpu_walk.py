@@ -1,0 +1,127 @@
+"""A replay run whole (one launch, every tile carried through all its hops) against the same replay run step
+by step, whose steps the parity tests hold against the oracle: same result, same messages of the last two
+steps -- at the edges of tiles, of the draws' batches and of the split over waves.  And the bounds
+check of super-group indices in front of a call."""
+import pytest
+import torch
+
+from paper_2602_08923_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+TOPO = {"ring": B.DQ_RING, "butterfly": B.DQ_BUTTERFLY, "chain": B.DQ_CHAIN}
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def gradients(n, n_sg, dtype, dev, seed):
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(seed)
+    scale = torch.exp(2.0 * torch.randn(n_sg, 1, generator=gen, device=dev)) * 1e-3
+    grads = []
+    for _ in range(n):
+        x = torch.randn(n_sg, 256, generator=gen, device=dev) * scale
+        x[::7, :32] = 0.0
+        x[::5, 16:48] *= -0.0
+        grads.append(x.reshape(-1).to(dtype))
+    return grads
+
+
+def whole_against_steps(rp, chunks):
+    for t in range(rp.n_steps):
+        rp.run_steps(t, 1)
+    torch.cuda.synchronize()
+    want = rp.out.clone()
+    msgs = {}
+    if chunks:
+        n = rp.ctx.n_workers
+        kept = [t for t in (n - 3, n - 2) if t >= 0]
+        msgs = {(t, b, c): rp.message(t, b, c) for t in kept for b in range(rp.desc.n_buckets) for c in range(chunks)}
+        saved = {k: v.clone() for k, v in msgs.items()}
+        for v in msgs.values():
+            v.fill_(0xA5)
+    rp.out.fill_(float("nan"))
+    rp.run()
+    torch.cuda.synchronize()
+    assert torch.equal(rp.out.view(torch.int32), want.view(torch.int32))
+    for k, v in msgs.items():
+        same = v == saved[k]
+        same[-15:] |= v[-15:] == 0xA5                      # padding bytes are never written
+        assert bool(same.all()), f"message of step, bucket, chunk {k}"
+
+
+CASES = [
+    # topology, workers, widths of the bucket(s), all_gather
+    ("ring", 2, [[1, 1, 0, 0]], False), ("ring", 3, [[3, 5, 4, 3]], True), ("ring", 5, [[20, 10, 4, 1], [0, 0, 0, 35]], False),
+    ("ring", 17, [[17, 40, 20, 8]], True), ("ring", 16, [[16, 60, 30, 6]], False), ("ring", 9, [[9, 9, 9, 0]], True),
+    ("chain", 2, [[0, 5, 0, 0]], True), ("chain", 4, [[6, 7, 9, 3]], False), ("chain", 33, [[5, 5, 5, 5]], True),
+    ("butterfly", 2, [[3, 2, 2, 1]], True), ("butterfly", 4, [[4, 12, 8, 0], [24, 0, 0, 0]], False),
+    ("butterfly", 8, [[10, 30, 20, 4]], True), ("butterfly", 32, [[32, 96, 30, 2]], False), ("butterfly", 64, [[0, 64, 64, 0]], True),
+]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("means", [False, True])
+@pytest.mark.parametrize("topology,n,widths,all_gather", CASES)
+def test_whole_replay_equals_its_steps(dev, topology, n, widths, all_gather, means, dtype):
+    J, nb = sum(widths[0]), len(widths)
+    grads = gradients(n, J * nb, dtype, dev, 100 * n + J)
+    ctx = B.Context(n, seed=n)
+    mu = None
+    if means:
+        mu = torch.stack([g.float().reshape(-1, 256).mean(dim=1) for g in grads]).mean(dim=0).contiguous()
+    rp = B.Replay(ctx, TOPO[topology], B.DQ_DYNAMIQ, grads, J, widths, n_buckets=nb, first_sg=2 ** 33 + 5, all_gather=all_gather, mu=mu)
+    whole_against_steps(rp, {"ring": n, "chain": 1, "butterfly": 0}[topology])
+
+
+@pytest.mark.parametrize("topology", ["ring", "butterfly"])
+@pytest.mark.parametrize("J", [8192, 66000])                # one tile per wave, and several waves' shares per chunk
+def test_whole_replay_on_original_tensors_over_the_whole_grid(dev, topology, J):
+    n = 4
+    grads = gradients(n, J, torch.bfloat16, dev, J)
+    widths = [[J // 4, J // 2, J // 4 - 600, 600]]
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(3)
+    origin = torch.randperm(J, generator=gen, device=dev).to(torch.int32)
+    mu = torch.randn(J, generator=gen, device=dev) * 1e-4
+    rp = B.Replay(B.Context(n, seed=2), TOPO[topology], B.DQ_DYNAMIQ, grads, J, widths, mu=mu, origin=origin, inputs_in_original_order=True)
+    whole_against_steps(rp, 0)
+
+
+@pytest.mark.parametrize("fmt", [B.DQ_MXFP8_E4M3, B.DQ_MXFP6_E3M2, B.DQ_MXFP4_E2M1])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("topology,n,J,nb,all_gather", [("ring", 2, 2, 1, False), ("ring", 5, 45, 2, True), ("chain", 7, 9, 1, False),
+                                                        ("chain", 3, 8, 1, True), ("butterfly", 2, 2, 3, True),
+                                                        ("butterfly", 16, 16 * 9, 2, False), ("ring", 4, 36000, 1, False)])
+def test_whole_mx_replay_equals_its_steps(dev, fmt, dtype, topology, n, J, nb, all_gather):
+    grads = gradients(n, J * nb, dtype, dev, J + n)
+    rp = B.Replay(B.Context(n), TOPO[topology], fmt, grads, J, n_buckets=nb, all_gather=all_gather)
+    whole_against_steps(rp, {"ring": n, "chain": 1, "butterfly": 0}[topology])
+
+
+@pytest.mark.parametrize("n_sg", [1, 4, 2049, 70001])
+def test_indices_out_of_bounds_are_refused_and_nothing_is_written(dev, n_sg):
+    ctx = B.Context(4, seed=1)
+    ch = B.make_chunk(0, [0, n_sg, 0])
+    x = gradients(1, n_sg, torch.bfloat16, dev, n_sg)[0]
+    good = torch.arange(n_sg - 1, -1, -1, dtype=torch.int32, device=dev)
+    want = ctx.dq_compress(x.reshape(-1, 256).flip(0).reshape(-1).contiguous(), ch, 1)
+    for at, value in ((0, n_sg), (n_sg - 1, -1)):
+        bad = good.clone()
+        bad[at] = value
+        out = torch.full_like(want, 7)
+        with pytest.raises(B.DqError, match="sg_index points outside"):
+            ctx.dq_compress(x, ch, 1, packed_out=out, sg_index=bad)
+        total = torch.full((n_sg * 256,), 7.0, device=dev)
+        with pytest.raises(B.DqError, match="holds every destination"):
+            ctx.dq_decompress_restore(want, ch, bad, total)
+        torch.cuda.synchronize()
+        assert bool((out == 7).all()) and bool((total == 7.0).all())
+    for _ in range(300):                                    # more calls than a workspace has slots
+        got = ctx.dq_compress(x, ch, 1, sg_index=good)
+    assert torch.equal(got, want)
