@@ -51,18 +51,14 @@ def simulated_allreduce(worker_grads, budget_bits, topology=B.DQ_RING, codec=B.D
         rp.run()
         return rp.out, {"replay_steps": rp.n_steps}
     dev = worker_grads[0].device
-    mu_all = torch.empty((n, n_sg), dtype=torch.float32, device=dev)
-    F_all = torch.empty((n, n_sg), dtype=torch.float32, device=dev)
-    for w, g in enumerate(worker_grads):
-        B.dq_sg_stats(g, mu_all[w], F_all[w])
-    mu, F = B.dq_stats_combine(mu_all, F_all)
+    mu, F = B.stats_of_workers(worker_grads)
     if not subtract_mean:
         mu = None
     counts = None
     if uniform_width is None:
         budget = int(math.floor(prep.code_bits(budget_bits) * J))
         widths, pos, counts = B.dq_allocate(F, J, budget, max_width=max_width)
-        by_width = [[int(v) for v in row[:4]] for row in counts.cpu().tolist()]
+        by_width = B.widths_of_buckets(counts)
     else:
         pos = torch.arange(J, dtype=torch.int32, device=dev).repeat(nb)
         row = [0, 0, 0, 0]

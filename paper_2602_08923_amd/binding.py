@@ -340,6 +340,26 @@ def dq_stats_combine(mu_all, F_all):
     return _native().stats_combine(mu_all, F_all)
 
 
+def stats_of_workers(tensors):
+    """dq_sg_stats of every worker's tensor and dq_stats_combine of the results: (mu, F) float32, the same bits.
+    Up to 256 workers in one launch."""
+    tensors = list(tensors)
+    if len(tensors) <= 256:
+        return _native().stats_all(tensors)
+    n_sg = tensors[0].numel() // 256
+    mu_all = torch.empty((len(tensors), n_sg), dtype=torch.float32, device=tensors[0].device)
+    F_all = torch.empty_like(mu_all)
+    for x, m, f in zip(tensors, mu_all.unbind(0), F_all.unbind(0)):
+        dq_sg_stats(x, m, f)
+    return dq_stats_combine(mu_all, F_all)
+
+
+def widths_of_buckets(counts):
+    """dq_allocate's counts [n_buckets, 5] on the host: [[#2-bit, #4-bit, #8-bit, #16-bit], ...] (waits for them)."""
+    v = _native().fetch(counts) if counts.numel() <= 1023 else counts.reshape(-1).cpu().tolist()
+    return [v[i:i + 4] for i in range(0, len(v), 5)]
+
+
 def dq_allocate(F, n_sg_per_bucket, max_code_bits, max_width=8):
     """F: float32 [n_buckets * n_sg_per_bucket] -> (widths uint8, pos int32 (holds uint32),
     counts int32 [n_buckets, 5] = #2-bit, #4-bit, #8-bit, #16-bit, threshold pattern)."""

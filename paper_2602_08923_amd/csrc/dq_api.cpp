@@ -8,7 +8,6 @@
 #include <string>
 #include <vector>
 
-#include "dq_bounds.h"
 #include "dq_device.h"
 
 namespace {
@@ -147,36 +146,27 @@ dq_status check_chunk(const dq_ctx *ctx, const dq_chunk *ch, uint32_t rank) {
   return DQ_OK;
 }
 
-}  // namespace
+// The level tables of one pair of level sets on one device: built and uploaded when the first context needs them, shared by all
+// contexts that use them, kept for the next one when the last is destroyed (building and uploading them took 80 us of a
+// context's 83, freeing them waited for the device) -- at most kIdleTables of them, the longest unused goes first.
+struct Tables {
+  double g4, g8;
+  int device;
+  uint32_t refs = 0;
+  uint64_t used = 0;
+  uint32_t *dev = nullptr;
+  dq::Params P;  // the fields that follow from the tables
+};
+constexpr size_t kIdleTables = 8;
+std::mutex g_tables_mutex;
+std::vector<Tables *> g_tables;
+uint64_t g_tables_clock = 0;
 
-dq_status dq::hip_status(hipError_t e) { return hip_ok(e) ? DQ_OK : DQ_EHIP; }
-
-extern "C" {
-
-const char *dq_status_str(dq_status s) {
-  switch (s) {
-    case DQ_OK: return "ok";
-    case DQ_EINVAL: return "invalid argument";
-    case DQ_EALIGN: return "pointer not 16-byte aligned";
-    case DQ_EUNSUPPORTED: return "unsupported configuration";
-    case DQ_EHIP: return "HIP error";
-  }
-  return "unknown";
-}
-
-const char *dq_last_hip_error(void) { return g_hip_error.c_str(); }
-
-dq_status dq_create(const dq_config *cfg, dq_ctx **out) {
-  if (!cfg || !out) return DQ_EINVAL;
-  *out = nullptr;
-  if (cfg->n_workers < 1 || cfg->n_workers > 8192) return DQ_EINVAL;
-  if (!(cfg->g4 > 1.0) || !(cfg->g8 > 1.0) || !isfinite(cfg->g4) || !isfinite(cfg->g8)) return DQ_EINVAL;
-
-  const int Rs[3] = {1, 7, 127};
-  const double gs[3] = {2.0, cfg->g4, cfg->g8};
-  std::vector<uint32_t> blob;
-  dq::Params P;
+// Builds the table blob and fills the fields of P that describe it.
+dq_status build_tables(double g4, double g8, dq::Params &P, std::vector<uint32_t> &blob) {
   memset(&P, 0, sizeof(P));
+  const int Rs[3] = {1, 7, 127};
+  const double gs[3] = {2.0, g4, g8};
   // Blob layout: the fixed-size tables first, on the constant offsets that dq_device.h declares
   // ([reciprocals][2-bit decode][4-bit decode][4-bit {T,D}][8-bit decode][8-bit {T,D}]), then the
   // two search tables, whose size follows the level sets.
@@ -259,45 +249,157 @@ dq_status dq_create(const dq_config *cfg, dq_ctx **out) {
       memcpy(&P.magic[wi], &bits, 4);
     }
   }
-  if (blob.size() * 4 > 60 * 1024) return DQ_EUNSUPPORTED;
+  // 64 KB of LDS with the parked draws, less the 3,200 bytes by which the level entries outgrew plain {T, D} pairs
+  if (blob.size() * 4 > 60 * 1024 + 3200) return DQ_EUNSUPPORTED;
+  P.blob_dwords = (uint32_t)blob.size();
+  return DQ_OK;
+}
 
-  dq_ctx *ctx = new (std::nothrow) dq_ctx;
-  if (!ctx) return DQ_EINVAL;
-  ctx->cfg = *cfg;
-  ctx->blob_dev = nullptr;
-  ctx->have_events = false;
-  for (int i = 0; i < 2; ++i) ctx->have_event[i] = false;
-  ctx->static_stage = nullptr;
+// Before anything is created: the same refusals whether or not the tables exist already.
+dq_status take_tables(double g4, double g8, int device, Tables **out) {
+  std::lock_guard<std::mutex> lock(g_tables_mutex);
+  for (Tables *t : g_tables)
+    if (t->g4 == g4 && t->g8 == g8 && t->device == device) {
+      ++t->refs;
+      *out = t;
+      return DQ_OK;
+    }
+  Tables *t = new (std::nothrow) Tables;
+  if (!t) return DQ_EINVAL;
+  t->g4 = g4;
+  t->g8 = g8;
+  t->device = device;
+  std::vector<uint32_t> blob;
+  dq_status st = build_tables(g4, g8, t->P, blob);
+  if (st == DQ_OK && (!hip_ok(hipMalloc((void **)&t->dev, blob.size() * 4)) ||
+                      !hip_ok(hipMemcpy(t->dev, blob.data(), blob.size() * 4, hipMemcpyHostToDevice))))
+    st = DQ_EHIP;
+  if (st != DQ_OK) {
+    if (t->dev) (void)hipFree(t->dev);
+    delete t;
+    return st;
+  }
+  t->P.blob = t->dev;
+  t->refs = 1;
+  g_tables.push_back(t);
+  *out = t;
+  return DQ_OK;
+}
+void return_tables(Tables *t) {
+  Tables *gone = nullptr;
+  {
+    std::lock_guard<std::mutex> lock(g_tables_mutex);
+    t->used = ++g_tables_clock;
+    if (--t->refs != 0) return;
+    size_t idle = 0, oldest = 0;
+    for (size_t i = 0; i < g_tables.size(); ++i)
+      if (g_tables[i]->refs == 0) {
+        if (idle == 0 || g_tables[i]->used < g_tables[oldest]->used) oldest = i;
+        ++idle;
+      }
+    if (idle <= kIdleTables) return;
+    gone = g_tables[oldest];
+    g_tables.erase(g_tables.begin() + oldest);
+  }
+  (void)hipFree(gone->dev);
+  delete gone;
+}
+
+// What does not change from context to context on a device.
+struct DeviceFacts {
+  bool known = false;
+  uint32_t n_cu = 0;
+  void *static_stage = nullptr;
+};
+std::mutex g_facts_mutex;
+DeviceFacts g_facts[kMaxDevices];
+dq_status learn_device(int device, DeviceFacts *out) {
+  std::lock_guard<std::mutex> lock(g_facts_mutex);
+  const bool keep = device >= 0 && device < kMaxDevices;
+  if (keep && g_facts[device].known) {
+    *out = g_facts[device];
+    return DQ_OK;
+  }
+  DeviceFacts f;
   hipDeviceProp_t prop;
   hipError_t sym_err = hipSuccess;
-  if (!hip_ok(hipGetDevice(&ctx->device)) || !hip_ok(hipGetDeviceProperties(&prop, ctx->device)) ||
-      !hip_ok(hipMalloc(&ctx->blob_dev, blob.size() * 4)) ||
-      !hip_ok(hipMemcpy(ctx->blob_dev, blob.data(), blob.size() * 4, hipMemcpyHostToDevice)) ||
-      ((ctx->static_stage = resolve_scratch(ctx->device, &sym_err)), !hip_ok(sym_err)) || !make_events(ctx)) {
-    if (ctx->blob_dev) (void)hipFree(ctx->blob_dev);
-    drop_events(ctx);
-    delete ctx;
+  if (!hip_ok(hipGetDeviceProperties(&prop, device)) || ((f.static_stage = resolve_scratch(device, &sym_err)), !hip_ok(sym_err)))
+    return DQ_EHIP;
+  f.n_cu = (uint32_t)prop.multiProcessorCount;
+  // the kernels address their tables from LDS byte 0: true as long as they have no static LDS
+  size_t static_lds = 0;
+  if (!hip_ok(dq::static_lds_bytes(&static_lds))) return DQ_EHIP;
+  if (static_lds != 0) {
+    g_hip_error = "codec kernels were built with static LDS: table addresses would be off";
     return DQ_EHIP;
   }
-  {  // the kernels address their tables from LDS byte 0: true as long as they have no static LDS
-    size_t static_lds = 0;
-    if (!hip_ok(dq::static_lds_bytes(&static_lds)) || static_lds != 0) {
-      if (static_lds != 0) g_hip_error = "codec kernels were built with static LDS: table addresses would be off";
-      (void)hipFree(ctx->blob_dev);
-      drop_events(ctx);
-      delete ctx;
-      return DQ_EHIP;
-    }
+  f.known = true;
+  if (keep) g_facts[device] = f;
+  *out = f;
+  return DQ_OK;
+}
+
+}  // namespace
+
+dq_status dq::hip_status(hipError_t e) { return hip_ok(e) ? DQ_OK : DQ_EHIP; }
+
+extern "C" {
+
+const char *dq_status_str(dq_status s) {
+  switch (s) {
+    case DQ_OK: return "ok";
+    case DQ_EINVAL: return "invalid argument";
+    case DQ_EALIGN: return "pointer not 16-byte aligned";
+    case DQ_EUNSUPPORTED: return "unsupported configuration";
+    case DQ_EHIP: return "HIP error";
   }
-  ctx->n_cu = (uint32_t)prop.multiProcessorCount;
+  return "unknown";
+}
+
+const char *dq_last_hip_error(void) { return g_hip_error.c_str(); }
+
+dq_status dq_create(const dq_config *cfg, dq_ctx **out) {
+  if (!cfg || !out) return DQ_EINVAL;
+  *out = nullptr;
+  if (cfg->n_workers < 1 || cfg->n_workers > 8192) return DQ_EINVAL;
+  if (!(cfg->g4 > 1.0) || !(cfg->g8 > 1.0) || !isfinite(cfg->g4) || !isfinite(cfg->g8)) return DQ_EINVAL;
+  int device = -1;
+  if (hipGetDevice(&device) != hipSuccess) device = -1;  // level sets are refused without a GPU too
+  {
+    std::vector<uint32_t> blob;
+    dq::Params unused;
+    dq_status st;
+    if (device < 0 && (st = build_tables(cfg->g4, cfg->g8, unused, blob)) != DQ_OK) return st;
+  }
+  Tables *tables = nullptr;
+  dq_status st = take_tables(cfg->g4, cfg->g8, device, &tables);
+  if (st != DQ_OK) return st;
+  DeviceFacts facts;
+  dq_ctx *ctx = new (std::nothrow) dq_ctx;
+  if (!ctx) {
+    return_tables(tables);
+    return DQ_EINVAL;
+  }
+  ctx->cfg = *cfg;
+  ctx->device = device;
+  ctx->tables = tables;
+  ctx->have_events = false;
+  for (int i = 0; i < 2; ++i) ctx->have_event[i] = false;
+  if ((st = learn_device(device, &facts)) != DQ_OK || !make_events(ctx)) {
+    drop_events(ctx);
+    delete ctx;
+    return_tables(tables);
+    return DQ_EHIP;
+  }
+  ctx->static_stage = facts.static_stage;
+  ctx->n_cu = facts.n_cu;
   // five blocks of four waves per CU: measured against 4, 6 and 7 (fewer waves hide too little of each other's
   // waits, more of them contend at the start of a short launch and pay the per-wave set-up more often)
   uint32_t per_cu = 5;
   const char *env = getenv("DQ_BLOCKS_PER_CU");  // tuning / test knob, read once per context
   if (env && atoi(env) >= 1 && atoi(env) <= 64) per_cu = (uint32_t)atoi(env);
   ctx->grid_blocks = ctx->n_cu * per_cu;
-  P.blob = ctx->blob_dev;
-  P.blob_dwords = (uint32_t)blob.size();
+  dq::Params P = tables->P;
   P.key0 = (uint32_t)cfg->seed;
   P.key1 = (uint32_t)(cfg->seed >> 32);
   P.round = cfg->round;
@@ -311,17 +413,15 @@ dq_status dq_create(const dq_config *cfg, dq_ctx **out) {
   P.inv_n512 = P.inv_n * (1.0f / 512.0f);
   P.s_n = P.inv_n * (1.0f / 256.0f);
   ctx->params = P;
-  dq::bounds_context(1);
   *out = ctx;
   return DQ_OK;
 }
 
 void dq_destroy(dq_ctx *ctx) {
   if (!ctx) return;
-  if (ctx->blob_dev) (void)hipFree(ctx->blob_dev);
+  return_tables(static_cast<Tables *>(ctx->tables));
   drop_events(ctx);
   delete ctx;
-  dq::bounds_context(-1);
 }
 
 dq_status dq_stream_probe(dq_ctx *ctx, const void *in, size_t in_bytes, void *out, size_t out_bytes, void *hip_stream) {

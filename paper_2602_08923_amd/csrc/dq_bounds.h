@@ -9,8 +9,8 @@ struct Bound {
   const uint32_t *index;  // device
   uint32_t n, limit;      // every index must be below limit
 };
+constexpr uint32_t kFetchWords = 1023;
 const uint32_t *armed_guard();     // this thread's armed verdict (device), or null
-void bounds_context(int change);   // a context was made (1) or destroyed (-1)
 }  // namespace dq
 
 extern "C" {
@@ -19,4 +19,10 @@ extern "C" {
 // if a bit is set.
 dq_status dqx_bounds_begin(const dq::Bound *bounds, int n_bounds, void *hip_stream);
 dq_status dqx_bounds_end(void *hip_stream, int *out_of_bounds);
+// n <= kFetchWords words of device memory as the stream's work so far leaves them (waits for it): a copy of a few words by
+// hipMemcpy costs 13 us on top of the wait.
+dq_status dqx_fetch(const uint32_t *src, uint32_t n, uint32_t *dst_host, void *hip_stream);
+// dq_sg_stats of n_workers (at most 256) tensors and dq_stats_combine in one launch.
+dq_status dqx_stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dtype, uint64_t n_sg, float *mu, float *F,
+                        void *hip_stream);
 }

@@ -1,9 +1,13 @@
-// Bounds check of super-group indices for the language binding, which knows how large the tensor is that
-// the indices point into (the C ABI does not).  The check is one small launch in front of the call on the same
+// What the Python binding needs beside the C ABI: a bounds check of super-group indices, and a few words brought to the host.
+//
+// The bounds check: the binding, unlike the C ABI, knows how large the tensor is that
+// the indices point into.  The check is one small launch in front of the call on the same
 // stream; the call's kernel starts by reading the verdict and does nothing if an index is out of bounds,
 // so the host can enqueue it without waiting and only then look at the verdict, which arrives in pinned host memory
 // while the call runs.  (Reductions on the stream, each waited for on the host before the call was enqueued, took 38 us
 // per index and left the GPU idle between calls.)
+#include <string.h>
+
 #include <mutex>
 #include <vector>
 
@@ -24,10 +28,10 @@ struct Workspace {
   int device = -1;
 };
 
-// Workspaces at rest; as many exist as calls have ever been in their check at the same time.  Freed with the last context.
+// Workspaces at rest (8 KB each), one for every call that was ever waiting at the same time as others, kIdle of them at most.
+constexpr size_t kIdle = 8;
 std::mutex g_mutex;
 std::vector<Workspace *> g_idle;
-uint32_t g_contexts = 0;
 
 thread_local Workspace *t_armed = nullptr;
 thread_local const uint32_t *t_guard = nullptr;
@@ -49,6 +53,14 @@ __global__ void __launch_bounds__(256) k_bounds(Bound a, Bound b, Slot *slot, ui
   __hip_atomic_store(host, 4 * call + verdict, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// A few words to pinned host memory, then the call number in front of them.
+__global__ void __launch_bounds__(256) k_fetch(const uint32_t *src, uint32_t n, uint32_t *host, uint32_t call) {
+  for (uint32_t i = threadIdx.x; i < n; i += 256) __hip_atomic_store(host + 1 + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(host, 4 * call, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 Workspace *take(hipError_t *err) {
   int device = -1;
   if ((*err = hipGetDevice(&device)) != hipSuccess) return nullptr;
@@ -65,7 +77,7 @@ Workspace *take(hipError_t *err) {
   w->device = device;
   if ((*err = hipMalloc((void **)&w->slots, kSlots * sizeof(Slot))) != hipSuccess ||
       (*err = hipMemset(w->slots, 0, kSlots * sizeof(Slot))) != hipSuccess ||
-      (*err = hipHostMalloc((void **)&w->host, 64, hipHostMallocDefault)) != hipSuccess) {
+      (*err = hipHostMalloc((void **)&w->host, 4 * (1 + kFetchWords), hipHostMallocDefault)) != hipSuccess) {
     if (w->slots) (void)hipFree(w->slots);
     delete w;
     return nullptr;
@@ -84,19 +96,35 @@ void drop(Workspace *w) {
 
 const uint32_t *armed_guard() { return t_guard; }
 
-void bounds_context(int change) {
-  std::vector<Workspace *> gone;
-  {
-    std::lock_guard<std::mutex> lock(g_mutex);
-    g_contexts += (uint32_t)change;
-    if (g_contexts == 0) gone.swap(g_idle);
-  }
-  for (Workspace *w : gone) drop(w);
-}
-
 }  // namespace dq
 
 extern "C" {
+
+static hipError_t await_call(dq::Workspace *w, void *hip_stream, uint32_t *word_out) {
+  volatile uint32_t *word = w->host;
+  hipError_t e = hipSuccess;
+  for (uint32_t spin = 0;; ++spin) {
+    *word_out = __atomic_load_n(word, __ATOMIC_ACQUIRE);
+    if (*word_out >> 2 == (w->calls & 0x3FFFFFFFu)) break;
+    if (spin > 200000) {  // long work ahead on the stream, or an error there: wait in the runtime
+      e = hipStreamSynchronize((hipStream_t)hip_stream);
+      *word_out = __atomic_load_n(word, __ATOMIC_ACQUIRE);
+      break;
+    }
+    __builtin_ia32_pause();
+  }
+  return e;
+}
+static void give_back(dq::Workspace *w) {
+  {
+    std::lock_guard<std::mutex> lock(dq::g_mutex);
+    if (dq::g_idle.size() < dq::kIdle) {
+      dq::g_idle.push_back(w);
+      return;
+    }
+  }
+  dq::drop(w);
+}
 
 dq_status dqx_bounds_begin(const dq::Bound *bounds, int n_bounds, void *hip_stream) {
   hipError_t e = hipSuccess;
@@ -112,8 +140,7 @@ dq_status dqx_bounds_begin(const dq::Bound *bounds, int n_bounds, void *hip_stre
   hipLaunchKernelGGL(dq::k_bounds, dim3(blocks ? blocks : 1), dim3(256), 0, (hipStream_t)hip_stream, a, b, slot, w->host, w->calls);
   e = hipGetLastError();
   if (e != hipSuccess) {
-    std::lock_guard<std::mutex> lock(dq::g_mutex);
-    dq::g_idle.push_back(w);
+    give_back(w);
     return dq::hip_status(e);
   }
   dq::t_armed = w;
@@ -126,24 +153,25 @@ dq_status dqx_bounds_end(void *hip_stream, int *out_of_bounds) {
   dq::t_armed = nullptr;
   dq::t_guard = nullptr;
   if (!w) return DQ_EINVAL;
-  volatile uint32_t *word = w->host;
-  uint32_t verdict = 0;
+  uint32_t word = 0;
+  const hipError_t e = await_call(w, hip_stream, &word);
+  *out_of_bounds = (int)(word & 3u);
+  give_back(w);
+  return dq::hip_status(e);
+}
+
+dq_status dqx_fetch(const uint32_t *src, uint32_t n, uint32_t *dst, void *hip_stream) {
+  if (n > dq::kFetchWords) return DQ_EUNSUPPORTED;
   hipError_t e = hipSuccess;
-  for (uint32_t spin = 0;; ++spin) {
-    verdict = __atomic_load_n(word, __ATOMIC_ACQUIRE);
-    if (verdict >> 2 == (w->calls & 0x3FFFFFFFu)) break;
-    if (spin > 200000) {  // long work ahead on the stream, or an error there: wait in the runtime
-      e = hipStreamSynchronize((hipStream_t)hip_stream);
-      verdict = __atomic_load_n(word, __ATOMIC_ACQUIRE);
-      break;
-    }
-    __builtin_ia32_pause();
-  }
-  *out_of_bounds = (int)(verdict & 3u);
-  {
-    std::lock_guard<std::mutex> lock(dq::g_mutex);
-    dq::g_idle.push_back(w);
-  }
+  dq::Workspace *w = dq::take(&e);
+  if (!w) return dq::hip_status(e);
+  ++w->calls;
+  hipLaunchKernelGGL(dq::k_fetch, dim3(1), dim3(256), 0, (hipStream_t)hip_stream, src, n, w->host, w->calls);
+  e = hipGetLastError();
+  uint32_t word = 0;
+  if (e == hipSuccess) e = await_call(w, hip_stream, &word);
+  if (e == hipSuccess) memcpy(dst, w->host + 1, 4 * (size_t)n);
+  give_back(w);
   return dq::hip_status(e);
 }
 

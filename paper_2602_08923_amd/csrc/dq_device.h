@@ -96,12 +96,14 @@ struct Walk {
   uint32_t n_paths;
   uint32_t widths;           // which widths some chunk has (bit k: 2 << k bits)
   uint32_t blocks, waves;    // grid, waves per block
+  uint32_t by_cost;          // shares of equal cost (0: of equal tile counts)
 };
 struct WalkShare {
   uint32_t path, tile;
 };
 constexpr uint32_t kStackCoded = 1280, kStackRaw = 2048;  // bytes of a pending message per wave: codes and scale, or raw bf16
-bool split_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths_host, Walk *W, std::vector<WalkShare> *shares);
+bool grid_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths_host, Walk *W);  // false: no launch fits
+void split_walk(const WalkPath *paths_host, const Walk &W, std::vector<WalkShare> *shares);
 hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W,
                        const Params &P, hipStream_t stream);
 
@@ -157,7 +159,7 @@ hipError_t launch_mx_walk(dq_codec fmt, dq_dtype dtype, bool tree, const MxWalk 
 struct dq_ctx {
   dq_config cfg;
   dq::Params params;
-  uint32_t *blob_dev;
+  void *tables;          // the level tables it shares with other contexts (dq_api.cpp)
   uint32_t n_cu;
   uint32_t grid_blocks;  // n_cu x blocks per CU (5, or the DQ_BLOCKS_PER_CU environment variable at dq_create)
   int device;

@@ -10,6 +10,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <string>
+#include <vector>
 
 #include "dq_bounds.h"
 
@@ -22,7 +23,7 @@ PyObject *g_error = nullptr;  // binding.DqError
   X(dq_packed_bytes) X(dq_compress) X(dq_dar_hop) X(dq_decompress) X(dq_decompress_restore) X(dq_mx_packed_bytes)       \
   X(dq_mx_compress) X(dq_mx_dar_hop) X(dq_mx_decompress) X(dq_replay_run) X(dq_replay_run_steps) X(dq_sg_stats) X(dq_stats_combine) \
   X(dq_allocate) X(dq_reorder) X(dq_reorder_mean) X(dq_restore) X(dq_status_str) X(dq_last_hip_error) X(dqx_bounds_begin) \
-  X(dqx_bounds_end)
+  X(dqx_bounds_end) X(dqx_fetch) X(dqx_stats_all)
 struct Lib {
 #define X(name) decltype(&::name) name = nullptr;
   DQ_SYMBOLS(X)
@@ -374,6 +375,40 @@ PyObject *py_check_index(PyObject *const *a, Py_ssize_t nargs) {  // sg_index, l
   }
   Py_RETURN_NONE;
 }
+PyObject *py_stats_all(PyObject *const *a, Py_ssize_t nargs) {  // list of tensors
+  DQ_ARGS(1)
+  const Py_ssize_t n = PyList_Check(a[0]) ? PyList_GET_SIZE(a[0]) : 0;
+  if (n == 0) fail("a list of the workers' tensors");
+  const at::Tensor &x = tensor(PyList_GET_ITEM(a[0], 0));
+  if (x.numel() % 256) fail("tensor length must be a multiple of 256");
+  std::vector<const void *> p((size_t)n);
+  for (Py_ssize_t w = 0; w < n; ++w) {
+    const at::Tensor &t = tensor(PyList_GET_ITEM(a[0], w));
+    if (t.numel() != x.numel() || t.scalar_type() != x.scalar_type()) fail("the workers' tensors have one length and type");
+    p[(size_t)w] = ptr(t);
+  }
+  const at::Tensor mu = make(x.numel() / 256, at::kFloat, x), F = make(x.numel() / 256, at::kFloat, x);
+  check(L.dqx_stats_all(p.data(), (uint32_t)n, local_dtype(x), x.numel() / 256, as<float>(ptr(mu)), as<float>(ptr(F)), stream()));
+  return pair(wrap(mu), wrap(F));
+}
+PyObject *py_fetch(PyObject *const *a, Py_ssize_t nargs) {  // int32 tensor of at most kFetchWords values -> list of its values
+  DQ_ARGS(1)
+  const at::Tensor &t = tensor(a[0]);
+  if (t.scalar_type() != at::kInt || t.numel() > dq::kFetchWords) fail("fetch takes a small int32 tensor");
+  int32_t v[dq::kFetchWords];
+  const uint32_t *p = as<uint32_t>(ptr(t));
+  const uint32_t n = (uint32_t)t.numel();
+  void *s = stream();
+  dq_status st;
+  Py_BEGIN_ALLOW_THREADS
+  st = L.dqx_fetch(p, n, reinterpret_cast<uint32_t *>(v), s);
+  Py_END_ALLOW_THREADS
+  check(st);
+  PyObject *list = PyList_New(n);
+  if (!list) throw Raised();
+  for (uint32_t i = 0; i < n; ++i) PyList_SET_ITEM(list, i, PyLong_FromLong(v[i]));
+  return list;
+}
 PyObject *py_init(PyObject *const *a, Py_ssize_t nargs) {  // path of libdq.so, DqError
   DQ_ARGS(2)
   const char *path = PyUnicode_AsUTF8(a[0]);
@@ -404,7 +439,7 @@ PyObject *guarded(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
 #define M(name) {#name, (PyCFunction)(void (*)(void))guarded<py_##name>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {M(init), M(compress), M(dar_hop), M(decompress), M(decompress_restore), M(mx_compress), M(mx_dar_hop),
                          M(mx_decompress), M(replay_run), M(replay_run_steps), M(sg_stats), M(stats_combine), M(allocate),
-                         M(reorder), M(reorder_mean), M(restore), M(check_index), {nullptr, nullptr, 0, nullptr}};
+                         M(reorder), M(reorder_mean), M(restore), M(check_index), M(stats_all), M(fetch), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_dqpy", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -6,6 +6,7 @@
 // all (worker, chunk) jobs of that step; the job tables are built once, here, on the host.
 #include <string.h>
 
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -132,7 +133,7 @@ void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, 
   const uint32_t levels = w.log_n > 1 ? w.log_n - 1 : 1;
   w.stack_bytes = levels * (raw ? dq::kStackRaw : dq::kStackCoded);
   if (w.stack_bytes < 2048) w.stack_bytes = 2048;
-  plan->walk = dq::split_walk(ctx->params, plan->tree, ctx->n_cu, plan->paths.data(), &w, &plan->shares);
+  plan->walk = dq::grid_walk(ctx->params, plan->tree, ctx->n_cu, plan->paths.data(), &w);
   if (!plan->walk) {
     plan->paths.clear();
     return;
@@ -142,7 +143,7 @@ void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, 
   *off += plan->paths.size() * sizeof(dq::WalkPath);
   *off = align_up(*off, 256);
   plan->shares_off = *off;
-  *off += plan->shares.size() * sizeof(dq::WalkShare);
+  *off += ((size_t)w.blocks * w.waves + 1) * sizeof(dq::WalkShare);
   *off = align_up(*off, 256);
   plan->grads_off = *off;
   *off += (size_t)n * sizeof(void *);
@@ -260,6 +261,11 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
 
   size_t off = 0;  // running scratch offset (job tables are appended at the end)
   plan->steps.clear();
+  const bool sizes_only = base == nullptr;
+  auto add = [&](Launch &L, const HostJob &j) {
+    ++L.n_jobs;
+    if (!sizes_only) L.jobs.push_back(j);
+  };
 
   if (d->topology == DQ_CHAIN || d->topology == DQ_RING) {
     // two message sets (ping-pong), each with one slot per (bucket, chunk)
@@ -294,7 +300,7 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
           void *o = t == n - 1 ? (void *)out_ptr(b, c) : (void *)(msg[t & 1] + slot[i]);
           HostJob j = mk(ci[i], in, local, true, o, w);
           if (t == n - 1 && !d->all_gather) j = finish(j, ci[i], b);
-          L.jobs.push_back(j);
+          add(L, j);
         }
       st.launches.push_back(std::move(L));
       plan->steps.push_back(std::move(st));
@@ -349,13 +355,13 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
             const ChunkInfo &x = ci[(size_t)b * n + c];
             const uint8_t *in = k == 1 ? nullptr : msg_ptr(k - 1, b, w, c);
             const void *local = k <= 2 ? grad_ptr(w, b, c) : (const void *)acc_ptr(w, b, c);
-            send.jobs.push_back(mk(x, in, local, k <= 2, msg_ptr(k, b, partner, c), w));
+            add(send, mk(x, in, local, k <= 2, msg_ptr(k, b, partner, c), w));
           }
           if (k >= 2)
             for (uint32_t c = klo; c < klo + half; ++c) {
               const ChunkInfo &x = ci[(size_t)b * n + c];
               const void *local = k == 2 ? grad_ptr(w, b, c) : (const void *)acc_ptr(w, b, c);
-              keep.jobs.push_back(mk(x, msg_ptr(k - 1, b, w, c), local, k == 2, acc_ptr(w, b, c), w));
+              add(keep, mk(x, msg_ptr(k - 1, b, w, c), local, k == 2, acc_ptr(w, b, c), w));
             }
         }
       st.launches.push_back(std::move(send));
@@ -373,7 +379,7 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
         const void *local = Lg == 1 ? grad_ptr(w, b, w) : (const void *)acc_ptr(w, b, w);
         HostJob j = mk(x, msg_ptr(Lg, b, w, w), local, Lg == 1, out_ptr(b, w), w);
         if (!d->all_gather) j = finish(j, x, b);
-        fin.jobs.push_back(j);
+        add(fin, j);
       }
     st.launches.push_back(std::move(fin));
     plan->steps.push_back(std::move(st));
@@ -403,8 +409,8 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
       for (uint32_t c = 0; c < n_chunks; ++c) {
         const size_t i = (size_t)b * n_chunks + c;
         const uint32_t sink = d->topology == DQ_CHAIN ? n - 1 : (d->topology == DQ_RING ? (c + n - 1) % n : c);
-        comp.jobs.push_back(mk(ci[i], nullptr, out_ptr(b, c), false, ag + slot[i], sink));
-        dec.jobs.push_back(finish(mk(ci[i], ag + slot[i], nullptr, false, out_ptr(b, c), sink), ci[i], b));
+        add(comp, mk(ci[i], nullptr, out_ptr(b, c), false, ag + slot[i], sink));
+        add(dec, finish(mk(ci[i], ag + slot[i], nullptr, false, out_ptr(b, c), sink), ci[i], b));
       }
     sc.launches.push_back(std::move(comp));
     sd.launches.push_back(std::move(dec));
@@ -420,8 +426,7 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
     for (Launch &L : st.launches) {
       off = align_up(off, 256);
       L.table_off = off;
-      L.n_jobs = (uint32_t)L.jobs.size();
-      off += L.jobs.size() * (mx ? sizeof(dq::MxJob) : sizeof(dq::Job));
+      off += (size_t)L.n_jobs * (mx ? sizeof(dq::MxJob) : sizeof(dq::Job));
       for (const HostJob &j : L.jobs) {
         if (j.src) L.gather = true;
         const uint32_t tiles = (j.n_sg[0] + 3) / 4 + (j.n_sg[1] + 3) / 4 + (j.n_sg[2] + 3) / 4 + (j.n_sg[3] + 3) / 4;
@@ -437,6 +442,49 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
 }
 
 }  // namespace
+
+// Pieces of scratch, in the order of their offsets, gathered and sent to the device in few copies: a copy waits for the
+// device, 13 us or more each, and a replay of 8 workers has a dozen tables.
+class Upload {
+ public:
+  explicit Upload(uint8_t *scratch) : scratch_(scratch) {}
+  void put(size_t off, const void *src, size_t bytes) {
+    if (bytes == 0) return;
+    if (!buf_.empty() && (off < first_ + buf_.size() || off - first_ + bytes > kMost)) send();
+    if (buf_.empty()) first_ = off;
+    buf_.resize(off - first_ + bytes);  // what lies between two pieces is padding
+    memcpy(buf_.data() + (off - first_), src, bytes);
+  }
+  dq_status finish() {
+    send();
+    return status_;
+  }
+
+ private:
+  static constexpr size_t kMost = 16u << 20, kPinned = 256u << 10;
+  void send() {
+    if (!buf_.empty() && status_ == DQ_OK) status_ = copy();
+    buf_.clear();
+  }
+  dq_status copy() {
+    // from pinned memory a copy of tens of KB takes half the time; one staging buffer serves all threads in turn
+    static std::mutex mutex;
+    static uint8_t *pinned = nullptr;
+    if (buf_.size() <= kPinned) {
+      std::lock_guard<std::mutex> lock(mutex);
+      if (pinned || hipHostMalloc((void **)&pinned, kPinned, hipHostMallocPortable) == hipSuccess) {
+        memcpy(pinned, buf_.data(), buf_.size());
+        return dq::hip_status(hipMemcpy(scratch_ + first_, pinned, buf_.size(), hipMemcpyHostToDevice));
+      }
+      pinned = nullptr;
+    }
+    return dq::hip_status(hipMemcpy(scratch_ + first_, buf_.data(), buf_.size(), hipMemcpyHostToDevice));
+  }
+  uint8_t *scratch_;
+  size_t first_ = 0;
+  std::vector<uint8_t> buf_;
+  dq_status status_ = DQ_OK;
+};
 
 struct dq_replay {
   dq_ctx *ctx;
@@ -480,33 +528,29 @@ dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *
     return st;
   }
   const bool mx = desc->codec != DQ_DYNAMIQ;
-  if (r->plan.walk) {
-    Plan &p = r->plan;
-    const size_t n_workers = ctx->cfg.n_workers;
-    hipError_t e = hipMemcpy(r->scratch + p.grads_off, worker_grads, n_workers * sizeof(void *), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !mx)
-      e = hipMemcpy(r->scratch + p.paths_off, p.paths.data(), p.paths.size() * sizeof(dq::WalkPath), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !mx)
-      e = hipMemcpy(r->scratch + p.shares_off, p.shares.data(), p.shares.size() * sizeof(dq::WalkShare), hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-      delete r;
-      return dq::hip_status(e);
+  Upload up(r->scratch);
+  Plan &p = r->plan;
+  if (p.walk) {  // in the order of their offsets
+    if (!mx) {
+      dq::split_walk(p.paths.data(), p.w, &p.shares);
+      up.put(p.paths_off, p.paths.data(), p.paths.size() * sizeof(dq::WalkPath));
+      up.put(p.shares_off, p.shares.data(), p.shares.size() * sizeof(dq::WalkShare));
     }
+    up.put(p.grads_off, worker_grads, (size_t)ctx->cfg.n_workers * sizeof(void *));
     p.w.grads = p.mx.grads = reinterpret_cast<const void *const *>(r->scratch + p.grads_off);
     std::vector<dq::WalkPath>().swap(p.paths);
     std::vector<dq::WalkShare>().swap(p.shares);
   }
-  for (Step &s : r->plan.steps)
+  for (Step &s : p.steps)
     for (Launch &L : s.launches) {
       if (L.jobs.empty()) continue;
-      hipError_t e;
       if (mx) {
         std::vector<dq::MxJob> t(L.jobs.size());
         for (size_t i = 0; i < t.size(); ++i) {
           const HostJob &j = L.jobs[i];
           t[i] = dq::MxJob{j.in, j.local, j.out, ((uint64_t)j.n_sg[0] + j.n_sg[1] + j.n_sg[2] + j.n_sg[3]) * 256};
         }
-        e = hipMemcpy(r->scratch + L.table_off, t.data(), t.size() * sizeof(dq::MxJob), hipMemcpyHostToDevice);
+        up.put(L.table_off, t.data(), t.size() * sizeof(dq::MxJob));
       } else {
         std::vector<dq::Job> t(L.jobs.size());
         for (size_t i = 0; i < t.size(); ++i) {
@@ -516,14 +560,14 @@ dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *
           t[i].dest = j.dest;
           t[i].back = j.back;
         }
-        e = hipMemcpy(r->scratch + L.table_off, t.data(), t.size() * sizeof(dq::Job), hipMemcpyHostToDevice);
-      }
-      if (e != hipSuccess) {
-        delete r;
-        return dq::hip_status(e);
+        up.put(L.table_off, t.data(), t.size() * sizeof(dq::Job));
       }
       std::vector<HostJob>().swap(L.jobs);
     }
+  if ((st = up.finish()) != DQ_OK) {
+    delete r;
+    return st;
+  }
   *plan_out = r;
   return DQ_OK;
 }

@@ -387,20 +387,19 @@ hipError_t go_walk(const WalkPath *paths, const WalkShare *shares, const Walk &W
 
 }  // namespace
 
-// The grid, and where every wave's share begins: equal shares of the tiles' cost in path order.  A tile's cost by
+// The grid (grid_walk), and where every wave's share begins (split_walk): equal shares of the tiles' cost in path order.  A tile's cost by
 // width was chosen by measurement (2-bit tiles need no search; 8-bit ones collide more in LDS): with equal costs the
 // chunks of one width finish early, 1150 us instead of 880 for eight 25 MB buckets through 16 workers' recursive
 // halving.  With less than two tiles per wave the count decides: a wave with one tile more takes twice as long whatever its width.
-bool split_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W, std::vector<WalkShare> *shares) {
-  static const uint32_t kCosts[2][4] = {{1, 1, 1, 1}, {6, 11, 12, 6}};
-  const uint32_t *kCost = kCosts[1];
-  uint64_t tiles = 0, cost = 0;
+static const uint32_t kCosts[2][4] = {{1, 1, 1, 1}, {6, 11, 12, 6}};
+
+bool grid_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W) {
+  uint64_t tiles = 0;
   W->widths = 0;
   for (uint32_t p = 0; p < W->n_paths; ++p)
     for (int w = 0; w < 4; ++w) {
       const uint64_t t = (paths[p].job.n_sg[w] + kWaveSGs - 1) / kWaveSGs;
       tiles += t;
-      cost += t * kCost[w];
       if (t) W->widths |= 1u << w;
     }
   if (tiles == 0) return false;
@@ -414,17 +413,22 @@ bool split_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths
   const uint64_t needed = (tiles + W->waves - 1) / W->waves;
   W->blocks = n_cu * per_cu;
   if (W->blocks > needed) W->blocks = (uint32_t)needed;
-  const uint32_t n = W->blocks * W->waves;
-  if (tiles < 2ull * n) {
-    kCost = kCosts[0];
-    cost = tiles;
-  }
+  W->by_cost = tiles >= 2ull * W->blocks * W->waves;
+  return true;
+}
+
+void split_walk(const WalkPath *paths, const Walk &W, std::vector<WalkShare> *shares) {
+  const uint32_t *kCost = kCosts[W.by_cost];
+  uint64_t cost = 0;
+  for (uint32_t p = 0; p < W.n_paths; ++p)
+    for (int w = 0; w < 4; ++w) cost += (uint64_t)((paths[p].job.n_sg[w] + kWaveSGs - 1) / kWaveSGs) * kCost[w];
+  const uint32_t n = W.blocks * W.waves;
   shares->resize((size_t)n + 1);
   // first tile of share v: the first whose cost before it reaches v * cost / n
   uint32_t p = 0, t = 0, w = 0, left = 0;  // tile t of path p is in width w's run, which has `left` tiles more
   uint64_t before = 0;
   auto settle = [&] {  // on to the next run that has tiles
-    while (left == 0 && p < W->n_paths) {
+    while (left == 0 && p < W.n_paths) {
       if (w == 4) { ++p; w = 0; t = 0; continue; }
       left = (paths[p].job.n_sg[w] + kWaveSGs - 1) / kWaveSGs;
       if (left == 0) ++w;
@@ -433,7 +437,7 @@ bool split_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths
   settle();
   for (uint32_t v = 0; v < n; ++v) {
     const uint64_t want = (uint64_t)(((unsigned __int128)cost * v) / n);
-    while (before < want && p < W->n_paths) {
+    while (before < want && p < W.n_paths) {
       const uint64_t take = (want - before + kCost[w] - 1) / kCost[w];
       const uint32_t k = take < left ? (uint32_t)take : left;
       before += (uint64_t)k * kCost[w];
@@ -441,10 +445,9 @@ bool split_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths
       left -= k;
       if (left == 0) { ++w; settle(); }
     }
-    (*shares)[v] = WalkShare{p, p < W->n_paths ? t : 0u};
+    (*shares)[v] = WalkShare{p, p < W.n_paths ? t : 0u};
   }
-  (*shares)[n] = WalkShare{W->n_paths, 0};
-  return true;
+  (*shares)[n] = WalkShare{W.n_paths, 0};
 }
 
 hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths, const WalkShare *shares, const Walk &W,

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dq_bounds.h"
 #include "dq_device.h"
 
 namespace {
@@ -39,6 +40,52 @@ __device__ __forceinline__ uint32_t bf16_rne(float f) {
 // 32 or 64 consecutive bytes), sums them left to right in fp32 (squares by fma), and the 16
 // lanes of a row are combined by a butterfly (partner distance 1, 2, 4, 8).
 template <typename LT>
+struct Entries {
+  u32x4 w[sizeof(LT) == 4 ? 4 : 2];  // a lane's 16 entries, raw
+};
+template <typename LT>
+__device__ __forceinline__ Entries<LT> load_entries(const void *x, uint64_t first) {
+  const uint8_t *p = static_cast<const uint8_t *>(x) + first * sizeof(LT);
+  Entries<LT> e;
+#pragma unroll
+  for (int i = 0; i < (sizeof(LT) == 4 ? 4 : 2); ++i) e.w[i] = gld<u32x4>(p + 16 * i);
+  return e;
+}
+// Sum and sum of squares over the row's super-group, the same bits in all 16 lanes.
+template <typename LT>
+__device__ __forceinline__ void row_sums(const Entries<LT> &e, float &s, float &f) {
+  float v[16];
+  if constexpr (sizeof(LT) == 4) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[4 * i] = u2f(e.w[i].x); v[4 * i + 1] = u2f(e.w[i].y); v[4 * i + 2] = u2f(e.w[i].z); v[4 * i + 3] = u2f(e.w[i].w);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t w[4] = {e.w[i].x, e.w[i].y, e.w[i].z, e.w[i].w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        v[8 * i + 2 * j] = u2f(w[j] << 16);
+        v[8 * i + 2 * j + 1] = u2f(w[j] & 0xFFFF0000u);
+      }
+    }
+  }
+  s = 0.0f;
+  f = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    s += v[k];
+    f = __builtin_fmaf(v[k], v[k], f);
+  }
+#pragma unroll
+  for (int d = 1; d < 16; d <<= 1) {
+    s += __shfl_xor(s, d, 64);
+    f += __shfl_xor(f, d, 64);
+  }
+}
+
+template <typename LT>
 __global__ void __launch_bounds__(kThreads) k_stats(const void *x, uint64_t n_sg, float *mu, float *F) {
   const uint32_t lane = threadIdx.x & 63u;
   const uint64_t wave = (uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
@@ -46,42 +93,43 @@ __global__ void __launch_bounds__(kThreads) k_stats(const void *x, uint64_t n_sg
   const uint64_t n_tiles = (n_sg + 3) / 4;
   for (uint64_t t = wave; t < n_tiles; t += n_waves) {
     const uint64_t sg = min(t * 4 + (lane >> 4), n_sg - 1);  // idle rows redo the last SG, store nothing
-    const uint64_t first = sg * kSG + (lane & 15u) * 16;
-    float v[16];
-    if constexpr (sizeof(LT) == 4) {
-      const uint8_t *p = static_cast<const uint8_t *>(x) + first * 4;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const f32x4 q = gld<f32x4>(p + 16 * i);
-        v[4 * i] = q.x; v[4 * i + 1] = q.y; v[4 * i + 2] = q.z; v[4 * i + 3] = q.w;
-      }
-    } else {
-      const uint8_t *p = static_cast<const uint8_t *>(x) + first * 2;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const u32x4 q = gld<u32x4>(p + 16 * i);
-        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          v[8 * i + 2 * j] = u2f(w[j] << 16);
-          v[8 * i + 2 * j + 1] = u2f(w[j] & 0xFFFF0000u);
-        }
-      }
-    }
-    float s = 0.0f, f = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      s += v[k];
-      f = __builtin_fmaf(v[k], v[k], f);
-    }
-#pragma unroll
-    for (int d = 1; d < 16; d <<= 1) {
-      s += __shfl_xor(s, d, 64);
-      f += __shfl_xor(f, d, 64);
-    }
+    float s, f;
+    row_sums<LT>(load_entries<LT>(x, sg * kSG + (lane & 15u) * 16), s, f);
     if ((lane & 15u) == 0 && t * 4 + (lane >> 4) < n_sg) {
       gst<float>(mu + sg, s * (1.0f / kSG));
       gst<float>(F + sg, f);
+    }
+  }
+}
+
+// k_stats of every worker and k_combine in one pass: a simulated all-reduce, which holds all workers' tensors, has no use for
+// the single workers' statistics.  One launch instead of n + 1.
+constexpr uint32_t kStatsWorkers = 256;
+struct WorkerTensors {
+  const void *x[kStatsWorkers];
+};
+template <typename LT>
+__global__ void __launch_bounds__(kThreads) k_stats_all(WorkerTensors W, uint32_t n, uint64_t n_sg, float *mu, float *F) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint64_t wave = (uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  const uint64_t n_waves = (uint64_t)gridDim.x * (kThreads / 64);
+  const uint64_t n_tiles = (n_sg + 3) / 4;
+  for (uint64_t t = wave; t < n_tiles; t += n_waves) {
+    const uint64_t sg = min(t * 4 + (lane >> 4), n_sg - 1), first = sg * kSG + (lane & 15u) * 16;
+    float sm = 0.0f, sf = 0.0f;
+    Entries<LT> e = load_entries<LT>(W.x[0], first);
+    for (uint32_t w = 0; w < n; ++w) {
+      Entries<LT> next = e;
+      if (w + 1 < n) next = load_entries<LT>(W.x[w + 1], first);
+      float s, f;
+      row_sums<LT>(e, s, f);
+      sm = sm + u2f(bf16_rne(s * (1.0f / kSG)) << 16);
+      sf = sf + u2f(bf16_rne(f) << 16);
+      e = next;
+    }
+    if ((lane & 15u) == 0 && t * 4 + (lane >> 4) < n_sg) {
+      gst<float>(mu + sg, sm / (float)n);
+      gst<float>(F + sg, sf);
     }
   }
 }
@@ -630,6 +678,23 @@ dq_status dq_stats_combine(const float *mu_all, const float *F_all, uint32_t n_w
   if ((n_sg + kThreads - 1) / kThreads > 0x7FFFFFFFull) return DQ_EUNSUPPORTED;
   hipLaunchKernelGGL(k_combine, dim3((uint32_t)((n_sg + kThreads - 1) / kThreads)), dim3(kThreads), 0,
                      (hipStream_t)hip_stream, mu_all, F_all, n_workers, n_sg, mu, F);
+  return launched();
+}
+
+dq_status dqx_stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dtype, uint64_t n_sg, float *mu, float *F,
+                        void *hip_stream) {
+  if (n_sg == 0) return DQ_OK;
+  if (!tensors || !mu || !F || n_workers == 0 || (dtype != DQ_F32 && dtype != DQ_BF16)) return DQ_EINVAL;
+  if (n_workers > kStatsWorkers) return DQ_EUNSUPPORTED;
+  WorkerTensors W = {};
+  for (uint32_t w = 0; w < n_workers; ++w) {
+    if (!aligned(tensors[w], 16)) return DQ_EALIGN;
+    W.x[w] = tensors[w];
+  }
+  const uint32_t blocks = stream_blocks(4 * (kThreads / 64), n_sg);
+  hipStream_t s = (hipStream_t)hip_stream;
+  if (dtype == DQ_F32) hipLaunchKernelGGL(k_stats_all<float>, dim3(blocks), dim3(kThreads), 0, s, W, n_workers, n_sg, mu, F);
+  else hipLaunchKernelGGL(k_stats_all<uint16_t>, dim3(blocks), dim3(kThreads), 0, s, W, n_workers, n_sg, mu, F);
   return launched();
 }
 
