@@ -150,7 +150,7 @@ __global__ void __launch_bounds__(kThreads) k_combine(const float *mu_all, const
 }
 
 // ---------------------------------------------------------------------------------------
-// Allocation: one block of 1024 threads per bucket.  Super-group j = 1024*k + t sits in slot k
+// Allocation: the search in one block of 1024 threads per bucket.  Super-group j = 1024*k + t sits in slot k
 // of thread t (a register when the bucket has at most 64 rows of 1024), so every global access
 // is coalesced.  Values are handled as int32 bit patterns: non-negative floats order like their
 // patterns, and the difference of two patterns below 2^31 has the sign of the comparison,
@@ -160,7 +160,6 @@ constexpr int kAllocThreads = 1024;
 constexpr int kAllocWaves = kAllocThreads / 64;
 constexpr int kRegs = 64;
 constexpr uint32_t kBins = 2048;  // 2 per thread
-constexpr uint32_t kCap = 4096;   // candidates kept per threshold
 
 __device__ __forceinline__ int32_t pattern_of(float f) { return f > 0.0f ? (int32_t)f2u(f) : 0; }
 
@@ -177,126 +176,344 @@ __device__ __forceinline__ int32_t p16_from(uint32_t pattern, bool allow16) {
 }
 
 // Widths and positions once the threshold is known (counts[5b..5b+4] as the search left them):
-// grid (ceil(J / 1024), buckets).  A block first counts the members of each class among the
-// super-groups before its own 1024 (at most 64 rows for the sizes this path takes), then ranks
-// its own: position = first place of the class + members before the block + members in earlier
-// waves + members in lower lanes.
+// grid (ceil(J / 1024), buckets), a block ranks its own 1024 super-groups: position = the row's first place of the
+// class + members in earlier waves + members in lower lanes.  The search left each row's four first places where the
+// row's own positions go (read here before they are overwritten); the last row, which may be shorter than that, counts
+// back from the classes' ends.  (A block that counted the rows before its own took 12.5 us for 51,200 super-groups.)
 __global__ void __launch_bounds__(kAllocThreads) k_alloc_positions(const float *F_all, uint32_t J, bool allow16,
                                                                    const uint32_t *counts_all, uint8_t *widths_all,
                                                                    uint32_t *pos_all) {
-  __shared__ uint32_t before[kAllocWaves][4], mine_w[kAllocWaves][4];
+  __shared__ uint32_t mine_w[kAllocWaves][4];
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   const uint64_t first = (uint64_t)blockIdx.y * J;
-  const float *F = F_all + first;
   const uint32_t *cnt = counts_all + 5ull * blockIdx.y;
+  const uint32_t j = blockIdx.x * kAllocThreads + tid;
+  const bool last = blockIdx.x + 1 == gridDim.x;
+  const float f = gld<float>(F_all + first + min(j, J - 1));
+  uint32_t at_row[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) at_row[c] = last ? gld<uint32_t>(cnt + c) : gld<uint32_t>(pos_all + first + (uint64_t)blockIdx.x * kAllocThreads + c);
   const uint32_t pattern = gld<uint32_t>(cnt + 4);
   const int32_t p8 = (int32_t)pattern, p4 = p4_from(pattern), p16 = p16_from(pattern, allow16);
-  const uint32_t n0 = gld<uint32_t>(cnt), n1 = gld<uint32_t>(cnt + 1), n2 = gld<uint32_t>(cnt + 2);
-  const uint32_t start[4] = {0u, n0, n0 + n1, n0 + n1 + n2};
-  uint32_t c[4] = {0u, 0u, 0u, 0u};
-  constexpr uint32_t kAhead = 32;  // rows of 1024 before this block, that many loads in flight
-  for (uint32_t r0 = 0; r0 < blockIdx.x; r0 += kAhead) {
-    float f[kAhead];
-#pragma unroll
-    for (uint32_t r = 0; r < kAhead; ++r) f[r] = gld<float>(F + min(r0 + r, blockIdx.x - 1) * kAllocThreads + tid);
-#pragma unroll
-    for (uint32_t r = 0; r < kAhead; ++r) {
-      const uint32_t k = r0 + r < blockIdx.x ? class_of(pattern_of(f[r]), p4, p8, p16) : 4u;
-#pragma unroll
-      for (uint32_t i = 0; i < 4; ++i) c[i] += k == i ? 1u : 0u;
-    }
-  }
-  const uint32_t j = blockIdx.x * kAllocThreads + tid;
-  const uint32_t k = j < J ? class_of(pattern_of(gld<float>(F + j)), p4, p8, p16) : 4u;
+  const uint32_t k = j < J ? class_of(pattern_of(f), p4, p8, p16) : 4u;
   const uint64_t b[4] = {__ballot(k == 0), __ballot(k == 1), __ballot(k == 2), __ballot(k == 3)};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) c[i] += __shfl_xor(c[i], d, 64);
-  }
   if (lane == 0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      before[wave][i] = c[i];
-      mine_w[wave][i] = (uint32_t)__builtin_popcountll(b[i]);
-    }
+    for (int i = 0; i < 4; ++i) mine_w[wave][i] = (uint32_t)__builtin_popcountll(b[i]);
   }
   __syncthreads();
   if (k < 4) {
-    uint32_t at = start[k];
+    uint32_t before = 0, all = 0;
 #pragma unroll
-    for (int w = 0; w < kAllocWaves; ++w) at += before[w][k] + ((uint32_t)w < wave ? mine_w[w][k] : 0u);
+    for (int w = 0; w < kAllocWaves; ++w) {
+      before += (uint32_t)w < wave ? mine_w[w][k] : 0u;
+      all += mine_w[w][k];
+    }
+    uint32_t at = k == 0 ? at_row[0] : (k == 1 ? at_row[1] : (k == 2 ? at_row[2] : at_row[3]));
+    if (last) {  // at_row holds the classes' sizes: the class's end less what this row adds to it
+      at = at_row[0] - all;
+      if (k > 0) at += at_row[1];
+      if (k > 1) at += at_row[2];
+      if (k > 2) at += at_row[3];
+    }
     const uint64_t mine = k == 0 ? b[0] : (k == 1 ? b[1] : (k == 2 ? b[2] : b[3]));
-    at += __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
+    at += before + __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
     gst<uint8_t>(widths_all + first + j, (uint8_t)(2u << k));
     gst<uint32_t>(pos_all + first + j, at);
   }
 }
 
-// IN_REGS (buckets of at most 65,536 super-groups): the kernel ends once counts[5b..5b+4] are
-// written, widths and positions are another launch (k_alloc_positions, spread over the GPU: ranking
-// 64 rows in this one block took longer than the whole search and spilled registers); larger
-// buckets do them here, 64 rows of 1024 at a time, reading the norms again.
-template <bool IN_REGS>
-__global__ void __launch_bounds__(kAllocThreads) k_allocate(const float *F_all, uint32_t J, uint64_t max_code_bits,
+// The search for buckets of at most 64 rows of 1024, the norms' patterns in registers (kRegs per thread; every pass skips
+// the rows that the bucket does not have, four at a time).
+//
+// Wanted: the smallest fp32 pattern in [1, +inf] whose allocation fits (the host has checked 2J <= budget).  With
+// c8, c4, c16 = norms at or above T_{4,8} and its tied thresholds, cost = 2J + 4 c8 + 2 c4 + 8 c16 never increases with
+// the threshold, so a bracket (lo does not fit or is 0, hi fits) is narrowed level by level: a histogram of the patterns
+// around each of the three thresholds, suffix counts, and for every bin boundary of the bracket a lower and an upper bound of its
+// cost (c8 is exact there, c4 and c16 lie between the counts of two bins).  2048 bins a level: the top 11 bits of
+// everything, then what is left of the bracket, 1 to 3 bins of 2^20, then single patterns.
+//
+// What bounds it: one CU's vector ALU (51,200 norms are 800 wave instructions for every instruction of a pass) and
+// the barriers.  It replaced a gather of the candidates (two LDS atomics with a result per row, 20 us), a
+// bisection with a barrier per step, and full counts per step where 16 bits are allowed.
+constexpr uint32_t kBins4 = 3072, kBins16 = 5120;  // the tied thresholds' brackets in bins of the same size: up to 1.07 and 2 times as many
+__global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits, bool allow16,
+                                                          uint32_t *pos_all, uint32_t *counts_all) {
+  __shared__ uint32_t h8[kBins + 2], h4[kBins4 + 2], h16[kBins16 + 2];
+  __shared__ uint32_t wsum[3][kAllocWaves], wbase[2][kAllocWaves], wfit[2][kAllocWaves];
+  __shared__ uint32_t tot[kRegs * kAllocWaves][4];  // per (row, wave): class counts, then their exclusive scan
+  const float *F = F_all + (uint64_t)blockIdx.x * J;
+  uint32_t *pos = pos_all + (uint64_t)blockIdx.x * J;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  int32_t fr[kRegs];
+  const uint32_t rows = (J + kAllocThreads - 1) / kAllocThreads;
+  auto each_row = [&](auto body) {
+#pragma unroll
+    for (int g = 0; g < kRegs; g += 4)
+      if ((uint32_t)g < rows) {
+#pragma unroll
+        for (int k = g; k < g + 4; ++k) body(k);
+      }
+  };
+  each_row([&](int k) { fr[k] = (int32_t)f2u(gld<float>(F + min(k * kAllocThreads + tid, J - 1))); });  // all in flight at once
+  each_row([&](int k) { fr[k] = k * kAllocThreads + tid < J ? pattern_of(u2f((uint32_t)fr[k])) : -1; });
+  auto p16_of = [&](uint32_t pattern) { return allow16 ? f2u(u2f(pattern) * (131072.0f / 257.0f)) : (uint32_t)kNever; };
+  auto p4_of = [](uint32_t pattern) { return f2u(u2f(pattern) * (17.0f / 512.0f)); };
+  // h[b] for b < PER * 1024 becomes the sum of h[b], h[b + 1], ...; two barriers, shared by up to three histograms
+  uint32_t inc[3], own[3];
+  auto sums_begin = [&](int which, const uint32_t *h, int per) {
+    uint32_t sum = 0;
+    for (int i = 0; i < per; ++i) sum += h[tid * per + i];
+    own[which] = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t up = __shfl_up(sum, d, 64);
+      if (lane >= (uint32_t)d) sum += up;
+    }
+    inc[which] = sum;
+    if (lane == 63) wsum[which][wave] = sum;
+  };
+  auto sums_end = [&](int which, uint32_t *h, int per) {
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kAllocWaves; ++w) {
+      const uint32_t t = wsum[which][w];
+      before += (uint32_t)w < wave ? t : 0u;
+      all += t;
+    }
+    uint32_t left = all - (before + inc[which] - own[which]);  // from this thread's first bin on
+    for (int i = 0; i < per; ++i) {
+      const uint32_t x = h[tid * per + i];
+      h[tid * per + i] = left;
+      left -= x;
+    }
+  };
+  // How many of the bin boundaries 1 .. n-1 surely do not fit, and how many may not: the bracket is between them.
+  auto bracket = [&](uint32_t n, auto cost_bounds, uint32_t &surely, uint32_t &perhaps) {
+    uint32_t a = 0, c = 0;
+    for (uint32_t b0 = 0; b0 < n; b0 += kAllocThreads) {  // uniform trips: every thread takes part in the ballots
+      const uint32_t bin = b0 + tid;
+      bool over = false, may = false;
+      if (bin >= 1 && bin < n) {
+        uint64_t c_min, c_max;
+        cost_bounds(bin, c_min, c_max);
+        over = c_min > max_code_bits;
+        may = c_max > max_code_bits;
+      }
+      a += (uint32_t)__builtin_popcountll(__ballot(over));
+      c += (uint32_t)__builtin_popcountll(__ballot(may));
+    }
+    if (lane == 0) {
+      wfit[0][wave] = a;
+      wfit[1][wave] = c;
+    }
+    __syncthreads();
+    surely = 0;
+    perhaps = 0;
+#pragma unroll
+    for (int w = 0; w < kAllocWaves; ++w) {
+      surely += wfit[0][w];
+      perhaps += wfit[1][w];
+    }
+  };
+
+  // level 1: bins of 2^20 patterns, 2040 << 20 is +infinity
+  for (uint32_t b = tid; b < kBins + 2; b += kAllocThreads) h8[b] = 0;
+  __syncthreads();
+  each_row([&](int k) {
+    if (fr[k] >= 0) atomicAdd(&h8[(uint32_t)fr[k] >> 20], 1u);
+  });
+  __syncthreads();
+  sums_begin(0, h8, kBins / kAllocThreads);
+  __syncthreads();
+  sums_end(0, h8, kBins / kAllocThreads);
+  __syncthreads();
+  uint32_t surely, perhaps;
+  bracket(kBins - 8, [&](uint32_t b, uint64_t &c_min, uint64_t &c_max) {
+    const uint32_t b4 = p4_of(b << 20) >> 20, b16 = p16_of(b << 20) >> 20;
+    const uint64_t fixed = 2ull * J + 4ull * h8[b];
+    c_min = fixed + 2ull * h8[b4 + 1] + 8ull * h8[b16 + 1];
+    c_max = fixed + 2ull * h8[b4] + 8ull * h8[b16];
+  }, surely, perhaps);
+  uint32_t lo = surely << 20, hi = (perhaps + 1) << 20;
+  uint32_t base8 = h8[perhaps + 1];  // norms at or above hi
+
+  bool exact = false;
+  while (hi - lo > 1 && !exact) {
+    const uint32_t width = hi - lo, lo4 = p4_of(lo), hi4 = p4_of(hi), lo16 = p16_of(lo), hi16 = p16_of(hi);
+    uint32_t s = 0, s4 = 0, s16 = 0;
+    while ((width - 1) >> s >= kBins) ++s;
+    while ((hi4 - lo4) >> s4 >= kBins4 || s4 < s) ++s4;
+    while ((hi16 - lo16) >> s16 >= kBins16 || s16 < s) ++s16;  // denormal thresholds: up to 510 patterns to one
+    const uint32_t n = ((width - 1) >> s) + 1;
+    __syncthreads();  // everybody has read the level before
+    for (uint32_t b = tid; b < kBins + 2; b += kAllocThreads) h8[b] = 0;
+    for (uint32_t b = tid; b < kBins4 + 2; b += kAllocThreads) h4[b] = 0;
+    if (allow16) for (uint32_t b = tid; b < kBins16 + 2; b += kAllocThreads) h16[b] = 0;
+    __syncthreads();
+    uint32_t above4 = 0, above16 = 0;
+    each_row([&](int k) {
+      const uint32_t v = (uint32_t)fr[k];
+      if (v - lo < width) atomicAdd(&h8[(v - lo) >> s], 1u);
+      if (v - lo4 < hi4 - lo4) atomicAdd(&h4[(v - lo4) >> s4], 1u);
+      above4 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= (int32_t)hi4));
+      if (allow16) {
+        if (v - lo16 < hi16 - lo16) atomicAdd(&h16[(v - lo16) >> s16], 1u);
+        above16 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= (int32_t)hi16));
+      }
+    });
+    if (lane == 0) {
+      wbase[0][wave] = above4;
+      wbase[1][wave] = above16;
+    }
+    __syncthreads();
+    sums_begin(0, h8, kBins / kAllocThreads);
+    sums_begin(1, h4, kBins4 / kAllocThreads);
+    if (allow16) sums_begin(2, h16, kBins16 / kAllocThreads);
+    __syncthreads();
+    sums_end(0, h8, kBins / kAllocThreads);
+    sums_end(1, h4, kBins4 / kAllocThreads);
+    if (allow16) sums_end(2, h16, kBins16 / kAllocThreads);
+    uint32_t base4 = 0, base16 = 0;
+#pragma unroll
+    for (int w = 0; w < kAllocWaves; ++w) {
+      base4 += wbase[0][w];
+      base16 += wbase[1][w];
+    }
+    __syncthreads();
+    bracket(n, [&](uint32_t b, uint64_t &c_min, uint64_t &c_max) {
+      const uint32_t T = lo + (b << s), b4 = (p4_of(T) - lo4) >> s4;
+      // a tied threshold on a bin's first pattern has that bin's count exactly
+      const bool on4 = ((p4_of(T) - lo4) & ((1u << s4) - 1u)) == 0;
+      const uint64_t fixed = 2ull * J + 4ull * (base8 + h8[b]);
+      c_min = fixed + 2ull * (base4 + h4[on4 ? b4 : b4 + 1]);
+      c_max = fixed + 2ull * (base4 + h4[b4]);
+      if (allow16) {
+        const uint32_t at = p16_of(T) - lo16, b16 = at >> s16;
+        c_min += 8ull * (base16 + h16[(at & ((1u << s16) - 1u)) == 0 ? b16 : b16 + 1]);
+        c_max += 8ull * (base16 + h16[b16]);
+      }
+    }, surely, perhaps);
+    const uint32_t new_lo = surely ? lo + (surely << s) : lo;
+    const uint32_t new_hi = perhaps + 1 < n ? lo + ((perhaps + 1) << s) : hi;
+    if (perhaps + 1 < n) base8 += h8[perhaps + 1];
+    exact = new_hi - new_lo > width / 2 && new_hi - new_lo > 1;  // bounds too loose to go on: count exactly below
+    lo = new_lo;
+    hi = new_hi;
+  }
+  // Exact counts at one threshold.
+  uint32_t turn = 0;
+  auto block_counts = [&](uint32_t pattern, uint32_t &c4, uint32_t &c8, uint32_t &c16) {
+    const int32_t p4 = p4_from(pattern), p8 = (int32_t)pattern, p16 = p16_from(pattern, allow16);
+    uint32_t a4 = 0, a8 = 0, a16 = 0;
+    each_row([&](int k) {
+      a4 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p4));
+      a8 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p8));
+      if (allow16) a16 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p16));
+    });
+    // the waves' counts meet in one of two buffers by turns, so that one barrier per round is enough
+    if (lane == 0) {
+      tot[turn * kAllocWaves + wave][0] = a4;
+      tot[turn * kAllocWaves + wave][1] = a8;
+      tot[turn * kAllocWaves + wave][2] = a16;
+    }
+    __syncthreads();
+    c4 = c8 = c16 = 0;
+#pragma unroll
+    for (int w = 0; w < kAllocWaves; ++w) {
+      c4 += tot[turn * kAllocWaves + w][0];
+      c8 += tot[turn * kAllocWaves + w][1];
+      c16 += tot[turn * kAllocWaves + w][2];
+    }
+    turn ^= 1u;
+  };
+  while (hi - lo > 1) {
+    const uint32_t mid = lo + (hi - lo) / 2;
+    uint32_t c4, c8, c16;
+    block_counts(mid, c4, c8, c16);
+    const uint64_t cost = 2ull * J + 2ull * c4 + 4ull * c8 + 8ull * c16;
+    if (cost <= max_code_bits) hi = mid; else lo = mid;
+  }
+  __syncthreads();
+  // class counts of every (row, wave), their exclusive scan in that order: the rows' first places
+  const int32_t p8 = (int32_t)hi, p4 = p4_from(hi), p16 = p16_from(hi, allow16);
+  each_row([&](int k) {
+    const int32_t v = fr[k];
+    const uint32_t at0 = (uint32_t)__builtin_popcountll(__ballot(v >= 0)), at4 = (uint32_t)__builtin_popcountll(__ballot(v >= p4)),
+                   at8 = (uint32_t)__builtin_popcountll(__ballot(v >= p8)),
+                   at16 = allow16 ? (uint32_t)__builtin_popcountll(__ballot(v >= p16)) : 0u;
+    if (lane == 0) {
+      tot[k * kAllocWaves + wave][0] = at0 - at4;
+      tot[k * kAllocWaves + wave][1] = at4 - at8;
+      tot[k * kAllocWaves + wave][2] = at8 - at16;
+      tot[k * kAllocWaves + wave][3] = at16;
+    }
+  });
+  __syncthreads();
+  uint32_t x[4], sum[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    x[c] = tid < rows * kAllocWaves ? tot[tid][c] : 0u;
+    sum[c] = x[c];
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t up = __shfl_up(sum[c], d, 64);
+      if (lane >= (uint32_t)d) sum[c] += up;
+    }
+  }
+  __syncthreads();
+  if (lane == 63) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) h8[4 * wave + c] = sum[c];
+  }
+  __syncthreads();
+  uint32_t n_class[4], row_first[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kAllocWaves; ++w) {
+      const uint32_t t = h8[4 * w + c];
+      before += (uint32_t)w < wave ? t : 0u;
+      all += t;
+    }
+    n_class[c] = all;
+    row_first[c] = before + sum[c] - x[c];
+  }
+  const uint32_t row = tid / kAllocWaves, class_first[4] = {0u, n_class[0], n_class[0] + n_class[1], n_class[0] + n_class[1] + n_class[2]};
+  if (tid % kAllocWaves == 0 && (row + 1) * kAllocThreads < J) {  // not the last row
+#pragma unroll
+    for (int c = 0; c < 4; ++c) gst<uint32_t>(pos + row * kAllocThreads + c, class_first[c] + row_first[c]);
+  }
+  if (tid == 0) {
+    uint32_t *cnt = counts_all + 5ull * blockIdx.x;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) gst<uint32_t>(cnt + c, n_class[c]);
+    gst<uint32_t>(cnt + 4, hi);
+  }
+}
+
+// Buckets of more than 65,536 super-groups: the norms are read again in every round of a bisection, widths and positions
+// are written here, 64 rows of 1024 at a time.
+__global__ void __launch_bounds__(kAllocThreads) k_allocate_large(const float *F_all, uint32_t J, uint64_t max_code_bits,
                                                             bool allow16, uint8_t *widths_all, uint32_t *pos_all,
                                                             uint32_t *counts_all) {
   __shared__ uint32_t red[2][3][kAllocWaves];
   __shared__ uint32_t tot[kRegs * kAllocWaves][4];  // per (row, wave): class counts, then their exclusive scan
   __shared__ uint32_t wsum[kAllocWaves][4];
-  __shared__ uint32_t hist[kBins + 2];   // top-11-bit histogram, then suffix counts (register path)
-  __shared__ int32_t cand[2][kCap];      // patterns that can still change c8 / c4
-  __shared__ uint32_t ncand[2];
   const float *F = F_all + (uint64_t)blockIdx.x * J;
   uint8_t *widths = widths_all + (uint64_t)blockIdx.x * J;
   uint32_t *pos = pos_all + (uint64_t)blockIdx.x * J;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   const uint32_t rows = (J + kAllocThreads - 1) / kAllocThreads;
-  int32_t fr[IN_REGS ? kRegs : 1];
-  if constexpr (IN_REGS) {
-#pragma unroll
-    for (int k = 0; k < kRegs; ++k) {
-      const uint32_t j = k * kAllocThreads + tid;  // all loads in flight at once: clamp, then mask
-      const int32_t v = pattern_of(gld<float>(F + min(j, J - 1)));
-      fr[k] = j < J ? v : -1;
-    }
-  }
-  // Counts over the wave of super-groups at or above T_{2,4} and T_{4,8}.  In registers a funnel
-  // shift collects the sign bits of 32 differences in a word and one population count per word
-  // turns them into the number below the threshold.
+  // Counts over the wave of super-groups at or above the thresholds.
   auto count = [&](int32_t p4, int32_t p8, int32_t p16, uint32_t &c4, uint32_t &c8, uint32_t &c16) {
     uint32_t a4 = 0, a8 = 0, a16 = 0;
-    if constexpr (IN_REGS) {
-      uint32_t below4 = 0, below8 = 0, below16 = 0;
-#pragma unroll
-      for (int h = 0; h < kRegs / 32; ++h) {
-        uint32_t m4 = 0, m8 = 0;
-#pragma unroll
-        for (int k = 0; k < 32; ++k) {
-          m4 = __builtin_amdgcn_alignbit(m4, (uint32_t)(fr[32 * h + k] - p4), 31);
-          m8 = __builtin_amdgcn_alignbit(m8, (uint32_t)(fr[32 * h + k] - p8), 31);
-        }
-        below4 += __builtin_popcount(m4);
-        below8 += __builtin_popcount(m8);
-        if (allow16) {
-          uint32_t m16 = 0;
-#pragma unroll
-          for (int k = 0; k < 32; ++k) m16 = __builtin_amdgcn_alignbit(m16, (uint32_t)(fr[32 * h + k] - p16), 31);
-          below16 += __builtin_popcount(m16);
-        } else {
-          below16 += 32;
-        }
-      }
-      a4 = kRegs - below4;
-      a8 = kRegs - below8;
-      a16 = kRegs - below16;
-    } else {
-      for (uint32_t j = tid; j < J; j += kAllocThreads) {
-        const int32_t v = pattern_of(gld<float>(F + j));
-        a4 += v >= p4 ? 1u : 0u;
-        a8 += v >= p8 ? 1u : 0u;
-        a16 += v >= p16 ? 1u : 0u;
-      }
+    for (uint32_t j = tid; j < J; j += kAllocThreads) {
+      const int32_t v = pattern_of(gld<float>(F + j));
+      a4 += v >= p4 ? 1u : 0u;
+      a8 += v >= p8 ? 1u : 0u;
+      a16 += v >= p16 ? 1u : 0u;
     }
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -331,156 +548,18 @@ __global__ void __launch_bounds__(kAllocThreads) k_allocate(const float *F_all, 
   // 2J <= budget).  An SG at or above T_{4,8} is also at or above T_{2,4}, so
   // cost = 2J + 2*c4 + 4*c8, which never increases with the threshold: bisection from any
   // bracket (lo does not fit or is 0, hi fits) ends at the same pattern.
-  auto p4_of = [](uint32_t pattern) { return f2u(u2f(pattern) * (17.0f / 512.0f)); };
   uint32_t lo = 0, hi = 0x7F800000u;
-  bool narrowed = false;
-  uint32_t base4 = 0, base8 = 0;
-  if constexpr (IN_REGS) {
-  if (!allow16) {  // with a third threshold in play everything is counted every round
-    // (1) Histogram of the patterns' top 11 bits (bin b = patterns [b << 20, (b+1) << 20);
-    //     2040 << 20 is +infinity), turned into suffix counts S[b] = #{v : bin(v) >= b}.
-    for (uint32_t b = tid; b < kBins + 2; b += kAllocThreads) hist[b] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kRegs; ++k)
-      if (fr[k] >= 0) atomicAdd(&hist[(uint32_t)fr[k] >> 20], 1u);
-    __syncthreads();
-    {
-      // thread t owns bins 2t and 2t+1; suffix scan = total - exclusive prefix
-      const uint32_t h0 = hist[2 * tid], h1 = hist[2 * tid + 1];
-      uint32_t inc = h0 + h1;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t up = __shfl_up(inc, d, 64);
-        if (lane >= (uint32_t)d) inc += up;
-      }
-      if (lane == 63) wsum[wave][0] = inc;
-      __syncthreads();
-      uint32_t before = 0, all = 0;
-#pragma unroll
-      for (int w = 0; w < kAllocWaves; ++w) {
-        const uint32_t t = wsum[w][0];
-        before += (uint32_t)w < wave ? t : 0u;
-        all += t;
-      }
-      const uint32_t excl = before + inc - (h0 + h1);  // patterns in bins below 2t
-      hist[2 * tid] = all - excl;
-      hist[2 * tid + 1] = all - excl - h0;
-      if (tid == 0) hist[kBins] = hist[kBins + 1] = 0;
-      __syncthreads();
-    }
-    // (2) Bracket in whole bins, by every thread alike (LDS reads only).  For a threshold on a
-    //     bin boundary c8 = S[b] is exact and c4 lies in [S[bin4 + 1], S[bin4]], bin4 the bin of
-    //     T_{2,4}: an upper and a lower bound of the cost, both monotone.
-    auto cost_bounds = [&](uint32_t b, uint64_t &c_min, uint64_t &c_max) {
-      const uint32_t bin4 = p4_of(b << 20) >> 20;
-      const uint64_t fixed = 2ull * J + 4ull * hist[b];
-      c_min = fixed + 2ull * hist[bin4 + 1];
-      c_max = fixed + 2ull * hist[bin4];
-    };
-    uint32_t b_no = 0, b_fit = kBins - 8;  // 2040: +infinity, everything at 2 bits
-    while (b_fit - b_no > 1) {             // smallest bin boundary that surely fits
-      const uint32_t mid = b_no + (b_fit - b_no) / 2;
-      uint64_t c_min, c_max;
-      cost_bounds(mid, c_min, c_max);
-      if (c_max <= max_code_bits) b_fit = mid; else b_no = mid;
-    }
-    uint32_t b_open = b_fit;
-    b_no = 0;                              // pattern 0 is no threshold: "does not fit"
-    while (b_open - b_no > 1) {            // largest bin boundary that surely does not fit
-      const uint32_t mid = b_no + (b_open - b_no) / 2;
-      uint64_t c_min, c_max;
-      cost_bounds(mid, c_min, c_max);
-      if (c_min > max_code_bits) b_no = mid; else b_open = mid;
-    }
-    lo = b_no << 20;
-    hi = b_fit << 20;
-    // (3) Only patterns strictly inside (lo, hi) can change c8 while the threshold moves in
-    //     (lo, hi], and only patterns in [p4(lo), p4(hi)) can change c4: collect them in LDS.
-    const int32_t lo8 = (int32_t)lo, hi8 = (int32_t)hi, lo4 = (int32_t)p4_of(lo), hi4 = (int32_t)p4_of(hi);
-    if (tid < 2) ncand[tid] = 0;
-    __syncthreads();
-    uint32_t always4 = 0;
-#pragma unroll
-    for (int k = 0; k < kRegs; ++k) {
-      const int32_t v = fr[k];
-      const bool in8 = v > lo8 && v < hi8, in4 = v >= lo4 && v < hi4;
-      always4 += v >= hi4 ? 1u : 0u;
-      const uint64_t m8 = __ballot(in8), m4 = __ballot(in4);
-      if (m8) {
-        uint32_t at = 0;
-        if (lane == 0) at = atomicAdd(&ncand[0], (uint32_t)__builtin_popcountll(m8));
-        at = __shfl(at, 0, 64) + __builtin_amdgcn_mbcnt_hi((uint32_t)(m8 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m8, 0u));
-        if (in8 && at < kCap) cand[0][at] = v;
-      }
-      if (m4) {
-        uint32_t at = 0;
-        if (lane == 0) at = atomicAdd(&ncand[1], (uint32_t)__builtin_popcountll(m4));
-        at = __shfl(at, 0, 64) + __builtin_amdgcn_mbcnt_hi((uint32_t)(m4 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m4, 0u));
-        if (in4 && at < kCap) cand[1][at] = v;
-      }
-    }
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) always4 += __shfl_xor(always4, d, 64);
-    if (lane == 0) red[0][0][wave] = always4;
-    __syncthreads();
-    const uint32_t n8 = ncand[0], n4 = ncand[1];
-    base8 = hist[b_fit];  // patterns at or above hi: exact, hi is a bin boundary
-#pragma unroll
-    for (int w = 0; w < kAllocWaves; ++w) base4 += red[0][0][w];
-    narrowed = n8 <= kCap && n4 <= kCap;  // otherwise (masses of equal values) count everything again
-    __syncthreads();                      // red is reused below
-    if (narrowed) {
-      // (4) bisection over the candidates
-      while (hi - lo > 1) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        const int32_t m8 = (int32_t)mid, m4 = (int32_t)p4_of(mid);
-        uint32_t a4 = 0, a8 = 0;
-        for (uint32_t i = tid; i < n8; i += kAllocThreads) a8 += cand[0][i] >= m8 ? 1u : 0u;
-        for (uint32_t i = tid; i < n4; i += kAllocThreads) a4 += cand[1][i] >= m4 ? 1u : 0u;
-        uint32_t both = a4 | (a8 << 16);  // at most kCap / 1024 each per lane
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) both += __shfl_xor(both, d, 64);
-        if (lane == 0) red[turn][0][wave] = both;
-        __syncthreads();
-        uint32_t s4 = base4, s8 = base8;
-#pragma unroll
-        for (int w = 0; w < kAllocWaves; ++w) {
-          const uint32_t t = red[turn][0][w];
-          s4 += t & 0xFFFFu;
-          s8 += t >> 16;
-        }
-        turn ^= 1u;
-        const uint64_t cost = 2ull * J + 2ull * s4 + 4ull * s8;
-        if (cost <= max_code_bits) hi = mid; else lo = mid;
-      }
-    }
-  }
-  }
-  if (!narrowed) {
-    while (hi - lo > 1) {
-      const uint32_t mid = lo + (hi - lo) / 2;
-      uint32_t s4, s8, s16;
-      block_counts(mid, s4, s8, s16);
-      const uint64_t cost = 2ull * J + 2ull * s4 + 4ull * s8 + 8ull * s16;
-      if (cost <= max_code_bits) hi = mid; else lo = mid;
-    }
+  while (hi - lo > 1) {
+    const uint32_t mid = lo + (hi - lo) / 2;
+    uint32_t s4, s8, s16;
+    block_counts(mid, s4, s8, s16);
+    const uint64_t cost = 2ull * J + 2ull * s4 + 4ull * s8 + 8ull * s16;
+    if (cost <= max_code_bits) hi = mid; else lo = mid;
   }
   uint32_t s4, s8, s16;
   block_counts(hi, s4, s8, s16);
   const int32_t p8 = (int32_t)hi, p4 = p4_from(hi), p16 = p16_from(hi, allow16);
   const uint32_t n_class[4] = {J - s4, s4 - s8, s8 - s16, s16};
-  if constexpr (IN_REGS) {
-    if (tid == 0) {
-      uint32_t *cnt = counts_all + 5ull * blockIdx.x;
-      gst<uint32_t>(cnt, n_class[0]);
-      gst<uint32_t>(cnt + 1, n_class[1]);
-      gst<uint32_t>(cnt + 2, n_class[2]);
-      gst<uint32_t>(cnt + 3, n_class[3]);
-      gst<uint32_t>(cnt + 4, hi);
-    }
-    return;
-  }
   // first position of each class in the reordered bucket, advanced chunk by chunk
   uint32_t next[4] = {0, n_class[0], n_class[0] + n_class[1], n_class[0] + n_class[1] + n_class[2]};
 
@@ -716,14 +795,13 @@ dq_status dq_allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_bucke
   if (max_code_bits < 2ull * n_sg_per_bucket) return DQ_EINVAL;  // fewer than 2 code bits per coordinate
   if (!aligned(F, 4) || !aligned(pos, 4) || !aligned(counts, 4)) return DQ_EALIGN;
   hipStream_t s = (hipStream_t)hip_stream;
-  if (n_sg_per_bucket <= (uint32_t)kRegs * kAllocThreads) {
-    // the search in one block per bucket, the norms in registers; widths and positions on a grid
-    hipLaunchKernelGGL(k_allocate<true>, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, n_sg_per_bucket, max_code_bits,
-                       max_width == 16, widths, pos, counts);
-    launch_positions(F, n_sg_per_bucket, n_buckets, max_width == 16, counts, widths, pos, s);
+  const bool allow16 = max_width == 16;
+  const uint32_t J = n_sg_per_bucket, rows = (J + kAllocThreads - 1) / kAllocThreads;
+  if (rows <= (uint32_t)kRegs) {
+    hipLaunchKernelGGL(k_search, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, allow16, pos, counts);
+    launch_positions(F, J, n_buckets, allow16, counts, widths, pos, s);
   } else
-    hipLaunchKernelGGL(k_allocate<false>, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, n_sg_per_bucket, max_code_bits,
-                       max_width == 16, widths, pos, counts);
+    hipLaunchKernelGGL(k_allocate_large, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, allow16, widths, pos, counts);
   return launched();
 }
 
