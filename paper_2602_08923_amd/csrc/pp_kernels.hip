@@ -4,6 +4,7 @@
 // increasing width order (Section 3.5), the means the main stage subtracts in that order
 // (Section 3.1) and the final restore (Section 3.4, last paragraph).  All of them stream each entry once; the allocation
 // works on 4 bytes per super-group.
+#include <type_traits>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -223,273 +224,303 @@ __global__ void __launch_bounds__(kAllocThreads) k_alloc_positions(const float *
   }
 }
 
-// The search for buckets of at most 64 rows of 1024, the norms' patterns in registers (kRegs per thread; every pass skips
-// the rows that the bucket does not have, four at a time).
+// The search for buckets of at most 64 rows of 1024, the norms' patterns in registers: register 4g + q of thread t holds
+// norm 4096 g + 4 t + q.  Every pass skips the groups of 4096 that the bucket does not have.
 //
 // Wanted: the smallest fp32 pattern in [1, +inf] whose allocation fits (the host has checked 2J <= budget).  With
 // c8, c4, c16 = norms at or above T_{4,8} and its tied thresholds, cost = 2J + 4 c8 + 2 c4 + 8 c16 never increases with
 // the threshold, so a bracket (lo does not fit or is 0, hi fits) is narrowed level by level: a histogram of the patterns
-// around each of the three thresholds, suffix counts, and for every bin boundary of the bracket a lower and an upper bound of its
-// cost (c8 is exact there, c4 and c16 lie between the counts of two bins).  2048 bins a level: the top 11 bits of
-// everything, then what is left of the bracket, 1 to 3 bins of 2^20, then single patterns.
+// around each of the three thresholds, suffix counts, and for the bin boundaries of the bracket a lower and an upper
+// bound of the cost (c8 is exact there, c4 and c16 lie between the counts of two bins).  The first level takes the top
+// 11 bits of everything, the second the 1 to 3 bins of 2^20 that are left in up to 4096, the third single patterns.  The
+// tied thresholds' brackets end on bins of the level before, so that the norms above them are known from its counts.
 //
-// What bounds it: one CU's vector ALU (51,200 norms are 800 wave instructions for every instruction of a pass) and
-// the barriers.  It replaced a gather of the candidates (two LDS atomics with a result per row, 20 us), a
-// bisection with a barrier per step, and full counts per step where 16 bits are allowed.
-constexpr uint32_t kBins4 = 3072, kBins16 = 5120;  // the tied thresholds' brackets in bins of the same size: up to 1.07 and 2 times as many
-__global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits, bool allow16,
+// What bounds it: one CU's vector ALU and LDS (51,200 norms are 800 wave instructions for every instruction of a pass,
+// and an LDS atomic of a wave takes 12 cycles) and, for small buckets, the barriers and scans of the levels.
+// 51,200 norms take 22 us (10 of them are the first level's and the two brackets' passes, 3 the loads and 9 x 0.4 the scans
+// and searches of the boundaries), 8192 10 us; a gather of the candidates (two LDS atomics with a result per row) with a
+// bisection, a barrier per step, took 46 and 35 us.
+constexpr uint32_t kBins8 = 4096, kBins4 = 6144, kBins16 = 8192;  // brackets of 3 bins, of 3 * 1.07 + 2 and of 3 * 2 + 2
+constexpr uint32_t kCopies = 8;
+
+// Inclusive sum over the lanes of a row of 16, and over the wave
+__device__ __forceinline__ uint32_t row_scan(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
+  return x;
+}
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+  x = row_scan(x);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row 0 into 1, row 2 into 3
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // rows 0 and 1 into 2 and 3
+  return x;
+}
+
+template <uint32_t BINS>
+struct OwnBins {
+  uint32_t n[BINS / kAllocThreads], before;
+};
+
+// The least s with x >> s < bins (bins between 2^12 and 2^13; thresholds' denormal ranges hold up to 510 patterns to one)
+__device__ __forceinline__ uint32_t shift_to(uint32_t x, uint32_t bins) {
+  const uint32_t s = x >> 13 ? 19u - (uint32_t)__builtin_clz(x) : 0u;
+  return s + (x >> s >= bins ? 1u : 0u);
+}
+
+template <bool ALLOW16>
+__global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits,
                                                           uint32_t *pos_all, uint32_t *counts_all) {
-  __shared__ uint32_t h8[kBins + 2], h4[kBins4 + 2], h16[kBins16 + 2];
-  __shared__ uint32_t wsum[3][kAllocWaves], wbase[2][kAllocWaves], wfit[2][kAllocWaves];
-  __shared__ uint32_t tot[kRegs * kAllocWaves][4];  // per (row, wave): class counts, then their exclusive scan
+  __shared__ alignas(16) uint32_t room[kBins8 + 4 + kBins4 + 4 + (ALLOW16 ? kBins16 + 4 : 8188)];  // level 1: 2049 * kCopies
+  __shared__ uint32_t wsum[3][kAllocWaves], wfit[kAllocWaves], row_n[kRegs][3];
+  uint32_t *const h8 = room, *const h4 = h8 + kBins8 + 4, *const h16 = h4 + kBins4 + 4;
   const float *F = F_all + (uint64_t)blockIdx.x * J;
   uint32_t *pos = pos_all + (uint64_t)blockIdx.x * J;
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int32_t fr[kRegs];
-  const uint32_t rows = (J + kAllocThreads - 1) / kAllocThreads;
-  auto each_row = [&](auto body) {
+  auto each_group = [&](auto body) {
 #pragma unroll
-    for (int g = 0; g < kRegs; g += 4)
-      if ((uint32_t)g < rows) {
-#pragma unroll
-        for (int k = g; k < g + 4; ++k) body(k);
-      }
+    for (int g = 0; g < kRegs / 4; ++g)
+      if (g * 4u * kAllocThreads < J) body(g);
   };
-  each_row([&](int k) { fr[k] = (int32_t)f2u(gld<float>(F + min(k * kAllocThreads + tid, J - 1))); });  // all in flight at once
-  each_row([&](int k) { fr[k] = k * kAllocThreads + tid < J ? pattern_of(u2f((uint32_t)fr[k])) : -1; });
-  auto p16_of = [&](uint32_t pattern) { return allow16 ? f2u(u2f(pattern) * (131072.0f / 257.0f)) : (uint32_t)kNever; };
-  auto p4_of = [](uint32_t pattern) { return f2u(u2f(pattern) * (17.0f / 512.0f)); };
-  // h[b] for b < PER * 1024 becomes the sum of h[b], h[b + 1], ...; two barriers, shared by up to three histograms
-  uint32_t inc[3], own[3];
-  auto sums_begin = [&](int which, const uint32_t *h, int per) {
-    uint32_t sum = 0;
-    for (int i = 0; i < per; ++i) sum += h[tid * per + i];
-    own[which] = sum;
+  auto each_norm = [&](auto body) {
+    each_group([&](int g) {
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t up = __shfl_up(sum, d, 64);
-      if (lane >= (uint32_t)d) sum += up;
-    }
-    inc[which] = sum;
-    if (lane == 63) wsum[which][wave] = sum;
+      for (int k = 4 * g; k < 4 * g + 4; ++k) body(k);
+    });
   };
-  auto sums_end = [&](int which, uint32_t *h, int per) {
-    uint32_t before = 0, all = 0;
+  each_group([&](int g) {  // all loads in flight at once; those beyond the end read the last four
+    const uint32_t e = (g * kAllocThreads + tid) * 4u;
+    if (J >= 4) {
+      typedef float Float4 __attribute__((ext_vector_type(4), aligned(4)));
+      const Float4 f = *(const __attribute__((address_space(1))) Float4 *)(uintptr_t)(F + min(e, J - 4));
 #pragma unroll
-    for (int w = 0; w < kAllocWaves; ++w) {
-      const uint32_t t = wsum[which][w];
-      before += (uint32_t)w < wave ? t : 0u;
-      all += t;
-    }
-    uint32_t left = all - (before + inc[which] - own[which]);  // from this thread's first bin on
-    for (int i = 0; i < per; ++i) {
-      const uint32_t x = h[tid * per + i];
-      h[tid * per + i] = left;
-      left -= x;
-    }
-  };
-  // How many of the bin boundaries 1 .. n-1 surely do not fit, and how many may not: the bracket is between them.
-  auto bracket = [&](uint32_t n, auto cost_bounds, uint32_t &surely, uint32_t &perhaps) {
-    uint32_t a = 0, c = 0;
-    for (uint32_t b0 = 0; b0 < n; b0 += kAllocThreads) {  // uniform trips: every thread takes part in the ballots
-      const uint32_t bin = b0 + tid;
-      bool over = false, may = false;
-      if (bin >= 1 && bin < n) {
-        uint64_t c_min, c_max;
-        cost_bounds(bin, c_min, c_max);
-        over = c_min > max_code_bits;
-        may = c_max > max_code_bits;
-      }
-      a += (uint32_t)__builtin_popcountll(__ballot(over));
-      c += (uint32_t)__builtin_popcountll(__ballot(may));
-    }
-    if (lane == 0) {
-      wfit[0][wave] = a;
-      wfit[1][wave] = c;
-    }
-    __syncthreads();
-    surely = 0;
-    perhaps = 0;
+      for (int q = 0; q < 4; ++q) fr[4 * g + q] = (int32_t)f2u(f[q]);
+    } else {
 #pragma unroll
-    for (int w = 0; w < kAllocWaves; ++w) {
-      surely += wfit[0][w];
-      perhaps += wfit[1][w];
+      for (int q = 0; q < 4; ++q) fr[4 * g + q] = (int32_t)f2u(gld<float>(F + min(e + q, J - 1)));
     }
-  };
-
-  // level 1: bins of 2^20 patterns, 2040 << 20 is +infinity
-  for (uint32_t b = tid; b < kBins + 2; b += kAllocThreads) h8[b] = 0;
-  __syncthreads();
-  each_row([&](int k) {
-    if (fr[k] >= 0) atomicAdd(&h8[(uint32_t)fr[k] >> 20], 1u);
   });
+  for (uint32_t b = tid; b < (kBins + 1) * kCopies; b += kAllocThreads) room[b] = 0;
+  if (tid < kRegs * 3) (&row_n[0][0])[tid] = 0;
+  each_group([&](int g) {
+    const uint32_t e = (g * kAllocThreads + tid) * 4u;
+    const uint32_t skip = J >= 4 && e > J - 4 ? e - (J - 4) : 0u;  // the four that were read start that much earlier
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t v = pattern_of(u2f((uint32_t)fr[4 * g + q]));
+      fr[4 * g + q] = J >= 4 ? ((uint32_t)q >= skip ? v : -1) : (e + q < J ? v : -1);
+    }
+  });
+  auto p16_of = [&](uint32_t pattern) { return f2u(u2f(pattern) * (131072.0f / 257.0f)); };
+  auto p4_of = [](uint32_t pattern) { return f2u(u2f(pattern) * (17.0f / 512.0f)); };
+  // h[b] for b < BINS becomes the sum of h[b], h[b + 1], ..., the thread's own bins in x between the two halves, which a
+  // barrier separates and up to three histograms share
+  auto sums_begin = [&](int which, auto &x) {
+    uint32_t sum = 0;
+    for (uint32_t one : x.n) sum += one;
+    const uint32_t upto = wave_scan(sum);
+    x.before = upto - sum;  // in the wave, before the thread's own bins
+    if (lane == 63) wsum[which][wave] = upto;
+  };
+  auto sums_end = [&](int which, auto &x, uint32_t *h) {
+    const uint32_t upto = row_scan(wsum[which][lane & 15u]), all = __builtin_amdgcn_readlane(upto, 15);
+    uint32_t left = all - (wave ? __builtin_amdgcn_readlane(upto, wave - 1) : 0u) - x.before;
+    uint32_t *own = h + tid * (sizeof(x.n) / 4);
+    for (uint32_t one : x.n) {
+      *own++ = left;
+      left -= one;
+    }
+  };
+  auto read_bins = [&](auto &x, const uint32_t *h) {
+    const uint32_t *own = h + tid * (sizeof(x.n) / 4);
+    for (uint32_t &one : x.n) one = *own++;
+  };
+  // The last of the bin boundaries 0 .. n-1 that surely does not fit and the last that may not (boundary 0 is the
+  // bracket's lower end): every PER-th first, then, by every wave for itself, those between.
+  auto bracket = [&](uint32_t n, auto bins, auto cost_bounds, uint32_t &surely, uint32_t &perhaps) {
+    constexpr uint32_t per = decltype(bins)::value / kAllocThreads;
+    auto fails = [&](uint32_t bin, bool &over, bool &may) {
+      uint64_t c_min = ~0ull, c_max = ~0ull;
+      if (bin) cost_bounds(min(bin, n - 1), c_min, c_max);
+      over = bin < n && c_min > max_code_bits;
+      may = bin < n && c_max > max_code_bits;
+    };
+    bool over, may;
+    fails(tid * per, over, may);
+    const uint32_t both = (uint32_t)__builtin_popcountll(__ballot(over)) + ((uint32_t)__builtin_popcountll(__ballot(may)) << 16);
+    if (lane == 0) wfit[wave] = both;
+    __syncthreads();
+    const uint32_t all = __builtin_amdgcn_readlane(row_scan(wfit[lane & 15u]), 15);
+    surely = ((all & 0xFFFFu) - 1) * per;
+    perhaps = ((all >> 16) - 1) * per;
+    const bool between = (lane & 31u) < per - 1;
+    fails((lane < 32 ? surely : perhaps) + 1 + (lane & 31u), over, may);
+    surely += (uint32_t)__builtin_popcountll(__ballot(between && lane < 32 && over));
+    perhaps += (uint32_t)__builtin_popcountll(__ballot(between && lane >= 32 && may));
+  };
+  using std::integral_constant;
+
+  // level 1: bins of 2^20 patterns, 2040 << 20 is +infinity.  The norms of a bucket share a few dozen bins: kCopies
+  // counters of each, in banks next to each other, keep the lanes of a wave from queueing for one word.  The bin before
+  // the first takes the threads beyond the bucket's end.
   __syncthreads();
-  sums_begin(0, h8, kBins / kAllocThreads);
+  uint32_t *mine = room + kCopies + (lane & (kCopies - 1));
+  each_norm([&](int k) { atomicAdd(mine + (fr[k] >> 20) * (int)kCopies, 1u); });
   __syncthreads();
-  sums_end(0, h8, kBins / kAllocThreads);
+  OwnBins<kBins> first;
+  for (uint32_t i = 0; i < kBins / kAllocThreads; ++i) {
+    first.n[i] = 0;
+#pragma unroll
+    for (uint32_t c = 0; c < kCopies; ++c) first.n[i] += room[(kBins / kAllocThreads * tid + i + 1) * kCopies + c];
+  }
+  sums_begin(0, first);
+  __syncthreads();
+  sums_end(0, first, h8);
+  if (tid < 2) h8[kBins + tid] = 0;
   __syncthreads();
   uint32_t surely, perhaps;
-  bracket(kBins - 8, [&](uint32_t b, uint64_t &c_min, uint64_t &c_max) {
-    const uint32_t b4 = p4_of(b << 20) >> 20, b16 = p16_of(b << 20) >> 20;
-    const uint64_t fixed = 2ull * J + 4ull * h8[b];
-    c_min = fixed + 2ull * h8[b4 + 1] + 8ull * h8[b16 + 1];
-    c_max = fixed + 2ull * h8[b4] + 8ull * h8[b16];
+  bracket(kBins - 8, integral_constant<int, kBins>{}, [&](uint32_t b, uint64_t &c_min, uint64_t &c_max) {
+    const uint32_t b4 = p4_of(b << 20) >> 20;
+    c_min = 2ull * J + 4ull * h8[b] + 2ull * h8[b4 + 1];
+    c_max = 2ull * J + 4ull * h8[b] + 2ull * h8[b4];
+    if (ALLOW16) {
+      const uint32_t b16 = p16_of(b << 20) >> 20;
+      c_min += 8ull * h8[b16 + 1];
+      c_max += 8ull * h8[b16];
+    }
   }, surely, perhaps);
   uint32_t lo = surely << 20, hi = (perhaps + 1) << 20;
-  uint32_t base8 = h8[perhaps + 1];  // norms at or above hi
+  uint32_t lo4 = p4_of(lo) >> 20 << 20, hi4 = ((p4_of(hi) >> 20) + 1) << 20, lo16 = 0, hi16 = 0;
+  uint32_t base8 = h8[hi >> 20], base4 = h8[hi4 >> 20], base16 = 0;  // norms at or above the brackets
+  if (ALLOW16) {
+    lo16 = p16_of(lo) >> 20 << 20;
+    hi16 = ((p16_of(hi) >> 20) + 1) << 20;
+    base16 = h8[hi16 >> 20];
+  }
 
   bool exact = false;
   while (hi - lo > 1 && !exact) {
-    const uint32_t width = hi - lo, lo4 = p4_of(lo), hi4 = p4_of(hi), lo16 = p16_of(lo), hi16 = p16_of(hi);
-    uint32_t s = 0, s4 = 0, s16 = 0;
-    while ((width - 1) >> s >= kBins) ++s;
-    while ((hi4 - lo4) >> s4 >= kBins4 || s4 < s) ++s4;
-    while ((hi16 - lo16) >> s16 >= kBins16 || s16 < s) ++s16;  // denormal thresholds: up to 510 patterns to one
+    const uint32_t width = hi - lo, width4 = hi4 - lo4, width16 = hi16 - lo16;
+    const uint32_t s = shift_to(width - 1, kBins8), s4 = shift_to(width4 - 1, kBins4), s16 = ALLOW16 ? shift_to(width16 - 1, kBins16) : 0;
     const uint32_t n = ((width - 1) >> s) + 1;
     __syncthreads();  // everybody has read the level before
-    for (uint32_t b = tid; b < kBins + 2; b += kAllocThreads) h8[b] = 0;
-    for (uint32_t b = tid; b < kBins4 + 2; b += kAllocThreads) h4[b] = 0;
-    if (allow16) for (uint32_t b = tid; b < kBins16 + 2; b += kAllocThreads) h16[b] = 0;
+    constexpr uint32_t kWords = kBins8 + 4 + kBins4 + 4 + (ALLOW16 ? kBins16 + 4 : 0);
+    for (uint32_t b = tid; b < kWords / 4; b += kAllocThreads) ((uint4 *)room)[b] = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    uint32_t above4 = 0, above16 = 0;
-    each_row([&](int k) {
+    each_norm([&](int k) {
       const uint32_t v = (uint32_t)fr[k];
       if (v - lo < width) atomicAdd(&h8[(v - lo) >> s], 1u);
-      if (v - lo4 < hi4 - lo4) atomicAdd(&h4[(v - lo4) >> s4], 1u);
-      above4 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= (int32_t)hi4));
-      if (allow16) {
-        if (v - lo16 < hi16 - lo16) atomicAdd(&h16[(v - lo16) >> s16], 1u);
-        above16 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= (int32_t)hi16));
-      }
+      if (v - lo4 < width4) atomicAdd(&h4[(v - lo4) >> s4], 1u);
+      if (ALLOW16 && v - lo16 < width16) atomicAdd(&h16[(v - lo16) >> s16], 1u);
     });
-    if (lane == 0) {
-      wbase[0][wave] = above4;
-      wbase[1][wave] = above16;
-    }
     __syncthreads();
-    sums_begin(0, h8, kBins / kAllocThreads);
-    sums_begin(1, h4, kBins4 / kAllocThreads);
-    if (allow16) sums_begin(2, h16, kBins16 / kAllocThreads);
+    OwnBins<kBins8> x8;
+    OwnBins<kBins4> x4;
+    OwnBins<kBins16> x16;
+    read_bins(x8, h8);
+    read_bins(x4, h4);
+    if (ALLOW16) read_bins(x16, h16);
+    sums_begin(0, x8);
+    sums_begin(1, x4);
+    if (ALLOW16) sums_begin(2, x16);
     __syncthreads();
-    sums_end(0, h8, kBins / kAllocThreads);
-    sums_end(1, h4, kBins4 / kAllocThreads);
-    if (allow16) sums_end(2, h16, kBins16 / kAllocThreads);
-    uint32_t base4 = 0, base16 = 0;
-#pragma unroll
-    for (int w = 0; w < kAllocWaves; ++w) {
-      base4 += wbase[0][w];
-      base16 += wbase[1][w];
-    }
+    sums_end(0, x8, h8);
+    sums_end(1, x4, h4);
+    if (ALLOW16) sums_end(2, x16, h16);
     __syncthreads();
-    bracket(n, [&](uint32_t b, uint64_t &c_min, uint64_t &c_max) {
-      const uint32_t T = lo + (b << s), b4 = (p4_of(T) - lo4) >> s4;
+    bracket(n, integral_constant<int, kBins8>{}, [&](uint32_t b, uint64_t &c_min, uint64_t &c_max) {
+      const uint32_t T = lo + (b << s), at4 = p4_of(T) - lo4, b4 = at4 >> s4;
       // a tied threshold on a bin's first pattern has that bin's count exactly
-      const bool on4 = ((p4_of(T) - lo4) & ((1u << s4) - 1u)) == 0;
       const uint64_t fixed = 2ull * J + 4ull * (base8 + h8[b]);
-      c_min = fixed + 2ull * (base4 + h4[on4 ? b4 : b4 + 1]);
+      c_min = fixed + 2ull * (base4 + h4[(at4 & ((1u << s4) - 1u)) == 0 ? b4 : b4 + 1]);
       c_max = fixed + 2ull * (base4 + h4[b4]);
-      if (allow16) {
+      if (ALLOW16) {
         const uint32_t at = p16_of(T) - lo16, b16 = at >> s16;
         c_min += 8ull * (base16 + h16[(at & ((1u << s16) - 1u)) == 0 ? b16 : b16 + 1]);
         c_max += 8ull * (base16 + h16[b16]);
       }
     }, surely, perhaps);
-    const uint32_t new_lo = surely ? lo + (surely << s) : lo;
-    const uint32_t new_hi = perhaps + 1 < n ? lo + ((perhaps + 1) << s) : hi;
-    if (perhaps + 1 < n) base8 += h8[perhaps + 1];
-    exact = new_hi - new_lo > width / 2 && new_hi - new_lo > 1;  // bounds too loose to go on: count exactly below
-    lo = new_lo;
-    hi = new_hi;
+    if (perhaps + 1 < n) {
+      hi = lo + ((perhaps + 1) << s);
+      base8 += h8[perhaps + 1];
+    }
+    lo += surely << s;
+    exact = hi - lo > width / 2 && hi - lo > 1;  // bounds too loose to go on: count exactly below
+    const uint32_t end4 = ((p4_of(hi) - lo4) >> s4) + 1;
+    base4 += h4[end4];
+    hi4 = lo4 + (end4 << s4);
+    lo4 += (p4_of(lo) - lo4) >> s4 << s4;
+    if (ALLOW16) {
+      const uint32_t end16 = ((p16_of(hi) - lo16) >> s16) + 1;
+      base16 += h16[end16];
+      hi16 = lo16 + (end16 << s16);
+      lo16 += (p16_of(lo) - lo16) >> s16 << s16;
+    }
   }
-  // Exact counts at one threshold.
+  // Exact counts at one threshold, the waves' counts in one of two buffers by turns: one barrier per round is enough.
   uint32_t turn = 0;
-  auto block_counts = [&](uint32_t pattern, uint32_t &c4, uint32_t &c8, uint32_t &c16) {
-    const int32_t p4 = p4_from(pattern), p8 = (int32_t)pattern, p16 = p16_from(pattern, allow16);
-    uint32_t a4 = 0, a8 = 0, a16 = 0;
-    each_row([&](int k) {
-      a4 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p4));
-      a8 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p8));
-      if (allow16) a16 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p16));
-    });
-    // the waves' counts meet in one of two buffers by turns, so that one barrier per round is enough
-    if (lane == 0) {
-      tot[turn * kAllocWaves + wave][0] = a4;
-      tot[turn * kAllocWaves + wave][1] = a8;
-      tot[turn * kAllocWaves + wave][2] = a16;
-    }
-    __syncthreads();
-    c4 = c8 = c16 = 0;
-#pragma unroll
-    for (int w = 0; w < kAllocWaves; ++w) {
-      c4 += tot[turn * kAllocWaves + w][0];
-      c8 += tot[turn * kAllocWaves + w][1];
-      c16 += tot[turn * kAllocWaves + w][2];
-    }
-    turn ^= 1u;
-  };
+  __syncthreads();
   while (hi - lo > 1) {
     const uint32_t mid = lo + (hi - lo) / 2;
-    uint32_t c4, c8, c16;
-    block_counts(mid, c4, c8, c16);
-    const uint64_t cost = 2ull * J + 2ull * c4 + 4ull * c8 + 8ull * c16;
+    const int32_t p4 = p4_from(mid), p8 = (int32_t)mid, p16 = p16_from(mid, ALLOW16);
+    uint32_t bits = 0;  // of the wave's norms, beyond 2 each
+    each_norm([&](int k) {
+      bits += 2u * (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p4)) + 4u * (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p8));
+      if (ALLOW16) bits += 8u * (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p16));
+    });
+    uint32_t *const all = room + turn * kAllocWaves;
+    if (lane == 0) all[wave] = bits;
+    __syncthreads();
+    const uint64_t cost = 2ull * J + __builtin_amdgcn_readlane(row_scan(all[lane & 15u]), 15);
     if (cost <= max_code_bits) hi = mid; else lo = mid;
+    turn ^= 1u;
   }
-  __syncthreads();
-  // class counts of every (row, wave), their exclusive scan in that order: the rows' first places
-  const int32_t p8 = (int32_t)hi, p4 = p4_from(hi), p16 = p16_from(hi, allow16);
-  each_row([&](int k) {
-    const int32_t v = fr[k];
-    const uint32_t at0 = (uint32_t)__builtin_popcountll(__ballot(v >= 0)), at4 = (uint32_t)__builtin_popcountll(__ballot(v >= p4)),
-                   at8 = (uint32_t)__builtin_popcountll(__ballot(v >= p8)),
-                   at16 = allow16 ? (uint32_t)__builtin_popcountll(__ballot(v >= p16)) : 0u;
-    if (lane == 0) {
-      tot[k * kAllocWaves + wave][0] = at0 - at4;
-      tot[k * kAllocWaves + wave][1] = at4 - at8;
-      tot[k * kAllocWaves + wave][2] = at8 - at16;
-      tot[k * kAllocWaves + wave][3] = at16;
+  // How many norms of each row are at or above the thresholds; the first wave turns that into the rows' first places.
+  const int32_t p8 = (int32_t)hi, p4 = p4_from(hi), p16 = p16_from(hi, ALLOW16);
+  uint32_t n4 = 0, n8 = 0, n16 = 0;  // lane g: of the wave's norms in group g
+  each_group([&](int g) {
+    uint32_t g4 = 0, g8 = 0, g16 = 0;
+#pragma unroll
+    for (int k = 4 * g; k < 4 * g + 4; ++k) {
+      g4 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p4));
+      g8 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p8));
+      if (ALLOW16) g16 += (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p16));
     }
+    n4 = lane == (uint32_t)g ? g4 : n4;
+    n8 = lane == (uint32_t)g ? g8 : n8;
+    if (ALLOW16) n16 = lane == (uint32_t)g ? g16 : n16;
   });
+  if (lane < kRegs / 4) {
+    uint32_t *const row = row_n[4 * lane + wave / 4];
+    atomicAdd(row, n4);
+    atomicAdd(row + 1, n8);
+    if (ALLOW16) atomicAdd(row + 2, n16);
+  }
   __syncthreads();
-  uint32_t x[4], sum[4];
+  if (wave == 0) {
+    const uint32_t from = lane * kAllocThreads, in_row = J > from ? min(J - from, (uint32_t)kAllocThreads) : 0u;
+    const uint32_t r4 = row_n[lane][0], r8 = row_n[lane][1], r16 = row_n[lane][2];
+    const uint32_t x[4] = {in_row - r4, r4 - r8, r8 - r16, r16};
+    uint32_t n_class[4], first[4], class_first = 0;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    x[c] = tid < rows * kAllocWaves ? tot[tid][c] : 0u;
-    sum[c] = x[c];
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t up = __shfl_up(sum[c], d, 64);
-      if (lane >= (uint32_t)d) sum[c] += up;
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t upto = wave_scan(x[c]);
+      n_class[c] = __builtin_amdgcn_readlane(upto, 63);
+      first[c] = class_first + upto - x[c];
+      class_first += n_class[c];
     }
-  }
-  __syncthreads();
-  if (lane == 63) {
+    if (from + kAllocThreads < J) {  // not the last row
 #pragma unroll
-    for (int c = 0; c < 4; ++c) h8[4 * wave + c] = sum[c];
-  }
-  __syncthreads();
-  uint32_t n_class[4], row_first[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    uint32_t before = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kAllocWaves; ++w) {
-      const uint32_t t = h8[4 * w + c];
-      before += (uint32_t)w < wave ? t : 0u;
-      all += t;
+      for (int c = 0; c < 4; ++c) gst<uint32_t>(pos + from + c, first[c]);
     }
-    n_class[c] = all;
-    row_first[c] = before + sum[c] - x[c];
-  }
-  const uint32_t row = tid / kAllocWaves, class_first[4] = {0u, n_class[0], n_class[0] + n_class[1], n_class[0] + n_class[1] + n_class[2]};
-  if (tid % kAllocWaves == 0 && (row + 1) * kAllocThreads < J) {  // not the last row
+    if (lane == 0) {
+      uint32_t *cnt = counts_all + 5ull * blockIdx.x;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) gst<uint32_t>(pos + row * kAllocThreads + c, class_first[c] + row_first[c]);
-  }
-  if (tid == 0) {
-    uint32_t *cnt = counts_all + 5ull * blockIdx.x;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) gst<uint32_t>(cnt + c, n_class[c]);
-    gst<uint32_t>(cnt + 4, hi);
+      for (int c = 0; c < 4; ++c) gst<uint32_t>(cnt + c, n_class[c]);
+      gst<uint32_t>(cnt + 4, hi);
+    }
   }
 }
 
@@ -798,7 +829,8 @@ dq_status dq_allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_bucke
   const bool allow16 = max_width == 16;
   const uint32_t J = n_sg_per_bucket, rows = (J + kAllocThreads - 1) / kAllocThreads;
   if (rows <= (uint32_t)kRegs) {
-    hipLaunchKernelGGL(k_search, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, allow16, pos, counts);
+    if (allow16) hipLaunchKernelGGL(k_search<true>, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, pos, counts);
+    else hipLaunchKernelGGL(k_search<false>, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, pos, counts);
     launch_positions(F, J, n_buckets, allow16, counts, widths, pos, s);
   } else
     hipLaunchKernelGGL(k_allocate_large, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, allow16, widths, pos, counts);
