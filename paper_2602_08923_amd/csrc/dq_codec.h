@@ -47,7 +47,13 @@ __device__ __forceinline__ uint4 gld16(const void *p) {
   const u32x4 t = gld<u32x4>(p);
   return make_uint4(t.x, t.y, t.z, t.w);
 }
-
+// A store that leaves the caches first, for the fp32 results: whole lines, the largest stream a launch writes, and none of its own
+// reads.  Sinks of 125 M entries 193 -> 187 us, eight 25 MB buffers' ring 78 -> 75 us.  (The packed codes and the loads
+// are better off in the caches, where the next launch or the neighbouring tile finds them.)
+template <typename T>
+__device__ __forceinline__ void gst_once(void *p, T v) {
+  __builtin_nontemporal_store(v, (__attribute__((address_space(1))) T *)p);
+}
 // ---- Philox4x32-10 (Salmon et al., SC'11): counter-based, so every lane draws its numbers
 // from (global group index, round, stream, rank) alone.
 struct U4 {
@@ -283,7 +289,7 @@ __device__ __forceinline__ void store_tile_f32(const Job &job, const Params &P, 
     const f32x4 o = lds_ldf4(xpose + w * 64 + ((c ^ ((w >> 2) & 3u)) * 16));
     // row r is one super-group, 1 KB: at its place in the chunk, or where job.dest sends it
     const size_t sg = job.dest ? (size_t)gld<uint32_t>(job.dest + sg0 + r) : sg0 + r;
-    gst<f32x4>(reinterpret_cast<float4 *>(out + sg * kSG) + lane, o);
+    gst_once<f32x4>(reinterpret_cast<float4 *>(out + sg * kSG) + lane, o);
   }
   __builtin_amdgcn_wave_barrier();
 }

@@ -21,10 +21,13 @@
 namespace dq {
 namespace {
 
-constexpr int kWalkWaves = 8;           // waves per block: they share one copy of the tables
-constexpr int kWalkThreads = kWalkWaves * 64;
+// Waves per SIMD, as many as the kernel's vector registers allow: 94 for a ring or chain of bf16 tensors, 101 to 127 for the
+// others.  (Five are 3 % faster than four where a wave has a few tiles, 25 MB through a ring of eight.)
+template <typename LT, bool TREE>
+constexpr int kWalkPerSimd = sizeof(LT) == 2 && !TREE ? 5 : 4;
 constexpr uint32_t kParkBytes = 1280;   // per wave: 64 scale draws of 16 bytes, 64 permutation slots
 constexpr uint32_t kXposeBytes = 2048;  // per wave: half a tile of fp32 results
+static_assert(4 * kParkBytes <= (kOffTab4 - kOffDec2) * 4, "a ring's draws lie over the decode tables");
 
 __device__ __forceinline__ void lds_st1(uint32_t a, uint32_t v) {
   *reinterpret_cast<__attribute__((address_space(3))) uint32_t *>(a) = v;
@@ -128,7 +131,7 @@ __device__ __forceinline__ void store_result(const Job &job, const Params &P, fl
       const uint32_t slot = q * 64 + lane, w = slot >> 2, c = slot & 3u;
       const f32x4 o = lds_ldf4(xpose + w * 64 + ((c ^ ((w >> 2) & 3u)) * 16));
       const size_t sg = job.dest ? (size_t)gld<uint32_t>(job.dest + sg0 + r) : sg0 + r;
-      gst<f32x4>(reinterpret_cast<float4 *>(out + sg * kSG) + lane, o);
+      gst_once<f32x4>(reinterpret_cast<float4 *>(out + sg * kSG) + lane, o);
     }
   }
   __builtin_amdgcn_wave_barrier();
@@ -142,6 +145,8 @@ struct Areas {
 enum { kNone = 0, kLevels = 1, kCodes = 2, kBoth = 3 };
 template <int N>
 struct How { static constexpr int value = N; };
+template <bool B>
+struct Is { static constexpr bool value = B; };
 
 // `len` consecutive tiles of width B from `pos` on.
 template <int B, typename LT, bool MU, bool TREE>
@@ -156,8 +161,8 @@ __device__ __forceinline__ void walk_tiles(const WalkPath &path, const Params &P
   for (uint32_t t = 0; t < len; ++t) {
     TilePos pos_next = pos;
     pos_next.tile_first += kWaveSGs;
-    const bool more = t + 1 < len;
     uint64_t at_next = at;
+    const bool more = t + 1 < len;
     if (more) at_next = slice_at<LT, MU>(job, pos_next, &mu_next);
     const uint32_t rowc = min(lane >> 4, pos.n_seg - 1 - pos.tile_first);
     const uint64_t gi = (job.first_sg + pos.seg_first + pos.tile_first + rowc) * 16 + g;  // global group index
@@ -168,7 +173,7 @@ __device__ __forceinline__ void walk_tiles(const WalkPath &path, const Params &P
     // encoding (kNone: it is the last).  The loops below are written so that every encoding variant has a body of its
     // own: behind a branch the compiler computes what the variants share for all 16 entries first and runs
     // out of registers.
-    auto leaf = [&](uint32_t i, bool has, uint32_t taken, auto how) {
+    auto leaf = [&](uint32_t i, bool has, uint32_t taken, auto how, auto is_last) {
       constexpr int kHow = decltype(how)::value;
       const uint32_t rank = leaf_of<TREE>(W, path.chunk, i);
       Draws d;
@@ -189,9 +194,12 @@ __device__ __forceinline__ void walk_tiles(const WalkPath &path, const Params &P
 #pragma unroll
         for (int k = 0; k < 16; ++k) v[k] = v[k] - mu;
       }
-      // the next leaf's entries, or the next tile's first
-      if (i + 1 < W.n) s = load_slice<LT>(W, leaf_of<TREE>(W, path.chunk, i + 1), at);
-      else if (more) s = load_slice<LT>(W, leaf_of<TREE>(W, path.chunk, 0u), at_next);
+      // the next leaf's entries, or the next tile's first.  Where there is none s is nothing, not what it was: to keep that the
+      // compiler would load into other registers, and wait for the data at every leaf's end to move it here.
+      Slice<LT> next;
+      if constexpr (!decltype(is_last)::value) next = load_slice<LT>(W, leaf_of<TREE>(W, path.chunk, i + 1), at);
+      else if (more) next = load_slice<LT>(W, leaf_of<TREE>(W, path.chunk, 0u), at_next);
+      s = next;
       if (has) {
 #pragma unroll
         for (int k = 0; k < 16; ++k) v[k] = __builtin_fmaf(level[k], sfg, v[k]);
@@ -234,24 +242,24 @@ __device__ __forceinline__ void walk_tiles(const WalkPath &path, const Params &P
     if constexpr (TREE) {
 #pragma unroll 1
       for (uint32_t i = 0;; i += 2) {
-        leaf(i, false, 0, How<kLevels>());
+        leaf(i, false, 0, How<kLevels>(), Is<false>());
         taken = __builtin_ctz(~(i >> 1));  // trailing ones above the lowest bit: the messages this node takes
         if (i + 1 == last) break;
-        leaf(i + 1, true, taken, How<kCodes>());
+        leaf(i + 1, true, taken, How<kCodes>(), Is<false>());
       }
     } else {
       uint32_t i = 0;
 #pragma unroll 1
-      for (; i < W.first_kept; ++i) leaf(i, i > 0, 0, How<kLevels>());
+      for (; i < W.first_kept; ++i) leaf(i, i > 0, 0, How<kLevels>(), Is<false>());
 #pragma unroll 1
-      for (; i < last; ++i) leaf(i, i > 0, 0, How<kBoth>());
+      for (; i < last; ++i) leaf(i, i > 0, 0, How<kBoth>(), Is<false>());
     }
     if (gathered) {  // what every worker decodes from the sink's message
-      leaf(last, true, taken, How<kLevels>());
+      leaf(last, true, taken, How<kLevels>(), Is<true>());
 #pragma unroll
       for (int k = 0; k < 16; ++k) v[k] = level[k] * sfg;
     } else {
-      leaf(last, true, taken, How<kNone>());
+      leaf(last, true, taken, How<kNone>(), Is<true>());
     }
     store_result(job, P, v, A.xpose, pos);
     pos = pos_next;
@@ -343,23 +351,23 @@ __device__ __forceinline__ void walk_range(const WalkPath &path, const Params &P
 
 // Wave w takes the tiles from S.shares[w] up to S.shares[w + 1] of the paths laid end to end (split_walk).
 template <typename LT, bool MU, bool TREE>
-__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_walk(const WalkPath *paths, const WalkShare *shares,
-                                                                                           Walk W, Params P) {
+__global__ __launch_bounds__((TREE ? 512 : 256)) __attribute__((amdgpu_waves_per_eu((kWalkPerSimd<LT, TREE>)))) void k_walk(
+    const WalkPath *paths, const WalkShare *shares, Walk W, Params P) {
   extern __shared__ uint4 lds_raw[];
   uint32_t *lds = reinterpret_cast<uint32_t *>(lds_raw);
   const uint32_t waves = blockDim.x / 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
-  for (int r = 0; r < kRanges; ++r)  // tables of widths no chunk has are left out; ring and chain never decode from codes
-    if (P.range_width[r] > 2 || (W.widths >> P.range_width[r] & 1u))
-      for (uint32_t i = P.range_lo[r] + threadIdx.x * 4; i < P.range_hi[r]; i += blockDim.x * 4)
+  for (int r = 0; r < kRanges; ++r)  // tables of widths no chunk has are left out, and a ring or chain never decodes from codes
+    if ((P.range_width[r] > 2 || (W.widths >> P.range_width[r] & 1u)) && (TREE || r != 1))
+      for (uint32_t i = (!TREE && r == 2 ? kOffTab4 : P.range_lo[r]) + threadIdx.x * 4; i < P.range_hi[r]; i += blockDim.x * 4)
         *reinterpret_cast<uint4 *>(&lds[i]) = gld16(&P.blob[i]);
   __syncthreads();
   const uint32_t v = __builtin_amdgcn_readfirstlane(blockIdx.x * waves + wave);
   const WalkShare from = table_entry(shares, v), to = table_entry(shares, v + 1);
   Areas A;
   const uint32_t end = P.blob_dwords * 4;
-  A.park = end + wave * kParkBytes;
-  A.stack = end + waves * kParkBytes + wave * (TREE ? W.stack_bytes : kXposeBytes);
+  A.park = (TREE ? end : kOffDec2 * 4) + wave * kParkBytes;  // ring, chain: over the decode tables, which they do not copy
+  A.stack = end + (TREE ? waves * kParkBytes : 0u) + wave * (TREE ? W.stack_bytes : kXposeBytes);
   A.xpose = A.stack;  // the stack is empty when a tile's result is stored
   const Vec V(P);
   for (uint32_t p = from.path, lo = from.tile; p < to.path || (p == to.path && lo < to.tile); ++p, lo = 0) {
@@ -375,7 +383,7 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4)
 }
 
 uint32_t walk_lds(const Params &P, bool tree, uint32_t stack_bytes, uint32_t waves) {
-  return P.blob_dwords * 4 + waves * (kParkBytes + (tree ? stack_bytes : kXposeBytes));
+  return P.blob_dwords * 4 + waves * (tree ? kParkBytes + stack_bytes : kXposeBytes);
 }
 
 template <typename LT, bool MU, bool TREE>
@@ -393,7 +401,7 @@ hipError_t go_walk(const WalkPath *paths, const WalkShare *shares, const Walk &W
 // halving.  With less than two tiles per wave the count decides: a wave with one tile more takes twice as long whatever its width.
 static const uint32_t kCosts[2][4] = {{1, 1, 1, 1}, {6, 11, 12, 6}};
 
-bool grid_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W) {
+bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W) {
   uint64_t tiles = 0;
   W->widths = 0;
   for (uint32_t p = 0; p < W->n_paths; ++p)
@@ -403,13 +411,15 @@ bool grid_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths,
       if (t) W->widths |= 1u << w;
     }
   if (tiles == 0) return false;
-  // blocks of eight waves share a copy of the tables; where there are fewer tiles than two waves for every SIMD, blocks of four
-  // reach all CUs
-  W->waves = tiles < (uint64_t)n_cu * 8 ? 4 : kWalkWaves;
+  // A butterfly's two blocks per CU share a copy of the tables each; where there are fewer tiles than two waves for every
+  // SIMD, blocks of four reach all CUs.  Rings and chains always take blocks of four, 29 KB at the levels of 25 MB and n = 8: five per CU.
+  // (Blocks of ten waves put three waves on two of the SIMDs, and the CU has no room for the second one: 97 us, not 75.)
+  const uint32_t most = 4 * (tree ? kWalkPerSimd<float, true> : (dtype == DQ_F32 ? kWalkPerSimd<float, false> : kWalkPerSimd<uint16_t, false>));
+  W->waves = tree && tiles >= (uint64_t)n_cu * 8 ? 8 : 4;
   const uint32_t lds = walk_lds(P, tree, W->stack_bytes, W->waves);
   uint32_t per_cu = 160u * 1024 / lds;
   if (per_cu == 0) return false;
-  if (per_cu > 16 / W->waves) per_cu = 16 / W->waves;
+  if (per_cu > most / W->waves) per_cu = most / W->waves;
   const uint64_t needed = (tiles + W->waves - 1) / W->waves;
   W->blocks = n_cu * per_cu;
   if (W->blocks > needed) W->blocks = (uint32_t)needed;
