@@ -102,7 +102,7 @@ struct WalkShare {
   uint32_t path, tile;
 };
 constexpr uint32_t kStackCoded = 1280, kStackRaw = 2048;  // bytes of a pending message per wave: codes and scale, or raw bf16
-bool grid_walk(const Params &P, bool tree, uint32_t n_cu, const WalkPath *paths_host, Walk *W);  // false: no launch fits
+bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths_host, Walk *W);  // false: no launch fits
 void split_walk(const WalkPath *paths_host, const Walk &W, std::vector<WalkShare> *shares);
 hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W,
                        const Params &P, hipStream_t stream);
@@ -112,7 +112,7 @@ hipError_t launch_one(Kind kind, dq_dtype dtype, bool has_local, const Job &job,
                       hipStream_t stream);
 // gather: some job of the batch has a `src` (jobs without one still take the contiguous path)
 hipError_t launch_batch(Kind kind, dq_dtype dtype, bool has_local, bool gather, const Job *jobs_dev, uint32_t n_jobs,
-                        uint32_t max_tiles_per_job, uint64_t total_tiles, const Params &p, uint32_t grid_blocks,
+                        uint32_t max_tiles_per_job, const Params &p, uint32_t grid_blocks,
                         hipStream_t stream);
 
 // 16 zero bytes at a 16-byte aligned device address, written by a kernel

@@ -156,7 +156,7 @@ __device__ __forceinline__ void tile_da(const Job &job, const Params &P, uint32_
 // Decompress-accumulate over `len` consecutive tiles of width B: the tile's operands are those of a DAR
 // hop (fetch<.., kDar, ..>); the next tile is requested before the current one's transpose and stores.
 template <int B, typename LT, bool MU>
-__device__ __forceinline__ void run_tiles_da(const Job &job, const Params &P, uint32_t xpose, TilePos pos, uint32_t len) {
+__device__ __forceinline__ void run_tiles_da(const Job &job, const Params &P, uint32_t xpose, TilePos pos, uint32_t len, uint32_t step) {
   constexpr uint32_t rec0 = kRec0;
   Fetch<B, kDar, LT> f = fetch<B, kDar, LT, MU>(job, pos);
   for (uint32_t i = 0; i < len; ++i) {
@@ -170,9 +170,11 @@ __device__ __forceinline__ void run_tiles_da(const Job &job, const Params &P, ui
     const float sfg = (float)f.rg_in * sf_over_255(f.sf_in, rec0);
     each_level<B, HopTables>(f.cw, [&](int k, float t) { v[k] = __builtin_fmaf(t, sfg, v[k]); });
     TilePos pos_next = pos;
-    pos_next.tile_first += kWaveSGs;
-    if (i + 1 < len) f = fetch<B, kDar, LT, MU>(job, pos_next);
+    pos_next.tile_first += step;
+    Fetch<B, kDar, LT> next;
+    if (i + 1 < len) next = fetch<B, kDar, LT, MU>(job, pos_next);
     store_tile_f32(job, P, v, xpose, tb.first_entry, tb.last_row);
+    f = next;
     pos = pos_next;
   }
 }
@@ -231,17 +233,17 @@ __device__ __forceinline__ void tile16(const Job &job, const Params &P, uint32_t
 
 // `len` consecutive tiles of width B starting at `pos` (their parked draws 128 bytes apart).
 template <int B, Kind KIND, typename LT, bool MU>
-__device__ __forceinline__ void run_tiles(const Job &job, const Params &P, const Vec &V, uint32_t stage, TilePos pos,
-                                          uint32_t len) {
+__device__ __forceinline__ void run_tiles(const Job &job, const Params &P, const Vec &V, uint32_t stage, uint32_t stage_step,
+                                          TilePos pos, uint32_t len, uint32_t step) {
   // The next tile of the run is requested from inside the current one (see compute's `ahead`): with five waves
   // per SIMD a wave's own wait for its tile is no longer covered by the others (measured: 3-7 % on the 25 MB
   // and the 100-bucket configurations, nothing on the largest launches).
   Fetch<B, KIND, LT> f = fetch<B, KIND, LT, MU>(job, pos);
   for (uint32_t i = 0; i < len; ++i) {
-    Fetch<B, KIND, LT> next = f;
+    Fetch<B, KIND, LT> next;  // nothing where there is no next tile, not f: see walk_tiles
     TilePos pos_next = pos;
-    pos_next.tile_first += kWaveSGs;
-    const Encoded<B> e = compute<B, KIND, LT, MU>(job, P, V, stage + i * 128, pos, f, [&] {
+    pos_next.tile_first += step;
+    const Encoded<B> e = compute<B, KIND, LT, MU>(job, P, V, stage + i * stage_step, pos, f, [&] {
       if (i + 1 < len) next = fetch<B, KIND, LT, MU>(job, pos_next);
     });
     put<B>(job, pos, e);
@@ -250,14 +252,13 @@ __device__ __forceinline__ void run_tiles(const Job &job, const Params &P, const
   }
 }
 
-// Per-SG draws of `nb` <= 8 consecutive tiles starting at tile `t_first`, made by one wave-wide
+// Per-SG draws of nb <= 8 tiles, tile(0) to tile(nb - 1), made by one wave-wide
 // Philox call and parked at `area` (128 bytes per tile: row r at [32r] this worker's slot of the
 // shared permutation, at [32r+16] the worker's group-scale stream).  Lane l draws for tile l/8, row (l%8)/2.
-__device__ __forceinline__ void park_draws(const Job &job, const Params &P, uint32_t t_first, uint32_t nb,
-                                           uint32_t area) {
+template <typename F>
+__device__ __forceinline__ void park_draws(const Job &job, const Params &P, uint32_t nb, uint32_t area, F tile) {
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t j = min(lane >> 3, nb - 1);
-  const TilePos p = locate(job, t_first + j);
+  const TilePos p = locate(job, tile(min(lane >> 3, nb - 1)));
   const uint32_t sgw = min(p.tile_first + ((lane >> 1) & 3u), p.n_seg - 1);
   const uint64_t G = job.first_sg + p.seg_first + sgw;
   const uint32_t c3 = (lane & 1u) ? ((1u << 16) | (job.rank & 0xFFFFu)) : ((2u << 16) | 0xFFFFu);
@@ -267,72 +268,86 @@ __device__ __forceinline__ void park_draws(const Job &job, const Params &P, uint
   lds_st4(area + lane * 16, u32x4{w0, d.y, d.z, d.w});
 }
 
-// Tiles [t_first, t_first + nb) of the job, whose draws are parked from `area` on.
+// A wave's tiles: first, first + stride, ... (n of them).
+struct Tiles {
+  uint32_t first, stride, n;
+};
+// How many of them, from the one at `p` on, are of its width, at most n
+__device__ __forceinline__ uint32_t same_width(const TilePos &p, uint32_t stride, uint32_t n) {
+  const uint32_t left = (p.n_seg - p.tile_first + kWaveSGs - 1) / kWaveSGs;  // tiles to the segment's end
+  return min(n, (left + stride - 1) / stride);
+}
+
+// Tiles T of the job, the draws of the first parked at `area`, the others' stage_step bytes apart.
 template <Kind KIND, typename LT>
-__device__ __forceinline__ void run_range(const Job &job, const Params &P, const Vec &V, uint32_t area,
-                                          uint32_t t_first, uint32_t nb) {
-  for (uint32_t j = 0; j < nb;) {
-    const TilePos p = locate(job, t_first + j);
-    const uint32_t left = (p.n_seg - p.tile_first + kWaveSGs - 1) / kWaveSGs;  // tiles to the segment's end
-    const uint32_t len = min(nb - j, left);
-    const uint32_t stage = area + j * 128;
+__device__ __forceinline__ void run_range(const Job &job, const Params &P, const Vec &V, uint32_t area, uint32_t stage_step, Tiles T) {
+  const uint32_t step = T.stride * kWaveSGs;
+  while (T.n) {
+    const TilePos p = locate(job, T.first);
+    const uint32_t len = same_width(p, T.stride, T.n);
     // two builds of the tile loop, with and without means: a branch on job.mu inside a tile makes the
     // path without means wait, at the branch's join, for the loads issued before it
     if (job.mu) {
-      if (p.wi == 0) run_tiles<2, KIND, LT, true>(job, P, V, stage, p, len);
-      else if (p.wi == 1) run_tiles<4, KIND, LT, true>(job, P, V, stage, p, len);
-      else if (p.wi == 2) run_tiles<8, KIND, LT, true>(job, P, V, stage, p, len);
+      if (p.wi == 0) run_tiles<2, KIND, LT, true>(job, P, V, area, stage_step, p, len, step);
+      else if (p.wi == 1) run_tiles<4, KIND, LT, true>(job, P, V, area, stage_step, p, len, step);
+      else if (p.wi == 2) run_tiles<8, KIND, LT, true>(job, P, V, area, stage_step, p, len, step);
     } else {
-      if (p.wi == 0) run_tiles<2, KIND, LT, false>(job, P, V, stage, p, len);
-      else if (p.wi == 1) run_tiles<4, KIND, LT, false>(job, P, V, stage, p, len);
-      else if (p.wi == 2) run_tiles<8, KIND, LT, false>(job, P, V, stage, p, len);
+      if (p.wi == 0) run_tiles<2, KIND, LT, false>(job, P, V, area, stage_step, p, len, step);
+      else if (p.wi == 1) run_tiles<4, KIND, LT, false>(job, P, V, area, stage_step, p, len, step);
+      else if (p.wi == 2) run_tiles<8, KIND, LT, false>(job, P, V, area, stage_step, p, len, step);
     }
     if (p.wi > 2) {
       TilePos q = p;
-      for (uint32_t i = 0; i < len; ++i, q.tile_first += kWaveSGs) tile16<KIND, LT>(job, P, 0u, q);
+      for (uint32_t i = 0; i < len; ++i, q.tile_first += step) tile16<KIND, LT>(job, P, 0u, q);
     }
-    j += len;
+    T.first += len * T.stride;
+    T.n -= len;
+    area += len * stage_step;
   }
 }
 
-// Decompress(+accumulate) over the job's tiles [w_lo, w_hi): tile by tile without a local slice, in
+// Decompress(+accumulate) over the tiles T of the job: tile by tile without a local slice, in
 // runs of one width (the next tile requested ahead) with one.
 template <typename LT>
-__device__ __forceinline__ void da_range(const Job &job, const Params &P, uint32_t xpose, uint32_t w_lo, uint32_t w_hi) {
+__device__ __forceinline__ void da_range(const Job &job, const Params &P, uint32_t xpose, Tiles T) {
   if constexpr (__is_same(LT, NoLocal)) {
-    for (uint32_t t = w_lo; t < w_hi; ++t) {
-      const TilePos p = locate(job, t);
+    for (; T.n; --T.n, T.first += T.stride) {
+      const TilePos p = locate(job, T.first);
       if (p.wi == 0) tile_da<2, LT>(job, P, xpose, p);
       else if (p.wi == 1) tile_da<4, LT>(job, P, xpose, p);
       else if (p.wi == 2) tile_da<8, LT>(job, P, xpose, p);
       else tile16<kDecompress, LT>(job, P, xpose, p);
     }
   } else {
-    for (uint32_t t = w_lo; t < w_hi;) {  // runs of one width, as in run_range
-      const TilePos p = locate(job, t);
-      const uint32_t left = (p.n_seg - p.tile_first + kWaveSGs - 1) / kWaveSGs;
-      const uint32_t len = min(w_hi - t, left);
+    const uint32_t step = T.stride * kWaveSGs;
+    while (T.n) {  // runs of one width, as in run_range
+      const TilePos p = locate(job, T.first);
+      const uint32_t len = same_width(p, T.stride, T.n);
       if (job.mu) {
-        if (p.wi == 0) run_tiles_da<2, LT, true>(job, P, xpose, p, len);
-        else if (p.wi == 1) run_tiles_da<4, LT, true>(job, P, xpose, p, len);
-        else if (p.wi == 2) run_tiles_da<8, LT, true>(job, P, xpose, p, len);
+        if (p.wi == 0) run_tiles_da<2, LT, true>(job, P, xpose, p, len, step);
+        else if (p.wi == 1) run_tiles_da<4, LT, true>(job, P, xpose, p, len, step);
+        else if (p.wi == 2) run_tiles_da<8, LT, true>(job, P, xpose, p, len, step);
       } else {
-        if (p.wi == 0) run_tiles_da<2, LT, false>(job, P, xpose, p, len);
-        else if (p.wi == 1) run_tiles_da<4, LT, false>(job, P, xpose, p, len);
-        else if (p.wi == 2) run_tiles_da<8, LT, false>(job, P, xpose, p, len);
+        if (p.wi == 0) run_tiles_da<2, LT, false>(job, P, xpose, p, len, step);
+        else if (p.wi == 1) run_tiles_da<4, LT, false>(job, P, xpose, p, len, step);
+        else if (p.wi == 2) run_tiles_da<8, LT, false>(job, P, xpose, p, len, step);
       }
       if (p.wi > 2) {
         TilePos q = p;
-        for (uint32_t i = 0; i < len; ++i, q.tile_first += kWaveSGs) tile16<kDecompress, LT>(job, P, xpose, q);
+        for (uint32_t i = 0; i < len; ++i, q.tile_first += step) tile16<kDecompress, LT>(job, P, xpose, q);
       }
-      t += len;
+      T.first += len * T.stride;
+      T.n -= len;
     }
   }
 }
 
-// The job's tiles are split evenly over all waves of the grid row (4 * gridDim.x waves):
-// wave w takes [w*T/W, (w+1)*T/W).  The launcher sizes the grid to what the GPU holds at
-// once, so a wave lives for the whole launch and the table copy is paid once.
+// The job's tiles go round the waves of the grid row (4 * gridDim.x waves): wave w takes w, w + W, w + 2W, ...  What the
+// waves read and write at one time is then one window of each stream, in the order of its addresses, and not W places in
+// it; and every wave meets the widths in about the same shares, so that they end together (2-bit tiles are cheaper).  The
+// launcher sizes the grid to what the GPU holds at once, so a wave lives for the whole launch and the table copy is paid
+// once.  Measured against shares of consecutive tiles: the sink of 125 M entries 191 -> 187.5 us, a hop of as many the
+// same with half the blocks that consecutive shares needed to even the widths out, 6400 super-groups' compress 5.6 -> 5.4 us.
 template <Kind KIND, typename LT>
 __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
   extern __shared__ uint4 lds_raw[];
@@ -341,28 +356,23 @@ __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
   const uint32_t t0 = (n0 + kWaveSGs - 1) / kWaveSGs, t1 = (n1 + kWaveSGs - 1) / kWaveSGs,
                  t2 = (n2 + kWaveSGs - 1) / kWaveSGs, t3 = (job.n_sg[3] + kWaveSGs - 1) / kWaveSGs;
   const uint32_t total = t0 + t1 + t2 + t3;
-  // even split of the tiles over the grid's waves in 32-bit arithmetic: wave v takes q tiles
-  // from v*q + min(v, r), one more if v < r (q, r = quotient and remainder of tiles by waves)
-  const uint32_t n_waves = gridDim.x * kBlockWaves;
-  const uint32_t q = total / n_waves, r = total - q * n_waves;
+  const uint32_t n_waves = gridDim.x * kBlockWaves, q = total / n_waves, r = total - q * n_waves;
   const uint32_t bw = blockIdx.x * kBlockWaves;
-  const uint32_t b_lo = bw * q + min(bw, r);
-  const uint32_t b_hi = (bw + kBlockWaves) * q + min(bw + kBlockWaves, r);
-  if (b_lo >= b_hi) return;
+  if (q == 0 && bw >= r) return;
   constexpr uint32_t lds0 = kLds0;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t wv = bw + wave;
-  const uint32_t w_lo = wv * q + min(wv, r);
-  const uint32_t w_hi = w_lo + q + (wv < r ? 1u : 0u);
+  const uint32_t mine = q + (bw + wave < r ? 1u : 0u);
   // parking area for per-SG draws: 1 KB (8 tiles) per wave, the four areas contiguous
   // (decompress needs no search tables: its blocks leave them out and are small enough for six per CU)
   const uint32_t park0 = lds0 + (KIND == kDecompress ? kOffLut4 : P.blob_dwords) * 4;
   // a block with at most 32 tiles makes all its draws up front, 8 tiles per wave-wide call,
-  // instead of one call per wave (waves of a small job hold only a tile or two each)
-  const bool block_draws = KIND != kDecompress && (b_hi - b_lo) <= 8u * kBlockWaves;
+  // instead of one call per wave (waves of a small job hold only a tile or two each): the block's tile k is wave k % 4's
+  const uint32_t in_block = q * kBlockWaves + min(r - min(r, bw), (uint32_t)kBlockWaves);
+  const bool block_draws = KIND != kDecompress && in_block <= 8u * kBlockWaves;
 
-  // copy the common tables and the table ranges of the widths this block meets; the first
-  // 16 bytes per thread of every range are requested together (one round trip, not six)
+  // copy the common tables and the table ranges of the widths this block meets (all, if it goes round the job more than
+  // once); the first 16 bytes per thread of every range are requested together (one round trip, not six)
+  const uint32_t b_hi = q ? total : min(bw + kBlockWaves, total), b_lo = q ? 0u : bw;
   const bool meets[4] = {b_lo < t0, b_lo < t0 + t1 && b_hi > t0, b_lo < t0 + t1 + t2 && b_hi > t0 + t1, true};
   constexpr int kEarly = kRanges;
   uint4 first[kEarly];
@@ -377,8 +387,11 @@ __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
     if (has[r]) first[r] = gld16(&P.blob[i]);
   }
   if constexpr (KIND != kDecompress) {
-    if (block_draws && 8u * wave < b_hi - b_lo)
-      park_draws(job, P, b_lo + 8u * wave, min(8u, b_hi - b_lo - 8u * wave), park0 + wave * 1024);
+    if (block_draws && 8u * wave < in_block)
+      park_draws(job, P, min(8u, in_block - 8u * wave), park0 + wave * 1024, [&](uint32_t j) {
+        const uint32_t k = 8u * wave + j;
+        return (k / kBlockWaves) * n_waves + bw + k % kBlockWaves;
+      });
   }
 #pragma unroll
   for (int r = 0; r < kEarly; ++r)
@@ -393,14 +406,18 @@ __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
   [[maybe_unused]] const uint32_t area = park0 + wave * 1024;     // compress, DAR: this wave's parked draws
   [[maybe_unused]] const uint32_t xpose = park0 + wave * (64 * 64);  // decompress: its transpose area, 64 lanes x 64 bytes
   const Vec V(P);
+  Tiles T = {bw + wave, n_waves, mine};
   if constexpr (KIND == kDecompress) {
-    da_range<LT>(job, P, xpose, w_lo, w_hi);
+    da_range<LT>(job, P, xpose, T);
+  } else if (block_draws) {
+    __builtin_amdgcn_wave_barrier();
+    run_range<KIND, LT>(job, P, V, park0 + wave * 128, kBlockWaves * 128, T);
   } else {
-    for (uint32_t tb = w_lo; tb < w_hi; tb += kBatch) {
-      const uint32_t nb = min((uint32_t)kBatch, w_hi - tb);
-      if (!block_draws) park_draws(job, P, tb, nb, area);
+    for (uint32_t left = mine; left; left -= T.n, T.first += T.n * n_waves) {
+      T.n = min((uint32_t)kBatch, left);
+      park_draws(job, P, T.n, area, [&](uint32_t j) { return T.first + j * n_waves; });
       __builtin_amdgcn_wave_barrier();
-      run_range<KIND, LT>(job, P, V, block_draws ? park0 + (tb - b_lo) * 128 : area, tb, nb);
+      run_range<KIND, LT>(job, P, V, area, 128u, T);
       __builtin_amdgcn_wave_barrier();
     }
   }
@@ -441,13 +458,13 @@ __global__ __launch_bounds__(kBlockThreads) void k_batch_small(const Job *jobs, 
   if (tiles == 0) return;
   const uint32_t park0 = kLds0 + (KIND == kDecompress ? kOffLut4 : P.blob_dwords) * 4;
   if constexpr (KIND == kDecompress) {
-    da_range<LT>(job, P, park0 + wave * (64 * 64), 0u, tiles);
+    da_range<LT>(job, P, park0 + wave * (64 * 64), Tiles{0u, 1u, tiles});
   } else {
     const Vec V(P);
     const uint32_t area = park0 + wave * 1024;
-    park_draws(job, P, 0u, tiles, area);
+    park_draws(job, P, tiles, area, [](uint32_t j) { return j; });
     __builtin_amdgcn_wave_barrier();
-    run_range<KIND, LT>(job, P, V, area, 0u, tiles);
+    run_range<KIND, LT>(job, P, V, area, 128u, Tiles{0u, 1u, tiles});
   }
 }
 
@@ -478,13 +495,7 @@ uint32_t job_tiles(const Job &j) {
 // Grid shape: `grid_blocks` (what the GPU holds at once: CUs x blocks per CU, fixed when the
 // context is made) shared between the jobs of the launch (one block holds 4 waves; a wave
 // then walks its share of the job's tiles).
-// Compress and DAR launches with many tiles per wave take twice the grid: the second half's blocks start wherever a
-// first one ends, which evens out what the even split by tile count leaves uneven (2-bit tiles are cheaper).  A 125 M entry hop at
-// 5 bits: 100.5 -> 97 us; three and four times the grid gain no more, and below 12 tiles per wave the second copy
-// of the tables costs more than it gives.  Decompress launches are bound by memory alone: no gain.
-template <Kind KIND>
-uint32_t blocks_per_job(uint32_t max_tiles, uint64_t total_tiles, uint32_t n_jobs, uint32_t grid_blocks) {
-  if (KIND != kDecompress && total_tiles >= 12ull * kBlockWaves * grid_blocks) grid_blocks *= 2;
+uint32_t blocks_per_job(uint32_t max_tiles, uint32_t n_jobs, uint32_t grid_blocks) {
   uint32_t blocks = (grid_blocks + n_jobs - 1) / n_jobs;
   const uint32_t needed = (max_tiles + kBlockWaves - 1) / kBlockWaves;
   if (blocks > needed) blocks = needed;
@@ -501,12 +512,12 @@ hipError_t go_one(const Job &job, Params p, uint32_t grid_blocks, hipStream_t s)
   const uint32_t tiles = job_tiles(job);
   if (tiles == 0) return hipSuccess;
   p.guard = armed_guard();
-  const uint32_t blocks = blocks_per_job<KIND>(tiles, tiles, 1, grid_blocks);
+  const uint32_t blocks = blocks_per_job(tiles, 1, grid_blocks);
   hipLaunchKernelGGL((k_one<KIND, LT>), dim3(blocks), dim3(kBlockThreads), lds_bytes(p, KIND), s, job, p);
   return hipGetLastError();
 }
 template <Kind KIND, typename LT>
-hipError_t go_batch(const Job *jobs, uint32_t n_jobs, uint32_t max_tiles, uint64_t total_tiles, Params p,
+hipError_t go_batch(const Job *jobs, uint32_t n_jobs, uint32_t max_tiles, Params p,
                     uint32_t grid_blocks, hipStream_t s) {
   if (n_jobs == 0 || max_tiles == 0) return hipSuccess;
   if (max_tiles <= (uint32_t)kBatch && n_jobs >= grid_blocks) {  // so many small jobs that a block per job would queue up
@@ -514,7 +525,7 @@ hipError_t go_batch(const Job *jobs, uint32_t n_jobs, uint32_t max_tiles, uint64
                        lds_bytes(p, KIND), s, jobs, n_jobs, p);
     return hipGetLastError();
   }
-  const uint32_t blocks = blocks_per_job<KIND>(max_tiles, total_tiles, n_jobs, grid_blocks);
+  const uint32_t blocks = blocks_per_job(max_tiles, n_jobs, grid_blocks);
   // the grid's y dimension (one row per job) holds at most 65,535 rows: more jobs take more launches
   for (uint32_t first = 0; first < n_jobs; first += kMaxGridRows) {
     const uint32_t rows = n_jobs - first < kMaxGridRows ? n_jobs - first : kMaxGridRows;
@@ -545,14 +556,14 @@ hipError_t launch_one(Kind kind, dq_dtype dtype, bool has_local, const Job &job,
 }
 
 hipError_t launch_batch(Kind kind, dq_dtype dtype, bool has_local, bool gather, const Job *jobs, uint32_t n_jobs,
-                        uint32_t max_tiles, uint64_t total_tiles, const Params &p, uint32_t grid_blocks, hipStream_t s) {
+                        uint32_t max_tiles, const Params &p, uint32_t grid_blocks, hipStream_t s) {
   const bool f32 = dtype == DQ_F32;
-#define ARGS (jobs, n_jobs, max_tiles, total_tiles, p, grid_blocks, s)
+#define ARGS (jobs, n_jobs, max_tiles, p, grid_blocks, s)
   switch (kind) {
     case kCompress: return DQ_DISPATCH_LOCAL(go_batch, kCompress);
     case kDar: return DQ_DISPATCH_LOCAL(go_batch, kDar);
     default:
-      if (!has_local) return go_batch<kDecompress, NoLocal>(jobs, n_jobs, max_tiles, total_tiles, p, grid_blocks, s);
+      if (!has_local) return go_batch<kDecompress, NoLocal>(jobs, n_jobs, max_tiles, p, grid_blocks, s);
       return DQ_DISPATCH_LOCAL(go_batch, kDecompress);
   }
 #undef ARGS

@@ -36,7 +36,6 @@ struct Launch {
   uint32_t n_jobs = 0;
   size_t table_off = 0;  // byte offset of this launch's job table in scratch
   uint32_t max_tiles = 0;
-  uint64_t total_tiles = 0;
   uint64_t max_entries = 0;
   uint64_t entries = 0;
 };
@@ -133,7 +132,7 @@ void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, 
   const uint32_t levels = w.log_n > 1 ? w.log_n - 1 : 1;
   w.stack_bytes = levels * (raw ? dq::kStackRaw : dq::kStackCoded);
   if (w.stack_bytes < 2048) w.stack_bytes = 2048;
-  plan->walk = dq::grid_walk(ctx->params, plan->tree, ctx->n_cu, plan->paths.data(), &w);
+  plan->walk = dq::grid_walk(ctx->params, d->dtype, plan->tree, ctx->n_cu, plan->paths.data(), &w);
   if (!plan->walk) {
     plan->paths.clear();
     return;
@@ -432,7 +431,6 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
         const uint32_t tiles = (j.n_sg[0] + 3) / 4 + (j.n_sg[1] + 3) / 4 + (j.n_sg[2] + 3) / 4 + (j.n_sg[3] + 3) / 4;
         const uint64_t e = ((uint64_t)j.n_sg[0] + j.n_sg[1] + j.n_sg[2] + j.n_sg[3]) * 256;
         if (tiles > L.max_tiles) L.max_tiles = tiles;
-        L.total_tiles += tiles;
         if (e > L.max_entries) L.max_entries = e;
         L.entries += e;
       }
@@ -606,7 +604,7 @@ static dq_status run_step(dq_replay *plan, size_t i, hipStream_t s, int only = -
                               L.n_jobs, L.max_entries, plan->ctx->n_cu, s);
     else
       e = dq::launch_batch(L.kind, L.dtype, L.has_local, L.gather, reinterpret_cast<const dq::Job *>(plan->scratch + L.table_off),
-                           L.n_jobs, L.max_tiles, L.total_tiles, plan->ctx->params, plan->ctx->grid_blocks, s);
+                           L.n_jobs, L.max_tiles, plan->ctx->params, plan->ctx->grid_blocks, s);
     if (e != hipSuccess) return dq::hip_status(e);
   }
   return DQ_OK;
