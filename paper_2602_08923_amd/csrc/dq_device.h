@@ -86,13 +86,15 @@ struct WalkPath {
   uint32_t chunk;
 };
 struct Walk {
-  const void *const *grads;  // device: the workers' tensors
+  const void *const *grads;  // device: the workers' tensors, all twice
   uint32_t n, log_n;         // workers (log_n: butterfly)
   uint32_t encodes;          // how many leaves are followed by an encoding: n - 1, or n with the all-gather
   uint32_t first_kept;       // ring, chain: first step whose message is written
   uint32_t chain;            // 1: leaf i is worker i
   uint32_t hops_log;         // log2 of the hops one call of the per-super-group draws covers
-  uint32_t stack_bytes;      // butterfly: LDS per wave for the pending messages
+  uint32_t levels, raw;      // butterfly: messages that can be pending beside the one in registers; whether some chunk has 16-bit super-groups
+  uint32_t stack_bytes;      // LDS per wave for them
+  uint32_t tile_sgs;         // super-groups of a wave's tile: 4 (dq_walk.hip), 2 or 1 (dq_thin.hip)
   uint32_t n_paths;
   uint32_t widths;           // which widths some chunk has (bit k: 2 << k bits)
   uint32_t blocks, waves;    // grid, waves per block
@@ -102,6 +104,10 @@ struct WalkShare {
   uint32_t path, tile;
 };
 constexpr uint32_t kStackCoded = 1280, kStackRaw = 2048;  // bytes of a pending message per wave: codes and scale, or raw bf16
+uint32_t thin_lds(const Params &P, uint32_t stack_bytes);           // per block
+uint32_t thin_stack(uint32_t tile_sgs, uint32_t levels);            // per wave
+hipError_t launch_thin(dq_dtype dtype, bool tree, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W, const Params &P,
+                       hipStream_t stream);
 bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths_host, Walk *W);  // false: no launch fits
 void split_walk(const WalkPath *paths_host, const Walk &W, std::vector<WalkShare> *shares);
 hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W,

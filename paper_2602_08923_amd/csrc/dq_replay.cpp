@@ -128,10 +128,8 @@ void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, 
       p.chunk = c;
       raw = raw || x.n_sg[3] != 0;
     }
-  // butterfly: a pending message for every level above the first; the area also stages half a tile's result
-  const uint32_t levels = w.log_n > 1 ? w.log_n - 1 : 1;
-  w.stack_bytes = levels * (raw ? dq::kStackRaw : dq::kStackCoded);
-  if (w.stack_bytes < 2048) w.stack_bytes = 2048;
+  w.levels = plan->tree && w.log_n > 1 ? w.log_n - 1 : 0;
+  w.raw = raw;
   plan->walk = dq::grid_walk(ctx->params, d->dtype, plan->tree, ctx->n_cu, plan->paths.data(), &w);
   if (!plan->walk) {
     plan->paths.clear();
@@ -145,7 +143,7 @@ void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, 
   *off += ((size_t)w.blocks * w.waves + 1) * sizeof(dq::WalkShare);
   *off = align_up(*off, 256);
   plan->grads_off = *off;
-  *off += (size_t)n * sizeof(void *);
+  *off += 2 * (size_t)n * sizeof(void *);
 }
 
 void plan_mx_walk(const dq_ctx *ctx, const dq_replay_desc *d, uint32_t n_chunks, uint64_t m, float *out, Plan *plan, size_t *off) {
@@ -172,7 +170,7 @@ void plan_mx_walk(const dq_ctx *ctx, const dq_replay_desc *d, uint32_t n_chunks,
   plan->walk = true;
   *off = align_up(*off, 256);
   plan->grads_off = *off;
-  *off += (size_t)n * sizeof(void *);
+  *off += 2 * (size_t)n * sizeof(void *);
 }
 
 // Builds the whole schedule.  With base == nullptr only sizes are computed (pointers are
@@ -534,7 +532,9 @@ dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *
       up.put(p.paths_off, p.paths.data(), p.paths.size() * sizeof(dq::WalkPath));
       up.put(p.shares_off, p.shares.data(), p.shares.size() * sizeof(dq::WalkShare));
     }
-    up.put(p.grads_off, worker_grads, (size_t)ctx->cfg.n_workers * sizeof(void *));
+    std::vector<const void *> twice;  // every tensor twice: a ring's order from any worker on is a run of entries
+    for (int k = 0; k < 2; ++k) twice.insert(twice.end(), worker_grads, worker_grads + ctx->cfg.n_workers);
+    up.put(p.grads_off, twice.data(), twice.size() * sizeof(void *));
     p.w.grads = p.mx.grads = reinterpret_cast<const void *const *>(r->scratch + p.grads_off);
     std::vector<dq::WalkPath>().swap(p.paths);
     std::vector<dq::WalkShare>().swap(p.shares);

@@ -1,0 +1,409 @@
+// A whole replay in one launch, as dq_walk.hip, for schedules with few super-groups: a lane holds E = 4 or 8 entries of
+// a group, not all 16, so a wave's tile is E / 4 super-groups and there are 16 / E times as many waves.
+//
+// Why: a tile's hops are a serial chain.  With a tile of four super-groups per wave, a schedule of fewer than some 4,000
+// super-groups leaves most SIMDs with one wave or none, and a hop takes 1.08 us whatever the size: the instructions of 16
+// entries one after the other, then the next slice's trip from memory.  With 4 entries per lane the chain of a hop is a
+// quarter of it, and the slices are requested four hops ahead (they are two registers each): 0.45 us per hop.  Measured, bf16, wide
+// tile to E = 8 to E = 4: ring of 100, 1,000 super-groups, 115 -> 70 -> 50 us; 64 workers' recursive halving 96 -> 50 -> 35;
+// ring of 256, 4,096 super-groups of 2 to 16 bits, 283 -> 213 -> 214.  grid_walk (dq_walk.hip) says which schedules come here.
+//
+// What differs from the wide tile:
+//   draws    : a lane draws the group's 16 bytes for ONE of the next 16 / E hops, and the group's lanes exchange them through
+//              LDS: per hop and group one generator call, as before.  Per-super-group draws cover 256 / E hops at a time.
+//   maxima   : within a group by quad permutes, within a super-group by row rotates and row / half-wave swaps.
+//   rounding : levels are looked up with 1 / maximum while the stored scales are still being worked out.  A group whose
+//              scale rounds to zero then has levels that are not zero, but they are multiplied by zero.
+//   messages : pending ones are signed levels and scale, also those of a recursive halving in LDS: nothing is decoded.
+//   result   : a lane's entries are whole 16-byte pieces, stored as they are.
+#include "dq_walk.h"
+
+namespace dq {
+namespace {
+
+constexpr uint32_t kAhead = 4;  // hops a slice is requested ahead of its use
+constexpr uint32_t kThinPark = 1280;   // per wave: 64 scale draws of 16 bytes, 64 permutation slots
+constexpr uint32_t kThinDraws = 1536;  // per wave: 64 groups' (of some hop) 16 bytes, their rounding offset and scale dither
+constexpr uint32_t kThinWaves = 4;     // per block
+static_assert(kThinWaves * kThinDraws <= (kOffTab4 - kOffDec2) * 4, "the draws lie over the decode tables, which are not copied");
+
+template <int E>
+constexpr uint32_t kThinStack = E * 256 + 256;  // per wave and level: signed levels and scale
+
+__device__ __forceinline__ void lds_st2(uint32_t a, u32x2 v) {
+  *reinterpret_cast<__attribute__((address_space(3))) u32x2 *>(a) = v;
+}
+__device__ __forceinline__ void lds_turn() {  // the wave's LDS writes before here, its reads after
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <typename LT, int E>
+struct Bit {
+  uint32_t w[E * sizeof(LT) / 4];  // a lane's E entries, raw
+};
+template <typename LT, int E>
+__device__ __forceinline__ Bit<LT, E> load_bit(uint64_t tensor, uint64_t at) {
+  constexpr int kWords = E * sizeof(LT) / 4;
+  const uint8_t *p = reinterpret_cast<const uint8_t *>(tensor) + at;
+  Bit<LT, E> s;
+  if constexpr (kWords == 2) {
+    const u32x2 t = gld<u32x2>(p);
+    s.w[0] = t.x; s.w[1] = t.y;
+  } else {
+#pragma unroll
+    for (int i = 0; i < kWords / 4; ++i) {
+      const u32x4 t = gld<u32x4>(p + 16 * i);
+      s.w[4 * i] = t.x; s.w[4 * i + 1] = t.y; s.w[4 * i + 2] = t.z; s.w[4 * i + 3] = t.w;
+    }
+  }
+  return s;
+}
+
+// Address of the i-th tensor a chunk meets.  (The table holds every tensor twice: a ring's leaves are consecutive entries.)
+template <bool TREE>
+__device__ __forceinline__ uint64_t tensor_of(const Walk &W, uint32_t chunk, uint32_t i) {
+  return table_entry(reinterpret_cast<const uint64_t *>(W.grads), TREE ? leaf_of<TREE>(W, chunk, i) : (W.chain ? 0u : chunk) + i);
+}
+
+// Maximum of magnitudes over the lanes of a group, then over those of a super-group.
+template <int E>
+__device__ __forceinline__ uint32_t group_max(uint32_t x) {
+  x = max(x, dpp_u<0xB1>(x));                        // quad_perm 1,0,3,2
+  if constexpr (E == 4) x = max(x, dpp_u<0x4E>(x));  // quad_perm 2,3,0,1
+  return x;
+}
+template <int E>
+__device__ __forceinline__ uint32_t sg_max(uint32_t x) {  // x: the group's maximum
+  if constexpr (E == 8) x = max(x, dpp_u<0x122>(x));  // row_ror:2
+  x = max(x, dpp_u<0x124>(x));                        // row_ror:4
+  x = max(x, dpp_u<0x128>(x));                        // row_ror:8
+  const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);  // rows 0 and 1, 2 and 3
+  x = max(a[0], a[1]);
+  if constexpr (E == 4) {
+    const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);  // the wave's halves
+    x = max(b[0], b[1]);
+  }
+  return x;
+}
+
+// What a wave holds of a tile before it walks it: where it is and the slices of its first hops.
+template <typename LT, int E>
+struct Start {
+  TilePos pos;
+  uint64_t at;  // byte offset of the lane's entries inside every worker's tensor
+  float mu;
+  Bit<LT, E> s[kAhead];
+};
+
+template <typename LT, bool TREE, int E>
+__device__ __forceinline__ Start<LT, E> start_tile(const WalkPath &path, const Walk &W, uint32_t t) {
+  constexpr uint32_t kSgs = E / 4;
+  const Job &job = path.job;
+  Start<LT, E> x;
+  uint32_t first = 0, w = 0;
+#pragma unroll
+  for (; w < 3; ++w) {
+    const uint32_t tiles = (job.n_sg[w] + kSgs - 1) / kSgs;
+    if (t < tiles) break;
+    t -= tiles;
+    first += job.n_sg[w];
+  }
+  x.pos = TilePos{first, w == 0 ? job.n_sg[0] : w == 1 ? job.n_sg[1] : w == 2 ? job.n_sg[2] : job.n_sg[3], t * kSgs, (int)w};
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t row = min(lane * kSgs / 64u, x.pos.n_seg - 1 - x.pos.tile_first);
+  const uint32_t sg0 = first + x.pos.tile_first + row;
+  const uint64_t sg = job.src ? (uint64_t)gld<uint32_t>(job.src + sg0) : (uint64_t)sg0;
+  x.mu = job.mu ? gld<float>(job.mu + sg0) : 0.0f;  // taking off 0 changes nothing
+  x.at = (uint64_t)reinterpret_cast<uintptr_t>(job.local) + sg * (kSG * sizeof(LT)) + (lane & (64u / kSgs - 1u)) * (E * (uint32_t)sizeof(LT));
+#pragma unroll
+  for (uint32_t j = 0; j < kAhead; ++j) {
+    x.s[j] = load_bit<LT, E>(tensor_of<TREE>(W, path.chunk, min(j, W.n - 1)), x.at);
+  }
+  return x;
+}
+
+// Places of the tile in a packed chunk, worked out here and now: the compiler would otherwise keep them in registers around
+// the hops of which only two write a message.
+template <int B>
+__device__ __forceinline__ TileBase<B> tile_base_here(const Job &job, const TilePos &pos) {
+  Job j = job;
+  TilePos p = pos;
+  asm volatile("" : "+s"(j.n_sg[0]), "+s"(j.n_sg[1]), "+s"(j.n_sg[2]), "+s"(j.n_sg[3]), "+s"(p.seg_first), "+s"(p.tile_first));
+  return TileBase<B>(j, p);
+}
+
+// B: 2, 4, 8, or 16 (raw: the message is the partial sum rounded to bf16)
+template <int B, typename LT, bool TREE, int E>
+__device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P, const Vec &V, const Walk &W, uint32_t park, uint32_t draws,
+                                          uint32_t stack0, Start<LT, E> &x) {
+  constexpr uint32_t kLanes = 16 / E, kSgs = E / 4, kHops = 64 / kSgs;  // lanes per group, super-groups per tile, hops per park
+  const Job &job = path.job;
+  const TilePos pos = x.pos;
+  const uint32_t lane = threadIdx.x & 63u, q = lane & (kLanes - 1u), g = (lane / kLanes) & 15u;
+  const uint32_t row = min(lane * kSgs / 64u, pos.n_seg - 1 - pos.tile_first);
+  const uint64_t gi = (job.first_sg + pos.seg_first + pos.tile_first + row) * 16 + g;  // global group index
+  const uint32_t last = W.n - 1;
+  float v[E], level[E], sfg = 0.0f;  // the pending message: level * sfg
+#pragma unroll
+  for (int k = 0; k < E; ++k) level[k] = -0.0f;  // nothing pending: adding -0 changes nothing
+
+  // kAhead hops from i0 on.  PLAIN: all of them encode, none writes its message, and the slices to request exist.
+  auto some_hops = [&](uint32_t i0, auto plain) {
+    constexpr bool PLAIN = decltype(plain)::value;
+    uint64_t tensor[kAhead];
+#pragma unroll
+    for (uint32_t j = 0; j < kAhead; ++j) tensor[j] = tensor_of<TREE>(W, path.chunk, PLAIN ? i0 + kAhead + j : min(i0 + kAhead + j, last));
+#pragma unroll
+    for (uint32_t j = 0; j < kAhead; ++j) {
+      // A hop past the last (the last four may be fewer) does nothing but load: behind a condition, or a way out of the loop, the
+      // compiler would load into other registers and wait at every hop's end to move the data.
+      const uint32_t i = i0 + j;
+      __builtin_amdgcn_sched_barrier(0);
+      float y[E];
+      if constexpr (sizeof(LT) == 4) {
+#pragma unroll
+        for (int k = 0; k < E; ++k) y[k] = u2f(x.s[j].w[k]) - x.mu;
+      } else {
+#pragma unroll
+        for (int k = 0; k < E / 2; ++k) {
+          y[2 * k] = u2f(x.s[j].w[k] << 16) - x.mu;
+          y[2 * k + 1] = u2f(x.s[j].w[k] & 0xFFFF0000u) - x.mu;
+        }
+      }
+      // past the last hop: the last slice again, out of the cache
+      x.s[j] = load_bit<LT, E>(tensor[j], x.at);
+      if (PLAIN || i <= last) {
+        if constexpr (B != 16) {
+          if (j % kLanes == 0) {
+            if (j == 0 && (i & (kHops - 1u)) == 0) {  // the super-groups' draws of the next kHops hops: lane = hop, super-group
+              const uint32_t r = min(lane & (kSgs - 1u), pos.n_seg - 1 - pos.tile_first);
+              const uint64_t G = job.first_sg + pos.seg_first + pos.tile_first + r;
+              const uint32_t rank = leaf_of<TREE>(W, path.chunk, min(i + lane / kSgs, last));
+              const U4 shared = philox4x32_10((uint32_t)G, (uint32_t)(G >> 32), P.round, (2u << 16) | 0xFFFFu, P.key0, P.key1);
+              const U4 scale = philox4x32_10((uint32_t)G, (uint32_t)(G >> 32), P.round, (1u << 16) | (rank & 0xFFFFu), P.key0, P.key1);
+              lds_turn();
+              lds_st4(park + lane * 16, u32x4{scale.x, scale.y, scale.z, scale.w});
+              lds_st1(park + 1024 + lane * 4, perm_slot(shared, P, rank));
+              lds_turn();
+            }
+            // the groups' draws of the next kLanes hops: lane q of a group draws for hop i + q
+            const uint32_t slot = ((i + q) & (kHops - 1u)) * kSgs + row;
+            const Draws d = draw_group(P, gi, leaf_of<TREE>(W, path.chunk, min(i + q, last)), lds_ld1(park + 1024 + slot * 4),
+                                       lds_ld1(park + slot * 16 + (g >> 2) * 4), g);
+            lds_turn();
+            lds_st4(draws + q * (64 * E) + (lane / kLanes) * 16, u32x4{d.gam.x, d.gam.y, d.gam.z, d.gam.w});
+            lds_st2(draws + 1024 + q * (512 / kLanes) + (lane / kLanes) * 8, u32x2{f2u(d.o_pi), f2u(d.us)});
+            lds_turn();
+          }
+        }
+        uint32_t gam[E / 4];
+        u32x2 offset = {0, 0};
+        if constexpr (B != 16) {
+          constexpr uint32_t kHop = 64 * E;
+          const uint32_t jj = j % kLanes;
+          if constexpr (E == 4) {
+            gam[0] = lds_ld1(draws + jj * kHop + lane * 4);
+          } else {
+            const u32x2 t = lds_ld2(draws + jj * kHop + lane * 8);
+            gam[0] = t.x; gam[1] = t.y;
+          }
+          offset = lds_ld2(draws + 1024 + jj * (512 / kLanes) + (lane / kLanes) * 8);
+        }
+#pragma unroll
+        for (int k = 0; k < E; ++k) v[k] = y[k];
+        if (!TREE || (j & 1)) {
+#pragma unroll
+          for (int k = 0; k < E; ++k) v[k] = B == 16 ? level[k] + v[k] : __builtin_fmaf(level[k], sfg, v[k]);
+        }
+        uint32_t stack = stack0;
+        if constexpr (TREE) {
+          if (j == 3) {
+#pragma unroll 1
+            for (uint32_t up = i >> 1; up & 1u; up >>= 1, stack += kThinStack<E>) {
+              const float f = u2f(lds_ld1(stack + E * 256 + lane * 4));
+#pragma unroll
+              for (int h = 0; h < E / 4; ++h) {
+                const f32x4 t = lds_ldf4(stack + h * 1024 + lane * 16);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[4 * h + k] = B == 16 ? t[k] + v[4 * h + k] : __builtin_fmaf(t[k], f, v[4 * h + k]);
+              }
+            }
+          }
+        }
+        if (PLAIN || i < W.encodes) {
+          const bool keep = !TREE && !PLAIN && i >= W.first_kept && i < last;  // the message is written
+          if constexpr (B == 16) {
+            uint32_t w[E / 2];
+#pragma unroll
+            for (int k = 0; k < E / 2; ++k) {
+              w[k] = bf16_rne_pair(v[2 * k], v[2 * k + 1]);
+              level[2 * k] = u2f(w[k] << 16);
+              level[2 * k + 1] = u2f(w[k] & 0xFFFF0000u);
+            }
+            if (keep) {
+              uint8_t *dst = path.msg[i & 1u] + tile_base_here<16>(job, pos).code_off + (row * 16 + g) * 32 + q * (2 * E);
+              if constexpr (E == 4) gst<u32x2>(dst, u32x2{w[0], w[1]});
+              else gst<u32x4>(dst, u32x4{w[0], w[1], w[2], w[3]});
+            }
+          } else {
+            float m = 0.0f;
+#pragma unroll
+            for (int k = 0; k < E; ++k) m = fmaxf(m, fabsf(v[k]));
+            const uint32_t mg = group_max<E>(f2u(m));
+            m = u2f(mg);
+            // Levels: a stored scale above zero implies m > 2^-118 (the super-group's is at least 2^-100, and the dither at least
+            // 1/512), so the bound only keeps the quotient finite where the levels do not count.
+            const float inv = m >= 0x1p-120f ? 1.0f / m : 0.0f;
+            // The scales, as in scale_group.  A super-group that is encoded as zero has its groups' maxima taken as zero instead of
+            // its results: as conditional results the compiler puts the chain behind a branch, after the levels' lookups.
+            uint32_t b = sg_max<E>(mg) + 0xFFFFu;
+            const bool tiny = b < 0x0D800000u;
+            b = tiny ? 0u : b;
+            const uint32_t sfb = b >> 16, ex = b & 0x7F800000u;
+            const u32x2 rec = lds_ld2(kRec0 + ((b >> 13) & 0x3F8u));
+            float xs[E];
+            u32x4 t[E];
+            auto uniform = [&](int k) { return __builtin_fmaf((float)((gam[k >> 2] >> (8 * (k & 3))) & 0xFFu), V.s_n, u2f(offset.x)); };
+            if constexpr (B == 2) {
+#pragma unroll
+              for (int k = 0; k < E; ++k) xs[k] = v[k] * inv;
+            } else {
+              u32x2 e[E];
+#pragma unroll
+              for (int k = 0; k < E; ++k) {
+                xs[k] = v[k] * inv;
+                e[k] = lds_ld2(f2u(fabsf(xs[k]) + (B == 4 ? V.magic4 : V.magic8)) & 0x1FFF8u);
+              }
+              __builtin_amdgcn_sched_barrier(0);  // all searches, then all levels: two trips to LDS, not eight
+#pragma unroll
+              for (int k = 0; k < E; ++k) t[k] = lds_ld4(or_and(f2u(fabsf(xs[k]) - u2f(e[k].x)) >> 27, 16u, e[k].y));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            const float ts = fminf((tiny ? 0.0f : m) * u2f(rec.y - ex), 255.0f), fl = floorf(ts);
+            const uint32_t rg = (uint32_t)fl + ((u2f(offset.y) < ts - fl) ? 1u : 0u);
+            sfg = (float)rg * fabsf(u2f(rec.x + ex));  // (without an exponent to add, the table's pattern has the sign bit)
+            bool up[E];
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+              const float ax = fabsf(xs[k]);
+              if constexpr (B == 2) {
+                up[k] = uniform(k) < ax;
+                level[k] = u2f(or_and(f2u(xs[k]), V.top, f2u(up[k] ? 1.0f : 0.0f)));
+              } else {
+                up[k] = __builtin_fmaf(uniform(k), u2f(t[k].y), u2f(t[k].x)) < ax;
+                level[k] = u2f(or_and(f2u(xs[k]), V.top, up[k] ? t[k].z : t[k].x));
+              }
+            }
+            if (keep) {
+              const TileBase<B> tb = tile_base_here<B>(job, pos);
+              uint8_t *out = path.msg[i & 1u];
+              const uint32_t lg = row * 16 + g;
+              uint64_t word = 0;
+#pragma unroll
+              for (int k = E - 1; k >= 0; --k) {
+                const uint32_t index = B == 2 ? 0u : t[k].w >> (32 - B);
+                word = (word << B) | (f2u(xs[k]) >> 31 << (B - 1)) | (rg ? index + (up[k] ? 1u : 0u) : 0u);
+              }
+              uint8_t *cp = out + tb.code_off + lg * (2 * B) + q * (E * B / 8);
+              if constexpr (E * B == 8) gst<uint8_t>(cp, (uint8_t)word);
+              else if constexpr (E * B == 16) gst<uint16_t>(cp, (uint16_t)word);
+              else if constexpr (E * B == 32) gst<uint32_t>(cp, (uint32_t)word);
+              else gst<u32x2>(cp, u32x2{(uint32_t)word, (uint32_t)(word >> 32)});
+              gst<uint8_t>(out + tb.gs_off + lg, (uint8_t)rg);  // all lanes of a group, of a super-group: the same value
+              gst<uint16_t>(out + tb.sf_off + row * 2, (uint16_t)sfb);
+            }
+          }
+          if constexpr (TREE) {
+            if ((j & 1) && (PLAIN || i < last)) {
+#pragma unroll
+              for (int h = 0; h < E / 4; ++h)
+                lds_stf4(stack + h * 1024 + lane * 16, f32x4{level[4 * h], level[4 * h + 1], level[4 * h + 2], level[4 * h + 3]});
+              lds_st1(stack + E * 256 + lane * 4, f2u(sfg));
+            }
+          }
+        }
+      }
+    }
+  };
+  uint32_t i0 = 0;
+  for (; i0 + 2 * kAhead <= W.n && (TREE || i0 + kAhead <= W.first_kept); i0 += kAhead) some_hops(i0, Is<true>());
+  for (; i0 < W.n; i0 += kAhead) some_hops(i0, Is<false>());
+  if (W.encodes == W.n) {  // what every worker decodes from the sink's message
+#pragma unroll
+    for (int k = 0; k < E; ++k) v[k] = B == 16 ? level[k] + 0.0f : level[k] * sfg;
+  }
+  const size_t sg0 = (size_t)pos.seg_first + pos.tile_first + row;
+  if (job.back) {
+    const float back = (float)P.n_workers * gld<float>(job.back + sg0);
+#pragma unroll
+    for (int k = 0; k < E; ++k) v[k] = v[k] + back;
+  }
+  const size_t sg = job.dest ? (size_t)gld<uint32_t>(job.dest + sg0) : sg0;
+  float *out = static_cast<float *>(job.out) + sg * kSG + (lane & (64u / kSgs - 1u)) * E;
+#pragma unroll
+  for (int h = 0; h < E / 4; ++h) gst_once<f32x4>(out + 4 * h, f32x4{v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]});
+}
+
+template <typename LT, bool TREE, int E>
+__global__ __launch_bounds__(kThinWaves * 64) __attribute__((amdgpu_waves_per_eu((E == 4 || sizeof(LT) == 2 ? 4 : 3)))) void k_thin(
+    const WalkPath *paths, const WalkShare *shares, Walk W, Params P) {
+  extern __shared__ uint4 lds_raw[];
+  uint32_t *lds = reinterpret_cast<uint32_t *>(lds_raw);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t share = __builtin_amdgcn_readfirstlane(blockIdx.x * kThinWaves + wave);
+  WalkShare at = table_entry(shares, share);
+  const WalkShare to = table_entry(shares, share + 1);
+  const bool any = at.path < to.path || (at.path == to.path && at.tile < to.tile);
+  WalkPath path;
+  Start<LT, E> x;
+  if (any) {  // the first tile's entries are on their way while the tables are copied
+    path = table_entry(paths, at.path);
+    x = start_tile<LT, TREE, E>(path, W, at.tile);
+  }
+#pragma unroll
+  for (int r = 0; r < kRanges; ++r)  // tables of widths no chunk has are left out, and nothing is decoded from codes
+    if ((P.range_width[r] > 2 || (W.widths >> P.range_width[r] & 1u)) && r != 1)
+      for (uint32_t i = (r == 2 ? kOffTab4 : r == 3 ? kOffTab8 : P.range_lo[r]) + threadIdx.x * 4; i < P.range_hi[r]; i += kThinWaves * 64 * 4)
+        *reinterpret_cast<uint4 *>(&lds[i]) = gld16(&P.blob[i]);
+  __syncthreads();
+  if (!any) return;
+  const uint32_t draws = kOffDec2 * 4 + wave * kThinDraws, park = P.blob_dwords * 4 + wave * kThinPark;
+  const uint32_t stack = P.blob_dwords * 4 + kThinWaves * kThinPark + wave * W.stack_bytes;
+  const Vec V(P);
+  for (;;) {
+    if (x.pos.wi == 0) walk_thin<2, LT, TREE, E>(path, P, V, W, park, draws, stack, x);
+    else if (x.pos.wi == 1) walk_thin<4, LT, TREE, E>(path, P, V, W, park, draws, stack, x);
+    else if (x.pos.wi == 2) walk_thin<8, LT, TREE, E>(path, P, V, W, park, draws, stack, x);
+    else walk_thin<16, LT, TREE, E>(path, P, V, W, park, draws, stack, x);
+    ++at.tile;
+    uint32_t tiles = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) tiles += (path.job.n_sg[w] + E / 4 - 1) / (E / 4);
+    if (at.tile == tiles) { ++at.path; at.tile = 0; }
+    if (at.path > to.path || (at.path == to.path && at.tile >= to.tile)) break;
+    path = table_entry(paths, at.path);
+    x = start_tile<LT, TREE, E>(path, W, at.tile);
+  }
+}
+
+template <typename LT, bool TREE>
+hipError_t go_thin(const WalkPath *paths, const WalkShare *shares, const Walk &W, const Params &P, hipStream_t s) {
+  const uint32_t lds = thin_lds(P, W.stack_bytes);
+  if (W.tile_sgs == 1) hipLaunchKernelGGL((k_thin<LT, TREE, 4>), dim3(W.blocks), dim3(kThinWaves * 64), lds, s, paths, shares, W, P);
+  else hipLaunchKernelGGL((k_thin<LT, TREE, 8>), dim3(W.blocks), dim3(kThinWaves * 64), lds, s, paths, shares, W, P);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+uint32_t thin_lds(const Params &P, uint32_t stack_bytes) { return P.blob_dwords * 4 + kThinWaves * (kThinPark + stack_bytes); }
+uint32_t thin_stack(uint32_t tile_sgs, uint32_t levels) { return levels * (tile_sgs == 1 ? kThinStack<4> : kThinStack<8>); }
+
+hipError_t launch_thin(dq_dtype dtype, bool tree, const WalkPath *paths, const WalkShare *shares, const Walk &W, const Params &P, hipStream_t s) {
+  if (dtype == DQ_F32) return tree ? go_thin<float, true>(paths, shares, W, P, s) : go_thin<float, false>(paths, shares, W, P, s);
+  return tree ? go_thin<uint16_t, true>(paths, shares, W, P, s) : go_thin<uint16_t, false>(paths, shares, W, P, s);
+}
+
+}  // namespace dq

@@ -1,0 +1,49 @@
+// Device code shared by the two kernels that carry a tile through all hops of a schedule (dq_walk.hip, dq_thin.hip).
+#pragma once
+#include "dq_codec.h"
+
+namespace dq {
+namespace {
+
+__device__ __forceinline__ void lds_st1(uint32_t a, uint32_t v) {
+  *reinterpret_cast<__attribute__((address_space(3))) uint32_t *>(a) = v;
+}
+
+// The lane's number, opaque to the compiler: what is derived from it is computed where it is used, once in many hops,
+// and not held in registers around the loops (a spilled register's reload waits for the tile's loads in flight).
+__device__ __forceinline__ uint32_t lane_here() {
+  uint32_t lane = threadIdx.x & 63u;
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+template <bool B>
+struct Is { static constexpr bool value = B; };
+
+// Worker whose entries are the i-th a chunk meets.
+template <bool TREE>
+__device__ __forceinline__ uint32_t leaf_of(const Walk &W, uint32_t chunk, uint32_t i) {
+  if constexpr (TREE) {
+    return chunk ^ (__brev(~i) >> (32u - W.log_n));
+  } else {
+    const uint32_t x = (W.chain ? 0u : chunk) + i;
+    return min(x, x - W.n);
+  }
+}
+
+// The launch's tables (tensors, paths, shares) are read through the constant address space, as nothing in the kernel
+// writes to them: scalar loads into scalar registers.  As global loads they are vector loads, and the one of the next
+// tensor's address waits in every hop for everything the wave has in flight.
+template <typename T>
+__device__ __forceinline__ T table_entry(const T *table, uint32_t i) {
+  constexpr uint32_t kWords = sizeof(T) / 4;
+  typedef __attribute__((address_space(4))) const uint32_t constant_u32;
+  constant_u32 *p = (constant_u32 *)(uintptr_t)table + (uint64_t)i * kWords;
+  struct Words { uint32_t w[kWords]; } words;
+#pragma unroll
+  for (uint32_t k = 0; k < kWords; ++k) words.w[k] = p[k];
+  return __builtin_bit_cast(T, words);
+}
+
+}  // namespace
+}  // namespace dq

@@ -16,7 +16,7 @@
 //                  others wait as packed codes in LDS (20 bytes per lane and level).
 // Per hop and tile the random numbers are the same Philox counters as in the step kernels; the per-super-group
 // draws of up to 16 hops are made by one wave-wide call (lane = tile of the batch, hop, row).
-#include "dq_codec.h"
+#include "dq_walk.h"
 
 namespace dq {
 namespace {
@@ -28,29 +28,6 @@ constexpr int kWalkPerSimd = sizeof(LT) == 2 && !TREE ? 5 : 4;
 constexpr uint32_t kParkBytes = 1280;   // per wave: 64 scale draws of 16 bytes, 64 permutation slots
 constexpr uint32_t kXposeBytes = 2048;  // per wave: half a tile of fp32 results
 static_assert(4 * kParkBytes <= (kOffTab4 - kOffDec2) * 4, "a ring's draws lie over the decode tables");
-
-__device__ __forceinline__ void lds_st1(uint32_t a, uint32_t v) {
-  *reinterpret_cast<__attribute__((address_space(3))) uint32_t *>(a) = v;
-}
-
-// The lane's number, opaque to the compiler: what is derived from it is computed where it is used, once in many hops,
-// and not held in registers around the loops (a spilled register's reload waits for the tile's loads in flight).
-__device__ __forceinline__ uint32_t lane_here() {
-  uint32_t lane = threadIdx.x & 63u;
-  asm volatile("" : "+v"(lane));
-  return lane;
-}
-
-// Worker whose entries are the i-th a chunk meets.
-template <bool TREE>
-__device__ __forceinline__ uint32_t leaf_of(const Walk &W, uint32_t chunk, uint32_t i) {
-  if constexpr (TREE) {
-    return chunk ^ (__brev(~i) >> (32u - W.log_n));
-  } else {
-    const uint32_t x = (W.chain ? 0u : chunk) + i;
-    return min(x, x - W.n);
-  }
-}
 
 // Per-super-group draws for 2^hops_log hops, starting at hop i, of 16 >> hops_log tiles, starting at `pos`.
 template <bool TREE>
@@ -71,19 +48,6 @@ template <typename LT>
 struct Slice {
   uint4 w[sizeof(LT) == 4 ? 4 : 2];  // a lane's 16 entries, raw
 };
-// The launch's tables (tensors, paths, shares) are read through the constant address space, as nothing in the kernel
-// writes to them: scalar loads into scalar registers.  As global loads they are vector loads, and the one of the next
-// tensor's address waits in every hop for everything the wave has in flight.
-template <typename T>
-__device__ __forceinline__ T table_entry(const T *table, uint32_t i) {
-  constexpr uint32_t kWords = sizeof(T) / 4;
-  typedef __attribute__((address_space(4))) const uint32_t constant_u32;
-  constant_u32 *p = (constant_u32 *)(uintptr_t)table + (uint64_t)i * kWords;
-  struct Words { uint32_t w[kWords]; } words;
-#pragma unroll
-  for (uint32_t k = 0; k < kWords; ++k) words.w[k] = p[k];
-  return __builtin_bit_cast(T, words);
-}
 template <typename LT>
 __device__ __forceinline__ Slice<LT> load_slice(const Walk &W, uint32_t leaf, uint64_t at) {
   const uint8_t *p = reinterpret_cast<const uint8_t *>(table_entry(reinterpret_cast<const uint64_t *>(W.grads), leaf)) + at;
@@ -145,8 +109,6 @@ struct Areas {
 enum { kNone = 0, kLevels = 1, kCodes = 2, kBoth = 3 };
 template <int N>
 struct How { static constexpr int value = N; };
-template <bool B>
-struct Is { static constexpr bool value = B; };
 
 // `len` consecutive tiles of width B from `pos` on.
 template <int B, typename LT, bool MU, bool TREE>
@@ -401,23 +363,60 @@ hipError_t go_walk(const WalkPath *paths, const WalkShare *shares, const Walk &W
 // halving.  With less than two tiles per wave the count decides: a wave with one tile more takes twice as long whatever its width.
 static const uint32_t kCosts[2][4] = {{1, 1, 1, 1}, {6, 11, 12, 6}};
 
-bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W) {
+static uint64_t count_tiles(const WalkPath *paths, uint32_t n_paths, uint32_t sgs, uint32_t *widths) {
   uint64_t tiles = 0;
-  W->widths = 0;
-  for (uint32_t p = 0; p < W->n_paths; ++p)
+  *widths = 0;
+  for (uint32_t p = 0; p < n_paths; ++p)
     for (int w = 0; w < 4; ++w) {
-      const uint64_t t = (paths[p].job.n_sg[w] + kWaveSGs - 1) / kWaveSGs;
-      tiles += t;
-      if (t) W->widths |= 1u << w;
+      tiles += (paths[p].job.n_sg[w] + sgs - 1) / sgs;
+      if (paths[p].job.n_sg[w]) *widths |= 1u << w;
     }
+  return tiles;
+}
+
+bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W) {
+  constexpr uint32_t kLds = 160u * 1024;
+  uint64_t tiles = count_tiles(paths, W->n_paths, 1, &W->widths);
   if (tiles == 0) return false;
+  // Narrow tiles (dq_thin.hip) where the wide ones would leave SIMDs idle or with one wave each: us per replay of bf16 tensors with
+  // tiles of 4 / 2 / 1 super-groups (256 CUs), by super-groups in the replay:
+  //             3,000           4,096           6,100           8,192           10,000
+  //   ring 4    13 / 12 / 9     14 / 14 / 11    16 / 17 / 16    18 / 22 / 22    20 / 25 / 23
+  //   ring 16   27 / 22 / 18    29 / 25 / 22    32 / 29 / 29    38 / 38 / 48    42 / 45 / 50
+  //   ring 100  117 / 86 / 75   129 / 104 / 106 137 / 131 / 131 172 / 162 / 208 181 / 177 / 226
+  //   tree 8    18 / 14 / 12    18 / 16 / 14    20 / 19 / 20    26 / 28 / 23    28 / 30 / 29
+  //   tree 64   97 / 59 / 50    99 / 88 / 88    106 / 108 / 95  176 / 139 / 134 214 / 162 / 161
+  // One super-group while four waves per SIMD hold them all; in short schedules, where a wave's start counts more than its hops, a
+  // half more.  Two as far as they gain: not as far with fp32 tensors in a ring or chain, whose waves are three per SIMD then
+  // (6,144 super-groups, ring 256: 345 us against 334).
+  const bool f32 = dtype == DQ_F32;
+  const uint32_t some = n_cu * (f32 ? 20u : 24u);
+  const uint32_t most1 = W->n <= 8 ? some : n_cu * 16u, most2 = W->n <= 8 ? 0 : W->n >= 32 && (tree || !f32) ? n_cu * 40u : some;
+  W->tile_sgs = tiles <= most1 ? 1 : tiles <= most2 ? 2 : kWaveSGs;
+  if (W->tile_sgs < kWaveSGs) {
+    tiles = count_tiles(paths, W->n_paths, W->tile_sgs, &W->widths);
+    W->stack_bytes = thin_stack(W->tile_sgs, W->levels);
+    W->waves = 4;
+    const uint64_t needed = (tiles + W->waves - 1) / W->waves;
+    if (thin_lds(P, W->stack_bytes) <= kLds) {
+      const uint64_t most = (uint64_t)n_cu * (kLds / thin_lds(P, W->stack_bytes));
+      W->blocks = (uint32_t)(needed < most ? needed : most);
+      W->by_cost = 0;
+      return true;
+    }
+    W->tile_sgs = kWaveSGs;
+  }
+  tiles = count_tiles(paths, W->n_paths, kWaveSGs, &W->widths);
+  // the stack area also stages half a tile's result
+  W->stack_bytes = W->levels * (W->raw ? kStackRaw : kStackCoded);
+  if (W->stack_bytes < kXposeBytes) W->stack_bytes = kXposeBytes;
   // A butterfly's two blocks per CU share a copy of the tables each; where there are fewer tiles than two waves for every
   // SIMD, blocks of four reach all CUs.  Rings and chains always take blocks of four, 29 KB at the levels of 25 MB and n = 8: five per CU.
   // (Blocks of ten waves put three waves on two of the SIMDs, and the CU has no room for the second one: 97 us, not 75.)
-  const uint32_t most = 4 * (tree ? kWalkPerSimd<float, true> : (dtype == DQ_F32 ? kWalkPerSimd<float, false> : kWalkPerSimd<uint16_t, false>));
+  const uint32_t most = 4 * (tree ? kWalkPerSimd<float, true> : (f32 ? kWalkPerSimd<float, false> : kWalkPerSimd<uint16_t, false>));
   W->waves = tree && tiles >= (uint64_t)n_cu * 8 ? 8 : 4;
   const uint32_t lds = walk_lds(P, tree, W->stack_bytes, W->waves);
-  uint32_t per_cu = 160u * 1024 / lds;
+  uint32_t per_cu = kLds / lds;
   if (per_cu == 0) return false;
   if (per_cu > most / W->waves) per_cu = most / W->waves;
   const uint64_t needed = (tiles + W->waves - 1) / W->waves;
@@ -429,24 +428,24 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
 
 void split_walk(const WalkPath *paths, const Walk &W, std::vector<WalkShare> *shares) {
   const uint32_t *kCost = kCosts[W.by_cost];
+  const uint32_t sgs = W.tile_sgs;
   uint64_t cost = 0;
   for (uint32_t p = 0; p < W.n_paths; ++p)
-    for (int w = 0; w < 4; ++w) cost += (uint64_t)((paths[p].job.n_sg[w] + kWaveSGs - 1) / kWaveSGs) * kCost[w];
+    for (int w = 0; w < 4; ++w) cost += (uint64_t)((paths[p].job.n_sg[w] + sgs - 1) / sgs) * kCost[w];
   const uint32_t n = W.blocks * W.waves;
   shares->resize((size_t)n + 1);
   // first tile of share v: the first whose cost before it reaches v * cost / n
   uint32_t p = 0, t = 0, w = 0, left = 0;  // tile t of path p is in width w's run, which has `left` tiles more
-  uint64_t before = 0;
+  uint64_t before = 0, want = 0, over = 0;  // want = floor(v * cost / n), over = the division's remainder
   auto settle = [&] {  // on to the next run that has tiles
     while (left == 0 && p < W.n_paths) {
       if (w == 4) { ++p; w = 0; t = 0; continue; }
-      left = (paths[p].job.n_sg[w] + kWaveSGs - 1) / kWaveSGs;
+      left = (paths[p].job.n_sg[w] + sgs - 1) / sgs;
       if (left == 0) ++w;
     }
   };
   settle();
   for (uint32_t v = 0; v < n; ++v) {
-    const uint64_t want = (uint64_t)(((unsigned __int128)cost * v) / n);
     while (before < want && p < W.n_paths) {
       const uint64_t take = (want - before + kCost[w] - 1) / kCost[w];
       const uint32_t k = take < left ? (uint32_t)take : left;
@@ -456,12 +455,16 @@ void split_walk(const WalkPath *paths, const Walk &W, std::vector<WalkShare> *sh
       if (left == 0) { ++w; settle(); }
     }
     (*shares)[v] = WalkShare{p, p < W.n_paths ? t : 0u};
+    want += cost / n;
+    over += cost % n;
+    if (over >= n) { over -= n; ++want; }
   }
   (*shares)[n] = WalkShare{W.n_paths, 0};
 }
 
 hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths, const WalkShare *shares, const Walk &W,
                        const Params &P, hipStream_t s) {
+  if (W.tile_sgs < kWaveSGs) return launch_thin(dtype, tree, paths, shares, W, P, s);
   const bool f32 = dtype == DQ_F32;
 #define DQ_WALK(T, M) (tree ? go_walk<T, M, true>(paths, shares, W, P, s) : go_walk<T, M, false>(paths, shares, W, P, s))
   if (means) return f32 ? DQ_WALK(float, true) : DQ_WALK(uint16_t, true);

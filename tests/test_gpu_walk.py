@@ -79,6 +79,18 @@ def test_whole_replay_equals_its_steps(dev, topology, n, widths, all_gather, mea
     whole_against_steps(rp, {"ring": n, "chain": 1, "butterfly": 0}[topology])
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("topology,n,widths,all_gather", [
+    # tiles of two super-groups, and of four, of a wave: chunks with remainders in every width
+    ("ring", 17, [[1001, 2002, 1503, 594]], True), ("chain", 33, [[1501, 2003, 1707, 302]], False),
+    ("butterfly", 64, [[1601, 3203, 1500, 608]], True), ("butterfly", 32, [[2049, 2047, 640, 0]], False),
+    ("ring", 5, [[1601, 3002, 1603, 304]], False), ("ring", 17, [[1501, 3002, 1503, 352]], True), ("chain", 33, [[0, 7003, 3300, 6]], True),
+    ("butterfly", 8, [[1601, 3002, 1693, 104]], True), ("butterfly", 64, [[3201, 6003, 1300, 56]], False),
+])
+def test_whole_replay_of_many_super_groups_equals_its_steps(dev, topology, n, widths, all_gather, dtype):
+    test_whole_replay_equals_its_steps(dev, topology, n, widths, all_gather, True, dtype)
+
+
 @pytest.mark.parametrize("topology", ["ring", "butterfly"])
 @pytest.mark.parametrize("J", [8192, 66000])                # one tile per wave, and several waves' shares per chunk
 def test_whole_replay_on_original_tensors_over_the_whole_grid(dev, topology, J):
