@@ -186,7 +186,8 @@ typedef struct {
 
 /* Device scratch the replay needs (job tables, packed messages, fp32 keep-buffers). */
 size_t dq_replay_scratch_bytes(const dq_ctx *ctx, const dq_replay_desc *desc);
-/* Build the schedule and upload its job tables into `scratch` (synchronous).
+/* Build the schedule and upload its job tables into `scratch` (synchronous; waits for the device first, as work
+ * enqueued earlier may still be using the same memory).
  * worker_grads: host array of n_workers device pointers.  scratch and out must stay valid
  * until dq_replay_destroy. */
 dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *const *worker_grads, void *scratch,

@@ -97,6 +97,7 @@ def lib():
         L.dq_replay_scratch_bytes.argtypes = [vp, C.POINTER(ReplayDesc)]
         L.dq_replay_scratch_bytes.restype = C.c_size_t
         L.dq_replay_create.argtypes = [vp, C.POINTER(ReplayDesc), C.POINTER(vp), vp, C.c_size_t, vp, C.POINTER(vp)]
+        L.dqx_replay_create.argtypes = [vp, C.POINTER(ReplayDesc), C.POINTER(vp), vp, C.c_size_t, vp, C.POINTER(vp), vp]
         L.dq_replay_n_steps.argtypes = [vp]
         L.dq_replay_n_steps.restype = u32
         L.dq_replay_run.argtypes = [vp, C.POINTER(C.c_float), vp]
@@ -292,8 +293,9 @@ class Replay:
         self.out = torch.empty(entries, dtype=torch.float32, device=dev)
         ptrs = (C.c_void_p * n)(*[g.data_ptr() for g in self.grads])
         self.h = C.c_void_p()
-        _check(lib().dq_replay_create(ctx.h, C.byref(desc), ptrs, _ptr(self.scratch), nbytes, _ptr(self.out),
-                                      C.byref(self.h)))
+        # the scratch may be memory that the current stream's earlier work still uses: its tables are sent in that order
+        _check(lib().dqx_replay_create(ctx.h, C.byref(desc), ptrs, _ptr(self.scratch), nbytes, _ptr(self.out),
+                                       C.byref(self.h), _stream()))
         self.n_steps = lib().dq_replay_n_steps(self.h)
 
     def run(self, timed=False):

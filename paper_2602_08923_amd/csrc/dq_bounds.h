@@ -22,6 +22,10 @@ dq_status dqx_bounds_end(void *hip_stream, int *out_of_bounds);
 // n <= kFetchWords words of device memory as the stream's work so far leaves them (waits for it): a copy of a few words by
 // hipMemcpy costs 13 us on top of the wait.
 dq_status dqx_fetch(const uint32_t *src, uint32_t n, uint32_t *dst_host, void *hip_stream);
+// dq_replay_create for a scratch that belongs to a stream (memory that its earlier work may still be using): the tables are
+// uploaded as work of that stream, nothing is waited for.  Not while the stream is captured.
+dq_status dqx_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *const *worker_grads, void *scratch, size_t scratch_bytes,
+                            float *out, dq_replay **plan, void *hip_stream);
 // dq_sg_stats of n_workers (at most 256) tensors and dq_stats_combine in one launch.
 dq_status dqx_stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dtype, uint64_t n_sg, float *mu, float *F,
                         void *hip_stream);

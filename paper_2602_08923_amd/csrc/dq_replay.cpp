@@ -6,10 +6,14 @@
 // all (worker, chunk) jobs of that step; the job tables are built once, here, on the host.
 #include <string.h>
 
+#include <atomic>
+#include <chrono>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <vector>
 
+#include "dq_bounds.h"
 #include "dq_device.h"
 
 namespace {
@@ -437,50 +441,118 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
   return DQ_OK;
 }
 
-}  // namespace
+// A plan's tables on their way to its scratch, in the order of their offsets; what lies between two pieces is padding.
+//
+// Scratch is recycled memory: the launch of an earlier replay, still running, may be reading its tables at the very place.  The binding
+// therefore names the stream that the scratch belongs to, and the tables go there as that stream's work: one block copies them
+// from pinned memory (55 KB for 8 workers' ring of 8,192 super-groups) and then says so in a flag that the host reads without a call
+// into the runtime, for launches on other streams and under capture wait for it.  Without a stream, and for tables
+// beyond kPinned, the host waits until nothing can be reading the scratch and copies.  (What bounds the one block is the trip over
+// PCIe, a few us for 55 KB.  A copy that the host waits for, besides needing an idle scratch: the all-reduce of 8 workers' 8,192
+// super-groups took 104 us instead of 92.)
+constexpr size_t kPinned = 256u << 10;
+constexpr size_t kStagings = 8;
+struct Staging {
+  uint8_t *host = nullptr;          // pinned: kPinned bytes, then the flag
+  volatile uint32_t *flag = nullptr;  // number of the last upload that has arrived
+  uint32_t number = 0;
+  bool arrived() const { return __atomic_load_n(flag, __ATOMIC_ACQUIRE) == number; }
+};
+std::mutex g_staging_mutex;
+std::vector<Staging *> g_stagings;  // at most kStagings, kept until the process ends; one is taken again when its last upload has arrived
 
-// Pieces of scratch, in the order of their offsets, gathered and sent to the device in few copies: a copy waits for the
-// device, 13 us or more each, and a replay of 8 workers has a dozen tables.
+__global__ void __launch_bounds__(1024) k_upload(const uint4 *src, uint4 *dst, uint32_t words, uint32_t *flag, uint32_t number) {
+  constexpr uint32_t kAhead = 4;  // latency of the host's memory: 64 KB in flight
+  for (uint32_t i = threadIdx.x; i < words; i += kAhead * 1024) {
+    uint4 w[kAhead];
+#pragma unroll
+    for (uint32_t k = 0; k < kAhead; ++k) w[k] = src[i + k * 1024 < words ? i + k * 1024 : i];
+#pragma unroll
+    for (uint32_t k = 0; k < kAhead; ++k)
+      if (i + k * 1024 < words) dst[i + k * 1024] = w[k];
+  }
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(flag, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // fenced above
+}
+
 class Upload {
  public:
-  explicit Upload(uint8_t *scratch) : scratch_(scratch) {}
+  // Stream: null pointer to one if the caller named none.
+  Upload(uint8_t *scratch, const hipStream_t *stream) : scratch_(scratch), stream_(stream) {}
   void put(size_t off, const void *src, size_t bytes) {
     if (bytes == 0) return;
     if (!buf_.empty() && (off < first_ + buf_.size() || off - first_ + bytes > kMost)) send();
     if (buf_.empty()) first_ = off;
-    buf_.resize(off - first_ + bytes);  // what lies between two pieces is padding
+    buf_.resize(off - first_ + bytes);
     memcpy(buf_.data() + (off - first_), src, bytes);
   }
-  dq_status finish() {
+  // *staging: what the tables wait in, or null if they have arrived; *number: of the upload.
+  dq_status finish(Staging **staging, uint32_t *number) {
+    *staging = nullptr;
+    if (buf_.empty() || status_ != DQ_OK) return status_;
+    if (stream_ && !waited_ && buf_.size() <= kPinned) {
+      hipError_t e = hipSuccess;
+      if (enqueue(staging, number, &e)) return dq::hip_status(e);
+    }
     send();
     return status_;
   }
 
  private:
-  static constexpr size_t kMost = 16u << 20, kPinned = 256u << 10;
+  static constexpr size_t kMost = 16u << 20;
+  static Staging *take() {  // its next upload is numbered `number`
+    std::lock_guard<std::mutex> lock(g_staging_mutex);
+    Staging *s = nullptr;
+    for (Staging *x : g_stagings)
+      if (x->arrived()) s = x;
+    if (!s) {
+      if (g_stagings.size() >= kStagings || !(s = new (std::nothrow) Staging)) return nullptr;
+      if (hipHostMalloc((void **)&s->host, kPinned + 64, hipHostMallocPortable) != hipSuccess) {
+        delete s;
+        return nullptr;
+      }
+      s->flag = reinterpret_cast<volatile uint32_t *>(s->host + kPinned);
+      *s->flag = 0;
+      g_stagings.push_back(s);
+    }
+    ++s->number;
+    return s;
+  }
+  bool enqueue(Staging **staging, uint32_t *number, hipError_t *err) {
+    Staging *s = take();
+    if (!s) return false;
+    const size_t bytes = align_up(buf_.size(), 16);  // scratch ends on a multiple of 256
+    memcpy(s->host, buf_.data(), buf_.size());
+    memset(s->host + buf_.size(), 0, bytes - buf_.size());
+    const uint32_t mine = s->number;
+    hipLaunchKernelGGL(k_upload, dim3(1), dim3(1024), 0, *stream_, reinterpret_cast<const uint4 *>(s->host),
+                       reinterpret_cast<uint4 *>(scratch_ + first_), (uint32_t)(bytes / 16), const_cast<uint32_t *>(s->flag), mine);
+    if ((*err = hipGetLastError()) == hipSuccess) {
+      *number = mine;
+      *staging = s;
+    } else {
+      __atomic_store_n(s->flag, mine, __ATOMIC_RELEASE);  // nothing reads it
+    }
+    return true;
+  }
   void send() {
-    if (!buf_.empty() && status_ == DQ_OK) status_ = copy();
+    if (status_ == DQ_OK && !waited_) {
+      status_ = dq::hip_status(stream_ ? hipStreamSynchronize(*stream_) : hipDeviceSynchronize());
+      waited_ = true;
+    }
+    if (!buf_.empty() && status_ == DQ_OK) status_ = dq::hip_status(hipMemcpy(scratch_ + first_, buf_.data(), buf_.size(), hipMemcpyHostToDevice));
     buf_.clear();
   }
-  dq_status copy() {
-    // from pinned memory a copy of tens of KB takes half the time; one staging buffer serves all threads in turn
-    static std::mutex mutex;
-    static uint8_t *pinned = nullptr;
-    if (buf_.size() <= kPinned) {
-      std::lock_guard<std::mutex> lock(mutex);
-      if (pinned || hipHostMalloc((void **)&pinned, kPinned, hipHostMallocPortable) == hipSuccess) {
-        memcpy(pinned, buf_.data(), buf_.size());
-        return dq::hip_status(hipMemcpy(scratch_ + first_, pinned, buf_.size(), hipMemcpyHostToDevice));
-      }
-      pinned = nullptr;
-    }
-    return dq::hip_status(hipMemcpy(scratch_ + first_, buf_.data(), buf_.size(), hipMemcpyHostToDevice));
-  }
   uint8_t *scratch_;
+  const hipStream_t *stream_;
   size_t first_ = 0;
   std::vector<uint8_t> buf_;
+  bool waited_ = false;  // for what may read the scratch
   dq_status status_ = DQ_OK;
 };
+
+}  // namespace
 
 struct dq_replay {
   dq_ctx *ctx;
@@ -490,7 +562,34 @@ struct dq_replay {
   std::vector<hipEvent_t> events;
   dq_dtype dtype;
   bool means;
+  // the upload of the tables: the stream it is ordered on, and what says that it has arrived (null: it has)
+  hipStream_t stream = nullptr;
+  std::atomic<Staging *> staging{nullptr};
+  uint32_t upload = 0;
 };
+
+// Before anything is enqueued on s: the tables are there, or will be by the order of s.  A captured launch runs at another time
+// and maybe on another stream, so for a capture they have to be there.
+static dq_status await_tables(dq_replay *r, hipStream_t s) {
+  Staging *staging = r->staging.load(std::memory_order_acquire);
+  if (!staging) return DQ_OK;
+  auto arrived = [&] { return (int32_t)(__atomic_load_n(staging->flag, __ATOMIC_ACQUIRE) - r->upload) >= 0; };  // later uploads count on
+  if (!arrived()) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &capture);
+    if (e != hipSuccess) return dq::hip_status(e);
+    if (s == r->stream && capture == hipStreamCaptureStatusNone) return DQ_OK;
+    for (uint32_t spin = 0; spin < 200000 && !arrived(); ++spin) __builtin_ia32_pause();
+    if (!arrived() && capture == hipStreamCaptureStatusNone) {  // long work ahead of it
+      const hipError_t d = hipDeviceSynchronize();
+      if (d != hipSuccess) return dq::hip_status(d);
+    }
+    for (uint32_t ms = 0; ms < 60000 && !arrived(); ++ms) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    if (!arrived()) return dq::hip_status(hipErrorNotReady);
+  }
+  r->staging.store(nullptr, std::memory_order_release);
+  return DQ_OK;
+}
 
 extern "C" {
 
@@ -500,8 +599,8 @@ size_t dq_replay_scratch_bytes(const dq_ctx *ctx, const dq_replay_desc *desc) {
   return p.scratch_bytes;
 }
 
-dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *const *worker_grads, void *scratch,
-                           size_t scratch_bytes, float *out, dq_replay **plan_out) {
+static dq_status create(dq_ctx *ctx, const dq_replay_desc *desc, const void *const *worker_grads, void *scratch, size_t scratch_bytes,
+                        float *out, dq_replay **plan_out, const hipStream_t *stream) {
   if (!ctx || !desc || !worker_grads || !scratch || !out || !plan_out) return DQ_EINVAL;
   *plan_out = nullptr;
   if (desc->n_grads != 0 && desc->n_grads != ctx->cfg.n_workers) return DQ_EINVAL;
@@ -524,7 +623,7 @@ dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *
     return st;
   }
   const bool mx = desc->codec != DQ_DYNAMIQ;
-  Upload up(r->scratch);
+  Upload up(r->scratch, stream);
   Plan &p = r->plan;
   if (p.walk) {  // in the order of their offsets
     if (!mx) {
@@ -562,12 +661,30 @@ dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *
       }
       std::vector<HostJob>().swap(L.jobs);
     }
-  if ((st = up.finish()) != DQ_OK) {
+  Staging *staging = nullptr;
+  if ((st = up.finish(&staging, &r->upload)) != DQ_OK) {
     delete r;
     return st;
   }
+  if (stream) r->stream = *stream;
+  r->staging = staging;
   *plan_out = r;
   return DQ_OK;
+}
+
+dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *const *worker_grads, void *scratch,
+                           size_t scratch_bytes, float *out, dq_replay **plan) {
+  return create(ctx, desc, worker_grads, scratch, scratch_bytes, out, plan, nullptr);
+}
+
+dq_status dqx_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *const *worker_grads, void *scratch, size_t scratch_bytes,
+                            float *out, dq_replay **plan, void *hip_stream) {
+  const hipStream_t s = (hipStream_t)hip_stream;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const hipError_t e = hipStreamIsCapturing(s, &capture);
+  if (e != hipSuccess) return dq::hip_status(e);
+  if (capture != hipStreamCaptureStatusNone) return dq::hip_status(hipErrorStreamCaptureUnsupported);  // the tables are sent once, now
+  return create(ctx, desc, worker_grads, scratch, scratch_bytes, out, plan, &s);
 }
 
 uint32_t dq_replay_n_steps(const dq_replay *plan) { return plan ? (uint32_t)plan->plan.steps.size() : 0; }
@@ -620,6 +737,8 @@ static dq_status run_walk(dq_replay *r, hipStream_t s) {
 
 dq_status dq_replay_run_steps(dq_replay *plan, uint32_t first, uint32_t count, void *hip_stream) {
   if (!plan || (size_t)first + count > plan->plan.steps.size()) return DQ_EINVAL;
+  const dq_status ready = await_tables(plan, (hipStream_t)hip_stream);
+  if (ready != DQ_OK) return ready;
   if (plan->plan.walk && count == plan->plan.steps.size()) return run_walk(plan, (hipStream_t)hip_stream);
   for (uint32_t i = first; i < first + count; ++i) {
     const dq_status st = run_step(plan, i, (hipStream_t)hip_stream);
@@ -630,6 +749,8 @@ dq_status dq_replay_run_steps(dq_replay *plan, uint32_t first, uint32_t count, v
 
 dq_status dq_replay_run_launch(dq_replay *plan, uint32_t step, uint32_t launch, void *hip_stream) {
   if (!plan || step >= plan->plan.steps.size() || launch >= plan->plan.steps[step].launches.size()) return DQ_EINVAL;
+  const dq_status ready = await_tables(plan, (hipStream_t)hip_stream);
+  if (ready != DQ_OK) return ready;
   return run_step(plan, step, (hipStream_t)hip_stream, (int)launch);
 }
 
@@ -637,6 +758,8 @@ dq_status dq_replay_run(dq_replay *plan, float *step_ms, void *hip_stream) {
   if (!plan) return DQ_EINVAL;
   hipStream_t s = (hipStream_t)hip_stream;
   const size_t ns = plan->plan.steps.size();
+  const dq_status ready = await_tables(plan, s);
+  if (ready != DQ_OK) return ready;
   if (plan->plan.walk && !step_ms) return run_walk(plan, s);
   hipError_t he = hipSuccess;
   while (step_ms && he == hipSuccess && plan->events.size() < ns + 1) {

@@ -2,9 +2,12 @@
 by step, whose steps the parity tests hold against the oracle: same result, same messages of the last two
 steps -- at the edges of tiles, of the draws' batches and of the split over waves.  And the bounds
 check of super-group indices in front of a call."""
+import threading
+
 import pytest
 import torch
 
+from paper_2602_08923_amd import allreduce
 from paper_2602_08923_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -137,3 +140,100 @@ def test_indices_out_of_bounds_are_refused_and_nothing_is_written(dev, n_sg):
     for _ in range(300):                                    # more calls than a workspace has slots
         got = ctx.dq_compress(x, ch, 1, sg_index=good)
     assert torch.equal(got, want)
+
+
+# ---- plans and streams: a plan's tables lie in memory that the stream's earlier work may still be using
+ALLREDUCE = [dict(codec=B.DQ_MXFP8_E4M3), dict(codec=B.DQ_MXFP4_E2M1), dict(uniform_width=4), dict(uniform_width=8, topology=B.DQ_BUTTERFLY),
+             dict(), dict(max_width=16, topology=B.DQ_BUTTERFLY)]
+
+
+def allreduce_inputs(dev, calls, n=8, n_sg=2048):
+    return [gradients(n, n_sg, torch.bfloat16, dev, 900 + k) for k in range(calls)]
+
+
+@pytest.mark.parametrize("options", ALLREDUCE)
+def test_allreduces_back_to_back_on_a_side_stream_keep_their_own_tables(dev, options):
+    calls = allreduce_inputs(dev, 6)
+    want = [allreduce.simulated_allreduce(g, 6.0, seed=k, **options)[0].clone() for k, g in enumerate(calls)]
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    got = []
+    with torch.cuda.stream(side):
+        for k, g in enumerate(calls):                       # each call's scratch is the one before's
+            got.append(allreduce.simulated_allreduce(g, 6.0, seed=k, **options)[0])
+    side.synchronize()
+    for k, (x, y) in enumerate(zip(got, want)):
+        assert torch.equal(x.view(torch.int32), y.view(torch.int32)), f"call {k}"
+
+
+def test_allreduces_of_several_threads_on_their_own_streams(dev):
+    calls = allreduce_inputs(dev, len(ALLREDUCE))
+    want = [allreduce.simulated_allreduce(g, 6.0, seed=k, **o)[0].clone() for k, (g, o) in enumerate(zip(calls, ALLREDUCE))]
+    torch.cuda.synchronize()
+    got, errors = [None] * len(calls), []
+
+    def work(k):
+        try:
+            side = torch.cuda.Stream()
+            with torch.cuda.stream(side):
+                for _ in range(10):
+                    got[k] = allreduce.simulated_allreduce(calls[k], 6.0, seed=k, **ALLREDUCE[k])[0]
+            side.synchronize()
+        except Exception as e:                              # noqa: BLE001 -- shown below
+            errors.append((k, e))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(calls))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors
+    for k, (x, y) in enumerate(zip(got, want)):
+        assert torch.equal(x.view(torch.int32), y.view(torch.int32)), f"thread {k}"
+
+
+@pytest.mark.parametrize("codec,n,J", [(B.DQ_DYNAMIQ, 8, 64), (B.DQ_MXFP6_E3M2, 8, 64), (B.DQ_DYNAMIQ, 64, 192)])   # the last: 360 KB of tables
+def test_a_plan_made_on_one_stream_runs_on_another_and_in_a_graph(dev, codec, n, J):
+    grads = gradients(n, J, torch.bfloat16, dev, 7)
+    ctx, widths = B.Context(n, seed=3), [[J // 4, J // 2, J // 4 - 8, 8]]
+    ref = B.Replay(ctx, B.DQ_RING, codec, grads, J, widths)
+    ref.run()
+    torch.cuda.synchronize()
+    want = ref.out.view(torch.int32).clone()
+    side, busy = torch.cuda.Stream(), torch.randn(4096, 4096, device=dev)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(8):
+            busy = busy @ busy * 1e-3                       # the upload has to wait for this
+        rp = B.Replay(ctx, B.DQ_RING, codec, grads, J, widths)
+        rp.out.zero_()
+    torch.cuda.current_stream().wait_stream(side)           # for the zeros; the library sees to its tables itself
+    rp.run()
+    torch.cuda.synchronize()
+    assert torch.equal(rp.out.view(torch.int32), want)
+
+    with torch.cuda.stream(side):
+        rp2 = B.Replay(ctx, B.DQ_RING, codec, grads, J, widths)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rp2.run()
+    for _ in range(4):
+        rp2.out.fill_(3.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(rp2.out.view(torch.int32), want)
+        ref.run()                                           # eager work between the replays
+        torch.cuda.synchronize()
+        assert torch.equal(ref.out.view(torch.int32), want)
+
+
+def test_a_plan_is_not_made_under_capture(dev):
+    grads = gradients(4, 16, torch.bfloat16, dev, 1)
+    ctx = B.Context(4)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        with pytest.raises(B.DqError, match="captur"):
+            B.Replay(ctx, B.DQ_RING, B.DQ_DYNAMIQ, grads, 16, [[4, 8, 4, 0]])
+        grads[0].zero_()                                    # a graph with something in it
+    graph.replay()
+    torch.cuda.synchronize()
