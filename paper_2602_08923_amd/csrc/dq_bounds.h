@@ -10,16 +10,20 @@ struct Bound {
   uint32_t n, limit;      // every index must be below limit
 };
 constexpr uint32_t kFetchWords = 1023;
-const uint32_t *armed_guard();     // this thread's armed verdict (device), or null
+struct Guard {
+  const uint32_t *word;  // device, or null: the call's kernels do nothing if it holds `call`
+  uint32_t call;
+};
+Guard armed_guard();  // of the check this thread has armed
 }  // namespace dq
 
 extern "C" {
-// Enqueue the check of one or two index arrays and arm its verdict for the calls this thread makes until
+// Enqueue the check of one or two index arrays (not under capture) and arm its verdict for the calls this thread makes until
 // dqx_bounds_end, which waits for it (bit k: array k has an index out of bounds).  The calls in between do nothing
 // if a bit is set.
 dq_status dqx_bounds_begin(const dq::Bound *bounds, int n_bounds, void *hip_stream);
 dq_status dqx_bounds_end(void *hip_stream, int *out_of_bounds);
-// n <= kFetchWords words of device memory as the stream's work so far leaves them (waits for it): a copy of a few words by
+// n <= kFetchWords words of device memory as the stream's work so far leaves them (waits for it; not under capture): a copy of a few words by
 // hipMemcpy costs 13 us on top of the wait.
 dq_status dqx_fetch(const uint32_t *src, uint32_t n, uint32_t *dst_host, void *hip_stream);
 // dq_replay_create for a scratch that belongs to a stream (memory that its earlier work may still be using): the tables are

@@ -9,6 +9,7 @@
 #include <string.h>
 
 #include <mutex>
+#include <new>
 #include <vector>
 
 #include "dq_bounds.h"
@@ -17,30 +18,35 @@
 namespace dq {
 namespace {
 
-constexpr uint32_t kSlots = 256;  // calls a workspace serves before its slots are used again
-struct Slot {
-  uint32_t found, guard;
+// A workspace belongs to one call at a time, from its enqueueing until its verdict has come, and goes to the next call, maybe on
+// another stream, as it is: nothing in it is reset, and the kernels of earlier calls may still look at `refused`.
+struct Tally {
+  unsigned long long done;  // blocks of all calls that have finished (kDoneBits), and above them those of this call that found something
+  uint32_t refused;         // the last call that had an index out of bounds; a call's kernels do nothing if it is theirs
 };
 struct Workspace {
-  Slot *slots = nullptr;      // device, zero at rest
-  uint32_t *host = nullptr;   // pinned: the last verdict, 4 * call number + [first array out of bounds] + 2 * [second]
+  Tally *tally = nullptr;    // device
+  uint32_t *host = nullptr;  // pinned: the last verdict, 4 * call number + [first array out of bounds] + 2 * [second]
   uint32_t calls = 0;
+  uint64_t done = 0;         // blocks of all calls so far
   int device = -1;
 };
+constexpr uint32_t kDoneBits = 40, kLastCall = (1u << 30) - 1;  // a workspace is retired before either count runs over
 
-// Workspaces at rest (2 KB each), one for every call that was ever waiting at the same time as others, kIdle of them at most.
+// Workspaces at rest (4 KB each), one for every call that was ever waiting at the same time as others, kIdle of them at most.
 constexpr size_t kIdle = 8;
 std::mutex g_mutex;
 std::vector<Workspace *> g_idle;
 
 thread_local Workspace *t_armed = nullptr;
-thread_local const uint32_t *t_guard = nullptr;
 
 // What bounds it is latency: eight indices per thread, all loaded before the first is looked at, and one atomic
-// per block, blocks done in its low ten bits, those that found something in the two fields above.  (Findings in a word of their
+// per block, which also says whether it found something.  (Findings in a word of their
 // own needed a fence per block, a write-back of the L2, and took 10 us for 488,282 indices, 6.4.)
 constexpr uint32_t kPerThread = 8, kMaxBlocks = 512;
-__global__ void __launch_bounds__(256) k_bounds(Bound a, Bound b, Slot *slot, uint32_t *host, uint32_t call) {
+constexpr uint32_t kBadA = kDoneBits, kBadB = kDoneBits + 12;  // fields of 12 bits for at most kMaxBlocks each
+__global__ void k_clear(Tally *tally) { *tally = Tally{0, 0}; }
+__global__ void __launch_bounds__(256) k_bounds(Bound a, Bound b, Tally *tally, uint32_t *host, uint32_t call, uint64_t last) {
   auto outside = [](const Bound &x) {
     const uint32_t stride = gridDim.x * 256;
     uint32_t most = 0;
@@ -59,11 +65,16 @@ __global__ void __launch_bounds__(256) k_bounds(Bound a, Bound b, Slot *slot, ui
   const bool out_a = outside(a), out_b = outside(b);
   const int bad_a = __syncthreads_or(out_a), bad_b = __syncthreads_or(out_b);
   if (threadIdx.x != 0) return;
-  const uint32_t mine = 1u + (bad_a ? 1u << 10 : 0u) + (bad_b ? 1u << 20 : 0u), all = atomicAdd(&slot->found, mine) + mine;
-  if ((all & 0x3FFu) != gridDim.x) return;
-  const uint32_t verdict = ((all >> 10 & 0x3FFu) ? 1u : 0u) + (all >> 20 ? 2u : 0u);
-  slot->found = 0;  // the next kernels on the stream see these two as they see any store
-  slot->guard = verdict;
+  const unsigned long long mine = 1ull + (bad_a ? 1ull << kBadA : 0ull) + (bad_b ? 1ull << kBadB : 0ull);
+  const unsigned long long all = atomicAdd(&tally->done, mine) + mine;
+  if ((all & ((1ull << kDoneBits) - 1)) != last) return;
+  const unsigned long long bad = all >> kDoneBits << kDoneBits;
+  uint32_t verdict = 0;
+  if (bad) {
+    verdict = (all >> kBadA & 0xFFFu ? 1u : 0u) + (all >> kBadB ? 2u : 0u);
+    atomicAdd(&tally->done, 0ull - bad);
+    tally->refused = call;  // the next kernel on the stream sees it as it sees any store; the host waits for the stream
+  }
   __hip_atomic_store(host, 4 * call + verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // nothing else to order
 }
 
@@ -75,7 +86,14 @@ __global__ void __launch_bounds__(256) k_fetch(const uint32_t *src, uint32_t n, 
   if (threadIdx.x == 0) __hip_atomic_store(host, 4 * call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // fenced above
 }
 
-Workspace *take(hipError_t *err) {
+// One for a call on stream s, which must not be under capture: a captured check would run again, with this call's number.
+Workspace *take(hipStream_t s, hipError_t *err) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if ((*err = hipStreamIsCapturing(s, &capture)) != hipSuccess) return nullptr;
+  if (capture != hipStreamCaptureStatusNone) {
+    *err = hipErrorStreamCaptureUnsupported;
+    return nullptr;
+  }
   int device = -1;
   if ((*err = hipGetDevice(&device)) != hipSuccess) return nullptr;
   {
@@ -87,106 +105,102 @@ Workspace *take(hipError_t *err) {
         return w;
       }
   }
-  Workspace *w = new Workspace;
+  Workspace *w = new (std::nothrow) Workspace;
+  if (!w) {
+    *err = hipErrorOutOfMemory;
+    return nullptr;
+  }
   w->device = device;
-  if ((*err = hipMalloc((void **)&w->slots, kSlots * sizeof(Slot))) != hipSuccess ||
-      (*err = hipMemset(w->slots, 0, kSlots * sizeof(Slot))) != hipSuccess ||
+  if ((*err = hipMalloc((void **)&w->tally, sizeof(Tally))) != hipSuccess ||
       (*err = hipHostMalloc((void **)&w->host, 4 * (1 + kFetchWords), hipHostMallocDefault)) != hipSuccess) {
-    if (w->slots) (void)hipFree(w->slots);
+    if (w->tally) (void)hipFree(w->tally);
     delete w;
     return nullptr;
   }
   *w->host = 0;
-  return w;
+  // ahead of the first call on its own stream; other streams meet the workspace only after that call's verdict
+  hipLaunchKernelGGL(k_clear, dim3(1), dim3(1), 0, s, w->tally);
+  *err = hipGetLastError();
+  return *err == hipSuccess ? w : nullptr;
 }
 
-void drop(Workspace *w) {
-  (void)hipFree(w->slots);
+// After a call whose verdict has come.  (After an error something may still write to the workspace: it is left alone for good.)
+void give_back(Workspace *w) {
+  if (w->calls < kLastCall && w->done < 1ull << (kDoneBits - 1)) {
+    std::lock_guard<std::mutex> lock(g_mutex);
+    if (g_idle.size() < kIdle) {
+      g_idle.push_back(w);
+      return;
+    }
+  }
+  (void)hipFree(w->tally);  // waits for the kernels that look at it
   (void)hipHostFree(w->host);
   delete w;
 }
 
+// The verdict of w's last call.
+hipError_t await_call(Workspace *w, hipStream_t s, uint32_t *word) {
+  for (uint32_t spin = 0; spin < 200000; ++spin) {
+    *word = __atomic_load_n(w->host, __ATOMIC_ACQUIRE);
+    if (*word >> 2 == w->calls) return hipSuccess;
+    __builtin_ia32_pause();
+  }
+  const hipError_t e = hipStreamSynchronize(s);  // long work ahead on the stream, or an error there
+  if (e != hipSuccess) return e;
+  *word = __atomic_load_n(w->host, __ATOMIC_ACQUIRE);
+  return *word >> 2 == w->calls ? hipSuccess : hipErrorLaunchFailure;
+}
+
 }  // namespace
 
-const uint32_t *armed_guard() { return t_guard; }
+Guard armed_guard() { return t_armed ? Guard{&t_armed->tally->refused, t_armed->calls} : Guard{nullptr, 0}; }
 
 }  // namespace dq
 
 extern "C" {
 
-static hipError_t await_call(dq::Workspace *w, void *hip_stream, uint32_t *word_out) {
-  volatile uint32_t *word = w->host;
-  hipError_t e = hipSuccess;
-  for (uint32_t spin = 0;; ++spin) {
-    *word_out = __atomic_load_n(word, __ATOMIC_ACQUIRE);
-    if (*word_out >> 2 == (w->calls & 0x3FFFFFFFu)) break;
-    if (spin > 200000) {  // long work ahead on the stream, or an error there: wait in the runtime
-      e = hipStreamSynchronize((hipStream_t)hip_stream);
-      *word_out = __atomic_load_n(word, __ATOMIC_ACQUIRE);
-      break;
-    }
-    __builtin_ia32_pause();
-  }
-  return e;
-}
-static void give_back(dq::Workspace *w) {
-  {
-    std::lock_guard<std::mutex> lock(dq::g_mutex);
-    if (dq::g_idle.size() < dq::kIdle) {
-      dq::g_idle.push_back(w);
-      return;
-    }
-  }
-  dq::drop(w);
-}
-
 dq_status dqx_bounds_begin(const dq::Bound *bounds, int n_bounds, void *hip_stream) {
   hipError_t e = hipSuccess;
-  dq::Workspace *w = dq::take(&e);
+  dq::Workspace *w = dq::take((hipStream_t)hip_stream, &e);
   if (!w) return dq::hip_status(e);
-  ++w->calls;
-  if (w->calls % dq::kSlots == 0) (void)hipDeviceSynchronize();  // a slot is read by its own call only: let all of them finish
-  dq::Slot *slot = w->slots + w->calls % dq::kSlots;
   const dq::Bound a = bounds[0], b = n_bounds > 1 ? bounds[1] : dq::Bound{nullptr, 0, 0};
   const uint32_t most = a.n > b.n ? a.n : b.n;
   uint32_t blocks = (most + 256 * dq::kPerThread - 1) / (256 * dq::kPerThread);
-  if (blocks > dq::kMaxBlocks) blocks = dq::kMaxBlocks;
-  hipLaunchKernelGGL(dq::k_bounds, dim3(blocks ? blocks : 1), dim3(256), 0, (hipStream_t)hip_stream, a, b, slot, w->host, w->calls);
-  e = hipGetLastError();
-  if (e != hipSuccess) {
-    give_back(w);
-    return dq::hip_status(e);
-  }
+  blocks = blocks > dq::kMaxBlocks ? dq::kMaxBlocks : blocks ? blocks : 1;
+  ++w->calls;
+  w->done += blocks;
+  hipLaunchKernelGGL(dq::k_bounds, dim3(blocks), dim3(256), 0, (hipStream_t)hip_stream, a, b, w->tally, w->host, w->calls, w->done);
+  if ((e = hipGetLastError()) != hipSuccess) return dq::hip_status(e);
   dq::t_armed = w;
-  dq::t_guard = &slot->guard;
   return DQ_OK;
 }
 
 dq_status dqx_bounds_end(void *hip_stream, int *out_of_bounds) {
   dq::Workspace *w = dq::t_armed;
   dq::t_armed = nullptr;
-  dq::t_guard = nullptr;
   if (!w) return DQ_EINVAL;
   uint32_t word = 0;
-  const hipError_t e = await_call(w, hip_stream, &word);
+  hipError_t e = dq::await_call(w, (hipStream_t)hip_stream, &word);
+  if (e != hipSuccess) return dq::hip_status(e);
   *out_of_bounds = (int)(word & 3u);
-  give_back(w);
-  return dq::hip_status(e);
+  // the refused call's kernel has read its refusal before another call can be refused
+  if (*out_of_bounds && (e = hipStreamSynchronize((hipStream_t)hip_stream)) != hipSuccess) return dq::hip_status(e);
+  dq::give_back(w);
+  return DQ_OK;
 }
 
 dq_status dqx_fetch(const uint32_t *src, uint32_t n, uint32_t *dst, void *hip_stream) {
   if (n > dq::kFetchWords) return DQ_EUNSUPPORTED;
   hipError_t e = hipSuccess;
-  dq::Workspace *w = dq::take(&e);
+  dq::Workspace *w = dq::take((hipStream_t)hip_stream, &e);
   if (!w) return dq::hip_status(e);
   ++w->calls;
   hipLaunchKernelGGL(dq::k_fetch, dim3(1), dim3(256), 0, (hipStream_t)hip_stream, src, n, w->host, w->calls);
-  e = hipGetLastError();
   uint32_t word = 0;
-  if (e == hipSuccess) e = await_call(w, hip_stream, &word);
-  if (e == hipSuccess) memcpy(dst, w->host + 1, 4 * (size_t)n);
-  give_back(w);
-  return dq::hip_status(e);
+  if ((e = hipGetLastError()) != hipSuccess || (e = dq::await_call(w, (hipStream_t)hip_stream, &word)) != hipSuccess) return dq::hip_status(e);
+  memcpy(dst, w->host + 1, 4 * (size_t)n);
+  dq::give_back(w);
+  return DQ_OK;
 }
 
 }  // extern "C"

@@ -60,7 +60,8 @@ constexpr int kRanges = 6;             // copy ranges: common, 2-bit, 4-bit fixe
 
 // Everything the kernels need besides the job: PRNG key, worker count, table blob.
 struct Params {
-  const uint32_t *guard; // null, or a word the single-chunk kernels read first: not zero means do nothing (dq_bounds.hip)
+  const uint32_t *guard; // null, or a word the single-chunk kernels read first: if it is guard_call they do nothing (dq_bounds.hip)
+  uint32_t guard_call;
   const uint32_t *blob;  // device copy of the table blob
   uint32_t blob_dwords;  // multiple of 4
   uint32_t range_lo[kRanges], range_hi[kRanges];  // dword ranges a block copies into LDS (multiples of 4) ...

@@ -427,7 +427,7 @@ __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
 // with fp32 locals use 82-88 since a tile's successor is requested from inside the tile, the others at most 80).
 template <Kind KIND, typename LT>
 __global__ __launch_bounds__(kBlockThreads) void k_one(Job job, Params P) {
-  if (P.guard && gld<uint32_t>(P.guard)) return;
+  if (P.guard && gld<uint32_t>(P.guard) == P.guard_call) return;
   run_job<KIND, LT>(job, P);
 }
 template <Kind KIND, typename LT>
@@ -511,7 +511,9 @@ template <Kind KIND, typename LT>
 hipError_t go_one(const Job &job, Params p, uint32_t grid_blocks, hipStream_t s) {
   const uint32_t tiles = job_tiles(job);
   if (tiles == 0) return hipSuccess;
-  p.guard = armed_guard();
+  const Guard guard = armed_guard();
+  p.guard = guard.word;
+  p.guard_call = guard.call;
   const uint32_t blocks = blocks_per_job(tiles, 1, grid_blocks);
   hipLaunchKernelGGL((k_one<KIND, LT>), dim3(blocks), dim3(kBlockThreads), lds_bytes(p, KIND), s, job, p);
   return hipGetLastError();

@@ -137,9 +137,68 @@ def test_indices_out_of_bounds_are_refused_and_nothing_is_written(dev, n_sg):
             ctx.dq_decompress_restore(want, ch, bad, total)
         torch.cuda.synchronize()
         assert bool((out == 7).all()) and bool((total == 7.0).all())
-    for _ in range(300):                                    # more calls than a workspace has slots
+    for _ in range(300):
         got = ctx.dq_compress(x, ch, 1, sg_index=good)
     assert torch.equal(got, want)
+
+
+def test_checks_of_several_threads_and_streams_do_not_mix(dev):
+    """Workspaces pass from call to call, over streams, without a reset: good and refused calls, two indices and one, side by side."""
+    n_sg, ctx = 5000, B.Context(4, seed=1)                  # three blocks of the check
+    ch = B.make_chunk(0, [0, n_sg, 0])
+    x = gradients(1, n_sg, torch.bfloat16, dev, 5)[0]
+    good = torch.arange(n_sg - 1, -1, -1, dtype=torch.int32, device=dev)
+    bad = good.clone()
+    bad[::1111] = n_sg
+    message = ctx.dq_compress(x, ch, 1, sg_index=good)
+    restored = ctx.dq_decompress_restore(message, ch, good, torch.empty(n_sg * 256, device=dev), local=x, sg_index=good)
+    torch.cuda.synchronize()
+    errors = []
+
+    def work(k):
+        try:
+            side = torch.cuda.Stream()
+            with torch.cuda.stream(side):
+                kept = torch.full_like(restored, 7.0)
+                for i in range(40):
+                    assert torch.equal(ctx.dq_compress(x, ch, 1, sg_index=good), message)
+                    for index, origin, text in ((bad, good, "sg_index"), (good, bad, "every destination")):
+                        if (i + k) % 3 == 0:
+                            with pytest.raises(B.DqError, match=text):
+                                ctx.dq_decompress_restore(message, ch, origin, kept, local=x, sg_index=index)
+                    out = ctx.dq_decompress_restore(message, ch, good, torch.empty_like(restored), local=x, sg_index=good)
+                    assert torch.equal(out.view(torch.int32), restored.view(torch.int32))
+                assert bool((kept == 7.0).all())
+        except BaseException as e:                          # noqa: BLE001 -- shown below
+            errors.append((k, e))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+
+
+def test_a_check_under_capture_is_refused_and_leaves_the_next_one_whole(dev):
+    n_sg, ctx = 100, B.Context(4, seed=1)
+    ch = B.make_chunk(0, [0, n_sg, 0])
+    x = gradients(1, n_sg, torch.bfloat16, dev, 6)[0]
+    index = torch.arange(n_sg - 1, -1, -1, dtype=torch.int32, device=dev)
+    want = ctx.dq_compress(x, ch, 1, sg_index=index)
+    counts = torch.arange(10, dtype=torch.int32, device=dev).reshape(2, 5)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        with pytest.raises(B.DqError, match="captur"):
+            ctx.dq_compress(x, ch, 1, packed_out=want, sg_index=index)
+        with pytest.raises(B.DqError, match="captur"):
+            B.widths_of_buckets(counts)
+        plain = ctx.dq_compress(x, ch, 1)                   # without indices there is nothing to check
+    for _ in range(3):
+        graph.replay()
+        assert torch.equal(ctx.dq_compress(x, ch, 1, sg_index=index), want)
+        assert torch.equal(ctx.dq_compress(x, ch, 1), plain)
+        assert B.widths_of_buckets(counts) == [[0, 1, 2, 3], [5, 6, 7, 8]]
 
 
 # ---- plans and streams: a plan's tables lie in memory that the stream's earlier work may still be using
