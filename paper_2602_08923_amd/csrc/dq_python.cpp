@@ -42,6 +42,19 @@ void check(dq_status st) {
   fail(msg);
 }
 
+// The interpreter's lock is given up for as long as f runs: whatever launches can wait for a queue, allocate or synchronise.
+// f touches no Python object; what it reads is kept alive by the call's arguments, or held by the caller.
+struct Unlocked {
+  PyThreadState *state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+template <typename F>
+auto unlocked(F f) {
+  Unlocked here;
+  return f();
+}
+#define CALL(...) check(unlocked([&] { return L.__VA_ARGS__; }))
+
 void *stream() { return (void *)c10::hip::getCurrentHIPStream().stream(); }
 
 const at::Tensor &tensor(PyObject *o) {
@@ -98,8 +111,13 @@ dq_chunk chunk_of(PyObject *o) {
 int64_t sgs(const dq_chunk &c) { return (int64_t)c.n_sg[0] + c.n_sg[1] + c.n_sg[2] + c.n_sg[3]; }
 
 at::Tensor make(int64_t n, at::ScalarType t, const at::Tensor &like, bool zero = false) {
-  const auto o = like.options().dtype(t);
-  return zero ? at::zeros({n}, o) : at::empty({n}, o);
+  return unlocked([&] {
+    const auto o = like.options().dtype(t);
+    return zero ? at::zeros({n}, o) : at::empty({n}, o);
+  });
+}
+at::Tensor make_like(const at::Tensor &like) {
+  return unlocked([&] { return at::empty_like(like); });
 }
 PyObject *wrap(const at::Tensor &t) { return THPVariable_Wrap(t); }
 PyObject *give(PyObject *given, const at::Tensor &made) {  // the caller's own object, or the new tensor
@@ -136,16 +154,15 @@ constexpr const char *kOutside = "sg_index points outside the tensor";
 template <typename F>
 void checked(const dq::Bound *b, int n, F call, const char *first = kOutside, const char *second = nullptr) {
   void *s = stream();
-  if (n == 0) return check(call(s));
-  check(L.dqx_bounds_begin(b, n, s));
-  const dq_status st = call(s);
+  if (n == 0) return check(unlocked([&] { return call(s); }));
   int outside = 0;
-  dq_status end;
-  Py_BEGIN_ALLOW_THREADS
-  end = L.dqx_bounds_end(s, &outside);
-  Py_END_ALLOW_THREADS
-  check(st);
-  check(end);
+  check(unlocked([&] {
+    dq_status st = L.dqx_bounds_begin(b, n, s);
+    if (st != DQ_OK) return st;
+    st = call(s);
+    const dq_status end = L.dqx_bounds_end(s, &outside);
+    return st != DQ_OK ? st : end;
+  }));
   if (outside) fail(outside & 1 ? first : second);
 }
 
@@ -231,7 +248,9 @@ PyObject *py_mx_compress(PyObject *const *a, Py_ssize_t nargs) {  // fmt, local,
   const at::Tensor &local = tensor(a[1]);
   const int64_t n = local.numel();
   const at::Tensor out = a[2] == Py_None ? make((int64_t)L.dq_mx_packed_bytes(fmt, n), at::kByte, local, true) : tensor(a[2]);
-  check(L.dq_mx_compress(fmt, ptr(local), local_dtype(local), n, ptr(out), stream()));
+  void *x = ptr(local), *o = ptr(out), *s = stream();
+  const dq_dtype t = local_dtype(local);
+  CALL(dq_mx_compress(fmt, x, t, n, o, s));
   return give(a[2], out);
 }
 PyObject *py_mx_dar_hop(PyObject *const *a, Py_ssize_t nargs) {  // fmt, packed_in, local, packed_out
@@ -241,7 +260,9 @@ PyObject *py_mx_dar_hop(PyObject *const *a, Py_ssize_t nargs) {  // fmt, packed_
   const int64_t n = local.numel(), bytes = (int64_t)L.dq_mx_packed_bytes(fmt, n);
   if (in.numel() < bytes) fail("packed_in too small");
   const at::Tensor out = a[3] == Py_None ? make(bytes, at::kByte, local, true) : tensor(a[3]);
-  check(L.dq_mx_dar_hop(fmt, ptr(in), ptr(local), local_dtype(local), n, ptr(out), stream()));
+  void *i = ptr(in), *x = ptr(local), *o = ptr(out), *s = stream();
+  const dq_dtype t = local_dtype(local);
+  CALL(dq_mx_dar_hop(fmt, i, x, t, n, o, s));
   return give(a[3], out);
 }
 PyObject *py_mx_decompress(PyObject *const *a, Py_ssize_t nargs) {  // fmt, packed_in, n_entries, local, out
@@ -252,18 +273,23 @@ PyObject *py_mx_decompress(PyObject *const *a, Py_ssize_t nargs) {  // fmt, pack
   const at::Tensor *local = tensor_or_null(a[3]);
   if (in.numel() < (int64_t)L.dq_mx_packed_bytes(fmt, n)) fail("packed_in too small");
   const at::Tensor out = a[4] == Py_None ? make(n, at::kFloat, in) : tensor(a[4]);
-  check(L.dq_mx_decompress(fmt, ptr(in), ptr(local), local ? local_dtype(*local) : DQ_F32, n, as<float>(ptr(out)), stream()));
+  void *i = ptr(in), *x = ptr(local), *o = ptr(out), *s = stream();
+  const dq_dtype t = local ? local_dtype(*local) : DQ_F32;
+  CALL(dq_mx_decompress(fmt, i, x, t, n, as<float>(o), s));
   return give(a[4], out);
 }
 
 PyObject *py_replay_run(PyObject *const *a, Py_ssize_t nargs) {  // replay
   DQ_ARGS(1)
-  check(L.dq_replay_run(as<dq_replay>(handle(a[0])), nullptr, stream()));
+  void *h = handle(a[0]), *s = stream();
+  CALL(dq_replay_run(as<dq_replay>(h), nullptr, s));
   Py_RETURN_NONE;
 }
 PyObject *py_replay_run_steps(PyObject *const *a, Py_ssize_t nargs) {  // replay, first, count
   DQ_ARGS(3)
-  check(L.dq_replay_run_steps(as<dq_replay>(handle(a[0])), (uint32_t)number(a[1]), (uint32_t)number(a[2]), stream()));
+  void *h = handle(a[0]), *s = stream();
+  const uint32_t first = (uint32_t)number(a[1]), count = (uint32_t)number(a[2]);
+  CALL(dq_replay_run_steps(as<dq_replay>(h), first, count, s));
   Py_RETURN_NONE;
 }
 
@@ -279,8 +305,9 @@ PyObject *py_sg_stats(PyObject *const *a, Py_ssize_t nargs) {  // x, mu_out, F_o
   if (x.numel() % 256) fail("tensor length must be a multiple of 256");
   const int64_t n = x.numel() / 256;
   const at::Tensor mu = a[1] == Py_None ? make(n, at::kFloat, x) : tensor(a[1]), F = a[2] == Py_None ? make(n, at::kFloat, x) : tensor(a[2]);
-  void *p = ptr(x);
-  check(L.dq_sg_stats(p, local_dtype(x), n, as<float>(ptr(mu)), as<float>(ptr(F)), stream()));
+  void *p = ptr(x), *m = ptr(mu), *f = ptr(F), *s = stream();
+  const dq_dtype t = local_dtype(x);
+  CALL(dq_sg_stats(p, t, n, as<float>(m), as<float>(f), s));
   return pair(give(a[1], mu), give(a[2], F));
 }
 PyObject *py_stats_combine(PyObject *const *a, Py_ssize_t nargs) {  // mu_all, F_all
@@ -290,7 +317,8 @@ PyObject *py_stats_combine(PyObject *const *a, Py_ssize_t nargs) {  // mu_all, F
     fail("statistics are two float32 tensors of the same [n_workers, n_sg] shape");
   const int64_t n = mu_all.size(0), J = mu_all.size(1);
   const at::Tensor mu = make(J, at::kFloat, mu_all), F = make(J, at::kFloat, mu_all);
-  check(L.dq_stats_combine(as<float>(ptr(mu_all)), as<float>(ptr(F_all)), (uint32_t)n, J, as<float>(ptr(mu)), as<float>(ptr(F)), stream()));
+  void *ma = ptr(mu_all), *fa = ptr(F_all), *m = ptr(mu), *f = ptr(F), *s = stream();
+  CALL(dq_stats_combine(as<float>(ma), as<float>(fa), (uint32_t)n, J, as<float>(m), as<float>(f), s));
   return pair(wrap(mu), wrap(F));
 }
 PyObject *py_allocate(PyObject *const *a, Py_ssize_t nargs) {  // F, n_sg_per_bucket, max_code_bits, max_width
@@ -304,9 +332,11 @@ PyObject *py_allocate(PyObject *const *a, Py_ssize_t nargs) {  // F, n_sg_per_bu
   if (F.scalar_type() != at::kFloat || F.numel() % J) fail("F is float32 with a whole number of buckets");
   const int64_t nb = F.numel() / J;
   const at::Tensor widths = make(F.numel(), at::kByte, F), pos = make(F.numel(), at::kInt, F);
-  const at::Tensor counts = at::empty({nb, 5}, F.options().dtype(at::kInt));
-  check(L.dq_allocate(as<float>(ptr(F)), (uint32_t)J, (uint32_t)nb, number(a[2]), (uint32_t)number(a[3]), as<uint8_t>(ptr(widths)),
-                      as<uint32_t>(ptr(pos)), as<uint32_t>(ptr(counts)), stream()));
+  const at::Tensor counts = unlocked([&] { return at::empty({nb, 5}, F.options().dtype(at::kInt)); });
+  void *f = ptr(F), *w = ptr(widths), *p = ptr(pos), *c = ptr(counts), *s = stream();
+  const unsigned long long budget = number(a[2]);
+  const uint32_t max_width = (uint32_t)number(a[3]);
+  CALL(dq_allocate(as<float>(f), (uint32_t)J, (uint32_t)nb, budget, max_width, as<uint8_t>(w), as<uint32_t>(p), as<uint32_t>(c), s));
   PyObject *t = PyTuple_New(3);
   PyTuple_SET_ITEM(t, 0, wrap(widths));
   PyTuple_SET_ITEM(t, 1, wrap(pos));
@@ -319,9 +349,11 @@ PyObject *py_reorder(PyObject *const *a, Py_ssize_t nargs) {  // x, pos, n_sg_pe
   const int64_t J = (int64_t)number(a[2]);
   if (J == 0 || x.numel() != pos.numel() * 256 || pos.numel() % J || pos.scalar_type() != at::kInt)
     fail("x holds 256 entries per position; positions are int32, a whole number of buckets");
-  const at::Tensor out = a[3] == Py_None ? at::empty_like(x) : tensor(a[3]);
-  void *p = ptr(x);
-  check(L.dq_reorder(p, local_dtype(x), as<uint32_t>(ptr(pos)), (uint32_t)J, (uint32_t)(pos.numel() / J), ptr(out), stream()));
+  const at::Tensor out = a[3] == Py_None ? make_like(x) : tensor(a[3]);
+  void *p = ptr(x), *q = ptr(pos), *o = ptr(out), *s = stream();
+  const dq_dtype t = local_dtype(x);
+  const uint32_t nb = (uint32_t)(pos.numel() / J);
+  CALL(dq_reorder(p, t, as<uint32_t>(q), (uint32_t)J, nb, o, s));
   return give(a[3], out);
 }
 PyObject *py_reorder_mean(PyObject *const *a, Py_ssize_t nargs) {  // mu, pos, n_sg_per_bucket, counts, out, with_origin
@@ -338,18 +370,18 @@ PyObject *py_reorder_mean(PyObject *const *a, Py_ssize_t nargs) {  // mu, pos, n
   if (!mu && !with_origin) fail("nothing to compute");
   at::Tensor out, origin;
   if (a[4] != Py_None) out = tensor(a[4]);
-  else if (mu) out = at::empty_like(*mu);
-  if (with_origin) origin = at::empty_like(pos);
-  check(L.dq_reorder_mean(as<float>(ptr(mu)), as<uint32_t>(ptr(pos)), as<uint32_t>(ptr(counts)), (uint32_t)J, (uint32_t)nb,
-                          mu ? as<float>(ptr(out)) : nullptr, with_origin ? as<uint32_t>(ptr(origin)) : nullptr, stream()));
-  PyObject *o;
+  else if (mu) out = make_like(*mu);
+  if (with_origin) origin = make_like(pos);
+  void *m = ptr(mu), *p = ptr(pos), *c = ptr(counts), *o = mu ? ptr(out) : nullptr, *g = with_origin ? ptr(origin) : nullptr, *s = stream();
+  CALL(dq_reorder_mean(as<float>(m), as<uint32_t>(p), as<uint32_t>(c), (uint32_t)J, (uint32_t)nb, as<float>(o), as<uint32_t>(g), s));
+  PyObject *first;
   if (!out.defined()) {
     Py_INCREF(Py_None);
-    o = Py_None;
+    first = Py_None;
   } else {
-    o = give(a[4], out);
+    first = give(a[4], out);
   }
-  return with_origin ? pair(o, wrap(origin)) : o;
+  return with_origin ? pair(first, wrap(origin)) : first;
 }
 PyObject *py_restore(PyObject *const *a, Py_ssize_t nargs) {  // total, pos, n_sg_per_bucket, n_workers, mu_main, out
   DQ_ARGS(6)
@@ -359,9 +391,10 @@ PyObject *py_restore(PyObject *const *a, Py_ssize_t nargs) {  // total, pos, n_s
   if (J == 0 || total.scalar_type() != at::kFloat || total.numel() != pos.numel() * 256 || pos.scalar_type() != at::kInt)
     fail("the main stage's result is float32, 256 entries per position");
   if (mu && (mu->scalar_type() != at::kFloat || mu->numel() != pos.numel())) fail("mu_main is float32, one per super-group");
-  const at::Tensor out = a[5] == Py_None ? at::empty_like(total) : tensor(a[5]);
-  check(L.dq_restore(as<float>(ptr(total)), as<uint32_t>(ptr(pos)), as<float>(ptr(mu)), (uint32_t)number(a[3]), (uint32_t)J,
-                     (uint32_t)(pos.numel() / J), as<float>(ptr(out)), stream()));
+  const at::Tensor out = a[5] == Py_None ? make_like(total) : tensor(a[5]);
+  void *x = ptr(total), *p = ptr(pos), *m = ptr(mu), *o = ptr(out), *s = stream();
+  const uint32_t n_workers = (uint32_t)number(a[3]), nb = (uint32_t)(pos.numel() / J);
+  CALL(dq_restore(as<float>(x), as<uint32_t>(p), as<float>(m), n_workers, (uint32_t)J, nb, as<float>(o), s));
   return give(a[5], out);
 }
 // The check of sg_index alone, waited for: for calls that run on other streams than the current one.
@@ -379,16 +412,21 @@ PyObject *py_stats_all(PyObject *const *a, Py_ssize_t nargs) {  // list of tenso
   DQ_ARGS(1)
   const Py_ssize_t n = PyList_Check(a[0]) ? PyList_GET_SIZE(a[0]) : 0;
   if (n == 0) fail("a list of the workers' tensors");
-  const at::Tensor &x = tensor(PyList_GET_ITEM(a[0], 0));
+  const at::Tensor x = tensor(PyList_GET_ITEM(a[0], 0));
   if (x.numel() % 256) fail("tensor length must be a multiple of 256");
   std::vector<const void *> p((size_t)n);
+  std::vector<at::Tensor> held;  // another thread may change the list
+  held.reserve((size_t)n);
   for (Py_ssize_t w = 0; w < n; ++w) {
-    const at::Tensor &t = tensor(PyList_GET_ITEM(a[0], w));
-    if (t.numel() != x.numel() || t.scalar_type() != x.scalar_type()) fail("the workers' tensors have one length and type");
-    p[(size_t)w] = ptr(t);
+    held.push_back(tensor(PyList_GET_ITEM(a[0], w)));
+    if (held.back().numel() != x.numel() || held.back().scalar_type() != x.scalar_type()) fail("the workers' tensors have one length and type");
+    p[(size_t)w] = ptr(held.back());
   }
   const at::Tensor mu = make(x.numel() / 256, at::kFloat, x), F = make(x.numel() / 256, at::kFloat, x);
-  check(L.dqx_stats_all(p.data(), (uint32_t)n, local_dtype(x), x.numel() / 256, as<float>(ptr(mu)), as<float>(ptr(F)), stream()));
+  void *m = ptr(mu), *f = ptr(F), *s = stream();
+  const dq_dtype t = local_dtype(x);
+  const uint64_t n_sg = (uint64_t)x.numel() / 256;
+  CALL(dqx_stats_all(p.data(), (uint32_t)n, t, n_sg, as<float>(m), as<float>(f), s));
   return pair(wrap(mu), wrap(F));
 }
 PyObject *py_fetch(PyObject *const *a, Py_ssize_t nargs) {  // int32 tensor of at most kFetchWords values -> list of its values
@@ -399,11 +437,7 @@ PyObject *py_fetch(PyObject *const *a, Py_ssize_t nargs) {  // int32 tensor of a
   const uint32_t *p = as<uint32_t>(ptr(t));
   const uint32_t n = (uint32_t)t.numel();
   void *s = stream();
-  dq_status st;
-  Py_BEGIN_ALLOW_THREADS
-  st = L.dqx_fetch(p, n, reinterpret_cast<uint32_t *>(v), s);
-  Py_END_ALLOW_THREADS
-  check(st);
+  CALL(dqx_fetch(p, n, reinterpret_cast<uint32_t *>(v), s));
   PyObject *list = PyList_New(n);
   if (!list) throw Raised();
   for (uint32_t i = 0; i < n; ++i) PyList_SET_ITEM(list, i, PyLong_FromLong(v[i]));

@@ -3,6 +3,7 @@ by step, whose steps the parity tests hold against the oracle: same result, same
 steps -- at the edges of tiles, of the draws' batches and of the split over waves.  And the bounds
 check of super-group indices in front of a call."""
 import threading
+import time
 
 import pytest
 import torch
@@ -296,3 +297,29 @@ def test_a_plan_is_not_made_under_capture(dev):
         grads[0].zero_()                                    # a graph with something in it
     graph.replay()
     torch.cuda.synchronize()
+
+
+def test_other_threads_run_while_a_call_enqueues(dev):
+    """Thousands of launches in one call: they wait for the queue, and the interpreter is free meanwhile."""
+    n = 6000
+    g = gradients(1, 4, torch.bfloat16, dev, 1)[0]
+    rp = B.Replay(B.Context(n), B.DQ_CHAIN, B.DQ_DYNAMIQ, [g] * n, 4, [[1, 2, 1, 0]])
+    rp.run_steps(0, 2)
+    torch.cuda.synchronize()
+    ticks, stop = [], threading.Event()
+
+    def tick():
+        while not stop.is_set():
+            ticks.append(time.perf_counter())
+            time.sleep(0.0002)
+
+    t = threading.Thread(target=tick)
+    t.start()
+    time.sleep(0.01)
+    begin = time.perf_counter()
+    rp.run_steps(0, n - 1)                                  # not the whole schedule: step by step
+    end = time.perf_counter()
+    stop.set()
+    t.join()
+    torch.cuda.synchronize()
+    assert end - begin > 0.005 and sum(begin < x < end for x in ticks) >= 5, (end - begin, len(ticks))
