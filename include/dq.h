@@ -199,7 +199,11 @@ uint32_t dq_replay_n_steps(const dq_replay *plan);
  * synchronises the stream before returning). */
 dq_status dq_replay_run(dq_replay *plan, float *step_ms, void *hip_stream);
 /* Enqueue steps first .. first+count-1 only (so that a caller can bracket a run of hop steps
- * with its own events); running all steps in order is the same as dq_replay_run. */
+ * with its own events); running all steps in order is the same as dq_replay_run.  Steps that continue from a
+ * whole replay (first > 0) meet what that replay would have left run step by step.  A butterfly's
+ * keep-buffers and an all-gather's messages never leave the chip in one launch, so the first such call runs the
+ * schedule step by step once, on the inputs as they are then.  (What runs as part of a HIP graph is not
+ * seen here: steps find the buffers as the calls outside the graph left them.) */
 dq_status dq_replay_run_steps(dq_replay *plan, uint32_t first, uint32_t count, void *hip_stream);
 /* Enqueue ONE kernel launch of a step: a butterfly step in which nodes both forward and keep
  * (kind 3 below) is two launches, 0 = the re-encoding one (compress at the first step, DAR after),

@@ -561,7 +561,11 @@ struct dq_replay {
   uint8_t *scratch;
   std::vector<hipEvent_t> events;
   dq_dtype dtype;
-  bool means;
+  bool means, all_gather;
+  // A whole replay in one launch leaves the steps' buffers behind: what they hold since then.
+  bool complete = true;   // all that steps can read (of a ring or chain without all-gather a whole replay writes it)
+  uint32_t filled = 0;    // else: the messages and keep-buffers of steps 0 .. filled-1
+  bool gathered = false;  // else: the all-gather's messages
   // the upload of the tables: the stream it is ordered on, and what says that it has arrived (null: it has)
   hipStream_t stream = nullptr;
   std::atomic<Staging *> staging{nullptr};
@@ -615,6 +619,7 @@ static dq_status create(dq_ctx *ctx, const dq_replay_desc *desc, const void *con
   r->codec = desc->codec;
   r->dtype = desc->dtype;
   r->means = desc->mu != nullptr;
+  r->all_gather = desc->all_gather != 0;
   r->scratch = static_cast<uint8_t *>(scratch);
   dq_status st = build_plan(ctx, desc, worker_grads, r->scratch, out, &r->plan);
   if (st == DQ_OK && r->plan.scratch_bytes > scratch_bytes) st = DQ_EINVAL;
@@ -727,9 +732,49 @@ static dq_status run_step(dq_replay *plan, size_t i, hipStream_t s, int only = -
   return DQ_OK;
 }
 
+// Before step `first` is enqueued on its own: what it reads is there.  After a whole replay in one launch the buffers of
+// a butterfly and of an all-gather hold an older replay's content, so the schedule is run step by step once, which leaves them as a
+// replay in steps would have, and then the steps that have been run since.
+static dq_status fill_buffers(dq_replay *r, uint32_t first, hipStream_t s) {
+  const size_t ns = r->plan.steps.size();
+  if (r->complete || first <= r->filled || (r->all_gather && (first + 2 == ns || (first + 1 == ns && r->gathered)))) return DQ_OK;
+  const size_t again = r->filled;
+  for (size_t i = 0; i < ns + again; ++i) {
+    const dq_status st = run_step(r, i < ns ? i : i - ns, s);
+    if (st != DQ_OK) return st;
+  }
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const hipError_t e = hipStreamIsCapturing(s, &capture);
+  if (e == hipSuccess && capture == hipStreamCaptureStatusNone) r->complete = true;
+  return dq::hip_status(e);
+}
+// After steps first .. end-1 have been enqueued.
+static dq_status note_steps(dq_replay *r, uint32_t first, uint32_t end, hipStream_t s) {
+  if (r->complete) return DQ_OK;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const hipError_t e = hipStreamIsCapturing(s, &capture);
+  if (e != hipSuccess || capture != hipStreamCaptureStatusNone) return dq::hip_status(e);  // captured: they have not run
+  const uint32_t ns = (uint32_t)r->plan.steps.size();
+  if (first + 2 <= ns && end + 1 >= ns) r->gathered = true;
+  if (first <= r->filled && end > r->filled) r->filled = end;
+  if (r->filled == ns) r->complete = true;
+  return DQ_OK;
+}
+
 // The whole schedule in one launch.
 static dq_status run_walk(dq_replay *r, hipStream_t s) {
   const Plan &p = r->plan;
+  const bool complete = p.ring_chunks != 0 && !r->all_gather;
+  if (r->complete != complete || r->filled || r->gathered) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &capture);
+    if (e != hipSuccess) return dq::hip_status(e);
+    if (capture == hipStreamCaptureStatusNone) {
+      r->complete = complete;
+      r->filled = 0;
+      r->gathered = false;
+    }
+  }
   if (r->codec != DQ_DYNAMIQ) return dq::hip_status(dq::launch_mx_walk(r->codec, r->dtype, p.tree, p.mx, r->ctx->n_cu, s));
   return dq::hip_status(dq::launch_walk(r->dtype, p.tree, r->means, reinterpret_cast<const dq::WalkPath *>(r->scratch + p.paths_off),
                                         reinterpret_cast<const dq::WalkShare *>(r->scratch + p.shares_off), p.w, r->ctx->params, s));
@@ -740,18 +785,20 @@ dq_status dq_replay_run_steps(dq_replay *plan, uint32_t first, uint32_t count, v
   const dq_status ready = await_tables(plan, (hipStream_t)hip_stream);
   if (ready != DQ_OK) return ready;
   if (plan->plan.walk && count == plan->plan.steps.size()) return run_walk(plan, (hipStream_t)hip_stream);
-  for (uint32_t i = first; i < first + count; ++i) {
-    const dq_status st = run_step(plan, i, (hipStream_t)hip_stream);
-    if (st != DQ_OK) return st;
-  }
-  return DQ_OK;
+  if (count == 0) return DQ_OK;
+  dq_status st = fill_buffers(plan, first, (hipStream_t)hip_stream);
+  for (uint32_t i = first; i < first + count && st == DQ_OK; ++i) st = run_step(plan, i, (hipStream_t)hip_stream);
+  return st == DQ_OK ? note_steps(plan, first, first + count, (hipStream_t)hip_stream) : st;
 }
 
 dq_status dq_replay_run_launch(dq_replay *plan, uint32_t step, uint32_t launch, void *hip_stream) {
   if (!plan || step >= plan->plan.steps.size() || launch >= plan->plan.steps[step].launches.size()) return DQ_EINVAL;
   const dq_status ready = await_tables(plan, (hipStream_t)hip_stream);
   if (ready != DQ_OK) return ready;
-  return run_step(plan, step, (hipStream_t)hip_stream, (int)launch);
+  dq_status st = fill_buffers(plan, step, (hipStream_t)hip_stream);
+  if (st == DQ_OK) st = run_step(plan, step, (hipStream_t)hip_stream, (int)launch);
+  const bool done = launch + 1 == plan->plan.steps[step].launches.size();
+  return st == DQ_OK && done ? note_steps(plan, step, step + 1, (hipStream_t)hip_stream) : st;
 }
 
 dq_status dq_replay_run(dq_replay *plan, float *step_ms, void *hip_stream) {
@@ -772,6 +819,10 @@ dq_status dq_replay_run(dq_replay *plan, float *step_ms, void *hip_stream) {
     const dq_status st = run_step(plan, i, s);
     if (st != DQ_OK) return st;
     if (step_ms) he = hipEventRecord(plan->events[i + 1], s);
+  }
+  if (he == hipSuccess) {
+    const dq_status st = note_steps(plan, 0, (uint32_t)ns, s);
+    if (st != DQ_OK) return st;
   }
   if (step_ms && he == hipSuccess) he = hipEventSynchronize(plan->events[ns]);
   for (size_t i = 0; step_ms && i < ns && he == hipSuccess; ++i)

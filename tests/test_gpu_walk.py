@@ -323,3 +323,45 @@ def test_other_threads_run_while_a_call_enqueues(dev):
     t.join()
     torch.cuda.synchronize()
     assert end - begin > 0.005 and sum(begin < x < end for x in ticks) >= 5, (end - begin, len(ticks))
+
+
+@pytest.mark.parametrize("codec", [B.DQ_DYNAMIQ, B.DQ_MXFP8_E4M3])
+@pytest.mark.parametrize("topology,n,all_gather", [("ring", 5, False), ("ring", 4, True), ("chain", 6, True), ("butterfly", 8, False),
+                                                   ("butterfly", 16, True), ("butterfly", 2, True)])
+def test_steps_continue_from_a_whole_replay(dev, topology, n, all_gather, codec):
+    """Steps, and launches of a step, after a whole replay meet the state that the same replay run step by step leaves:
+    not messages and keep-buffers of an older run on other inputs."""
+    J = 3 * n
+    inputs = [gradients(n, J, torch.bfloat16, dev, seed) for seed in (1, 2)]
+    widths = [[J // 3, J // 3, J // 3, 0]]
+
+    def play(whole, continue_with):
+        grads = [g.clone() for g in inputs[0]]
+        rp = B.Replay(B.Context(n, seed=3), TOPO[topology], codec, grads, J, widths, all_gather=all_gather)
+
+        def steps():
+            for t in range(rp.n_steps):
+                rp.run_steps(t, 1)
+        steps()
+        for g, x in zip(grads, inputs[1]):
+            g.copy_(x)
+        rp.run() if whole else steps()
+        if continue_with == "launches":
+            kinds = [rp.step_info(t)[0] for t in range(rp.n_steps)]
+            for t in range(1, rp.n_steps):
+                for launch in range(2 if kinds[t] == 3 else 1):
+                    rp.run_launch(t, launch)
+        else:
+            for first, count in continue_with:
+                rp.run_steps(first, count)
+        torch.cuda.synchronize()
+        return rp.out.view(torch.int32).clone()
+
+    ns = {"ring": n, "chain": n, "butterfly": n.bit_length()}[topology] + (2 if all_gather else 0)
+    plays = [[(k, ns - k)] for k in range(1, ns)] + [[(0, 1), (ns - 1, 1)], [(0, 2), (2, ns - 2)], [(ns - 1, 1), (ns - 1, 1)], "launches"]
+    if all_gather:
+        plays += [[(ns - 2, 1), (ns - 1, 1)], [(1, 1), (ns - 1, 1)]]
+    for continue_with in plays:
+        if continue_with != "launches" and any(c < 1 or f < 1 and c == ns for f, c in continue_with):
+            continue
+        assert torch.equal(play(True, continue_with), play(False, continue_with)), continue_with
