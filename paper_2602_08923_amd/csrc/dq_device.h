@@ -127,8 +127,18 @@ hipError_t launch_batch(Kind kind, dq_dtype dtype, bool has_local, bool gather, 
 // on are written as zero: the copy that stands in for the wire puts a packed block's padding down itself
 hipError_t wire_copy(void *dst, const void *src, size_t bytes, size_t valid, hipStream_t stream);
 
-// Largest static LDS size over the codec kernels (must be 0: they address their tables from LDS byte 0)
+// Largest static LDS size over the kernels that address their tables from LDS byte 0 (must be 0): all kernels
+// of dq_kernels.hip that take a table, of dq_walk.hip and of dq_thin.hip
 hipError_t static_lds_bytes(size_t *bytes);
+hipError_t walk_static_lds(size_t *bytes);  // raise *bytes to what their kernels have
+hipError_t thin_static_lds(size_t *bytes);
+template <typename K>
+hipError_t add_static_lds(K kernel, size_t *bytes) {
+  hipFuncAttributes attr;
+  const hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(kernel));
+  if (e == hipSuccess && attr.sharedSizeBytes > *bytes) *bytes = attr.sharedSizeBytes;
+  return e;
+}
 
 // streaming probe (probe_kernels.hip): reads in_bytes, writes out_bytes (multiples of 16, out <= in)
 hipError_t stream_probe(const void *in, size_t in_bytes, void *out, size_t out_bytes, uint32_t n_cu, hipStream_t stream);

@@ -573,17 +573,11 @@ hipError_t launch_batch(Kind kind, dq_dtype dtype, bool has_local, bool gather, 
 #undef DQ_DISPATCH_LOCAL
 
 namespace {
-template <typename K>
-hipError_t add_static_lds(K kernel, size_t *bytes) {
-  hipFuncAttributes attr;
-  const hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(kernel));
-  if (e == hipSuccess && attr.sharedSizeBytes > *bytes) *bytes = attr.sharedSizeBytes;
-  return e;
-}
 template <Kind KIND, typename LT>
 hipError_t add_static_lds_of(size_t *bytes) {
-  const hipError_t e = add_static_lds(k_one<KIND, LT>, bytes);
-  return e != hipSuccess ? e : add_static_lds(k_batch<KIND, LT>, bytes);
+  hipError_t e = add_static_lds(k_one<KIND, LT>, bytes);
+  if (e == hipSuccess) e = add_static_lds(k_batch<KIND, LT>, bytes);
+  return e != hipSuccess ? e : add_static_lds(k_batch_small<KIND, LT>, bytes);
 }
 }  // namespace
 
@@ -599,7 +593,8 @@ hipError_t static_lds_bytes(size_t *bytes) {
   DQ_ONE_KIND(kDar)
   DQ_ONE_KIND(kDecompress)
 #undef DQ_ONE_KIND
-  return e;
+  if (e == hipSuccess) e = walk_static_lds(bytes);
+  return e != hipSuccess ? e : thin_static_lds(bytes);
 }
 
 hipError_t wire_copy(void *dst, const void *src, size_t bytes, size_t valid, hipStream_t s) {

@@ -396,7 +396,20 @@ hipError_t go_thin(const WalkPath *paths, const WalkShare *shares, const Walk &W
   return hipGetLastError();
 }
 
+template <typename LT>
+hipError_t static_lds_of(size_t *bytes) {
+  hipError_t e = add_static_lds(k_thin<LT, false, 4>, bytes);
+  if (e == hipSuccess) e = add_static_lds(k_thin<LT, false, 8>, bytes);
+  if (e == hipSuccess) e = add_static_lds(k_thin<LT, true, 4>, bytes);
+  return e != hipSuccess ? e : add_static_lds(k_thin<LT, true, 8>, bytes);
+}
+
 }  // namespace
+
+hipError_t thin_static_lds(size_t *bytes) {
+  const hipError_t e = static_lds_of<float>(bytes);
+  return e != hipSuccess ? e : static_lds_of<uint16_t>(bytes);
+}
 
 uint32_t thin_lds(const Params &P, uint32_t stack_bytes) { return P.blob_dwords * 4 + kThinWaves * (kThinPark + stack_bytes); }
 uint32_t thin_stack(uint32_t tile_sgs, uint32_t levels) { return levels * (tile_sgs == 1 ? kThinStack<4> : kThinStack<8>); }

@@ -355,7 +355,20 @@ hipError_t go_walk(const WalkPath *paths, const WalkShare *shares, const Walk &W
   return hipGetLastError();
 }
 
+template <typename LT>
+hipError_t static_lds_of(size_t *bytes) {
+  hipError_t e = add_static_lds(k_walk<LT, false, false>, bytes);
+  if (e == hipSuccess) e = add_static_lds(k_walk<LT, false, true>, bytes);
+  if (e == hipSuccess) e = add_static_lds(k_walk<LT, true, false>, bytes);
+  return e != hipSuccess ? e : add_static_lds(k_walk<LT, true, true>, bytes);
+}
+
 }  // namespace
+
+hipError_t walk_static_lds(size_t *bytes) {
+  const hipError_t e = static_lds_of<float>(bytes);
+  return e != hipSuccess ? e : static_lds_of<uint16_t>(bytes);
+}
 
 // The grid (grid_walk), and where every wave's share begins (split_walk): equal shares of the tiles' cost in path order.  A tile's cost by
 // width was chosen by measurement (2-bit tiles need no search; 8-bit ones collide more in LDS): with equal costs the

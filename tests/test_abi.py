@@ -69,3 +69,15 @@ def test_replay_binding_checks_the_worker_count():
 
     with pytest.raises(B.DqError, match="3 worker gradients for a context of 8"):
         B.Replay(FakeCtx(), B.DQ_RING, B.DQ_DYNAMIQ, [torch.zeros(256 * 8, dtype=torch.bfloat16)] * 3, 8, [[0, 8, 0]])
+
+
+def test_every_kernel_that_reads_tables_from_lds_byte_0_is_checked_for_static_lds():
+    """A table's place is an immediate offset from LDS byte 0, which holds while the kernel has no static LDS: dq_create asks the
+    runtime, for every kernel of the files that address tables so."""
+    csrc = os.path.join(ROOT, "paper_2602_08923_amd", "csrc")
+    for name, without in (("dq_kernels.hip", {"k_wire_copy"}), ("dq_walk.hip", set()), ("dq_thin.hip", set())):
+        text = open(os.path.join(csrc, name)).read()
+        kernels = set(re.findall(r"__global__[^;{]*?\b(k_\w+)\s*\(", text)) - without
+        assert kernels and kernels == set(re.findall(r"add_static_lds\((k_\w+)<", text)), name
+        if name == "dq_kernels.hip":
+            assert "walk_static_lds(bytes)" in text and "thin_static_lds(bytes)" in text
