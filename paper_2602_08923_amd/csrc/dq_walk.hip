@@ -387,56 +387,96 @@ static uint64_t count_tiles(const WalkPath *paths, uint32_t n_paths, uint32_t sg
   return tiles;
 }
 
-bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W) {
+// The launch of W's schedule with tiles of W->tile_sgs super-groups.  *resident: waves that a CU holds at once.  False: no block fits.
+static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, uint64_t tiles, Walk *W, uint32_t *resident) {
   constexpr uint32_t kLds = 160u * 1024;
-  uint64_t tiles = count_tiles(paths, W->n_paths, 1, &W->widths);
-  if (tiles == 0) return false;
-  // Narrow tiles (dq_thin.hip) where the wide ones would leave SIMDs idle or with one wave each: us per replay of bf16 tensors with
-  // tiles of 4 / 2 / 1 super-groups (256 CUs), by super-groups in the replay:
-  //             3,000           4,096           6,100           8,192           10,000
-  //   ring 4    13 / 12 / 9     14 / 14 / 11    16 / 17 / 16    18 / 22 / 22    20 / 25 / 23
-  //   ring 16   27 / 22 / 18    29 / 25 / 22    32 / 29 / 29    38 / 38 / 48    42 / 45 / 50
-  //   ring 100  117 / 86 / 75   129 / 104 / 106 137 / 131 / 131 172 / 162 / 208 181 / 177 / 226
-  //   tree 8    18 / 14 / 12    18 / 16 / 14    20 / 19 / 20    26 / 28 / 23    28 / 30 / 29
-  //   tree 64   97 / 59 / 50    99 / 88 / 88    106 / 108 / 95  176 / 139 / 134 214 / 162 / 161
-  // One super-group while four waves per SIMD hold them all; in short schedules, where a wave's start counts more than its hops, a
-  // half more.  Two as far as they gain: not as far with fp32 tensors in a ring or chain, whose waves are three per SIMD then
-  // (6,144 super-groups, ring 256: 345 us against 334).
-  const bool f32 = dtype == DQ_F32;
-  const uint32_t some = n_cu * (f32 ? 20u : 24u);
-  const uint32_t most1 = W->n <= 8 ? some : n_cu * 16u, most2 = W->n <= 8 ? 0 : W->n >= 32 && (tree || !f32) ? n_cu * 40u : some;
-  W->tile_sgs = tiles <= most1 ? 1 : tiles <= most2 ? 2 : kWaveSGs;
+  uint32_t lds, most;  // most: waves that fit a CU's registers
   if (W->tile_sgs < kWaveSGs) {
-    tiles = count_tiles(paths, W->n_paths, W->tile_sgs, &W->widths);
     W->stack_bytes = thin_stack(W->tile_sgs, W->levels);
     W->waves = 4;
-    const uint64_t needed = (tiles + W->waves - 1) / W->waves;
-    if (thin_lds(P, W->stack_bytes) <= kLds) {
-      const uint64_t most = (uint64_t)n_cu * (kLds / thin_lds(P, W->stack_bytes));
-      W->blocks = (uint32_t)(needed < most ? needed : most);
-      W->by_cost = 0;
-      return true;
-    }
-    W->tile_sgs = kWaveSGs;
+    lds = thin_lds(P, W->stack_bytes);
+    most = f32 && W->tile_sgs == 2 ? 12 : 16;
+  } else {
+    // the stack area also stages half a tile's result
+    W->stack_bytes = W->levels * (W->raw ? kStackRaw : kStackCoded);
+    if (W->stack_bytes < kXposeBytes) W->stack_bytes = kXposeBytes;
+    // A butterfly's two blocks per CU share a copy of the tables each; where there are fewer tiles than two waves for every
+    // SIMD, blocks of four reach all CUs.  Rings and chains always take blocks of four, 29 KB at the levels of 25 MB and n = 8: five per CU.
+    // (Blocks of ten waves put three waves on two of the SIMDs, and the CU has no room for the second one: 97 us, not 75.)
+    W->waves = tree && tiles >= (uint64_t)n_cu * 8 ? 8 : 4;
+    if (walk_lds(P, tree, W->stack_bytes, W->waves) > kLds) W->waves = 4;  // raw chunks of 1,024 workers and more
+    lds = walk_lds(P, tree, W->stack_bytes, W->waves);
+    most = 4 * (tree ? kWalkPerSimd<float, true> : (f32 ? kWalkPerSimd<float, false> : kWalkPerSimd<uint16_t, false>));
   }
-  tiles = count_tiles(paths, W->n_paths, kWaveSGs, &W->widths);
-  // the stack area also stages half a tile's result
-  W->stack_bytes = W->levels * (W->raw ? kStackRaw : kStackCoded);
-  if (W->stack_bytes < kXposeBytes) W->stack_bytes = kXposeBytes;
-  // A butterfly's two blocks per CU share a copy of the tables each; where there are fewer tiles than two waves for every
-  // SIMD, blocks of four reach all CUs.  Rings and chains always take blocks of four, 29 KB at the levels of 25 MB and n = 8: five per CU.
-  // (Blocks of ten waves put three waves on two of the SIMDs, and the CU has no room for the second one: 97 us, not 75.)
-  const uint32_t most = 4 * (tree ? kWalkPerSimd<float, true> : (f32 ? kWalkPerSimd<float, false> : kWalkPerSimd<uint16_t, false>));
-  W->waves = tree && tiles >= (uint64_t)n_cu * 8 ? 8 : 4;
-  const uint32_t lds = walk_lds(P, tree, W->stack_bytes, W->waves);
   uint32_t per_cu = kLds / lds;
   if (per_cu == 0) return false;
-  if (per_cu > most / W->waves) per_cu = most / W->waves;
-  const uint64_t needed = (tiles + W->waves - 1) / W->waves;
-  W->blocks = n_cu * per_cu;
-  if (W->blocks > needed) W->blocks = (uint32_t)needed;
-  W->by_cost = tiles >= 2ull * W->blocks * W->waves;
+  const uint32_t held = per_cu < most / W->waves ? per_cu : most / W->waves;
+  *resident = held * W->waves;
+  if (W->tile_sgs == kWaveSGs) per_cu = held;
+  const uint64_t needed = (tiles + W->waves - 1) / W->waves, blocks = (uint64_t)n_cu * per_cu;
+  W->blocks = (uint32_t)(needed < blocks ? needed : blocks);
+  W->by_cost = W->tile_sgs == kWaveSGs && tiles >= 2ull * W->blocks * W->waves;
   return true;
+}
+
+// Tiles of 1, 2 (dq_thin.hip) or 4 super-groups: the narrower, the shorter a hop's chain and the more hops' worth of
+// instructions there are in all, so narrow ones pay where wide ones would leave SIMDs idle or with a wave or two each.
+// us per replay with all-gather, tiles of 1 / 2 / 4 super-groups, bf16 tensors, 256 CUs, by super-groups (profiles/replay_tile_sizes.txt has
+// all that was measured, bf16 and fp32, 2 to 256 workers):
+//              3,000          4,096           6,100           8,192           10,000          12,288
+//   ring 4     8/11/12        10/12/12        13/15/14        19/18/16        21/23/18        21/26/20
+//   ring 16    16/20/26       21/22/27        28/26/33        46/32/34        47/39/42        48/44/43
+//   ring 100   71/80/113      85/81/125       128/115/155     208/141/157     224/172/208     266/272/212
+//   tree 8     10/13/16       12/14/16        18/18/20        21/26/22        27/27/29        30/28/30
+//   tree 64    49/57/95       85/56/95        87/98/109       125/144/166     156/157/213     179/163/220
+//   tree 256   246/340/358    269/341/357     385/647/695     511/810/648     636/840/832     761/1005/856
+// Short schedules and rings: one super-group while four waves per SIMD hold them all (three for 16 workers' trees, whose stacks take
+// LDS), and half as many again with few workers, where a wave's start counts more than its hops; two up to the sizes at which four
+// are better with that dtype and n.  What the CUs hold of a wider butterfly falls with the levels of its stack, differently for each
+// tile size, so there the time is estimated, up to 48 super-groups per CU: beyond, the three are within 20 % of each other with no order.
+// Of the 288 rows up to 12,288 super-groups the rule takes a choice within 6 % of the best in 263, the geometric mean of what it loses is
+// 1.2 % (the thresholds that were here before, the same for butterflies of all widths: 219, 4.6 %).  It is further off where the super-groups
+// are one tile more than the waves that the CUs hold and that tile is a cheap one (tree 64, 4,096), and takes the slowest of the three
+// for 16 workers' trees of 10,000 (51 us for 41): between 6,144 and 8,192 four are better there, and a third line is not worth it.
+static uint64_t tree_time(uint32_t n, uint32_t n_cu, uint32_t sgs, uint64_t tiles, uint32_t resident) {
+  // in 0.01 us, fitted to the measurement: the launch, a tile's start, a hop alone and by the waves of the same SIMD
+  struct Cost { uint32_t launch, start, hop, wave; };
+  const Cost c = sgs == 1 ? Cost{640, 200, 31, 12} : sgs == 2 ? Cost{600, 240, 34, 25} : Cost{670, 0, 78, 56};
+  const uint64_t at_once = (uint64_t)n_cu * resident, full = tiles / at_once, rest = tiles % at_once;
+  const uint64_t rounds = full + (rest != 0), waves = full * resident / 4 + (rest + 4 * n_cu - 1) / (4 * n_cu);
+  return c.launch + rounds * c.start + n * (rounds * c.hop + waves * c.wave);
+}
+// Super-groups of a tile, or 0: by tree_time.
+static uint32_t tile_for(uint32_t n, bool f32, bool tree, uint32_t n_cu, uint64_t super_groups) {
+  const uint32_t per_cu = (uint32_t)((super_groups + n_cu - 1) / n_cu);
+  if (n <= 8) return per_cu <= (tree && (f32 || n <= 4) ? 20 : 24) ? 1 : kWaveSGs;
+  if (tree && n >= 32) return per_cu <= 48 ? 0 : kWaveSGs;
+  return per_cu <= (tree ? 12 : 16) ? 1 : per_cu <= (!tree && n >= 16 && !f32 ? 40 : 24) ? 2 : kWaveSGs;
+}
+
+bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W) {
+  const bool f32 = dtype == DQ_F32;
+  const uint64_t super_groups = count_tiles(paths, W->n_paths, 1, &W->widths);
+  if (super_groups == 0) return false;
+  const uint32_t wanted = tile_for(W->n, f32, tree, n_cu, super_groups);
+  Walk best = *W;
+  uint64_t best_time = 0;
+  bool found = false;
+  for (uint32_t sgs = kWaveSGs; sgs >= (wanted ? wanted : 1); sgs /= 2) {  // the wanted one, or the next wider that fits
+    Walk w = *W;
+    w.tile_sgs = sgs;
+    uint32_t resident = 0;
+    const uint64_t tiles = count_tiles(paths, W->n_paths, sgs, &w.widths);
+    if (!grid_of_tiles(P, f32, tree, n_cu, tiles, &w, &resident)) continue;
+    const uint64_t time = wanted ? 0 : tree_time(W->n, n_cu, sgs, tiles, resident);
+    if (!found || time <= best_time) {
+      best = w;
+      best_time = time;
+      found = true;
+    }
+  }
+  if (found) *W = best;
+  return found;
 }
 
 void split_walk(const WalkPath *paths, const Walk &W, std::vector<WalkShare> *shares) {

@@ -365,3 +365,22 @@ def test_steps_continue_from_a_whole_replay(dev, topology, n, all_gather, codec)
         if continue_with != "launches" and any(c < 1 or f < 1 and c == ns for f, c in continue_with):
             continue
         assert torch.equal(play(True, continue_with), play(False, continue_with)), continue_with
+
+
+@pytest.mark.parametrize("topology,n,widths,dtype", [
+    # wide trees, whose tile size follows an estimate: each size of tile, several rounds of tiles per wave
+    ("butterfly", 32, [[300, 2500, 900, 396]], torch.bfloat16), ("butterfly", 128, [[201, 1500, 300, 47]], torch.float32),
+    ("butterfly", 128, [[1001, 5002, 2003, 186]], torch.bfloat16), ("butterfly", 256, [[511, 1025, 400, 112]], torch.bfloat16),
+    ("butterfly", 256, [[0, 5000, 2900, 292]], torch.float32), ("butterfly", 64, [[3201, 9003, 900, 80]], torch.bfloat16),
+    ("ring", 256, [[257, 513, 200, 54]], torch.float32), ("ring", 256, [[1025, 4097, 1900, 146]], torch.bfloat16),
+    ("chain", 200, [[1501, 4003, 2707, 302]], torch.bfloat16),
+    # raw chunks of so many workers that the stacks of eight waves do not fit a CU
+    ("butterfly", 1024, [[4000, 4000, 4000, 1312]], torch.bfloat16),
+])
+def test_whole_replay_of_many_workers_equals_its_steps(dev, topology, n, widths, dtype):
+    J = sum(widths[0])
+    assert topology == "chain" or J % n == 0
+    grads = gradients(8, J, dtype, dev, n + J)
+    rp = B.Replay(B.Context(n, seed=n), TOPO[topology], B.DQ_DYNAMIQ, [grads[(3 * w + w // 8) % 8] for w in range(n)], J, widths, all_gather=True,
+                  mu=torch.randn(J, device=dev) * 1e-4)
+    whole_against_steps(rp, {"ring": n, "chain": 1, "butterfly": 0}[topology])
