@@ -447,8 +447,8 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
 // therefore names the stream that the scratch belongs to, and the tables go there as that stream's work: one block copies them
 // from pinned memory (55 KB for 8 workers' ring of 8,192 super-groups) and then says so in a flag that the host reads without a call
 // into the runtime, for launches on other streams and under capture wait for it.  Without a stream, and for tables
-// beyond kPinned, the host waits until nothing can be reading the scratch and copies.  (What bounds the one block is the trip over
-// PCIe, a few us for 55 KB.  A copy that the host waits for, besides needing an idle scratch: the all-reduce of 8 workers' 8,192
+// beyond kPinned, the host waits until nothing can be reading the scratch and copies.  (The one block is bound by its trips over
+// PCIe, 8 us by the profiler.  A copy that the host waits for, besides needing an idle scratch: the all-reduce of 8 workers' 8,192
 // super-groups took 104 us instead of 92.)
 constexpr size_t kPinned = 256u << 10;
 constexpr size_t kStagings = 8;
@@ -462,14 +462,13 @@ std::mutex g_staging_mutex;
 std::vector<Staging *> g_stagings;  // at most kStagings, kept until the process ends; one is taken again when its last upload has arrived
 
 __global__ void __launch_bounds__(1024) k_upload(const uint4 *src, uint4 *dst, uint32_t words, uint32_t *flag, uint32_t number) {
-  constexpr uint32_t kAhead = 4;  // latency of the host's memory: 64 KB in flight
-  for (uint32_t i = threadIdx.x; i < words; i += kAhead * 1024) {
-    uint4 w[kAhead];
-#pragma unroll
-    for (uint32_t k = 0; k < kAhead; ++k) w[k] = src[i + k * 1024 < words ? i + k * 1024 : i];
-#pragma unroll
-    for (uint32_t k = 0; k < kAhead; ++k)
-      if (i + k * 1024 < words) dst[i + k * 1024] = w[k];
+  for (uint32_t i = threadIdx.x; i < words; i += 4096) {  // latency of the host's memory: 64 KB in flight
+    const uint32_t j = i + 1024, k = i + 2048, l = i + 3072;
+    const uint4 a = src[i], b = src[j < words ? j : i], c = src[k < words ? k : i], d = src[l < words ? l : i];
+    dst[i] = a;
+    if (j < words) dst[j] = b;
+    if (k < words) dst[k] = c;
+    if (l < words) dst[l] = d;
   }
   __threadfence_system();
   __syncthreads();
