@@ -3,19 +3,20 @@
 
 A "step" is one pass of the whole hot path over one batch of synthetic input: the full
 reduce-scatter hop replay of the chosen workload (compress, every DAR hop, every
-decompress-accumulate) for all simulated workers, inputs resident in HBM.  The default
+decompress-accumulate) for all simulated workers, inputs resident in HBM.  Every step of the
+timed region is the same call, a whole replay, which is one kernel launch.  The default
 workload is benchmark configuration 2: 8-worker ring over one 25 MB bf16 DDP bucket per
 worker (13,107,200 entries, N(0,1e-3) with 0.1 % x100 outliers), DynamiQ at ~4 bits/entry.
 
 Prints ONE JSON line.  `value` = gradient bytes processed per second over the whole replay
-(entries handled by every hop x sizeof(gradient dtype) / time).  `roofline` prices the
-dominant kernel (the DAR hop) by its algorithmic bytes per entry / its launch duration
-measured with HIP events on the launch stream inside the timed region, and carries
-`copy_ceiling`: a streaming probe with the DAR hop's read : write ratio, run in the same
-process.  `roofline_by_config` repeats the DAR measurement on the other configurations
-(3: the three MX formats, 4: the 100-bucket butterfly, 5: the 64-worker chain), each set up
-and torn down in turn.  `cpu_baseline` times the CPU oracle on a bounded sample of the
-headline workload on one host core.
+(entries handled by every hop x sizeof(gradient dtype) / time).  `roofline` prices that launch by
+what a replay cannot do without (every worker's entries and the means read once, the sums written
+once); `copy_ceiling` in it is a streaming probe with the same read : write sizes, run in the same
+process.  `roofline_dar_hop` prices the DAR hop as a launch of its own, the form in which one GPU
+per worker would run it: step-by-step replays AFTER the timed region, their DAR launches bracketed
+by HIP events.  `roofline_by_config` repeats both on the other configurations (3: the three MX
+formats, 4: the 100-bucket butterfly, 5: the 64-worker chain), each set up and torn down in turn.
+`cpu_baseline` times the CPU oracle on a bounded sample of the headline workload on one host core.
 """
 import argparse
 import gc
@@ -28,14 +29,16 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 # Figures that only a profiler run can give, each from a summary under profiles/ made with this
-# script (the summary names its command).  Key: (workload, codec).  Workloads without an entry
-# print null: nothing is carried over from another configuration.
-#   traffic: HBM bytes per DAR launch from two `rocprofv3 --pmc` runs (FETCH_SIZE, then WRITE_SIZE;
+# script (the summary names its command).  Key: (workload, codec), then the launch.  Workloads without
+# an entry print null: nothing is carried over from another configuration.
+#   traffic: HBM bytes per launch from two `rocprofv3 --pmc` runs (FETCH_SIZE, then WRITE_SIZE;
 #            KiB per dispatch), each scaled by what the same counter reads for a plain copy of 2^30
 #            bytes on the same box: FETCH_SIZE counts half the bytes read (x2.0), WRITE_SIZE all (x1.0).
-#   valu:    vector-ALU wave instructions per DAR launch (SQ_INSTS_VALU); one is 64 lane operations.
+#   valu:    vector-ALU wave instructions per launch (SQ_INSTS_VALU); one is 64 lane operations.
 MEASURED = {
-    (2, 0): {"traffic": int((16261.1 * 2.0 + 6228.8 * 1.0) * 1024), "valu": 5_244_460, "profile": "profiles/dq_dar_hop_cfg2_pmc.txt"},
+    (2, 0): {"replay": {"traffic": int((129761.4 * 2.0 + 99916.1 * 1.0) * 1024), "valu": 32_672_069},
+             "dar_hop": {"traffic": int((16476.8 * 2.0 + 6203.2 * 1.0) * 1024), "valu": 5_331_100},
+             "profile": "profiles/cfg2_pmc.txt"},
 }
 # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz: lane operations per second the vector ALUs can issue
 VALU_PEAK_TLANEOPS = 256 * 4 * 16 * 2.4e9 / 1e12
@@ -146,14 +149,17 @@ class Workload:
         self.dar_with_mean = [self.mu is not None and (wl.topology != "butterfly" or i <= 1)
                               for (_, i, _, is_dar, _) in self.calls if is_dar]
 
-    def replay(self, events=None):
-        """Enqueue one whole replay.  events: a list that receives (start, end) event pairs, one per
+    def replay_bytes(self):
+        """What a replay must read and write: every worker's entries and the means once, the sums once."""
+        entries = self.n_sg * 256 * self.n_buckets
+        read = self.n * entries * self.dtype_bytes + (0 if self.mu is None else 4 * self.n_sg * self.n_buckets)
+        return read, 4 * entries
+
+    def replay_by_steps(self, events):
+        """Enqueue one replay step by step.  events: a list that receives (start, end) event pairs, one per
         maximal run of consecutive DAR launches."""
         import torch
         rp = self.rp
-        if events is None:
-            rp.run_steps(0, rp.n_steps)
-            return
         in_run = False
         for what, step, launch, is_dar, _ in self.calls:
             if is_dar and not in_run:
@@ -175,29 +181,35 @@ class Workload:
             events.append((a, b))
 
     def measure(self, steps, warmup):
-        """Time exactly `steps` replays; every `every`-th carries the event brackets of its DAR launches."""
-        import numpy as np
+        """Time exactly `steps` whole replays; then, apart from them, the DAR launches of a few replays by steps."""
         import torch
         for _ in range(warmup):
-            self.replay()
-        # two event records and extra calls into the library cost a few us per bracket: most replays run plain
-        every = max(1, min(8, steps // 8))
-        brackets = []
+            self.rp.run()
+        first, last = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
-        for i in range(steps):
-            self.replay(brackets if i % every == 0 else None)
+        first.record()
+        for _ in range(steps):
+            self.rp.run()
+        last.record()
         torch.cuda.synchronize()
         t1 = time.perf_counter()
         ms_per_step = (t1 - t0) * 1e3 / steps
-        value = self.hop_entries * self.dtype_bytes / (ms_per_step * 1e-3) / 1e9
+        read, written = self.replay_bytes()
+        launch_ms = first.elapsed_time(last) / steps
+        res = {"ms_per_step": ms_per_step, "value": self.hop_entries * self.dtype_bytes / (ms_per_step * 1e-3) / 1e9,
+               "replay_us": launch_ms * 1e3, "replay_GBps": (read + written) / (launch_ms * 1e-3) / 1e9}
         dar = [(e, lb, wm) for (_, _, _, is_dar, e), lb, wm in
                zip([c for c in self.calls if c[3]], self.dar_local_bytes, self.dar_with_mean)]
-        n_dar = len(dar)
-        res = {"ms_per_step": ms_per_step, "value": value, "n_dar": n_dar, "bracketed_replays": (steps + every - 1) // every,
-               "every": every}
+        n_dar = res["n_dar"] = len(dar)
         if n_dar:
-            total_ms = float(sum(a.elapsed_time(b) for a, b in brackets)) / res["bracketed_replays"]  # per replay
+            rounds = res["dar_rounds"] = max(2, min(8, steps // 4))
+            brackets = []
+            self.replay_by_steps([])
+            for _ in range(rounds):
+                self.replay_by_steps(brackets)
+            torch.cuda.synchronize()
+            total_ms = float(sum(a.elapsed_time(b) for a, b in brackets)) / rounds  # per replay
             total_bytes = sum(e * algorithmic_bytes_per_entry(self.codec, self.counts_total, self.n_sg * self.n_buckets, lb, "dar", wm)
                               for e, lb, wm in dar)
             res.update({
@@ -229,11 +241,20 @@ class Workload:
         torch.cuda.empty_cache()
 
 
+def alu_view(valu, us):
+    """The same launch against the rate at which the vector ALUs issue at four cycles an instruction and the peak clock (the codec is
+    bound by their issue, not by HBM)."""
+    if not valu:
+        return None
+    rate = valu * 64 / (us * 1e-6) / 1e12
+    return {"bound": "alu", "unit": "T lane-op/s", "peak": round(VALU_PEAK_TLANEOPS, 2), "achieved": round(rate, 2),
+            "frac": round(rate / VALU_PEAK_TLANEOPS, 4), "valu_wave_instructions_per_launch": valu}
+
+
 def copy_ceiling(ctx, read_bytes, write_bytes, dev, reps=40):
-    """The streaming probe at the DAR launch's read and write sizes: once cycling through as many
-    distinct input regions as the replay's DAR launches read between two visits of the same data
-    (same footprint, so the 256 MB Infinity Cache helps or not as it does for the replay), once over
-    inputs of 4 GB (HBM only)."""
+    """The streaming probe at a launch's read and write sizes: once cycling through eight distinct input
+    regions, as a step-by-step replay's DAR launches cycle through the workers' gradients (same footprint, so
+    the 256 MB Infinity Cache helps or not as it does for them), once over inputs of 4 GB (HBM only)."""
     import torch
     from paper_2602_08923_amd import binding as B
     if read_bytes > (1 << 30):  # a probe launch of 1 GiB is in the streaming regime already: keep the ratio, cap the size
@@ -441,7 +462,7 @@ def main():
     ap.add_argument("--no-prepost", action="store_true",
                     help="skip the context timings of the steps before and after the main stage")
     ap.add_argument("--no-by-config", action="store_true",
-                    help="skip the DAR measurements on the other configurations (roofline_by_config)")
+                    help="skip the measurements on the other configurations (roofline_by_config)")
     ap.add_argument("--no-copy-ceiling", action="store_true", help="skip the streaming probe")
     ap.add_argument("--no-mean", action="store_true",
                     help="run the main stage without per-super-group means (the default subtracts them, Section 3.1)")
@@ -466,30 +487,37 @@ def main():
     reps = max(1, min(args.steps, 20))
     step_ms_by_kind = W.step_times(reps)
     known = MEASURED.get((args.workload, codec), {}) if args.entries is None and not args.no_mean else {}
+    replay, dar = known.get("replay", {}), known.get("dar_hop", {})
+    read_b, write_b = W.replay_bytes()
     roofline = {
-        "bound": "hbm", "kernel": "dq_dar_hop" if codec == 0 else "dq_mx_dar_hop",
-        "achieved": round(m.get("dar_achieved_GBps", 0.0), 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
-        "frac": round(m.get("dar_achieved_GBps", 0.0) / HBM_PEAK_GBPS, 4),
-        "traffic": known.get("traffic"),
-        "algorithmic_bytes_per_entry": m.get("dar_bytes_per_entry"), "entries_per_launch": m.get("dar_entries"),
-        "avg_launch_us": round(m.get("dar_us", float("nan")), 2),
-        "gradient_GBps_per_dar_hop": round(m.get("dar_gradient_GBps", 0.0), 1),
-        "launches_per_replay": m["n_dar"],
-        # the kernel is bound by vector-ALU issue, not by HBM: the same launch priced against the issue rate
-        "alu_view": None if not known.get("valu") or not m["n_dar"] else {
-            "bound": "alu", "unit": "T lane-op/s", "peak": round(VALU_PEAK_TLANEOPS, 2),
-            "achieved": round(known["valu"] * 64 / (m["dar_us"] * 1e-6) / 1e12, 2),
-            "frac": round(known["valu"] * 64 / (m["dar_us"] * 1e-6) / 1e12 / VALU_PEAK_TLANEOPS, 4),
-            "valu_wave_instructions_per_launch": known["valu"]},
-        "counters_from": known.get("profile") if known.get("traffic") or known.get("valu") else None,
-        "timing": f"HIP events on the launch stream bracketing every run of consecutive DAR launches of every "
-                  f"{m['every']}-th replay inside the timed region ({m['bracketed_replays']} replays bracketed)",
+        "bound": "hbm", "kernel": "whole replay (dq_replay_run: every tile through all hops in one launch)",
+        "achieved": round(m["replay_GBps"], 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
+        "frac": round(m["replay_GBps"] / HBM_PEAK_GBPS, 4), "traffic": replay.get("traffic"),
+        "algorithmic_bytes_per_launch": read_b + write_b, "avg_launch_us": round(m["replay_us"], 2),
+        "alu_view": alu_view(replay.get("valu"), m["replay_us"]),
+        "counters_from": known.get("profile") if replay.get("traffic") else None,
+        "timing": f"HIP events around the {args.steps} launches of the timed region",
     }
-    if not args.no_copy_ceiling and m["n_dar"]:
-        read_b = m["dar_entries"] * (m["dar_bytes_per_entry"] - packed_bytes_per_entry(codec, W.counts_total, W.n_sg * W.n_buckets))
-        write_b = m["dar_entries"] * packed_bytes_per_entry(codec, W.counts_total, W.n_sg * W.n_buckets)
-        roofline["copy_ceiling"] = copy_ceiling(W.ctx, int(read_b), int(write_b), dev)
-        roofline["frac_of_copy_ceiling"] = round(m["dar_achieved_GBps"] / roofline["copy_ceiling"]["same_footprint_GBps"], 4)
+    if not args.no_copy_ceiling:
+        roofline["copy_ceiling"] = copy_ceiling(W.ctx, read_b, write_b, dev)
+        roofline["frac_of_copy_ceiling"] = round(m["replay_GBps"] / roofline["copy_ceiling"]["same_footprint_GBps"], 4)
+    roofline_dar = None
+    if m["n_dar"]:
+        roofline_dar = {
+            "bound": "hbm", "kernel": "dq_dar_hop" if codec == 0 else "dq_mx_dar_hop",
+            "achieved": round(m["dar_achieved_GBps"], 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
+            "frac": round(m["dar_achieved_GBps"] / HBM_PEAK_GBPS, 4), "traffic": dar.get("traffic"),
+            "algorithmic_bytes_per_entry": m["dar_bytes_per_entry"], "entries_per_launch": m["dar_entries"],
+            "avg_launch_us": round(m["dar_us"], 2), "gradient_GBps_per_dar_hop": round(m["dar_gradient_GBps"], 1),
+            "launches_per_replay": m["n_dar"], "alu_view": alu_view(dar.get("valu"), m["dar_us"]),
+            "counters_from": known.get("profile") if dar.get("traffic") else None,
+            "timing": f"HIP events bracketing every run of consecutive DAR launches of {m['dar_rounds']} replays by steps, after the timed region",
+        }
+        if not args.no_copy_ceiling:
+            packed = packed_bytes_per_entry(codec, W.counts_total, W.n_sg * W.n_buckets)
+            cc = roofline_dar["copy_ceiling"] = copy_ceiling(W.ctx, int(m["dar_entries"] * (m["dar_bytes_per_entry"] - packed)),
+                                                             int(m["dar_entries"] * packed), dev)
+            roofline_dar["frac_of_copy_ceiling"] = round(m["dar_achieved_GBps"] / cc["same_footprint_GBps"], 4)
 
     prepost = None
     if codec == 0 and not args.no_prepost and W.wl.topology != "chain" and W.n_buckets == 1:
@@ -514,7 +542,7 @@ def main():
     W.close()
     del W
 
-    # ---- the DAR hop on the other configurations, one after the other in this process
+    # ---- the other configurations, one after the other in this process
     by_config = None
     if not args.no_by_config:
         by_config = {}
@@ -531,6 +559,7 @@ def main():
                     "dar_achieved_GBps": round(r["dar_achieved_GBps"], 1), "avg_launch_us": round(r["dar_us"], 2),
                     "entries_per_launch": r["dar_entries"], "algorithmic_bytes_per_entry": round(r["dar_bytes_per_entry"], 6),
                     "launches_per_replay": r["n_dar"], "value_GBps": round(r["value"], 2), "ms_per_step": round(r["ms_per_step"], 4),
+                    "replay_GBps": round(r["replay_GBps"], 1), "replay_frac_of_hbm_peak": round(r["replay_GBps"] / HBM_PEAK_GBPS, 4),
                     "steps": k, "warmup": w}
                 if r["n_dar"]:
                     pk = packed_bytes_per_entry(X.codec, X.counts_total, X.n_sg * X.n_buckets)
@@ -550,6 +579,7 @@ def main():
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": config,
         "roofline": roofline,
+        "roofline_dar_hop": roofline_dar,
         "roofline_by_config": by_config,
         "prepost": prepost,
         "cpu_baseline": cpu,
