@@ -2,11 +2,12 @@
 // a group, not all 16, so a wave's tile is E / 4 super-groups and there are 16 / E times as many waves.
 //
 // Why: a tile's hops are a serial chain.  With a tile of four super-groups per wave, a schedule of fewer than some 4,000
-// super-groups leaves most SIMDs with one wave or none, and a hop takes 1.08 us whatever the size: the instructions of 16
+// super-groups leaves most SIMDs with one wave or none, and a hop takes 1.1 us whatever the size: the instructions of 16
 // entries one after the other, then the next slice's trip from memory.  With 4 entries per lane the chain of a hop is a
-// quarter of it, and the slices are requested four hops ahead (they are two registers each): 0.45 us per hop.  Measured, bf16, wide
-// tile to E = 8 to E = 4: ring of 100, 1,000 super-groups, 115 -> 70 -> 50 us; 64 workers' recursive halving 96 -> 50 -> 35;
-// ring of 256, 4,096 super-groups of 2 to 16 bits, 283 -> 213 -> 214.  grid_walk (dq_walk.hip) says which schedules come here.
+// quarter of it, and the slices are requested four hops ahead (they are two registers each): 0.45 to 0.5 us per hop.  Measured, bf16, wide
+// tile to E = 8 to E = 4: ring of 100, 1,000 super-groups, 114 -> 68 -> 50 us; 64 workers' recursive halving 94 -> 48 -> 34;
+// ring of 256, 4,096 super-groups of 2 to 16 bits, 284 -> 209 -> 222 (profiles/replay_tile_sizes.txt).  grid_walk (dq_walk.hip) says which
+// schedules come here.
 //
 // What differs from the wide tile:
 //   draws    : a lane draws the group's 16 bytes for ONE of the next 16 / E hops, and the group's lanes exchange them through

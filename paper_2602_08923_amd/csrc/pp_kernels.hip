@@ -237,8 +237,7 @@ __global__ void __launch_bounds__(kAllocThreads) k_alloc_positions(const float *
 //
 // What bounds it: one CU's vector ALU and LDS (51,200 norms are 800 wave instructions for every instruction of a pass,
 // and an LDS atomic of a wave takes 12 cycles) and, for small buckets, the barriers and scans of the levels.
-// 51,200 norms take 22 us (10 of them are the first level's and the two brackets' passes, 3 the loads and 9 x 0.4 the scans
-// and searches of the boundaries), 8192 10 us; a gather of the candidates (two LDS atomics with a result per row) with a
+// 51,200 norms take 22 us, 8192 10 us; a gather of the candidates (two LDS atomics with a result per row) with a
 // bisection, a barrier per step, took 46 and 35 us.
 constexpr uint32_t kBins8 = 4096, kBins4 = 6144, kBins16 = 8192;  // brackets of 3 bins, of 3 * 1.07 + 2 and of 3 * 2 + 2
 constexpr uint32_t kCopies = 8;
