@@ -272,7 +272,8 @@ dq_status take_tables(double g4, double g8, int device, Tables **out) {
   std::vector<uint32_t> blob;
   dq_status st = build_tables(g4, g8, t->P, blob);
   if (st == DQ_OK && (!hip_ok(hipMalloc((void **)&t->dev, blob.size() * 4)) ||
-                      !hip_ok(hipMemcpy(t->dev, blob.data(), blob.size() * 4, hipMemcpyHostToDevice))))
+                      !hip_ok(hipMemcpy(t->dev, blob.data(), blob.size() * 4, hipMemcpyHostToDevice)) ||
+                      !hip_ok(hipStreamSynchronize(nullptr))))  // side streams are not ordered after the copy
     st = DQ_EHIP;
   if (st != DQ_OK) {
     if (t->dev) (void)hipFree(t->dev);

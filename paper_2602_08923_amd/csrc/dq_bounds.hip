@@ -88,9 +88,9 @@ __global__ void __launch_bounds__(256) k_fetch(const uint32_t *src, uint32_t n, 
 
 // One for a call on stream s, which must not be under capture: a captured check would run again, with this call's number.
 Workspace *take(hipStream_t s, hipError_t *err) {
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if ((*err = hipStreamIsCapturing(s, &capture)) != hipSuccess) return nullptr;
-  if (capture != hipStreamCaptureStatusNone) {
+  bool captured;
+  if ((*err = is_captured(s, &captured)) != hipSuccess) return nullptr;
+  if (captured) {
     *err = hipErrorStreamCaptureUnsupported;
     return nullptr;
   }

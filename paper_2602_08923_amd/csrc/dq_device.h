@@ -143,6 +143,17 @@ hipError_t add_static_lds(K kernel, size_t *bytes) {
 // streaming probe (probe_kernels.hip): reads in_bytes, writes out_bytes (multiples of 16, out <= in)
 hipError_t stream_probe(const void *in, size_t in_bytes, void *out, size_t out_bytes, uint32_t n_cu, hipStream_t stream);
 
+// Whether work enqueued on s goes into a graph.  (The null stream is never captured; asked while another stream is, the runtime may
+// answer with an error.)
+inline hipError_t is_captured(hipStream_t s, bool *yes) {
+  *yes = false;
+  if (!s) return hipSuccess;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  const hipError_t e = hipStreamIsCapturing(s, &status);
+  *yes = status != hipStreamCaptureStatusNone;
+  return e;
+}
+
 // DQ_OK, or DQ_EHIP after recording the error's text for dq_last_hip_error (dq_api.cpp)
 dq_status hip_status(hipError_t e);
 

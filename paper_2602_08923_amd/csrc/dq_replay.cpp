@@ -449,7 +449,7 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
 // into the runtime, for launches on other streams and under capture wait for it.  Without a stream, and for tables
 // beyond kPinned, the host waits until nothing can be reading the scratch and copies.  (The one block is bound by its trips over
 // PCIe, 8 us by the profiler.  A copy that the host waits for, besides needing an idle scratch: the all-reduce of 8 workers' 8,192
-// super-groups took 104 us instead of 92.)
+// super-groups took 104 us instead of 88.)
 constexpr size_t kPinned = 256u << 10;
 constexpr size_t kStagings = 8;
 struct Staging {
@@ -495,6 +495,7 @@ class Upload {
       if (enqueue(staging, number, &e)) return dq::hip_status(e);
     }
     send();
+    if (status_ == DQ_OK) status_ = dq::hip_status(hipStreamSynchronize(nullptr));  // pageable memory: the copy may return before it is done
     return status_;
   }
 
@@ -578,12 +579,12 @@ static dq_status await_tables(dq_replay *r, hipStream_t s) {
   if (!staging) return DQ_OK;
   auto arrived = [&] { return (int32_t)(__atomic_load_n(staging->flag, __ATOMIC_ACQUIRE) - r->upload) >= 0; };  // later uploads count on
   if (!arrived()) {
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const hipError_t e = hipStreamIsCapturing(s, &capture);
+    bool captured;
+    const hipError_t e = dq::is_captured(s, &captured);
     if (e != hipSuccess) return dq::hip_status(e);
-    if (s == r->stream && capture == hipStreamCaptureStatusNone) return DQ_OK;
+    if (s == r->stream && !captured) return DQ_OK;
     for (uint32_t spin = 0; spin < 200000 && !arrived(); ++spin) __builtin_ia32_pause();
-    if (!arrived() && capture == hipStreamCaptureStatusNone) {  // long work ahead of it
+    if (!arrived() && !captured) {  // long work ahead of it
       const hipError_t d = hipDeviceSynchronize();
       if (d != hipSuccess) return dq::hip_status(d);
     }
@@ -684,10 +685,10 @@ dq_status dq_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *
 dq_status dqx_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *const *worker_grads, void *scratch, size_t scratch_bytes,
                             float *out, dq_replay **plan, void *hip_stream) {
   const hipStream_t s = (hipStream_t)hip_stream;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  const hipError_t e = hipStreamIsCapturing(s, &capture);
+  bool captured;
+  const hipError_t e = dq::is_captured(s, &captured);
   if (e != hipSuccess) return dq::hip_status(e);
-  if (capture != hipStreamCaptureStatusNone) return dq::hip_status(hipErrorStreamCaptureUnsupported);  // the tables are sent once, now
+  if (captured) return dq::hip_status(hipErrorStreamCaptureUnsupported);  // the tables are sent once, now
   return create(ctx, desc, worker_grads, scratch, scratch_bytes, out, plan, &s);
 }
 
@@ -742,17 +743,17 @@ static dq_status fill_buffers(dq_replay *r, uint32_t first, hipStream_t s) {
     const dq_status st = run_step(r, i < ns ? i : i - ns, s);
     if (st != DQ_OK) return st;
   }
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  const hipError_t e = hipStreamIsCapturing(s, &capture);
-  if (e == hipSuccess && capture == hipStreamCaptureStatusNone) r->complete = true;
+  bool captured;
+  const hipError_t e = dq::is_captured(s, &captured);
+  if (e == hipSuccess && !captured) r->complete = true;
   return dq::hip_status(e);
 }
 // After steps first .. end-1 have been enqueued.
 static dq_status note_steps(dq_replay *r, uint32_t first, uint32_t end, hipStream_t s) {
   if (r->complete) return DQ_OK;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  const hipError_t e = hipStreamIsCapturing(s, &capture);
-  if (e != hipSuccess || capture != hipStreamCaptureStatusNone) return dq::hip_status(e);  // captured: they have not run
+  bool captured;
+  const hipError_t e = dq::is_captured(s, &captured);
+  if (e != hipSuccess || captured) return dq::hip_status(e);  // captured: they have not run
   const uint32_t ns = (uint32_t)r->plan.steps.size();
   if (first + 2 <= ns && end + 1 >= ns) r->gathered = true;
   if (first <= r->filled && end > r->filled) r->filled = end;
@@ -765,10 +766,10 @@ static dq_status run_walk(dq_replay *r, hipStream_t s) {
   const Plan &p = r->plan;
   const bool complete = p.ring_chunks != 0 && !r->all_gather;
   if (r->complete != complete || r->filled || r->gathered) {
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const hipError_t e = hipStreamIsCapturing(s, &capture);
+    bool captured;
+    const hipError_t e = dq::is_captured(s, &captured);
     if (e != hipSuccess) return dq::hip_status(e);
-    if (capture == hipStreamCaptureStatusNone) {
+    if (!captured) {
       r->complete = complete;
       r->filled = 0;
       r->gathered = false;

@@ -384,3 +384,35 @@ def test_whole_replay_of_many_workers_equals_its_steps(dev, topology, n, widths,
     rp = B.Replay(B.Context(n, seed=n), TOPO[topology], B.DQ_DYNAMIQ, [grads[(3 * w + w // 8) % 8] for w in range(n)], J, widths, all_gather=True,
                   mu=torch.randn(J, device=dev) * 1e-4)
     whole_against_steps(rp, {"ring": n, "chain": 1, "butterfly": 0}[topology])
+
+
+def test_calls_on_the_default_stream_while_another_thread_captures(dev):
+    n_sg, ctx = 300, B.Context(4, seed=1)
+    ch = B.make_chunk(0, [0, n_sg, 0])
+    x = gradients(1, n_sg, torch.bfloat16, dev, 8)[0]
+    index = torch.arange(n_sg - 1, -1, -1, dtype=torch.int32, device=dev)
+    want, plain = ctx.dq_compress(x, ch, 1, sg_index=index), ctx.dq_compress(x, ch, 1)
+    out, errors = torch.zeros_like(want), []
+    torch.cuda.synchronize()
+
+    def work():
+        try:
+            for _ in range(5):
+                ctx.dq_compress(x, ch, 1, packed_out=out, sg_index=index)
+        except Exception as e:                              # noqa: BLE001 -- shown below
+            errors.append(e)
+
+    graph = torch.cuda.CUDAGraph()
+    got = torch.zeros_like(plain)
+    with torch.cuda.graph(graph, capture_error_mode="thread_local"):
+        ctx.dq_compress(x, ch, 1, packed_out=got)
+        t = threading.Thread(target=work)
+        t.start()
+        t.join()
+        ctx.dq_compress(x, ch, 1, packed_out=got)
+    assert not errors, errors
+    assert torch.equal(out, want)
+    for _ in range(3):
+        got.zero_()
+        graph.replay()
+        assert torch.equal(got, plain)
