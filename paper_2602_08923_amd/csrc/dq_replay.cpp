@@ -445,11 +445,11 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
 //
 // Scratch is recycled memory: the launch of an earlier replay, still running, may be reading its tables at the very place.  The binding
 // therefore names the stream that the scratch belongs to, and the tables go there as that stream's work: one block copies them
-// from pinned memory (55 KB for 8 workers' ring of 8,192 super-groups) and then says so in a flag that the host reads without a call
+// from pinned memory (25 KB for 8 workers' ring of 8,192 super-groups) and then says so in a flag that the host reads without a call
 // into the runtime, for launches on other streams and under capture wait for it.  Without a stream, and for tables
 // beyond kPinned, the host waits until nothing can be reading the scratch and copies.  (The one block is bound by its trips over
 // PCIe, 8 us by the profiler.  A copy that the host waits for, besides needing an idle scratch: the all-reduce of 8 workers' 8,192
-// super-groups took 104 us instead of 88.)
+// super-groups took 103 us instead of 88 to 91.)
 constexpr size_t kPinned = 256u << 10;
 constexpr size_t kStagings = 8;
 struct Staging {
