@@ -294,22 +294,24 @@ class Replay:
         ptrs = (C.c_void_p * n)(*[g.data_ptr() for g in self.grads])
         self.h = C.c_void_p()
         # the scratch may be memory that the current stream's earlier work still uses: its tables are sent in that order
+        self._made_on = _stream()
         _check(lib().dqx_replay_create(ctx.h, C.byref(desc), ptrs, _ptr(self.scratch), nbytes, _ptr(self.out),
-                                       C.byref(self.h), _stream()))
+                                       C.byref(self.h), self._made_on))
         self.n_steps = lib().dq_replay_n_steps(self.h)
 
     def run(self, timed=False):
         if timed:
             ms = (C.c_float * self.n_steps)()
             _check(lib().dq_replay_run(self.h, ms, _stream()))
-            return list(ms)
-        return _py.replay_run(self.h)
+            return list(ms)                                 # waited for
+        return _py.replay_run(self.h, self._made_on, self.scratch, self.out)
 
     def run_steps(self, first, count):
-        _py.replay_run_steps(self.h, first, count)
+        _py.replay_run_steps(self.h, first, count, self._made_on, self.scratch, self.out)
 
     def run_launch(self, step, launch):
         _check(lib().dq_replay_run_launch(self.h, step, launch, _stream()))
+        _py.replay_used(self._made_on, self.scratch, self.out)
 
     def step_info(self, step):
         kind, a, b = C.c_uint32(), C.c_uint64(), C.c_uint64()

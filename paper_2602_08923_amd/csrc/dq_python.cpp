@@ -279,17 +279,35 @@ PyObject *py_mx_decompress(PyObject *const *a, Py_ssize_t nargs) {  // fmt, pack
   return give(a[4], out);
 }
 
-PyObject *py_replay_run(PyObject *const *a, Py_ssize_t nargs) {  // replay
-  DQ_ARGS(1)
-  void *h = handle(a[0]), *s = stream();
-  CALL(dq_replay_run(as<dq_replay>(h), nullptr, s));
+// A plan's own memory used on another stream than it was made on: it must not be given out again before that stream's work is done.
+void used_here(PyObject *made_on, PyObject *scratch, PyObject *out) {
+  const c10::hip::HIPStream now = c10::hip::getCurrentHIPStream();
+  if ((unsigned long long)(uintptr_t)now.stream() == number(made_on)) return;
+  // (PyTorch's tensors call the device CUDA)
+  const c10::Stream as_cuda(c10::Stream::UNSAFE, c10::Device(c10::DeviceType::CUDA, now.device_index()), now.id());
+  for (PyObject *o : {scratch, out}) {
+    const at::Tensor t = tensor(o);
+    unlocked([&] { t.record_stream(as_cuda); });
+  }
+}
+PyObject *py_replay_used(PyObject *const *a, Py_ssize_t nargs) {  // stream it was made on, scratch, out
+  DQ_ARGS(3)
+  used_here(a[0], a[1], a[2]);
   Py_RETURN_NONE;
 }
-PyObject *py_replay_run_steps(PyObject *const *a, Py_ssize_t nargs) {  // replay, first, count
-  DQ_ARGS(3)
+PyObject *py_replay_run(PyObject *const *a, Py_ssize_t nargs) {  // replay, stream it was made on, scratch, out
+  DQ_ARGS(4)
+  void *h = handle(a[0]), *s = stream();
+  CALL(dq_replay_run(as<dq_replay>(h), nullptr, s));
+  used_here(a[1], a[2], a[3]);
+  Py_RETURN_NONE;
+}
+PyObject *py_replay_run_steps(PyObject *const *a, Py_ssize_t nargs) {  // replay, first, count, stream it was made on, scratch, out
+  DQ_ARGS(6)
   void *h = handle(a[0]), *s = stream();
   const uint32_t first = (uint32_t)number(a[1]), count = (uint32_t)number(a[2]);
   CALL(dq_replay_run_steps(as<dq_replay>(h), first, count, s));
+  used_here(a[3], a[4], a[5]);
   Py_RETURN_NONE;
 }
 
@@ -472,7 +490,7 @@ PyObject *guarded(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
 }
 #define M(name) {#name, (PyCFunction)(void (*)(void))guarded<py_##name>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {M(init), M(compress), M(dar_hop), M(decompress), M(decompress_restore), M(mx_compress), M(mx_dar_hop),
-                         M(mx_decompress), M(replay_run), M(replay_run_steps), M(sg_stats), M(stats_combine), M(allocate),
+                         M(mx_decompress), M(replay_used), M(replay_run), M(replay_run_steps), M(sg_stats), M(stats_combine), M(allocate),
                          M(reorder), M(reorder_mean), M(restore), M(check_index), M(stats_all), M(fetch), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_dqpy", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

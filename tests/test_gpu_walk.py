@@ -287,6 +287,41 @@ def test_a_plan_made_on_one_stream_runs_on_another_and_in_a_graph(dev, codec, n,
         assert torch.equal(ref.out.view(torch.int32), want)
 
 
+@pytest.mark.parametrize("how", ["run", "run_steps", "run_launch"])
+def test_a_plan_dropped_while_another_stream_runs_it_keeps_its_scratch(dev, how):
+    n, J = 8, 512
+    inputs = [gradients(n, J, torch.bfloat16, dev, seed) for seed in (1, 2)]
+    ctx = B.Context(n, seed=3)
+    make = lambda k: B.Replay(ctx, B.DQ_RING, B.DQ_MXFP8_E4M3, inputs[k], J)   # noqa: E731
+    ref = make(0)
+    ref.run()
+    torch.cuda.synchronize()
+    want = ref.out.clone()
+    side, busy = torch.cuda.Stream(), torch.randn(4096, 4096, device=dev)
+    rp = make(0)
+    out, scratch = rp.out, rp.scratch.data_ptr()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(8):
+            busy = busy @ busy * 1e-3                       # the replay has to wait for this
+        if how == "run":
+            rp.run()
+        elif how == "run_steps":
+            rp.run_steps(0, rp.n_steps - 1)
+            rp.run_steps(rp.n_steps - 1, 1)
+        else:
+            for t in range(rp.n_steps):
+                rp.run_launch(t, 0)
+    rp.close()
+    del rp
+    others = [make(1) for _ in range(3)]
+    assert all(x.scratch.data_ptr() != scratch for x in others)
+    for x in others:
+        x.run()
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int32), want.view(torch.int32))
+
+
 def test_a_plan_is_not_made_under_capture(dev):
     grads = gradients(4, 16, torch.bfloat16, dev, 1)
     ctx = B.Context(4)
