@@ -398,12 +398,19 @@ def dq_dar_hop_pipelined(ctx, wire_in, local, chunk, rank, block_sg, compute_str
                          wire_out=None, mu=None, sg_index=None):
     """One hop of a chunk in blocks of block_sg super-groups: block i is encoded on compute_stream
     while block i-1 travels (a device copy) on copy_stream.  wire_in None: the first hop."""
-    dev = local.device
+    dev, made = local.device, []
     if stage is None:
         # zeros: the kernels never write the padding at the end of a packed block
         stage = torch.zeros(dq_pipelined_stage_bytes(chunk, block_sg), dtype=torch.uint8, device=dev)
+        made.append(stage)
     if wire_out is None:
         wire_out = torch.zeros(dq_pipelined_wire_bytes(chunk, block_sg), dtype=torch.uint8, device=dev)
+        made.append(wire_out)
+    if made:                                             # zeroed on the current stream, used on the other two
+        compute_stream.wait_stream(torch.cuda.current_stream())
+        for t in made:
+            t.record_stream(compute_stream)
+            t.record_stream(copy_stream)
     _check(lib().dq_dar_hop_pipelined(ctx.h, _ptr(wire_in), _local(local, chunk, mu, sg_index),
                                       C.byref(chunk), rank, block_sg,
                                       _ptr(stage), _ptr(wire_out), C.c_void_p(compute_stream.cuda_stream),

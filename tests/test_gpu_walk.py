@@ -451,3 +451,20 @@ def test_calls_on_the_default_stream_while_another_thread_captures(dev):
         got.zero_()
         graph.replay()
         assert torch.equal(got, plain)
+
+
+def test_a_pipelined_hop_orders_and_keeps_the_buffers_it_makes(dev):
+    n_sg = [300, 411, 200, 90]
+    ctx, ch = B.Context(8, seed=21), B.make_chunk(5000, n_sg)
+    x = gradients(1, sum(n_sg), torch.bfloat16, dev, 4)[0]
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    want = B.dq_dar_hop_pipelined(ctx, None, x, ch, 0, 96, s1, s2)
+    torch.cuda.synchronize()
+    want, busy = want.clone(), torch.randn(4096, 4096, device=dev)
+    torch.cuda.synchronize()
+    for _ in range(8):
+        busy = busy @ busy * 1e-3                           # the zeros of stage and wire wait behind this
+    got = B.dq_dar_hop_pipelined(ctx, None, x, ch, 0, 96, s1, s2)
+    spoil = [torch.full((B.dq_pipelined_stage_bytes(ch, 96),), 255, dtype=torch.uint8, device=dev) for _ in range(4)]
+    torch.cuda.synchronize()
+    assert torch.equal(got, want) and len(spoil) == 4
