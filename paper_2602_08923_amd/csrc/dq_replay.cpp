@@ -449,7 +449,7 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
 // into the runtime, for launches on other streams and under capture wait for it.  Without a stream, and for tables
 // beyond kPinned, the host waits until nothing can be reading the scratch and copies.  (The one block is bound by its trips over
 // PCIe, 8 us by the profiler.  A copy that the host waits for, besides needing an idle scratch: the all-reduce of 8 workers' 8,192
-// super-groups took 103 us instead of 88 to 91.)
+// super-groups took 103 us instead of 88 to 94.)
 constexpr size_t kPinned = 256u << 10;
 constexpr size_t kStagings = 8;
 struct Staging {
