@@ -244,7 +244,7 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
               level[2 * k + 1] = u2f(w[k] & 0xFFFF0000u);
             }
             if (keep) {
-              uint8_t *dst = path.msg[i & 1u] + tile_base_here<16>(job, pos).code_off + (row * 16 + g) * 32 + q * (2 * E);
+              uint8_t *dst = message_of(path, i) + tile_base_here<16>(job, pos).code_off + (row * 16 + g) * 32 + q * (2 * E);
               if constexpr (E == 4) gst<u32x2>(dst, u32x2{w[0], w[1]});
               else gst<u32x4>(dst, u32x4{w[0], w[1], w[2], w[3]});
             }
@@ -299,7 +299,7 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
             }
             if (keep) {
               const TileBase<B> tb = tile_base_here<B>(job, pos);
-              uint8_t *out = path.msg[i & 1u];
+              uint8_t *out = message_of(path, i);
               const uint32_t lg = row * 16 + g;
               uint64_t word = 0;
 #pragma unroll

@@ -192,7 +192,7 @@ __device__ __forceinline__ void walk_tiles(const WalkPath &path, const Params &P
           lds_st4(stack + lane * 16, m);
           lds_st1(stack + 1024 + lane * 4, f2u(sc.sfg));
         } else {
-          if constexpr (kHow == kBoth) store_codes<B>(path.msg[i & 1u], TileBase<B>(job, pos), rowc * 16 + g, rowc, ow, sc.rg, sc.sfb);
+          if constexpr (kHow == kBoth) store_codes<B>(message_of(path, i), TileBase<B>(job, pos), rowc * 16 + g, rowc, ow, sc.rg, sc.sfb);
 #pragma unroll
           for (int k = 0; k < 16; ++k) level[k] = v[k];
         }
@@ -279,7 +279,7 @@ __device__ __forceinline__ void walk_tile16(const WalkPath &path, const Params &
           lds_st4(stack + 1024 + lane * 16, u32x4{m[4], m[5], m[6], m[7]});
         }
       } else if (i >= W.first_kept && i + 1 < W.n) {
-        uint8_t *dst = path.msg[i & 1u] + TileBase<16>(job, pos).code_off + lg * 32;
+        uint8_t *dst = message_of(path, i) + TileBase<16>(job, pos).code_off + lg * 32;
         gst<u32x4>(dst, u32x4{m[0], m[1], m[2], m[3]});
         gst<u32x4>(dst + 16, u32x4{m[4], m[5], m[6], m[7]});
       }
