@@ -18,8 +18,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) const uint32_t lds_u32;
 typedef __attribute__((address_space(3))) const u32x2 lds_u2;
-typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
-typedef __attribute__((address_space(3))) const u32x3 lds_u3;
 typedef __attribute__((address_space(3))) const u32x4 lds_u4;
 typedef __attribute__((address_space(3))) u32x4 lds_w4;
 __device__ __forceinline__ uint32_t lds_ld1(uint32_t a) { return *reinterpret_cast<lds_u32 *>(a); }
@@ -355,17 +353,11 @@ __device__ __forceinline__ uint32_t or_and(uint32_t a, uint32_t b, uint32_t c) {
   return __builtin_amdgcn_bitop3_b32(a, b, c, 0xEA);
 }
 
-// A level's entry {T, D, T of the next level, index << (32 - B)}; without codes the index is not read.
-template <bool CODES>
-struct LevelEntry {
-  typedef u32x4 type;
-  static __device__ __forceinline__ type load(uint32_t a) { return lds_ld4(a); }
-};
-template <>
-struct LevelEntry<false> {
-  typedef u32x3 type;
-  static __device__ __forceinline__ type load(uint32_t a) { return *reinterpret_cast<lds_u3 *>(a); }
-};
+// A level's entry {T, D, T of the next level, index << (32 - B)}, read as 16 bytes also where the index is not wanted: a 12-byte LDS read
+// takes three times as long here (of the 14 entries of the 4-bit set 5.9 ns per instruction and CU against 1.8, of the 8-bit
+// set's 254 8.5 against 5.1).  25 MB through a ring of eight, half of it 2-bit, is the same; a chain of 64 workers at 5 bits
+// 436 -> 412 us, a ring of eight at 6 bits and 100 M entries 504 -> 486, of 8,192 super-groups 20.2 -> 19.5.
+__device__ __forceinline__ u32x4 load_level(uint32_t a) { return lds_ld4(a); }
 
 // The 16 entries of a group, quantized (v is consumed).
 // x' = |v| * inv needs no clamp: |v| <= m and inv is the correctly rounded 1/m, so the exact
@@ -405,9 +397,8 @@ __device__ __forceinline__ void quantize(float (&v)[16], float inv, const U4 &ga
     constexpr int kG = 2, kGroups = 16 / kG;
     const float magic = B == 4 ? V.magic4 : V.magic8;
     constexpr int per_word = 32 / B;
-    using Entry = typename LevelEntry<CODES>::type;
     u32x2 e[2][kG];
-    Entry t[2][kG];
+    u32x4 t[2][kG];
     // search: adding the magic number leaves the search table's LDS address plus round(x * 2^(m+3)) in the low
     // mantissa bits; without its three lowest bits that is the address of entry q = that integer / 8
     auto search = [&](int g) {
@@ -424,7 +415,7 @@ __device__ __forceinline__ void quantize(float (&v)[16], float inv, const U4 &ga
 #pragma unroll
       for (int j = 0; j < kG; ++j) {
         const u32x2 q = e[g & 1][j];
-        t[g & 1][j] = LevelEntry<CODES>::load(or_and(f2u(fabsf(v[15 - g * kG - j]) - u2f(q.x)) >> 27, 16u, q.y));
+        t[g & 1][j] = load_level(or_and(f2u(fabsf(v[15 - g * kG - j]) - u2f(q.x)) >> 27, 16u, q.y));
       }
     };
     auto round = [&](int g) {
@@ -432,7 +423,7 @@ __device__ __forceinline__ void quantize(float (&v)[16], float inv, const U4 &ga
       for (int j = 0; j < kG; ++j) {
         const int k = 15 - g * kG - j;
         const float xs = v[k], x = fabsf(xs);
-        const Entry q = t[g & 1][j];
+        const u32x4 q = t[g & 1][j];
         const float theta = __builtin_fmaf(uniform(k), u2f(q.y), u2f(q.x));  // below x': round up
         if constexpr (CODES) {
           // append sign and level index in one funnel shift, then the rounding: level index + 1 <= R, no carry into the sign
