@@ -1,4 +1,4 @@
-// Between libdq and its Python binding (not part of the C ABI): see dq_bounds.hip.
+// Between libdq and its Python binding and tests (not part of the C ABI): see dq_bounds.hip.
 #pragma once
 #include <stdint.h>
 
@@ -30,6 +30,8 @@ dq_status dqx_fetch(const uint32_t *src, uint32_t n, uint32_t *dst_host, void *h
 // uploaded as work of that stream, nothing is waited for.  Not while the stream is captured.
 dq_status dqx_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *const *worker_grads, void *scratch, size_t scratch_bytes,
                             float *out, dq_replay **plan, void *hip_stream);
+// Adds to *wrong (device) how many results of the codec's reciprocal differ from the division's.
+dq_status dqx_reciprocals(uint32_t *wrong, void *hip_stream);
 // dq_sg_stats of n_workers (at most 256) tensors and dq_stats_combine in one launch.
 dq_status dqx_stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dtype, uint64_t n_sg, float *mu, float *F,
                         void *hip_stream);

@@ -256,7 +256,7 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
             m = u2f(mg);
             // Levels: a stored scale above zero implies m > 2^-118 (the super-group's is at least 2^-100, and the dither at least
             // 1/512), so the bound only keeps the quotient finite where the levels do not count.
-            const float inv = m >= 0x1p-120f ? 1.0f / m : 0.0f;
+            const float inv = TREE ? (m >= 0x1p-120f ? 1.0f / m : 0.0f) : reciprocal(fmaxf(m, 0x1p-120f));
             // The scales, as in scale_group.  A super-group that is encoded as zero has its groups' maxima taken as zero instead of
             // its results: as conditional results the compiler puts the chain behind a branch, after the levels' lookups.
             uint32_t b = sg_max<E>(mg) + 0xFFFFu;

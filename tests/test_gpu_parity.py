@@ -4,6 +4,8 @@ Bar: packed codes, u8 group scales, bf16 super-group scales and E8M0 bytes bit-e
 fp32 decoded sums within 1e-6 relative (they are expected to be bit-exact too, the slack is
 the tolerance the benchmark spec states for floating point).
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -256,6 +258,14 @@ def test_stream_probe_reads_and_writes_every_word(dev):
         B.dq_stream_probe(ctx, s, d)
         torch.cuda.synchronize()
         assert np.array_equal(host(d).view(np.uint32).reshape(n_out, 4), want), (n_in, n_out)
+
+
+def test_reciprocal_is_the_division_for_every_pattern(dev):
+    """1 / m by the hardware's reciprocal and one step on its remainder, and the division where that is denormal."""
+    wrong = torch.zeros(1, dtype=torch.int32, device=dev)
+    assert B.lib().dqx_reciprocals(ctypes.c_void_p(wrong.data_ptr()), None) == 0
+    torch.cuda.synchronize()
+    assert int(wrong) == 0
 
 
 @pytest.mark.parametrize("topology", ["ring", "butterfly"])

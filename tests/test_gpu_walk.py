@@ -95,6 +95,20 @@ def test_whole_replay_of_many_super_groups_equals_its_steps(dev, topology, n, wi
     test_whole_replay_equals_its_steps(dev, topology, n, widths, all_gather, True, dtype)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("topology,J", [("ring", 64), ("butterfly", 64), ("ring", 8192), ("butterfly", 8192)])   # one and four super-groups per tile
+def test_whole_replay_of_extreme_magnitudes_equals_its_steps(dev, topology, J, dtype):
+    """Groups whose maximum's reciprocal is denormal, groups too small for a scale beside ones that are not, super-groups encoded as zero."""
+    grads = gradients(8, J, dtype, dev, J)
+    for w, g in enumerate(grads):
+        x = g.view(J, 16, 16)
+        x[::3, ::2] *= 2.0 ** -124
+        x[1::6] *= 0.0 if w % 2 else 2.0 ** -118
+        x[2::6, w] = torch.sign(x[2::6, w]) * 1.5e38
+    ctx = B.Context(8, seed=5)
+    whole_against_steps(B.Replay(ctx, TOPO[topology], B.DQ_DYNAMIQ, grads, J, [[J // 4, J // 2, J // 4, 0]]), 8 if topology == "ring" else 0)
+
+
 @pytest.mark.parametrize("topology", ["ring", "butterfly"])
 @pytest.mark.parametrize("J", [8192, 66000])                # one tile per wave, and several waves' shares per chunk
 def test_whole_replay_on_original_tensors_over_the_whole_grid(dev, topology, J):
