@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdq.so")
 EXT = os.path.join(HERE, "_dqpy.so")
-SOURCES = ["dq_kernels.hip", "dq_walk.hip", "dq_thin.hip", "dq_bounds.hip", "mx_kernels.hip", "pp_kernels.hip", "probe_kernels.hip", "dq_api.cpp", "dq_replay.cpp"]
+SOURCES = ["dq_kernels.hip", "dq_few.hip", "dq_walk.hip", "dq_thin.hip", "dq_bounds.hip", "mx_kernels.hip", "pp_kernels.hip", "probe_kernels.hip", "dq_api.cpp", "dq_replay.cpp"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-ffp-contract=off", "-fhip-fp32-correctly-rounded-divide-sqrt",

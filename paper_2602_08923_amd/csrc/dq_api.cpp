@@ -466,7 +466,7 @@ dq_status dq_compress(dq_ctx *ctx, const dq_local *local, const dq_chunk *chunk,
   if (!aligned16(packed_out)) return DQ_EALIGN;
   dq::Job j = dq::make_job(nullptr, nullptr, nullptr, packed_out, chunk->first_sg, chunk->n_sg, rank);
   if ((st = take_local(local, &j)) != DQ_OK) return st;
-  return dq::hip_status(dq::launch_one(dq::kCompress, local->dtype, true, j, ctx->params, ctx->grid_blocks, (hipStream_t)hip_stream));
+  return dq::hip_status(dq::launch_one(dq::kCompress, local->dtype, true, j, ctx->params, ctx->n_cu, ctx->grid_blocks, (hipStream_t)hip_stream));
 }
 
 dq_status dq_dar_hop(dq_ctx *ctx, const void *packed_in, const dq_local *local, const dq_chunk *chunk, uint32_t rank,
@@ -478,7 +478,7 @@ dq_status dq_dar_hop(dq_ctx *ctx, const void *packed_in, const dq_local *local, 
   if (!aligned16(packed_in) || !aligned16(packed_out)) return DQ_EALIGN;
   dq::Job j = dq::make_job((const uint8_t *)packed_in, nullptr, nullptr, packed_out, chunk->first_sg, chunk->n_sg, rank);
   if ((st = take_local(local, &j)) != DQ_OK) return st;
-  return dq::hip_status(dq::launch_one(dq::kDar, local->dtype, true, j, ctx->params, ctx->grid_blocks, (hipStream_t)hip_stream));
+  return dq::hip_status(dq::launch_one(dq::kDar, local->dtype, true, j, ctx->params, ctx->n_cu, ctx->grid_blocks, (hipStream_t)hip_stream));
 }
 
 dq_status dq_decompress(dq_ctx *ctx, const void *packed_in, const dq_local *local_or_null, const dq_chunk *chunk,
@@ -493,7 +493,7 @@ dq_status dq_decompress(dq_ctx *ctx, const void *packed_in, const dq_local *loca
   // a gathered local cannot be accumulated in place: other super-groups' inputs would be overwritten
   if (local_or_null && local_or_null->sg_index && local_or_null->data == (const void *)out) return DQ_EINVAL;
   return dq::hip_status(dq::launch_one(dq::kDecompress, local_or_null ? local_or_null->dtype : DQ_F32, local_or_null != nullptr,
-                                       j, ctx->params, ctx->grid_blocks, (hipStream_t)hip_stream));
+                                       j, ctx->params, ctx->n_cu, ctx->grid_blocks, (hipStream_t)hip_stream));
 }
 
 dq_status dq_decompress_restore(dq_ctx *ctx, const void *packed_in, const dq_local *local_or_null, const dq_chunk *chunk,
@@ -509,7 +509,7 @@ dq_status dq_decompress_restore(dq_ctx *ctx, const void *packed_in, const dq_loc
   j.dest = origin;
   j.back = mu_back_or_null;
   return dq::hip_status(dq::launch_one(dq::kDecompress, local_or_null ? local_or_null->dtype : DQ_F32, local_or_null != nullptr,
-                                       j, ctx->params, ctx->grid_blocks, (hipStream_t)hip_stream));
+                                       j, ctx->params, ctx->n_cu, ctx->grid_blocks, (hipStream_t)hip_stream));
 }
 
 }  // extern "C"
@@ -636,7 +636,7 @@ static dq_status pipelined_hop(dq_ctx *ctx, const void *wire_in, const dq_local 
                              whole.src ? whole.local : static_cast<const uint8_t *>(whole.local) + sg_first * 256 * es,
                              whole.mu ? whole.mu + sg_first : nullptr, stg, blk.first_sg, blk.n_sg, rank);
     j.src = whole.src ? whole.src + sg_first : nullptr;
-    if (!hip_ok(dq::launch_one(wire_in ? dq::kDar : dq::kCompress, dtype, true, j, ctx->params, ctx->grid_blocks, lane[slot])))
+    if (!hip_ok(dq::launch_one(wire_in ? dq::kDar : dq::kCompress, dtype, true, j, ctx->params, ctx->n_cu, ctx->grid_blocks, lane[slot])))
       return DQ_EHIP;
     // the transfer: a device copy standing in for the wire; it writes the block's padding as zero, which
     // the codec kernels leave untouched in the stage

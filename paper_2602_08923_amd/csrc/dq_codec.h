@@ -96,6 +96,27 @@ __device__ __forceinline__ float row_max16(float m) {
   return u2f(x);
 }
 
+// With E = 4 or 8 entries per lane: maximum of magnitudes over the lanes of a group, then over those of a super-group.
+template <int E>
+__device__ __forceinline__ uint32_t group_max(uint32_t x) {
+  x = max(x, dpp_u<0xB1>(x));                        // quad_perm 1,0,3,2
+  if constexpr (E == 4) x = max(x, dpp_u<0x4E>(x));  // quad_perm 2,3,0,1
+  return x;
+}
+template <int E>
+__device__ __forceinline__ uint32_t sg_max(uint32_t x) {  // x: the group's maximum
+  if constexpr (E == 8) x = max(x, dpp_u<0x122>(x));  // row_ror:2
+  x = max(x, dpp_u<0x124>(x));                        // row_ror:4
+  x = max(x, dpp_u<0x128>(x));                        // row_ror:8
+  const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);  // rows 0 and 1, 2 and 3
+  x = max(a[0], a[1]);
+  if constexpr (E == 4) {
+    const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);  // the wave's halves
+    x = max(b[0], b[1]);
+  }
+  return x;
+}
+
 template <int B>
 struct Width;
 template <>
@@ -336,14 +357,17 @@ struct Draws {
 // slot0: this worker's slot of the super-group's permutation (group g uses slot0 + g mod n); sc_word: the word of
 // the worker's scale stream that holds group g's byte.  g mod n is a nibble of P.g_mod (g itself above 16 workers),
 // so slot0 + it is below 2n and one subtraction and minimum reduce it for any n.
-__device__ __forceinline__ Draws draw_group(const Params &P, uint64_t gi, uint32_t rank, uint32_t slot0, uint32_t sc_word,
-                                            uint32_t g) {
-  Draws d;
-  d.gam = philox4x32_10((uint32_t)gi, (uint32_t)(gi >> 32), P.round, rank & 0xFFFFu, P.key0, P.key1);
+__device__ __forceinline__ void draw_offsets(const Params &P, uint32_t slot0, uint32_t sc_word, uint32_t g, Draws &d) {
   const uint32_t s = slot0 + ((uint32_t)(P.g_mod >> (4 * g)) & 15u);
   const uint32_t slot = min(s, s - P.n_slots);
   d.o_pi = __builtin_fmaf((float)slot, P.inv_n, P.inv_n512);  // (slot + 1/512) * inv_n: the same real number, rounded once
   d.us = __builtin_fmaf((float)((sc_word >> (8 * (g & 3u))) & 0xFFu), 1.0f / 256.0f, 1.0f / 512.0f);  // exact
+}
+__device__ __forceinline__ Draws draw_group(const Params &P, uint64_t gi, uint32_t rank, uint32_t slot0, uint32_t sc_word,
+                                            uint32_t g) {
+  Draws d;
+  d.gam = philox4x32_10((uint32_t)gi, (uint32_t)(gi >> 32), P.round, rank & 0xFFFFu, P.key0, P.key1);
+  draw_offsets(P, slot0, sc_word, g, d);
   return d;
 }
 
@@ -352,12 +376,9 @@ struct Scales {
   float inv;         // 1 / group maximum, 0 for a group whose scale rounded to zero (it keeps only its signs)
   float sfg;         // what the stored scales decode to: rg * (sf / 255)
 };
-__device__ __forceinline__ Scales scale_group(const float (&v)[16], float us, uint32_t rec0) {
+// m, M: maxima of the group and of its super-group
+__device__ __forceinline__ Scales scales_of(float m, float M, float us, uint32_t rec0) {
   Scales s;
-  float m = 0.0f;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) m = fmaxf(m, fabsf(v[k]));
-  const float M = row_max16(m);
   uint32_t b = f2u(M) + 0xFFFFu;         // upper half: smallest bf16 >= M
   b = b < 0x0D800000u ? 0u : b;          // below 2^-100: the super-group is encoded as zero
   s.sfb = b >> 16;
@@ -369,6 +390,12 @@ __device__ __forceinline__ Scales scale_group(const float (&v)[16], float us, ui
   s.inv = s.rg ? 1.0f / m : 0.0f;
   s.sfg = s.sfb ? (float)s.rg * u2f(q.x + e) : 0.0f;
   return s;
+}
+__device__ __forceinline__ Scales scale_group(const float (&v)[16], float us, uint32_t rec0) {
+  float m = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) m = fmaxf(m, fabsf(v[k]));
+  return scales_of(m, row_max16(m), us, rec0);
 }
 
 // Launch constants that vector instructions use once per entry, held in vector registers.  On this chip an

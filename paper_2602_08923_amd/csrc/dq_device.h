@@ -115,8 +115,11 @@ hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *pa
                        const Params &P, hipStream_t stream);
 
 // kernel launchers (dq_kernels.hip); grid_blocks = thread blocks the GPU keeps resident at once
-hipError_t launch_one(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &p, uint32_t grid_blocks,
+hipError_t launch_one(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &p, uint32_t n_cu, uint32_t grid_blocks,
                       hipStream_t stream);
+// the same for chunks of few super-groups (dq_few.hip), and whether a call is one
+hipError_t launch_few(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &p, hipStream_t stream);
+bool takes_few(Kind kind, const Job &job, const Params &p, uint32_t n_cu);
 // gather: some job of the batch has a `src` (jobs without one still take the contiguous path)
 hipError_t launch_batch(Kind kind, dq_dtype dtype, bool has_local, bool gather, const Job *jobs_dev, uint32_t n_jobs,
                         uint32_t max_tiles_per_job, const Params &p, uint32_t grid_blocks,
@@ -128,10 +131,11 @@ hipError_t launch_batch(Kind kind, dq_dtype dtype, bool has_local, bool gather, 
 hipError_t wire_copy(void *dst, const void *src, size_t bytes, size_t valid, hipStream_t stream);
 
 // Largest static LDS size over the kernels that address their tables from LDS byte 0 (must be 0): all kernels
-// of dq_kernels.hip that take a table, of dq_walk.hip and of dq_thin.hip
+// of dq_kernels.hip that take a table, of dq_few.hip, of dq_walk.hip and of dq_thin.hip
 hipError_t static_lds_bytes(size_t *bytes);
 hipError_t walk_static_lds(size_t *bytes);  // raise *bytes to what their kernels have
 hipError_t thin_static_lds(size_t *bytes);
+hipError_t few_static_lds(size_t *bytes);
 template <typename K>
 hipError_t add_static_lds(K kernel, size_t *bytes) {
   hipFuncAttributes attr;

@@ -508,12 +508,8 @@ size_t lds_bytes(const Params &p, Kind kind) {
 }
 
 template <Kind KIND, typename LT>
-hipError_t go_one(const Job &job, Params p, uint32_t grid_blocks, hipStream_t s) {
+hipError_t go_one(const Job &job, const Params &p, uint32_t grid_blocks, hipStream_t s) {
   const uint32_t tiles = job_tiles(job);
-  if (tiles == 0) return hipSuccess;
-  const Guard guard = armed_guard();
-  p.guard = guard.word;
-  p.guard_call = guard.call;
   const uint32_t blocks = blocks_per_job(tiles, 1, grid_blocks);
   hipLaunchKernelGGL((k_one<KIND, LT>), dim3(blocks), dim3(kBlockThreads), lds_bytes(p, KIND), s, job, p);
   return hipGetLastError();
@@ -543,8 +539,14 @@ hipError_t go_batch(const Job *jobs, uint32_t n_jobs, uint32_t max_tiles, Params
   (gather ? (f32 ? CALL<KINDV, Gathered<float>> ARGS : CALL<KINDV, Gathered<uint16_t>> ARGS) \
           : (f32 ? CALL<KINDV, float> ARGS : CALL<KINDV, uint16_t> ARGS))
 
-hipError_t launch_one(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &p, uint32_t grid_blocks,
+hipError_t launch_one(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &params, uint32_t n_cu, uint32_t grid_blocks,
                       hipStream_t s) {
+  if (job_tiles(job) == 0) return hipSuccess;
+  const Guard guard = armed_guard();
+  Params p = params;
+  p.guard = guard.word;
+  p.guard_call = guard.call;
+  if (takes_few(kind, job, p, n_cu)) return launch_few(kind, dtype, has_local, job, p, s);
   const bool f32 = dtype == DQ_F32, gather = job.src != nullptr;
 #define ARGS (job, p, grid_blocks, s)
   switch (kind) {
@@ -593,6 +595,7 @@ hipError_t static_lds_bytes(size_t *bytes) {
   DQ_ONE_KIND(kDar)
   DQ_ONE_KIND(kDecompress)
 #undef DQ_ONE_KIND
+  if (e == hipSuccess) e = few_static_lds(bytes);
   if (e == hipSuccess) e = walk_static_lds(bytes);
   return e != hipSuccess ? e : thin_static_lds(bytes);
 }

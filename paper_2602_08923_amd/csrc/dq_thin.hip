@@ -68,27 +68,6 @@ __device__ __forceinline__ uint64_t tensor_of(const Walk &W, uint32_t chunk, uin
   return table_entry(reinterpret_cast<const uint64_t *>(W.grads), TREE ? leaf_of<TREE>(W, chunk, i) : (W.chain ? 0u : chunk) + i);
 }
 
-// Maximum of magnitudes over the lanes of a group, then over those of a super-group.
-template <int E>
-__device__ __forceinline__ uint32_t group_max(uint32_t x) {
-  x = max(x, dpp_u<0xB1>(x));                        // quad_perm 1,0,3,2
-  if constexpr (E == 4) x = max(x, dpp_u<0x4E>(x));  // quad_perm 2,3,0,1
-  return x;
-}
-template <int E>
-__device__ __forceinline__ uint32_t sg_max(uint32_t x) {  // x: the group's maximum
-  if constexpr (E == 8) x = max(x, dpp_u<0x122>(x));  // row_ror:2
-  x = max(x, dpp_u<0x124>(x));                        // row_ror:4
-  x = max(x, dpp_u<0x128>(x));                        // row_ror:8
-  const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);  // rows 0 and 1, 2 and 3
-  x = max(a[0], a[1]);
-  if constexpr (E == 4) {
-    const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);  // the wave's halves
-    x = max(b[0], b[1]);
-  }
-  return x;
-}
-
 // What a wave holds of a tile before it walks it: where it is and the slices of its first hops.
 template <typename LT, int E>
 struct Start {

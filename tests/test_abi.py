@@ -81,3 +81,11 @@ def test_every_kernel_that_reads_tables_from_lds_byte_0_is_checked_for_static_ld
         assert kernels and kernels == set(re.findall(r"add_static_lds\((k_\w+)<", text)), name
         if name == "dq_kernels.hip":
             assert "walk_static_lds(bytes)" in text and "thin_static_lds(bytes)" in text
+
+
+def test_the_kernel_for_few_super_groups_is_checked_for_static_lds_too():
+    csrc = os.path.join(ROOT, "paper_2602_08923_amd", "csrc")
+    text = open(os.path.join(csrc, "dq_few.hip")).read()
+    kernels = set(re.findall(r"__global__[^;{]*?\b(k_\w+)\s*\(", text))
+    assert kernels and kernels == set(re.findall(r"add_static_lds\((k_\w+)<", text))
+    assert "few_static_lds(bytes)" in open(os.path.join(csrc, "dq_kernels.hip")).read()

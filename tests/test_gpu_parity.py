@@ -260,6 +260,44 @@ def test_stream_probe_reads_and_writes_every_word(dev):
         assert np.array_equal(host(d).view(np.uint32).reshape(n_out, 4), want), (n_in, n_out)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_sg", [[1, 0, 0, 0], [3, 2, 1, 1], [2, 3, 2, 1], [4, 2, 2, 1], [2000, 4000, 2100, 92], [2000, 4000, 2100, 93],
+                                  [2000, 5000, 3100, 140], [2000, 5000, 3100, 141]])
+def test_calls_at_the_edges_of_the_kernel_for_few_super_groups(dev, n_sg, dtype):
+    """One super-group per wave, eight per block, up to 32 (decompress: 40) per CU: at 256 CUs the last sizes lie on both sides of the
+    two lines.  Also hops and decompress-accumulates that write over what they read, means, gathered inputs and a scattered restore."""
+    n, S, first = 6, sum(n_sg), 2 ** 33 + 5
+    rng = np.random.default_rng(S)
+    a, b = make_local(rng, S * 256, dtype), make_local(rng, S * 256, dtype)
+    mu = (rng.standard_normal(S) * 1e-4).astype(np.float32)
+    orc, ctx = O.Oracle(n, seed=3), B.Context(n, seed=3)
+    och, gch = O.make_chunk(first, n_sg), B.make_chunk(first, n_sg)
+    w1 = orc.compress(och, 1, a, mu=mu)
+    w2 = orc.dar_hop(och, 2, w1, b, mu=mu)
+    w3 = orc.decompress(och, w2, a, mu=mu)
+    da, db, dmu = to_dev(a, dev), to_dev(b, dev), to_dev(mu, dev)
+    index = rng.permutation(S).astype(np.int32)
+    dix = torch.from_numpy(index).to(dev)
+    scattered = [to_dev(np.ascontiguousarray(x.reshape(S, 256)[np.argsort(index)]).reshape(-1), dev) for x in (a, b)]
+    g1 = ctx.dq_compress(da, gch, 1, mu=dmu)
+    assert np.array_equal(host(g1), w1)
+    assert np.array_equal(host(ctx.dq_compress(scattered[0], gch, 1, mu=dmu, sg_index=dix)), w1)
+    assert np.array_equal(host(ctx.dq_dar_hop(g1, db, gch, 2, mu=dmu)), w2)
+    assert np.array_equal(host(ctx.dq_dar_hop(g1, scattered[1], gch, 2, mu=dmu, sg_index=dix)), w2)
+    g2 = ctx.dq_dar_hop(g1, db, gch, 2, packed_out=g1, mu=dmu)
+    assert g2 is g1 and np.array_equal(host(g2), w2)
+    assert_bits = lambda got, want: np.testing.assert_array_equal(host(got).view(np.uint32), np.asarray(want, np.float32).view(np.uint32))
+    assert_bits(ctx.dq_decompress(g2, gch, local=da, mu=dmu), w3)
+    assert_bits(ctx.dq_decompress(g2, gch), orc.decompress(och, w2, None))
+    if dtype == "f32":
+        over = da.clone()
+        assert_bits(ctx.dq_decompress(g2, gch, local=over, out=over, mu=dmu), w3)
+    out = torch.empty(S * 256, dtype=torch.float32, device=dev)
+    ctx.dq_decompress_restore(g2, gch, dix, out, local=scattered[0], mu=dmu, mu_back=dmu, sg_index=dix)
+    back = (w3.reshape(S, 256) + (np.float32(n) * mu)[:, None]).astype(np.float32)
+    assert_bits(out.view(S, 256)[dix.long()], back)
+
+
 def test_reciprocal_is_the_division_for_every_pattern(dev):
     """1 / m by the hardware's reciprocal and one step on its remainder, and the division where that is denormal."""
     wrong = torch.zeros(1, dtype=torch.int32, device=dev)
