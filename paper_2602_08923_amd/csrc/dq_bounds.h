@@ -14,12 +14,21 @@ struct Guard {
   const uint32_t *word;  // device, or null: the call's kernels do nothing if it holds `call`
   uint32_t call;
 };
-Guard armed_guard();  // of the check this thread has armed
+// A check made by the blocks of the call's own kernel.
+struct OwnCheck {
+  Bound a, b;
+  uint32_t *host;       // where the verdict goes, with the call's number
+  uint32_t call;
+  uint32_t src_limit;   // of the indices that the kernel reads through before it knows the verdict
+};
+// Of the check that this thread has armed: to be made by the kernel itself (false: there is none, or not so) ...
+bool take_own_check(const uint32_t *src, OwnCheck *check);
+// ... or enqueued in front of it: armed_guard (dq_device.h)
 }  // namespace dq
 
 extern "C" {
-// Enqueue the check of one or two index arrays (not under capture) and arm its verdict for the calls this thread makes until
-// dqx_bounds_end, which waits for it (bit k: array k has an index out of bounds).  The calls in between do nothing
+// Arm a check of one or two index arrays (not under capture) for the one call that this thread makes until
+// dqx_bounds_end, which waits for the verdict (bit k: array k has an index out of bounds).  The call in between does nothing
 // if a bit is set.
 dq_status dqx_bounds_begin(const dq::Bound *bounds, int n_bounds, void *hip_stream);
 dq_status dqx_bounds_end(void *hip_stream, int *out_of_bounds);

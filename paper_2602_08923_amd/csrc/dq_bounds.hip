@@ -1,10 +1,11 @@
 // What the Python binding needs beside the C ABI: a bounds check of super-group indices, and a few words brought to the host.
 //
 // The bounds check: the binding, unlike the C ABI, knows how large the tensor is that
-// the indices point into.  The check is one small launch in front of the call on the same
-// stream; the call's kernel starts by reading the verdict and does nothing if an index is out of bounds,
-// so the host can enqueue it without waiting and only then look at the verdict, which arrives in pinned host memory
-// while the call runs.  (Reductions on the stream, each waited for on the host before the call was enqueued, took 38 us
+// the indices point into.  The host enqueues check and call without waiting and only then looks at the verdict, which arrives in pinned
+// host memory while the call runs.  A call on few super-groups checks all its indices itself, in every block, beside the trips that
+// the block waits for anyway (dq_few.hip).  For others the check is one small launch in front of the call on the same stream; the call's
+// kernel starts by reading the verdict and does nothing if an index is out of bounds.
+// (Reductions on the stream, each waited for on the host before the call was enqueued, took 38 us
 // per index and left the GPU idle between calls.)
 #include <string.h>
 
@@ -38,7 +39,12 @@ constexpr size_t kIdle = 8;
 std::mutex g_mutex;
 std::vector<Workspace *> g_idle;
 
-thread_local Workspace *t_armed = nullptr;
+struct Armed {
+  Workspace *w = nullptr;
+  Bound a, b;
+  bool started = false;  // enqueued, or left to the call's kernel
+};
+thread_local Armed t_armed;
 
 // What bounds it is latency: eight indices per thread, all loaded before the first is looked at, and one atomic
 // per block, which also says whether it found something.  (Findings in a word of their
@@ -151,9 +157,34 @@ hipError_t await_call(Workspace *w, hipStream_t s, uint32_t *word) {
   return *word >> 2 == w->calls ? hipSuccess : hipErrorLaunchFailure;
 }
 
+// The armed check as a launch of its own.
+hipError_t enqueue_check(hipStream_t s) {
+  Workspace *w = t_armed.w;
+  const uint32_t most = t_armed.a.n > t_armed.b.n ? t_armed.a.n : t_armed.b.n;
+  uint32_t blocks = (most + 256 * kPerThread - 1) / (256 * kPerThread);
+  blocks = blocks > kMaxBlocks ? kMaxBlocks : blocks ? blocks : 1;
+  w->done += blocks;
+  t_armed.started = true;
+  hipLaunchKernelGGL(k_bounds, dim3(blocks), dim3(256), 0, s, t_armed.a, t_armed.b, w->tally, w->host, w->calls, w->done);
+  return hipGetLastError();
+}
+
 }  // namespace
 
-Guard armed_guard() { return t_armed ? Guard{&t_armed->tally->refused, t_armed->calls} : Guard{nullptr, 0}; }
+bool take_own_check(const uint32_t *src, OwnCheck *check) {
+  Armed &x = t_armed;
+  if (!x.w || x.started || x.a.limit == 0 || (x.b.n && x.b.limit == 0)) return false;
+  *check = OwnCheck{x.a, x.b, x.w->host, x.w->calls, src == x.a.index ? x.a.limit : src && src == x.b.index ? x.b.limit : 0xFFFFFFFFu};
+  x.started = true;
+  return true;
+}
+
+hipError_t armed_guard(hipStream_t s, Guard *guard) {
+  *guard = Guard{nullptr, 0};
+  if (!t_armed.w) return hipSuccess;
+  *guard = Guard{&t_armed.w->tally->refused, t_armed.w->calls};
+  return t_armed.started ? hipSuccess : enqueue_check(s);
+}
 
 }  // namespace dq
 
@@ -163,24 +194,18 @@ dq_status dqx_bounds_begin(const dq::Bound *bounds, int n_bounds, void *hip_stre
   hipError_t e = hipSuccess;
   dq::Workspace *w = dq::take((hipStream_t)hip_stream, &e);
   if (!w) return dq::hip_status(e);
-  const dq::Bound a = bounds[0], b = n_bounds > 1 ? bounds[1] : dq::Bound{nullptr, 0, 0};
-  const uint32_t most = a.n > b.n ? a.n : b.n;
-  uint32_t blocks = (most + 256 * dq::kPerThread - 1) / (256 * dq::kPerThread);
-  blocks = blocks > dq::kMaxBlocks ? dq::kMaxBlocks : blocks ? blocks : 1;
   ++w->calls;
-  w->done += blocks;
-  hipLaunchKernelGGL(dq::k_bounds, dim3(blocks), dim3(256), 0, (hipStream_t)hip_stream, a, b, w->tally, w->host, w->calls, w->done);
-  if ((e = hipGetLastError()) != hipSuccess) return dq::hip_status(e);
-  dq::t_armed = w;
+  dq::t_armed = dq::Armed{w, bounds[0], n_bounds > 1 ? bounds[1] : dq::Bound{nullptr, 0, 0}};
   return DQ_OK;
 }
 
 dq_status dqx_bounds_end(void *hip_stream, int *out_of_bounds) {
-  dq::Workspace *w = dq::t_armed;
-  dq::t_armed = nullptr;
+  dq::Workspace *w = dq::t_armed.w;
   if (!w) return DQ_EINVAL;
+  hipError_t e = dq::t_armed.started ? hipSuccess : dq::enqueue_check((hipStream_t)hip_stream);  // no call came to it
+  dq::t_armed = dq::Armed{};
   uint32_t word = 0;
-  hipError_t e = dq::await_call(w, (hipStream_t)hip_stream, &word);
+  if (e == hipSuccess) e = dq::await_call(w, (hipStream_t)hip_stream, &word);
   if (e != hipSuccess) return dq::hip_status(e);
   *out_of_bounds = (int)(word & 3u);
   // the refused call's kernel has read its refusal before another call can be refused

@@ -23,6 +23,9 @@ typedef __attribute__((address_space(3))) u32x4 lds_w4;
 __device__ __forceinline__ uint32_t lds_ld1(uint32_t a) { return *reinterpret_cast<lds_u32 *>(a); }
 __device__ __forceinline__ u32x2 lds_ld2(uint32_t a) { return *reinterpret_cast<lds_u2 *>(a); }
 __device__ __forceinline__ u32x4 lds_ld4(uint32_t a) { return *reinterpret_cast<lds_u4 *>(a); }
+__device__ __forceinline__ void lds_st1(uint32_t a, uint32_t v) {
+  *reinterpret_cast<__attribute__((address_space(3))) uint32_t *>(a) = v;
+}
 __device__ __forceinline__ void lds_st4(uint32_t a, u32x4 v) { *reinterpret_cast<lds_w4 *>(a) = v; }
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) f32x4 lds_f4;

@@ -118,12 +118,16 @@ hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *pa
 hipError_t launch_one(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &p, uint32_t n_cu, uint32_t grid_blocks,
                       hipStream_t stream);
 // the same for chunks of few super-groups (dq_few.hip), and whether a call is one
-hipError_t launch_few(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &p, hipStream_t stream);
+hipError_t launch_few(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &p, hipStream_t stream);  // makes an armed check itself
 bool takes_few(Kind kind, const Job &job, const Params &p, uint32_t n_cu);
 // gather: some job of the batch has a `src` (jobs without one still take the contiguous path)
 hipError_t launch_batch(Kind kind, dq_dtype dtype, bool has_local, bool gather, const Job *jobs_dev, uint32_t n_jobs,
                         uint32_t max_tiles_per_job, const Params &p, uint32_t grid_blocks,
                         hipStream_t stream);
+
+// The check that this thread has armed (dq_bounds.h), enqueued now if it has not been: what the call's kernel reads first
+struct Guard;
+hipError_t armed_guard(hipStream_t stream, Guard *guard);
 
 // 16 zero bytes at a 16-byte aligned device address, written by a kernel
 // dst[0..bytes) = src[0..bytes) in 16-byte words (bytes a multiple of 16), except that the bytes from `valid`

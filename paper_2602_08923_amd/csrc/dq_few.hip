@@ -54,13 +54,13 @@ __device__ __forceinline__ Place place_of(const Job &job, uint32_t sg) {
 }
 
 template <Kind KIND, typename LT>
-__device__ __forceinline__ Piece<LT> fetch_piece(const Job &job, const Place &p) {
+__device__ __forceinline__ Piece<LT> fetch_piece(const Job &job, const Place &p, uint32_t src_limit) {
   constexpr bool kHasLocal = !__is_same(LT, NoLocal);
   const uint32_t lane = threadIdx.x & 63u;
   Piece<LT> f;
   uint64_t from = p.sg;
   if constexpr (kHasLocal)
-    if (job.src) from = gld<uint32_t>(job.src + p.sg);
+    if (job.src) from = min(gld<uint32_t>(job.src + p.sg), src_limit - 1u);
   if constexpr (KIND != kCompress) {
     const uint8_t *code = job.in + p.code;
     f.code = f.code_hi = f.rg = f.sf = 0;
@@ -205,8 +205,38 @@ __device__ __forceinline__ void finish_piece(const Job &job, const Params &P, co
   }
 }
 
-template <Kind KIND, typename LT>
-__global__ __launch_bounds__(kFewWaves * 64) void k_few(Job job_, Params P_) {
+// A check of the call's indices in its own blocks: every block looks at all of them, so that all know the verdict; the largest index
+// decides.  That takes up to 40 KB per block out of the L2, beside what the block waits for anyway.  A gathered hop of 3,187 super-groups
+// takes 8.5 us, which is the host's time from one launch to the next with a look at the verdict between; 9.7 to 10.3 with the check as a launch
+// in front of the call.  (The first indices requested ahead of everything else: no difference.)
+__device__ __forceinline__ uint32_t largest_index(const Bound &x) {
+  typedef uint32_t Four __attribute__((ext_vector_type(4), aligned(4)));
+  constexpr uint32_t kRound = kFewWaves * 64;
+  const uint32_t fours = x.n / 4;
+  uint32_t most = 0;
+  for (uint32_t i = threadIdx.x; i < fours; i += 4 * kRound) {
+    Four v[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) v[k] = gld<Four>(x.index + 4 * min(i + k * kRound, fours - 1));
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) most = max(max(max(most, v[k].x), max(v[k].y, v[k].z)), v[k].w);
+  }
+  if (threadIdx.x < (x.n & 3u)) most = max(most, gld<uint32_t>(x.index + 4 * fours + threadIdx.x));
+  return most;
+}
+// Bit k: this wave has found an index of array k out of bounds.
+__device__ __forceinline__ uint32_t wave_verdict(const OwnCheck &c) {
+  const uint32_t a = largest_index(c.a);
+  uint32_t bits = __builtin_amdgcn_ballot_w64(a >= c.a.limit) ? 1u : 0u;
+  if (c.b.n) {
+    const uint32_t b = c.b.index == c.a.index && c.b.n == c.a.n ? a : largest_index(c.b);  // a restore of what was gathered: one array
+    bits |= __builtin_amdgcn_ballot_w64(b >= c.b.limit) ? 2u : 0u;
+  }
+  return bits;
+}
+
+template <Kind KIND, typename LT, bool CHECK>
+__global__ __launch_bounds__(kFewWaves * 64) void k_few(Job job_, Params P_, OwnCheck check) {
   extern __shared__ uint4 lds_raw[];
   uint32_t *lds = reinterpret_cast<uint32_t *>(lds_raw);
   // every argument in one go: read where it is used, each would be a trip of its own
@@ -214,15 +244,14 @@ __global__ __launch_bounds__(kFewWaves * 64) void k_few(Job job_, Params P_) {
   Params P = P_;
   asm volatile("" : "+s"(job.in), "+s"(job.local), "+s"(job.mu), "+s"(job.src), "+s"(job.out), "+s"(job.dest), "+s"(job.back),
                "+s"(job.first_sg), "+s"(job.n_sg[0]), "+s"(job.n_sg[1]), "+s"(job.n_sg[2]), "+s"(job.n_sg[3]), "+s"(job.rank));
-  asm volatile("" : "+s"(P.guard), "+s"(P.guard_call), "+s"(P.blob), "+s"(P.blob_dwords), "+s"(P.magic[1]), "+s"(P.magic[2]), "+s"(P.key0),
+  asm volatile("" : "+s"(P.blob), "+s"(P.blob_dwords), "+s"(P.magic[1]), "+s"(P.magic[2]), "+s"(P.key0),
                "+s"(P.key1), "+s"(P.round), "+s"(P.n_workers), "+s"(P.perm_bits), "+s"(P.n_slots), "+s"(P.slot_keep), "+s"(P.g_mod),
                "+s"(P.inv_n), "+s"(P.inv_n512), "+s"(P.s_n));
-  if (P.guard && gld<uint32_t>(P.guard) == P.guard_call) return;
   const uint32_t total = job.n_sg[0] + job.n_sg[1] + job.n_sg[2] + job.n_sg[3];
   const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t sg = blockIdx.x * kFewWaves + wave;
   const Place p = place_of(job, min(sg, total - 1));
-  const Piece<LT> f = fetch_piece<KIND, LT>(job, p);
+  const Piece<LT> f = fetch_piece<KIND, LT>(job, p, CHECK ? check.src_limit : 0xFFFFFFFFu);
   // all tables, whatever widths the block meets: to choose would take longer
   const uint32_t words = KIND == kDecompress ? kOffLut4 / 4 : P.blob_dwords / 4;
   constexpr uint32_t kRounds = KIND == kDecompress ? 2 : kFewTableBytes / (kFewWaves * 64 * 16);
@@ -234,7 +263,8 @@ __global__ __launch_bounds__(kFewWaves * 64) void k_few(Job job_, Params P_) {
     part[r] = gld16(&P.blob[at[r]]);
   }
   Draws d = {};
-  const uint32_t area = P.blob_dwords * 4;  // the super-groups' draws, 32 bytes each: slot of the permutation, scale stream
+  const uint32_t area = words * 16;  // the super-groups' draws, 32 bytes each: slot of the permutation, scale stream
+  const uint32_t verdicts = area + kFewWaves * 32;
   if constexpr (KIND != kDecompress) {
     if (wave == 0) {  // lanes 2i, 2i + 1: the shared draw of the block's i-th super-group, the worker's for its scales
       const uint64_t G = job.first_sg + min(blockIdx.x * kFewWaves + (lane >> 1), total - 1);
@@ -248,7 +278,19 @@ __global__ __launch_bounds__(kFewWaves * 64) void k_few(Job job_, Params P_) {
   }
 #pragma unroll
   for (uint32_t r = 0; r < kRounds; ++r) *reinterpret_cast<uint4 *>(&lds[at[r]]) = part[r];
+  if constexpr (CHECK) {
+    const uint32_t bits = wave_verdict(check);
+    if (lane == 0) lds_st1(verdicts + wave * 4, bits);
+  }
   __syncthreads();
+  if constexpr (CHECK) {
+    static_assert(kFewWaves == 8, "two reads");
+    const u32x4 a = lds_ld4(verdicts), b = lds_ld4(verdicts + 16);
+    const uint32_t bits = __builtin_amdgcn_readfirstlane(a.x | a.y | a.z | a.w | b.x | b.y | b.z | b.w);
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+      __hip_atomic_store(check.host, 4 * check.call + bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // nothing else to order
+    if (bits) return;
+  }
   if (sg >= total) return;  // not the last super-group once more: a hop may write where it reads
   if constexpr (KIND != kDecompress) {
     const uint32_t g = lane >> 2, mine = area + wave * 32;
@@ -262,8 +304,11 @@ __global__ __launch_bounds__(kFewWaves * 64) void k_few(Job job_, Params P_) {
 
 template <Kind KIND, typename LT>
 hipError_t go_few(const Job &job, const Params &p, uint32_t super_groups, hipStream_t s) {
-  const size_t lds = KIND == kDecompress ? (size_t)kOffLut4 * 4 : (size_t)p.blob_dwords * 4 + kFewWaves * 32;
-  hipLaunchKernelGGL((k_few<KIND, LT>), dim3((super_groups + kFewWaves - 1) / kFewWaves), dim3(kFewWaves * 64), lds, s, job, p);
+  const size_t lds = (KIND == kDecompress ? (size_t)kOffLut4 * 4 : (size_t)p.blob_dwords * 4) + kFewWaves * 36;
+  const dim3 grid((super_groups + kFewWaves - 1) / kFewWaves), block(kFewWaves * 64);
+  OwnCheck check = {};
+  if (take_own_check(job.src, &check)) hipLaunchKernelGGL((k_few<KIND, LT, true>), grid, block, lds, s, job, p, check);
+  else hipLaunchKernelGGL((k_few<KIND, LT, false>), grid, block, lds, s, job, p, check);
   return hipGetLastError();
 }
 
@@ -290,7 +335,10 @@ hipError_t launch_few(Kind kind, dq_dtype dtype, bool has_local, const Job &job,
 
 namespace {
 template <Kind KIND, typename LT>
-hipError_t static_lds_of(size_t *bytes) { return add_static_lds(k_few<KIND, LT>, bytes); }
+hipError_t static_lds_of(size_t *bytes) {
+  const hipError_t e = add_static_lds(k_few<KIND, LT, false>, bytes);
+  return e != hipSuccess ? e : add_static_lds(k_few<KIND, LT, true>, bytes);
+}
 }  // namespace
 
 hipError_t few_static_lds(size_t *bytes) {

@@ -542,11 +542,13 @@ hipError_t go_batch(const Job *jobs, uint32_t n_jobs, uint32_t max_tiles, Params
 hipError_t launch_one(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &params, uint32_t n_cu, uint32_t grid_blocks,
                       hipStream_t s) {
   if (job_tiles(job) == 0) return hipSuccess;
-  const Guard guard = armed_guard();
   Params p = params;
+  if (takes_few(kind, job, p, n_cu)) return launch_few(kind, dtype, has_local, job, p, s);
+  Guard guard;
+  const hipError_t armed = armed_guard(s, &guard);
+  if (armed != hipSuccess) return armed;
   p.guard = guard.word;
   p.guard_call = guard.call;
-  if (takes_few(kind, job, p, n_cu)) return launch_few(kind, dtype, has_local, job, p, s);
   const bool f32 = dtype == DQ_F32, gather = job.src != nullptr;
 #define ARGS (job, p, grid_blocks, s)
   switch (kind) {

@@ -5,10 +5,6 @@
 namespace dq {
 namespace {
 
-__device__ __forceinline__ void lds_st1(uint32_t a, uint32_t v) {
-  *reinterpret_cast<__attribute__((address_space(3))) uint32_t *>(a) = v;
-}
-
 // The lane's number, opaque to the compiler: what is derived from it is computed where it is used, once in many hops,
 // and not held in registers around the loops (a spilled register's reload waits for the tile's loads in flight).
 __device__ __forceinline__ uint32_t lane_here() {

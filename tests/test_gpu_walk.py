@@ -134,6 +134,41 @@ def test_whole_mx_replay_equals_its_steps(dev, fmt, dtype, topology, n, J, nb, a
     whole_against_steps(rp, {"ring": n, "chain": 1, "butterfly": 0}[topology])
 
 
+@pytest.mark.parametrize("at", [0, 3, 4, 4095, 8190, 8191, 8192, 10239, 10240])
+def test_a_call_of_few_super_groups_checks_every_index_itself(dev, at):
+    """Rounds of 8,192 indices per block, fours and the rest of the array; at 10,241 the check is a launch of its own again.  Two arrays: the
+    same one within two tensors of different length, and two."""
+    ctx = B.Context(4, seed=1)
+    for n_sg in {at + 1, at + 2, min(at + 5, 10241)}:
+        ch = B.make_chunk(0, [0, n_sg, 0])
+        x = gradients(1, n_sg, torch.bfloat16, dev, n_sg)[0]
+        message = ctx.dq_compress(x, ch, 1)
+        bad = torch.arange(n_sg, dtype=torch.int32, device=dev)
+        good = bad.clone()
+        bad[at] = n_sg
+        longer = torch.cat([x, x[:256]])
+        def restored(local, index, origin, out_sgs):
+            out = torch.full((out_sgs * 256,), 7.0, device=dev)
+            try:
+                ctx.dq_decompress_restore(message, ch, origin, out, local=local, sg_index=index)
+                return "written"
+            except B.DqError as e:
+                torch.cuda.synchronize()
+                assert bool((out == 7.0).all())
+                return str(e)[:8]
+        assert restored(x, good, good, n_sg) == "written"
+        assert restored(x, bad, bad, n_sg + 1) == "sg_index"[:8]
+        assert restored(longer, bad, bad, n_sg) == "out_base"[:8]
+        assert restored(longer, bad, good, n_sg) == "written"
+        assert restored(longer, good, bad, n_sg) == "out_base"[:8]
+        assert restored(x, bad[:n_sg].clone(), good, n_sg) == "sg_index"[:8]
+        hop = torch.full_like(message, 9)
+        with pytest.raises(B.DqError, match="sg_index"):
+            ctx.dq_dar_hop(message, x, ch, 2, packed_out=hop, sg_index=bad)
+        torch.cuda.synchronize()
+        assert bool((hop == 9).all())
+
+
 @pytest.mark.parametrize("n_sg", [1, 4, 2049, 70001])
 def test_indices_out_of_bounds_are_refused_and_nothing_is_written(dev, n_sg):
     ctx = B.Context(4, seed=1)
