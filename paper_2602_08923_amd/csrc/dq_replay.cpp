@@ -444,26 +444,35 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
 // A plan's tables on their way to its scratch, in the order of their offsets; what lies between two pieces is padding.
 //
 // Scratch is recycled memory: the launch of an earlier replay, still running, may be reading its tables at the very place.  The binding
-// therefore names the stream that the scratch belongs to, and the tables go there as that stream's work: one block copies them
-// from pinned memory (25 KB for 8 workers' ring of 8,192 super-groups) and then says so in a flag that the host reads without a call
-// into the runtime, for launches on other streams and under capture wait for it.  Without a stream, and for tables
-// beyond kPinned, the host waits until nothing can be reading the scratch and copies.  (The one block is bound by its trips over
-// PCIe, 8 us by the profiler.  A copy that the host waits for, besides needing an idle scratch: the all-reduce of 8 workers' 8,192
-// super-groups took 103 us instead of 88 to 94.)
+// therefore names the stream that the scratch belongs to, and the tables go there as that stream's work: a few blocks copy them
+// from pinned memory (25 KB for 8 workers' ring of 8,192 super-groups) and then say so in flags that the host reads without a call
+// into the runtime, for launches on other streams and under capture wait for them.  Without a stream, and for tables
+// beyond kPinned, the host waits until nothing can be reading the scratch and copies.  (What bounds the blocks are their trips over
+// PCIe, of which a CU has only so many under way: 25 KB take one block 8.0 us, sixteen 4.7.  A copy that the host waits for, besides needing
+// an idle scratch: the all-reduce of 8 workers' 8,192 super-groups took 103 us instead of 88 to 94.)
 constexpr size_t kPinned = 256u << 10;
 constexpr size_t kStagings = 8;
+constexpr uint32_t kUploadBlocks = 16, kUploadThreads = 128;
 struct Staging {
-  uint8_t *host = nullptr;          // pinned: kPinned bytes, then the flag
-  volatile uint32_t *flag = nullptr;  // number of the last upload that has arrived
+  uint8_t *host = nullptr;            // pinned: kPinned bytes, then the flags
+  volatile uint32_t *flag = nullptr;  // per block: number of the last upload of which its part has arrived
   uint32_t number = 0;
-  bool arrived() const { return __atomic_load_n(flag, __ATOMIC_ACQUIRE) == number; }
+  bool arrived(uint32_t upload) const {  // or a later one
+    bool all = true;
+    for (uint32_t b = 0; b < kUploadBlocks; ++b) all = all && (int32_t)(__atomic_load_n(flag + b, __ATOMIC_ACQUIRE) - upload) >= 0;
+    return all;
+  }
+  void set(uint32_t upload) {
+    for (uint32_t b = 0; b < kUploadBlocks; ++b) __atomic_store_n(flag + b, upload, __ATOMIC_RELEASE);
+  }
 };
 std::mutex g_staging_mutex;
 std::vector<Staging *> g_stagings;  // at most kStagings, kept until the process ends; one is taken again when its last upload has arrived
 
-__global__ void __launch_bounds__(1024) k_upload(const uint4 *src, uint4 *dst, uint32_t words, uint32_t *flag, uint32_t number) {
-  for (uint32_t i = threadIdx.x; i < words; i += 4096) {  // latency of the host's memory: 64 KB in flight
-    const uint32_t j = i + 1024, k = i + 2048, l = i + 3072;
+__global__ void __launch_bounds__(kUploadThreads) k_upload(const uint4 *src, uint4 *dst, uint32_t words, uint32_t *flag, uint32_t number) {
+  constexpr uint32_t kAll = kUploadBlocks * kUploadThreads;
+  for (uint32_t i = blockIdx.x * kUploadThreads + threadIdx.x; i < words; i += 4 * kAll) {  // latency of the host's memory: four loads at a time
+    const uint32_t j = i + kAll, k = i + 2 * kAll, l = i + 3 * kAll;
     const uint4 a = src[i], b = src[j < words ? j : i], c = src[k < words ? k : i], d = src[l < words ? l : i];
     dst[i] = a;
     if (j < words) dst[j] = b;
@@ -472,7 +481,7 @@ __global__ void __launch_bounds__(1024) k_upload(const uint4 *src, uint4 *dst, u
   }
   __threadfence_system();
   __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(flag, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // fenced above
+  if (threadIdx.x == 0) __hip_atomic_store(flag + blockIdx.x, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // fenced above
 }
 
 class Upload {
@@ -505,15 +514,15 @@ class Upload {
     std::lock_guard<std::mutex> lock(g_staging_mutex);
     Staging *s = nullptr;
     for (Staging *x : g_stagings)
-      if (x->arrived()) s = x;
+      if (x->arrived(x->number)) s = x;
     if (!s) {
       if (g_stagings.size() >= kStagings || !(s = new (std::nothrow) Staging)) return nullptr;
-      if (hipHostMalloc((void **)&s->host, kPinned + 64, hipHostMallocPortable) != hipSuccess) {
+      if (hipHostMalloc((void **)&s->host, kPinned + 4 * kUploadBlocks, hipHostMallocPortable) != hipSuccess) {
         delete s;
         return nullptr;
       }
       s->flag = reinterpret_cast<volatile uint32_t *>(s->host + kPinned);
-      *s->flag = 0;
+      s->set(0);
       g_stagings.push_back(s);
     }
     ++s->number;
@@ -526,13 +535,13 @@ class Upload {
     memcpy(s->host, buf_.data(), buf_.size());
     memset(s->host + buf_.size(), 0, bytes - buf_.size());
     const uint32_t mine = s->number;
-    hipLaunchKernelGGL(k_upload, dim3(1), dim3(1024), 0, *stream_, reinterpret_cast<const uint4 *>(s->host),
+    hipLaunchKernelGGL(k_upload, dim3(kUploadBlocks), dim3(kUploadThreads), 0, *stream_, reinterpret_cast<const uint4 *>(s->host),
                        reinterpret_cast<uint4 *>(scratch_ + first_), (uint32_t)(bytes / 16), const_cast<uint32_t *>(s->flag), mine);
     if ((*err = hipGetLastError()) == hipSuccess) {
       *number = mine;
       *staging = s;
     } else {
-      __atomic_store_n(s->flag, mine, __ATOMIC_RELEASE);  // nothing reads it
+      s->set(mine);  // nothing reads it
     }
     return true;
   }
@@ -577,7 +586,7 @@ struct dq_replay {
 static dq_status await_tables(dq_replay *r, hipStream_t s) {
   Staging *staging = r->staging.load(std::memory_order_acquire);
   if (!staging) return DQ_OK;
-  auto arrived = [&] { return (int32_t)(__atomic_load_n(staging->flag, __ATOMIC_ACQUIRE) - r->upload) >= 0; };  // later uploads count on
+  auto arrived = [&] { return staging->arrived(r->upload); };
   if (!arrived()) {
     bool captured;
     const hipError_t e = dq::is_captured(s, &captured);

@@ -374,7 +374,10 @@ hipError_t walk_static_lds(size_t *bytes) {
 // width was chosen by measurement (2-bit tiles need no search; 8-bit ones collide more in LDS): with equal costs the
 // chunks of one width finish early, 1150 us instead of 880 for eight 25 MB buckets through 16 workers' recursive
 // halving.  With less than two tiles per wave the count decides: a wave with one tile more takes twice as long whatever its width.
-static const uint32_t kCosts[2][4] = {{1, 1, 1, 1}, {6, 11, 12, 6}};
+static constexpr uint32_t kCosts[2][4] = {{1, 1, 1, 1}, {6, 11, 12, 6}};
+static_assert(kCosts[1][0] == kCosts[1][3] && kCosts[0][0] == 1, "split_walk");
+template <uint32_t C>
+struct Cost { static constexpr uint32_t value = C; };
 
 static uint64_t count_tiles(const WalkPath *paths, uint32_t n_paths, uint32_t sgs, uint32_t *widths) {
   uint64_t tiles = 0;
@@ -481,38 +484,43 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
 
 void split_walk(const WalkPath *paths, const Walk &W, std::vector<WalkShare> *shares) {
   const uint32_t *kCost = kCosts[W.by_cost];
-  const uint32_t sgs = W.tile_sgs;
+  const uint32_t sgs = W.tile_sgs, n = W.blocks * W.waves;
   uint64_t cost = 0;
   for (uint32_t p = 0; p < W.n_paths; ++p)
     for (int w = 0; w < 4; ++w) cost += (uint64_t)((paths[p].job.n_sg[w] + sgs - 1) / sgs) * kCost[w];
-  const uint32_t n = W.blocks * W.waves;
   shares->resize((size_t)n + 1);
-  // first tile of share v: the first whose cost before it reaches v * cost / n
-  uint32_t p = 0, t = 0, w = 0, left = 0;  // tile t of path p is in width w's run, which has `left` tiles more
-  uint64_t before = 0, want = 0, over = 0;  // want = floor(v * cost / n), over = the division's remainder
-  auto settle = [&] {  // on to the next run that has tiles
-    while (left == 0 && p < W.n_paths) {
-      if (w == 4) { ++p; w = 0; t = 0; continue; }
-      left = (paths[p].job.n_sg[w] + sgs - 1) / sgs;
-      if (left == 0) ++w;
+  // Share v begins with the first tile whose cost before it reaches want = floor(v * cost / n); over = that division's remainder.
+  WalkShare *share = shares->data(), *const end = share + n;
+  const uint64_t step = cost / n, rest = cost % n;
+  uint64_t want = 0, over = 0, before = 0;  // before: cost of all runs of one width before this one
+  uint32_t first = 0;                       // tile of this run
+  // The shares that begin in a run of `tiles` tiles.  The cost is a constant: dividing by it is a multiplication.  (With a division per share
+  // 2,049 shares took the host 15 us of a plan's 17.)
+  auto fill = [&](auto cost_of_tile, uint32_t p, uint32_t tiles) {
+    constexpr uint64_t c = decltype(cost_of_tile)::value;
+    for (const uint64_t last = before + (tiles - 1) * c; share != end && want <= last;) {
+      const uint64_t at = want > before ? want - before : 0;
+      *share++ = WalkShare{p, first + (uint32_t)((at + c - 1) / c)};
+      over += rest;
+      const uint64_t carry = over >= n ? 1 : 0;
+      over -= n & (0 - carry);
+      want += step + carry;
     }
+    before += tiles * c;
+    first += tiles;
   };
-  settle();
-  for (uint32_t v = 0; v < n; ++v) {
-    while (before < want && p < W.n_paths) {
-      const uint64_t take = (want - before + kCost[w] - 1) / kCost[w];
-      const uint32_t k = take < left ? (uint32_t)take : left;
-      before += (uint64_t)k * kCost[w];
-      t += k;
-      left -= k;
-      if (left == 0) { ++w; settle(); }
+  for (uint32_t p = 0; p < W.n_paths; ++p) {
+    first = 0;
+    for (int w = 0; w < 4; ++w) {
+      const uint32_t tiles = (paths[p].job.n_sg[w] + sgs - 1) / sgs;
+      if (tiles == 0) continue;
+      if (!W.by_cost) fill(Cost<1>(), p, tiles);
+      else if (w == 1) fill(Cost<kCosts[1][1]>(), p, tiles);
+      else if (w == 2) fill(Cost<kCosts[1][2]>(), p, tiles);
+      else fill(Cost<kCosts[1][0]>(), p, tiles);
     }
-    (*shares)[v] = WalkShare{p, p < W.n_paths ? t : 0u};
-    want += cost / n;
-    over += cost % n;
-    if (over >= n) { over -= n; ++want; }
   }
-  (*shares)[n] = WalkShare{W.n_paths, 0};
+  while (share != end + 1) *share++ = WalkShare{W.n_paths, 0};
 }
 
 hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths, const WalkShare *shares, const Walk &W,
