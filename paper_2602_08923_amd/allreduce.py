@@ -57,8 +57,7 @@ def simulated_allreduce(worker_grads, budget_bits, topology=B.DQ_RING, codec=B.D
     counts = None
     if uniform_width is None:
         budget = int(math.floor(prep.code_bits(budget_bits) * J))
-        widths, pos, counts = B.dq_allocate(F, J, budget, max_width=max_width)
-        by_width = B.widths_of_buckets(counts)
+        widths, pos, counts, by_width = B.allocate_ahead(F, J, budget, max_width=max_width)
     else:
         pos = torch.arange(J, dtype=torch.int32, device=dev).repeat(nb)
         row = [0, 0, 0, 0]
@@ -73,4 +72,4 @@ def simulated_allreduce(worker_grads, budget_bits, topology=B.DQ_RING, codec=B.D
                   mu=mu_main, origin=origin if fused_restore else None, inputs_in_original_order=gather)
     rp.run()
     out = rp.out if fused_restore else B.dq_restore(rp.out, pos, J, n, mu_main=mu_main)
-    return out, {"sg_by_width": by_width, "replay_steps": rp.n_steps}
+    return out, {"sg_by_width": by_width() if callable(by_width) else by_width, "replay_steps": rp.n_steps}

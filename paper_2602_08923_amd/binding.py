@@ -257,7 +257,8 @@ class Replay:
 
     def __init__(self, ctx, topology, codec, worker_grads, n_sg_bucket, n_sg_by_width=None, n_buckets=1, first_sg=0,
                  all_gather=False, mu=None, origin=None, inputs_in_original_order=False):
-        """mu: None, or the float32 means of all n_buckets * n_sg_bucket super-groups in reordered order.
+        """n_sg_by_width: per bucket the super-groups of 2, 4, 8 and 16 bits, or a function that returns them (allocate_ahead).
+        mu: None, or the float32 means of all n_buckets * n_sg_bucket super-groups in reordered order.
         origin: None, or int32 [n_buckets * n_sg_bucket] (from dq_reorder_mean): the result is then written
         in the original order with the means added back.  inputs_in_original_order (needs origin): the
         worker gradients are the original tensors; the kernels gather their super-groups through origin."""
@@ -274,10 +275,14 @@ class Replay:
         dev = self.grads[0].device
         n = len(self.grads)
         flat = (C.c_uint32 * (4 * n_buckets))()
-        if n_sg_by_width is not None:
+
+        def fill(rows):
             for b in range(n_buckets):
-                for k in range(len(n_sg_by_width[b])):      # 2, 4, 8 bits and optionally 16
-                    flat[4 * b + k] = int(n_sg_by_width[b][k])
+                for k in range(len(rows[b])):               # 2, 4, 8 bits and optionally 16
+                    flat[4 * b + k] = int(rows[b][k])
+
+        if n_sg_by_width is not None and not callable(n_sg_by_width):
+            fill(n_sg_by_width)
         self._widths = flat
         desc = ReplayDesc(topology, codec, _dtype(self.grads[0]), n_buckets, n_sg_bucket, flat, first_sg,
                           1 if all_gather else 0, _ptr(mu), _ptr(origin), 1 if inputs_in_original_order else 0, n)
@@ -286,15 +291,19 @@ class Replay:
         for g in self.grads:
             if g.numel() != entries or _dtype(g) != desc.dtype:
                 raise DqError("every worker gradient must hold n_buckets * n_sg_bucket * 256 entries of one dtype")
-        nbytes = lib().dq_replay_scratch_bytes(ctx.h, C.byref(desc))
-        if nbytes == 0:
-            raise DqError("invalid replay description")
-        self.scratch = torch.empty(nbytes, dtype=torch.uint8, device=dev)
-        self.out = torch.empty(entries, dtype=torch.float32, device=dev)
         ptrs = (C.c_void_p * n)(*[g.data_ptr() for g in self.grads])
         self.h = C.c_void_p()
         # the scratch may be memory that the current stream's earlier work still uses: its tables are sent in that order
         self._made_on = _stream()
+        if callable(n_sg_by_width):                         # waited for, with all done that does not need them
+            self.out = torch.empty(entries, dtype=torch.float32, device=dev)
+            fill(n_sg_by_width())
+        nbytes = lib().dq_replay_scratch_bytes(ctx.h, C.byref(desc))
+        if nbytes == 0:
+            raise DqError("invalid replay description")
+        self.scratch = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        if not callable(n_sg_by_width):
+            self.out = torch.empty(entries, dtype=torch.float32, device=dev)
         _check(lib().dqx_replay_create(ctx.h, C.byref(desc), ptrs, _ptr(self.scratch), nbytes, _ptr(self.out),
                                        C.byref(self.h), self._made_on))
         self.n_steps = lib().dq_replay_n_steps(self.h)
@@ -368,6 +377,20 @@ def dq_allocate(F, n_sg_per_bucket, max_code_bits, max_width=8):
     """F: float32 [n_buckets * n_sg_per_bucket] -> (widths uint8, pos int32 (holds uint32),
     counts int32 [n_buckets, 5] = #2-bit, #4-bit, #8-bit, #16-bit, threshold pattern)."""
     return _native().allocate(F, n_sg_per_bucket, int(max_code_bits), int(max_width))
+
+
+def allocate_ahead(F, n_sg_per_bucket, max_code_bits, max_width=8):
+    """dq_allocate, and a function that returns widths_of_buckets(counts).  The search sends the counts to the host as soon as it
+    has them: what is enqueued between this call and that one runs while the host waits and plans."""
+    widths, pos, counts, ticket = _native().allocate_begin(F, n_sg_per_bucket, int(max_code_bits), int(max_width))
+    known = []
+
+    def by_width():
+        if not known:
+            known.append(widths_of_buckets(counts) if ticket is None else _py.allocate_end(ticket))
+        return known[0]
+
+    return widths, pos, counts, by_width
 
 
 def dq_reorder(x, pos, n_sg_per_bucket, out=None):

@@ -35,6 +35,12 @@ dq_status dqx_bounds_end(void *hip_stream, int *out_of_bounds);
 // n <= kFetchWords words of device memory as the stream's work so far leaves them (waits for it; not under capture): a copy of a few words by
 // hipMemcpy costs 13 us on top of the wait.
 dq_status dqx_fetch(const uint32_t *src, uint32_t n, uint32_t *dst_host, void *hip_stream);
+// dq_allocate, with the class counts sent to the host as soon as the search has them, while the rest of the call and what is enqueued after
+// it run (not under capture); dqx_allocate_end waits for them: rows of four.  A null ticket: not so (buckets above 65,536 super-groups,
+// more than 500 of them); dqx_fetch of the counts then.
+dq_status dqx_allocate_begin(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width,
+                             uint8_t *widths, uint32_t *pos, uint32_t *counts, void *hip_stream, void **ticket);
+dq_status dqx_allocate_end(void *ticket, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32_t *rows, void *hip_stream);
 // dq_replay_create for a scratch that belongs to a stream (memory that its earlier work may still be using): the tables are
 // uploaded as work of that stream, nothing is waited for.  Not while the stream is captured.
 dq_status dqx_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *const *worker_grads, void *scratch, size_t scratch_bytes,

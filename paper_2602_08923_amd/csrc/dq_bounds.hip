@@ -186,9 +186,51 @@ hipError_t armed_guard(hipStream_t s, Guard *guard) {
   return t_armed.started ? hipSuccess : enqueue_check(s);
 }
 
+// Counts ahead of an allocation.  The host needs nothing of it but how many super-groups have each width; with them it plans the replay,
+// meanwhile the GPU writes positions, origins and means.  Fetched by a launch behind the allocation they came 10 us later, and
+// what followed was enqueued after the wait.  (With the plan's own part of it, split_walk and k_upload, the all-reduce of 8 workers' 8,192
+// super-groups takes 58.5 us; 76.6 without the counts ahead, 89 before.)
+// Their words lie behind the workspace's first two.
+constexpr uint32_t kAnnounced = (kFetchWords - 1) / 2;
+static uint64_t *announced(Workspace *w) { return reinterpret_cast<uint64_t *>(w->host + 2); }
+static uint32_t tag_of(const Workspace *w) { return w->calls % 8191 + 1; }
+hipError_t announce_begin(uint32_t n_buckets, hipStream_t s, Announce *announce, void **ticket) {
+  if (n_buckets > kAnnounced) return hipSuccess;
+  hipError_t e = hipSuccess;
+  Workspace *w = take(s, &e);
+  if (!w) return e;
+  ++w->calls;
+  for (uint32_t b = 0; b < n_buckets; ++b) __atomic_store_n(announced(w) + b, 0, __ATOMIC_RELAXED);
+  *announce = Announce{announced(w), tag_of(w)};
+  *ticket = w;
+  return hipSuccess;
+}
+void announce_drop(void *ticket) { give_back(static_cast<Workspace *>(ticket)); }
+
 }  // namespace dq
 
 extern "C" {
+
+dq_status dqx_allocate_end(void *ticket, uint32_t J, uint32_t n_buckets, uint32_t *rows, void *hip_stream) {
+  dq::Workspace *w = static_cast<dq::Workspace *>(ticket);
+  if (!w) return DQ_EINVAL;
+  for (uint32_t b = 0, spin = 0; b < n_buckets;) {
+    const uint64_t word = __atomic_load_n(dq::announced(w) + b, __ATOMIC_ACQUIRE);
+    if (word >> 51 == dq::tag_of(w)) {
+      uint32_t *row = rows + 4 * (size_t)b++;
+      for (int k = 0; k < 3; ++k) row[k] = (uint32_t)(word >> (17 * k)) & 0x1FFFFu;
+      row[3] = J - row[0] - row[1] - row[2];
+    } else if (++spin > 200000) {  // long work ahead on the stream, or an error there
+      if (spin != 200001) return dq::hip_status(hipErrorLaunchFailure);
+      const hipError_t e = hipStreamSynchronize((hipStream_t)hip_stream);
+      if (e != hipSuccess) return dq::hip_status(e);
+    } else {
+      __builtin_ia32_pause();
+    }
+  }
+  dq::give_back(w);
+  return DQ_OK;
+}
 
 dq_status dqx_bounds_begin(const dq::Bound *bounds, int n_bounds, void *hip_stream) {
   hipError_t e = hipSuccess;

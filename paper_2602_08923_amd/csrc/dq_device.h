@@ -125,6 +125,15 @@ hipError_t launch_batch(Kind kind, dq_dtype dtype, bool has_local, bool gather, 
                         uint32_t max_tiles_per_job, const Params &p, uint32_t grid_blocks,
                         hipStream_t stream);
 
+// Class counts that a search tells the host as soon as it has them (dq_bounds.hip): per bucket one word in pinned memory, counts of
+// 17 bits with a tag above them.  Null: not told.  No ticket for more buckets than a workspace holds.
+struct Announce {
+  uint64_t *host;
+  uint32_t tag;
+};
+hipError_t announce_begin(uint32_t n_buckets, hipStream_t stream, Announce *announce, void **ticket);
+void announce_drop(void *ticket);  // nothing has been enqueued
+
 // The check that this thread has armed (dq_bounds.h), enqueued now if it has not been: what the call's kernel reads first
 struct Guard;
 hipError_t armed_guard(hipStream_t stream, Guard *guard);

@@ -23,7 +23,7 @@ PyObject *g_error = nullptr;  // binding.DqError
   X(dq_packed_bytes) X(dq_compress) X(dq_dar_hop) X(dq_decompress) X(dq_decompress_restore) X(dq_mx_packed_bytes)       \
   X(dq_mx_compress) X(dq_mx_dar_hop) X(dq_mx_decompress) X(dq_replay_run) X(dq_replay_run_steps) X(dq_sg_stats) X(dq_stats_combine) \
   X(dq_allocate) X(dq_reorder) X(dq_reorder_mean) X(dq_restore) X(dq_status_str) X(dq_last_hip_error) X(dqx_bounds_begin) \
-  X(dqx_bounds_end) X(dqx_fetch) X(dqx_stats_all)
+  X(dqx_bounds_end) X(dqx_fetch) X(dqx_allocate_begin) X(dqx_allocate_end) X(dqx_stats_all)
 struct Lib {
 #define X(name) decltype(&::name) name = nullptr;
   DQ_SYMBOLS(X)
@@ -339,8 +339,34 @@ PyObject *py_stats_combine(PyObject *const *a, Py_ssize_t nargs) {  // mu_all, F
   CALL(dq_stats_combine(as<float>(ma), as<float>(fa), (uint32_t)n, J, as<float>(m), as<float>(f), s));
   return pair(wrap(mu), wrap(F));
 }
-PyObject *py_allocate(PyObject *const *a, Py_ssize_t nargs) {  // F, n_sg_per_bucket, max_code_bits, max_width
-  DQ_ARGS(4)
+// An allocation whose counts are still to come.
+struct Ticket {
+  void *workspace, *stream;
+  uint32_t J, nb;
+};
+constexpr const char *kTicket = "paper_2602_08923_amd.ticket";
+std::vector<uint32_t> counts_of(Ticket *t) {  // once
+  std::vector<uint32_t> rows(4 * (size_t)t->nb);
+  void *w = t->workspace;
+  t->workspace = nullptr;
+  CALL(dqx_allocate_end(w, t->J, t->nb, rows.data(), t->stream));
+  return rows;
+}
+void drop_ticket(PyObject *capsule) {
+  Ticket *t = static_cast<Ticket *>(PyCapsule_GetPointer(capsule, kTicket));
+  if (t->workspace) {  // nobody asked: the workspace is free when the counts have come
+    PyObject *type, *value, *trace;
+    PyErr_Fetch(&type, &value, &trace);
+    try {
+      counts_of(t);
+    } catch (const Raised &) {
+      PyErr_Clear();
+    }
+    PyErr_Restore(type, value, trace);
+  }
+  delete t;
+}
+PyObject *allocate(PyObject *const *a, bool ahead) {
   const at::Tensor &F = tensor(a[0]);
   const int64_t J = (int64_t)number(a[1]);
   if (J == 0) {
@@ -351,15 +377,42 @@ PyObject *py_allocate(PyObject *const *a, Py_ssize_t nargs) {  // F, n_sg_per_bu
   const int64_t nb = F.numel() / J;
   const at::Tensor widths = make(F.numel(), at::kByte, F), pos = make(F.numel(), at::kInt, F);
   const at::Tensor counts = unlocked([&] { return at::empty({nb, 5}, F.options().dtype(at::kInt)); });
-  void *f = ptr(F), *w = ptr(widths), *p = ptr(pos), *c = ptr(counts), *s = stream();
+  void *f = ptr(F), *w = ptr(widths), *p = ptr(pos), *c = ptr(counts), *s = stream(), *ticket = nullptr;
   const unsigned long long budget = number(a[2]);
   const uint32_t max_width = (uint32_t)number(a[3]);
-  CALL(dq_allocate(as<float>(f), (uint32_t)J, (uint32_t)nb, budget, max_width, as<uint8_t>(w), as<uint32_t>(p), as<uint32_t>(c), s));
-  PyObject *t = PyTuple_New(3);
+  if (ahead) CALL(dqx_allocate_begin(as<float>(f), (uint32_t)J, (uint32_t)nb, budget, max_width, as<uint8_t>(w), as<uint32_t>(p), as<uint32_t>(c), s, &ticket));
+  else CALL(dq_allocate(as<float>(f), (uint32_t)J, (uint32_t)nb, budget, max_width, as<uint8_t>(w), as<uint32_t>(p), as<uint32_t>(c), s));
+  PyObject *t = PyTuple_New(ahead ? 4 : 3);
   PyTuple_SET_ITEM(t, 0, wrap(widths));
   PyTuple_SET_ITEM(t, 1, wrap(pos));
   PyTuple_SET_ITEM(t, 2, wrap(counts));
+  if (ahead) {
+    PyObject *capsule = Py_None;
+    if (ticket) capsule = PyCapsule_New(new Ticket{ticket, s, (uint32_t)J, (uint32_t)nb}, kTicket, drop_ticket);
+    else Py_INCREF(capsule);
+    PyTuple_SET_ITEM(t, 3, capsule);
+  }
   return t;
+}
+PyObject *py_allocate(PyObject *const *a, Py_ssize_t nargs) {  // F, n_sg_per_bucket, max_code_bits, max_width
+  DQ_ARGS(4)
+  return allocate(a, false);
+}
+PyObject *py_allocate_begin(PyObject *const *a, Py_ssize_t nargs) {  // the same; also a ticket for the counts on the host, or None
+  DQ_ARGS(4)
+  return allocate(a, true);
+}
+PyObject *py_allocate_end(PyObject *const *a, Py_ssize_t nargs) {  // ticket -> rows of four counts
+  DQ_ARGS(1)
+  Ticket *t = static_cast<Ticket *>(PyCapsule_GetPointer(a[0], kTicket));
+  if (!t) throw Raised();
+  if (!t->workspace) fail("the counts have been taken");
+  const std::vector<uint32_t> rows = counts_of(t);
+  PyObject *list = PyList_New(t->nb);
+  if (!list) throw Raised();
+  for (uint32_t b = 0; b < t->nb; ++b)
+    PyList_SET_ITEM(list, b, Py_BuildValue("[IIII]", rows[4 * b], rows[4 * b + 1], rows[4 * b + 2], rows[4 * b + 3]));
+  return list;
 }
 PyObject *py_reorder(PyObject *const *a, Py_ssize_t nargs) {  // x, pos, n_sg_per_bucket, out
   DQ_ARGS(4)
@@ -490,7 +543,7 @@ PyObject *guarded(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
 }
 #define M(name) {#name, (PyCFunction)(void (*)(void))guarded<py_##name>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {M(init), M(compress), M(dar_hop), M(decompress), M(decompress_restore), M(mx_compress), M(mx_dar_hop),
-                         M(mx_decompress), M(replay_used), M(replay_run), M(replay_run_steps), M(sg_stats), M(stats_combine), M(allocate),
+                         M(mx_decompress), M(replay_used), M(replay_run), M(replay_run_steps), M(sg_stats), M(stats_combine), M(allocate), M(allocate_begin), M(allocate_end),
                          M(reorder), M(reorder_mean), M(restore), M(check_index), M(stats_all), M(fetch), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_dqpy", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

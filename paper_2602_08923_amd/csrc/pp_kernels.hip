@@ -286,8 +286,8 @@ __device__ __forceinline__ uint32_t shift_to(uint32_t x, uint32_t bins) {
 }
 
 template <bool ALLOW16>
-__global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits,
-                                                          uint32_t *pos_all, uint32_t *counts_all) {
+__global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits, uint32_t *pos_all,
+                                                          uint32_t *counts_all, dq::Announce announce) {
   __shared__ alignas(16) uint32_t room[kBins8 + 4 + kBins4 + 4 + (ALLOW16 ? kBins16 + 4 : 8188)];  // level 1: 2049 * kCopies
   __shared__ uint32_t wsum[3][kAllocWaves], wfit[kAllocWaves], row_n[kRegs][3];
   uint32_t *const h8 = room, *const h4 = h8 + kBins8 + 4, *const h16 = h4 + kBins4 + 4;
@@ -536,6 +536,9 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
 #pragma unroll
       for (int c = 0; c < 4; ++c) gst<uint32_t>(cnt + c, n_class[c]);
       gst<uint32_t>(cnt + 4, hi);
+      if (announce.host)  // one store, so that nothing needs to be ordered; the fourth class is the rest
+        __hip_atomic_store(announce.host + blockIdx.x, n_class[0] | (uint64_t)n_class[1] << 17 | (uint64_t)n_class[2] << 34 | (uint64_t)announce.tag << 51,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
 }
@@ -836,8 +839,8 @@ static void launch_positions(const float *F, uint32_t J, uint32_t n_buckets, boo
   }
 }
 
-dq_status dq_allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits,
-                      uint32_t max_width, uint8_t *widths, uint32_t *pos, uint32_t *counts, void *hip_stream) {
+static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits,
+                          uint32_t max_width, uint8_t *widths, uint32_t *pos, uint32_t *counts, dq::Announce announce, void *hip_stream) {
   if (n_sg_per_bucket == 0 || n_buckets == 0) return DQ_OK;
   if (!F || !widths || !pos || !counts || (max_width != 8 && max_width != 16)) return DQ_EINVAL;
   if (max_code_bits < 2ull * n_sg_per_bucket) return DQ_EINVAL;  // fewer than 2 code bits per coordinate
@@ -846,12 +849,33 @@ dq_status dq_allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_bucke
   const bool allow16 = max_width == 16;
   const uint32_t J = n_sg_per_bucket, rows = (J + kAllocThreads - 1) / kAllocThreads;
   if (rows <= (uint32_t)kRegs) {
-    if (allow16) hipLaunchKernelGGL(k_search<true>, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, pos, counts);
-    else hipLaunchKernelGGL(k_search<false>, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, pos, counts);
+    if (allow16) hipLaunchKernelGGL(k_search<true>, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, pos, counts, announce);
+    else hipLaunchKernelGGL(k_search<false>, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, pos, counts, announce);
     launch_positions(F, J, n_buckets, allow16, counts, widths, pos, s);
   } else
     hipLaunchKernelGGL(k_allocate_large, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, allow16, widths, pos, counts);
   return launched();
+}
+
+dq_status dq_allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits,
+                      uint32_t max_width, uint8_t *widths, uint32_t *pos, uint32_t *counts, void *hip_stream) {
+  return allocate(F, n_sg_per_bucket, n_buckets, max_code_bits, max_width, widths, pos, counts, dq::Announce{nullptr, 0}, hip_stream);
+}
+
+dq_status dqx_allocate_begin(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width,
+                             uint8_t *widths, uint32_t *pos, uint32_t *counts, void *hip_stream, void **ticket) {
+  *ticket = nullptr;
+  dq::Announce announce = {nullptr, 0};
+  if (n_buckets != 0 && n_sg_per_bucket != 0 && n_sg_per_bucket <= (uint32_t)(kRegs * kAllocThreads)) {
+    const hipError_t e = dq::announce_begin(n_buckets, (hipStream_t)hip_stream, &announce, ticket);
+    if (e != hipSuccess) return dq::hip_status(e);
+  }
+  const dq_status st = allocate(F, n_sg_per_bucket, n_buckets, max_code_bits, max_width, widths, pos, counts, announce, hip_stream);
+  if (st != DQ_OK && *ticket) {
+    dq::announce_drop(*ticket);
+    *ticket = nullptr;
+  }
+  return st;
 }
 
 dq_status dq_reorder(const void *x, dq_dtype dtype, const uint32_t *pos, uint32_t n_sg_per_bucket, uint32_t n_buckets,

@@ -193,6 +193,24 @@ def test_allocate_budget_edges(dev):
 
 
 # ---------------------------------------------------------------- reorder / restore
+@pytest.mark.parametrize("J,nb,max_width", [(1, 1, 8), (1000, 3, 16), (65536, 1, 8), (65536, 2, 16), (65537, 1, 8), (4, 511, 16), (4, 512, 8)])
+def test_counts_ahead_of_the_allocation_are_its_counts(dev, J, nb, max_width):
+    """The largest counts that fit 17 bits and one beyond, the most buckets that a workspace holds and one beyond; asked for once, twice,
+    late and never, on one workspace after the other."""
+    F = torch.from_numpy(np.concatenate([lognormal_F(7 * b + 1, J) for b in range(nb)])).to(dev)
+    for bits in (2, 3, 16) if max_width == 16 else (2, 3, 8):   # all of the narrowest, some of each, all of the widest
+        want = [[int(v) for v in row[:4]] for row in B.dq_allocate(F, J, bits * J, max_width=max_width)[2].cpu().tolist()]
+        widths, pos, counts, by_width = B.allocate_ahead(F, J, bits * J, max_width=max_width)
+        B.allocate_ahead(F, J, bits * J, max_width=max_width)
+        late = B.allocate_ahead(F, J, 2 * J, max_width=max_width)[3]
+        assert by_width() == want and by_width() == want
+        torch.cuda.synchronize()
+        assert late() == [[J, 0, 0, 0]] * nb
+        assert [[int(v) for v in row[:4]] for row in counts.cpu().tolist()] == want
+    with pytest.raises(B.DqError):
+        B.allocate_ahead(F, J, 2 * J - 1, max_width=max_width)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("J,nb", [(1, 1), (37, 3), (1030, 2)])
 def test_reorder_and_restore(dev, dtype, J, nb):
