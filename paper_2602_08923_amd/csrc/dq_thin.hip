@@ -9,9 +9,14 @@
 // ring of 256, 4,096 super-groups of 2 to 16 bits, 284 -> 209 -> 222 (profiles/replay_tile_sizes.txt).  grid_walk (dq_walk.hip) says which
 // schedules come here.
 //
+// What bounds it is how much of a hop's chain four waves per SIMD cover: two vector instructions can go per four cycles, from two waves,
+// and about half of that is reached (256 workers, 4,096 super-groups: 106 instructions per hop, 184 us; 101 would be their issue).  So all
+// instructions count, on the path or beside it, scalar ones and waits too: both super-group draws made by one generator call, the next four tensors
+// by one scalar load and the group scale left in fp32 took 188 us there to 184, four workers' fp32 ring of 4,096 with all-gather from 9.9 to 9.1.
+//
 // What differs from the wide tile:
 //   draws    : a lane draws the group's 16 bytes for ONE of the next 16 / E hops, and the group's lanes exchange them through
-//              LDS: per hop and group one generator call, as before.  Per-super-group draws cover 256 / E hops at a time.
+//              LDS: per hop and group one generator call, as before.  Per-super-group draws cover 128 / E hops at a time.
 //   maxima   : within a group by quad permutes, within a super-group by row rotates and row / half-wave swaps.
 //   rounding : levels are looked up with 1 / maximum while the stored scales are still being worked out.  A group whose
 //              scale rounds to zero then has levels that are not zero, but they are multiplied by zero.
@@ -23,7 +28,7 @@ namespace dq {
 namespace {
 
 constexpr uint32_t kAhead = 4;  // hops a slice is requested ahead of its use
-constexpr uint32_t kThinPark = 1280;   // per wave: 64 scale draws of 16 bytes, 64 permutation slots
+constexpr uint32_t kThinPark = 640;    // per wave: 32 scale draws of 16 bytes, 32 permutation slots
 constexpr uint32_t kThinDraws = 1536;  // per wave: 64 groups' (of some hop) 16 bytes, their rounding offset and scale dither
 constexpr uint32_t kThinWaves = 4;     // per block
 static_assert(kThinWaves * kThinDraws <= (kOffTab4 - kOffDec2) * 4, "the draws lie over the decode tables, which are not copied");
@@ -118,7 +123,7 @@ __device__ __forceinline__ TileBase<B> tile_base_here(const Job &job, const Tile
 template <int B, typename LT, bool TREE, int E>
 __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P, const Vec &V, const Walk &W, uint32_t park, uint32_t draws,
                                           uint32_t stack0, Start<LT, E> &x) {
-  constexpr uint32_t kLanes = 16 / E, kSgs = E / 4, kHops = 64 / kSgs;  // lanes per group, super-groups per tile, hops per park
+  constexpr uint32_t kLanes = 16 / E, kSgs = E / 4, kHops = 32 / kSgs;  // lanes per group, super-groups per tile, hops per park
   const Job &job = path.job;
   const TilePos pos = x.pos;
   const uint32_t lane = threadIdx.x & 63u, q = lane & (kLanes - 1u), g = (lane / kLanes) & 15u;
@@ -133,6 +138,12 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
   auto some_hops = [&](uint32_t i0, auto plain) {
     constexpr bool PLAIN = decltype(plain)::value;
     uint64_t tensor[kAhead];
+    if constexpr (PLAIN && !TREE) {  // a run of the table: one scalar load
+      struct Run { uint64_t at[kAhead]; };
+      const Run run = table_entry(reinterpret_cast<const Run *>(W.grads + (W.chain ? 0u : path.chunk) + i0 + kAhead), 0u);
+#pragma unroll
+      for (uint32_t j = 0; j < kAhead; ++j) tensor[j] = run.at[j];
+    } else
 #pragma unroll
     for (uint32_t j = 0; j < kAhead; ++j) tensor[j] = tensor_of<TREE>(W, path.chunk, PLAIN ? i0 + kAhead + j : min(i0 + kAhead + j, last));
 #pragma unroll
@@ -157,20 +168,21 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
       if (PLAIN || i <= last) {
         if constexpr (B != 16) {
           if (j % kLanes == 0) {
-            if (j == 0 && (i & (kHops - 1u)) == 0) {  // the super-groups' draws of the next kHops hops: lane = hop, super-group
-              const uint32_t r = min(lane & (kSgs - 1u), pos.n_seg - 1 - pos.tile_first);
+            if (j == 0 && (i & (kHops - 1u)) == 0) {  // the super-groups' draws of the next kHops hops: lane = stream, hop, super-group
+              const uint32_t l = lane & 31u, r = min(l & (kSgs - 1u), pos.n_seg - 1 - pos.tile_first);
               const uint64_t G = job.first_sg + pos.seg_first + pos.tile_first + r;
-              const uint32_t rank = leaf_of<TREE>(W, path.chunk, min(i + lane / kSgs, last));
-              const U4 shared = philox4x32_10((uint32_t)G, (uint32_t)(G >> 32), P.round, (2u << 16) | 0xFFFFu, P.key0, P.key1);
-              const U4 scale = philox4x32_10((uint32_t)G, (uint32_t)(G >> 32), P.round, (1u << 16) | (rank & 0xFFFFu), P.key0, P.key1);
+              const uint32_t rank = leaf_of<TREE>(W, path.chunk, min(i + l / kSgs, last));
+              const U4 w = philox4x32_10((uint32_t)G, (uint32_t)(G >> 32), P.round, lane < 32 ? (1u << 16) | (rank & 0xFFFFu) : (2u << 16) | 0xFFFFu,
+                                         P.key0, P.key1);
+              const uint32_t slot = perm_slot(w, P, rank);  // of the shared draw; nothing in the other half
               lds_turn();
-              lds_st4(park + lane * 16, u32x4{scale.x, scale.y, scale.z, scale.w});
-              lds_st1(park + 1024 + lane * 4, perm_slot(shared, P, rank));
+              if (lane < 32) lds_st4(park + l * 16, u32x4{w.x, w.y, w.z, w.w});
+              else lds_st1(park + 512 + l * 4, slot);
               lds_turn();
             }
             // the groups' draws of the next kLanes hops: lane q of a group draws for hop i + q
             const uint32_t slot = ((i + q) & (kHops - 1u)) * kSgs + row;
-            const Draws d = draw_group(P, gi, leaf_of<TREE>(W, path.chunk, min(i + q, last)), lds_ld1(park + 1024 + slot * 4),
+            const Draws d = draw_group(P, gi, leaf_of<TREE>(W, path.chunk, min(i + q, last)), lds_ld1(park + 512 + slot * 4),
                                        lds_ld1(park + slot * 16 + (g >> 2) * 4), g);
             lds_turn();
             lds_st4(draws + q * (64 * E) + (lane / kLanes) * 16, u32x4{d.gam.x, d.gam.y, d.gam.z, d.gam.w});
@@ -235,7 +247,7 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
             m = u2f(mg);
             // Levels: a stored scale above zero implies m > 2^-118 (the super-group's is at least 2^-100, and the dither at least
             // 1/512), so the bound only keeps the quotient finite where the levels do not count.
-            const float inv = TREE ? (m >= 0x1p-120f ? 1.0f / m : 0.0f) : reciprocal(fmaxf(m, 0x1p-120f));
+            const float inv = TREE ? (m >= 0x1p-120f ? 1.0f / m : 0.0f) : reciprocal(u2f(max(mg, f2u(0x1p-120f))));
             // The scales, as in scale_group.  A super-group that is encoded as zero has its groups' maxima taken as zero instead of
             // its results: as conditional results the compiler puts the chain behind a branch, after the levels' lookups.
             uint32_t b = sg_max<E>(mg) + 0xFFFFu;
@@ -262,8 +274,8 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
             }
             __builtin_amdgcn_sched_barrier(0);
             const float ts = fminf((tiny ? 0.0f : m) * u2f(rec.y - ex), 255.0f), fl = floorf(ts);
-            const uint32_t rg = (uint32_t)fl + ((u2f(offset.y) < ts - fl) ? 1u : 0u);
-            sfg = (float)rg * fabsf(u2f(rec.x + ex));  // (without an exponent to add, the table's pattern has the sign bit)
+            const float rg = fl + (u2f(offset.y) < ts - fl ? 1.0f : 0.0f);  // a whole number
+            sfg = rg * fabsf(u2f(rec.x + ex));  // (without an exponent to add, the table's pattern has the sign bit)
             bool up[E];
 #pragma unroll
             for (int k = 0; k < E; ++k) {
@@ -284,7 +296,7 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
 #pragma unroll
               for (int k = E - 1; k >= 0; --k) {
                 const uint32_t index = B == 2 ? 0u : t[k].w >> (32 - B);
-                word = (word << B) | (f2u(xs[k]) >> 31 << (B - 1)) | (rg ? index + (up[k] ? 1u : 0u) : 0u);
+                word = (word << B) | (f2u(xs[k]) >> 31 << (B - 1)) | (rg != 0.0f ? index + (up[k] ? 1u : 0u) : 0u);
               }
               uint8_t *cp = out + tb.code_off + lg * (2 * B) + q * (E * B / 8);
               if constexpr (E * B == 8) gst<uint8_t>(cp, (uint8_t)word);
