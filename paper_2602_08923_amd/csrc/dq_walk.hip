@@ -392,7 +392,7 @@ static uint64_t count_tiles(const WalkPath *paths, uint32_t n_paths, uint32_t sg
 
 // The launch of W's schedule with tiles of W->tile_sgs super-groups.  *resident: waves that a CU holds at once.  False: no block fits.
 static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, uint64_t tiles, Walk *W, uint32_t *resident) {
-  constexpr uint32_t kLds = 160u * 1024;
+  constexpr uint32_t kLds = 160u * 1024, kGranule = 1280;  // LDS is given out in 128 pieces
   uint32_t lds, most;  // most: waves that fit a CU's registers
   if (W->tile_sgs < kWaveSGs) {
     W->stack_bytes = thin_stack(W->tile_sgs, W->levels);
@@ -411,8 +411,8 @@ static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, u
     lds = walk_lds(P, tree, W->stack_bytes, W->waves);
     most = 4 * (tree ? kWalkPerSimd<float, true> : (f32 ? kWalkPerSimd<float, false> : kWalkPerSimd<uint16_t, false>));
   }
-  uint32_t per_cu = kLds / lds;
-  if (per_cu == 0) return false;
+  if (lds > kLds) return false;
+  uint32_t per_cu = kLds / ((lds + kGranule - 1) / kGranule * kGranule);
   const uint32_t held = per_cu < most / W->waves ? per_cu : most / W->waves;
   *resident = held * W->waves;
   if (W->tile_sgs == kWaveSGs) per_cu = held;
@@ -427,24 +427,25 @@ static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, u
 // us per replay with all-gather, tiles of 1 / 2 / 4 super-groups, bf16 tensors, 256 CUs, by super-groups (profiles/replay_tile_sizes.txt has
 // all that was measured, bf16 and fp32, 2 to 256 workers):
 //              3,000          4,096           6,100           8,192           10,000          12,288
-//   ring 4     8/11/12        10/12/12        13/15/14        19/18/16        21/23/18        21/26/20
-//   ring 16    16/20/26       21/22/27        28/26/33        46/32/34        47/39/42        48/44/43
-//   ring 100   71/80/113      85/81/125       128/115/155     208/141/157     224/172/208     266/272/212
-//   tree 8     10/13/16       12/14/16        18/18/20        21/26/22        27/27/29        30/28/30
-//   tree 64    49/57/95       85/56/95        87/98/109       125/144/166     156/157/213     179/163/220
-//   tree 256   246/340/358    269/341/357     385/647/695     511/810/648     636/840/832     761/1005/856
-// Short schedules and rings: one super-group while four waves per SIMD hold them all (three for 16 workers' trees, whose stacks take
-// LDS), and half as many again with few workers, where a wave's start counts more than its hops; two up to the sizes at which four
-// are better with that dtype and n.  What the CUs hold of a wider butterfly falls with the levels of its stack, differently for each
+//   ring 4     8/10/10        9/11/10         13/12/12        19/15/12        20/20/14        20/22/15
+//   ring 16    15/19/23       19/21/24        26/24/27        42/29/28        45/36/33        46/40/34
+//   ring 100   66/79/113      80/80/121       117/105/126     200/134/136     215/173/164     259/266/190
+//   tree 8     10/12/16       11/13/16        16/17/18        20/25/20        25/26/26        27/27/26
+//   tree 64    47/56/96       84/57/96        84/98/104       122/145/170     151/159/203     167/166/208
+//   tree 256   235/341/368    259/346/368     379/653/722     503/839/663     626/849/791     752/1019/805
+// Rings and short trees: one super-group while four waves per SIMD hold them all, a little longer with few workers in bf16, where a wave's
+// start counts more than its hops; two up to 24 per CU, for bf16 rings of 32 workers and more up to 32, where eight waves hold them;
+// then four.  (Rings of 100 and more workers are the same with one and two within 4 % from 14 to 16 per CU.)  What the CUs hold of a wider
+// butterfly falls with the levels of its stack, differently for each
 // tile size, so there the time is estimated, up to 48 super-groups per CU: beyond, the three are within 20 % of each other with no order.
-// Of the 288 rows up to 12,288 super-groups the rule takes a choice within 6 % of the best in 263, the geometric mean of what it loses is
-// 1.2 % (the thresholds that were here before, the same for butterflies of all widths: 219, 4.6 %).  It is further off where the super-groups
-// are one tile more than the waves that the CUs hold and that tile is a cheap one (tree 64, 4,096), and takes the slowest of the three
-// for 16 workers' trees of 10,000 (51 us for 41): between 6,144 and 8,192 four are better there, and a third line is not worth it.
+// Of the 352 rows up to 16,384 super-groups the rule takes a choice within 6 % of the best in 333; the geometric mean of what it loses is
+// 0.9 %.  It is furthest off, by a fifth, for 32 and 64 workers' trees of 8,192.  LDS is counted in the pieces it is given out in, and tiles of
+// one and two without those that the widths' ends add, which the last waves take beside cheap ones: without that 128 workers' tree
+// of 4,096 took 219 us with tiles of one for 109 with two.
 static uint64_t tree_time(uint32_t n, uint32_t n_cu, uint32_t sgs, uint64_t tiles, uint32_t resident) {
   // in 0.01 us, fitted to the measurement: the launch, a tile's start, a hop alone and by the waves of the same SIMD
   struct Cost { uint32_t launch, start, hop, wave; };
-  const Cost c = sgs == 1 ? Cost{640, 200, 31, 12} : sgs == 2 ? Cost{600, 240, 34, 25} : Cost{670, 0, 78, 56};
+  const Cost c = sgs == 1 ? Cost{640, 200, 31, 12} : sgs == 2 ? Cost{600, 240, 34, 25} : Cost{670, 0, 122, 18};
   const uint64_t at_once = (uint64_t)n_cu * resident, full = tiles / at_once, rest = tiles % at_once;
   const uint64_t rounds = full + (rest != 0), waves = full * resident / 4 + (rest + 4 * n_cu - 1) / (4 * n_cu);
   return c.launch + rounds * c.start + n * (rounds * c.hop + waves * c.wave);
@@ -452,9 +453,15 @@ static uint64_t tree_time(uint32_t n, uint32_t n_cu, uint32_t sgs, uint64_t tile
 // Super-groups of a tile, or 0: by tree_time.
 static uint32_t tile_for(uint32_t n, bool f32, bool tree, uint32_t n_cu, uint64_t super_groups) {
   const uint32_t per_cu = (uint32_t)((super_groups + n_cu - 1) / n_cu);
-  if (n <= 8) return per_cu <= (tree && (f32 || n <= 4) ? 20 : 24) ? 1 : kWaveSGs;
   if (tree && n >= 32) return per_cu <= 48 ? 0 : kWaveSGs;
-  return per_cu <= (tree ? 12 : 16) ? 1 : per_cu <= (!tree && n >= 16 && !f32 ? 40 : 24) ? 2 : kWaveSGs;
+  uint32_t one = 16, two = 24;  // up to so many per CU
+  if (tree) {
+    one = f32 ? (n <= 8 ? 16 : 12) : n <= 4 ? 20 : n <= 8 ? 28 : 16;
+  } else if (!f32) {
+    if (n > 4 && n <= 8) one = 24;
+    two = n <= 4 ? 16 : n >= 32 ? 32 : 24;
+  }
+  return per_cu <= one ? 1 : per_cu <= two ? 2 : kWaveSGs;
 }
 
 bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W) {
@@ -471,7 +478,7 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
     uint32_t resident = 0;
     const uint64_t tiles = count_tiles(paths, W->n_paths, sgs, &w.widths);
     if (!grid_of_tiles(P, f32, tree, n_cu, tiles, &w, &resident)) continue;
-    const uint64_t time = wanted ? 0 : tree_time(W->n, n_cu, sgs, tiles, resident);
+    const uint64_t time = wanted ? 0 : tree_time(W->n, n_cu, sgs, sgs == kWaveSGs ? tiles : (super_groups + sgs - 1) / sgs, resident);
     if (!found || time <= best_time) {
       best = w;
       best_time = time;
