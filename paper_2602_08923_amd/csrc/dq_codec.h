@@ -387,11 +387,11 @@ __device__ __forceinline__ Scales scales_of(float m, float M, float us, uint32_t
   s.sfb = b >> 16;
   const u32x2 q = lds_ld2(rec0 + ((b >> 13) & 0x3F8u));
   const uint32_t e = b & 0x7F800000u;
-  const float ts = fminf(m * u2f(q.y - e), 255.0f);
-  const float fl = floorf(ts);
-  s.rg = s.sfb ? (uint32_t)fl + ((us < ts - fl) ? 1u : 0u) : 0u;
-  s.inv = s.rg ? 1.0f / m : 0.0f;
-  s.sfg = s.sfb ? (float)s.rg * u2f(q.x + e) : 0.0f;
+  // floor(ts) + [us < ts - floor(ts)] is the ceiling of ts - us: that difference is exact, or lies between -1 and 0
+  const float rg = fabsf(ceilf(fminf(m * u2f(q.y - e), 255.0f) - us));
+  s.rg = s.sfb ? (uint32_t)rg : 0u;
+  s.inv = s.sfb && rg != 0.0f ? 1.0f / m : 0.0f;
+  s.sfg = s.sfb ? rg * u2f(q.x + e) : 0.0f;
   return s;
 }
 __device__ __forceinline__ Scales scale_group(const float (&v)[16], float us, uint32_t rec0) {

@@ -10,9 +10,11 @@
 // schedules come here.
 //
 // What bounds it is how much of a hop's chain four waves per SIMD cover: two vector instructions can go per four cycles, from two waves,
-// and about half of that is reached (256 workers, 4,096 super-groups: 106 instructions per hop, 184 us; 101 would be their issue).  So all
+// and about half of that is reached (256 workers, 4,096 super-groups: 97 instructions per hop, 177 us; 92 would be their issue).  So all
 // instructions count, on the path or beside it, scalar ones and waits too: both super-group draws made by one generator call, the next four tensors
-// by one scalar load and the group scale left in fp32 took 188 us there to 184, four workers' fp32 ring of 4,096 with all-gather from 9.9 to 9.1.
+// by one scalar load and the group scale left in fp32 took 188 us there to 184, four workers' fp32 ring of 4,096 with all-gather from 9.9 to 9.1;
+// the super-group's maximum and scale in scalar registers and the rounding of the group scale in two instructions 185 to 177.
+// (All comparisons of a hop before its selections, which saves the waits between them: 192.)
 //
 // What differs from the wide tile:
 //   draws    : a lane draws the group's 16 bytes for ONE of the next 16 / E hops, and the group's lanes exchange them through
@@ -28,7 +30,7 @@ namespace dq {
 namespace {
 
 constexpr uint32_t kAhead = 4;  // hops a slice is requested ahead of its use
-constexpr uint32_t kThinPark = 640;    // per wave: 32 scale draws of 16 bytes, 32 permutation slots
+constexpr uint32_t kThinPark = 656;    // per wave: 32 scale draws of 16 bytes, 32 permutation slots, 16 bytes of zero
 constexpr uint32_t kThinDraws = 1536;  // per wave: 64 groups' (of some hop) 16 bytes, their rounding offset and scale dither
 constexpr uint32_t kThinWaves = 4;     // per block
 static_assert(kThinWaves * kThinDraws <= (kOffTab4 - kOffDec2) * 4, "the draws lie over the decode tables, which are not copied");
@@ -71,6 +73,15 @@ __device__ __forceinline__ Bit<LT, E> load_bit(uint64_t tensor, uint64_t at) {
 template <bool TREE>
 __device__ __forceinline__ uint64_t tensor_of(const Walk &W, uint32_t chunk, uint32_t i) {
   return table_entry(reinterpret_cast<const uint64_t *>(W.grads), TREE ? leaf_of<TREE>(W, chunk, i) : (W.chain ? 0u : chunk) + i);
+}
+
+// Maximum over a super-group of which every lane of the wave has its group's maximum
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+  x = max(x, dpp_u<0x124>(x));  // row_ror:4
+  x = max(x, dpp_u<0x128>(x));  // row_ror:8
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x142, 0xA, 0xF, false));  // row 0 into 1, row 2 into 3
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x143, 0xC, 0xF, false));  // row 1 into 2 and 3
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
 // What a wave holds of a tile before it walks it: where it is and the slices of its first hops.
@@ -129,7 +140,7 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
   const uint32_t lane = threadIdx.x & 63u, q = lane & (kLanes - 1u), g = (lane / kLanes) & 15u;
   const uint32_t row = min(lane * kSgs / 64u, pos.n_seg - 1 - pos.tile_first);
   const uint64_t gi = (job.first_sg + pos.seg_first + pos.tile_first + row) * 16 + g;  // global group index
-  const uint32_t last = W.n - 1;
+  const uint32_t last = W.n - 1, zeros = park + 640;
   float v[E], level[E], sfg = 0.0f;  // the pending message: level * sfg
 #pragma unroll
   for (int k = 0; k < E; ++k) level[k] = -0.0f;  // nothing pending: adding -0 changes nothing
@@ -248,13 +259,14 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
             // Levels: a stored scale above zero implies m > 2^-118 (the super-group's is at least 2^-100, and the dither at least
             // 1/512), so the bound only keeps the quotient finite where the levels do not count.
             const float inv = TREE ? (m >= 0x1p-120f ? 1.0f / m : 0.0f) : reciprocal(u2f(max(mg, f2u(0x1p-120f))));
-            // The scales, as in scale_group.  A super-group that is encoded as zero has its groups' maxima taken as zero instead of
-            // its results: as conditional results the compiler puts the chain behind a branch, after the levels' lookups.
-            uint32_t b = sg_max<E>(mg) + 0xFFFFu;
-            const bool tiny = b < 0x0D800000u;
-            b = tiny ? 0u : b;
-            const uint32_t sfb = b >> 16, ex = b & 0x7F800000u;
-            const u32x2 rec = lds_ld2(kRec0 + ((b >> 13) & 0x3F8u));
+            // The scales, as in scale_group.  With one super-group per wave its maximum and what follows from it are scalar, and a
+            // super-group that is encoded as zero finds zeros for its reciprocals.  With two such a one has its groups' maxima taken as zero instead
+            // of its results: as conditional results the compiler puts the chain behind a branch, after the levels' lookups.
+            const uint32_t top = (E == 4 ? wave_max(mg) : sg_max<E>(mg)) + 0xFFFFu;
+            const bool tiny = top < 0x0D800000u;
+            const uint32_t b = tiny ? 0u : top, sfb = b >> 16, ex = b & 0x7F800000u;
+            const u32x2 rec = lds_ld2(E == 4 && tiny ? zeros : kRec0 + ((b >> 13) & 0x3F8u));
+            if (E != 4 && tiny) m = 0.0f;
             float xs[E];
             u32x4 t[E];
             auto uniform = [&](int k) { return __builtin_fmaf((float)((gam[k >> 2] >> (8 * (k & 3))) & 0xFFu), V.s_n, u2f(offset.x)); };
@@ -273,8 +285,8 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
               for (int k = 0; k < E; ++k) t[k] = lds_ld4(or_and(f2u(fabsf(xs[k]) - u2f(e[k].x)) >> 27, 16u, e[k].y));
             }
             __builtin_amdgcn_sched_barrier(0);
-            const float ts = fminf((tiny ? 0.0f : m) * u2f(rec.y - ex), 255.0f), fl = floorf(ts);
-            const float rg = fl + (u2f(offset.y) < ts - fl ? 1.0f : 0.0f);  // a whole number
+            // floor(ts) + [us < ts - floor(ts)] is the ceiling of ts - us: that difference is exact, or lies between -1 and 0
+            const float ts = fminf(m * u2f(rec.y - ex), 255.0f), rg = fabsf(ceilf(ts - u2f(offset.y)));
             sfg = rg * fabsf(u2f(rec.x + ex));  // (without an exponent to add, the table's pattern has the sign bit)
             bool up[E];
 #pragma unroll
@@ -363,6 +375,7 @@ __global__ __launch_bounds__(kThinWaves * 64) __attribute__((amdgpu_waves_per_eu
   if (!any) return;
   const uint32_t draws = kOffDec2 * 4 + wave * kThinDraws, park = P.blob_dwords * 4 + wave * kThinPark;
   const uint32_t stack = P.blob_dwords * 4 + kThinWaves * kThinPark + wave * W.stack_bytes;
+  lds_st4(park + 640, u32x4{0, 0, 0, 0});
   const Vec V(P);
   for (;;) {
     if (x.pos.wi == 0) walk_thin<2, LT, TREE, E>(path, P, V, W, park, draws, stack, x);
