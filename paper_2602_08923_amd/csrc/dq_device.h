@@ -97,7 +97,6 @@ struct Walk {
   uint32_t stack_bytes;      // LDS per wave for them
   uint32_t tile_sgs;         // super-groups of a wave's tile: 4 (dq_walk.hip), 2 or 1 (dq_thin.hip)
   uint32_t n_paths;
-  uint32_t widths;           // which widths some chunk has (bit k: 2 << k bits)
   uint32_t blocks, waves;    // grid, waves per block
   uint32_t by_cost;          // shares of equal cost (0: of equal tile counts)
 };

@@ -366,11 +366,7 @@ __global__ __launch_bounds__(kThinWaves * 64) __attribute__((amdgpu_waves_per_eu
     path = table_entry(paths, at.path);
     x = start_tile<LT, TREE, E>(path, W, at.tile);
   }
-#pragma unroll
-  for (int r = 0; r < kRanges; ++r)  // tables of widths no chunk has are left out, and nothing is decoded from codes
-    if ((P.range_width[r] > 2 || (W.widths >> P.range_width[r] & 1u)) && r != 1)
-      for (uint32_t i = (r == 2 ? kOffTab4 : r == 3 ? kOffTab8 : P.range_lo[r]) + threadIdx.x * 4; i < P.range_hi[r]; i += kThinWaves * 64 * 4)
-        *reinterpret_cast<uint4 *>(&lds[i]) = gld16(&P.blob[i]);
+  copy_tables(lds, P, kOffTab4);  // nothing is decoded from codes
   __syncthreads();
   if (!any) return;
   const uint32_t draws = kOffDec2 * 4 + wave * kThinDraws, park = P.blob_dwords * 4 + wave * kThinPark;

@@ -318,14 +318,10 @@ __global__ __launch_bounds__((TREE ? 512 : 256)) __attribute__((amdgpu_waves_per
   extern __shared__ uint4 lds_raw[];
   uint32_t *lds = reinterpret_cast<uint32_t *>(lds_raw);
   const uint32_t waves = blockDim.x / 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-#pragma unroll
-  for (int r = 0; r < kRanges; ++r)  // tables of widths no chunk has are left out, and a ring or chain never decodes from codes
-    if ((P.range_width[r] > 2 || (W.widths >> P.range_width[r] & 1u)) && (TREE || r != 1))
-      for (uint32_t i = (!TREE && r == 2 ? kOffTab4 : P.range_lo[r]) + threadIdx.x * 4; i < P.range_hi[r]; i += blockDim.x * 4)
-        *reinterpret_cast<uint4 *>(&lds[i]) = gld16(&P.blob[i]);
-  __syncthreads();
   const uint32_t v = __builtin_amdgcn_readfirstlane(blockIdx.x * waves + wave);
   const WalkShare from = table_entry(shares, v), to = table_entry(shares, v + 1);
+  copy_tables(lds, P, TREE ? kOffDec2 : kOffTab4);  // a ring or chain never decodes from codes
+  __syncthreads();
   Areas A;
   const uint32_t end = P.blob_dwords * 4;
   A.park = (TREE ? end : kOffDec2 * 4) + wave * kParkBytes;  // ring, chain: over the decode tables, which they do not copy
@@ -379,14 +375,10 @@ static_assert(kCosts[1][0] == kCosts[1][3] && kCosts[0][0] == 1, "split_walk");
 template <uint32_t C>
 struct Cost { static constexpr uint32_t value = C; };
 
-static uint64_t count_tiles(const WalkPath *paths, uint32_t n_paths, uint32_t sgs, uint32_t *widths) {
+static uint64_t count_tiles(const WalkPath *paths, uint32_t n_paths, uint32_t sgs) {
   uint64_t tiles = 0;
-  *widths = 0;
   for (uint32_t p = 0; p < n_paths; ++p)
-    for (int w = 0; w < 4; ++w) {
-      tiles += (paths[p].job.n_sg[w] + sgs - 1) / sgs;
-      if (paths[p].job.n_sg[w]) *widths |= 1u << w;
-    }
+    for (int w = 0; w < 4; ++w) tiles += (paths[p].job.n_sg[w] + sgs - 1) / sgs;
   return tiles;
 }
 
@@ -466,7 +458,7 @@ static uint32_t tile_for(uint32_t n, bool f32, bool tree, uint32_t n_cu, uint64_
 
 bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W) {
   const bool f32 = dtype == DQ_F32;
-  const uint64_t super_groups = count_tiles(paths, W->n_paths, 1, &W->widths);
+  const uint64_t super_groups = count_tiles(paths, W->n_paths, 1);
   if (super_groups == 0) return false;
   const uint32_t wanted = tile_for(W->n, f32, tree, n_cu, super_groups);
   Walk best = *W;
@@ -476,7 +468,7 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
     Walk w = *W;
     w.tile_sgs = sgs;
     uint32_t resident = 0;
-    const uint64_t tiles = count_tiles(paths, W->n_paths, sgs, &w.widths);
+    const uint64_t tiles = count_tiles(paths, W->n_paths, sgs);
     if (!grid_of_tiles(P, f32, tree, n_cu, tiles, &w, &resident)) continue;
     const uint64_t time = wanted ? 0 : tree_time(W->n, n_cu, sgs, sgs == kWaveSGs ? tiles : (super_groups + sgs - 1) / sgs, resident);
     if (!found || time <= best_time) {
