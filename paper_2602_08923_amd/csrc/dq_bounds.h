@@ -21,7 +21,10 @@ struct OwnCheck {
   uint32_t call;
   uint32_t src_limit;   // of the indices that the kernel reads through before it knows the verdict
 };
-// Of the check that this thread has armed: to be made by the kernel itself (false: there is none, or not so) ...
+// Of the check that this thread has armed: how many indices a kernel that makes it itself would look at (0: none is armed; all ones: it is
+// to be a launch of its own, as a tensor smaller than a super-group leaves no index that may be used meanwhile) ...
+uint64_t own_check_due();
+// ... to be made by the kernel itself (false: there is none, or not so) ...
 bool take_own_check(const uint32_t *src, OwnCheck *check);
 // ... or enqueued in front of it: armed_guard (dq_device.h)
 }  // namespace dq

@@ -171,9 +171,16 @@ hipError_t enqueue_check(hipStream_t s) {
 
 }  // namespace
 
+uint64_t own_check_due() {
+  const Armed &x = t_armed;
+  if (!x.w) return 0;
+  return x.started || x.a.limit == 0 || (x.b.n && x.b.limit == 0) ? ~0ull : (uint64_t)x.a.n + x.b.n;
+}
+
 bool take_own_check(const uint32_t *src, OwnCheck *check) {
   Armed &x = t_armed;
-  if (!x.w || x.started || x.a.limit == 0 || (x.b.n && x.b.limit == 0)) return false;
+  const uint64_t due = own_check_due();
+  if (due == 0 || due == ~0ull) return false;
   *check = OwnCheck{x.a, x.b, x.w->host, x.w->calls, src == x.a.index ? x.a.limit : src && src == x.b.index ? x.b.limit : 0xFFFFFFFFu};
   x.started = true;
   return true;

@@ -317,6 +317,7 @@ hipError_t go_few(const Job &job, const Params &p, uint32_t super_groups, hipStr
 // Where the table above crosses (2-bit chunks cross a little earlier, at 30 super-groups per CU, 8-bit ones later).  Larger tables than the
 // default level sets' (21 KB) are copied by more blocks than they are worth here.
 bool takes_few(Kind kind, const Job &job, const Params &P, uint32_t n_cu) {
+  if (own_check_due() == ~0ull) return false;
   const uint64_t n = (uint64_t)job.n_sg[0] + job.n_sg[1] + job.n_sg[2] + job.n_sg[3];
   return kind == kDecompress ? n <= 40ull * n_cu : n <= 32ull * n_cu && P.blob_dwords * 4 <= kFewTableBytes;
 }

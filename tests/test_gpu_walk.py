@@ -169,6 +169,23 @@ def test_a_call_of_few_super_groups_checks_every_index_itself(dev, at):
         assert bool((hop == 9).all())
 
 
+def test_a_result_smaller_than_a_super_group_is_refused(dev):
+    """No destination is good, and none may be written to before the check has spoken."""
+    ctx, n_sg = B.Context(4, seed=1), 9
+    ch = B.make_chunk(0, [2, n_sg - 2, 0])
+    x = gradients(1, n_sg, torch.bfloat16, dev, 1)[0]
+    index = torch.arange(n_sg, dtype=torch.int32, device=dev)
+    message = ctx.dq_compress(x, ch, 1)
+    out = torch.full((n_sg * 256,), 7.0, device=dev)
+    for kw in ({}, {"local": x}, {"local": x, "sg_index": index}):
+        with pytest.raises(B.DqError, match="out_base"):
+            ctx.dq_decompress_restore(message, ch, index, out[:255], **kw)
+    with pytest.raises(B.DqError):
+        ctx.dq_dar_hop(message, x[:0], ch, 2, sg_index=index)
+    torch.cuda.synchronize()
+    assert bool((out == 7.0).all())
+
+
 @pytest.mark.parametrize("n_sg", [1, 4, 2049, 70001])
 def test_indices_out_of_bounds_are_refused_and_nothing_is_written(dev, n_sg):
     ctx = B.Context(4, seed=1)
