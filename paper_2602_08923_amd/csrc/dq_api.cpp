@@ -172,11 +172,6 @@ dq_status build_tables(double g4, double g8, dq::Params &P, std::vector<uint32_t
   // two search tables, whose size follows the level sets.
   std::vector<uint32_t> lut[3];
   int bins_log[3] = {0, 0, 0};
-  auto range = [&](int r, uint32_t lo, uint32_t width) {
-    P.range_lo[r] = lo;
-    P.range_hi[r] = (uint32_t)blob.size();
-    P.range_width[r] = width;
-  };
   {
     std::vector<uint32_t> rec(256);
     for (int m = 0; m < 128; ++m) {
@@ -188,7 +183,6 @@ dq_status build_tables(double g4, double g8, dq::Params &P, std::vector<uint32_t
     uint32_t off;
     append_aligned(blob, rec, &off);
     if (off != dq::kOffRec) return DQ_EINVAL;
-    range(0, off, 3);
   }
   const uint32_t want_dec[3] = {dq::kOffDec2, dq::kOffDec4, dq::kOffDec8};
   const uint32_t want_tab[3] = {0, dq::kOffTab4, dq::kOffTab8};
@@ -231,18 +225,15 @@ dq_status build_tables(double g4, double g8, dq::Params &P, std::vector<uint32_t
       bins_log[wi] = m;
     }
     while (blob.size() % 4) blob.push_back(0);
-    range(1 + wi, off_dec, (uint32_t)wi);
   }
   {
     uint32_t off;
     append_aligned(blob, lut[1], &off);
     if (off != dq::kOffLut4) return DQ_EINVAL;
     while (blob.size() % 4) blob.push_back(0);
-    range(4, off, 1);
     uint32_t off8;
     append_aligned(blob, lut[2], &off8);
     while (blob.size() % 4) blob.push_back(0);
-    range(5, off8, 2);
     const uint32_t lut_at[3] = {0, off * 4, off8 * 4};  // LDS byte addresses
     for (int wi = 1; wi < 3; ++wi) {
       const uint32_t bits = fbits((float)ldexp(1.0, 20 - bins_log[wi])) + lut_at[wi];

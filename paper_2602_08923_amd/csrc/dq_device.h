@@ -56,15 +56,12 @@ constexpr uint32_t kOffTab4 = 1792;    // 4-bit levels: 7 pairs of entries {T[r]
 constexpr uint32_t kOffDec8 = 1848;    // 8-bit decode: 256 signed levels
 constexpr uint32_t kOffTab8 = 2104;    // 8-bit levels: 127 pairs of entries {T[r], D[r], T[r+1], r << 24}
 constexpr uint32_t kOffLut4 = 3120;    // search table of the 4-bit set: (2^m + 1) pairs {next level, address of the candidate's pair}
-constexpr int kRanges = 6;             // copy ranges: common, 2-bit, 4-bit fixed, 8-bit fixed, 4-bit search, 8-bit search
 
 // Everything the kernels need besides the job: PRNG key, worker count, table blob.
 struct Params {
   const uint32_t *guard; // null, or a word the single-chunk kernels read first: if it is guard_call they do nothing (dq_bounds.hip)
   const uint32_t *blob;  // device copy of the table blob
   uint32_t blob_dwords;  // multiple of 4
-  uint32_t range_lo[kRanges], range_hi[kRanges];  // dword ranges a block copies into LDS (multiples of 4) ...
-  uint32_t range_width[kRanges];                  // ... if it meets tiles of this width index (3: always)
   float magic[3];        // 2^(20-m) plus the search table's LDS address in units of its last bit (see quantize_codes)
   uint32_t key0, key1, round;
   uint32_t n_workers;

@@ -6,12 +6,12 @@
 // (SG), so the group maximum is in-lane and the SG maximum is four row-rotate DPP steps; a
 // wave64 processes 4 SGs per tile and a run of consecutive tiles per launch.  Codes travel as
 // one 32/64/128-bit access per lane (2/4/8-bit widths), the local slice as 128-bit accesses.
-// Level tables live in LDS from byte 0 on (a block copies only the widths it meets):
+// Level tables live in LDS from byte 0 on:
 //   dec[byte]      the 8/b signed levels (+-T[r]) one byte of packed codes holds  -> decode
-//   lut[q]         {T[rc+1], rc} for q = round(x' * 2^m): rc is the level index at the
-//                  lower edge of the bin, and bins are narrower than any gap, so the
+//   lut[q]         {T[rc+1], address of rc's pair} for q = round(x' * 2^m): rc is the level index
+//                  at the lower edge of the bin, and bins are narrower than any gap, so the
 //                  level at or below x' is rc or rc+1 -- one compare settles it
-//   tab[r]         {T[r], D[r]}                                                    -> rounding
+//   tab[rc]        the entries {T[r], D[r], T[r+1], code} of r = rc+1 and r = rc   -> rounding
 // The stochastic rounding follows the division-free form  T + u*D < x'  with
 // u = (pi + gamma)/n built from one Philox byte per entry (Section 3.3 "Correlated rounding").
 // The per-SG random numbers (group-scale bytes, shared permutation) of up to 8 tiles are
@@ -342,6 +342,35 @@ __device__ __forceinline__ void da_range(const Job &job, const Params &P, uint32
   }
 }
 
+// The tables on their way into a block's LDS: 16-byte words requested together before anything else is, put down after the draws are
+// made.  All the tables, whatever widths the block meets (decompress: what lies before the search tables); a level set with larger ones
+// takes further trips.  Only the tables of the widths that a block met, a trip for each of their six
+// ranges beyond its first 4 KB, took longer at every size, us per call, bf16, 2- to 8-bit super-groups, ranges -> together:
+//                 12,288         20,000         40,000          100,000
+//   hop           6.9 -> 6.2     8.3 -> 7.2     11.5 -> 10.3    20.2 -> 18.8
+//   compress      6.7 -> 5.9     7.9 -> 6.8     10.3 -> 9.1     17.9 -> 16.8
+//   sink          5.9 -> 5.1     6.8 -> 6.0     10.7 -> 9.7     27.8 -> 27.0
+// A ring of eight step by step: 384 super-groups 4.9 -> 4.3 per step, 4,096 5.75 -> 4.85, 48,832 13.8 -> 12.5.
+template <Kind KIND>
+struct BlockTables {
+  // Words per thread: the default sets' 21 KB; decompress's 12.5 KB in two trips, as with all four words at once the restore of 488,282
+  // gathered super-groups took 192 us instead of 186.5, where it was 187.4 range by range (and smaller ones the same).
+  static constexpr uint32_t kTogether = KIND == kDecompress ? 2 : 6;
+  uint4 part[kTogether];
+  uint32_t words;
+  __device__ __forceinline__ explicit BlockTables(const Params &P) : words(KIND == kDecompress ? kOffLut4 / 4 : P.blob_dwords / 4) {
+#pragma unroll
+    for (uint32_t k = 0; k < kTogether; ++k) part[k] = gld16(&P.blob[min(threadIdx.x + k * kBlockThreads, words - 1) * 4]);
+  }
+  __device__ __forceinline__ void put_down(uint32_t *lds, const Params &P) const {
+#pragma unroll
+    for (uint32_t k = 0; k < kTogether; ++k)
+      *reinterpret_cast<uint4 *>(&lds[min(threadIdx.x + k * kBlockThreads, words - 1) * 4]) = part[k];
+    for (uint32_t i = threadIdx.x + kTogether * kBlockThreads; i < words; i += kBlockThreads)
+      *reinterpret_cast<uint4 *>(&lds[i * 4]) = gld16(&P.blob[i * 4]);
+  }
+};
+
 // The job's tiles go round the waves of the grid row (4 * gridDim.x waves): wave w takes w, w + W, w + 2W, ...  What the
 // waves read and write at one time is then one window of each stream, in the order of its addresses, and not W places in
 // it; and every wave meets the widths in about the same shares, so that they end together (2-bit tiles are cheaper).  The
@@ -370,22 +399,7 @@ __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
   const uint32_t in_block = q * kBlockWaves + min(r - min(r, bw), (uint32_t)kBlockWaves);
   const bool block_draws = KIND != kDecompress && in_block <= 8u * kBlockWaves;
 
-  // copy the common tables and the table ranges of the widths this block meets (all, if it goes round the job more than
-  // once); the first 16 bytes per thread of every range are requested together (one round trip, not six)
-  const uint32_t b_hi = q ? total : min(bw + kBlockWaves, total), b_lo = q ? 0u : bw;
-  const bool meets[4] = {b_lo < t0, b_lo < t0 + t1 && b_hi > t0, b_lo < t0 + t1 + t2 && b_hi > t0 + t1, true};
-  constexpr int kEarly = kRanges;
-  uint4 first[kEarly];
-  bool need[kRanges], has[kEarly];
-#pragma unroll
-  for (int r = 0; r < kRanges; ++r)
-    need[r] = meets[P.range_width[r] & 3u] && !(KIND == kDecompress && P.range_lo[r] >= kOffLut4);
-#pragma unroll
-  for (int r = 0; r < kEarly; ++r) {
-    const uint32_t i = P.range_lo[r] + threadIdx.x * 4;
-    has[r] = need[r] && i < P.range_hi[r];
-    if (has[r]) first[r] = gld16(&P.blob[i]);
-  }
+  BlockTables<KIND> tables(P);
   if constexpr (KIND != kDecompress) {
     if (block_draws && 8u * wave < in_block)
       park_draws(job, P, min(8u, in_block - 8u * wave), park0 + wave * 1024, [&](uint32_t j) {
@@ -393,14 +407,7 @@ __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
         return (k / kBlockWaves) * n_waves + bw + k % kBlockWaves;
       });
   }
-#pragma unroll
-  for (int r = 0; r < kEarly; ++r)
-    if (has[r]) *reinterpret_cast<uint4 *>(&lds[P.range_lo[r] + threadIdx.x * 4]) = first[r];
-#pragma unroll
-  for (int r = 0; r < kRanges; ++r)
-    if (need[r])
-      for (uint32_t i = P.range_lo[r] + ((r < kEarly ? kBlockThreads : 0) + threadIdx.x) * 4; i < P.range_hi[r]; i += kBlockThreads * 4)
-        *reinterpret_cast<uint4 *>(&lds[i]) = gld16(&P.blob[i]);
+  tables.put_down(lds, P);
   __syncthreads();
 
   [[maybe_unused]] const uint32_t area = park0 + wave * 1024;     // compress, DAR: this wave's parked draws
@@ -423,8 +430,7 @@ __device__ __forceinline__ void run_job(const Job &job, const Params &P) {
   }
 }
 
-// Five blocks of four waves are resident per CU (the launcher's grid): at most 96 vector registers (the kernels
-// with fp32 locals use 82-88 since a tile's successor is requested from inside the tile, the others at most 80).
+// Five blocks of four waves are resident per CU (the launcher's grid): at most 96 vector registers (they use 73 to 95).
 template <Kind KIND, typename LT>
 __global__ __launch_bounds__(kBlockThreads) void k_one(Job job, Params P) {
   if (P.guard && gld<uint32_t>(P.guard) == P.guard_call) return;
@@ -442,12 +448,7 @@ template <Kind KIND, typename LT>
 __global__ __launch_bounds__(kBlockThreads) void k_batch_small(const Job *jobs, uint32_t n_jobs, Params P) {
   extern __shared__ uint4 lds_raw[];
   uint32_t *lds = reinterpret_cast<uint32_t *>(lds_raw);
-  // every table range: the block's four jobs may meet any width (decompress never needs the search tables)
-#pragma unroll
-  for (int r = 0; r < kRanges; ++r)
-    if (!(KIND == kDecompress && P.range_lo[r] >= kOffLut4))
-      for (uint32_t i = P.range_lo[r] + threadIdx.x * 4; i < P.range_hi[r]; i += kBlockThreads * 4)
-        *reinterpret_cast<uint4 *>(&lds[i]) = gld16(&P.blob[i]);
+  BlockTables<KIND>(P).put_down(lds, P);
   __syncthreads();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t j = __builtin_amdgcn_readfirstlane(blockIdx.x * kBlockWaves + wave);
