@@ -5,11 +5,11 @@
 // almost to itself.  Here the arguments are read at once, the tile is requested before the tables, the draws are made while both are on
 // their way, and the chain of the entries is a quarter as long.  Measured, us per call back to back, bf16, 2- to 8-bit super-groups, tiles of
 // four -> one per wave (the host takes 3.2 to 3.9 for a launch):
-//                 16             2,048          4,096          6,144          8,192          10,240         12,288
-//   hop           4.6 -> 3.9     5.4 -> 4.0     5.6 -> 4.2     6.0 -> 4.9     6.1 -> 5.5     6.5 -> 6.35    6.8 -> 7.1
-//   compress      4.4 -> 3.9     5.1 -> 4.0     5.2 -> 4.0     5.6 -> 4.6     5.65 -> 5.3    6.0 -> 6.1     6.3 -> 6.7
-//   sink          3.6 -> 3.4     4.2 -> 3.5     4.4 -> 3.5     4.8 -> 4.0     4.9 -> 4.4     5.3 -> 4.9     5.4 -> 5.4
-//   receive       3.4 -> 3.2     4.0 -> 3.3     4.25 -> 3.3    4.6 -> 3.8     4.7 -> 4.1     5.1 -> 4.6     5.1 -> 5.0
+//                 3,000          4,096          6,000          8,192          10,240         12,288
+//   hop           4.9 -> 4.0     5.1 -> 4.05    5.25 -> 4.7    5.5 -> 5.4     5.85 -> 6.15   6.15 -> 6.85
+//   compress      4.75 -> 3.65   4.8 -> 3.75    5.0 -> 4.3     5.25 -> 5.0    5.45 -> 5.65   5.7 -> 6.3
+//   sink          4.2 -> 3.3     4.35 -> 3.4    4.45 -> 3.75   4.6 -> 4.2     4.75 -> 4.7    5.0 -> 5.2
+//   receive       4.0 -> 3.2     4.05 -> 3.35   4.2 -> 3.65    4.45 -> 4.0    4.65 -> 4.45   4.75 -> 4.85
 // What bounds it: up to one block per CU the latencies, from there vector-ALU issue (370 instructions per super-group and
 // wave, against 100 per super-group in tiles of four; 450 when every wave drew its super-group's numbers itself, and 0.8 us
 // more per block and CU).
@@ -314,12 +314,22 @@ hipError_t go_few(const Job &job, const Params &p, uint32_t super_groups, hipStr
 
 }  // namespace
 
-// Where the table above crosses (2-bit chunks cross a little earlier, at 30 super-groups per CU, 8-bit ones later).  Larger tables than the
-// default level sets' (21 KB) are copied by more blocks than they are worth here.
+// Super-groups per CU up to which one per wave is faster (us per call at 256 CUs, bf16, one per wave against tiles of four):
+//   several widths, or 8- and 16-bit ones only: hop 32 (9,000: 6.05 against 5.85), decompress 40;
+//   2- or 4-bit ones only, whose wide tiles run one short piece of code: 24 (6,144: hop 4.7 against 4.85; 7,000: 5.4 against 5.0; sink 3.8
+//   against 4.0; 4.25 against 4.05);
+//   with a check of indices armed, which the wide kernel leaves to a launch in front of it: hop and decompress of two arrays 40 (8,192: 8.3
+//   against 9.9; 10,240: 9.3 against 9.3), decompress of one array 56 (12,288: 8.7 against 9.3; 14,336: 9.35 against 9.4): every block looks
+//   at every index.
+// Tables larger than the default level sets' (21 KB) are copied by more blocks than they are worth here.
 bool takes_few(Kind kind, const Job &job, const Params &P, uint32_t n_cu) {
-  if (own_check_due() == ~0ull) return false;
-  const uint64_t n = (uint64_t)job.n_sg[0] + job.n_sg[1] + job.n_sg[2] + job.n_sg[3];
-  return kind == kDecompress ? n <= 40ull * n_cu : n <= 32ull * n_cu && P.blob_dwords * 4 <= kFewTableBytes;
+  const uint64_t n = (uint64_t)job.n_sg[0] + job.n_sg[1] + job.n_sg[2] + job.n_sg[3], due = own_check_due();
+  if (due == ~0ull || (kind != kDecompress && P.blob_dwords * 4 > kFewTableBytes)) return false;
+  uint32_t most;
+  if (due) most = kind == kDecompress && due == n ? 56 : 40;
+  else if (n == job.n_sg[0] || n == job.n_sg[1]) most = 24;
+  else most = kind == kDecompress ? 40 : 32;
+  return n <= (uint64_t)most * n_cu;
 }
 
 hipError_t launch_few(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &p, hipStream_t s) {

@@ -262,10 +262,11 @@ def test_stream_probe_reads_and_writes_every_word(dev):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("n_sg", [[1, 0, 0, 0], [3, 2, 1, 1], [2, 3, 2, 1], [4, 2, 2, 1], [2000, 4000, 2100, 92], [2000, 4000, 2100, 93],
-                                  [2000, 5000, 3100, 140], [2000, 5000, 3100, 141]])
+                                  [2000, 5000, 3100, 140], [2000, 5000, 3100, 141], [6144, 0, 0, 0], [0, 6145, 0, 0],
+                                  [0, 8000, 6336, 0], [0, 8000, 6337, 0]])
 def test_calls_at_the_edges_of_the_kernel_for_few_super_groups(dev, n_sg, dtype):
-    """One super-group per wave, eight per block, up to 32 (decompress: 40) per CU: at 256 CUs the last sizes lie on both sides of the
-    two lines.  Also hops and decompress-accumulates that write over what they read, means, gathered inputs and a scattered restore."""
+    """One super-group per wave, eight per block, up to 24 to 56 per CU: at 256 CUs the sizes from 6,144 on lie on both sides of the
+    lines.  Also hops and decompress-accumulates that write over what they read, means, gathered inputs and a scattered restore."""
     n, S, first = 6, sum(n_sg), 2 ** 33 + 5
     rng = np.random.default_rng(S)
     a, b = make_local(rng, S * 256, dtype), make_local(rng, S * 256, dtype)

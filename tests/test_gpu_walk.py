@@ -134,12 +134,12 @@ def test_whole_mx_replay_equals_its_steps(dev, fmt, dtype, topology, n, J, nb, a
     whole_against_steps(rp, {"ring": n, "chain": 1, "butterfly": 0}[topology])
 
 
-@pytest.mark.parametrize("at", [0, 3, 4, 4095, 8190, 8191, 8192, 10239, 10240])
+@pytest.mark.parametrize("at", [0, 3, 4, 4095, 8190, 8191, 8192, 10238, 10239, 14334, 14335])
 def test_a_call_of_few_super_groups_checks_every_index_itself(dev, at):
-    """Rounds of 8,192 indices per block, fours and the rest of the array; at 10,241 the check is a launch of its own again.  Two arrays: the
-    same one within two tensors of different length, and two."""
+    """Rounds of 8,192 indices per block, fours and the rest of the array; from 10,241 (one array
+    of a decompress: 14,337) on the check is a launch of its own again.  Two arrays: the same one within two tensors of different length, and two."""
     ctx = B.Context(4, seed=1)
-    for n_sg in {at + 1, at + 2, min(at + 5, 10241)}:
+    for n_sg in {at + 1, at + 2, at + 5}:
         ch = B.make_chunk(0, [0, n_sg, 0])
         x = gradients(1, n_sg, torch.bfloat16, dev, n_sg)[0]
         message = ctx.dq_compress(x, ch, 1)
