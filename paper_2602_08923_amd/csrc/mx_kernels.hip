@@ -6,6 +6,8 @@
 //
 // Mapping: one lane owns one block of 32 entries (its maximum is in-lane); a wave64 covers
 // 2048 entries per tile.
+#include <type_traits>
+
 #include "dq_device.h"
 
 namespace dq {
@@ -84,6 +86,15 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x32 __attribute__((ext_vector_type(32)));
+
+// 32 entries (in the order a0 b0 a1 b1 ...) to 6-bit codes.  The instruction works in several passes, and the compiler may give
+// its result the registers of an operand that dies here: with the scale's, later passes met another scale.  So the operands live on
+// behind it.
+__device__ __forceinline__ u32x6 to_bf6(const f32x16 &a, const f32x16 &b, float X) {
+  u32x6 r = __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(a, b, X);
+  asm("" : "+v"(r) : "v"(a), "v"(b), "v"(X));
+  return r;
+}
 
 // A block's code words and scale byte.
 template <int FMT>
@@ -192,7 +203,7 @@ __device__ __forceinline__ MxMsg<FMT> mx_encode(float (&v)[32]) {
     f32x16 a, b;
 #pragma unroll
     for (int k = 0; k < 16; ++k) { a[k] = v[2 * k]; b[k] = v[2 * k + 1]; }  // the two inputs interleave
-    const u32x6 r = __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(a, b, X);
+    const u32x6 r = to_bf6(a, b, X);
 #pragma unroll
     for (int i = 0; i < 6; ++i) out.w[i] = r[i];
   }
@@ -264,7 +275,7 @@ __global__ __launch_bounds__(kBlockThreads) void mx_batch(const MxJob *jobs) {
   mx_run<FMT, KIND, LT>(job);
 }
 
-// A whole replay in one launch, as in dq_walk.hip: a wave carries 64 blocks of a chunk through all hops of the schedule,
+// A whole replay in one launch, as in dq_walk.hip (mx_walk; small and very large ones: mx_quad below): a wave carries 64 blocks of a chunk through all hops of the schedule,
 // the pending message in registers (a recursive halving's higher levels in LDS).  A replay of a ring of 8 over 25 MB: 57 us, 4.6 TB/s,
 // the rate of a large copy on this card; 94 us in eight launches, bound by the messages' way to memory and back and
 // by the launches' fixed parts.  Three waves per SIMD without spills beat four with (57 and 59 us); grids of 3 to 7 blocks
@@ -389,8 +400,276 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3
   }
 }
 
+// The same with four lanes to a block, eight entries each: a tile of 16 blocks per wave, eight leaves requested ahead.
+//
+// Why: with a lane per block and one leaf ahead a replay of few tiles is a chain of trips to memory, 0.55 us (fp32: 0.95) for each worker
+// whatever the size.  Eight entries leave registers for eight leaves (16 or 32 bytes each) on their way, a hop is a quarter as long, and
+// there are four times as many waves.  Measured, us, walk -> this:
+//   MXFP8 bf16, 2,048 super-groups: ring of 8 7.2 -> 4.9, of 64 34.8 -> 14.8; 4,096: 7.7 -> 5.9, 35.5 -> 24.6, of 256 180 -> 97
+//   MXFP8 butterfly of 128 workers, 128 super-groups 73.5 -> 26.4, 4,096 79.8 -> 42.1; fp32, 16 workers, 4,096 18.1 -> 14.3
+//   MXFP4 fp32 chain of 174 workers, 1,823 super-groups 166 -> 54.6 (the reads alone, at the rate of a large copy: 66)
+//   MXFP8 fp32 ring of 8, 131,072 super-groups 256 -> 230; bf16 142 -> 132
+// What bounds it: few tiles, instructions of a hop, one per four cycles and wave; many, memory.
+constexpr uint32_t kQuadBlocks = 16;      // blocks per tile
+constexpr uint32_t kQuadLevel = 12 * 64;  // two code words and the scale per lane
+constexpr int kAhead = 8;                 // leaves on their way
+
+// A lane's eight entries' codes (6-bit ones: in the first 48 bits; 4-bit ones: in the first word) and the block's scale byte.
+struct QuadMsg {
+  uint32_t w[2], e;
+};
+template <int FMT, bool ADD>
+__device__ __forceinline__ void quad_decode(const QuadMsg &m, float (&v)[8]) {
+  constexpr int cw = Fmt<FMT>::cb;
+  const float X = u2f(m.e << 23);
+  float d[8];
+  if constexpr (cw == 8) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const f32x2 lo = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(m.w[i], X, false);
+      const f32x2 hi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(m.w[i], X, true);
+      d[4 * i] = lo.x; d[4 * i + 1] = lo.y; d[4 * i + 2] = hi.x; d[4 * i + 3] = hi.y;
+    }
+  } else if constexpr (cw == 4) {
+    const f32x2 b0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(m.w[0], X, 0);
+    const f32x2 b1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(m.w[0], X, 1);
+    const f32x2 b2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(m.w[0], X, 2);
+    const f32x2 b3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(m.w[0], X, 3);
+    d[0] = b0.x; d[1] = b0.y; d[2] = b1.x; d[3] = b1.y; d[4] = b2.x; d[5] = b2.y; d[6] = b3.x; d[7] = b3.y;
+  } else {  // the conversion takes 32 entries: a quarter of what it returns is used
+    const f32x32 all = __builtin_amdgcn_cvt_scalef32_pk32_f32_bf6(u32x6{m.w[0], m.w[1], 0u, 0u, 0u, 0u}, X);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) d[k] = all[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) v[k] = ADD ? d[k] + v[k] : d[k];
+}
+// The maximum of a block with a NaN among what the workers gave, as mx_encode finds it: the hardware's maximum turns a signalling NaN into a
+// quiet one, so that only what comes behind it counts, and the order of all 32 entries does.  (A sum is never signalling.)
+template <int CTRL>
+__device__ __forceinline__ void quad_lane(const float (&v)[8], float *all) {  // the eight entries of one of the four lanes
+#pragma unroll
+  for (int k = 0; k < 8; ++k) all[k] = u2f((uint32_t)__builtin_amdgcn_mov_dpp((int)f2u(v[k]), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ uint32_t quad_nan_max(const float (&v)[8]) {
+  float all[32], m = 0.0f;
+  quad_lane<0x00>(v, all);
+  quad_lane<0x55>(v, all + 8);
+  quad_lane<0xAA>(v, all + 16);
+  quad_lane<0xFF>(v, all + 24);
+#pragma unroll
+  for (int k = 0; k < 32; ++k) m = fmaxf(m, fabsf(all[k]));
+  return f2u(m);
+}
+// given: v may be what a worker gave, not a sum
+template <int FMT>
+__device__ __forceinline__ QuadMsg quad_encode(float (&v)[8], bool given) {
+  using F = Fmt<FMT>;
+  constexpr int cw = F::cb;
+  QuadMsg out;
+  float m = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) m = fmaxf(m, fabsf(v[k]));
+  // bit patterns of values without a sign order as they do, and NaN is gone: the block's maximum over its four lanes
+  uint32_t b = f2u(m);
+  b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0xB1, 0xF, 0xF, true));  // quad_perm [1, 0, 3, 2]
+  b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x4E, 0xF, 0xF, true));  // quad_perm [2, 3, 0, 1]
+  if (given) {
+    const float sum = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    if (__builtin_amdgcn_ballot_w64(sum != sum)) b = quad_nan_max(v);
+  }
+  int e = (int)(b >> 23) - F::emax;
+  e = e < 0 ? 0 : (e > 254 ? 254 : e);
+  const float X = u2f((uint32_t)e << 23);
+  out.w[1] = 0;
+  if constexpr (cw == 8) {
+    const float top = 448.0f * X;  // saturated before the conversion, as in mx_encode
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = __builtin_amdgcn_fmed3f(v[k], -top, top);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      s16x2 r = {0, 0};
+      r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, v[4 * i], v[4 * i + 1], X, false);
+      r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, v[4 * i + 2], v[4 * i + 3], X, true);
+      out.w[i] = __builtin_bit_cast(uint32_t, r);
+    }
+  } else if constexpr (cw == 4) {
+    uint32_t r = 0;
+    r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[0], v[1], X, 0);
+    r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[2], v[3], X, 1);
+    r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[4], v[5], X, 2);
+    r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[6], v[7], X, 3);
+    out.w[0] = r;
+  } else {
+    f32x16 a, c;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) { a[k] = v[2 * (k & 3)]; c[k] = v[2 * (k & 3) + 1]; }  // 32 entries: ours four times
+    const u32x6 r = to_bf6(a, c, X);
+    out.w[0] = r[0];
+    out.w[1] = r[1] & 0xFFFFu;
+  }
+  out.e = (uint32_t)e;
+  return out;
+}
+// lane: of the block, 0 to 3
+template <int FMT>
+__device__ __forceinline__ void quad_store(uint8_t *packed, uint64_t n_blocks, uint64_t bl, uint32_t lane, const QuadMsg &m) {
+  constexpr int cw = Fmt<FMT>::cb;
+  uint8_t *dst = packed + (size_t)bl * (cw * 4) + lane * cw;
+  if constexpr (cw == 8) {
+    gst<u32x2>(dst, u32x2{m.w[0], m.w[1]});
+  } else if constexpr (cw == 4) {
+    gst<uint32_t>(dst, m.w[0]);
+  } else {  // six bytes at an even address
+    gst<uint16_t>(dst, (uint16_t)m.w[0]);
+    gst<uint16_t>(dst + 2, (uint16_t)(m.w[0] >> 16));
+    gst<uint16_t>(dst + 4, (uint16_t)m.w[1]);
+  }
+  if (lane == 0) gst<uint8_t>(packed + (size_t)n_blocks * (cw * 4) + bl, (uint8_t)m.e);
+}
+template <typename LT>
+struct QuadSlice {
+  u32x4 w[sizeof(LT) == 4 ? 2 : 1];
+};
+template <typename LT>
+__device__ __forceinline__ QuadSlice<LT> quad_slice(uint64_t tensor, uint64_t at) {
+  const uint8_t *p = reinterpret_cast<const uint8_t *>(tensor) + at;
+  QuadSlice<LT> s;
+#pragma unroll
+  for (int i = 0; i < (sizeof(LT) == 4 ? 2 : 1); ++i) s.w[i] = gld<u32x4>(p + 16 * i);
+  return s;
+}
+template <typename LT>
+__device__ __forceinline__ void quad_widen(const QuadSlice<LT> &s, float (&v)[8]) {
+  if constexpr (sizeof(LT) == 4) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      v[4 * i] = u2f(s.w[i].x); v[4 * i + 1] = u2f(s.w[i].y); v[4 * i + 2] = u2f(s.w[i].z); v[4 * i + 3] = u2f(s.w[i].w);
+    }
+  } else {
+    const uint32_t w[4] = {s.w[0].x, s.w[0].y, s.w[0].z, s.w[0].w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[2 * j] = u2f(w[j] << 16);
+      v[2 * j + 1] = u2f(w[j] & 0xFFFF0000u);
+    }
+  }
+}
+
+template <int FMT, typename LT, bool TREE>
+__global__ __launch_bounds__(kBlockThreads) void mx_quad(MxWalk W) {
+  extern __shared__ float4 mx_lds[];
+  const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  [[maybe_unused]] const uint32_t area = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float4 *)mx_lds + wave * W.wave_bytes;
+  typedef __attribute__((address_space(3))) uint32_t lds_u32;
+  const uint32_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * kBlockWaves + wave), last = W.n - 1, leaves = W.n;
+  if (t >= W.n_tiles) return;
+  const uint32_t path = t / W.tiles_per_path, chunk = path % W.n_chunks;
+  const uint64_t bi = (uint64_t)(t - path * W.tiles_per_path) * kQuadBlocks + (lane >> 2);
+  const uint64_t bl = min(bi, W.chunk_blocks - 1);  // lanes past the end redo the last block
+  const uint64_t entry = ((uint64_t)path * W.chunk_blocks + bl) * 32 + (lane & 3u) * 8, at = entry * sizeof(LT);
+  typedef __attribute__((address_space(4))) const uint64_t constant_u64;  // scalar loads: nothing here writes the table
+  auto tensor = [&](uint32_t i) { return ((constant_u64 *)(uintptr_t)W.grads)[mx_leaf<TREE>(W, chunk, i)]; };
+  // Behind the last leaf all lanes read the last tensor's first words, which costs next to nothing: with every request made, the wait for a
+  // leaf leaves those behind it on their way.
+  auto request = [&](uint64_t tensor, uint32_t i) { return quad_slice<LT>(tensor, i < leaves ? at : 0); };
+  QuadSlice<LT> s[kAhead];
+  uint64_t p[kAhead];
+#pragma unroll
+  for (uint32_t k = 0; k < kAhead; ++k) p[k] = tensor(min(k, last));
+#pragma unroll
+  for (uint32_t k = 0; k < kAhead; ++k) s[k] = request(p[k], k);
+  float v[8];
+  QuadMsg m;
+  // leaf i0 + k; false: it was the last
+  auto hop = [&](uint32_t i0, uint32_t k, QuadSlice<LT> &mine, auto refill, auto may_end) {
+    const uint32_t i = i0 + k;
+    quad_widen<LT>(mine, v);
+    refill();
+    if (TREE ? (i & 1u) : i > 0) quad_decode<FMT, true>(m, v);
+    [[maybe_unused]] uint32_t stack = area;
+    if constexpr (TREE) {
+      if (i & 1u) {
+#pragma unroll 1
+        for (uint32_t q = i >> 1; q & 1u; q >>= 1, stack += kQuadLevel) {
+          QuadMsg x;
+          x.w[0] = *reinterpret_cast<lds_u32 *>(stack + lane * 4);
+          x.w[1] = *reinterpret_cast<lds_u32 *>(stack + 256 + lane * 4);
+          x.e = *reinterpret_cast<lds_u32 *>(stack + 512 + lane * 4);
+          quad_decode<FMT, true>(x, v);
+        }
+      }
+    }
+    if (may_end && i == W.encodes) return false;
+    m = quad_encode<FMT>(v, TREE ? !(k & 1u) : k == 0 && i0 == 0);
+    if (may_end && i == last) {  // all-gather: what every worker decodes from the sink's message
+      quad_decode<FMT, false>(m, v);
+      return false;
+    }
+    if constexpr (TREE) {
+      if (i & 1u) {
+        *reinterpret_cast<lds_u32 *>(stack + lane * 4) = m.w[0];
+        *reinterpret_cast<lds_u32 *>(stack + 256 + lane * 4) = m.w[1];
+        *reinterpret_cast<lds_u32 *>(stack + 512 + lane * 4) = m.e;
+      }
+    } else if (i >= W.first_kept) {
+      quad_store<FMT>(W.msg[i & 1u] + (size_t)path * W.msg_stride, W.chunk_blocks, bl, lane & 3u, m);
+    }
+    return true;
+  };
+  uint32_t i0 = 0;
+#pragma unroll 1
+  for (; i0 + 2 * kAhead <= leaves; i0 += kAhead) {  // eight leaves with eight or more behind them
+#pragma unroll
+    for (uint32_t k = 0; k < kAhead; ++k) p[k] = tensor(i0 + kAhead + k);
+#pragma unroll
+    for (uint32_t k = 0; k < kAhead; ++k) hop(i0, k, s[k], [&] { s[k] = quad_slice<LT>(p[k], at); }, std::false_type{});
+  }
+#pragma unroll 1
+  for (;; i0 += kAhead) {
+#pragma unroll
+    for (uint32_t k = 0; k < kAhead; ++k) p[k] = tensor(min(i0 + kAhead + k, last));
+#pragma unroll
+    for (uint32_t k = 0; k < kAhead; ++k)
+      if (!hop(i0, k, s[k], [&] { s[k] = request(p[k], i0 + kAhead + k); }, std::true_type{})) goto done;
+  }
+done:
+  if (bi < W.chunk_blocks) {
+    float *o = W.out + entry;
+    gst<f32x4>(o, f32x4{v[0], v[1], v[2], v[3]});
+    gst<f32x4>(o + 4, f32x4{v[4], v[5], v[6], v[7]});
+  }
+}
+
+// Tiles per CU (half a super-group each at 256 CUs: 4,096 super-groups are 8) between which the walk is faster.  Below: its waves have a
+// SIMD to themselves; 6-bit codes, whose conversions take 32 entries whether there are or not, meet at 9 (4,096 super-groups, ring of 64:
+// 25.2 against 31.4; 5,120: 33.9 against 32), others at 13 to 15 (bf16; 6,144: 33.5 against 36; 8,192: 50 against 43) and 11 (fp32; 5,120:
+// 60.5 against 75.6, ring of 8 10.7 against 11.6; 6,144: 12 against 11.9); two or three workers, who leave most of the eight requests
+// idle, at 5 (bf16; 2,048: 3.5 against 3.9; 3,072: 4.05 against 4.1) and 9 (fp32; 4,096: 4.7 against 5.2; 5,120: 6.2 against 5.4).  Above,
+// from 8 workers on: more requests are on their way than one leaf of each wave (fp32, from 64: 65,536, ring of 8 117 against 129, of 16
+// 221 against 236; bf16 rings and chains, from 256: 132 against 142 of 8, 848 against 880 of 64; butterflies of 128 lose, 430 against 401).
+template <int FMT, typename LT, bool TREE>
+bool takes_quad(uint32_t n, uint64_t tiles, uint32_t n_cu) {
+  constexpr bool six = FMT == DQ_MXFP6_E3M2, wide = sizeof(LT) == 4;
+  if (tiles >= 1u << 25) return false;  // threads of a launch: below 2^31
+  const uint64_t few = n < 4 ? (wide ? 8 : 4) : six ? 8 : wide ? 10 : 12;
+  return tiles <= few * n_cu || (!six && n >= 8 && (wide || !TREE) && tiles >= (wide ? 64ull : 256ull) * n_cu);
+}
+
+template <int FMT, typename LT, bool TREE>
+hipError_t go_mx_quad(MxWalk W, uint32_t n_paths, hipStream_t s) {
+  W.tiles_per_path = (uint32_t)((W.chunk_blocks + kQuadBlocks - 1) / kQuadBlocks);
+  W.n_tiles = n_paths * W.tiles_per_path;
+  W.wave_bytes = TREE && W.log_n > 1 ? (W.log_n - 1) * kQuadLevel : 0;
+  const uint32_t blocks = (W.n_tiles + kBlockWaves - 1) / kBlockWaves;
+  hipLaunchKernelGGL((mx_quad<FMT, LT, TREE>), dim3(blocks), dim3(kBlockThreads), W.wave_bytes * kBlockWaves, s, W);
+  return hipGetLastError();
+}
+
 template <int FMT, typename LT, bool TREE>
 hipError_t go_mx_walk(MxWalk W, uint32_t n_cu, hipStream_t s) {
+  const uint32_t n_paths = W.n_tiles / W.tiles_per_path;
+  if (takes_quad<FMT, LT, TREE>(W.n, n_paths * ((W.chunk_blocks + kQuadBlocks - 1) / kQuadBlocks), n_cu)) return go_mx_quad<FMT, LT, TREE>(W, n_paths, s);
   const uint32_t levels = TREE && W.log_n > 1 ? W.log_n - 1 : 0;
   W.wave_bytes = levels * kMxStackLevel > kMxXpose ? levels * kMxStackLevel : kMxXpose;
   const uint32_t lds = W.wave_bytes * kBlockWaves;

@@ -127,11 +127,38 @@ def test_whole_replay_on_original_tensors_over_the_whole_grid(dev, topology, J):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("topology,n,J,nb,all_gather", [("ring", 2, 2, 1, False), ("ring", 5, 45, 2, True), ("chain", 7, 9, 1, False),
                                                         ("chain", 3, 8, 1, True), ("butterfly", 2, 2, 3, True),
-                                                        ("butterfly", 16, 16 * 9, 2, False), ("ring", 4, 36000, 1, False)])
+                                                        ("butterfly", 16, 16 * 9, 2, False), ("ring", 4, 36000, 1, False),
+                                                        # groups of eight leaves; both sides of the sizes at which the split changes
+                                                        ("ring", 8, 24, 1, False), ("ring", 15, 45, 1, True), ("chain", 16, 7, 1, False),
+                                                        ("ring", 17, 17, 1, False), ("chain", 24, 3, 1, True), ("butterfly", 32, 96, 1, True),
+                                                        ("chain", 3, 4096, 1, False), ("chain", 2, 5121, 1, False), ("ring", 4, 6144, 1, False),
+                                                        ("ring", 4, 6148, 1, False), ("ring", 8, 32768, 1, False), ("butterfly", 8, 32760, 1, False),
+                                                        ("ring", 8, 131072, 1, False)])
 def test_whole_mx_replay_equals_its_steps(dev, fmt, dtype, topology, n, J, nb, all_gather):
     grads = gradients(n, J * nb, dtype, dev, J + n)
     rp = B.Replay(B.Context(n), TOPO[topology], fmt, grads, J, n_buckets=nb, all_gather=all_gather)
     whole_against_steps(rp, {"ring": n, "chain": 1, "butterfly": 0}[topology])
+
+
+@pytest.mark.parametrize("fmt", [B.DQ_MXFP8_E4M3, B.DQ_MXFP6_E3M2, B.DQ_MXFP4_E2M1])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("topology,n,J", [("ring", 5, 45), ("ring", 17, 17), ("butterfly", 16, 48)])
+def test_whole_mx_replay_of_any_pattern_equals_its_steps(dev, fmt, dtype, topology, n, J):
+    """Infinities, quiet and signalling NaN, denormals: every bit pattern may come from a worker."""
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n)
+    word = torch.int32 if dtype == torch.float32 else torch.int16
+    info = torch.iinfo(word)
+    grads = [torch.randint(info.min, info.max, (J * 256,), dtype=word, device=dev, generator=gen).view(dtype) for _ in range(n)]
+    rp = B.Replay(B.Context(n), TOPO[topology], fmt, grads, J)
+    for t in range(rp.n_steps):
+        rp.run_steps(t, 1)
+    torch.cuda.synchronize()
+    want = rp.out.clone()
+    rp.run()
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isnan(rp.out), torch.isnan(want))
+    assert torch.equal(torch.nan_to_num(rp.out, nan=7.0).view(torch.int32), torch.nan_to_num(want, nan=7.0).view(torch.int32))
 
 
 @pytest.mark.parametrize("at", [0, 3, 4, 4095, 8190, 8191, 8192, 10238, 10239, 14334, 14335])
