@@ -641,19 +641,34 @@ done:
   }
 }
 
-// Tiles per CU (half a super-group each at 256 CUs: 4,096 super-groups are 8) between which the walk is faster.  Below: its waves have a
-// SIMD to themselves; 6-bit codes, whose conversions take 32 entries whether there are or not, meet at 9 (4,096 super-groups, ring of 64:
-// 25.2 against 31.4; 5,120: 33.9 against 32), others at 13 to 15 (bf16; 6,144: 33.5 against 36; 8,192: 50 against 43) and 11 (fp32; 5,120:
-// 60.5 against 75.6, ring of 8 10.7 against 11.6; 6,144: 12 against 11.9); two or three workers, who leave most of the eight requests
-// idle, at 5 (bf16; 2,048: 3.5 against 3.9; 3,072: 4.05 against 4.1) and 9 (fp32; 4,096: 4.7 against 5.2; 5,120: 6.2 against 5.4).  Above,
-// from 8 workers on: more requests are on their way than one leaf of each wave (fp32, from 64: 65,536, ring of 8 117 against 129, of 16
-// 221 against 236; bf16 rings and chains, from 256: 132 against 142 of 8, 848 against 880 of 64; butterflies of 128 lose, 430 against 401).
+// By tiles per CU (4,096 super-groups are 8 at 256 CUs; a block of the walk does the work of 16).
+// Few: the walk's waves have a SIMD to themselves.  6-bit codes, whose conversions take 32 entries whether there are or not, meet at 9
+// (4,096 super-groups, ring of 64: 25.2 us against the walk's 31.4; 5,120: 33.9 against 32), others at 13 to 15 (bf16; 6,144: 33.5 against
+// 36; 8,192: 50 against 43) and 11 (fp32; 5,120: 60.5 against 75.6, ring of 8 10.7 against 11.6; 6,144: 12 against 11.9); two or three
+// workers, who leave most of the eight requests idle, at 5 (bf16; 2,048: 3.5 against 3.9; 3,072: 4.05 against 4.1) and 9 (fp32; 4,096: 4.7
+// against 5.2; 5,120: 6.2 against 5.4).
+// Above 16, 32, 48: some CUs have a block of the walk more than others, and everyone waits for them.  fp32, us against the walk's: ring of
+// 64, 8,320: 109 against 191, 12,288: 150 against 193; of 16, 18,432: 60 against 76, 14,336: 42 against 40.4; of 8, 9,216: 17.8 against 22.9,
+// 12,288: 22 against 23, 14,336: 25.1 against 23.7, 17,408: 29 against 32, 20,480: 33 against 33.1, 24,576: 39.5 against 37, 28,672: 47.8
+// against 51.5; of 4, 10,240: 13.1 against 14, 12,288: 15.3 against 14.8; butterfly of 16, 9,216: 26.4 against 40; 6-bit ring of 8, 9,216:
+// 18.3 against 20.3, 12,288: 22.4 against 20.8.  bf16, ring of 64, 9,216: 56 against 61, 12,288: 82 against 77; of 8, 11.4 against 11.2.
+// Many: more requests are on their way than one worker's of each wave (fp32: 65,536, ring of 8 117 against 129, of 16 221
+// against 236, butterfly of 128 over 32,768 766 against 826; bf16 rings and chains from 256 on: 132 against 142 of 8, 848 against 880 of 64;
+// butterflies of 128 lose, 430 against 401).
 template <int FMT, typename LT, bool TREE>
 bool takes_quad(uint32_t n, uint64_t tiles, uint32_t n_cu) {
   constexpr bool six = FMT == DQ_MXFP6_E3M2, wide = sizeof(LT) == 4;
   if (tiles >= 1u << 25) return false;  // threads of a launch: below 2^31
   const uint64_t few = n < 4 ? (wide ? 8 : 4) : six ? 8 : wide ? 10 : 12;
-  return tiles <= few * n_cu || (!six && n >= 8 && (wide || !TREE) && tiles >= (wide ? 64ull : 256ull) * n_cu);
+  if (tiles <= few * n_cu) return true;
+  if (tiles <= 16ull * n_cu) return false;
+  if (six) return wide && n >= 8 && tiles <= 20ull * n_cu;
+  if (wide) {
+    const auto within = [&](uint64_t lo, uint64_t hi) { return tiles > lo * n_cu && tiles <= hi * n_cu; };
+    if (n < 8) return n >= 4 && within(16, 20);
+    return n >= 64 || within(16, 24) || (tiles > 32ull * n_cu && (n >= 16 || !within(40, 48)));
+  }
+  return (n >= 64 && tiles <= 18ull * n_cu) || (!TREE && n >= 8 && tiles >= 256ull * n_cu);
 }
 
 template <int FMT, typename LT, bool TREE>
