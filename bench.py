@@ -36,8 +36,8 @@ sys.path.insert(0, ROOT)
 #            bytes on the same box: FETCH_SIZE counts half the bytes read (x2.0), WRITE_SIZE all (x1.0).
 #   valu:    vector-ALU wave instructions per launch (SQ_INSTS_VALU); one is 64 lane operations.
 MEASURED = {
-    (2, 0): {"replay": {"traffic": int((129761.4 * 2.0 + 99916.1 * 1.0) * 1024), "valu": 32_672_069},
-             "dar_hop": {"traffic": int((16476.8 * 2.0 + 6203.2 * 1.0) * 1024), "valu": 5_331_100},
+    (2, 0): {"replay": {"traffic": int((103082.4 * 2.0 + 64129.2 * 1.0) * 1024), "valu": 32_276_505},
+             "dar_hop": {"traffic": int((16459.2 * 2.0 + 6203.2 * 1.0) * 1024), "valu": 5_248_210},
              "profile": "profiles/cfg2_pmc.txt"},
 }
 # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz: lane operations per second the vector ALUs can issue

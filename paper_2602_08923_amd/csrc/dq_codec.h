@@ -403,9 +403,8 @@ __device__ __forceinline__ Scales scale_group(const float (&v)[16], float us, ui
 
 // Launch constants that vector instructions use once per entry, held in vector registers.  On this chip an
 // instruction of the simple kind (mul, add, and/or/xor, right shift; fma nearly) whose operands are all vector registers
-// or constants issues in little more than half the time of any other, and beside one of the other kind; with a
-// scalar-register operand it is of the other kind itself.  (1.0 ns per wave instruction against 1.7, measured with eight waves
-// per SIMD; a comparison and an fma together 2.1: profiles/valu_issue.txt.)
+// or constants issues in little more than half the time of any other; with a scalar-register operand it is of the other
+// kind itself.  (1.0 ns per wave instruction against 1.7, measured with eight waves per SIMD: profiles/valu_issue.txt.)
 struct Vec {
   float magic4, magic8, s_n;
   uint32_t top;  // the sign bit
