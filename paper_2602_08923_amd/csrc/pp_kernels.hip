@@ -803,6 +803,9 @@ uint32_t stream_blocks(uint64_t units_per_block_round, uint64_t units, uint32_t 
   return (uint32_t)(need < 1 ? 1 : (need < cap ? need : cap));
 }
 
+// A launch has fewer than 2^32 threads.
+constexpr uint32_t kMostBlocks = 0xFFFFFFFFu / kThreads;
+
 dq_status launched() { return dq::hip_status(hipGetLastError()); }
 
 }  // namespace
@@ -813,12 +816,19 @@ dq_status dq_sg_stats(const void *x, dq_dtype dtype, uint64_t n_sg, float *mu_ou
   if (n_sg == 0) return DQ_OK;
   if (!x || !mu_out || !F_out || (dtype != DQ_F32 && dtype != DQ_BF16)) return DQ_EINVAL;
   if (!aligned(x, 16) || !aligned(mu_out, 4) || !aligned(F_out, 4)) return DQ_EALIGN;
-  const uint64_t blocks = (n_sg + 4 * (kThreads / 64) - 1) / (4 * (kThreads / 64));
-  if (blocks > 0x7FFFFFFFull) return DQ_EUNSUPPORTED;
   hipStream_t s = (hipStream_t)hip_stream;
-  if (dtype == DQ_F32) hipLaunchKernelGGL(k_stats<float>, dim3((uint32_t)blocks), dim3(kThreads), 0, s, x, n_sg, mu_out, F_out);
-  else hipLaunchKernelGGL(k_stats<uint16_t>, dim3((uint32_t)blocks), dim3(kThreads), 0, s, x, n_sg, mu_out, F_out);
-  return launched();
+  constexpr uint32_t kPerBlock = 4 * (kThreads / 64);
+  constexpr uint64_t kMost = (uint64_t)kMostBlocks * kPerBlock;  // from 2^28 super-groups on, 137 GB in bf16, several launches
+  for (uint64_t first = 0; first < n_sg; first += kMost) {
+    const uint64_t n = n_sg - first < kMost ? n_sg - first : kMost;
+    const void *from = static_cast<const uint8_t *>(x) + first * kSG * (dtype == DQ_F32 ? 4 : 2);
+    const dim3 grid((uint32_t)((n + kPerBlock - 1) / kPerBlock));
+    if (dtype == DQ_F32) hipLaunchKernelGGL(k_stats<float>, grid, dim3(kThreads), 0, s, from, n, mu_out + first, F_out + first);
+    else hipLaunchKernelGGL(k_stats<uint16_t>, grid, dim3(kThreads), 0, s, from, n, mu_out + first, F_out + first);
+    const dq_status st = launched();
+    if (st != DQ_OK) return st;
+  }
+  return DQ_OK;
 }
 
 dq_status dq_stats_combine(const float *mu_all, const float *F_all, uint32_t n_workers, uint64_t n_sg, float *mu,
