@@ -859,17 +859,6 @@ dq_status dqx_stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype
   return launched();
 }
 
-// k_alloc_positions over all buckets, 65,535 (the grid's second dimension) per launch
-static void launch_positions(const float *F, uint32_t J, uint32_t n_buckets, bool allow16, const uint32_t *counts,
-                             uint8_t *widths, uint32_t *pos, hipStream_t s) {
-  for (uint32_t b0 = 0; b0 < n_buckets; b0 += 65535u) {
-    const uint32_t nb = n_buckets - b0 < 65535u ? n_buckets - b0 : 65535u;
-    const uint64_t off = (uint64_t)b0 * J;
-    hipLaunchKernelGGL(k_alloc_positions, dim3((J + kAllocThreads - 1) / kAllocThreads, nb), dim3(kAllocThreads), 0, s,
-                       F + off, J, allow16, counts + 5ull * b0, widths + off, pos + off);
-  }
-}
-
 static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits,
                           uint32_t max_width, uint8_t *widths, uint32_t *pos, uint32_t *counts, dq::Announce announce, void *hip_stream) {
   if (n_sg_per_bucket == 0 || n_buckets == 0) return DQ_OK;
@@ -879,13 +868,21 @@ static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_b
   hipStream_t s = (hipStream_t)hip_stream;
   const bool allow16 = max_width == 16;
   const uint32_t J = n_sg_per_bucket, rows = (J + kAllocThreads - 1) / kAllocThreads;
-  if (rows <= (uint32_t)kRegs) {
-    if (allow16) hipLaunchKernelGGL(k_search<true>, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, pos, counts, announce);
-    else hipLaunchKernelGGL(k_search<false>, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, pos, counts, announce);
-    launch_positions(F, J, n_buckets, allow16, counts, widths, pos, s);
-  } else
-    hipLaunchKernelGGL(k_allocate_large, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, allow16, widths, pos, counts);
-  return launched();
+  for (uint32_t b0 = 0; b0 < n_buckets;) {  // the grid's second dimension holds 65,535; the counts are announced of fewer only
+    const uint32_t nb = n_buckets - b0 < 65535u ? n_buckets - b0 : 65535u;
+    const uint64_t off = (uint64_t)b0 * J;
+    uint32_t *const cnt = counts + 5ull * b0;
+    if (rows <= (uint32_t)kRegs) {
+      if (allow16) hipLaunchKernelGGL(k_search<true>, dim3(nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, pos + off, cnt, announce);
+      else hipLaunchKernelGGL(k_search<false>, dim3(nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, pos + off, cnt, announce);
+      hipLaunchKernelGGL(k_alloc_positions, dim3(rows, nb), dim3(kAllocThreads), 0, s, F + off, J, allow16, cnt, widths + off, pos + off);
+    } else
+      hipLaunchKernelGGL(k_allocate_large, dim3(nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, allow16, widths + off, pos + off, cnt);
+    const dq_status st = launched();
+    if (st != DQ_OK) return st;
+    b0 += nb;
+  }
+  return DQ_OK;
 }
 
 dq_status dq_allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits,

@@ -6,11 +6,12 @@
 typedef struct { uint32_t x, y, z; } dim3_t;
 typedef struct {
   uint32_t grid[3], block[3];
-  uint64_t args[4]; /* the first four, taken as 8 bytes each */
+  uint64_t args[4]; /* the first args_taken, as 8 bytes each */
 } launch_t;
 
 static launch_t launches[4096];
 static int n_launches, failed;
+int args_taken = 0; /* of a launch, at most four: the kernels have as many */
 static struct { dim3_t grid, block; size_t shared; void *stream; } pushed;
 
 int recorded(launch_t *out, int most) {
@@ -35,7 +36,7 @@ int hipLaunchKernel(const void *kernel, dim3_t grid, dim3_t block, void **args, 
     launch_t *l = &launches[n_launches++];
     l->grid[0] = grid.x; l->grid[1] = grid.y; l->grid[2] = grid.z;
     l->block[0] = block.x; l->block[1] = block.y; l->block[2] = block.z;
-    for (int i = 0; i < 4; ++i) memcpy(&l->args[i], args[i], 8);
+    for (int i = 0; i < args_taken; ++i) memcpy(&l->args[i], args[i], 8);
   }
   return 0;
 }

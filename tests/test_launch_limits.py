@@ -19,7 +19,7 @@ def recorder(tmp_path_factory):
     return so
 
 
-def run(recorder, body):
+def run(recorder, body, args):
     """`body` in an interpreter of its own, whose library finds the recorder's launches ahead of the runtime's."""
     head = f"""
         import ctypes as C
@@ -27,7 +27,8 @@ def run(recorder, body):
             _fields_ = [("grid", C.c_uint32 * 3), ("block", C.c_uint32 * 3), ("args", C.c_uint64 * 4)]
         R = C.CDLL({recorder!r}, mode=C.RTLD_GLOBAL)
         L = C.CDLL({B.LIB_PATH!r})
-        P, U = C.c_void_p, C.c_uint64
+        P, U, W = C.c_void_p, C.c_uint64, C.c_uint32
+        C.c_int.in_dll(R, "args_taken").value = {args}
         def launches():
             a = (Launch * 4096)()
             return a[:R.recorded(a, 4096)]
@@ -51,4 +52,29 @@ def test_statistics_of_any_size(recorder, n, dtype, size):
             assert list(l.block) == [256, 1, 1] and list(l.grid) == [(count + 15) // 16, 1, 1]
             at += count
         assert at == {n}
-    """)
+    """, 4)
+
+
+# A search has 1,024 threads to a bucket: 2^22 buckets are 2^32 threads.  Buckets above 65,536 super-groups take another kernel.
+@pytest.mark.parametrize("J,n", [(1, 1), (1, 65535), (1, 65536), (5, 2 ** 22 - 1), (5, 2 ** 22), (1025, 2 ** 22 + 7), (65537, 65537)])
+@pytest.mark.parametrize("width", [8, 16])
+def test_allocation_of_any_number_of_buckets(recorder, J, n, width):
+    run(recorder, f"""
+        J, F, widths, pos, counts = {J}, 1 << 40, 1 << 50, 1 << 52, 1 << 54
+        L.dq_allocate.argtypes = [P, W, W, U, W, P, P, P, P]
+        assert L.dq_allocate(F, J, {n}, 4 * J, {width}, widths, pos, counts, None) == 0
+        at = 0
+        for l in launches():
+            assert list(l.block) == [1024, 1, 1] and l.args[0] == F + 4 * J * at and l.args[1] & 0xFFFFFFFF == J
+            positions = J <= 65536 and l.args[3] == counts + 20 * at
+            if positions:                                            # behind the search of the same buckets
+                assert list(l.grid) == [(J + 1023) // 1024, searched, 1]
+            else:
+                assert l.args[2] == 4 * J and list(l.grid)[1:] == [1, 1]
+                if J <= 65536:
+                    assert l.args[3] == pos + 4 * J * at
+                searched = l.grid[0]
+            if positions or J > 65536:
+                at += searched
+        assert at == {n}
+    """, 4)
