@@ -144,9 +144,9 @@ __global__ void __launch_bounds__(kThreads) k_stats_all(WorkerTensors W, uint32_
 // order in fp32; the mean of the means by one division.  A thread per super-group, eight workers' numbers requested at a time: what
 // bounds it are the trips to memory (8 workers, 51,200 super-groups: 3.2 us with one, 4.8 with one per worker).
 __global__ void __launch_bounds__(kThreads) k_combine(const float *mu_all, const float *F_all, uint32_t n, uint64_t J,
-                                                      float *mu, float *F) {
+                                                      uint64_t count, float *mu, float *F) {
   const uint64_t j = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (j >= J) return;
+  if (j >= count) return;  // of a worker's J
   float sm = 0.0f, sf = 0.0f;
   for (uint32_t i = 0; i < n; i += 8) {
     float m[8], f[8];
@@ -836,10 +836,15 @@ dq_status dq_stats_combine(const float *mu_all, const float *F_all, uint32_t n_w
   if (n_sg == 0) return DQ_OK;
   if (!mu_all || !F_all || !mu || !F || n_workers == 0) return DQ_EINVAL;
   if (!aligned(mu_all, 4) || !aligned(F_all, 4) || !aligned(mu, 4) || !aligned(F, 4)) return DQ_EALIGN;
-  if ((n_sg + kThreads - 1) / kThreads > 0x7FFFFFFFull) return DQ_EUNSUPPORTED;
-  hipLaunchKernelGGL(k_combine, dim3((uint32_t)((n_sg + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                     (hipStream_t)hip_stream, mu_all, F_all, n_workers, n_sg, mu, F);
-  return launched();
+  constexpr uint64_t kMost = (uint64_t)kMostBlocks * kThreads;
+  for (uint64_t first = 0; first < n_sg; first += kMost) {
+    const uint64_t count = n_sg - first < kMost ? n_sg - first : kMost;
+    hipLaunchKernelGGL(k_combine, dim3((uint32_t)((count + kThreads - 1) / kThreads)), dim3(kThreads), 0, (hipStream_t)hip_stream,
+                       mu_all + first, F_all + first, n_workers, n_sg, count, mu + first, F + first);
+    const dq_status st = launched();
+    if (st != DQ_OK) return st;
+  }
+  return DQ_OK;
 }
 
 dq_status dqx_stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dtype, uint64_t n_sg, float *mu, float *F,

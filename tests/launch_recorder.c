@@ -6,12 +6,12 @@
 typedef struct { uint32_t x, y, z; } dim3_t;
 typedef struct {
   uint32_t grid[3], block[3];
-  uint64_t args[4]; /* the first args_taken, as 8 bytes each */
+  uint64_t args[8]; /* the first args_taken, as 8 bytes each */
 } launch_t;
 
 static launch_t launches[4096];
 static int n_launches, failed;
-int args_taken = 0; /* of a launch, at most four: the kernels have as many */
+int args_taken = 0; /* of a launch, at most eight: the kernels have as many */
 static struct { dim3_t grid, block; size_t shared; void *stream; } pushed;
 
 int recorded(launch_t *out, int most) {

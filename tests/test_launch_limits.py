@@ -24,7 +24,7 @@ def run(recorder, body, args):
     head = f"""
         import ctypes as C
         class Launch(C.Structure):
-            _fields_ = [("grid", C.c_uint32 * 3), ("block", C.c_uint32 * 3), ("args", C.c_uint64 * 4)]
+            _fields_ = [("grid", C.c_uint32 * 3), ("block", C.c_uint32 * 3), ("args", C.c_uint64 * 8)]
         R = C.CDLL({recorder!r}, mode=C.RTLD_GLOBAL)
         L = C.CDLL({B.LIB_PATH!r})
         P, U, W = C.c_void_p, C.c_uint64, C.c_uint32
@@ -48,7 +48,7 @@ def test_statistics_of_any_size(recorder, n, dtype, size):
         at = 0
         for l in launches():
             count = l.args[1]
-            assert list(l.args) == [x + at * 256 * {size}, count, mu + 4 * at, F + 4 * at]
+            assert l.args[:4] == [x + at * 256 * {size}, count, mu + 4 * at, F + 4 * at]
             assert list(l.block) == [256, 1, 1] and list(l.grid) == [(count + 15) // 16, 1, 1]
             at += count
         assert at == {n}
@@ -78,3 +78,21 @@ def test_allocation_of_any_number_of_buckets(recorder, J, n, width):
                 at += searched
         assert at == {n}
     """, 4)
+
+
+# A thread per super-group.
+@pytest.mark.parametrize("n", [1, 256, 257, 2 ** 32 - 257, 2 ** 32 - 256, 2 ** 32 - 255, 2 ** 32, 2 ** 33 + 1])
+def test_combination_of_any_size(recorder, n):
+    run(recorder, f"""
+        mu_all, F_all, mu, F = 1 << 40, 1 << 50, 1 << 52, 1 << 54
+        L.dq_stats_combine.argtypes = [P, P, W, U, P, P, P]
+        assert L.dq_stats_combine(mu_all, F_all, 3, {n}, mu, F, None) == 0
+        at = 0
+        for l in launches():
+            assert l.args[0] == mu_all + 4 * at and l.args[1] == F_all + 4 * at and l.args[2] & 0xFFFFFFFF == 3
+            count = l.args[4]
+            assert l.args[3] == {n} and l.args[5] == mu + 4 * at and l.args[6] == F + 4 * at
+            assert list(l.block) == [256, 1, 1] and list(l.grid) == [(count + 255) // 256, 1, 1]
+            at += count
+        assert at == {n}
+    """, 7)
