@@ -258,7 +258,7 @@ __global__ void __launch_bounds__(kAllocThreads) k_alloc_positions(const float *
 // bisection, a barrier per step, took 46 and 35 us.
 constexpr uint32_t kBins8 = 4096, kBins4 = 6144, kBins16 = 8192;  // brackets of 3 bins, of 3 * 1.07 + 2 and of 3 * 2 + 2
 constexpr uint32_t kCopies = 8;
-constexpr uint32_t kKept = 16;
+constexpr uint32_t kKept = 14;
 
 // Inclusive sum over the lanes of a row of 16, and over the wave
 __device__ __forceinline__ uint32_t row_scan(uint32_t x) {
@@ -286,13 +286,25 @@ __device__ __forceinline__ uint32_t shift_to(uint32_t x, uint32_t bins) {
   return s + (x >> s >= bins ? 1u : 0u);
 }
 
-template <bool ALLOW16>
+// A block's LDS: a level's counters, of the first (kCopies of each) or of the others, and behind these ASIDE, for buckets of more than 16 rows, the
+// norms that the levels look at: 67 KB without, 104 with them (with 16-bit widths 75 and 137).  A search that runs beside a whole replay waits
+// for a CU that has that much in one piece, and registers for sixteen waves.  One block of k_walk (29 KB, 96 registers) may stay beside 104 KB if it is the
+// CU's first or second of five, and beside 108 only if it is the first: an allocation of 51,200 norms adds 13.5 us to a ring of eight's replay of 50.5
+// with kKept 14 or less, 15.7 with 15 and 16.5 with 145 KB (kKept 16, no overlap); without the norms set aside 13.5, but alone 27.5 instead of 25.5.
+constexpr uint32_t search_bins(bool allow16) { return kBins8 + 4 + kBins4 + 4 + (allow16 ? kBins16 + 4 : 0); }
+constexpr uint32_t search_words(bool allow16, bool aside) {
+  const uint32_t first = (kBins + 1) * kCopies, others = search_bins(allow16) + (aside ? (kKept + 1) * kAllocThreads : 0);
+  return first > others ? first : others;
+}
+
+template <bool ALLOW16, bool ASIDE>
 __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits, uint32_t *pos_all,
                                                           uint32_t *counts_all, dq::Announce announce) {
-  __shared__ alignas(16) uint32_t room[kBins8 + 4 + kBins4 + 4 + (ALLOW16 ? kBins16 + 4 : 8188)];  // level 1: 2049 * kCopies
+  __shared__ alignas(16) uint32_t room[search_words(ALLOW16, ASIDE)];
   __shared__ uint32_t wsum[3][kAllocWaves], wfit[kAllocWaves], row_n[kRegs][3];
-  __shared__ uint32_t kept[kKept + 1][kAllocThreads];  // per thread its norms inside the brackets, and a place for what is not kept
   uint32_t *const h8 = room, *const h4 = h8 + kBins8 + 4, *const h16 = h4 + kBins4 + 4;
+  // per thread its norms inside the brackets, and a place for what is not kept
+  uint32_t(*const kept)[kAllocThreads] = reinterpret_cast<uint32_t(*)[kAllocThreads]>(room + search_bins(ALLOW16));
   const float *F = F_all + (uint64_t)blockIdx.x * J;
   uint32_t *pos = pos_all + (uint64_t)blockIdx.x * J;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -419,12 +431,13 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
   }
 
   // A level looks at every norm, with branches around two or three atomics each time, 4 us for 51,200, though few of them lie in the
-  // brackets: where threads have more than kKept norms and no more than a tenth are inside, which the counts above say, the threads set
+  // brackets: where threads have more than 16 norms and no more than a tenth are inside, which the counts above say, the threads set
   // theirs aside first, without a branch, and the levels look at those.  (22.4 -> 21.2 us; of those 4.5 are the first level's atomics, 3.7 this.
-  // Norms within a factor of two of each other, or masses of equal ones, go the other way.)
+  // Norms within a factor of two of each other, or masses of equal ones, go the other way, and so does a bucket of which one thread has more
+  // than kKept inside.)
   uint32_t n_kept = 0, inside = h8[lo >> 20] - base8 + h8[lo4 >> 20] - base4;
   if (ALLOW16) inside += h8[lo16 >> 20] - base16;
-  bool few = J > kKept * (uint32_t)kAllocThreads && inside <= J / 10;
+  bool few = ASIDE && inside <= J / 10;
   if (few) {
     const uint32_t width = hi - lo, width4 = hi4 - lo4, width16 = hi16 - lo16;
     each_norm([&](int k) {
@@ -440,8 +453,7 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
     const uint32_t s = shift_to(width - 1, kBins8), s4 = shift_to(width4 - 1, kBins4), s16 = ALLOW16 ? shift_to(width16 - 1, kBins16) : 0;
     const uint32_t n = ((width - 1) >> s) + 1;
     __syncthreads();  // everybody has read the level before
-    constexpr uint32_t kWords = kBins8 + 4 + kBins4 + 4 + (ALLOW16 ? kBins16 + 4 : 0);
-    for (uint32_t b = tid; b < kWords / 4; b += kAllocThreads) ((uint4 *)room)[b] = make_uint4(0, 0, 0, 0);
+    for (uint32_t b = tid; b < search_bins(ALLOW16) / 4; b += kAllocThreads) ((uint4 *)room)[b] = make_uint4(0, 0, 0, 0);
     __syncthreads();
     auto count = [&](uint32_t v) {
       if (v - lo < width) atomicAdd(&h8[(v - lo) >> s], 1u);
@@ -878,8 +890,8 @@ static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_b
     const uint64_t off = (uint64_t)b0 * J;
     uint32_t *const cnt = counts + 5ull * b0;
     if (rows <= (uint32_t)kRegs) {
-      if (allow16) hipLaunchKernelGGL(k_search<true>, dim3(nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, pos + off, cnt, announce);
-      else hipLaunchKernelGGL(k_search<false>, dim3(nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, pos + off, cnt, announce);
+      const auto search = rows > 16 ? (allow16 ? k_search<true, true> : k_search<false, true>) : (allow16 ? k_search<true, false> : k_search<false, false>);
+      hipLaunchKernelGGL(search, dim3(nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, pos + off, cnt, announce);
       hipLaunchKernelGGL(k_alloc_positions, dim3(rows, nb), dim3(kAllocThreads), 0, s, F + off, J, allow16, cnt, widths + off, pos + off);
     } else
       hipLaunchKernelGGL(k_allocate_large, dim3(nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, allow16, widths + off, pos + off, cnt);

@@ -164,6 +164,22 @@ def test_allocate_narrow_value_ranges(dev):
     check_allocate(dev, F3, 4097, int(math.floor(prep.code_bits(4.0) * 4097)))   # 3 buckets, 5 rows each, ragged
 
 
+@pytest.mark.parametrize("J", [16384, 16385, 51200, 65536])       # from 16,385 on the search sets norms aside, up to 14 per thread
+@pytest.mark.parametrize("max_width", [8, 16])
+def test_allocate_at_the_edges_of_what_is_set_aside(dev, J, max_width):
+    """Few norms around the threshold, but one thread (norms 4096 g + 4 t + 0..3) has 13 to 16 of its own there."""
+    rng = np.random.default_rng(J)
+    spread = np.exp(rng.normal(-14, 6, J)).astype(f32)
+    budget = int(math.floor(prep.code_bits(4.0) * J))
+    T = P.allocate(spread, budget, max_width=max_width)[1]
+    for t in (0, 1, 1023):
+        own = [j for j in range(J) if j % 4096 // 4 == t]
+        for m in (13, 14, 15, 16):
+            F = spread.copy()
+            F[own[:m]] = (T + 3 * np.arange(m, dtype=np.uint32)).astype(np.uint32).view(f32)
+            check_allocate(dev, F, J, budget, max_width=max_width)
+
+
 def test_allocate_more_buckets_than_a_grid_dimension(dev):
     """70,000 buckets of 5 super-groups: the positions launch is cut at 65,535 buckets (the grid's second
     dimension); buckets on both sides of the cut must come out right."""
