@@ -641,34 +641,36 @@ done:
   }
 }
 
-// By tiles per CU (4,096 super-groups are 8 at 256 CUs; a block of the walk does the work of 16).
-// Few: the walk's waves have a SIMD to themselves.  6-bit codes, whose conversions take 32 entries whether there are or not, meet at 9
-// (4,096 super-groups, ring of 64: 25.2 us against the walk's 31.4; 5,120: 33.9 against 32), others at 13 to 15 (bf16; 6,144: 33.5 against
-// 36; 8,192: 50 against 43) and 11 (fp32; 5,120: 60.5 against 75.6, ring of 8 10.7 against 11.6; 6,144: 12 against 11.9); two or three
-// workers, who leave most of the eight requests idle, at 5 (bf16; 2,048: 3.5 against 3.9; 3,072: 4.05 against 4.1) and 9 (fp32; 4,096: 4.7
-// against 5.2; 5,120: 6.2 against 5.4).
-// Above 16, 32, 48: some CUs have a block of the walk more than others, and everyone waits for them.  fp32, us against the walk's: ring of
-// 64, 8,320: 109 against 191, 12,288: 150 against 193; of 16, 18,432: 60 against 76, 14,336: 42 against 40.4; of 8, 9,216: 17.8 against 22.9,
-// 12,288: 22 against 23, 14,336: 25.1 against 23.7, 17,408: 29 against 32, 20,480: 33 against 33.1, 24,576: 39.5 against 37, 28,672: 47.8
-// against 51.5; of 4, 10,240: 13.1 against 14, 12,288: 15.3 against 14.8; butterfly of 16, 9,216: 26.4 against 40; 6-bit ring of 8, 9,216:
-// 18.3 against 20.3, 12,288: 22.4 against 20.8.  bf16, ring of 64, 9,216: 56 against 61, 12,288: 82 against 77; of 8, 11.4 against 11.2.
-// Many: more requests are on their way than one worker's of each wave (fp32: 65,536, ring of 8 117 against 129, of 16 221
-// against 236, butterfly of 128 over 32,768 766 against 826; bf16 rings and chains from 256 on: 132 against 142 of 8, 848 against 880 of 64;
-// butterflies of 128 lose, 430 against 401).
+// By tiles per CU (512 super-groups are one at 256 CUs); a block of the walk does the work of 16 of them.  Ratios below: this kernel's time over the
+// walk's, fp32 and bf16 rings, chains and butterflies of 2 to 128 workers in the three formats, 5,598 in all (profiles/mx_replay_splits.txt).
+//   Up to 16, one block of the walk per CU, whose waves have a SIMD to themselves: the tiles' chains are a quarter as long here, 0.3 to 0.9 at 8, until
+// the CU's lanes are full: at 10 in fp32 (8 workers 0.95 to 0.99; 11: 1.04), 12 in bf16 (0.85 to 0.91 of 8, 0.86 to 1.04 of 32), 10 or 11 for rings and chains of 12
+// to 23 (15 at 11: 1.04 to 1.06, 12 at 11 0.92 and at 12 1.07).  6-bit codes, whose conversions take 32 entries whether there are or not, end at 8; two or three
+// workers, who leave most of the eight requests idle, at 8 in fp32 (0.9; 9: 1.15) and 4 in bf16.
+//   Above, everyone waits for the CUs that have a block more than others.  With c blocks of the walk on these the walk takes what 16 c tiles per CU take, this
+// kernel what there are, in fp32 at a rate that is better the more workers there are: 16 and more all of 17 to 64 (0.5 to 0.98); 12 to 15 all but the
+// second block's upper half (48: 1.0; 28: 0.96 to 1.0); 8 to 11 the parts where slack * c says so (24: 0.95, 28: 1.02; 42: 0.98, 44: 1.0; 60: 0.95, 64: 1.02 to 1.08; from
+// 65 on 0.85 to 0.96); 4 to 7 a quarter of the second block (0.78 to 0.92).  6-bit: the same quarter of 8 workers and more (0.7 to 0.95).  bf16, whose walk
+// has the better rate: an eighth, of 64 workers and more (0.84 to 0.9; chains of 100 and more 1.05 to 1.07).
+//   Many: more requests are on their way than one worker's of each wave: from 256 on bf16 rings and chains of 8 workers and more (0.91 to 0.98).
 template <int FMT, typename LT, bool TREE>
-bool takes_quad(uint32_t n, uint64_t tiles, uint32_t n_cu) {
+bool takes_quad(uint32_t n, uint32_t n_chunks, uint64_t tiles, uint32_t n_cu) {
   constexpr bool six = FMT == DQ_MXFP6_E3M2, wide = sizeof(LT) == 4;
   if (tiles >= 1u << 25) return false;  // threads of a launch: below 2^31
-  const uint64_t few = n < 4 ? (wide ? 8 : 4) : six ? 8 : wide ? 10 : 12;
+  const uint64_t half_full = TREE || n < 12 || n >= 24 ? 12 : n < 14 ? 11 : 10;
+  const uint64_t few = n < 4 ? (wide ? 8 : 4) : six ? 8 : wide ? 10 : half_full;
   if (tiles <= few * n_cu) return true;
   if (tiles <= 16ull * n_cu) return false;
-  if (six) return wide && n >= 8 && tiles <= 20ull * n_cu;
+  const uint64_t c = (tiles + 16ull * n_cu - 1) / (16ull * n_cu), slack = 16ull * c * n_cu - tiles;  // slack: tiles that the fullest CUs' last blocks lack
+  if (six) return wide && n >= 8 && c == 2 && slack >= 12ull * n_cu;
   if (wide) {
-    const auto within = [&](uint64_t lo, uint64_t hi) { return tiles > lo * n_cu && tiles <= hi * n_cu; };
-    if (n < 8) return n >= 4 && within(16, 20);
-    return n >= 64 || within(16, 24) || (tiles > 32ull * n_cu && (n >= 16 || !within(40, 48)));
+    if (n >= 16) return true;
+    if (n >= 12) return c > 2 || slack >= 8ull * n_cu;
+    if (n >= 8) return c > 4 || slack * c >= 16ull * n_cu;
+    return n >= 4 && c == 2 && slack >= 12ull * n_cu;
   }
-  return (n >= 64 && tiles <= 18ull * n_cu) || (!TREE && n >= 8 && tiles >= 256ull * n_cu);
+  if (c == 2 && slack >= 14ull * n_cu) return n >= 64 && (n_chunks > 1 || n < 100);
+  return !TREE && n >= 8 && tiles >= 256ull * n_cu;
 }
 
 template <int FMT, typename LT, bool TREE>
@@ -684,7 +686,7 @@ hipError_t go_mx_quad(MxWalk W, uint32_t n_paths, hipStream_t s) {
 template <int FMT, typename LT, bool TREE>
 hipError_t go_mx_walk(MxWalk W, uint32_t n_cu, hipStream_t s) {
   const uint32_t n_paths = W.n_tiles / W.tiles_per_path;
-  if (takes_quad<FMT, LT, TREE>(W.n, n_paths * ((W.chunk_blocks + kQuadBlocks - 1) / kQuadBlocks), n_cu)) return go_mx_quad<FMT, LT, TREE>(W, n_paths, s);
+  if (takes_quad<FMT, LT, TREE>(W.n, W.n_chunks, n_paths * ((W.chunk_blocks + kQuadBlocks - 1) / kQuadBlocks), n_cu)) return go_mx_quad<FMT, LT, TREE>(W, n_paths, s);
   const uint32_t levels = TREE && W.log_n > 1 ? W.log_n - 1 : 0;
   W.wave_bytes = levels * kMxStackLevel > kMxXpose ? levels * kMxStackLevel : kMxXpose;
   const uint32_t lds = W.wave_bytes * kBlockWaves;

@@ -134,7 +134,9 @@ def test_whole_replay_on_original_tensors_over_the_whole_grid(dev, topology, J):
                                                         ("chain", 3, 4096, 1, False), ("chain", 2, 5121, 1, False), ("ring", 4, 6144, 1, False),
                                                         ("ring", 4, 6148, 1, False), ("ring", 8, 32768, 1, False), ("butterfly", 8, 32760, 1, False),
                                                         ("ring", 8, 131072, 1, False), ("ring", 8, 8200, 1, False), ("ring", 4, 10244, 1, False),
-                                                        ("butterfly", 8, 16392, 1, False), ("ring", 64, 8256, 1, False)])
+                                                        ("butterfly", 8, 16392, 1, False), ("ring", 64, 8256, 1, False),
+                                                        ("chain", 14, 5120, 1, True), ("chain", 14, 5121, 1, False), ("ring", 16, 14400, 1, True),
+                                                        ("ring", 8, 21840, 1, False), ("ring", 8, 21856, 1, False), ("chain", 99, 9216, 1, False)])
 def test_whole_mx_replay_equals_its_steps(dev, fmt, dtype, topology, n, J, nb, all_gather):
     grads = gradients(n, J * nb, dtype, dev, J + n)
     rp = B.Replay(B.Context(n), TOPO[topology], fmt, grads, J, n_buckets=nb, all_gather=all_gather)
