@@ -299,6 +299,52 @@ def test_calls_at_the_edges_of_the_kernel_for_few_super_groups(dev, n_sg, dtype)
     assert_bits(out.view(S, 256)[dix.long()], back)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("wi", [0, 1, 2, 3])
+def test_infinities_and_nan_meet_the_same_arithmetic_on_both_sides_of_the_line(dev, wi, dtype):
+    """What the library leaves unspecified, but what a call gives must not depend on its chunk's size: 40 super-groups of 2 or 16 bits
+    as a chunk of their own (one super-group per wave) and as the first of a chunk for the wide kernel.  4- and 8-bit levels are looked up by the
+    normalised value, which has to be a number: there, a leaf with finite entries above the largest bf16 only."""
+    small, n_cu = 40, torch.cuda.get_device_properties(dev).multi_processor_count
+    large = 64 * n_cu
+    rng = np.random.default_rng(wi)
+    locals_ = []
+    for k in range(3):
+        x = (rng.standard_normal(large * 256) * 1e-3).astype(np.float32)
+        at = rng.integers(0, small * 256, 60)
+        x[at] = rng.choice(np.array([3.3e38, -3.3e38, 3.4e38, -3.4e38, np.inf, -np.inf, np.nan][:4 if wi in (1, 2) else 7], np.float32), 60)
+        if wi not in (1, 2):
+            x[(7 + k) * 256:(8 + k) * 256] = np.inf
+            x[(20 + k) * 256:(21 + k) * 256] = np.nan
+        locals_.append((x.view(np.uint32) >> 16).astype(np.uint16) if dtype == "bf16" else x)
+    counts = lambda n: [n if w == wi else 0 for w in range(4)]
+    ctx = B.Context(6, seed=5)
+    chunks = [B.make_chunk(77, counts(n)) for n in (small, large)]
+    pieces = [[to_dev(x[:n * 256], dev) for x in locals_] for n in (small, large)]
+
+    def same(a, b):   # packed chunks: codes, group scales and scales of the first super-groups
+        a, b, code = host(a), host(b), (64, 128, 256, 512)[wi]
+        assert np.array_equal(a[:small * code], b[:small * code])
+        if wi < 3:
+            a, b = a[small * code:], b[large * code:]
+            assert np.array_equal(a[:small * 16], b[:small * 16])
+            assert np.array_equal(a[small * 16:small * 18], b[large * 16:large * 16 + small * 2])
+
+    def same_results(a, b):
+        a, b = host(a), host(b)[:small * 256]
+        assert np.array_equal(np.isnan(a), np.isnan(b))
+        assert np.array_equal(np.nan_to_num(a, nan=7.0, posinf=8.0, neginf=9.0), np.nan_to_num(b, nan=7.0, posinf=8.0, neginf=9.0))
+
+    leaf = [ctx.dq_compress(x[0], c, 1) for x, c in zip(pieces, chunks)]
+    same(*leaf)
+    if wi in (1, 2):
+        return
+    hop = [ctx.dq_dar_hop(m, x[1], c, 2) for m, x, c in zip(leaf, pieces, chunks)]
+    same(*hop)
+    same_results(*[ctx.dq_decompress(m, c, local=x[2]) for m, x, c in zip(hop, pieces, chunks)])
+    same_results(*[ctx.dq_decompress(m, c) for m, c in zip(hop, chunks)])
+
+
 def test_reciprocal_is_the_division_for_every_pattern(dev):
     """1 / m by the hardware's reciprocal and one step on its remainder, and the division where that is denormal."""
     wrong = torch.zeros(1, dtype=torch.int32, device=dev)
