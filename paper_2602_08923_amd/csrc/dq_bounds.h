@@ -50,6 +50,9 @@ dq_status dqx_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void 
                             float *out, dq_replay **plan, void *hip_stream);
 // Adds to *wrong (device) how many results of the codec's reciprocal differ from the division's.
 dq_status dqx_reciprocals(uint32_t *wrong, void *hip_stream);
+// Where the waves of a replay of n_paths paths begin (dq_walk.hip), {path, tile} each and an end.
+void dqx_split(const uint32_t *n_sg, uint32_t n_paths, uint32_t n_workers, int f32, int tree, uint32_t tile_sgs, uint32_t blocks, uint32_t waves,
+               uint32_t *shares);
 // dq_sg_stats of n_workers (at most 256) tensors and dq_stats_combine in one launch.
 dq_status dqx_stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dtype, uint64_t n_sg, float *mu, float *F,
                         void *hip_stream);

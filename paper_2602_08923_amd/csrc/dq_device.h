@@ -95,8 +95,9 @@ struct Walk {
   uint32_t tile_sgs;         // super-groups of a wave's tile: 4 (dq_walk.hip), 2 or 1 (dq_thin.hip)
   uint32_t n_paths;
   uint32_t blocks, waves;    // grid, waves per block
-  uint32_t by_cost;          // shares of equal cost (0: of equal tile counts)
+  uint32_t order;            // which share a wave takes (share_of): 0, kReversed, or the CUs that the shares are spread over
 };
+constexpr uint32_t kReversed = 0xFFFFFFFFu;
 struct WalkShare {
   uint32_t path, tile;
 };
@@ -106,7 +107,7 @@ uint32_t thin_stack(uint32_t tile_sgs, uint32_t levels);            // per wave
 hipError_t launch_thin(dq_dtype dtype, bool tree, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W, const Params &P,
                        hipStream_t stream);
 bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths_host, Walk *W);  // false: no launch fits
-void split_walk(const WalkPath *paths_host, const Walk &W, std::vector<WalkShare> *shares);
+void split_walk(const WalkPath *paths_host, dq_dtype dtype, bool tree, const Walk &W, std::vector<WalkShare> *shares);
 hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W,
                        const Params &P, hipStream_t stream);
 

@@ -139,6 +139,17 @@ void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, 
     plan->paths.clear();
     return;
   }
+  if (d->n_buckets > 1 && (uint64_t)d->n_buckets * d->n_sg_bucket < 8ull * w.tile_sgs * w.blocks * w.waves) {
+    // Few tiles per wave: the buckets' chunks of the same place, which have about the same widths, one after the other.  The order of all tiles
+    // goes from narrow to wide once, and the waves that share a CU take them from different places of it, not from the same place of several
+    // buckets.  (From some eight tiles per wave on they meet all widths anyway, and the order of the memory is the better one: recursive halving
+    // over 16, eight buckets of 51,200 super-groups, 825 us against 838.)
+    std::vector<dq::WalkPath> by_chunk;
+    by_chunk.reserve(plan->paths.size());
+    for (uint32_t c = 0; c < n_chunks; ++c)
+      for (uint32_t b = 0; b < d->n_buckets; ++b) by_chunk.push_back(plan->paths[(size_t)b * n_chunks + c]);
+    plan->paths.swap(by_chunk);
+  }
   *off = align_up(*off, 256);
   plan->paths_off = *off;
   *off += plan->paths.size() * sizeof(dq::WalkPath);
@@ -641,7 +652,7 @@ static dq_status create(dq_ctx *ctx, const dq_replay_desc *desc, const void *con
   Plan &p = r->plan;
   if (p.walk) {  // in the order of their offsets
     if (!mx) {
-      dq::split_walk(p.paths.data(), p.w, &p.shares);
+      dq::split_walk(p.paths.data(), desc->dtype, p.tree, p.w, &p.shares);
       up.put(p.paths_off, p.paths.data(), p.paths.size() * sizeof(dq::WalkPath));
       up.put(p.shares_off, p.shares.data(), p.shares.size() * sizeof(dq::WalkShare));
     }

@@ -356,7 +356,7 @@ __global__ __launch_bounds__(kThinWaves * 64) __attribute__((amdgpu_waves_per_eu
   extern __shared__ uint4 lds_raw[];
   uint32_t *lds = reinterpret_cast<uint32_t *>(lds_raw);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t share = __builtin_amdgcn_readfirstlane(blockIdx.x * kThinWaves + wave);
+  const uint32_t share = __builtin_amdgcn_readfirstlane(share_of<false>(W, wave, kThinWaves));
   WalkShare at = table_entry(shares, share);
   const WalkShare to = table_entry(shares, share + 1);
   const bool any = at.path < to.path || (at.path == to.path && at.tile < to.tile);

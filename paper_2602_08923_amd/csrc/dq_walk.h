@@ -16,6 +16,22 @@ __device__ __forceinline__ uint32_t lane_here() {
 template <bool B>
 struct Is { static constexpr bool value = B; };
 
+// Which share a wave takes (the order goes from narrow to wide).  Where no wave has more than a tile the wide ones go first, so that the blocks that are
+// dispatched last, beside another on their CU or after it, have the narrow ones.  With more, a ring's four or five blocks of four waves per CU take
+// shares from as many places of the order.  A recursive halving has two blocks of eight: there the i-th waves of all CUs take the i-th
+// stretch of the shares, so that every CU has some of all widths, and CUs with a block more have the narrowest in it.
+// (The number of blocks is read with the other arguments: gridDim is a trip of its own, 0.2 us.)
+template <bool TREE>
+__device__ __forceinline__ uint32_t share_of(const Walk &W, uint32_t wave, uint32_t waves) {
+  const uint32_t b = blockIdx.x;
+  if (W.order == kReversed) return (W.blocks - 1 - b) * waves + wave;
+  if (TREE && W.order) {
+    const uint32_t cus = W.order, row = b / cus, rows = W.blocks / cus, rest = W.blocks - rows * cus;
+    return row < rows ? rest * waves + (row * waves + wave) * cus + b % cus : wave * rest + b % cus;
+  }
+  return b * waves + wave;
+}
+
 // Worker whose entries are the i-th a chunk meets.
 template <bool TREE>
 __device__ __forceinline__ uint32_t leaf_of(const Walk &W, uint32_t chunk, uint32_t i) {

@@ -16,6 +16,9 @@
 //                  others wait as packed codes in LDS (20 bytes per lane and level).
 // Per hop and tile the random numbers are the same Philox counters as in the step kernels; the per-super-group
 // draws of up to 16 hops are made by one wave-wide call (lane = tile of the batch, hop, row).
+#include <string.h>
+
+#include "dq_bounds.h"
 #include "dq_walk.h"
 
 namespace dq {
@@ -318,7 +321,7 @@ __global__ __launch_bounds__((TREE ? 512 : 256)) __attribute__((amdgpu_waves_per
   extern __shared__ uint4 lds_raw[];
   uint32_t *lds = reinterpret_cast<uint32_t *>(lds_raw);
   const uint32_t waves = blockDim.x / 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t v = __builtin_amdgcn_readfirstlane(blockIdx.x * waves + wave);
+  const uint32_t v = __builtin_amdgcn_readfirstlane(share_of<TREE>(W, wave, waves));
   const WalkShare from = table_entry(shares, v), to = table_entry(shares, v + 1);
   copy_tables(lds, P, TREE ? kOffDec2 : kOffTab4);  // a ring or chain never decodes from codes
   __syncthreads();
@@ -366,15 +369,6 @@ hipError_t walk_static_lds(size_t *bytes) {
   return e != hipSuccess ? e : static_lds_of<uint16_t>(bytes);
 }
 
-// The grid (grid_walk), and where every wave's share begins (split_walk): equal shares of the tiles' cost in path order.  A tile's cost by
-// width was chosen by measurement (2-bit tiles need no search; 8-bit ones collide more in LDS): with equal costs the
-// chunks of one width finish early, 1150 us instead of 880 for eight 25 MB buckets through 16 workers' recursive
-// halving.  With less than two tiles per wave the count decides: a wave with one tile more takes twice as long whatever its width.
-static constexpr uint32_t kCosts[2][4] = {{1, 1, 1, 1}, {6, 11, 12, 6}};
-static_assert(kCosts[1][0] == kCosts[1][3] && kCosts[0][0] == 1, "split_walk");
-template <uint32_t C>
-struct Cost { static constexpr uint32_t value = C; };
-
 static uint64_t count_tiles(const WalkPath *paths, uint32_t n_paths, uint32_t sgs) {
   uint64_t tiles = 0;
   for (uint32_t p = 0; p < n_paths; ++p)
@@ -410,7 +404,6 @@ static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, u
   if (W->tile_sgs == kWaveSGs) per_cu = held;
   const uint64_t needed = (tiles + W->waves - 1) / W->waves, blocks = (uint64_t)n_cu * per_cu;
   W->blocks = (uint32_t)(needed < blocks ? needed : blocks);
-  W->by_cost = W->tile_sgs == kWaveSGs && tiles >= 2ull * W->blocks * W->waves;
   return true;
 }
 
@@ -477,46 +470,148 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
       found = true;
     }
   }
-  if (found) *W = best;
-  return found;
+  if (!found) return false;
+  *W = best;
+  const uint64_t tiles = count_tiles(paths, W->n_paths, W->tile_sgs), waves = (uint64_t)W->blocks * W->waves;
+  const bool spread = tree && W->n > 4 && W->tile_sgs == kWaveSGs && tiles < 8 * waves;
+  // (Not with 16-bit tiles, the cheapest, at the end: ring of 6, three buckets of 4,476, a quarter of them 16-bit, 15.0 us and 15.8 reversed.)
+  W->order = spread ? n_cu : tiles <= waves && !W->raw ? kReversed : 0;
+  return true;
 }
 
-void split_walk(const WalkPath *paths, const Walk &W, std::vector<WalkShare> *shares) {
-  const uint32_t *kCost = kCosts[W.by_cost];
-  const uint32_t sgs = W.tile_sgs, n = W.blocks * W.waves;
-  uint64_t cost = 0;
-  for (uint32_t p = 0; p < W.n_paths; ++p)
-    for (int w = 0; w < 4; ++w) cost += (uint64_t)((paths[p].job.n_sg[w] + sgs - 1) / sgs) * kCost[w];
-  shares->resize((size_t)n + 1);
-  // Share v begins with the first tile whose cost before it reaches want = floor(v * cost / n); over = that division's remainder.
-  WalkShare *share = shares->data(), *const end = share + n;
-  const uint64_t step = cost / n, rest = cost % n;
-  uint64_t want = 0, over = 0, before = 0;  // before: cost of all runs of one width before this one
-  uint32_t first = 0;                       // tile of this run
-  // The shares that begin in a run of `tiles` tiles.  The cost is a constant: dividing by it is a multiplication.  (With a division per share
-  // 2,049 shares took the host 15 us of a plan's 17.)
-  auto fill = [&](auto cost_of_tile, uint32_t p, uint32_t tiles) {
-    constexpr uint64_t c = decltype(cost_of_tile)::value;
-    for (const uint64_t last = before + (tiles - 1) * c; share != end && want <= last;) {
-      const uint64_t at = want > before ? want - before : 0;
-      *share++ = WalkShare{p, first + (uint32_t)((at + c - 1) / c)};
-      over += rest;
-      const uint64_t carry = over >= n ? 1 : 0;
-      over -= n & (0 - carry);
-      want += step + carry;
-    }
-    before += tiles * c;
-    first += tiles;
+// Where every wave's share of the tiles begins.  All waves are resident at once and a SIMD's waves share its issue, so what counts is how much the
+// fullest waves hold: one with three tiles where the others have two works on alone for a third of the launch, and shares of equal cost (or equal
+// count) leave that to chance.  Here every width gets a most, the tiles of it that a wave may hold, such that the fullest wave costs as little as
+// possible and then each most, the dearest first, is as small as the waves allow; and the costs are raised just so far that equal shares keep to it.
+// us, equal cost (below two tiles per wave: equal count) -> this, passes in turn over three sets of tensors; super-groups by width:
+//   ring of 8, 51,200 in bf16: 17,608/33,584/8  60.5 -> 59.6;  a quarter, a quarter, a half  69.1 -> 61.4;  of 11, 25,322  57.5 -> 49.5
+//   recursive halving in bf16 over 8, 18,504  36.8 -> 23.8;  over 32, 20,128  119 -> 91;  over 16, 8 x 51,200 at 3 bits  833 -> 831
+//   in fp32: ring of 6, 8 x 44,976  687 -> 573;  halving over 2, 8 x 40,450  269 -> 214
+// The geometric mean of 230 schedules of 2 to 100 workers and 14,000 to 400,000 super-groups: rings in bf16 and fp32 3.9 and 2.7 % faster, halvings
+// 10.5 and 6.6 (8 of the 230 lose more than 5 %, mostly where half the waves have one tile and half two).
+// A tile's costs: what its instructions take beside the memory's time, which all widths have alike, measured as the ratios that are fastest: 1.8 to 2.2 with
+// bf16 tensors of five workers and more, 1.1 to 1.25 where a hop moves more bytes (fp32, or a result of 4 bytes per few workers).  (12/15/16
+// instead of 12/24/26 for the first ring above: 64.2.)
+namespace {
+struct Costs { uint32_t of[4]; };
+Costs costs_of(bool f32, bool tree, uint32_t n) {
+  if (f32 || n <= 4) return Costs{{12, 14, 15, 12}};
+  return tree ? Costs{{12, 20, 22, 12}} : Costs{{12, 24, 26, 12}};
+}
+// The most tiles per wave of every width (0: there is none of it), at most `waves` waves.
+void most_per_wave(const uint64_t tiles[4], const uint32_t cost[4], uint32_t waves, uint64_t most[4]) {
+  auto fits = [&] {
+    double need = 0;
+    for (int w = 0; w < 4; ++w)
+      if (tiles[w]) {
+        if (most[w] == 0) return false;
+        need += (double)tiles[w] / (double)most[w];
+      }
+    return need <= (double)waves;
   };
+  auto within = [&](uint64_t s) {
+    for (int w = 0; w < 4; ++w) most[w] = !tiles[w] ? 0 : s >> 32 ? s / cost[w] : (uint32_t)s / cost[w];
+    return fits();
+  };
+  // the least cost of the fullest wave, which is at least the mean
+  uint64_t all = 0, lo, hi, by = cost[0];
+  for (int w = 0; w < 4; ++w) all += tiles[w] * cost[w];
+  lo = all / waves ? all / waves - 1 : 0;
+  for (hi = lo + by; !within(hi); hi += by *= 2) lo = hi;
+  while (hi - lo > 1) {
+    const uint64_t mid = lo + (hi - lo) / 2;
+    if (within(mid)) hi = mid; else lo = mid;
+  }
+  within(hi);
+  for (bool less = true; less;) {
+    less = false;
+    int order[4] = {0, 1, 2, 3};
+    for (int i = 1; i < 4; ++i)
+      for (int k = i; k > 0 && most[order[k]] * cost[order[k]] > most[order[k - 1]] * cost[order[k - 1]]; --k) {
+        const int t = order[k];
+        order[k] = order[k - 1];
+        order[k - 1] = t;
+      }
+    for (int i = 0; i < 4 && !less; ++i) {
+      const int w = order[i];
+      if (most[w] < 2) continue;
+      --most[w];
+      less = fits();
+      if (!less) ++most[w];
+    }
+  }
+}
+}  // namespace
+
+void split_walk(const WalkPath *paths, dq_dtype dtype, bool tree, const Walk &W, std::vector<WalkShare> *shares) {
+  const uint32_t sgs = W.tile_sgs, n = W.blocks * W.waves;
+  uint64_t tiles[4] = {0, 0, 0, 0}, most[4], cost[4], total = 0;
+  for (uint32_t p = 0; p < W.n_paths; ++p)
+    for (int w = 0; w < 4; ++w) tiles[w] += (paths[p].job.n_sg[w] + sgs - 1) / sgs;
+  const Costs c = costs_of(dtype == DQ_F32, tree, W.n);
+  most_per_wave(tiles, c.of, n, most);
+  // Equal shares of cost total / n hold at most `most` tiles of a width that costs at least that over `most`.  The costs rise until that is so, each
+  // round by less; where the waves are just enough it is so at the cost of the fullest.
+  constexpr uint64_t kUnit = 1u << 20;
+  uint64_t fullest = 0;
+  for (int w = 0; w < 4; ++w) {
+    cost[w] = c.of[w] * kUnit;
+    fullest = most[w] * cost[w] > fullest ? most[w] * cost[w] : fullest;
+  }
+  for (int round = 0;; ++round) {
+    total = 0;
+    for (int w = 0; w < 4; ++w) total += tiles[w] * cost[w];
+    const uint64_t share = round < 8 ? (total + n - 1) / n : fullest;
+    bool raised = false;
+    for (int w = 0; w < 4; ++w)
+      if (most[w] && cost[w] * most[w] < share) {
+        cost[w] = (share + most[w] - 1) / most[w];
+        raised = true;
+      }
+    if (!raised || round > 8) break;
+  }
+  shares->resize((size_t)n + 1);
+  // Share v begins with the first tile whose cost before it reaches want = floor(v * total / n); over = that division's remainder.
+  WalkShare *share = shares->data(), *const end = share + n;
+  const uint64_t step = total / n, rest = total % n;
+  uint64_t tiles_on[4], part_on[4];  // step in tiles
+  for (int w = 0; w < 4; ++w) {
+    tiles_on[w] = step / cost[w];
+    part_on[w] = step % cost[w];
+  }
+  uint64_t want = 0, over = 0, before = 0;  // before: cost of all runs of one width before this one
   for (uint32_t p = 0; p < W.n_paths; ++p) {
-    first = 0;
+    uint32_t first = 0;  // tile of this run
     for (int w = 0; w < 4; ++w) {
-      const uint32_t tiles = (paths[p].job.n_sg[w] + sgs - 1) / sgs;
-      if (tiles == 0) continue;
-      if (!W.by_cost) fill(Cost<1>(), p, tiles);
-      else if (w == 1) fill(Cost<kCosts[1][1]>(), p, tiles);
-      else if (w == 2) fill(Cost<kCosts[1][2]>(), p, tiles);
-      else fill(Cost<kCosts[1][0]>(), p, tiles);
+      const uint32_t count = (paths[p].job.n_sg[w] + sgs - 1) / sgs;
+      if (count == 0) continue;
+      const uint64_t each = cost[w], last = before + (count - 1) * each;
+      // The shares that begin in this run: at = tile * each + part.  (With a division per share 2,049 shares took the host 15 us of a
+      // plan's 17.)
+      uint64_t tile = 0, part = 0;
+      bool inside = false;
+      while (share != end && want <= last) {
+        if (!inside && want >= before) {
+          tile = (want - before) / each;
+          part = (want - before) % each;
+          inside = true;
+        }
+        *share++ = WalkShare{p, first + (uint32_t)(inside ? tile + (part != 0) : 0)};
+        over += rest;
+        const uint64_t carry = over >= n ? 1 : 0;
+        over -= n & (0 - carry);
+        want += step + carry;
+        if (inside) {
+          tile += tiles_on[w];
+          part += part_on[w] + carry;
+          if (part >= each) {
+            part -= each;
+            ++tile;
+          }
+        }
+      }
+      before += count * each;
+      first += count;
     }
   }
   while (share != end + 1) *share++ = WalkShare{W.n_paths, 0};
@@ -533,3 +628,19 @@ hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *pa
 }
 
 }  // namespace dq
+
+// The shares of a launch, for the tests: n_sg[p][4] super-groups by width of every path; shares[2 * (blocks * waves + 1)].
+extern "C" void dqx_split(const uint32_t *n_sg, uint32_t n_paths, uint32_t n_workers, int f32, int tree, uint32_t tile_sgs, uint32_t blocks,
+                          uint32_t waves, uint32_t *shares) {
+  std::vector<dq::WalkPath> paths(n_paths, dq::WalkPath{});
+  for (uint32_t p = 0; p < n_paths; ++p) memcpy(paths[p].job.n_sg, n_sg + 4 * (size_t)p, 16);
+  dq::Walk W = {};
+  W.n = n_workers;
+  W.n_paths = n_paths;
+  W.tile_sgs = tile_sgs;
+  W.blocks = blocks;
+  W.waves = waves;
+  std::vector<dq::WalkShare> s;
+  dq::split_walk(paths.data(), f32 ? DQ_F32 : DQ_BF16, tree != 0, W, &s);
+  memcpy(shares, s.data(), s.size() * sizeof(dq::WalkShare));
+}

@@ -96,6 +96,16 @@ def test_whole_replay_of_many_super_groups_equals_its_steps(dev, topology, n, wi
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("topology,n,widths", [
+    # between one and three tiles of four per wave, several buckets, the last row of blocks on the CUs not full: waves hold 0 to 5 tiles of a width
+    ("butterfly", 8, [[2401, 3202, 1501, 96]] * 3), ("butterfly", 2, [[9001, 6002, 5001, 0], [0, 4, 20000, 0]]), ("butterfly", 16, [[23001, 9, 1230, 0]]),
+    ("ring", 6, [[9001, 602, 501, 96]] * 3), ("ring", 3, [[20000, 31000, 1, 8]]), ("ring", 9, [[2, 16000, 8001, 0]]),
+])
+def test_whole_replay_of_few_tiles_per_wave_equals_its_steps(dev, topology, n, widths, dtype):
+    test_whole_replay_equals_its_steps(dev, topology, n, widths, False, True, dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("topology,J", [("ring", 64), ("butterfly", 64), ("ring", 8192), ("butterfly", 8192)])   # one and four super-groups per tile
 def test_whole_replay_of_extreme_magnitudes_equals_its_steps(dev, topology, J, dtype):
     """Groups whose maximum's reciprocal is denormal, groups too small for a scale beside ones that are not, super-groups encoded as zero."""
