@@ -90,6 +90,8 @@ struct Start {
   TilePos pos;
   uint64_t at;  // byte offset of the lane's entries inside every worker's tensor
   float mu;
+  uint32_t dest;  // with one super-group per wave: where its result goes, and what is added to it
+  float back;
   Bit<LT, E> s[kAhead];
 };
 
@@ -112,6 +114,12 @@ __device__ __forceinline__ Start<LT, E> start_tile(const WalkPath &path, const W
   const uint32_t sg0 = first + x.pos.tile_first + row;
   const uint64_t sg = job.src ? (uint64_t)gld<uint32_t>(job.src + sg0) : (uint64_t)sg0;
   x.mu = job.mu ? gld<float>(job.mu + sg0) : 0.0f;  // taking off 0 changes nothing
+  if constexpr (E == 4) {  // on the index's trip, not one of their own behind the last hop
+    x.dest = sg0;
+    x.back = 0.0f;
+    if (job.dest) x.dest = (uint32_t)__builtin_amdgcn_readfirstlane((int)(job.dest == job.src ? (uint32_t)sg : gld<uint32_t>(job.dest + sg0)));
+    if (job.back) x.back = u2f((uint32_t)__builtin_amdgcn_readfirstlane((int)f2u(job.back == job.mu ? x.mu : gld<float>(job.back + sg0))));
+  }
   x.at = (uint64_t)reinterpret_cast<uintptr_t>(job.local) + sg * (kSG * sizeof(LT)) + (lane & (64u / kSgs - 1u)) * (E * (uint32_t)sizeof(LT));
 #pragma unroll
   for (uint32_t j = 0; j < kAhead; ++j) {
@@ -340,11 +348,11 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
   }
   const size_t sg0 = (size_t)pos.seg_first + pos.tile_first + row;
   if (job.back) {
-    const float back = (float)P.n_workers * gld<float>(job.back + sg0);
+    const float back = (float)P.n_workers * (E == 4 ? x.back : gld<float>(job.back + sg0));
 #pragma unroll
     for (int k = 0; k < E; ++k) v[k] = v[k] + back;
   }
-  const size_t sg = job.dest ? (size_t)gld<uint32_t>(job.dest + sg0) : sg0;
+  const size_t sg = E == 4 ? (size_t)x.dest : job.dest ? (size_t)gld<uint32_t>(job.dest + sg0) : sg0;
   float *out = static_cast<float *>(job.out) + sg * kSG + (lane & (64u / kSgs - 1u)) * E;
 #pragma unroll
   for (int h = 0; h < E / 4; ++h) gst_once<f32x4>(out + 4 * h, f32x4{v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]});
