@@ -9,6 +9,10 @@ struct Bound {
   const uint32_t *index;  // device
   uint32_t n, limit;      // every index must be below limit
 };
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline bool same_array(const Bound &a, const Bound &b) { return a.index == b.index && a.n == b.n; }
 constexpr uint32_t kFetchWords = 1023;
 struct Guard {
   const uint32_t *word;  // device, or null: the call's kernels do nothing if it holds `call`

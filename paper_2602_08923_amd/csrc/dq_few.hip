@@ -206,9 +206,9 @@ __device__ __forceinline__ void finish_piece(const Job &job, const Params &P, co
 }
 
 // A check of the call's indices in its own blocks: every block looks at all of them, so that all know the verdict; the largest index
-// decides.  That takes up to 40 KB per block out of the L2, beside what the block waits for anyway.  A gathered hop of 3,187 super-groups
-// takes 8.5 us, which is the host's time from one launch to the next with a look at the verdict between; 9.7 to 10.3 with the check as a launch
-// in front of the call.  (The first indices requested ahead of everything else: no difference.)
+// decides.  That takes up to 64 KB per block out of the L2, beside what the block waits for anyway.  A gathered hop of 3,187 super-groups
+// takes 7.3 us, which is the host's time from one launch to the next with a look at the verdict between; 9.7 to 10.3 with the check as a launch
+// in front of the call.
 __device__ __forceinline__ uint32_t largest_index(const Bound &x) {
   typedef uint32_t Four __attribute__((ext_vector_type(4), aligned(4)));
   constexpr uint32_t kRound = kFewWaves * 64;
@@ -229,16 +229,43 @@ __device__ __forceinline__ uint32_t wave_verdict(const OwnCheck &c) {
   const uint32_t a = largest_index(c.a);
   uint32_t bits = __builtin_amdgcn_ballot_w64(a >= c.a.limit) ? 1u : 0u;
   if (c.b.n) {
-    const uint32_t b = c.b.index == c.a.index && c.b.n == c.a.n ? a : largest_index(c.b);  // a restore of what was gathered: one array
+    const uint32_t b = same_array(c.a, c.b) ? a : largest_index(c.b);  // a restore of what was gathered: one array
     bits |= __builtin_amdgcn_ballot_w64(b >= c.b.limit) ? 2u : 0u;
   }
   return bits;
+}
+
+// The block's, at whose barrier the waves' meet in LDS.
+__device__ __forceinline__ void put_verdict(const OwnCheck &c, uint32_t at) {
+  const uint32_t bits = wave_verdict(c);
+  if ((threadIdx.x & 63u) == 0) lds_st1(at + (threadIdx.x >> 6) * 4, bits);
+}
+__device__ __forceinline__ uint32_t verdict_at(uint32_t at) {
+  static_assert(kFewWaves == 8, "two reads");
+  const u32x4 a = lds_ld4(at), b = lds_ld4(at + 16);
+  return __builtin_amdgcn_readfirstlane(a.x | a.y | a.z | a.w | b.x | b.y | b.z | b.w);
+}
+
+// The first block of a checked call does nothing but look and tell the host, which waits for it.  Told by a block that also worked, behind the
+// tables' trip and the draws, the verdict came a microsecond later (a gathered hop of 3,187 super-groups 8.4 us a call instead of 7.3).
+__device__ __forceinline__ void post_verdict(const OwnCheck &check) {
+  put_verdict(check, 0);
+  __syncthreads();
+  const uint32_t bits = verdict_at(0);
+  if (threadIdx.x == 0)
+    __hip_atomic_store(check.host, 4 * check.call + bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // nothing else to order
 }
 
 template <Kind KIND, typename LT, bool CHECK>
 __global__ __launch_bounds__(kFewWaves * 64) void k_few(Job job_, Params P_, OwnCheck check) {
   extern __shared__ uint4 lds_raw[];
   uint32_t *lds = reinterpret_cast<uint32_t *>(lds_raw);
+  if constexpr (CHECK)
+    if (blockIdx.x == 0) {
+      post_verdict(check);
+      return;
+    }
+  const uint32_t block = blockIdx.x - (CHECK ? 1 : 0);
   // every argument in one go: read where it is used, each would be a trip of its own
   Job job = job_;
   Params P = P_;
@@ -249,7 +276,7 @@ __global__ __launch_bounds__(kFewWaves * 64) void k_few(Job job_, Params P_, Own
                "+s"(P.inv_n), "+s"(P.inv_n512), "+s"(P.s_n));
   const uint32_t total = job.n_sg[0] + job.n_sg[1] + job.n_sg[2] + job.n_sg[3];
   const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t sg = blockIdx.x * kFewWaves + wave;
+  const uint32_t sg = block * kFewWaves + wave;
   const Place p = place_of(job, min(sg, total - 1));
   const Piece<LT> f = fetch_piece<KIND, LT>(job, p, CHECK ? check.src_limit : 0xFFFFFFFFu);
   // all tables, whatever widths the block meets: to choose would take longer
@@ -267,7 +294,7 @@ __global__ __launch_bounds__(kFewWaves * 64) void k_few(Job job_, Params P_, Own
   const uint32_t verdicts = area + kFewWaves * 32;
   if constexpr (KIND != kDecompress) {
     if (wave == 0) {  // lanes 2i, 2i + 1: the shared draw of the block's i-th super-group, the worker's for its scales
-      const uint64_t G = job.first_sg + min(blockIdx.x * kFewWaves + (lane >> 1), total - 1);
+      const uint64_t G = job.first_sg + min(block * kFewWaves + (lane >> 1), total - 1);
       const U4 w = philox4x32_10((uint32_t)G, (uint32_t)(G >> 32), P.round, lane & 1u ? (1u << 16) | (job.rank & 0xFFFFu) : (2u << 16) | 0xFFFFu,
                                  P.key0, P.key1);
       const uint32_t w0 = lane & 1u ? w.x : perm_slot(w, P, job.rank);
@@ -278,19 +305,10 @@ __global__ __launch_bounds__(kFewWaves * 64) void k_few(Job job_, Params P_, Own
   }
 #pragma unroll
   for (uint32_t r = 0; r < kRounds; ++r) *reinterpret_cast<uint4 *>(&lds[at[r]]) = part[r];
-  if constexpr (CHECK) {
-    const uint32_t bits = wave_verdict(check);
-    if (lane == 0) lds_st1(verdicts + wave * 4, bits);
-  }
+  if constexpr (CHECK) put_verdict(check, verdicts);
   __syncthreads();
-  if constexpr (CHECK) {
-    static_assert(kFewWaves == 8, "two reads");
-    const u32x4 a = lds_ld4(verdicts), b = lds_ld4(verdicts + 16);
-    const uint32_t bits = __builtin_amdgcn_readfirstlane(a.x | a.y | a.z | a.w | b.x | b.y | b.z | b.w);
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-      __hip_atomic_store(check.host, 4 * check.call + bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // nothing else to order
-    if (bits) return;
-  }
+  if constexpr (CHECK)
+    if (verdict_at(verdicts)) return;
   if (sg >= total) return;  // not the last super-group once more: a hop may write where it reads
   if constexpr (KIND != kDecompress) {
     const uint32_t g = lane >> 2, mine = area + wave * 32;
@@ -305,10 +323,11 @@ __global__ __launch_bounds__(kFewWaves * 64) void k_few(Job job_, Params P_, Own
 template <Kind KIND, typename LT>
 hipError_t go_few(const Job &job, const Params &p, uint32_t super_groups, hipStream_t s) {
   const size_t lds = (KIND == kDecompress ? (size_t)kOffLut4 * 4 : (size_t)p.blob_dwords * 4) + kFewWaves * 36;
-  const dim3 grid((super_groups + kFewWaves - 1) / kFewWaves), block(kFewWaves * 64);
+  const uint32_t blocks = (super_groups + kFewWaves - 1) / kFewWaves;
+  const dim3 block(kFewWaves * 64);
   OwnCheck check = {};
-  if (take_own_check(job.src, &check)) hipLaunchKernelGGL((k_few<KIND, LT, true>), grid, block, lds, s, job, p, check);
-  else hipLaunchKernelGGL((k_few<KIND, LT, false>), grid, block, lds, s, job, p, check);
+  if (take_own_check(job.src, &check)) hipLaunchKernelGGL((k_few<KIND, LT, true>), dim3(blocks + 1), block, lds, s, job, p, check);
+  else hipLaunchKernelGGL((k_few<KIND, LT, false>), dim3(blocks), block, lds, s, job, p, check);
   return hipGetLastError();
 }
 
@@ -318,15 +337,15 @@ hipError_t go_few(const Job &job, const Params &p, uint32_t super_groups, hipStr
 //   several widths, or 8- and 16-bit ones only: hop 32 (9,000: 6.05 against 5.85), decompress 40;
 //   2- or 4-bit ones only, whose wide tiles run one short piece of code: 24 (6,144: hop 4.7 against 4.85; 7,000: 5.4 against 5.0; sink 3.8
 //   against 4.0; 4.25 against 4.05);
-//   with a check of indices armed, which the wide kernel leaves to a launch in front of it: hop and decompress of two arrays 40 (8,192: 8.3
-//   against 9.9; 10,240: 9.3 against 9.3), decompress of one array 56 (12,288: 8.7 against 9.3; 14,336: 9.35 against 9.4): every block looks
-//   at every index.
+//   with a check of indices armed, which the wide kernel leaves to a launch in front of it: hop and compress 48 (12,288: hop 10.2 against 10.6;
+//   14,336: 11.5 against 11.0), decompress 64 (16,384: sink 10.8 against 10.95, in fp32 11.2 against 11.5; 18,432: 13.4 against 11.0), of two
+//   different arrays 40: every block looks at every index.
 // Tables larger than the default level sets' (21 KB) are copied by more blocks than they are worth here.
 bool takes_few(Kind kind, const Job &job, const Params &P, uint32_t n_cu) {
   const uint64_t n = (uint64_t)job.n_sg[0] + job.n_sg[1] + job.n_sg[2] + job.n_sg[3], due = own_check_due();
   if (due == ~0ull || (kind != kDecompress && P.blob_dwords * 4 > kFewTableBytes)) return false;
   uint32_t most;
-  if (due) most = kind == kDecompress && due == n ? 56 : 40;
+  if (due) most = due > n ? 40 : kind == kDecompress ? 64 : 48;
   else if (n == job.n_sg[0] || n == job.n_sg[1]) most = 24;
   else most = kind == kDecompress ? 40 : 32;
   return n <= (uint64_t)most * n_cu;

@@ -176,8 +176,8 @@ def test_whole_mx_replay_of_any_pattern_equals_its_steps(dev, fmt, dtype, topolo
 
 @pytest.mark.parametrize("at", [0, 3, 4, 4095, 8190, 8191, 8192, 10238, 10239, 14334, 14335])
 def test_a_call_of_few_super_groups_checks_every_index_itself(dev, at):
-    """Rounds of 8,192 indices per block, fours and the rest of the array; from 10,241 (one array
-    of a decompress: 14,337) on the check is a launch of its own again.  Two arrays: the same one within two tensors of different length, and two."""
+    """Rounds of 8,192 indices per block, fours and the rest of the array; beyond 12,288 (decompress: of one array 16,384, of two
+    10,240) the check is a launch of its own again.  Two arrays: the same one within two tensors of different length, and two."""
     ctx = B.Context(4, seed=1)
     for n_sg in {at + 1, at + 2, at + 5}:
         ch = B.make_chunk(0, [0, n_sg, 0])
@@ -207,6 +207,11 @@ def test_a_call_of_few_super_groups_checks_every_index_itself(dev, at):
             ctx.dq_dar_hop(message, x, ch, 2, packed_out=hop, sg_index=bad)
         torch.cuda.synchronize()
         assert bool((hop == 9).all())
+
+
+@pytest.mark.parametrize("at", [12286, 12287, 12288, 16382, 16383, 16384])
+def test_a_call_at_the_edge_of_its_own_check(dev, at):
+    test_a_call_of_few_super_groups_checks_every_index_itself(dev, at)
 
 
 def test_a_result_smaller_than_a_super_group_is_refused(dev):
