@@ -50,6 +50,14 @@ def simulated_allreduce(worker_grads, budget_bits, topology=B.DQ_RING, codec=B.D
         rp = B.Replay(ctx, topology, codec, worker_grads, J, n_buckets=nb, all_gather=all_gather)
         rp.run()
         return rp.out, {"replay_steps": rp.n_steps}
+    gather = fused_reorder and fused_restore
+    if gather and uniform_width is None:
+        whole = B.allreduce_whole(ctx, list(worker_grads), J, topology, math.floor(prep.code_bits(budget_bits) * J), max_width, all_gather,
+                                  subtract_mean)
+        if whole is not None:
+            out, by_width = whole
+            steps = (n if topology == B.DQ_RING else n.bit_length()) + (2 if all_gather else 0)
+            return out, {"sg_by_width": by_width(), "replay_steps": steps}
     dev = worker_grads[0].device
     mu, F = B.stats_of_workers(worker_grads)
     if not subtract_mean:
@@ -66,7 +74,6 @@ def simulated_allreduce(worker_grads, budget_bits, topology=B.DQ_RING, codec=B.D
         if uniform_width == 16:
             mu = None                                    # uncompressed super-groups are not normalized
     mu_main, origin = B.dq_reorder_mean(mu, pos, J, counts, with_origin=True)
-    gather = fused_reorder and fused_restore
     inputs = worker_grads if gather else [B.dq_reorder(g, pos, J) for g in worker_grads]
     rp = B.Replay(ctx, topology, B.DQ_DYNAMIQ, inputs, J, by_width, n_buckets=nb, all_gather=all_gather,
                   mu=mu_main, origin=origin if fused_restore else None, inputs_in_original_order=gather)

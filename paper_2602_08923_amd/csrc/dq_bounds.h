@@ -52,6 +52,18 @@ dq_status dqx_allocate_end(void *ticket, uint32_t n_sg_per_bucket, uint32_t n_bu
 // uploaded as work of that stream, nothing is waited for.  Not while the stream is captured.
 dq_status dqx_replay_create(dq_ctx *ctx, const dq_replay_desc *desc, const void *const *worker_grads, void *scratch, size_t scratch_bytes,
                             float *out, dq_replay **plan, void *hip_stream);
+// A whole simulated all-reduce of n_workers (the context's) tensors in their original order, ring or recursive halving, codec DynamiQ: dq_sg_stats,
+// dq_stats_combine, dq_allocate, dq_reorder_mean and a replay with origin and inputs_in_original_order, the same bits, without waiting (not under
+// capture).  The class counts come with the ticket (dqx_allocate_end).  0 bytes: not such a call, or too large for it.
+struct dqx_whole {
+  dq_topology topology;
+  dq_dtype dtype;
+  uint32_t n_sg_bucket, n_buckets;
+  uint64_t max_code_bits;
+  uint32_t max_width, all_gather, means;
+};
+size_t dqx_whole_scratch_bytes(const dq_ctx *ctx, const dqx_whole *desc);
+dq_status dqx_whole_run(const dq_ctx *ctx, const dqx_whole *desc, const void *const *tensors, void *scratch, float *out, void *hip_stream, void **ticket);
 // Adds to *wrong (device) how many results of the codec's reciprocal differ from the division's.
 dq_status dqx_reciprocals(uint32_t *wrong, void *hip_stream);
 // Where the waves of a replay of n_paths paths begin (dq_walk.hip), {path, tile} each and an end.

@@ -198,10 +198,9 @@ hipError_t armed_guard(hipStream_t s, Guard *guard) {
 
 // Counts ahead of an allocation.  The host needs nothing of it but how many super-groups have each width; with them it plans the replay,
 // meanwhile the GPU writes positions, origins and means.  Fetched by a launch behind the allocation they came 10 us later, and
-// what followed was enqueued after the wait.  (With the plan's own part of it, split_walk and k_upload, the all-reduce of 8 workers' 8,192
-// super-groups takes 58.5 us; 76.6 without the counts ahead, 89 before.)
+// what followed was enqueued after the wait.  (An all-reduce that is enqueued whole, dqx_whole_run, only reports them.)
 // Their words lie behind the workspace's first two.
-constexpr uint32_t kAnnounced = (kFetchWords - 1) / 2;
+static_assert(kAnnounced == (kFetchWords - 1) / 2, "two words each");
 static uint64_t *announced(Workspace *w) { return reinterpret_cast<uint64_t *>(w->host + 2); }
 static uint32_t tag_of(const Workspace *w) { return w->calls % 8191 + 1; }
 hipError_t announce_begin(uint32_t n_buckets, hipStream_t s, Announce *announce, void **ticket) {

@@ -106,10 +106,45 @@ uint32_t thin_lds(const Params &P, uint32_t stack_bytes);           // per block
 uint32_t thin_stack(uint32_t tile_sgs, uint32_t levels);            // per wave
 hipError_t launch_thin(dq_dtype dtype, bool tree, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W, const Params &P,
                        hipStream_t stream);
-bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths_host, Walk *W);  // false: no launch fits
+// tiles: of one, two and four super-groups.  False: no launch fits
+bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const uint64_t tiles[3], Walk *W);
+struct Costs { uint32_t of[4]; };
+Costs costs_of(dq_dtype dtype, bool tree, uint32_t n);  // of a tile, by width
 void split_walk(const WalkPath *paths_host, dq_dtype dtype, bool tree, const Walk &W, std::vector<WalkShare> *shares);
 hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W,
                        const Params &P, hipStream_t stream);
+
+// Class counts that a search tells the host as soon as it has them (dq_bounds.hip): per bucket one word in pinned memory, counts of
+// 17 bits with a tag above them.  Null: not told.  No ticket for more buckets than a workspace holds.
+struct Announce {
+  uint64_t *host;
+  uint32_t tag;
+};
+// The tables of a whole replay on the original tensors, made on the device from the allocation's class counts (pp_kernels.hip).
+struct Tables {
+  WalkPath *paths;
+  WalkShare *shares;
+  float *out;
+  const uint32_t *origin;
+  const float *mu;          // in reordered order, or null
+  uint32_t n_chunks, n_buckets, chunk_sgs, bucket_sgs;
+  uint32_t by_chunk;        // paths of the same chunk number next to each other
+  uint32_t entry_bytes;
+  uint32_t waves, tile_log;  // shares; log2 of a tile's super-groups
+  Costs cost;
+};
+constexpr uint32_t kMostTablePaths = 1024;  // a thread each
+constexpr uint32_t kMostTensors = 256;      // whose addresses travel in a launch's arguments
+// dq_sg_stats of all workers and dq_stats_combine in one launch; grads (or null): the tensors' addresses, all twice, are put down there
+dq_status stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dtype, uint64_t n_sg, float *mu, float *F, const void **grads,
+                    hipStream_t stream);
+// The search of an allocation alone: counts, and every row's first places in `places`.  Buckets of at most kMostSearched super-groups.
+constexpr uint32_t kMostSearched = 65536;
+dq_status search(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width, uint32_t *places,
+                 uint32_t *counts, Announce announce, hipStream_t stream);
+// Behind it: the means in reordered order (mu and mu_main, or both null), the origins, and the tables.
+dq_status arrange(const float *F, const float *mu, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32_t max_width, const uint32_t *counts,
+                  const uint32_t *places, float *mu_main, uint32_t *origin, const Tables &tables, hipStream_t stream);
 
 // kernel launchers (dq_kernels.hip); grid_blocks = thread blocks the GPU keeps resident at once
 hipError_t launch_one(Kind kind, dq_dtype dtype, bool has_local, const Job &job, const Params &p, uint32_t n_cu, uint32_t grid_blocks,
@@ -122,12 +157,7 @@ hipError_t launch_batch(Kind kind, dq_dtype dtype, bool has_local, bool gather, 
                         uint32_t max_tiles_per_job, const Params &p, uint32_t grid_blocks,
                         hipStream_t stream);
 
-// Class counts that a search tells the host as soon as it has them (dq_bounds.hip): per bucket one word in pinned memory, counts of
-// 17 bits with a tag above them.  Null: not told.  No ticket for more buckets than a workspace holds.
-struct Announce {
-  uint64_t *host;
-  uint32_t tag;
-};
+constexpr uint32_t kAnnounced = 511;  // buckets
 hipError_t announce_begin(uint32_t n_buckets, hipStream_t stream, Announce *announce, void **ticket);
 void announce_drop(void *ticket);  // nothing has been enqueued
 

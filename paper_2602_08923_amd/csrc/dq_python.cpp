@@ -23,7 +23,8 @@ PyObject *g_error = nullptr;  // binding.DqError
   X(dq_packed_bytes) X(dq_compress) X(dq_dar_hop) X(dq_decompress) X(dq_decompress_restore) X(dq_mx_packed_bytes)       \
   X(dq_mx_compress) X(dq_mx_dar_hop) X(dq_mx_decompress) X(dq_replay_run) X(dq_replay_run_steps) X(dq_sg_stats) X(dq_stats_combine) \
   X(dq_allocate) X(dq_reorder) X(dq_reorder_mean) X(dq_restore) X(dq_status_str) X(dq_last_hip_error) X(dqx_bounds_begin) \
-  X(dqx_bounds_end) X(dqx_fetch) X(dqx_allocate_begin) X(dqx_allocate_end) X(dqx_stats_all)
+  X(dqx_bounds_end) X(dqx_fetch) X(dqx_allocate_begin) X(dqx_allocate_end) X(dqx_stats_all) \
+  X(dqx_whole_scratch_bytes) X(dqx_whole_run)
 struct Lib {
 #define X(name) decltype(&::name) name = nullptr;
   DQ_SYMBOLS(X)
@@ -500,6 +501,42 @@ PyObject *py_stats_all(PyObject *const *a, Py_ssize_t nargs) {  // list of tenso
   CALL(dqx_stats_all(p.data(), (uint32_t)n, t, n_sg, as<float>(m), as<float>(f), s));
   return pair(wrap(mu), wrap(F));
 }
+// ctx, list of tensors, n_sg_per_bucket, topology, max_code_bits, max_width, all_gather, means -> (result, ticket for the counts), or None if the
+// call is not one that is enqueued whole (what it is called with may be wrong: the steps say so)
+PyObject *py_whole(PyObject *const *a, Py_ssize_t nargs) {
+  DQ_ARGS(8)
+  const Py_ssize_t n = PyList_Check(a[1]) ? PyList_GET_SIZE(a[1]) : 0;
+  if (n < 2 || !PyLong_Check(a[4])) Py_RETURN_NONE;
+  const int64_t J = (int64_t)number(a[2]);
+  std::vector<const void *> p((size_t)n);
+  std::vector<at::Tensor> held;  // another thread may change the list
+  held.reserve((size_t)n);
+  for (Py_ssize_t w = 0; w < n; ++w) {
+    PyObject *o = PyList_GET_ITEM(a[1], w);
+    if (!THPVariable_Check(o)) Py_RETURN_NONE;
+    held.push_back(THPVariable_Unpack(o));
+    const at::Tensor &x = held.back(), &first = held.front();
+    if (!x.is_cuda() || !x.is_contiguous() || x.numel() != first.numel() || x.scalar_type() != first.scalar_type() || x.device() != first.device()) Py_RETURN_NONE;
+    p[(size_t)w] = x.data_ptr();
+    if (reinterpret_cast<uintptr_t>(p[(size_t)w]) % 16) Py_RETURN_NONE;
+  }
+  const at::Tensor &x = held.front();
+  if (J <= 0 || J > INT32_MAX || x.numel() == 0 || x.numel() % (J * 256) || x.numel() / (J * 256) > INT32_MAX || (x.scalar_type() != at::kFloat && x.scalar_type() != at::kBFloat16))
+    Py_RETURN_NONE;
+  int overflow = 0;
+  const long long budget = PyLong_AsLongLongAndOverflow(a[4], &overflow);
+  if (overflow || budget < 0) Py_RETURN_NONE;
+  const dqx_whole d = {(dq_topology)number(a[3]), local_dtype(x), (uint32_t)J, (uint32_t)(x.numel() / (J * 256)), (uint64_t)budget, (uint32_t)number(a[5]),
+                       (uint32_t)number(a[6]), (uint32_t)number(a[7])};
+  const dq_ctx *ctx = as<dq_ctx>(handle(a[0]));
+  const size_t bytes = L.dqx_whole_scratch_bytes(ctx, &d);
+  if (bytes == 0) Py_RETURN_NONE;
+  const at::Tensor scratch = make((int64_t)bytes, at::kByte, x), out = make(x.numel(), at::kFloat, x);
+  void *s = stream(), *w = scratch.data_ptr(), *o = out.data_ptr(), *ticket = nullptr;
+  CALL(dqx_whole_run(ctx, &d, p.data(), w, as<float>(o), s, &ticket));
+  PyObject *capsule = PyCapsule_New(new Ticket{ticket, s, d.n_sg_bucket, d.n_buckets}, kTicket, drop_ticket);
+  return capsule ? pair(wrap(out), capsule) : nullptr;
+}
 PyObject *py_fetch(PyObject *const *a, Py_ssize_t nargs) {  // int32 tensor of at most kFetchWords values -> list of its values
   DQ_ARGS(1)
   const at::Tensor &t = tensor(a[0]);
@@ -544,7 +581,7 @@ PyObject *guarded(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
 #define M(name) {#name, (PyCFunction)(void (*)(void))guarded<py_##name>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {M(init), M(compress), M(dar_hop), M(decompress), M(decompress_restore), M(mx_compress), M(mx_dar_hop),
                          M(mx_decompress), M(replay_used), M(replay_run), M(replay_run_steps), M(sg_stats), M(stats_combine), M(allocate), M(allocate_begin), M(allocate_end),
-                         M(reorder), M(reorder_mean), M(restore), M(check_index), M(stats_all), M(fetch), {nullptr, nullptr, 0, nullptr}};
+                         M(reorder), M(reorder_mean), M(restore), M(check_index), M(stats_all), M(whole), M(fetch), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_dqpy", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -96,6 +96,25 @@ struct ChunkInfo {
   size_t bytes;
 };
 
+// Few tiles per wave: the buckets' chunks of the same place, which have about the same widths, one after the other.  The order of all tiles
+// goes from narrow to wide once, and the waves that share a CU take them from different places of it, not from the same place of several
+// buckets.  (From some eight tiles per wave on they meet all widths anyway, and the order of the memory is the better one: recursive halving
+// over 16, eight buckets of 51,200 super-groups, 825 us against 838.)
+bool by_chunk_number(const dq::Walk &w, uint32_t n_buckets, uint64_t n_sg_bucket) {
+  return n_buckets > 1 && n_buckets * n_sg_bucket < 8ull * w.tile_sgs * w.blocks * w.waves;
+}
+
+// The schedule's part of W.
+void describe(uint32_t n, dq_topology topology, bool all_gather, dq::Walk *w) {
+  w->n = n;
+  while ((1u << w->log_n) < n) ++w->log_n;
+  w->encodes = all_gather ? n : n - 1;
+  w->first_kept = n > 3 ? n - 3 : 0;
+  w->chain = topology == DQ_CHAIN;
+  while ((1u << w->hops_log) < w->encodes && w->hops_log < 4) ++w->hops_log;
+  w->levels = topology == DQ_BUTTERFLY && w->log_n > 1 ? w->log_n - 1 : 0;
+}
+
 // The same schedule as one launch that carries every tile through all its hops (dq_walk.hip).
 void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, uint32_t n_chunks, uint64_t m, float *out, Plan *plan,
                size_t *off) {
@@ -103,12 +122,7 @@ void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, 
   const size_t es = elt_size(d->dtype);
   const uint64_t bucket_bytes = d->n_sg_bucket * 256 * es;
   dq::Walk &w = plan->w;
-  w.n = n;
-  while ((1u << w.log_n) < n) ++w.log_n;
-  w.encodes = d->all_gather ? n : n - 1;
-  w.first_kept = n > 3 ? n - 3 : 0;
-  w.chain = d->topology == DQ_CHAIN;
-  while ((1u << w.hops_log) < w.encodes && w.hops_log < 4) ++w.hops_log;
+  describe(n, d->topology, d->all_gather != 0, &w);
   plan->tree = d->topology == DQ_BUTTERFLY;
   bool raw = false;
   w.n_paths = d->n_buckets * n_chunks;
@@ -132,18 +146,20 @@ void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, 
       p.chunk = c;
       raw = raw || x.n_sg[3] != 0;
     }
-  w.levels = plan->tree && w.log_n > 1 ? w.log_n - 1 : 0;
   w.raw = raw;
-  plan->walk = dq::grid_walk(ctx->params, d->dtype, plan->tree, ctx->n_cu, plan->paths.data(), &w);
+  uint64_t tiles[3] = {0, 0, 0};
+  for (const dq::WalkPath &p : plan->paths)
+    for (uint32_t k : p.job.n_sg) {
+      tiles[0] += k;
+      tiles[1] += (k + 1) / 2;
+      tiles[2] += (k + 3) / 4;
+    }
+  plan->walk = dq::grid_walk(ctx->params, d->dtype, plan->tree, ctx->n_cu, tiles, &w);
   if (!plan->walk) {
     plan->paths.clear();
     return;
   }
-  if (d->n_buckets > 1 && (uint64_t)d->n_buckets * d->n_sg_bucket < 8ull * w.tile_sgs * w.blocks * w.waves) {
-    // Few tiles per wave: the buckets' chunks of the same place, which have about the same widths, one after the other.  The order of all tiles
-    // goes from narrow to wide once, and the waves that share a CU take them from different places of it, not from the same place of several
-    // buckets.  (From some eight tiles per wave on they meet all widths anyway, and the order of the memory is the better one: recursive halving
-    // over 16, eight buckets of 51,200 super-groups, 825 us against 838.)
+  if (by_chunk_number(w, d->n_buckets, d->n_sg_bucket)) {
     std::vector<dq::WalkPath> by_chunk;
     by_chunk.reserve(plan->paths.size());
     for (uint32_t c = 0; c < n_chunks; ++c)
@@ -460,7 +476,7 @@ dq_status build_plan(const dq_ctx *ctx, const dq_replay_desc *d, const void *con
 // into the runtime, for launches on other streams and under capture wait for them.  Without a stream, and for tables
 // beyond kPinned, the host waits until nothing can be reading the scratch and copies.  (What bounds the blocks are their trips over
 // PCIe, of which a CU has only so many under way: 25 KB take one block 8.0 us, sixteen 4.7.  A copy that the host waits for, besides needing
-// an idle scratch: the all-reduce of 8 workers' 8,192 super-groups took 103 us instead of 88 to 94.)
+// an idle scratch: an all-reduce of 8 workers' 8,192 super-groups that made such a plan took 103 us instead of 88 to 94.)
 constexpr size_t kPinned = 256u << 10;
 constexpr size_t kStagings = 8;
 constexpr uint32_t kUploadBlocks = 16, kUploadThreads = 128;
@@ -866,6 +882,115 @@ void dq_replay_destroy(dq_replay *plan) {
   if (!plan) return;
   for (hipEvent_t e : plan->events) (void)hipEventDestroy(e);
   delete plan;
+}
+
+}  // extern "C"
+
+// ---- a whole simulated all-reduce on the original tensors, enqueued without waiting: statistics, search, then (arrange) means, origins and the
+// tables of the replay, then the replay.  The host never needs the class counts to go on: how many waves there are follows from the
+// schedule's super-groups, and which tiles each takes is worked out on the device.  With the counts sent to the host and the plan made there the GPU
+// waited 15 us for it, and 5.4 for the tables' upload: 8 workers' ring of 8,192 super-groups in bf16 58.1 -> 39.5 us, 16 workers' of 1,936 60.9 -> 37.9,
+// recursive halving over 2 of 30,416 61.4 -> 47.2.
+namespace {
+struct WholePlan {
+  dq::Walk w = {};
+  dq::Tables t = {};
+  size_t paths = 0, shares = 0, grads = 0, mu = 0, F = 0, places = 0, counts = 0, mu_main = 0, origin = 0, bytes = 0;
+};
+// False: not for these kernels.
+bool plan_whole(const dq_ctx *ctx, const dqx_whole *d, WholePlan *p) {
+  const uint32_t n = ctx->cfg.n_workers, J = d->n_sg_bucket, nb = d->n_buckets;
+  const bool tree = d->topology == DQ_BUTTERFLY;
+  if ((d->topology != DQ_RING && !tree) || (d->dtype != DQ_F32 && d->dtype != DQ_BF16) || n < 2 || n > dq::kMostTensors || J == 0 || nb == 0 || nb > dq::kAnnounced || J % n ||
+      (tree && (n & (n - 1))) || J > dq::kMostSearched || (uint64_t)n * nb > dq::kMostTablePaths || (d->max_width != 8 && d->max_width != 16) ||
+      d->max_code_bits < 2ull * J)
+    return false;
+  const uint32_t m = J / n;
+  dq::Walk &w = p->w;
+  describe(n, d->topology, d->all_gather != 0, &w);
+  w.first_kept = n - 1;  // nobody asks for messages
+  w.raw = d->max_width == 16;
+  w.n_paths = n * nb;
+  // at most: a bucket's three edges between widths each begin a tile anew
+  const uint64_t tiles[3] = {(uint64_t)J * nb, (uint64_t)nb * (n * ((m + 1) / 2) + 3), (uint64_t)nb * (n * ((m + 3) / 4) + 3)};
+  if (!dq::grid_walk(ctx->params, d->dtype, tree, ctx->n_cu, tiles, &w)) return false;
+  dq::Tables &t = p->t;
+  t.n_chunks = n;
+  t.n_buckets = nb;
+  t.chunk_sgs = m;
+  t.bucket_sgs = J;
+  t.by_chunk = by_chunk_number(w, nb, J);
+  t.entry_bytes = (uint32_t)elt_size(d->dtype);
+  t.waves = w.blocks * w.waves;
+  t.tile_log = w.tile_sgs / 2;
+  t.cost = dq::costs_of(d->dtype, tree, n);
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = off;
+    off = align_up(off + bytes, 256);
+    return at;
+  };
+  const size_t sgs = (size_t)J * nb;
+  p->paths = take(w.n_paths * sizeof(dq::WalkPath));
+  p->shares = take(((size_t)t.waves + 1) * sizeof(dq::WalkShare));
+  p->grads = take(2 * (size_t)n * sizeof(void *));
+  p->mu = take(4 * sgs);
+  p->F = take(4 * sgs);
+  p->places = take(4 * sgs);
+  p->counts = take(20 * (size_t)nb);
+  p->mu_main = take(4 * sgs);
+  p->origin = take(4 * sgs);
+  p->bytes = off;
+  return true;
+}
+}  // namespace
+
+extern "C" {
+
+size_t dqx_whole_scratch_bytes(const dq_ctx *ctx, const dqx_whole *desc) {
+  WholePlan p;
+  return ctx && desc && plan_whole(ctx, desc, &p) ? p.bytes : 0;
+}
+
+dq_status dqx_whole_run(const dq_ctx *ctx, const dqx_whole *desc, const void *const *tensors, void *scratch, float *out, void *hip_stream, void **ticket) {
+  WholePlan p;
+  *ticket = nullptr;
+  if (!ctx || !desc || !tensors || !scratch || !out || !plan_whole(ctx, desc, &p)) return DQ_EINVAL;
+  if ((reinterpret_cast<uintptr_t>(scratch) & 255u) || (reinterpret_cast<uintptr_t>(out) & 15u)) return DQ_EALIGN;
+  uint8_t *const base = static_cast<uint8_t *>(scratch);
+  auto floats = [&](size_t at) { return reinterpret_cast<float *>(base + at); };
+  auto words = [&](size_t at) { return reinterpret_cast<uint32_t *>(base + at); };
+  const hipStream_t s = (hipStream_t)hip_stream;
+  const uint32_t J = desc->n_sg_bucket, nb = desc->n_buckets;
+  const bool means = desc->means != 0;
+  dq::Announce announce = {nullptr, 0};
+  const hipError_t e = dq::announce_begin(nb, s, &announce, ticket);
+  if (e != hipSuccess) return dq::hip_status(e);
+  p.t.paths = reinterpret_cast<dq::WalkPath *>(base + p.paths);
+  p.t.shares = reinterpret_cast<dq::WalkShare *>(base + p.shares);
+  p.t.out = out;
+  p.t.origin = words(p.origin);
+  p.t.mu = means ? floats(p.mu_main) : nullptr;
+  const void **grads = reinterpret_cast<const void **>(base + p.grads);
+  p.w.grads = grads;
+  bool searched = false;
+  dq_status st = *ticket ? dq::stats_all(tensors, ctx->cfg.n_workers, desc->dtype, (uint64_t)J * nb, floats(p.mu), floats(p.F), grads, s) : DQ_EINVAL;
+  if (st == DQ_OK) {
+    searched = true;
+    st = dq::search(floats(p.F), J, nb, desc->max_code_bits, desc->max_width, words(p.places), words(p.counts), announce, s);
+  }
+  if (st == DQ_OK)
+    st = dq::arrange(floats(p.F), means ? floats(p.mu) : nullptr, J, nb, desc->max_width, words(p.counts), words(p.places),
+                     means ? floats(p.mu_main) : nullptr, words(p.origin), p.t, s);
+  if (st == DQ_OK)
+    st = dq::hip_status(dq::launch_walk(desc->dtype, desc->topology == DQ_BUTTERFLY, means, p.t.paths, p.t.shares, p.w, ctx->params, s));
+  if (st != DQ_OK && *ticket) {  // a search that runs still writes to the ticket's workspace: its counts are waited for
+    std::vector<uint32_t> rows(4 * (size_t)nb);
+    if (searched) (void)dqx_allocate_end(*ticket, J, nb, rows.data(), hip_stream);
+    else dq::announce_drop(*ticket);
+    *ticket = nullptr;
+  }
+  return st;
 }
 
 }  // extern "C"

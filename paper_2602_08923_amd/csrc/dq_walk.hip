@@ -369,13 +369,6 @@ hipError_t walk_static_lds(size_t *bytes) {
   return e != hipSuccess ? e : static_lds_of<uint16_t>(bytes);
 }
 
-static uint64_t count_tiles(const WalkPath *paths, uint32_t n_paths, uint32_t sgs) {
-  uint64_t tiles = 0;
-  for (uint32_t p = 0; p < n_paths; ++p)
-    for (int w = 0; w < 4; ++w) tiles += (paths[p].job.n_sg[w] + sgs - 1) / sgs;
-  return tiles;
-}
-
 // The launch of W's schedule with tiles of W->tile_sgs super-groups.  *resident: waves that a CU holds at once.  False: no block fits.
 static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, uint64_t tiles, Walk *W, uint32_t *resident) {
   constexpr uint32_t kLds = 160u * 1024, kGranule = 1280;  // LDS is given out in 128 pieces
@@ -449,9 +442,9 @@ static uint32_t tile_for(uint32_t n, bool f32, bool tree, uint32_t n_cu, uint64_
   return per_cu <= one ? 1 : per_cu <= two ? 2 : kWaveSGs;
 }
 
-bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const WalkPath *paths, Walk *W) {
+bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const uint64_t tiles_of[3], Walk *W) {
   const bool f32 = dtype == DQ_F32;
-  const uint64_t super_groups = count_tiles(paths, W->n_paths, 1);
+  const uint64_t super_groups = tiles_of[0];
   if (super_groups == 0) return false;
   const uint32_t wanted = tile_for(W->n, f32, tree, n_cu, super_groups);
   Walk best = *W;
@@ -461,7 +454,7 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
     Walk w = *W;
     w.tile_sgs = sgs;
     uint32_t resident = 0;
-    const uint64_t tiles = count_tiles(paths, W->n_paths, sgs);
+    const uint64_t tiles = tiles_of[sgs / 2];
     if (!grid_of_tiles(P, f32, tree, n_cu, tiles, &w, &resident)) continue;
     const uint64_t time = wanted ? 0 : tree_time(W->n, n_cu, sgs, sgs == kWaveSGs ? tiles : (super_groups + sgs - 1) / sgs, resident);
     if (!found || time <= best_time) {
@@ -472,7 +465,7 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
   }
   if (!found) return false;
   *W = best;
-  const uint64_t tiles = count_tiles(paths, W->n_paths, W->tile_sgs), waves = (uint64_t)W->blocks * W->waves;
+  const uint64_t tiles = tiles_of[W->tile_sgs / 2], waves = (uint64_t)W->blocks * W->waves;
   const bool spread = tree && W->n > 4 && W->tile_sgs == kWaveSGs && tiles < 8 * waves;
   // (Not with 16-bit tiles, the cheapest, at the end: ring of 6, three buckets of 4,476, a quarter of them 16-bit, 15.0 us and 15.8 reversed.)
   W->order = spread ? n_cu : tiles <= waves && !W->raw ? kReversed : 0;
@@ -492,12 +485,11 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
 // A tile's costs: what its instructions take beside the memory's time, which all widths have alike, measured as the ratios that are fastest: 1.8 to 2.2 with
 // bf16 tensors of five workers and more, 1.1 to 1.25 where a hop moves more bytes (fp32, or a result of 4 bytes per few workers).  (12/15/16
 // instead of 12/24/26 for the first ring above: 64.2.)
-namespace {
-struct Costs { uint32_t of[4]; };
-Costs costs_of(bool f32, bool tree, uint32_t n) {
-  if (f32 || n <= 4) return Costs{{12, 14, 15, 12}};
+Costs costs_of(dq_dtype dtype, bool tree, uint32_t n) {
+  if (dtype == DQ_F32 || n <= 4) return Costs{{12, 14, 15, 12}};
   return tree ? Costs{{12, 20, 22, 12}} : Costs{{12, 24, 26, 12}};
 }
+namespace {
 // The most tiles per wave of every width (0: there is none of it), at most `waves` waves.
 void most_per_wave(const uint64_t tiles[4], const uint32_t cost[4], uint32_t waves, uint64_t most[4]) {
   auto fits = [&] {
@@ -548,7 +540,7 @@ void split_walk(const WalkPath *paths, dq_dtype dtype, bool tree, const Walk &W,
   uint64_t tiles[4] = {0, 0, 0, 0}, most[4], cost[4], total = 0;
   for (uint32_t p = 0; p < W.n_paths; ++p)
     for (int w = 0; w < 4; ++w) tiles[w] += (paths[p].job.n_sg[w] + sgs - 1) / sgs;
-  const Costs c = costs_of(dtype == DQ_F32, tree, W.n);
+  const Costs c = costs_of(dtype, tree, W.n);
   most_per_wave(tiles, c.of, n, most);
   // Equal shares of cost total / n hold at most `most` tiles of a width that costs at least that over `most`.  The costs rise until that is so, each
   // round by less; where the waves are just enough it is so at the cost of the fullest.

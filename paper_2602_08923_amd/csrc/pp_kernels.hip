@@ -110,12 +110,13 @@ __global__ void __launch_bounds__(kThreads) k_stats(const void *x, uint64_t n_sg
 
 // k_stats of every worker and k_combine in one pass: a simulated all-reduce, which holds all workers' tensors, has no use for
 // the single workers' statistics.  One launch instead of n + 1.
-constexpr uint32_t kStatsWorkers = 256;
 struct WorkerTensors {
-  const void *x[kStatsWorkers];
+  const void *x[dq::kMostTensors];
 };
 template <typename LT>
-__global__ void __launch_bounds__(kThreads) k_stats_all(WorkerTensors W, uint32_t n, uint64_t n_sg, float *mu, float *F) {
+__global__ void __launch_bounds__(kThreads) k_stats_all(WorkerTensors W, uint32_t n, uint64_t n_sg, float *mu, float *F, const void **grads) {
+  if (grads && blockIdx.x == 0)
+    for (uint32_t i = threadIdx.x; i < 2 * n; i += kThreads) grads[i] = W.x[i < n ? i : i - n];
   const uint32_t lane = threadIdx.x & 63u;
   const uint64_t wave = (uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   const uint64_t n_waves = (uint64_t)gridDim.x * (kThreads / 64);
@@ -198,19 +199,17 @@ __device__ __forceinline__ int32_t p16_from(uint32_t pattern, bool allow16) {
 // class + members in earlier waves + members in lower lanes.  The search left each row's four first places where the
 // row's own positions go (read here before they are overwritten); the last row, which may be shorter than that, counts
 // back from the classes' ends.  (A block that counted the rows before its own took 12.5 us for 51,200 super-groups.)
-__global__ void __launch_bounds__(kAllocThreads) k_alloc_positions(const float *F_all, uint32_t J, bool allow16,
-                                                                   const uint32_t *counts_all, uint8_t *widths_all,
-                                                                   uint32_t *pos_all) {
-  __shared__ uint32_t mine_w[kAllocWaves][4];
+struct Placed {
+  uint32_t k, at;  // class (4: beyond the bucket), position
+};
+__device__ __forceinline__ Placed place_row(const float *F, uint32_t J, bool allow16, const uint32_t *cnt, const uint32_t *places, uint32_t row,
+                                            bool last, uint32_t (*mine_w)[4]) {
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-  const uint64_t first = (uint64_t)blockIdx.y * J;
-  const uint32_t *cnt = counts_all + 5ull * blockIdx.y;
-  const uint32_t j = blockIdx.x * kAllocThreads + tid;
-  const bool last = blockIdx.x + 1 == gridDim.x;
-  const float f = gld<float>(F_all + first + min(j, J - 1));
+  const uint32_t j = row * kAllocThreads + tid;
+  const float f = gld<float>(F + min(j, J - 1));
   uint32_t at_row[4];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) at_row[c] = last ? gld<uint32_t>(cnt + c) : gld<uint32_t>(pos_all + first + (uint64_t)blockIdx.x * kAllocThreads + c);
+  for (int c = 0; c < 4; ++c) at_row[c] = last ? gld<uint32_t>(cnt + c) : gld<uint32_t>(places + (uint64_t)row * kAllocThreads + c);
   const uint32_t pattern = gld<uint32_t>(cnt + 4);
   const int32_t p8 = (int32_t)pattern, p4 = p4_from(pattern), p16 = p16_from(pattern, allow16);
   const uint32_t k = j < J ? class_of(pattern_of(f), p4, p8, p16) : 4u;
@@ -220,24 +219,34 @@ __global__ void __launch_bounds__(kAllocThreads) k_alloc_positions(const float *
     for (int i = 0; i < 4; ++i) mine_w[wave][i] = (uint32_t)__builtin_popcountll(b[i]);
   }
   __syncthreads();
-  if (k < 4) {
-    uint32_t before = 0, all = 0;
+  if (k == 4) return Placed{4u, 0u};
+  uint32_t before = 0, all = 0;
 #pragma unroll
-    for (int w = 0; w < kAllocWaves; ++w) {
-      before += (uint32_t)w < wave ? mine_w[w][k] : 0u;
-      all += mine_w[w][k];
-    }
-    uint32_t at = k == 0 ? at_row[0] : (k == 1 ? at_row[1] : (k == 2 ? at_row[2] : at_row[3]));
-    if (last) {  // at_row holds the classes' sizes: the class's end less what this row adds to it
-      at = at_row[0] - all;
-      if (k > 0) at += at_row[1];
-      if (k > 1) at += at_row[2];
-      if (k > 2) at += at_row[3];
-    }
-    const uint64_t mine = k == 0 ? b[0] : (k == 1 ? b[1] : (k == 2 ? b[2] : b[3]));
-    at += before + __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
-    gst<uint8_t>(widths_all + first + j, (uint8_t)(2u << k));
-    gst<uint32_t>(pos_all + first + j, at);
+  for (int w = 0; w < kAllocWaves; ++w) {
+    before += (uint32_t)w < wave ? mine_w[w][k] : 0u;
+    all += mine_w[w][k];
+  }
+  uint32_t at = k == 0 ? at_row[0] : (k == 1 ? at_row[1] : (k == 2 ? at_row[2] : at_row[3]));
+  if (last) {  // at_row holds the classes' sizes: the class's end less what this row adds to it
+    at = at_row[0] - all;
+    if (k > 0) at += at_row[1];
+    if (k > 1) at += at_row[2];
+    if (k > 2) at += at_row[3];
+  }
+  const uint64_t mine = k == 0 ? b[0] : (k == 1 ? b[1] : (k == 2 ? b[2] : b[3]));
+  return Placed{k, at + before + __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u))};
+}
+
+__global__ void __launch_bounds__(kAllocThreads) k_alloc_positions(const float *F_all, uint32_t J, bool allow16,
+                                                                   const uint32_t *counts_all, uint8_t *widths_all,
+                                                                   uint32_t *pos_all) {
+  __shared__ uint32_t mine_w[kAllocWaves][4];
+  const uint64_t first = (uint64_t)blockIdx.y * J;
+  const uint32_t j = blockIdx.x * kAllocThreads + threadIdx.x;
+  const Placed x = place_row(F_all + first, J, allow16, counts_all + 5ull * blockIdx.y, pos_all + first, blockIdx.x, blockIdx.x + 1 == gridDim.x, mine_w);
+  if (x.k < 4) {
+    gst<uint8_t>(widths_all + first + j, (uint8_t)(2u << x.k));
+    gst<uint32_t>(pos_all + first + j, x.at);
   }
 }
 
@@ -576,6 +585,223 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
   }
 }
 
+// Behind the search of an all-reduce that replays on the original tensors: what k_alloc_positions and k_reorder_mean do between them, but for the
+// widths and positions themselves, which nobody reads, and in the first block the replay's tables.
+//
+// The tables, as plan_walk and split_walk (dq_walk.hip) make them on the host: a thread per path, then the most tiles per wave of every width, then a
+// share per thread and turn.  What bounds it is latency: a chain of 5.7 us, beside the other blocks' 3.6 (8 workers, 8,192 super-groups).  Divisions are products with v_rcp_f32's
+// result: that the fullest wave's tiles come out one more than they might be costs nothing but time, and any costs give shares that
+// cover the tiles once, as a share ends where the next begins.  Sums of costs are whole numbers below 2^53, so doubles hold them exactly.
+__device__ __forceinline__ float quick(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ float lane_f(float x, int l) { return u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(x), l)); }
+
+// Costs of a tile by width such that equal shares hold at most the bounded number of tiles (split_walk); by one wave.
+__device__ __forceinline__ void raise_costs(const float (&tiles)[4], const dq::Costs &c, float waves, uint32_t lane, float (&cost)[4], float &fullest) {
+  float each[4], most[4], all = 0.0f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    each[w] = (float)c.of[w];
+    all += tiles[w] * each[w];
+  }
+  const float mean = floorf(all * quick(waves)), step = 1.0f + floorf(mean * (1.0f / 64.0f));
+  // the least cost of the fullest wave: 64 candidates at a time
+  float s = 0.0f;
+  for (float from = mean; ; from += 64.0f * step) {
+    const float mine = from + step * (float)lane;
+    float need = 0.0f;
+    bool ok = true;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float k = floorf((mine + 0.5f) * quick(each[w]));
+      ok = ok && (tiles[w] == 0.0f || k >= 1.0f);
+      need += tiles[w] * quick(fmaxf(k, 1.0f));
+    }
+    const uint64_t fit = __ballot(ok && need <= waves * (1.0f - 1e-6f));
+    if (fit || from > all + 64.0f) {  // a wave that could take all of it: such a cost always fits four waves
+      s = from + step * (float)(fit ? __builtin_ctzll(fit) : 63);
+      break;
+    }
+  }
+  fullest = 0.0f;
+  float need = 0.0f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    most[w] = fmaxf(floorf((s + 0.5f) * quick(each[w])), 1.0f);
+    need += tiles[w] * quick(most[w]);
+  }
+  // each most as small as the waves allow, the dearest first
+  bool done[4] = {tiles[0] == 0.0f, tiles[1] == 0.0f, tiles[2] == 0.0f, tiles[3] == 0.0f};
+  for (int turn = 0; turn < 4; ++turn) {
+    int at = -1;
+    float dearest = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (!done[w] && most[w] * each[w] > dearest) {
+        dearest = most[w] * each[w];
+        at = w;
+      }
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (w == at) {
+        done[w] = true;
+        const float others = need - tiles[w] * quick(most[w]), room = waves * (1.0f - 1e-6f) - others;
+        if (room > 0.0f) {
+          const float least = fmaxf(ceilf(tiles[w] * quick(room)), 1.0f);
+          if (least < most[w]) most[w] = least;
+        }
+        need = others + tiles[w] * quick(most[w]);
+      }
+  }
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    cost[w] = each[w];
+    if (tiles[w] != 0.0f) fullest = fmaxf(fullest, most[w] * each[w]);
+  }
+  for (int round = 0; round <= 8; ++round) {
+    float share = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) share += tiles[w] * cost[w];
+    share = round < 8 ? share * quick(waves) : fullest;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) cost[w] = fmaxf(cost[w], share * quick(most[w]));
+  }
+}
+
+struct TableSpace {
+  double upto[dq::kMostTablePaths];  // cost of the paths before
+  uint32_t tiles[dq::kMostTablePaths][4];
+  uint32_t total[4], cost[4];
+  double wave_sum[kAllocWaves];
+};
+__device__ __forceinline__ void make_tables(const dq::Tables &T, const uint32_t *counts_all, TableSpace &L) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t n_paths = T.n_chunks * T.n_buckets;
+  if (tid < 4) L.total[tid] = 0;
+  __syncthreads();
+  uint32_t t[4] = {0, 0, 0, 0};
+  if (wave * 64 < n_paths) {
+    const uint32_t p = min(tid, n_paths - 1);
+    const uint32_t b = T.by_chunk ? p % T.n_buckets : p / T.n_chunks, c = T.by_chunk ? p / T.n_buckets : p % T.n_chunks;
+    const uint32_t *cnt = counts_all + 5ull * b;
+    const uint32_t lo = c * T.chunk_sgs, hi = lo + T.chunk_sgs;
+    uint32_t n_sg[4], edge = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const uint32_t end = edge + gld<uint32_t>(cnt + w), from = max(lo, edge), to = min(hi, end);
+      n_sg[w] = to > from ? to - from : 0u;
+      edge = end;
+    }
+    if (tid < n_paths) {
+      const uint64_t sg = (uint64_t)b * T.bucket_sgs + lo;
+      dq::WalkPath x = {};
+      x.job.local = reinterpret_cast<const void *>((uintptr_t)((uint64_t)b * T.bucket_sgs * kSG * T.entry_bytes));
+      x.job.mu = T.mu ? T.mu + sg : nullptr;
+      x.job.src = T.origin + sg;
+      x.job.out = T.out + (uint64_t)b * T.bucket_sgs * kSG;
+      x.job.dest = T.origin + sg;
+      x.job.back = x.job.mu;
+      x.job.first_sg = sg;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        x.job.n_sg[w] = n_sg[w];
+        t[w] = (n_sg[w] + (1u << T.tile_log) - 1u) >> T.tile_log;
+        L.tiles[tid][w] = t[w];
+      }
+      x.chunk = c;
+      T.paths[tid] = x;
+    }
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const uint32_t sum = __builtin_amdgcn_readlane(wave_scan(t[w]), 63);
+      if (lane == 0) atomicAdd(&L.total[w], sum);
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+    float tiles[4], cost[4], fullest;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) tiles[w] = (float)L.total[w];
+    raise_costs(tiles, T.cost, (float)T.waves, lane, cost, fullest);
+    const float unit = fullest < 16384.0f ? 65536.0f : 128.0f;
+    if (lane < 4) L.cost[lane] = (uint32_t)ceilf(unit * (lane == 0 ? cost[0] : lane == 1 ? cost[1] : lane == 2 ? cost[2] : cost[3]));
+  }
+  __syncthreads();
+  double mine = 0.0, sum;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) mine += (double)t[w] * (double)L.cost[w];
+  sum = mine;
+  if (wave * 64 < n_paths) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const double up = __shfl_up(sum, d, 64);
+      if (lane >= (uint32_t)d) sum += up;
+    }
+  }
+  if (lane == 63) L.wave_sum[wave] = sum;
+  __syncthreads();
+  double before = 0.0, total = 0.0;
+#pragma unroll
+  for (int w = 0; w < kAllocWaves; ++w) {
+    before += (uint32_t)w < wave ? L.wave_sum[w] : 0.0;
+    total += L.wave_sum[w];
+  }
+  if (tid < n_paths) L.upto[tid] = before + sum - mine;
+  __syncthreads();
+  const double ratio = total / (double)T.waves;
+  for (uint32_t v = tid; v <= T.waves; v += kAllocThreads) {
+    uint32_t path = n_paths, tile = 0;
+    if (v < T.waves) {
+      const double want = floor((double)v * ratio);
+      path = 0;
+      for (uint32_t span = n_paths; span > 1;) {  // the last path that begins at or before `want`
+        const uint32_t half = span / 2;
+        if (L.upto[path + half] <= want) path += half;
+        span -= half;
+      }
+      double rest = want - L.upto[path];
+      bool found = false;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const uint32_t n = L.tiles[path][w];
+        const double each = (double)L.cost[w];
+        if (!found && n) {
+          if (rest <= (double)(n - 1) * each) {
+            tile += min((uint32_t)ceil(rest / each), n - 1);
+            found = true;
+          } else {
+            rest = fmax(0.0, rest - (double)n * each);
+            tile += n;
+          }
+        }
+      }
+      if (!found) {  // within the path's last tile
+        ++path;
+        tile = 0;
+      }
+    }
+    T.shares[v] = dq::WalkShare{path, tile};
+  }
+}
+
+__global__ void __launch_bounds__(kAllocThreads) k_arrange(const float *F_all, const float *mu_all, uint32_t J, bool allow16, const uint32_t *counts_all,
+                                                           const uint32_t *places_all, float *mu_main, uint32_t *origin, dq::Tables T) {
+  __shared__ uint32_t mine_w[kAllocWaves][4];
+  __shared__ TableSpace space;
+  if (blockIdx.x == 0) {
+    if (blockIdx.y == 0) make_tables(T, counts_all, space);
+    return;
+  }
+  const uint32_t row = blockIdx.x - 1;
+  const uint64_t first = (uint64_t)blockIdx.y * J;
+  const uint32_t j = row * kAllocThreads + threadIdx.x;
+  const float m = mu_all ? gld<float>(mu_all + first + min(j, J - 1)) : 0.0f;
+  const Placed x = place_row(F_all + first, J, allow16, counts_all + 5ull * blockIdx.y, places_all + first, row, row + 2 == gridDim.x, mine_w);
+  if (x.k < 4) {
+    if (mu_all) gst<float>(mu_main + first + x.at, x.k == 3 ? 0.0f : m);
+    gst<uint32_t>(origin + first + x.at, j);
+  }
+}
+
 // Buckets of more than 65,536 super-groups: the norms are read again in every round of a bisection, widths and positions
 // are written here, 64 rows of 1024 at a time.
 __global__ void __launch_bounds__(kAllocThreads) k_allocate_large(const float *F_all, uint32_t J, uint64_t max_code_bits,
@@ -822,6 +1048,42 @@ dq_status launched() { return dq::hip_status(hipGetLastError()); }
 
 }  // namespace
 
+namespace dq {
+
+dq_status stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dtype, uint64_t n_sg, float *mu, float *F, const void **grads,
+                    hipStream_t s) {
+  if (n_sg == 0) return DQ_OK;
+  if (!tensors || !mu || !F || n_workers == 0 || (dtype != DQ_F32 && dtype != DQ_BF16)) return DQ_EINVAL;
+  if (n_workers > kMostTensors) return DQ_EUNSUPPORTED;
+  WorkerTensors W = {};
+  for (uint32_t w = 0; w < n_workers; ++w) {
+    if (!aligned(tensors[w], 16)) return DQ_EALIGN;
+    W.x[w] = tensors[w];
+  }
+  const uint32_t blocks = stream_blocks(4 * (kThreads / 64), n_sg);
+  if (dtype == DQ_F32) hipLaunchKernelGGL(k_stats_all<float>, dim3(blocks), dim3(kThreads), 0, s, W, n_workers, n_sg, mu, F, grads);
+  else hipLaunchKernelGGL(k_stats_all<uint16_t>, dim3(blocks), dim3(kThreads), 0, s, W, n_workers, n_sg, mu, F, grads);
+  return launched();
+}
+
+static_assert(kMostSearched == (uint32_t)kRegs * kAllocThreads && kMostTablePaths <= (uint32_t)kAllocThreads, "a register per norm, a thread per path");
+dq_status search(const float *F, uint32_t J, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width, uint32_t *places, uint32_t *counts,
+                 Announce announce, hipStream_t s) {
+  const bool allow16 = max_width == 16, aside = J > 16u * kAllocThreads;
+  const auto kernel = aside ? (allow16 ? k_search<true, true> : k_search<false, true>) : (allow16 ? k_search<true, false> : k_search<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, places, counts, announce);
+  return launched();
+}
+
+dq_status arrange(const float *F, const float *mu, uint32_t J, uint32_t n_buckets, uint32_t max_width, const uint32_t *counts, const uint32_t *places,
+                  float *mu_main, uint32_t *origin, const Tables &tables, hipStream_t s) {
+  const uint32_t rows = (J + kAllocThreads - 1) / kAllocThreads;
+  hipLaunchKernelGGL(k_arrange, dim3(rows + 1, n_buckets), dim3(kAllocThreads), 0, s, F, mu, J, max_width == 16, counts, places, mu_main, origin, tables);
+  return launched();
+}
+
+}  // namespace dq
+
 extern "C" {
 
 dq_status dq_sg_stats(const void *x, dq_dtype dtype, uint64_t n_sg, float *mu_out, float *F_out, void *hip_stream) {
@@ -861,19 +1123,7 @@ dq_status dq_stats_combine(const float *mu_all, const float *F_all, uint32_t n_w
 
 dq_status dqx_stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dtype, uint64_t n_sg, float *mu, float *F,
                         void *hip_stream) {
-  if (n_sg == 0) return DQ_OK;
-  if (!tensors || !mu || !F || n_workers == 0 || (dtype != DQ_F32 && dtype != DQ_BF16)) return DQ_EINVAL;
-  if (n_workers > kStatsWorkers) return DQ_EUNSUPPORTED;
-  WorkerTensors W = {};
-  for (uint32_t w = 0; w < n_workers; ++w) {
-    if (!aligned(tensors[w], 16)) return DQ_EALIGN;
-    W.x[w] = tensors[w];
-  }
-  const uint32_t blocks = stream_blocks(4 * (kThreads / 64), n_sg);
-  hipStream_t s = (hipStream_t)hip_stream;
-  if (dtype == DQ_F32) hipLaunchKernelGGL(k_stats_all<float>, dim3(blocks), dim3(kThreads), 0, s, W, n_workers, n_sg, mu, F);
-  else hipLaunchKernelGGL(k_stats_all<uint16_t>, dim3(blocks), dim3(kThreads), 0, s, W, n_workers, n_sg, mu, F);
-  return launched();
+  return dq::stats_all(tensors, n_workers, dtype, n_sg, mu, F, nullptr, (hipStream_t)hip_stream);
 }
 
 static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits,
@@ -890,8 +1140,8 @@ static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_b
     const uint64_t off = (uint64_t)b0 * J;
     uint32_t *const cnt = counts + 5ull * b0;
     if (rows <= (uint32_t)kRegs) {
-      const auto search = rows > 16 ? (allow16 ? k_search<true, true> : k_search<false, true>) : (allow16 ? k_search<true, false> : k_search<false, false>);
-      hipLaunchKernelGGL(search, dim3(nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, pos + off, cnt, announce);
+      const dq_status st = dq::search(F + off, J, nb, max_code_bits, max_width, pos + off, cnt, announce, s);
+      if (st != DQ_OK) return st;
       hipLaunchKernelGGL(k_alloc_positions, dim3(rows, nb), dim3(kAllocThreads), 0, s, F + off, J, allow16, cnt, widths + off, pos + off);
     } else
       hipLaunchKernelGGL(k_allocate_large, dim3(nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, allow16, widths + off, pos + off, cnt);

@@ -337,6 +337,32 @@ def test_allreduces_back_to_back_on_a_side_stream_keep_their_own_tables(dev, opt
         assert torch.equal(x.view(torch.int32), y.view(torch.int32)), f"call {k}"
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("topology,n,J,nb,bits,max_width", [
+    ("ring", 2, 2, 1, 4.0, 8), ("ring", 3, 1023, 2, 5.0, 16), ("ring", 5, 1025, 1, 3.3, 8), ("ring", 8, 8192, 1, 4.6875, 8), ("ring", 61, 61, 3, 8.0, 16),
+    ("ring", 7, 16387, 1, 5.0, 8), ("ring", 6, 20004, 2, 6.0, 16), ("ring", 64, 128, 16, 4.0, 8), ("ring", 64, 128, 17, 4.0, 8), ("ring", 256, 512, 1, 4.5, 8),
+    ("ring", 257, 514, 1, 4.5, 8), ("ring", 4, 65536, 1, 3.0, 8), ("ring", 4, 65540, 1, 3.0, 8), ("ring", 2, 4, 500, 4.0, 8), ("ring", 2, 4, 512, 4.0, 8),
+    ("butterfly", 2, 4096, 3, 5.5, 8), ("butterfly", 4, 4, 1, 3.0, 8), ("butterfly", 8, 8200, 1, 6.5, 16), ("butterfly", 16, 20656, 1, 4.3, 8),
+    ("butterfly", 64, 4096, 2, 4.0, 16), ("butterfly", 128, 640, 1, 3.5, 8),
+])
+def test_an_allreduce_enqueued_whole_equals_its_steps(dev, topology, n, J, nb, bits, max_width, dtype):
+    """Rows of 1,024 and their remainders, one path to 1,024 (and the first sizes that go step by step: 1,025 paths, 257 tensors, 65,537 super-groups,
+    512 buckets); all gathered or not, with means or without, norms alike and masses of equal ones."""
+    J = J // n * n
+    for seed, spread in ((1, 3.0), (2, 0.0)):
+        grads = gradients(n, J * nb, dtype, dev, seed + J)
+        scale = torch.exp(spread * torch.randn(J * nb, 1, device=dev, generator=torch.Generator(dev).manual_seed(seed)))
+        grads = [(g.reshape(-1, 256).float() * scale).to(dtype).reshape(-1).contiguous() for g in grads]
+        if seed == 2:
+            grads = [g.reshape(-1, 256)[:1].repeat(J * nb, 1).reshape(-1).contiguous() for g in grads]
+        for options in ({"all_gather": True}, {"all_gather": False, "subtract_mean": False}):
+            kw = dict(topology=TOPO[topology], seed=seed, n_sg_bucket=J, max_width=max_width, **options)
+            got, info = allreduce.simulated_allreduce(grads, bits, **kw)
+            want, parts = allreduce.simulated_allreduce(grads, bits, fused_reorder=False, **kw)
+            assert info == parts
+            assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+
+
 def test_allreduces_of_several_threads_on_their_own_streams(dev):
     calls = allreduce_inputs(dev, len(ALLREDUCE))
     want = [allreduce.simulated_allreduce(g, 6.0, seed=k, **o)[0].clone() for k, (g, o) in enumerate(zip(calls, ALLREDUCE))]
