@@ -255,19 +255,21 @@ __global__ void __launch_bounds__(kAllocThreads) k_alloc_positions(const float *
 //
 // Wanted: the smallest fp32 pattern in [1, +inf] whose allocation fits (the host has checked 2J <= budget).  With
 // c8, c4, c16 = norms at or above T_{4,8} and its tied thresholds, cost = 2J + 4 c8 + 2 c4 + 8 c16 never increases with
-// the threshold, so a bracket (lo does not fit or is 0, hi fits) is narrowed level by level: a histogram of the patterns
-// around each of the three thresholds, suffix counts, and for the bin boundaries of the bracket a lower and an upper
-// bound of the cost (c8 is exact there, c4 and c16 lie between the counts of two bins).  The first level takes the top
-// 11 bits of everything, the second the 1 to 3 bins of 2^20 that are left in up to 4096, the third single patterns.  The
-// tied thresholds' brackets end on bins of the level before, so that the norms above them are known from its counts.
+// the threshold, so a bracket (lo does not fit or is 0, hi fits) is narrowed.  The first level is a histogram of the top 11 bits of all norms: its
+// suffix counts give at the bins' boundaries a lower and an upper bound of the cost (c8 is exact there, c4 and c16 lie between the counts of two
+// bins), which leave 1 to 3 bins of 2^20 patterns.  The next two look at the places where the cost falls: a norm v costs 4 bits less beyond the threshold v,
+// 2 less beyond the last threshold T whose tied one is at most v, 8 less beyond the last whose other tied one is.  One histogram of those places,
+// weighted, has the cost at every boundary as a suffix sum: up to 4096 bins, then 1024 of single patterns.
 //
 // What bounds it: one CU's vector ALU and LDS (51,200 norms are 800 wave instructions for every instruction of a pass,
 // and an LDS atomic of a wave takes 12 cycles) and, for small buckets, the barriers and scans of the levels.
-// 51,200 norms take 21 us, 8192 10 us; a gather of the candidates (two LDS atomics with a result per row) with a
-// bisection, a barrier per step, took 46 and 35 us.
-constexpr uint32_t kBins8 = 4096, kBins4 = 6144, kBins16 = 8192;  // brackets of 3 bins, of 3 * 1.07 + 2 and of 3 * 2 + 2
+// 51,200 norms take 18.4 us, 8,192 8.1; with a histogram for each of the thresholds at every level, and bounds of the cost gathered from them, 21.0 and 11.3 (a
+// whole allocation with 16-bit widths 24.4 and 11.6 instead of 28.6 and 16.5; 51,200 norms within a tenth of each other 29.9 instead of 28.1, 51,200
+// equal ones 63 instead of 109).
 constexpr uint32_t kCopies = 8;
-constexpr uint32_t kKept = 14;
+constexpr uint32_t kKept = 15;  // of a thread's up to 64 norms; up to 16 always fit
+constexpr uint32_t kPlaces = 4096, kLastPlaces = 1024;  // bins of the second and third level
+static_assert(kPlaces == 4 * kAllocThreads && kLastPlaces == kAllocThreads, "four and one per thread");
 
 // Inclusive sum over the lanes of a row of 16, and over the wave
 __device__ __forceinline__ uint32_t row_scan(uint32_t x) {
@@ -295,28 +297,39 @@ __device__ __forceinline__ uint32_t shift_to(uint32_t x, uint32_t bins) {
   return s + (x >> s >= bins ? 1u : 0u);
 }
 
-// A block's LDS: a level's counters, of the first (kCopies of each) or of the others, and behind these ASIDE, for buckets of more than 16 rows, the
-// norms that the levels look at: 67 KB without, 104 with them (with 16-bit widths 75 and 137).  A search that runs beside a whole replay waits
-// for a CU that has that much in one piece, and registers for sixteen waves.  One block of k_walk (29 KB, 96 registers) may stay beside 104 KB if it is the
-// CU's first or second of five, and beside 108 only if it is the first: an allocation of 51,200 norms adds 13.5 us to a ring of eight's replay of 50.5
-// with kKept 14 or less, 15.7 with 15 and 16.5 with 145 KB (kKept 16, no overlap); without the norms set aside 13.5, but alone 27.5 instead of 25.5.
-constexpr uint32_t search_bins(bool allow16) { return kBins8 + 4 + kBins4 + 4 + (allow16 ? kBins16 + 4 : 0); }
-constexpr uint32_t search_words(bool allow16, bool aside) {
-  const uint32_t first = (kBins + 1) * kCopies, others = search_bins(allow16) + (aside ? (kKept + 1) * kAllocThreads : 0);
-  return first > others ? first : others;
+// The last pattern T with tied(T) <= v, where tied multiplies by `by`, as far as [lo, hi] goes (lo - 1: none of it; hi: all): within a few of v
+// divided by it, but where either is denormal or infinite.
+__device__ __forceinline__ uint32_t last_tied(uint32_t v, float by, float back, uint32_t lo, uint32_t hi) {
+  auto at_most = [&](uint32_t T) { return f2u(u2f(T) * by) <= v; };
+  const uint32_t x = max(f2u(u2f(v) * back), 2u) - 2u;
+  if (at_most(x) && !at_most(x + 5)) return x + (at_most(x + 1) ? 1u : 0u) + (at_most(x + 2) ? 1u : 0u) + (at_most(x + 3) ? 1u : 0u) + (at_most(x + 4) ? 1u : 0u);
+  if (!at_most(lo)) return lo - 1;
+  if (at_most(hi)) return hi;
+  uint32_t below = lo, above = hi;
+  while (above - below > 1) {
+    const uint32_t mid = below + (above - below) / 2;
+    if (at_most(mid)) below = mid; else above = mid;
+  }
+  return below;
 }
+
+// A block's LDS: the first level's counters, over which buckets of more than 16 rows then lay the norms that the other levels look at, and those
+// levels' counters: 86 KB.  A search that runs beside a whole replay waits for a CU that has that much in one piece, and registers for sixteen waves; two blocks
+// of k_walk (29 KB, 96 registers) may stay beside it.
+constexpr uint32_t kFirstWords = (kBins + 1) * kCopies;
+static_assert((kKept + 1) * kAllocThreads <= kFirstWords, "the norms set aside");
 
 template <bool ALLOW16, bool ASIDE>
 __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits, uint32_t *pos_all,
                                                           uint32_t *counts_all, dq::Announce announce) {
-  __shared__ alignas(16) uint32_t room[search_words(ALLOW16, ASIDE)];
-  __shared__ uint32_t wsum[3][kAllocWaves], wfit[kAllocWaves], row_n[kRegs][3];
-  uint32_t *const h8 = room, *const h4 = h8 + kBins8 + 4, *const h16 = h4 + kBins4 + 4;
-  // per thread its norms inside the brackets, and a place for what is not kept
-  uint32_t(*const kept)[kAllocThreads] = reinterpret_cast<uint32_t(*)[kAllocThreads]>(room + search_bins(ALLOW16));
+  __shared__ alignas(16) uint32_t room[kFirstWords];
+  __shared__ alignas(16) uint32_t places[kPlaces + 4], last_places[kLastPlaces];  // places[kPlaces]: beyond the bracket
+  __shared__ uint32_t wsum[2][kAllocWaves], wfit[kAllocWaves], row_n[kRegs][3], crossing[2][2], exact[2][3][kAllocWaves];
+  uint32_t *const h8 = room;
   const float *F = F_all + (uint64_t)blockIdx.x * J;
   uint32_t *pos = pos_all + (uint64_t)blockIdx.x * J;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t(*const kept)[kAllocThreads] = reinterpret_cast<uint32_t(*)[kAllocThreads]>(room);  // per thread its norms inside the brackets
   int32_t fr[kRegs];
   auto each_group = [&](auto body) {
 #pragma unroll
@@ -341,7 +354,10 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
       for (int q = 0; q < 4; ++q) fr[4 * g + q] = (int32_t)f2u(gld<float>(F + min(e + q, J - 1)));
     }
   });
-  for (uint32_t b = tid; b < (kBins + 1) * kCopies; b += kAllocThreads) room[b] = 0;
+  for (uint32_t b = tid; b < kFirstWords / 4; b += kAllocThreads) reinterpret_cast<uint4 *>(room)[b] = make_uint4(0, 0, 0, 0);
+  reinterpret_cast<uint4 *>(places)[tid] = make_uint4(0, 0, 0, 0);
+  last_places[tid] = 0;
+  if (tid == 0) places[kPlaces] = 0;
   if (tid < kRegs * 3) (&row_n[0][0])[tid] = 0;
   each_group([&](int g) {
     const uint32_t e = (g * kAllocThreads + tid) * 4u;
@@ -355,7 +371,7 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
   auto p16_of = [&](uint32_t pattern) { return f2u(u2f(pattern) * (131072.0f / 257.0f)); };
   auto p4_of = [](uint32_t pattern) { return f2u(u2f(pattern) * (17.0f / 512.0f)); };
   // h[b] for b < BINS becomes the sum of h[b], h[b + 1], ..., the thread's own bins in x between the two halves, which a
-  // barrier separates and up to three histograms share
+  // barrier separates
   auto sums_begin = [&](int which, auto &x) {
     uint32_t sum = 0;
     for (uint32_t one : x.n) sum += one;
@@ -371,10 +387,6 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
       *own++ = left;
       left -= one;
     }
-  };
-  auto read_bins = [&](auto &x, const uint32_t *h) {
-    const uint32_t *own = h + tid * (sizeof(x.n) / 4);
-    for (uint32_t &one : x.n) one = *own++;
   };
   // The last of the bin boundaries 0 .. n-1 that surely does not fit and the last that may not (boundary 0 is the
   // bracket's lower end): every PER-th first, then, by every wave for itself, those between.
@@ -439,102 +451,152 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
     base16 = h8[hi16 >> 20];
   }
 
-  // A level looks at every norm, with branches around two or three atomics each time, 4 us for 51,200, though few of them lie in the
-  // brackets: where threads have more than 16 norms and no more than a tenth are inside, which the counts above say, the threads set
-  // theirs aside first, without a branch, and the levels look at those.  (22.4 -> 21.2 us; of those 4.5 are the first level's atomics, 3.7 this.
-  // Norms within a factor of two of each other, or masses of equal ones, go the other way, and so does a bucket of which one thread has more
-  // than kKept inside.)
-  uint32_t n_kept = 0, inside = h8[lo >> 20] - base8 + h8[lo4 >> 20] - base4;
-  if (ALLOW16) inside += h8[lo16 >> 20] - base16;
-  bool few = ASIDE && inside <= J / 10;
-  if (few) {
-    const uint32_t width = hi - lo, width4 = hi4 - lo4, width16 = hi16 - lo16;
-    each_norm([&](int k) {
-      const uint32_t v = (uint32_t)fr[k];
-      kept[min(n_kept, kKept)][tid] = v;
-      n_kept += ((v - lo < width) | (v - lo4 < width4) | (ALLOW16 && v - lo16 < width16)) ? 1u : 0u;
-    });
-    few = !__syncthreads_or(n_kept > kKept);
+  uint32_t base = 2 * J + 4 * base8 + 2 * base4 + 8 * base16;  // cost at hi, but for the tied norms between its tied thresholds and the bins' ends
+  // Looking at every norm takes a level some 4 us for 51,200, though few of them lie in the brackets: the threads set theirs aside first and the levels
+  // look at those.  Where more than a tenth are inside (norms within a factor of two of each other, masses of equal ones), or one thread has more of its
+  // up to 64 inside than fit, the bracket is halved by exact counts: until a tenth is left, or to its end.
+  uint32_t n_kept = 0;
+  const uint32_t budget = (uint32_t)min(max_code_bits, (uint64_t)0xFFFFFFFFu);
+  uint32_t at_lo = h8[lo >> 20] + h8[lo4 >> 20], at_hi = base8 + base4;  // norms at or above the brackets' ends, in all
+  uint32_t cost_lo = 2 * J + 4 * h8[lo >> 20] + 2 * h8[lo4 >> 20];       // at most
+  if (ALLOW16) {
+    at_lo += h8[lo16 >> 20];
+    cost_lo += 8 * h8[lo16 >> 20];
+    at_hi += base16;
   }
-  bool exact = false;
-  while (hi - lo > 1 && !exact) {
+  __syncthreads();  // everybody has read the counts
+  bool fits = true;
+  for (uint32_t probe = 0; hi - lo > 1; ++probe) {
+    const uint32_t turn = probe & 1u;
+    if (fits && at_lo - at_hi <= J / 10) {
+      const uint32_t width = hi - lo, width4 = hi4 - lo4, width16 = hi16 - lo16;
+      n_kept = 0;
+      each_norm([&](int k) {
+        if (!ASIDE && k >= 16) return;
+        const uint32_t v = (uint32_t)fr[k];
+        kept[ASIDE ? min(n_kept, kKept) : n_kept][tid] = v;
+        n_kept += ((v - lo < width) | (v - lo4 < width4) | (ALLOW16 && v - lo16 < width16)) ? 1u : 0u;
+      });
+      if (!ASIDE) break;
+      fits = !__syncthreads_or(n_kept > kKept);
+      if (fits) break;
+    }
+    // the first two probes a little behind and before the place where the cost would meet the budget if it fell evenly
+    const uint32_t width = hi - lo;
+    uint32_t mid = lo + width / 2;
+    if (probe < 2 && lo && cost_lo > budget) {
+      const uint32_t even = (uint32_t)((float)width * (float)(cost_lo - budget) / (float)(cost_lo - base));
+      mid = lo + min(max(probe ? (int32_t)(even - width / 16) : (int32_t)(even + width / 16), 1), (int32_t)width - 1);
+    }
+    const uint32_t p4 = p4_of(mid), p16 = ALLOW16 ? p16_of(mid) : 0u;
+    uint32_t n8 = 0, n4 = 0, n16 = 0;
+    each_norm([&](int k) {  // per lane: ballots, whose bits the scalar unit counts, take twice as long
+      n8 += fr[k] >= (int32_t)mid ? 1u : 0u;
+      n4 += fr[k] >= (int32_t)p4 ? 1u : 0u;
+      if (ALLOW16) n16 += fr[k] >= (int32_t)p16 ? 1u : 0u;
+    });
+    n8 = wave_scan(n8);
+    n4 = wave_scan(n4);
+    if (ALLOW16) n16 = wave_scan(n16);
+    if (lane == 63) {
+      exact[turn][0][wave] = n8;
+      exact[turn][1][wave] = n4;
+      exact[turn][2][wave] = n16;
+    }
+    __syncthreads();
+    n8 = __builtin_amdgcn_readlane(row_scan(exact[turn][0][lane & 15u]), 15);
+    n4 = __builtin_amdgcn_readlane(row_scan(exact[turn][1][lane & 15u]), 15);
+    if (ALLOW16) n16 = __builtin_amdgcn_readlane(row_scan(exact[turn][2][lane & 15u]), 15);
+    const uint32_t cost = 2 * J + 4 * n8 + 2 * n4 + 8 * n16;
+    if (cost <= budget) {
+      hi = mid;
+      hi4 = p4;
+      hi16 = p16;
+      base = cost;
+      at_hi = n8 + n4 + n16;
+    } else {
+      lo = mid;
+      lo4 = p4;
+      lo16 = p16;
+      at_lo = n8 + n4 + n16;
+      cost_lo = cost;
+    }
+  }
+  // One level: of the boundaries lo + (b << s) the last that does not fit (the first, if none: lo) and the one behind it are the new bracket.
+  auto level = [&](uint32_t *h, auto per_thread, uint32_t s, uint32_t turn) {
+    constexpr uint32_t kOwn = decltype(per_thread)::value;
     const uint32_t width = hi - lo, width4 = hi4 - lo4, width16 = hi16 - lo16;
-    const uint32_t s = shift_to(width - 1, kBins8), s4 = shift_to(width4 - 1, kBins4), s16 = ALLOW16 ? shift_to(width16 - 1, kBins16) : 0;
-    const uint32_t n = ((width - 1) >> s) + 1;
-    __syncthreads();  // everybody has read the level before
-    for (uint32_t b = tid; b < search_bins(ALLOW16) / 4; b += kAllocThreads) ((uint4 *)room)[b] = make_uint4(0, 0, 0, 0);
-    __syncthreads();
-    auto count = [&](uint32_t v) {
-      if (v - lo < width) atomicAdd(&h8[(v - lo) >> s], 1u);
-      if (v - lo4 < width4) atomicAdd(&h4[(v - lo4) >> s4], 1u);
-      if (ALLOW16 && v - lo16 < width16) atomicAdd(&h16[(v - lo16) >> s16], 1u);
-    };
-    if (few)
-      for (uint32_t i = 0; i < n_kept; ++i) count(kept[i][tid]);
-    else
-      each_norm([&](int k) { count((uint32_t)fr[k]); });
-    __syncthreads();
-    OwnBins<kBins8> x8;
-    OwnBins<kBins4> x4;
-    OwnBins<kBins16> x16;
-    read_bins(x8, h8);
-    read_bins(x4, h4);
-    if (ALLOW16) read_bins(x16, h16);
-    sums_begin(0, x8);
-    sums_begin(1, x4);
-    if (ALLOW16) sums_begin(2, x16);
-    __syncthreads();
-    sums_end(0, x8, h8);
-    sums_end(1, x4, h4);
-    if (ALLOW16) sums_end(2, x16, h16);
-    __syncthreads();
-    bracket(n, integral_constant<int, kBins8>{}, [&](uint32_t b, uint64_t &c_min, uint64_t &c_max) {
-      const uint32_t T = lo + (b << s), at4 = p4_of(T) - lo4, b4 = at4 >> s4;
-      // a tied threshold on a bin's first pattern has that bin's count exactly
-      const uint64_t fixed = 2ull * J + 4ull * (base8 + h8[b]);
-      c_min = fixed + 2ull * (base4 + h4[(at4 & ((1u << s4) - 1u)) == 0 ? b4 : b4 + 1]);
-      c_max = fixed + 2ull * (base4 + h4[b4]);
-      if (ALLOW16) {
-        const uint32_t at = p16_of(T) - lo16, b16 = at >> s16;
-        c_min += 8ull * (base16 + h16[(at & ((1u << s16) - 1u)) == 0 ? b16 : b16 + 1]);
-        c_max += 8ull * (base16 + h16[b16]);
+    // a norm of a tied bracket: beyond the bracket, or in the bin of the last pattern whose tied one is at most v, which v divided by the
+    // ratio misses by two patterns at most
+    auto fall = [&](uint32_t v, float by, float back, uint32_t from, uint32_t end, uint32_t weight) {
+      if (v >= end) {
+        atomicAdd(&places[kPlaces], weight);
+      } else if (v >= from) {
+        uint32_t b;
+        if (kOwn > 1 && s >= 2 && v >= 0x06000000u) {  // nothing denormal: a bin before or behind, at most
+          auto at_most = [&](uint32_t T) { return f2u(u2f(T) * by) <= v; };
+          b = (min(max(f2u(u2f(v) * back), lo), hi - 1) - lo) >> s;
+          const uint32_t T = lo + (b << s);
+          b = at_most(T + (1u << s)) ? b + 1 : at_most(T) ? b : b - 1;
+        } else {
+          b = (last_tied(v, by, back, lo, hi) - lo) >> s;
+        }
+        atomicAdd(&h[b], weight);
       }
-    }, surely, perhaps);
-    if (perhaps + 1 < n) {
-      hi = lo + ((perhaps + 1) << s);
-      base8 += h8[perhaps + 1];
-    }
-    lo += surely << s;
-    exact = hi - lo > width / 2 && hi - lo > 1;  // bounds too loose to go on: count exactly below
-    const uint32_t end4 = ((p4_of(hi) - lo4) >> s4) + 1;
-    base4 += h4[end4];
-    hi4 = lo4 + (end4 << s4);
-    lo4 += (p4_of(lo) - lo4) >> s4 << s4;
-    if (ALLOW16) {
-      const uint32_t end16 = ((p16_of(hi) - lo16) >> s16) + 1;
-      base16 += h16[end16];
-      hi16 = lo16 + (end16 << s16);
-      lo16 += (p16_of(lo) - lo16) >> s16 << s16;
-    }
-  }
-  // Exact counts at one threshold, the waves' counts in one of two buffers by turns: one barrier per round is enough.
-  uint32_t turn = 0;
-  __syncthreads();
-  while (hi - lo > 1) {
-    const uint32_t mid = lo + (hi - lo) / 2;
-    const int32_t p4 = p4_from(mid), p8 = (int32_t)mid, p16 = p16_from(mid, ALLOW16);
-    uint32_t bits = 0;  // of the wave's norms, beyond 2 each
-    each_norm([&](int k) {
-      bits += 2u * (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p4)) + 4u * (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p8));
-      if (ALLOW16) bits += 8u * (uint32_t)__builtin_popcountll(__ballot(fr[k] >= p16));
-    });
-    uint32_t *const all = room + turn * kAllocWaves;
-    if (lane == 0) all[wave] = bits;
+    };
+    const uint32_t from4 = p4_of(lo), end4 = p4_of(hi), from16 = ALLOW16 ? p16_of(lo) : 0u, end16 = ALLOW16 ? p16_of(hi) : 0u;
+    auto count = [&](uint32_t v) {
+      if (v - lo < width) atomicAdd(&h[(v - lo) >> s], 4u);
+      if (v - lo4 < width4) fall(v, 17.0f / 512.0f, 512.0f / 17.0f, from4, end4, 2u);
+      if (ALLOW16 && v - lo16 < width16) fall(v, 131072.0f / 257.0f, 257.0f / 131072.0f, from16, end16, 8u);
+    };
+    for (uint32_t i = 0; i < n_kept; ++i) count(kept[i][tid]);
     __syncthreads();
-    const uint64_t cost = 2ull * J + __builtin_amdgcn_readlane(row_scan(all[lane & 15u]), 15);
-    if (cost <= max_code_bits) hi = mid; else lo = mid;
-    turn ^= 1u;
+    uint32_t own[kOwn], sum = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kOwn; ++i) {
+      own[i] = h[tid * kOwn + i];
+      sum += own[i];
+    }
+    const uint32_t beyond = kOwn > 1 ? places[kPlaces] : 0u;
+    const uint32_t upto = wave_scan(sum);
+    if (lane == 63) wsum[turn][wave] = upto;
+    __syncthreads();
+    const uint32_t waves_upto = row_scan(wsum[turn][lane & 15u]), all = __builtin_amdgcn_readlane(waves_upto, 15);
+    uint32_t behind = base + beyond + all - (wave ? __builtin_amdgcn_readlane(waves_upto, wave - 1) : 0u) - upto;  // cost behind the thread's bins
+    if (behind <= budget && (behind + sum > budget || tid == 0)) {
+      uint32_t b = kOwn - 1;  // of the thread's bins
+#pragma unroll
+      for (uint32_t i = kOwn - 1; i > 0; --i)
+        if (b == i && behind + own[i] <= budget) {
+          behind += own[i];
+          b = i - 1;
+        }
+      crossing[turn][0] = tid * kOwn + b;
+      crossing[turn][1] = behind;
+    }
+    __syncthreads();
+    const bool none = base + beyond > budget;  // infinite norms: not even +inf fits
+    const uint32_t bin = none ? (width - 1) >> s : crossing[turn][0];
+    base = none ? base + beyond : crossing[turn][1];
+    lo += bin << s;
+    hi = min(hi, lo + (1u << s));
+    lo4 = p4_of(lo);
+    hi4 = p4_of(hi);
+    if (ALLOW16) {
+      lo16 = p16_of(lo);
+      hi16 = p16_of(hi);
+    }
+  };
+  if (hi - lo > 1) level(places, integral_constant<uint32_t, 4>{}, shift_to(hi - lo - 1, kPlaces), 0);
+  while (hi - lo > kLastPlaces) {  // a first bracket of more than four bins
+    places[4 * tid] = places[4 * tid + 1] = places[4 * tid + 2] = places[4 * tid + 3] = 0;
+    if (tid == 0) places[kPlaces] = 0;
+    __syncthreads();
+    level(places, integral_constant<uint32_t, 4>{}, shift_to(hi - lo - 1, kPlaces), 0);
+    __syncthreads();
   }
+  if (hi - lo > 1) level(last_places, integral_constant<uint32_t, 1>{}, 0, 1);
   // How many norms of each row are at or above the thresholds; the first wave turns that into the rows' first places.
   const int32_t p8 = (int32_t)hi, p4 = p4_from(hi), p16 = p16_from(hi, ALLOW16);
   uint32_t n4 = 0, n8 = 0, n16 = 0;  // lane g: of the wave's norms in group g

@@ -180,6 +180,34 @@ def test_allocate_at_the_edges_of_what_is_set_aside(dev, J, max_width):
             check_allocate(dev, F, J, budget, max_width=max_width)
 
 
+@pytest.mark.parametrize("J", [3, 63, 1025, 8192, 16385, 65536])
+@pytest.mark.parametrize("max_width", [8, 16])
+@pytest.mark.parametrize("kind", ["patterns", "denormals", "infinities", "steps", "narrow"])
+def test_allocate_any_patterns(dev, J, max_width, kind):
+    """Thresholds in every range of the format: where the tied ones are denormal or infinite, many patterns to one, a bin apart or in one bin."""
+    rng = np.random.default_rng(J)
+    if kind == "patterns":        # the whole range, evenly over the patterns
+        pat = rng.integers(0, 0x7F800000, J, dtype=np.uint32)
+    elif kind == "denormals":     # on both sides of the smallest normal, and its 512/17 and 257/131072
+        pat = rng.integers(0, 0x00800000 << rng.integers(0, 4), J, dtype=np.uint32) >> rng.integers(0, 24, J, dtype=np.uint32)
+    elif kind == "infinities":
+        pat = np.where(rng.random(J) < 0.3, 0x7F800000, rng.integers(0x7A000000, 0x7F800000, J)).astype(np.uint32)
+    elif kind == "narrow":        # masses a few thousand patterns wide, tied by the ratios
+        values = np.float32(0.7) * np.float32([1.0, 17 / 512, 131072 / 257])
+        pat = rng.choice(values.view(np.uint32), J) + rng.integers(0, 1 << rng.integers(0, 13), J, dtype=np.uint32)
+    else:                         # a few values tied by the ratios, one pattern below, at and above
+        values = np.float32(1e-4) * np.float32([1.0, 512 / 17, 17 / 512, 257 / 131072, (17 / 512) ** 2])
+        pat = rng.choice(values.view(np.uint32), J) + rng.integers(0, 3, J, dtype=np.uint32) - 1
+    F = pat.astype(np.uint32).view(f32)
+    for bits in (2, 3, 4, 6, 8, 15):
+        for budget in (bits * J, bits * J + 1):
+            if kind == "infinities" and budget < 2 * J + (6 if max_width == 8 else 14) * int(np.isinf(F).sum()):
+                counts = host(B.dq_allocate(torch.from_numpy(F).to(dev), J, budget, max_width=max_width)[2]).view(np.uint32)
+                assert counts[0][4] == 0x7F800000      # not even +infinity fits: the allocation is that of +infinity
+            else:
+                check_allocate(dev, F, J, budget, max_width=max_width)
+
+
 def test_allocate_more_buckets_than_a_grid_dimension(dev):
     """70,000 buckets of 5 super-groups: the positions launch is cut at 65,535 buckets (the grid's second
     dimension); buckets on both sides of the cut must come out right."""
