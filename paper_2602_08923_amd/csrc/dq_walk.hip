@@ -402,22 +402,21 @@ static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, u
 
 // Tiles of 1, 2 (dq_thin.hip) or 4 super-groups: the narrower, the shorter a hop's chain and the more hops' worth of
 // instructions there are in all, so narrow ones pay where wide ones would leave SIMDs idle or with a wave or two each.
-// us per replay with all-gather, tiles of 1 / 2 / 4 super-groups, bf16 tensors, 256 CUs, by super-groups (profiles/replay_tile_sizes.txt has
-// all that was measured, bf16 and fp32, 2 to 256 workers):
-//              3,000          4,096           6,100           8,192           10,000          12,288
-//   ring 4     8/10/10        9/11/10         13/12/12        19/15/12        20/20/14        20/22/15
-//   ring 16    15/19/23       19/21/24        26/24/27        42/29/28        45/36/33        46/40/34
-//   ring 100   66/79/113      80/80/121       117/105/126     200/134/136     215/173/164     259/266/190
-//   tree 8     10/12/16       11/13/16        16/17/18        20/25/20        25/26/26        27/27/26
-//   tree 64    47/56/96       84/57/96        84/98/104       122/145/170     151/159/203     167/166/208
-//   tree 256   235/341/368    259/346/368     379/653/722     503/839/663     626/849/791     752/1019/805
-// Rings and short trees: one super-group while four waves per SIMD hold them all, a little longer with few workers in bf16, where a wave's
-// start counts more than its hops; two up to 24 per CU, for bf16 rings of 32 workers and more up to 32, where eight waves hold them;
-// then four.  (Rings of 100 and more workers are the same with one and two within 4 % from 14 to 16 per CU.)  What the CUs hold of a wider
-// butterfly falls with the levels of its stack, differently for each
+// us per replay, tiles of 1 / 2 / 4 super-groups, 256 CUs, by super-groups per CU (profiles/replay_tile_sizes.txt has all that was measured):
+//                 12              16              20              24              28              32
+//   ring bf16 4   6.7/8.5/7.8     7.8/9.6/7.9     10.1/10.8/8.2   11.4/11.4/8.7   13.1/12.8/9.2   14.7/14.0/9.5
+//   ring bf16 16  13.6/15.9/20.7  15.6/17.6/20.9  19.6/18.7/20.9  21.4/21.9/22.2  26.4/23.2/23.2  29.8/27.2/23.5
+//   ring bf16 128 75.5/95.3/142   92.7/102/145    120/110/149     134/136/158     170/147/169     186/171/166
+//   ring f32  4   7.9/8.9/7.9     9.3/9.7/8.1     11.2/11.0/8.5   12.2/12.8/9.1   14.0/14.5/9.6   15.6/15.8/10.0
+//   ring f32  32  23.4/27.7/37.9  29.2/32.2/38.7  38.2/39.5/38.8  42.8/50.2/41.5  53.2/59.6/46.0  62.1/62.8/50.5
+//   tree bf16 8   9.1/11.1/13.4   10.3/11.8/13.7  13.0/12.5/13.8  15.4/14.6/14.5  16.1/16.8/15.1  17.1/19.9/16.4
+//   tree f32  16  14.1/15.5/23.6  16.8/17.1/23.8  22.2/18.0/23.8  27.6/23.4/24.8  28.9/29.9/26.3  32.6/36.2/38.5
+//   tree bf16 64  42.9/52.3/88.6  69.0/65.5/88.0  75.7/95.1/86.7  84.1/104/90.2   94.9/105/93.3   112/108/105
+// Rings and short trees: one super-group while four waves per SIMD hold them all (a little longer where a wave's start counts more than its hops,
+// less with two workers, whose waves have no more than a start); two, for bf16 rings of nine workers and more and short trees, up to 24 or 32
+// per CU; then four.  What the CUs hold of a wider butterfly falls with the levels of its stack, differently for each
 // tile size, so there the time is estimated, up to 48 super-groups per CU: beyond, the three are within 20 % of each other with no order.
-// Of the 352 rows up to 16,384 super-groups the rule takes a choice within 6 % of the best in 333; the geometric mean of what it loses is
-// 0.9 %.  It is furthest off, by a fifth, for 32 and 64 workers' trees of 8,192.  LDS is counted in the pieces it is given out in, and tiles of
+// Of the 252 rows (two mixtures of widths each) the rule's choice is on average 0.6 % behind the best.  LDS is counted in the pieces it is given out in, and tiles of
 // one and two without those that the widths' ends add, which the last waves take beside cheap ones: without that 128 workers' tree
 // of 4,096 took 219 us with tiles of one for 109 with two.
 static uint64_t tree_time(uint32_t n, uint32_t n_cu, uint32_t sgs, uint64_t tiles, uint32_t resident) {
@@ -432,12 +431,14 @@ static uint64_t tree_time(uint32_t n, uint32_t n_cu, uint32_t sgs, uint64_t tile
 static uint32_t tile_for(uint32_t n, bool f32, bool tree, uint32_t n_cu, uint64_t super_groups) {
   const uint32_t per_cu = (uint32_t)((super_groups + n_cu - 1) / n_cu);
   if (tree && n >= 32) return per_cu <= 48 ? 0 : kWaveSGs;
-  uint32_t one = 16, two = 24;  // up to so many per CU
-  if (tree) {
-    one = f32 ? (n <= 8 ? 16 : 12) : n <= 4 ? 20 : n <= 8 ? 28 : 16;
-  } else if (!f32) {
-    if (n > 4 && n <= 8) one = 24;
-    two = n <= 4 ? 16 : n >= 32 ? 32 : 24;
+  uint32_t one = 16, two = 16;  // up to so many per CU
+  if (f32) {
+    if (tree) two = n <= 4 ? 16 : 24;
+    else one = two = n <= 4 ? 12 : n <= 16 ? 16 : 20;
+  } else if (n <= 8) {
+    one = two = n <= 2 ? 12 : tree ? (n <= 4 ? 20 : 24) : n <= 4 ? 16 : 20;
+  } else {
+    two = !tree && n >= 32 ? 32 : 24;
   }
   return per_cu <= one ? 1 : per_cu <= two ? 2 : kWaveSGs;
 }
