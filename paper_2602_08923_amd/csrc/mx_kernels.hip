@@ -642,17 +642,19 @@ done:
 }
 
 // By tiles per CU (512 super-groups are one at 256 CUs); a block of the walk does the work of 16 of them.  Ratios below: this kernel's time over the
-// walk's, fp32 and bf16 rings, chains and butterflies of 2 to 128 workers in the three formats, 5,598 in all (profiles/mx_replay_splits.txt).
+// walk's, fp32 and bf16 rings, chains and butterflies of 2 to 128 workers in the three formats (profiles/mx_replay_splits.txt).
 //   Up to 16, one block of the walk per CU, whose waves have a SIMD to themselves: the tiles' chains are a quarter as long here, 0.3 to 0.9 at 8, until
 // the CU's lanes are full: at 10 in fp32 (8 workers 0.95 to 0.99; 11: 1.04), 12 in bf16 (0.85 to 0.91 of 8, 0.86 to 1.04 of 32), 10 or 11 for rings and chains of 12
 // to 23 (15 at 11: 1.04 to 1.06, 12 at 11 0.92 and at 12 1.07).  6-bit codes, whose conversions take 32 entries whether there are or not, end at 8; two or three
 // workers, who leave most of the eight requests idle, at 8 in fp32 (0.9; 9: 1.15) and 4 in bf16.
-//   Above, everyone waits for the CUs that have a block more than others.  With c blocks of the walk on these the walk takes what 16 c tiles per CU take, this
-// kernel what there are, in fp32 at a rate that is better the more workers there are: 16 and more all of 17 to 64 (0.5 to 0.98); 12 to 15 all but the
-// second block's upper half (48: 1.0; 28: 0.96 to 1.0); 8 to 11 the parts where slack * c says so (24: 0.95, 28: 1.02; 42: 0.98, 44: 1.0; 60: 0.95, 64: 1.02 to 1.08; from
-// 65 on 0.85 to 0.96); 4 to 7 a quarter of the second block (0.78 to 0.92).  6-bit: the same quarter of 8 workers and more (0.7 to 0.95).  bf16, whose walk
-// has the better rate: an eighth, of 64 workers and more (0.84 to 0.9; chains of 100 and more 1.05 to 1.07).
-//   Many: more requests are on their way than one worker's of each wave: from 256 on bf16 rings and chains of 8 workers and more (0.91 to 0.98).
+//   Above, most inputs come from memory, and what counts is how many requests are on their way: this kernel's are eight leaves' of each wave, the walk's one or two
+// workers' of each of three blocks per CU.  But everyone waits for the CUs that have a block of the walk more than others, where inputs stay in the cache.
+// fp32: of 16 workers and more all (0.84 to 1.0); of 8 to 15 all but the second block's last quarter (32 tiles per CU: 1.0 to 1.13; 40: 0.84 to 0.9); 4 to 7
+// from the third block on (0.9 to 1.0) and in a quarter of the second (0.78 to 0.92); fewer never (1.05 to 1.3).  6-bit from 45 (16 workers; 0.88 to 1.0) and 75 (8).
+// bf16, whose walk moves half the bytes and has less to wait for: 8 to 47 workers from 50 tiles per CU (0.87 to 0.98; 40: 0.95 to 1.05; halvings of 8 from 65), more workers
+// from 100 (0.93 to 0.98; 46 to 75: 0.93 to 1.09); 4 to 7 from 165 to 400 (0.87 to 0.96); an eighth of the second block of 64 workers and more
+// (0.84 to 0.9; chains of 100 and more 1.05 to 1.07).  6-bit from 100 (16 workers: 0.89 to 0.97) and 150 (8: 0.87 to 0.97).
+//   600 drawn replays against the walk wherever fp32's or a large bf16 ring's shape did not ask for this: 1.00 to 1.06 of their time by format, type and workers; 1.7 % on average.
 template <int FMT, typename LT, bool TREE>
 bool takes_quad(uint32_t n, uint32_t n_chunks, uint64_t tiles, uint32_t n_cu) {
   constexpr bool six = FMT == DQ_MXFP6_E3M2, wide = sizeof(LT) == 4;
@@ -662,15 +664,18 @@ bool takes_quad(uint32_t n, uint32_t n_chunks, uint64_t tiles, uint32_t n_cu) {
   if (tiles <= few * n_cu) return true;
   if (tiles <= 16ull * n_cu) return false;
   const uint64_t c = (tiles + 16ull * n_cu - 1) / (16ull * n_cu), slack = 16ull * c * n_cu - tiles;  // slack: tiles that the fullest CUs' last blocks lack
-  if (six) return wide && n >= 8 && c == 2 && slack >= 12ull * n_cu;
+  const uint64_t per_cu = tiles / n_cu;
+  const bool last_quarter = c == 2 && slack >= 12ull * n_cu;  // of the second block per CU only a quarter is there
   if (wide) {
+    if (six) return n >= 8 && (per_cu >= (n >= 16 ? 45 : 75) || last_quarter);
     if (n >= 16) return true;
-    if (n >= 12) return c > 2 || slack >= 8ull * n_cu;
-    if (n >= 8) return c > 4 || slack * c >= 16ull * n_cu;
-    return n >= 4 && c == 2 && slack >= 12ull * n_cu;
+    if (n >= 8) return c != 2 || slack >= 4ull * n_cu;
+    return n >= 4 && (per_cu >= 36 || last_quarter);
   }
-  if (c == 2 && slack >= 14ull * n_cu) return n >= 64 && (n_chunks > 1 || n < 100);
-  return !TREE && n >= 8 && tiles >= 256ull * n_cu;
+  if (c == 2 && slack >= 14ull * n_cu && !six) return n >= 64 && (n_chunks > 1 || n < 100);
+  if (six) return n >= 8 && per_cu >= (n >= 16 ? 100 : 150);
+  if (n >= 8) return per_cu >= (n >= 48 ? 100 : TREE && n < 16 ? 65 : 50);
+  return n >= 4 && per_cu >= 165 && per_cu < 400;
 }
 
 template <int FMT, typename LT, bool TREE>
@@ -691,7 +696,10 @@ hipError_t go_mx_walk(MxWalk W, uint32_t n_cu, hipStream_t s) {
   W.wave_bytes = levels * kMxStackLevel > kMxXpose ? levels * kMxStackLevel : kMxXpose;
   const uint32_t lds = W.wave_bytes * kBlockWaves;
   uint32_t per_cu = 160u * 1024 / lds;
-  if (per_cu > 4) per_cu = 4;
+  // Three blocks fit a CU (168 registers); a fourth begins when one ends and has a last round to itself.  bf16: three and a longer walk each 3 to 10 % faster from 32 tiles
+  // per CU on, and for 4 workers and more of the 8- and 4-bit formats from the start (0 to 5 %); 2 workers at 21 to 26 tiles 2 to 7 % slower; fp32 0 to 3 % either way.
+  const uint32_t most = sizeof(LT) == 2 && (W.n_tiles >= 32 * n_cu || (FMT != DQ_MXFP6_E3M2 && W.n >= 4)) ? 3 : 4;
+  if (per_cu > most) per_cu = most;
   if (per_cu < 1) per_cu = 1;
   uint32_t blocks = (W.n_tiles + kBlockWaves - 1) / kBlockWaves;
   if (blocks > n_cu * per_cu) blocks = n_cu * per_cu;

@@ -155,6 +155,16 @@ def test_whole_mx_replay_equals_its_steps(dev, fmt, dtype, topology, n, J, nb, a
 
 @pytest.mark.parametrize("fmt", [B.DQ_MXFP8_E4M3, B.DQ_MXFP6_E3M2, B.DQ_MXFP4_E2M1])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("topology,n,J", [("ring", 4, 18428), ("ring", 4, 18432), ("ring", 8, 20480), ("ring", 16, 23040), ("ring", 8, 25592), ("ring", 8, 25600),
+                                          ("butterfly", 8, 33272), ("butterfly", 8, 33280), ("ring", 48, 51216), ("butterfly", 4, 84480), ("chain", 2, 24577)])
+def test_a_large_whole_mx_replay_equals_its_steps(dev, fmt, dtype, topology, n, J):
+    """Both sides of the sizes, by tiles per CU, from which inputs that come from memory go four lanes to a block, and of the blocks per CU of the others."""
+    rp = B.Replay(B.Context(n), TOPO[topology], fmt, gradients(n, J, dtype, dev, J + n), J)
+    whole_against_steps(rp, {"ring": n, "chain": 1, "butterfly": 0}[topology])
+
+
+@pytest.mark.parametrize("fmt", [B.DQ_MXFP8_E4M3, B.DQ_MXFP6_E3M2, B.DQ_MXFP4_E2M1])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("topology,n,J", [("ring", 5, 45), ("ring", 17, 17), ("butterfly", 16, 48)])
 def test_whole_mx_replay_of_any_pattern_equals_its_steps(dev, fmt, dtype, topology, n, J):
     """Infinities, quiet and signalling NaN, denormals: every bit pattern may come from a worker."""
