@@ -100,7 +100,7 @@ struct ChunkInfo {
 // goes from narrow to wide once, and the waves that share a CU take them from different places of it, not from the same place of several
 // buckets.  (From some eight tiles per wave on they meet all widths anyway, and the order of the memory is the better one: recursive halving
 // over 16, eight buckets of 51,200 super-groups, 825 us against 838.  Up to four workers, whose tiles cost memory's time and not their width's, it is no
-// better either, 0.4 % either way on average of 146 schedules, but in some: halving over 2 in fp32, 3 x 11,456 at 4 bits, 20.0 against 20.8; 19.3 with the shares of old.)
+// better either, 0.4 % either way on average of 146 schedules, but in some: halving over 2 in fp32, 3 x 11,456 at 4 bits, 20.0 against 20.8.)
 bool by_chunk_number(const dq::Walk &w, uint32_t n_buckets, uint64_t n_sg_bucket) {
   return n_buckets > 1 && w.n > 4 && n_buckets * n_sg_bucket < 8ull * w.tile_sgs * w.blocks * w.waves;
 }

@@ -164,7 +164,7 @@ def test_allocate_narrow_value_ranges(dev):
     check_allocate(dev, F3, 4097, int(math.floor(prep.code_bits(4.0) * 4097)))   # 3 buckets, 5 rows each, ragged
 
 
-@pytest.mark.parametrize("J", [16384, 16385, 51200, 65536])       # from 16,385 on the search sets norms aside, up to 14 per thread
+@pytest.mark.parametrize("J", [16384, 16385, 51200, 65536])       # from 16,385 on the search sets norms aside, up to 15 per thread
 @pytest.mark.parametrize("max_width", [8, 16])
 def test_allocate_at_the_edges_of_what_is_set_aside(dev, J, max_width):
     """Few norms around the threshold, but one thread (norms 4096 g + 4 t + 0..3) has 13 to 16 of its own there."""
