@@ -648,10 +648,12 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
 }
 
 // Behind the search of an all-reduce that replays on the original tensors: what k_alloc_positions and k_reorder_mean do between them, but for the
-// widths and positions themselves, which nobody reads, and in the first block the replay's tables.
+// widths and positions themselves, which nobody reads, and in the first blocks the replay's tables.
 //
 // The tables, as plan_walk and split_walk (dq_walk.hip) make them on the host: a thread per path, then the most tiles per wave of every width, then a
-// share per thread and turn.  What bounds it is latency: a chain of 5.7 us, beside the other blocks' 3.6 (8 workers, 8,192 super-groups).  Divisions are products with v_rcp_f32's
+// share per thread; what is common to all shares every block works out for itself.  What bounds it is latency: a chain of 5.3 us, beside the other blocks' 3.6
+// (8 workers, 8,192 super-groups, 4,096 shares; with all shares in one block, four to a thread, 6.1; the search's block doing this and the positions too: 8.7 behind the
+// search).  Divisions are products with v_rcp_f32's
 // result: that the fullest wave's tiles come out one more than they might be costs nothing but time, and any costs give shares that
 // cover the tiles once, as a share ends where the next begins.  Sums of costs are whole numbers below 2^53, so doubles hold them exactly.
 __device__ __forceinline__ float quick(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -729,13 +731,14 @@ __device__ __forceinline__ void raise_costs(const float (&tiles)[4], const dq::C
   }
 }
 
+__device__ __host__ __forceinline__ uint32_t table_parts(const dq::Tables &T) { return T.waves / kAllocThreads + 1; }  // a share per thread
 struct TableSpace {
   double upto[dq::kMostTablePaths];  // cost of the paths before
   uint32_t tiles[dq::kMostTablePaths][4];
   uint32_t total[4], cost[4];
   double wave_sum[kAllocWaves];
 };
-__device__ __forceinline__ void make_tables(const dq::Tables &T, const uint32_t *counts_all, TableSpace &L) {
+__device__ __forceinline__ void make_tables(const dq::Tables &T, const uint32_t *counts_all, uint32_t part, TableSpace &L) {
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t n_paths = T.n_chunks * T.n_buckets;
   if (tid < 4) L.total[tid] = 0;
@@ -770,7 +773,7 @@ __device__ __forceinline__ void make_tables(const dq::Tables &T, const uint32_t 
         L.tiles[tid][w] = t[w];
       }
       x.chunk = c;
-      T.paths[tid] = x;
+      if (part == 0) T.paths[tid] = x;
     }
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -810,7 +813,8 @@ __device__ __forceinline__ void make_tables(const dq::Tables &T, const uint32_t 
   if (tid < n_paths) L.upto[tid] = before + sum - mine;
   __syncthreads();
   const double ratio = total / (double)T.waves;
-  for (uint32_t v = tid; v <= T.waves; v += kAllocThreads) {
+  const uint32_t v = part * kAllocThreads + tid;
+  if (v <= T.waves) {
     uint32_t path = n_paths, tile = 0;
     if (v < T.waves) {
       const double want = floor((double)v * ratio);
@@ -849,15 +853,16 @@ __global__ void __launch_bounds__(kAllocThreads) k_arrange(const float *F_all, c
                                                            const uint32_t *places_all, float *mu_main, uint32_t *origin, dq::Tables T) {
   __shared__ uint32_t mine_w[kAllocWaves][4];
   __shared__ TableSpace space;
-  if (blockIdx.x == 0) {
-    if (blockIdx.y == 0) make_tables(T, counts_all, space);
+  const uint32_t parts = table_parts(T);
+  if (blockIdx.x < parts) {
+    if (blockIdx.y == 0) make_tables(T, counts_all, blockIdx.x, space);
     return;
   }
-  const uint32_t row = blockIdx.x - 1;
+  const uint32_t row = blockIdx.x - parts;
   const uint64_t first = (uint64_t)blockIdx.y * J;
   const uint32_t j = row * kAllocThreads + threadIdx.x;
   const float m = mu_all ? gld<float>(mu_all + first + min(j, J - 1)) : 0.0f;
-  const Placed x = place_row(F_all + first, J, allow16, counts_all + 5ull * blockIdx.y, places_all + first, row, row + 2 == gridDim.x, mine_w);
+  const Placed x = place_row(F_all + first, J, allow16, counts_all + 5ull * blockIdx.y, places_all + first, row, row + parts + 1 == gridDim.x, mine_w);
   if (x.k < 4) {
     if (mu_all) gst<float>(mu_main + first + x.at, x.k == 3 ? 0.0f : m);
     gst<uint32_t>(origin + first + x.at, j);
@@ -1140,7 +1145,7 @@ dq_status search(const float *F, uint32_t J, uint32_t n_buckets, uint64_t max_co
 dq_status arrange(const float *F, const float *mu, uint32_t J, uint32_t n_buckets, uint32_t max_width, const uint32_t *counts, const uint32_t *places,
                   float *mu_main, uint32_t *origin, const Tables &tables, hipStream_t s) {
   const uint32_t rows = (J + kAllocThreads - 1) / kAllocThreads;
-  hipLaunchKernelGGL(k_arrange, dim3(rows + 1, n_buckets), dim3(kAllocThreads), 0, s, F, mu, J, max_width == 16, counts, places, mu_main, origin, tables);
+  hipLaunchKernelGGL(k_arrange, dim3(rows + table_parts(tables), n_buckets), dim3(kAllocThreads), 0, s, F, mu, J, max_width == 16, counts, places, mu_main, origin, tables);
   return launched();
 }
 
