@@ -657,7 +657,6 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
 // result: that the fullest wave's tiles come out one more than they might be costs nothing but time, and any costs give shares that
 // cover the tiles once, as a share ends where the next begins.  Sums of costs are whole numbers below 2^53, so doubles hold them exactly.
 __device__ __forceinline__ float quick(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ float lane_f(float x, int l) { return u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(x), l)); }
 
 // Costs of a tile by width such that equal shares hold at most the bounded number of tiles (split_walk); by one wave.
 __device__ __forceinline__ void raise_costs(const float (&tiles)[4], const dq::Costs &c, float waves, uint32_t lane, float (&cost)[4], float &fullest) {
