@@ -61,6 +61,7 @@ struct dqx_whole {
   uint32_t n_sg_bucket, n_buckets;
   uint64_t max_code_bits;
   uint32_t max_width, all_gather, means;
+  uint32_t n_tensors;  // as many as the context has workers
 };
 size_t dqx_whole_scratch_bytes(const dq_ctx *ctx, const dqx_whole *desc);
 dq_status dqx_whole_run(const dq_ctx *ctx, const dqx_whole *desc, const void *const *tensors, void *scratch, float *out, void *hip_stream, void **ticket);

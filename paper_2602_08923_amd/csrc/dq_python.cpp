@@ -527,7 +527,7 @@ PyObject *py_whole(PyObject *const *a, Py_ssize_t nargs) {
   const long long budget = PyLong_AsLongLongAndOverflow(a[4], &overflow);
   if (overflow || budget < 0) Py_RETURN_NONE;
   const dqx_whole d = {(dq_topology)number(a[3]), local_dtype(x), (uint32_t)J, (uint32_t)(x.numel() / (J * 256)), (uint64_t)budget, (uint32_t)number(a[5]),
-                       (uint32_t)number(a[6]), (uint32_t)number(a[7])};
+                       (uint32_t)number(a[6]), (uint32_t)number(a[7]), (uint32_t)n};
   const dq_ctx *ctx = as<dq_ctx>(handle(a[0]));
   const size_t bytes = L.dqx_whole_scratch_bytes(ctx, &d);
   if (bytes == 0) Py_RETURN_NONE;

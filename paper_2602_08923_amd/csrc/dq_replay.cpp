@@ -902,7 +902,7 @@ struct WholePlan {
 bool plan_whole(const dq_ctx *ctx, const dqx_whole *d, WholePlan *p) {
   const uint32_t n = ctx->cfg.n_workers, J = d->n_sg_bucket, nb = d->n_buckets;
   const bool tree = d->topology == DQ_BUTTERFLY;
-  if ((d->topology != DQ_RING && !tree) || (d->dtype != DQ_F32 && d->dtype != DQ_BF16) || n < 2 || n > dq::kMostTensors || J == 0 || nb == 0 || nb > dq::kAnnounced || J % n ||
+  if ((d->topology != DQ_RING && !tree) || (d->dtype != DQ_F32 && d->dtype != DQ_BF16) || n < 2 || n > dq::kMostTensors || d->n_tensors != n || J == 0 || nb == 0 || nb > dq::kAnnounced || J % n ||
       (tree && (n & (n - 1))) || J > dq::kMostSearched || (uint64_t)n * nb > dq::kMostTablePaths || (d->max_width != 8 && d->max_width != 16) ||
       d->max_code_bits < 2ull * J)
     return false;

@@ -373,6 +373,27 @@ def test_an_allreduce_enqueued_whole_equals_its_steps(dev, topology, n, J, nb, b
             assert torch.equal(got.view(torch.int32), want.view(torch.int32))
 
 
+class Miscounted(list):
+    """A list that another thread makes longer or shorter once its length has been asked for."""
+    def __init__(self, items, count):
+        super().__init__(items)
+        self.count = count
+
+    def __len__(self):
+        return self.count
+
+
+@pytest.mark.parametrize("topology", ["ring", "butterfly"])
+@pytest.mark.parametrize("held,workers", [(2, 4), (3, 4), (5, 4), (8, 4), (4, 2), (7, 8)])
+def test_a_whole_allreduce_takes_one_tensor_per_worker(dev, topology, held, workers):
+    """Refused before anything is enqueued, as the steps refuse it."""
+    J = 64
+    grads = gradients(held, J, torch.bfloat16, dev, 5)
+    assert B.allreduce_whole(B.Context(workers), grads, J, TOPO[topology], 4 * J, 8, True, True) is None
+    with pytest.raises(B.DqError, match=f"{held} worker gradients for a context of {workers}"):
+        allreduce.simulated_allreduce(Miscounted(grads, workers), 4.6875, topology=TOPO[topology])
+
+
 def test_allreduces_of_several_threads_on_their_own_streams(dev):
     calls = allreduce_inputs(dev, len(ALLREDUCE))
     want = [allreduce.simulated_allreduce(g, 6.0, seed=k, **o)[0].clone() for k, (g, o) in enumerate(zip(calls, ALLREDUCE))]
