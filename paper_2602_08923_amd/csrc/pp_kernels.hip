@@ -484,7 +484,7 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
     // the first two probes a little behind and before the place where the cost would meet the budget if it fell evenly
     const uint32_t width = hi - lo;
     uint32_t mid = lo + width / 2;
-    if (probe < 2 && lo && cost_lo > budget) {
+    if (probe < 2 && lo && cost_lo > budget && base <= budget) {  // (beyond it where norms are infinite and even +inf is too dear)
       const uint32_t even = (uint32_t)((float)width * (float)(cost_lo - budget) / (float)(cost_lo - base));
       mid = lo + min(max(probe ? (int32_t)(even - width / 16) : (int32_t)(even + width / 16), 1), (int32_t)width - 1);
     }

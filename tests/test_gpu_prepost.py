@@ -208,6 +208,22 @@ def test_allocate_any_patterns(dev, J, max_width, kind):
                 check_allocate(dev, F, J, budget, max_width=max_width)
 
 
+@pytest.mark.parametrize("J", [3, 100, 9000, 16385, 65536])
+@pytest.mark.parametrize("max_width", [8, 16])
+@pytest.mark.parametrize("share", [0.02, 0.5, 0.999])
+def test_allocate_when_not_even_infinity_fits(dev, J, max_width, share):
+    """Infinite norms are all above any threshold: the allocation is that of +infinity, whatever it costs."""
+    rng = np.random.default_rng(J)
+    pat = np.where(np.arange(J) < max(1, int(share * J)), 0x7F800000, rng.integers(0x7F000000, 0x7F800000, J)).astype(np.uint32)
+    F = rng.permutation(pat).view(f32)
+    for budget in (2 * J, 2 * J + 1, 2 * J + 5):
+        widths, pos, counts = B.dq_allocate(torch.from_numpy(F).to(dev), J, budget, max_width=max_width)
+        w = np.where(np.isinf(F), max_width, 2).astype(np.uint8)
+        p, c = P.positions(w)
+        assert np.array_equal(host(widths), w) and np.array_equal(host(pos).view(np.uint32), p)
+        assert host(counts).view(np.uint32)[0].tolist() == c + [0x7F800000]
+
+
 def test_allocate_more_buckets_than_a_grid_dimension(dev):
     """70,000 buckets of 5 super-groups: the positions launch is cut at 65,535 buckets (the grid's second
     dimension); buckets on both sides of the cut must come out right."""
