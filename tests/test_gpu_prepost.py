@@ -224,6 +224,16 @@ def test_allocate_when_not_even_infinity_fits(dev, J, max_width, share):
         assert host(counts).view(np.uint32)[0].tolist() == c + [0x7F800000]
 
 
+@pytest.mark.parametrize("J", [1, 2, 5, 8, 9, 11, 100, 8191, 8192, 8193, 16383, 16384])
+@pytest.mark.parametrize("max_width", [8, 16])
+def test_allocate_norms_close_together(dev, J, max_width):
+    """Up to 8,192 norms around the threshold the levels take as they are, more the search halves away first: equal ones, and ones within a tenth and a factor of two."""
+    rng = np.random.default_rng(J)
+    for F in (np.full(J, 3.0), 1.0 + 0.1 * rng.random(J), 1.0 + rng.random(J)):
+        for bits in (2.0, 3.3, 4.7, 7.9, 13.0):
+            check_allocate(dev, F.astype(f32), J, int(bits * J), max_width=max_width)
+
+
 def test_allocate_more_buckets_than_a_grid_dimension(dev):
     """70,000 buckets of 5 super-groups: the positions launch is cut at 65,535 buckets (the grid's second
     dimension); buckets on both sides of the cut must come out right."""
