@@ -264,8 +264,8 @@ __global__ void __launch_bounds__(kAllocThreads) k_alloc_positions(const float *
 // What bounds it: one CU's vector ALU and LDS (51,200 norms are 800 wave instructions for every instruction of a pass,
 // and an LDS atomic of a wave takes 12 cycles) and, for small buckets, the barriers and scans of the levels.
 // 51,200 norms take 18.4 us, 8,192 8.1; with a histogram for each of the thresholds at every level, and bounds of the cost gathered from them, 21.0 and 11.3 (a
-// whole allocation with 16-bit widths 24.4 and 11.6 instead of 28.6 and 16.5; 51,200 norms within a tenth of each other 29.9 instead of 28.1, 51,200
-// equal ones 63 instead of 109).
+// whole allocation with 16-bit widths 22.8 and 10.8 instead of 27.8 and 16.4; of 51,200 norms within a tenth of each other 28.2 instead of 29.5, within a
+// factor of two 28.7 instead of 27.2, of equal ones 62 instead of 109).
 constexpr uint32_t kCopies = 8;
 constexpr uint32_t kKept = 15;  // of a thread's up to 64 norms; up to 16 always fit
 constexpr uint32_t kPlaces = 4096, kLastPlaces = 1024;  // bins of the second and third level
@@ -456,7 +456,7 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
   // look at those.  Where more than a tenth are inside (norms within a factor of two of each other, masses of equal ones), or one thread has more of its
   // up to 64 inside than fit, the bracket is halved by exact counts: until a tenth is left, or to its end.  Up to 16 norms per thread always fit, and the levels take up
   // to 8 per thread in less time than the counts, half a us to a round of some twenty: an allocation of 8 norms 8.1 us, with a tenth there too 20.6; of 1,000 equal
-  // ones 11.4 and 20.3, of 8,192 24.9 and 24.1, of 16,384 (the other way here) 41 and 30.
+  // ones 11.4 and 20.3, of 8,192 24.9 and 24.1, of 16,384 (the other way here) 41 and 30.  More: three per thread are as good as a tenth or better.
   uint32_t n_kept = 0;
   const uint32_t budget = (uint32_t)min(max_code_bits, (uint64_t)0xFFFFFFFFu);
   uint32_t at_lo = h8[lo >> 20] + h8[lo4 >> 20], at_hi = base8 + base4;  // norms at or above the brackets' ends, in all
@@ -467,10 +467,10 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
     at_hi += base16;
   }
   __syncthreads();  // everybody has read the counts
-  bool fits = true;
+  bool fits = true, last_fit = false;
   for (uint32_t probe = 0; hi - lo > 1; ++probe) {
     const uint32_t turn = probe & 1u;
-    if (fits && at_lo - at_hi <= (ASIDE ? J / 10 : 8u * kAllocThreads)) {
+    if (fits && at_lo - at_hi <= (ASIDE ? max(J / 10, 3u * kAllocThreads) : 8u * kAllocThreads)) {
       const uint32_t width = hi - lo, width4 = hi4 - lo4, width16 = hi16 - lo16;
       n_kept = 0;
       each_norm([&](int k) {
@@ -483,12 +483,14 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
       fits = !__syncthreads_or(n_kept > kKept);
       if (fits) break;
     }
-    // the first two probes a little behind and before the place where the cost would meet the budget if it fell evenly
+    // The first three where the cost would meet the budget if it fell evenly; the second and third a little to the side on which the one before was not,
+    // so that they close the bracket from there.  (Halved only: 51,200 norms within a tenth 34.8 us instead of 28.2, half of them equal 74.5 and 63.3; equal ones
+    // all, which fall at one place, 60.4 and 62.4.)
     const uint32_t width = hi - lo;
     uint32_t mid = lo + width / 2;
-    if (probe < 2 && lo && cost_lo > budget && base <= budget) {  // (beyond it where norms are infinite and even +inf is too dear)
-      const uint32_t even = (uint32_t)((float)width * (float)(cost_lo - budget) / (float)(cost_lo - base));
-      mid = lo + min(max(probe ? (int32_t)(even - width / 16) : (int32_t)(even + width / 16), 1), (int32_t)width - 1);
+    if (probe < 3 && lo && cost_lo > budget && base <= budget) {  // (beyond the budget where norms are infinite and even +inf is too dear)
+      const int32_t even = (int32_t)((float)width * ((float)(cost_lo - budget) / (float)(cost_lo - base))), off = (int32_t)(width >> (probe == 1 ? 5 : 4));
+      mid = lo + (uint32_t)min(max(probe == 0 ? even : last_fit ? even - off : even + off, 1), (int32_t)width - 1);
     }
     const uint32_t p4 = p4_of(mid), p16 = ALLOW16 ? p16_of(mid) : 0u;
     uint32_t n8 = 0, n4 = 0, n16 = 0;
@@ -510,7 +512,8 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
     n4 = __builtin_amdgcn_readlane(row_scan(exact[turn][1][lane & 15u]), 15);
     if (ALLOW16) n16 = __builtin_amdgcn_readlane(row_scan(exact[turn][2][lane & 15u]), 15);
     const uint32_t cost = 2 * J + 4 * n8 + 2 * n4 + 8 * n16;
-    if (cost <= budget) {
+    last_fit = cost <= budget;
+    if (last_fit) {
       hi = mid;
       hi4 = p4;
       hi16 = p16;
