@@ -485,10 +485,12 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
 // 10.5 and 6.6 (8 of the 230 lose more than 5 %, mostly where half the waves have one tile and half two).
 // A tile's costs: what its instructions take beside the memory's time, which all widths have alike, measured as the ratios that are fastest: 1.8 to 2.2 with
 // bf16 tensors of five workers and more, 1.1 to 1.25 where a hop moves more bytes (fp32, or a result of 4 bytes per few workers).  (12/15/16
-// instead of 12/24/26 for the first ring above: 64.2.)
+// instead of 12/24/26 for the first ring above: 64.2.)  A raw tile has the fewest instructions but waits for every slice: as dear as a 2-bit one it came four
+// to a wave where others held one (bf16 ring of 24, 5,354/9,868/5,525/10,261: 111 to 116 us, 95 so, 98 with equal counts).  Only in halvings over 16 workers
+// and more, whose stack it hardly uses, it is no dearer (55 such schedules of bf16 at 2 to 4 tiles per wave 1 % faster so).
 Costs costs_of(dq_dtype dtype, bool tree, uint32_t n) {
-  if (dtype == DQ_F32 || n <= 4) return Costs{{12, 14, 15, 12}};
-  return tree ? Costs{{12, 20, 22, 12}} : Costs{{12, 24, 26, 12}};
+  if (dtype == DQ_F32 || n <= 4) return Costs{{12, 14, 15, 15}};
+  return tree ? Costs{{12, 20, 22, n <= 12 ? 15u : 12u}} : Costs{{12, 24, 26, 15}};
 }
 namespace {
 // The most tiles per wave of every width (0: there is none of it), at most `waves` waves.

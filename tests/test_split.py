@@ -19,7 +19,7 @@ def split(rows, n, f32, tree, sgs, blocks, waves):
 
 
 def costs(f32, tree, n):
-    return (12, 14, 15, 12) if f32 or n <= 4 else (12, 20, 22, 12) if tree else (12, 24, 26, 12)
+    return (12, 14, 15, 15) if f32 or n <= 4 else (12, 20, 22, 15 if n <= 12 else 12) if tree else (12, 24, 26, 15)
 
 
 def least_fullest(tiles, cost, waves):
@@ -63,6 +63,30 @@ def test_shares_cover_every_tile_once_and_the_fullest_is_small(seed):
             assert all(k <= m for k, m in zip(held, most)), (held, most)
         # at an edge between widths: one tile of either may be begun
         assert sum(k * x for k, x in zip(held, c)) <= least + 2 * max(c)
+
+
+def chunks(by_width, n):
+    """A bucket's chunks, super-groups by width of each."""
+    m, edges = sum(by_width) // n, [0, *itertools.accumulate(by_width)]
+    return [[max(0, min(hi, (c + 1) * m) - max(lo, c * m)) for lo, hi in zip(edges, edges[1:])] for c in range(n)]
+
+
+def held_by_waves(rows, shares, sgs=4):
+    """Tiles by width of every wave."""
+    flat, first = [], []
+    for row in rows:
+        first.append(len(flat))
+        flat += itertools.chain.from_iterable([w] * -(-k // sgs) for w, k in enumerate(row))
+    at = [first[p] + t if p < len(rows) else len(flat) for p, t in shares]
+    return [[flat[lo:hi].count(w) for w in range(4)] for lo, hi in zip(at, at[1:])]
+
+
+@pytest.mark.parametrize("tree,n,blocks,waves,by_width,most", [(0, 24, 1280, 4, (5354, 9868, 5525, 10261), 3), (1, 2, 512, 8, (12249, 12534, 880, 8941), 2)])
+def test_raw_tiles_are_dearer_than_two_bit_ones(tree, n, blocks, waves, by_width, most):
+    """At equal cost the waves held one more: 18 and 8 % slower than with shares of equal counts."""
+    rows = chunks(by_width, n)
+    held = held_by_waves(rows, split(rows, n, 0, tree, 4, blocks, waves))
+    assert max(h[3] for h in held) <= most and max(map(sum, held)) <= 3
 
 
 def test_a_schedule_beyond_32_bits_of_cost():
