@@ -467,7 +467,11 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
   if (!found) return false;
   *W = best;
   const uint64_t tiles = tiles_of[W->tile_sgs / 2], waves = (uint64_t)W->blocks * W->waves;
-  const bool spread = tree && W->n > 4 && W->tile_sgs == kWaveSGs && tiles < 8 * waves;
+  // Halvings over few workers: what counts is each CU's tiles, as memory's time is most of it.  With bounded shares in path order the waves of a CU hold
+  // two or three of one width while another's hold one (over 4 in bf16, 7,433/0/15,439: 23.6 us, 19.3 so, 20.9 with equal counts; 300 schedules over 2 and 4 6.4 instead
+  // of 5.2 % faster than with equal shares); but where no wave has more than one tile, or over 2 workers two, path order is the better one (1 to 3 % on average, some 16 %).
+  const bool several = tiles > (W->n == 2 ? 2 : 1) * waves;
+  const bool spread = tree && (W->n > 4 || several) && W->tile_sgs == kWaveSGs && tiles < 8 * waves;
   // (Not with 16-bit tiles, the cheapest, at the end: ring of 6, three buckets of 4,476, a quarter of them 16-bit, 15.0 us and 15.8 reversed.)
   W->order = spread ? n_cu : tiles <= waves && !W->raw ? kReversed : 0;
   return true;
