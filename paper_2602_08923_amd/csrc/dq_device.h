@@ -96,6 +96,7 @@ struct Walk {
   uint32_t n_paths;
   uint32_t blocks, waves;    // grid, waves per block
   uint32_t order;            // which share a wave takes (share_of): 0, kReversed, or the CUs that the shares are spread over
+  uint32_t raw_beside;       // spread: CUs with a block more have the last shares in it, raw ones, not the first
 };
 constexpr uint32_t kReversed = 0xFFFFFFFFu;
 struct WalkShare {

@@ -148,13 +148,17 @@ void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, 
       raw = raw || x.n_sg[3] != 0;
     }
   w.raw = raw;
-  uint64_t tiles[3] = {0, 0, 0};
-  for (const dq::WalkPath &p : plan->paths)
+  uint64_t tiles[3] = {0, 0, 0}, two = 0, sixteen = 0;
+  for (const dq::WalkPath &p : plan->paths) {
+    two += p.job.n_sg[0];
+    sixteen += p.job.n_sg[3];
     for (uint32_t k : p.job.n_sg) {
       tiles[0] += k;
       tiles[1] += (k + 1) / 2;
       tiles[2] += (k + 3) / 4;
     }
+  }
+  w.raw_beside = sixteen > two;
   plan->walk = dq::grid_walk(ctx->params, d->dtype, plan->tree, ctx->n_cu, tiles, &w);
   if (!plan->walk) {
     plan->paths.clear();

@@ -19,7 +19,8 @@ struct Is { static constexpr bool value = B; };
 // Which share a wave takes (the order goes from narrow to wide).  Where no wave has more than a tile the wide ones go first, so that the blocks that are
 // dispatched last, beside another on their CU or after it, have the narrow ones.  With more, a ring's four or five blocks of four waves per CU take
 // shares from as many places of the order.  A recursive halving has two blocks of eight: there the i-th waves of all CUs take the i-th
-// stretch of the shares, so that every CU has some of all widths, and CUs with a block more have the narrowest in it.
+// stretch of the shares, so that every CU has some of all widths, and CUs with a block more have the cheapest in it: the first shares, of two bits, or
+// the last, if there are more raw tiles (over 16 in bf16, 385/376/4,981/3,570: 28.3 us; with the few 2-bit ones there 38.8, in path order 30.8).
 // (The number of blocks is read with the other arguments: gridDim is a trip of its own, 0.2 us.)
 template <bool TREE>
 __device__ __forceinline__ uint32_t share_of(const Walk &W, uint32_t wave, uint32_t waves) {
@@ -27,7 +28,8 @@ __device__ __forceinline__ uint32_t share_of(const Walk &W, uint32_t wave, uint3
   if (W.order == kReversed) return (W.blocks - 1 - b) * waves + wave;
   if (TREE && W.order) {
     const uint32_t cus = W.order, row = b / cus, rows = W.blocks / cus, rest = W.blocks - rows * cus;
-    return row < rows ? rest * waves + (row * waves + wave) * cus + b % cus : wave * rest + b % cus;
+    const uint32_t beside = W.raw_beside ? rows * cus * waves : 0, all = W.raw_beside ? 0 : rest * waves;
+    return row < rows ? all + (row * waves + wave) * cus + b % cus : beside + wave * rest + b % cus;
   }
   return b * waves + wave;
 }

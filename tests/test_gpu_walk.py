@@ -99,6 +99,8 @@ def test_whole_replay_of_many_super_groups_equals_its_steps(dev, topology, n, wi
 @pytest.mark.parametrize("topology,n,widths", [
     # between one and three tiles of four per wave, several buckets, the last row of blocks on the CUs not full: waves hold 0 to 5 tiles of a width
     ("butterfly", 8, [[2401, 3202, 1501, 96]] * 3), ("butterfly", 2, [[9001, 6002, 5001, 0], [0, 4, 20000, 0]]), ("butterfly", 16, [[23001, 9, 1230, 0]]),
+    # CUs with a block more, which take the 16-bit tiles
+    ("butterfly", 16, [[385, 376, 4981, 3570]]), ("butterfly", 8, [[289, 1687, 55, 1161]] * 3), ("butterfly", 8, [[1, 9, 0, 8790]]),
     ("butterfly", 4, [[7433, 0, 15439, 0]]), ("butterfly", 4, [[5601, 3002, 1502, 207]] * 2), ("butterfly", 2, [[21001, 13802, 2, 1001]]),
     ("ring", 6, [[9001, 602, 501, 96]] * 3), ("ring", 3, [[20000, 31000, 1, 8]]), ("ring", 9, [[2, 16000, 8001, 0]]),
 ])
