@@ -65,6 +65,12 @@ struct dqx_whole {
 };
 size_t dqx_whole_scratch_bytes(const dq_ctx *ctx, const dqx_whole *desc);
 dq_status dqx_whole_run(const dq_ctx *ctx, const dqx_whole *desc, const void *const *tensors, void *scratch, float *out, void *hip_stream, void **ticket);
+// Where its scratch holds the shares of the replay's waves, blocks * waves and an end, {path, tile} each; for the tests.
+struct dqx_tables {
+  size_t shares;
+  uint32_t blocks, waves, tile_sgs, by_chunk;  // by_chunk: paths of the same chunk next to each other, not of the same bucket
+};
+dq_status dqx_whole_tables(const dq_ctx *ctx, const dqx_whole *desc, dqx_tables *tables);
 // Adds to *wrong (device) how many results of the codec's reciprocal differ from the division's.
 dq_status dqx_reciprocals(uint32_t *wrong, void *hip_stream);
 // Where the waves of a replay of n_paths paths begin (dq_walk.hip), {path, tile} each and an end.

@@ -957,6 +957,13 @@ size_t dqx_whole_scratch_bytes(const dq_ctx *ctx, const dqx_whole *desc) {
   return ctx && desc && plan_whole(ctx, desc, &p) ? p.bytes : 0;
 }
 
+dq_status dqx_whole_tables(const dq_ctx *ctx, const dqx_whole *desc, dqx_tables *tables) {
+  WholePlan p;
+  if (!ctx || !desc || !tables || !plan_whole(ctx, desc, &p)) return DQ_EINVAL;
+  *tables = dqx_tables{p.shares, p.w.blocks, p.w.waves, p.w.tile_sgs, p.t.by_chunk};
+  return DQ_OK;
+}
+
 dq_status dqx_whole_run(const dq_ctx *ctx, const dqx_whole *desc, const void *const *tensors, void *scratch, float *out, void *hip_stream, void **ticket) {
   WholePlan p;
   *ticket = nullptr;

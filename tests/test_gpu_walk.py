@@ -358,10 +358,18 @@ def test_allreduces_back_to_back_on_a_side_stream_keep_their_own_tables(dev, opt
     ("butterfly", 2, 4096, 3, 5.5, 8), ("butterfly", 4, 4, 1, 3.0, 8), ("butterfly", 8, 8200, 1, 6.5, 16), ("butterfly", 16, 20656, 1, 4.3, 8),
     ("butterfly", 64, 4096, 2, 4.0, 16), ("butterfly", 128, 640, 1, 3.5, 8),
 ])
-def test_an_allreduce_enqueued_whole_equals_its_steps(dev, topology, n, J, nb, bits, max_width, dtype):
+def test_an_allreduce_enqueued_whole_equals_its_steps(dev, monkeypatch, topology, n, J, nb, bits, max_width, dtype):
     """Rows of 1,024 and their remainders, one path to 1,024 (and the first sizes that go step by step: 1,025 paths, 257 tensors, 65,537 super-groups,
     512 buckets); all gathered or not, with means or without, norms alike and masses of equal ones."""
     J = J // n * n
+    whole, enqueued = B.allreduce_whole, []
+
+    def spy(*args):
+        got = whole(*args)
+        enqueued.append(got is not None)
+        return got
+
+    monkeypatch.setattr(B, "allreduce_whole", spy)
     for seed, spread in ((1, 3.0), (2, 0.0)):
         grads = gradients(n, J * nb, dtype, dev, seed + J)
         scale = torch.exp(spread * torch.randn(J * nb, 1, device=dev, generator=torch.Generator(dev).manual_seed(seed)))
@@ -374,6 +382,7 @@ def test_an_allreduce_enqueued_whole_equals_its_steps(dev, topology, n, J, nb, b
             want, parts = allreduce.simulated_allreduce(grads, bits, fused_reorder=False, **kw)
             assert info == parts
             assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+    assert enqueued == [n <= 256 and n * nb <= 1024 and J <= 65536 and nb <= 511] * 4
 
 
 class Miscounted(list):

@@ -1,12 +1,15 @@
-"""The shares of a whole replay's waves (dqx_split): they cover every tile once, in order, and the fullest wave holds no more than the least
-that any bound per width allows (no GPU needed)."""
+"""The shares of a whole replay's waves, made on the host (dqx_split, no GPU needed) and on the device for an all-reduce that is enqueued whole: they cover
+every tile once, in order, and the fullest wave holds no more than the least that any bound per width allows."""
 import ctypes as C
 import itertools
+import math
 import random
 
 import pytest
+import torch
 
 from paper_2602_08923_amd import binding as B
+from paper_2602_08923_amd import prep, workloads
 
 
 def split(rows, n, f32, tree, sgs, blocks, waves):
@@ -27,8 +30,26 @@ def least_fullest(tiles, cost, waves):
     while True:
         most = [s // c for c in cost]
         if all(m or not t for t, m in zip(tiles, most)) and sum(t / m for t, m in zip(tiles, most) if t) <= waves:
-            return s, most
+            return s
         s += 1
+
+
+def check_shares(rows, shares, cost, waves, sgs, coarse=0):
+    """coarse: by how much the fullest wave's cost may be above the least."""
+    order = [(p, t, w) for p, row in enumerate(rows)
+             for t, w in enumerate(itertools.chain.from_iterable([w] * -(-k // sgs) for w, k in enumerate(row)))]
+    place = {(p, t): i for i, (p, t, _) in enumerate(order)}
+    place[(len(rows), 0)] = len(order)
+    at = [place[s] for s in shares]          # every share begins at a tile, or at the end
+    assert len(at) == waves + 1 and at[0] == 0 and at[-1] == len(order) and at == sorted(at)
+    least = least_fullest([sum(1 for x in order if x[2] == w) for w in range(4)], cost, waves) + coarse
+    most = [least // c for c in cost]
+    for lo, hi in zip(at, at[1:]):
+        held = [sum(1 for x in order[lo:hi] if x[2] == w) for w in range(4)]
+        if sum(1 for k in held if k) == 1:   # within the most of its width
+            assert all(k <= m for k, m in zip(held, most)), (held, most)
+        # at an edge between widths: one tile of either may be begun
+        assert sum(k * x for k, x in zip(held, cost)) <= least + 2 * max(cost)
 
 
 @pytest.mark.parametrize("seed", range(40))
@@ -47,22 +68,53 @@ def test_shares_cover_every_tile_once_and_the_fullest_is_small(seed):
         rows.append(row)
     if not any(map(sum, rows)):
         rows[0][1] = 5
-    order = [(p, t, w) for p, row in enumerate(rows)
-             for t, w in enumerate(itertools.chain.from_iterable([w] * -(-k // sgs) for w, k in enumerate(row)))]
-    shares = split(rows, n, f32, tree, sgs, blocks, waves)
-    place = {(p, t): i for i, (p, t, _) in enumerate(order)}
-    place[(len(rows), 0)] = len(order)
-    at = [place[s] for s in shares]          # every share begins at a tile, or at the end
-    assert at[0] == 0 and at[-1] == len(order) and at == sorted(at)
-    c = costs(f32, tree, n)
-    tiles = [sum(1 for x in order if x[2] == w) for w in range(4)]
-    least, most = least_fullest(tiles, c, blocks * waves)
-    for lo, hi in zip(at, at[1:]):
-        held = [sum(1 for x in order[lo:hi] if x[2] == w) for w in range(4)]
-        if sum(1 for k in held if k) == 1:   # within the most of its width
-            assert all(k <= m for k, m in zip(held, most)), (held, most)
-        # at an edge between widths: one tile of either may be begun
-        assert sum(k * x for k, x in zip(held, c)) <= least + 2 * max(c)
+    check_shares(rows, split(rows, n, f32, tree, sgs, blocks, waves), costs(f32, tree, n), blocks * waves, sgs)
+
+
+class Whole(C.Structure):
+    _fields_ = [("topology", C.c_int), ("dtype", C.c_int), ("n_sg_bucket", C.c_uint32), ("n_buckets", C.c_uint32), ("max_code_bits", C.c_uint64),
+                ("max_width", C.c_uint32), ("all_gather", C.c_uint32), ("means", C.c_uint32), ("n_tensors", C.c_uint32)]
+
+
+class Tables(C.Structure):
+    _fields_ = [("shares", C.c_size_t), ("blocks", C.c_uint32), ("waves", C.c_uint32), ("tile_sgs", C.c_uint32), ("by_chunk", C.c_uint32)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("topology,n,J,nb,bits,max_width", [
+    # a tile for every wave and none over: at the bound of a width every wave has to count
+    ("ring", 3, 204, 1, 7.15, 16), ("ring", 16, 1936, 1, 4.5, 8), ("ring", 2, 512, 3, 6.0, 16), ("butterfly", 8, 912, 1, 3.71, 8), ("butterfly", 32, 2688, 1, 5.5, 16),
+    # tiles of two and four, a few waves over; several tiles per wave
+    ("ring", 7, 4508, 1, 5.0, 8), ("ring", 8, 8192, 1, 4.6875, 8), ("ring", 20, 14160, 1, 8.43, 16), ("butterfly", 2, 11456, 3, 4.01, 8),
+    ("butterfly", 16, 20656, 1, 4.3, 8), ("ring", 5, 50005, 2, 6.5, 16), ("butterfly", 4, 65536, 1, 5.0, 8),
+])
+def test_shares_made_on_the_device(topology, n, J, nb, bits, max_width, dtype):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    L, dev, ctx, tree = B.lib(), torch.device("cuda:0"), B.Context(n, seed=3), topology == "butterfly"
+    f32 = dtype == torch.float32
+    J = J // n * n
+    magnitudes = workloads.mixture_magnitudes(J * nb, seed=J, device=dev).clamp_(1e-12, 1e3).unsqueeze(1)
+    gen = torch.Generator(device=dev).manual_seed(n)
+    grads = [(torch.randn(J * nb, 256, generator=gen, device=dev) * magnitudes).to(dtype).contiguous() for _ in range(n)]
+    desc = Whole(B.DQ_BUTTERFLY if tree else B.DQ_RING, B.DQ_F32 if f32 else B.DQ_BF16, J, nb, math.floor(prep.code_bits(bits) * J), max_width, 1, 1, n)
+    L.dqx_whole_scratch_bytes.restype = C.c_size_t
+    scratch = torch.empty(L.dqx_whole_scratch_bytes(ctx.h, C.byref(desc)), dtype=torch.uint8, device=dev)
+    assert scratch.numel()
+    out, ticket, counts, tables = torch.empty(J * nb * 256, device=dev), C.c_void_p(), (C.c_uint32 * (4 * nb))(), Tables()
+    addresses, stream = (C.c_void_p * n)(*[g.data_ptr() for g in grads]), C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert L.dqx_whole_tables(ctx.h, C.byref(desc), C.byref(tables)) == 0
+    assert L.dqx_whole_run(ctx.h, C.byref(desc), addresses, C.c_void_p(scratch.data_ptr()), C.c_void_p(out.data_ptr()), stream, C.byref(ticket)) == 0
+    assert L.dqx_allocate_end(ticket, C.c_uint32(J), C.c_uint32(nb), counts, stream) == 0
+    waves = tables.blocks * tables.waves
+    got = scratch[tables.shares:tables.shares + 8 * (waves + 1)].view(torch.int32).cpu().reshape(-1, 2).tolist()
+    per_bucket = [chunks(counts[4 * b:4 * b + 4], n) for b in range(nb)]
+    rows = [per_bucket[b][c] for c in range(n) for b in range(nb)] if tables.by_chunk else [row for bucket in per_bucket for row in bucket]
+    cost = costs(f32, tree, n)
+    mean = sum(-(-k // tables.tile_sgs) * c for row in rows for k, c in zip(row, cost)) // waves
+    # the device looks for the cost of the fullest wave in steps of 1 + a 64th of the mean
+    check_shares(rows, [tuple(x) for x in got], cost, waves, tables.tile_sgs, coarse=mean // 64)
 
 
 def chunks(by_width, n):
