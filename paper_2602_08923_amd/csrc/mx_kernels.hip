@@ -650,11 +650,14 @@ done:
 //   Above, most inputs come from memory, and what counts is how many requests are on their way: this kernel's are eight leaves' of each wave, the walk's one or two
 // workers' of each of three blocks per CU.  But everyone waits for the CUs that have a block of the walk more than others, where inputs stay in the cache.
 // fp32: of 16 workers and more all (0.84 to 1.0); of 8 to 15 all but the second block's last quarter (32 tiles per CU: 1.0 to 1.13; 40: 0.84 to 0.9); 4 to 7
-// from the third block on (0.9 to 1.0) and in a quarter of the second (0.78 to 0.92); fewer never (1.05 to 1.3).  6-bit from 45 (16 workers; 0.88 to 1.0) and 75 (8).
+// from 36 on (0.9 to 1.0) and in a quarter of the second (0.78 to 0.92); fewer never (1.05 to 1.3).  6-bit from 45 (16 workers; 0.88 to 1.0) and 75 (8).
 // bf16, whose walk moves half the bytes and has less to wait for: 8 to 47 workers from 50 tiles per CU (0.87 to 0.98; 40: 0.95 to 1.05; halvings of 8 from 65), more workers
 // from 100 (0.93 to 0.98; 46 to 75: 0.93 to 1.09); 4 to 7 from 165 to 400 (0.87 to 0.96); an eighth of the second block of 64 workers and more
 // (0.84 to 0.9; chains of 100 and more 1.05 to 1.07).  6-bit from 100 (16 workers: 0.89 to 0.97) and 150 (8: 0.87 to 0.97).
-//   600 drawn replays against the walk wherever fp32's or a large bf16 ring's shape did not ask for this: 1.00 to 1.06 of their time by format, type and workers; 1.7 % on average.
+//   Inputs that are used again and again, or were just written, come from the cache up to some 250 MB, and lose by that: bf16 of 8 to 15 workers between 50 tiles per CU and that size
+// 1.03 to 1.18 where from memory it is 0.87 to 1.04; fp32 of 4 to 7 workers 1.0 to 1.16 for 0.9 to 1.0; fp32 of 8 to 15 at 28 and 48 tiles per CU 1.03 and 1.09 for 0.87.  The walk from the
+// cache and this kernel from memory cannot both be had, as the library does not know where its inputs are.
+//   600 drawn replays from memory against the walk wherever fp32's or a large bf16 ring's shape did not ask for this: 1.00 to 1.06 of their time by format, type and workers; 1.7 % on average.
 template <int FMT, typename LT, bool TREE>
 bool takes_quad(uint32_t n, uint32_t n_chunks, uint64_t tiles, uint32_t n_cu) {
   constexpr bool six = FMT == DQ_MXFP6_E3M2, wide = sizeof(LT) == 4;
