@@ -477,7 +477,7 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
   return true;
 }
 
-// Where every wave's share of the tiles begins.  All waves are resident at once and a SIMD's waves share its issue, so what counts is how much the
+// Where every wave's share of the tiles begins.  All waves of tiles of four are resident at once (of narrower ones mostly, too) and a SIMD's waves share its issue, so what counts is how much the
 // fullest waves hold: one with three tiles where the others have two works on alone for a third of the launch, and shares of equal cost (or equal
 // count) leave that to chance.  Here every width gets a most, the tiles of it that a wave may hold, such that the fullest wave costs as little as
 // possible and then each most, the dearest first, is as small as the waves allow; and the costs are raised just so far that equal shares keep to it.
@@ -485,16 +485,17 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
 //   ring of 8, 51,200 in bf16: 17,608/33,584/8  60.5 -> 59.6;  a quarter, a quarter, a half  69.1 -> 61.4;  of 11, 25,322  57.5 -> 49.5
 //   recursive halving in bf16 over 8, 18,504  36.8 -> 23.8;  over 32, 20,128  119 -> 91;  over 16, 8 x 51,200 at 3 bits  833 -> 831
 //   in fp32: ring of 6, 8 x 44,976  687 -> 573;  halving over 2, 8 x 40,450  269 -> 214
-// The geometric mean of 230 schedules of 2 to 100 workers and 14,000 to 400,000 super-groups: rings in bf16 and fp32 3.9 and 2.7 % faster, halvings
-// 10.5 and 6.6 (8 of the 230 lose more than 5 %, mostly where half the waves have one tile and half two).
+// The geometric mean of 240 schedules of 2 to 100 workers and 1,000 to 40,700 super-groups: rings in bf16 and fp32 4.8 and 1.5 % faster, halvings
+// 8.2 and 4.1 (of 14,000 and more 7.4, 1.2, 9.6 and 8.3); ten of the 240 lose more than 3 %, three more than 5 (profiles/replay_shares.txt).
 // A tile's costs: what its instructions take beside the memory's time, which all widths have alike, measured as the ratios that are fastest: 1.8 to 2.2 with
-// bf16 tensors of five workers and more, 1.1 to 1.25 where a hop moves more bytes (fp32, or a result of 4 bytes per few workers).  (12/15/16
-// instead of 12/24/26 for the first ring above: 64.2.)  A raw tile has the fewest instructions but waits for every slice: as dear as a 2-bit one it came four
+// bf16 tensors of five workers and more, 1.1 to 1.25 where a hop moves more bytes (fp32, or a result of 4 bytes per two or three workers).  (12/15/16
+// instead of 12/24/26 for the first ring above: 64.2.  58 schedules over 4 in bf16 with 12/20/22 1.2 % faster than with 12/14/15, halving of 9,872/24,561/2,107 25.6 -> 23.1; 92 over 2
+// and 3 1.2 % slower.)  A raw tile has the fewest instructions but waits for every slice: as dear as a 2-bit one it came four
 // to a wave where others held one (bf16 ring of 24, 5,354/9,868/5,525/10,261: 111 to 116 us, 95 so, 98 with equal counts).  Only in halvings over 16 workers
 // and more, whose stack it hardly uses, it is no dearer (55 such schedules of bf16 at 2 to 4 tiles per wave 1 % faster so).
 Costs costs_of(dq_dtype dtype, bool tree, uint32_t n) {
-  if (dtype == DQ_F32 || n <= 4) return Costs{{12, 14, 15, 15}};
-  return tree ? Costs{{12, 20, 22, n <= 12 ? 15u : 12u}} : Costs{{12, 24, 26, 15}};
+  if (dtype == DQ_F32 || n <= 3) return Costs{{12, 14, 15, 15}};
+  return tree || n == 4 ? Costs{{12, 20, 22, n <= 12 ? 15u : 12u}} : Costs{{12, 24, 26, 15}};
 }
 namespace {
 // The most tiles per wave of every width (0: there is none of it), at most `waves` waves.

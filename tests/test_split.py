@@ -22,7 +22,7 @@ def split(rows, n, f32, tree, sgs, blocks, waves):
 
 
 def costs(f32, tree, n):
-    return (12, 14, 15, 15) if f32 or n <= 4 else (12, 20, 22, 15 if n <= 12 else 12) if tree else (12, 24, 26, 15)
+    return (12, 14, 15, 15) if f32 or n <= 3 else (12, 20, 22, 15 if n <= 12 else 12) if tree or n == 4 else (12, 24, 26, 15)
 
 
 def least_fullest(tiles, cost, waves):
