@@ -413,7 +413,8 @@ static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, u
 //   tree f32  16  14.1/15.5/23.6  16.8/17.1/23.8  22.2/18.0/23.8  27.6/23.4/24.8  28.9/29.9/26.3  32.6/36.2/38.5
 //   tree bf16 64  42.9/52.3/88.6  69.0/65.5/88.0  75.7/95.1/86.7  84.1/104/90.2   94.9/105/93.3   112/108/105
 // Rings and short trees: one super-group while four waves per SIMD hold them all (a little longer where a wave's start counts more than its hops,
-// less with two workers, whose waves have no more than a start); two, for bf16 rings of nine workers and more and short trees, up to 24 or 32
+// less with two workers, whose waves have no more than a start: 12 per CU, but 20 and 16 with an all-gather behind it, halving over 2 at 16 on the original tensors
+// 6.2/7.1/7.0 with and 5.7/6.6/6.0 without); two, for bf16 rings of nine workers and more and short trees, up to 24 or 32
 // per CU; then four.  What the CUs hold of a wider butterfly falls with the levels of its stack, differently for each
 // tile size, so there the time is estimated, up to 48 super-groups per CU: beyond, the three are within 20 % of each other with no order.
 // Of the 252 rows (two mixtures of widths each) the rule's choice is on average 0.6 % behind the best.  LDS is counted in the pieces it is given out in, and tiles of
@@ -428,7 +429,7 @@ static uint64_t tree_time(uint32_t n, uint32_t n_cu, uint32_t sgs, uint64_t tile
   return c.launch + rounds * c.start + n * (rounds * c.hop + waves * c.wave);
 }
 // Super-groups of a tile, or 0: by tree_time.
-static uint32_t tile_for(uint32_t n, bool f32, bool tree, uint32_t n_cu, uint64_t super_groups) {
+static uint32_t tile_for(uint32_t n, bool f32, bool tree, bool all_gather, uint32_t n_cu, uint64_t super_groups) {
   const uint32_t per_cu = (uint32_t)((super_groups + n_cu - 1) / n_cu);
   if (tree && n >= 32) return per_cu <= 48 ? 0 : kWaveSGs;
   uint32_t one = 16, two = 16;  // up to so many per CU
@@ -436,7 +437,7 @@ static uint32_t tile_for(uint32_t n, bool f32, bool tree, uint32_t n_cu, uint64_
     if (tree) two = n <= 4 ? 16 : 24;
     else one = two = n <= 4 ? 12 : n <= 16 ? 16 : 20;
   } else if (n <= 8) {
-    one = two = n <= 2 ? 12 : tree ? (n <= 4 ? 20 : 24) : n <= 4 ? 16 : 20;
+    one = two = n <= 2 ? (!all_gather ? 12 : tree ? 20 : 16) : tree ? (n <= 4 ? 20 : 24) : n <= 4 ? 16 : 20;
   } else {
     two = !tree && n >= 32 ? 32 : 24;
   }
@@ -447,7 +448,7 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
   const bool f32 = dtype == DQ_F32;
   const uint64_t super_groups = tiles_of[0];
   if (super_groups == 0) return false;
-  const uint32_t wanted = tile_for(W->n, f32, tree, n_cu, super_groups);
+  const uint32_t wanted = tile_for(W->n, f32, tree, W->encodes == W->n, n_cu, super_groups);
   Walk best = *W;
   uint64_t best_time = 0;
   bool found = false;

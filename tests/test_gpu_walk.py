@@ -108,6 +108,13 @@ def test_whole_replay_of_few_tiles_per_wave_equals_its_steps(dev, topology, n, w
     test_whole_replay_equals_its_steps(dev, topology, n, widths, False, True, dtype)
 
 
+@pytest.mark.parametrize("all_gather", [False, True])
+@pytest.mark.parametrize("topology,J", [("ring", 3072), ("ring", 3074), ("ring", 4096), ("ring", 4098), ("butterfly", 3074), ("butterfly", 5120), ("butterfly", 5122)])
+def test_whole_replay_of_two_workers_equals_its_steps(dev, topology, J, all_gather):
+    """Both sides of the sizes from which tiles of four super-groups are taken, which the all-gather moves."""
+    test_whole_replay_equals_its_steps(dev, topology, 2, [[J // 3, J - J // 3 - 901, 701, 200]], all_gather, True, torch.bfloat16)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("topology,J", [("ring", 64), ("butterfly", 64), ("ring", 8192), ("butterfly", 8192)])   # one and four super-groups per tile
 def test_whole_replay_of_extreme_magnitudes_equals_its_steps(dev, topology, J, dtype):
