@@ -110,7 +110,7 @@ hipError_t launch_thin(dq_dtype dtype, bool tree, const WalkPath *paths_dev, con
 // tiles: of one, two and four super-groups.  False: no launch fits
 bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const uint64_t tiles[3], Walk *W);
 struct Costs { uint32_t of[4]; };
-Costs costs_of(dq_dtype dtype, bool tree, uint32_t n);  // of a tile, by width
+Costs costs_of(dq_dtype dtype, bool tree, uint32_t n, uint32_t tile_sgs);  // of a tile, by width
 void split_walk(const WalkPath *paths_host, dq_dtype dtype, bool tree, const Walk &W, std::vector<WalkShare> *shares);
 hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W,
                        const Params &P, hipStream_t stream);

@@ -928,7 +928,7 @@ bool plan_whole(const dq_ctx *ctx, const dqx_whole *d, WholePlan *p) {
   t.entry_bytes = (uint32_t)elt_size(d->dtype);
   t.waves = w.blocks * w.waves;
   t.tile_log = w.tile_sgs / 2;
-  t.cost = dq::costs_of(d->dtype, tree, n);
+  t.cost = dq::costs_of(d->dtype, tree, n, w.tile_sgs);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t at = off;

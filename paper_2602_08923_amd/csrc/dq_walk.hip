@@ -414,7 +414,7 @@ static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, u
 //   tree bf16 64  42.9/52.3/88.6  69.0/65.5/88.0  75.7/95.1/86.7  84.1/104/90.2   94.9/105/93.3   112/108/105
 // Rings and short trees: one super-group while four waves per SIMD hold them all (a little longer where a wave's start counts more than its hops,
 // less with two workers, whose waves have no more than a start: 12 per CU, but 20 and 16 with an all-gather behind it, halving over 2 at 16 on the original tensors
-// 6.2/7.1/7.0 with and 5.7/6.6/6.0 without); two, for bf16 rings of nine workers and more and short trees, up to 24 or 32
+// 6.2/7.1/7.0 with and 5.7/6.6/6.0 without); two, for fp32 rings of 11 to 16 (16 at 17 19.5/19.4/21.5) and fp32 halvings over 2 and 4 with an all-gather (2 at 18 8.2/7.2/7.8) up to 21, for bf16 rings of nine workers and more and short trees, up to 24 or 32
 // per CU; then four.  What the CUs hold of a wider butterfly falls with the levels of its stack, differently for each
 // tile size, so there the time is estimated, up to 48 super-groups per CU: beyond, the three are within 20 % of each other with no order.
 // Of the 252 rows (two mixtures of widths each) the rule's choice is on average 0.6 % behind the best.  LDS is counted in the pieces it is given out in, and tiles of
@@ -434,8 +434,12 @@ static uint32_t tile_for(uint32_t n, bool f32, bool tree, bool all_gather, uint3
   if (tree && n >= 32) return per_cu <= 48 ? 0 : kWaveSGs;
   uint32_t one = 16, two = 16;  // up to so many per CU
   if (f32) {
-    if (tree) two = n <= 4 ? 16 : 24;
-    else one = two = n <= 4 ? 12 : n <= 16 ? 16 : 20;
+    if (tree) {
+      two = n > 4 ? 24 : all_gather ? 21 : 16;
+    } else {
+      one = n <= 4 ? 12 : n <= 16 ? 16 : 20;
+      two = n <= 10 ? one : n <= 16 ? 21 : 20;
+    }
   } else if (n <= 8) {
     one = two = n <= 2 ? (!all_gather ? 12 : tree ? 20 : 16) : tree ? (n <= 4 ? 20 : 24) : n <= 4 ? 16 : 20;
   } else {
@@ -492,11 +496,13 @@ bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const 
 // bf16 tensors of five workers and more, 1.1 to 1.25 where a hop moves more bytes (fp32, or a result of 4 bytes per two or three workers).  (12/15/16
 // instead of 12/24/26 for the first ring above: 64.2.  58 schedules over 4 in bf16 with 12/20/22 1.2 % faster than with 12/14/15, halving of 9,872/24,561/2,107 25.6 -> 23.1; 92 over 2
 // and 3 1.2 % slower.)  A raw tile has the fewest instructions but waits for every slice: as dear as a 2-bit one it came four
-// to a wave where others held one (bf16 ring of 24, 5,354/9,868/5,525/10,261: 111 to 116 us, 95 so, 98 with equal counts).  Only in halvings over 16 workers
-// and more, whose stack it hardly uses, it is no dearer (55 such schedules of bf16 at 2 to 4 tiles per wave 1 % faster so).
-Costs costs_of(dq_dtype dtype, bool tree, uint32_t n) {
-  if (dtype == DQ_F32 || n <= 3) return Costs{{12, 14, 15, 15}};
-  return tree || n == 4 ? Costs{{12, 20, 22, n <= 12 ? 15u : 12u}} : Costs{{12, 24, 26, 15}};
+// to a wave where others held one (bf16 ring of 24, 5,354/9,868/5,525/10,261: 111 to 116 us, 95 so, 98 with equal counts).  It is no dearer in bf16 halvings
+// over 16 workers and more, whose stack it hardly uses (55 schedules at 2 to 4 tiles per wave 1 % faster so), and in tiles of one and two, where it is the shortest (halving over 8 of
+// 1,126/427/565/2,058 12.6 us, 14.1 at 15; 110 schedules the same or faster).
+Costs costs_of(dq_dtype dtype, bool tree, uint32_t n, uint32_t tile_sgs) {
+  const uint32_t raw = tile_sgs < kWaveSGs || (dtype != DQ_F32 && tree && n > 12) ? 12 : 15;
+  if (dtype == DQ_F32 || n <= 3) return Costs{{12, 14, 15, raw}};
+  return tree || n == 4 ? Costs{{12, 20, 22, raw}} : Costs{{12, 24, 26, raw}};
 }
 namespace {
 // The most tiles per wave of every width (0: there is none of it), at most `waves` waves.
@@ -549,7 +555,7 @@ void split_walk(const WalkPath *paths, dq_dtype dtype, bool tree, const Walk &W,
   uint64_t tiles[4] = {0, 0, 0, 0}, most[4], cost[4], total = 0;
   for (uint32_t p = 0; p < W.n_paths; ++p)
     for (int w = 0; w < 4; ++w) tiles[w] += (paths[p].job.n_sg[w] + sgs - 1) / sgs;
-  const Costs c = costs_of(dtype, tree, W.n);
+  const Costs c = costs_of(dtype, tree, W.n, sgs);
   most_per_wave(tiles, c.of, n, most);
   // Equal shares of cost total / n hold at most `most` tiles of a width that costs at least that over `most`.  The costs rise until that is so, each
   // round by less; where the waves are just enough it is so at the cost of the fullest.

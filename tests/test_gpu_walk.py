@@ -108,11 +108,14 @@ def test_whole_replay_of_few_tiles_per_wave_equals_its_steps(dev, topology, n, w
     test_whole_replay_equals_its_steps(dev, topology, n, widths, False, True, dtype)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("all_gather", [False, True])
-@pytest.mark.parametrize("topology,J", [("ring", 3072), ("ring", 3074), ("ring", 4096), ("ring", 4098), ("butterfly", 3074), ("butterfly", 5120), ("butterfly", 5122)])
-def test_whole_replay_of_two_workers_equals_its_steps(dev, topology, J, all_gather):
-    """Both sides of the sizes from which tiles of four super-groups are taken, which the all-gather moves."""
-    test_whole_replay_equals_its_steps(dev, topology, 2, [[J // 3, J - J // 3 - 901, 701, 200]], all_gather, True, torch.bfloat16)
+@pytest.mark.parametrize("topology,n,J", [("ring", 2, 3072), ("ring", 2, 3074), ("ring", 2, 4096), ("ring", 2, 4098), ("butterfly", 2, 3074), ("butterfly", 2, 4098),
+                                          ("butterfly", 2, 5120), ("butterfly", 2, 5122), ("butterfly", 4, 4100), ("butterfly", 4, 5376), ("butterfly", 4, 5380), ("ring", 11, 5368),
+                                          ("ring", 16, 5376), ("ring", 16, 5392)])
+def test_whole_replay_of_few_super_groups_per_cu_equals_its_steps(dev, topology, n, J, all_gather, dtype):
+    """Both sides of the sizes from which tiles of two and of four super-groups are taken; the all-gather moves some."""
+    test_whole_replay_equals_its_steps(dev, topology, n, [[J // 3, J - J // 3 - 901, 701, 200]], all_gather, True, dtype)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])

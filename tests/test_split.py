@@ -21,8 +21,9 @@ def split(rows, n, f32, tree, sgs, blocks, waves):
     return [(got[2 * i], got[2 * i + 1]) for i in range(blocks * waves + 1)]
 
 
-def costs(f32, tree, n):
-    return (12, 14, 15, 15) if f32 or n <= 3 else (12, 20, 22, 15 if n <= 12 else 12) if tree or n == 4 else (12, 24, 26, 15)
+def costs(f32, tree, n, sgs):
+    raw = 12 if sgs < 4 or (not f32 and tree and n > 12) else 15
+    return (12, 14, 15, raw) if f32 or n <= 3 else (12, 20, 22, raw) if tree or n == 4 else (12, 24, 26, raw)
 
 
 def least_fullest(tiles, cost, waves):
@@ -68,7 +69,7 @@ def test_shares_cover_every_tile_once_and_the_fullest_is_small(seed):
         rows.append(row)
     if not any(map(sum, rows)):
         rows[0][1] = 5
-    check_shares(rows, split(rows, n, f32, tree, sgs, blocks, waves), costs(f32, tree, n), blocks * waves, sgs)
+    check_shares(rows, split(rows, n, f32, tree, sgs, blocks, waves), costs(f32, tree, n, sgs), blocks * waves, sgs)
 
 
 class Whole(C.Structure):
@@ -111,7 +112,7 @@ def test_shares_made_on_the_device(topology, n, J, nb, bits, max_width, dtype):
     got = scratch[tables.shares:tables.shares + 8 * (waves + 1)].view(torch.int32).cpu().reshape(-1, 2).tolist()
     per_bucket = [chunks(counts[4 * b:4 * b + 4], n) for b in range(nb)]
     rows = [per_bucket[b][c] for c in range(n) for b in range(nb)] if tables.by_chunk else [row for bucket in per_bucket for row in bucket]
-    cost = costs(f32, tree, n)
+    cost = costs(f32, tree, n, tables.tile_sgs)
     mean = sum(-(-k // tables.tile_sgs) * c for row in rows for k, c in zip(row, cost)) // waves
     # the device looks for the cost of the fullest wave in steps of 1 + a 64th of the mean
     check_shares(rows, [tuple(x) for x in got], cost, waves, tables.tile_sgs, coarse=mean // 64)
