@@ -441,7 +441,7 @@ static uint32_t tile_for(uint32_t n, bool f32, bool tree, bool all_gather, uint3
       two = n <= 10 ? one : n <= 16 ? 21 : 20;
     }
   } else if (n <= 8) {
-    one = two = n <= 2 ? (!all_gather ? 12 : tree ? 20 : 16) : tree ? (n <= 4 ? 20 : 24) : n <= 4 ? 16 : 20;
+    one = two = n <= 2 ? (!all_gather ? 12 : tree ? 20 : 16) : tree ? (n <= 4 ? 22 : 24) : n <= 4 ? 16 : 20;
   } else {
     two = !tree && n >= 32 ? 32 : 24;
   }

@@ -111,7 +111,7 @@ def test_whole_replay_of_few_tiles_per_wave_equals_its_steps(dev, topology, n, w
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("all_gather", [False, True])
 @pytest.mark.parametrize("topology,n,J", [("ring", 2, 3072), ("ring", 2, 3074), ("ring", 2, 4096), ("ring", 2, 4098), ("butterfly", 2, 3074), ("butterfly", 2, 4098),
-                                          ("butterfly", 2, 5120), ("butterfly", 2, 5122), ("butterfly", 4, 4100), ("butterfly", 4, 5376), ("butterfly", 4, 5380), ("ring", 11, 5368),
+                                          ("butterfly", 2, 5120), ("butterfly", 2, 5122), ("butterfly", 4, 4100), ("butterfly", 4, 5376), ("butterfly", 4, 5380), ("butterfly", 4, 5632), ("butterfly", 4, 5636), ("ring", 11, 5368),
                                           ("ring", 16, 5376), ("ring", 16, 5392)])
 def test_whole_replay_of_few_super_groups_per_cu_equals_its_steps(dev, topology, n, J, all_gather, dtype):
     """Both sides of the sizes from which tiles of two and of four super-groups are taken; the all-gather moves some."""
