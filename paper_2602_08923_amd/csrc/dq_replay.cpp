@@ -894,8 +894,8 @@ void dq_replay_destroy(dq_replay *plan) {
 // ---- a whole simulated all-reduce on the original tensors, enqueued without waiting: statistics, search, then (arrange) means, origins and the
 // tables of the replay, then the replay.  The host never needs the class counts to go on: how many waves there are follows from the
 // schedule's super-groups, and which tiles each takes is worked out on the device.  With the counts sent to the host and the plan made there the GPU
-// waited 15 us for it, and 5.4 for the tables' upload: 8 workers' ring of 8,192 super-groups in bf16 58.1 -> 39.5 us, 16 workers' of 1,936 60.9 -> 37.9,
-// recursive halving over 2 of 30,416 61.4 -> 47.2.
+// waited 15 us for it, and 5.4 for the tables' upload: 8 workers' ring of 8,192 super-groups in bf16 58.1 -> 36.3 us, 16 workers' of 1,936 60.9 -> 32.2,
+// recursive halving over 2 of 30,416 61.4 -> 42.2.
 namespace {
 struct WholePlan {
   dq::Walk w = {};

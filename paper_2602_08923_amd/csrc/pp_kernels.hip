@@ -313,12 +313,12 @@ __device__ __forceinline__ uint32_t last_tied(uint32_t v, float by, float back, 
   return below;
 }
 
-// A block's LDS: the first level's counters, over which buckets of more than 16 rows then lay the norms that the other levels look at, and those
-// levels' counters: 86 KB.  A search that runs beside a whole replay waits for a CU that has that much in one piece, and registers for sixteen waves; two blocks
+// A block's LDS: the first level's counters, over which the threads then lay their norms that the other levels look at, and those levels' counters: 86 KB.  A search that runs beside a whole replay waits for a CU that has that much in one piece, and registers for sixteen waves; two blocks
 // of k_walk (29 KB, 96 registers) may stay beside it.
 constexpr uint32_t kFirstWords = (kBins + 1) * kCopies;
 static_assert((kKept + 1) * kAllocThreads <= kFirstWords, "the norms set aside");
 
+// ASIDE: buckets of more than 16 rows, whose threads hold up to 64 norms each, so that those inside the brackets may be more than the kKept that have room.
 template <bool ALLOW16, bool ASIDE>
 __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits, uint32_t *pos_all,
                                                           uint32_t *counts_all, dq::Announce announce) {
