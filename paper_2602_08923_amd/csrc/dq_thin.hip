@@ -10,7 +10,7 @@
 // schedules come here.
 //
 // What bounds it is how much of a hop's chain four waves per SIMD cover: two vector instructions can go per four cycles, from two waves,
-// and about half of that is reached (256 workers, 4,096 super-groups: 97 instructions per hop, 177 us; 92 would be their issue).  So all
+// and about half of that is reached (256 workers, 4,096 super-groups: 93 instructions per hop, 169 to 175 us; 88 would be their issue).  So all
 // instructions count, on the path or beside it, scalar ones and waits too: both super-group draws made by one generator call, the next four tensors
 // by one scalar load and the group scale left in fp32 took 188 us there to 184, four workers' fp32 ring of 4,096 with all-gather from 9.9 to 9.1;
 // the super-group's maximum and scale in scalar registers and the rounding of the group scale in two instructions 185 to 177.
@@ -75,13 +75,22 @@ __device__ __forceinline__ uint64_t tensor_of(const Walk &W, uint32_t chunk, uin
   return table_entry(reinterpret_cast<const uint64_t *>(W.grads), TREE ? leaf_of<TREE>(W, chunk, i) : (W.chain ? 0u : chunk) + i);
 }
 
-// Maximum over a super-group of which every lane of the wave has its group's maximum
+// Maximum over a super-group of which every lane of the wave has its group's maximum.  (As one block, as the compiler makes three instructions of each of the
+// last two maxima.  A maximum reads what the one before it wrote from other lanes: two wait states between them.)
 __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
-  x = max(x, dpp_u<0x124>(x));  // row_ror:4
-  x = max(x, dpp_u<0x128>(x));  // row_ror:8
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x142, 0xA, 0xF, false));  // row 0 into 1, row 2 into 3
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x143, 0xC, 0xF, false));  // row 1 into 2 and 3
-  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+  uint32_t top;
+  asm("s_nop 1\n\t"
+      "v_max_u32_dpp %1, %1, %1 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\t"
+      "v_max_u32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\t"
+      "v_max_u32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"  // row 0 into 1, row 2 into 3
+      "s_nop 1\n\t"
+      "v_max_u32_dpp %1, %1, %1 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"  // row 1 into 2 and 3
+      "s_nop 1\n\t"
+      "v_readlane_b32 %0, %1, 63"
+      : "=s"(top), "+v"(x));
+  return top;
 }
 
 // What a wave holds of a tile before it walks it: where it is and the slices of its first hops.
@@ -152,6 +161,25 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
   float v[E], level[E], sfg = 0.0f;  // the pending message: level * sfg
 #pragma unroll
   for (int k = 0; k < E; ++k) level[k] = -0.0f;  // nothing pending: adding -0 changes nothing
+  auto widen = [&](const Bit<LT, E> &b, float (&y)[E]) {
+    if constexpr (sizeof(LT) == 4) {
+#pragma unroll
+      for (int k = 0; k < E; ++k) y[k] = u2f(b.w[k]) - x.mu;
+    } else {
+#pragma unroll
+      for (int k = 0; k < E / 2; ++k) {
+        y[2 * k] = u2f(b.w[k] << 16) - x.mu;
+        y[2 * k + 1] = u2f(b.w[k] & 0xFFFF0000u) - x.mu;
+      }
+    }
+  };
+  // Whether a hop's steps stand in the order in which the next needs them: the searches, beside their trip to LDS the scale of the super-group; the levels,
+  // beside theirs all that does not depend on them: the group's scale, the random numbers, the next hop's entries.  Where a wave is alone or in
+  // throughput, bf16 rings are faster so (256 workers 172.8 -> 171.0 us, 100 of 2,000 super-groups 47.3 -> 46.3); in fp32, whose entries then wait
+  // for memory a hop earlier, slower (32 of 4,096 30.3 -> 32.9), and recursive halvings (128 of 384 53.6 -> 54.8).
+  constexpr bool kEarly = !TREE && E == 4 && sizeof(LT) == 2;
+  float next[E];  // kEarly: the next hop's entries
+  if constexpr (kEarly) widen(x.s[0], next);
 
   // kAhead hops from i0 on.  PLAIN: all of them encode, none writes its message, and the slices to request exist.
   auto some_hops = [&](uint32_t i0, auto plain) {
@@ -172,18 +200,8 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
       const uint32_t i = i0 + j;
       __builtin_amdgcn_sched_barrier(0);
       float y[E];
-      if constexpr (sizeof(LT) == 4) {
-#pragma unroll
-        for (int k = 0; k < E; ++k) y[k] = u2f(x.s[j].w[k]) - x.mu;
-      } else {
-#pragma unroll
-        for (int k = 0; k < E / 2; ++k) {
-          y[2 * k] = u2f(x.s[j].w[k] << 16) - x.mu;
-          y[2 * k + 1] = u2f(x.s[j].w[k] & 0xFFFF0000u) - x.mu;
-        }
-      }
-      // past the last hop: the last slice again, out of the cache
-      x.s[j] = load_bit<LT, E>(tensor[j], x.at);
+      if constexpr (!kEarly) widen(x.s[j], y);
+      x.s[j] = load_bit<LT, E>(tensor[j], x.at);  // past the last hop: the last slice again, out of the cache
       if (PLAIN || i <= last) {
         if constexpr (B != 16) {
           if (j % kLanes == 0) {
@@ -223,7 +241,8 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
           offset = lds_ld2(draws + 1024 + jj * (512 / kLanes) + (lane / kLanes) * 8);
         }
 #pragma unroll
-        for (int k = 0; k < E; ++k) v[k] = y[k];
+        for (int k = 0; k < E; ++k) v[k] = kEarly ? next[k] : y[k];
+        if constexpr (B == 16 && kEarly) widen(x.s[(j + 1) % kAhead], next);
         if (!TREE || (j & 1)) {
 #pragma unroll
           for (int k = 0; k < E; ++k) v[k] = B == 16 ? level[k] + v[k] : __builtin_fmaf(level[k], sfg, v[k]);
@@ -270,43 +289,68 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
             // The scales, as in scale_group.  With one super-group per wave its maximum and what follows from it are scalar, and a
             // super-group that is encoded as zero finds zeros for its reciprocals.  With two such a one has its groups' maxima taken as zero instead
             // of its results: as conditional results the compiler puts the chain behind a branch, after the levels' lookups.
-            const uint32_t top = (E == 4 ? wave_max(mg) : sg_max<E>(mg)) + 0xFFFFu;
-            const bool tiny = top < 0x0D800000u;
-            const uint32_t b = tiny ? 0u : top, sfb = b >> 16, ex = b & 0x7F800000u;
-            const u32x2 rec = lds_ld2(E == 4 && tiny ? zeros : kRec0 + ((b >> 13) & 0x3F8u));
-            if (E != 4 && tiny) m = 0.0f;
-            float xs[E];
+            // The scales, as in scale_group.  With one super-group per wave its maximum and what follows from it are scalar, and a
+            // super-group that is encoded as zero finds zeros for its reciprocals.  With two such a one has its groups' maxima taken as zero instead
+            // of its results: as conditional results the compiler puts the chain behind a branch, after the levels' lookups.
+            uint32_t sfb, ex;
+            u32x2 rec;
+            auto look_up_scale = [&] {
+              const uint32_t top = (E == 4 ? wave_max(mg) : sg_max<E>(mg)) + 0xFFFFu;
+              const bool tiny = top < 0x0D800000u;
+              const uint32_t b = tiny ? 0u : top;
+              sfb = b >> 16;
+              ex = b & 0x7F800000u;
+              rec = lds_ld2(E == 4 && tiny ? zeros : kRec0 + ((b >> 13) & 0x3F8u));
+              if (E != 4 && tiny) m = 0.0f;
+            };
+            if constexpr (!kEarly) look_up_scale();
+            float xs[E], u[E];
+            u32x2 e[E];
             u32x4 t[E];
-            auto uniform = [&](int k) { return __builtin_fmaf((float)((gam[k >> 2] >> (8 * (k & 3))) & 0xFFu), V.s_n, u2f(offset.x)); };
-            if constexpr (B == 2) {
 #pragma unroll
-              for (int k = 0; k < E; ++k) xs[k] = v[k] * inv;
-            } else {
-              u32x2 e[E];
-#pragma unroll
-              for (int k = 0; k < E; ++k) {
-                xs[k] = v[k] * inv;
-                e[k] = lds_ld2(f2u(fabsf(xs[k]) + (B == 4 ? V.magic4 : V.magic8)) & 0x1FFF8u);
-              }
-              __builtin_amdgcn_sched_barrier(0);  // all searches, then all levels: two trips to LDS, not eight
+            for (int k = 0; k < E; ++k) {
+              xs[k] = v[k] * inv;
+              if constexpr (B != 2) e[k] = lds_ld2(f2u(fabsf(xs[k]) + (B == 4 ? V.magic4 : V.magic8)) & 0x1FFF8u);
+            }
+            if constexpr (B != 2 || kEarly) __builtin_amdgcn_sched_barrier(0);  // all searches, then all levels: two trips to LDS, not eight
+            if constexpr (kEarly) {  // beside the searches
+              look_up_scale();
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (B != 2) {
 #pragma unroll
               for (int k = 0; k < E; ++k) t[k] = lds_ld4(or_and(f2u(fabsf(xs[k]) - u2f(e[k].x)) >> 27, 16u, e[k].y));
             }
             __builtin_amdgcn_sched_barrier(0);
+            auto uniform = [&](int k) { return __builtin_fmaf((float)((gam[k >> 2] >> (8 * (k & 3))) & 0xFFu), V.s_n, u2f(offset.x)); };
+            if constexpr (kEarly) {  // beside the levels
+#pragma unroll
+              for (int k = 0; k < E; ++k) u[k] = uniform(k);
+              widen(x.s[(j + 1) % kAhead], next);
+            }
             // floor(ts) + [us < ts - floor(ts)] is the ceiling of ts - us: that difference is exact, or lies between -1 and 0
             const float ts = fminf(m * u2f(rec.y - ex), 255.0f), rg = fabsf(ceilf(ts - u2f(offset.y)));
             sfg = rg * fabsf(u2f(rec.x + ex));  // (without an exponent to add, the table's pattern has the sign bit)
+            if constexpr (kEarly) __builtin_amdgcn_sched_barrier(0);
             bool up[E];
 #pragma unroll
             for (int k = 0; k < E; ++k) {
               const float ax = fabsf(xs[k]);
+              if constexpr (!kEarly) u[k] = uniform(k);
               if constexpr (B == 2) {
-                up[k] = uniform(k) < ax;
+                up[k] = u[k] < ax;
                 level[k] = u2f(or_and(f2u(xs[k]), V.top, f2u(up[k] ? 1.0f : 0.0f)));
               } else {
-                up[k] = __builtin_fmaf(uniform(k), u2f(t[k].y), u2f(t[k].x)) < ax;
+                up[k] = __builtin_fmaf(u[k], u2f(t[k].y), u2f(t[k].x)) < ax;
                 level[k] = u2f(or_and(f2u(xs[k]), V.top, up[k] ? t[k].z : t[k].x));
               }
+            }
+            // A level's fourth word counts as read here: the compiler would take its register for another purpose while the read is under way, and wait
+            // for the first entry's level before it asks for the others' (ring of 16, 496 super-groups, 10.0 us instead of 9.5; a chain of 100 of 600 in fp32
+            // 43.4 and 39.9).  With eight entries per lane there are no registers for that: halving over 8 of 5,600 in fp32 14.8 instead of 13.1.
+            if constexpr (B != 2 && E == 4) {
+#pragma unroll
+              for (int k = 0; k < E; ++k) asm volatile("" ::"v"(t[k].w));
             }
             if (keep) {
               const TileBase<B> tb = tile_base_here<B>(job, pos);
