@@ -95,6 +95,7 @@ struct Walk {
   uint32_t tile_sgs;         // super-groups of a wave's tile: 4 (dq_walk.hip), 2 or 1 (dq_thin.hip)
   uint32_t n_paths;
   uint32_t blocks, waves;    // grid, waves per block
+  uint32_t most_blocks;      // of such a grid
   uint32_t order;            // which share a wave takes (share_of): 0, kReversed, or the CUs that the shares are spread over
   uint32_t raw_beside;       // spread: CUs with a block more have the last shares in it, raw ones, not the first
 };
@@ -132,6 +133,7 @@ struct Tables {
   uint32_t by_chunk;        // paths of the same chunk number next to each other
   uint32_t entry_bytes;
   uint32_t waves, tile_log;  // shares; log2 of a tile's super-groups
+  uint32_t slots;            // waves of every path, one tile at most for each; 0: shares by cost
   Costs cost;
 };
 constexpr uint32_t kMostTablePaths = 1024;  // a thread each
@@ -143,6 +145,10 @@ dq_status stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dty
 constexpr uint32_t kMostSearched = 65536;
 dq_status search(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width, uint32_t *places,
                  uint32_t *counts, Announce announce, hipStream_t stream);
+// Both in one launch, where they are small.
+bool takes_search_arrange(uint32_t n_sg_per_bucket, uint32_t n_buckets);
+dq_status search_arrange(const float *F, const float *mu, uint32_t n_sg, uint64_t max_code_bits, uint32_t max_width, float *mu_main, uint32_t *origin,
+                         Announce announce, const Tables &tables, hipStream_t stream);
 // Behind it: the means in reordered order (mu and mu_main, or both null), the origins, and the tables.
 dq_status arrange(const float *F, const float *mu, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32_t max_width, const uint32_t *counts,
                   const uint32_t *places, float *mu_main, uint32_t *origin, const Tables &tables, hipStream_t stream);

@@ -926,6 +926,12 @@ bool plan_whole(const dq_ctx *ctx, const dqx_whole *d, WholePlan *p) {
   t.bucket_sgs = J;
   t.by_chunk = by_chunk_number(w, nb, J);
   t.entry_bytes = (uint32_t)elt_size(d->dtype);
+  // A tile per wave at most, found by counting, where the waves that a path's one to three tiles fewer leave without one are few.
+  const uint64_t each = (m + w.tile_sgs - 1) / w.tile_sgs, slots = w.tile_sgs == 1 ? each : each + 3, slot_blocks = (slots * w.n_paths + w.waves - 1) / w.waves;
+  if (slot_blocks <= w.most_blocks && slots <= each + each / 8) {
+    t.slots = (uint32_t)slots;
+    w.blocks = (uint32_t)slot_blocks;
+  }
   t.waves = w.blocks * w.waves;
   t.tile_log = w.tile_sgs / 2;
   t.cost = dq::costs_of(d->dtype, tree, n, w.tile_sgs);
@@ -987,11 +993,16 @@ dq_status dqx_whole_run(const dq_ctx *ctx, const dqx_whole *desc, const void *co
   p.w.grads = grads;
   bool searched = false;
   dq_status st = *ticket ? dq::stats_all(tensors, ctx->cfg.n_workers, desc->dtype, (uint64_t)J * nb, floats(p.mu), floats(p.F), grads, s) : DQ_EINVAL;
-  if (st == DQ_OK) {
+  const bool both = dq::takes_search_arrange(J, nb);
+  if (st == DQ_OK && both) {
+    searched = true;
+    st = dq::search_arrange(floats(p.F), means ? floats(p.mu) : nullptr, J, desc->max_code_bits, desc->max_width, means ? floats(p.mu_main) : nullptr,
+                            words(p.origin), announce, p.t, s);
+  } else if (st == DQ_OK) {
     searched = true;
     st = dq::search(floats(p.F), J, nb, desc->max_code_bits, desc->max_width, words(p.places), words(p.counts), announce, s);
   }
-  if (st == DQ_OK)
+  if (st == DQ_OK && !both)
     st = dq::arrange(floats(p.F), means ? floats(p.mu) : nullptr, J, nb, desc->max_width, words(p.counts), words(p.places),
                      means ? floats(p.mu_main) : nullptr, words(p.origin), p.t, s);
   if (st == DQ_OK)

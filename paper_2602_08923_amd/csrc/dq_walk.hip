@@ -397,6 +397,7 @@ static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, u
   if (W->tile_sgs == kWaveSGs) per_cu = held;
   const uint64_t needed = (tiles + W->waves - 1) / W->waves, blocks = (uint64_t)n_cu * per_cu;
   W->blocks = (uint32_t)(needed < blocks ? needed : blocks);
+  W->most_blocks = (uint32_t)blocks;
   return true;
 }
 

@@ -318,16 +318,24 @@ __device__ __forceinline__ uint32_t last_tied(uint32_t v, float by, float back, 
 constexpr uint32_t kFirstWords = (kBins + 1) * kCopies;
 static_assert((kKept + 1) * kAllocThreads <= kFirstWords, "the norms set aside");
 
+struct SearchSpace {
+  alignas(16) uint32_t room[kFirstWords];
+  alignas(16) uint32_t places[kPlaces + 4], last_places[kLastPlaces];  // places[kPlaces]: beyond the bracket
+  uint32_t wsum[2][kAllocWaves], wfit[kAllocWaves], row_n[kRegs][3], crossing[2][2], exact[2][3][kAllocWaves];
+};
+// The threshold's pattern; S.row_n holds, for every row, how many norms are at or above the three thresholds.
 // ASIDE: buckets of more than 16 rows, whose threads hold up to 64 norms each, so that those inside the brackets may be more than the kKept that have room.
 template <bool ALLOW16, bool ASIDE>
-__global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits, uint32_t *pos_all,
-                                                          uint32_t *counts_all, dq::Announce announce) {
-  __shared__ alignas(16) uint32_t room[kFirstWords];
-  __shared__ alignas(16) uint32_t places[kPlaces + 4], last_places[kLastPlaces];  // places[kPlaces]: beyond the bracket
-  __shared__ uint32_t wsum[2][kAllocWaves], wfit[kAllocWaves], row_n[kRegs][3], crossing[2][2], exact[2][3][kAllocWaves];
+__device__ __forceinline__ uint32_t search_block(const float *F, uint32_t J, uint64_t max_code_bits, SearchSpace &S) {
+  auto &room = S.room;
+  auto &places = S.places;
+  auto &last_places = S.last_places;
+  auto &wsum = S.wsum;
+  auto &wfit = S.wfit;
+  auto &row_n = S.row_n;
+  auto &crossing = S.crossing;
+  auto &exact = S.exact;
   uint32_t *const h8 = room;
-  const float *F = F_all + (uint64_t)blockIdx.x * J;
-  uint32_t *pos = pos_all + (uint64_t)blockIdx.x * J;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   uint32_t(*const kept)[kAllocThreads] = reinterpret_cast<uint32_t(*)[kAllocThreads]>(room);  // per thread its norms inside the brackets
   int32_t fr[kRegs];
@@ -624,31 +632,53 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
     if (ALLOW16) atomicAdd(row + 2, n16);
   }
   __syncthreads();
-  if (wave == 0) {
-    const uint32_t from = lane * kAllocThreads, in_row = J > from ? min(J - from, (uint32_t)kAllocThreads) : 0u;
-    const uint32_t r4 = row_n[lane][0], r8 = row_n[lane][1], r16 = row_n[lane][2];
-    const uint32_t x[4] = {in_row - r4, r4 - r8, r8 - r16, r16};
-    uint32_t n_class[4], first[4], class_first = 0;
+  return hi;
+}
+
+// In lane k: the first place of every class in row k.  In all lanes: the classes' sizes.
+struct RowPlaces {
+  uint32_t first[4], n_class[4];
+};
+__device__ __forceinline__ RowPlaces row_places(uint32_t J, const SearchSpace &S) {
+  const uint32_t lane = threadIdx.x & 63u, from = lane * kAllocThreads, in_row = J > from ? min(J - from, (uint32_t)kAllocThreads) : 0u;
+  const uint32_t r4 = S.row_n[lane][0], r8 = S.row_n[lane][1], r16 = S.row_n[lane][2];
+  const uint32_t x[4] = {in_row - r4, r4 - r8, r8 - r16, r16};
+  RowPlaces p;
+  uint32_t class_first = 0;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const uint32_t upto = wave_scan(x[c]);
-      n_class[c] = __builtin_amdgcn_readlane(upto, 63);
-      first[c] = class_first + upto - x[c];
-      class_first += n_class[c];
-    }
-    if (from + kAllocThreads < J) {  // not the last row
+  for (int c = 0; c < 4; ++c) {
+    const uint32_t upto = wave_scan(x[c]);
+    p.n_class[c] = __builtin_amdgcn_readlane(upto, 63);
+    p.first[c] = class_first + upto - x[c];
+    class_first += p.n_class[c];
+  }
+  return p;
+}
+__device__ __forceinline__ void tell(const uint32_t (&n)[4], const dq::Announce &announce, uint32_t bucket) {
+  if (announce.host)  // one store, so that nothing needs to be ordered; the fourth class is the rest
+    __hip_atomic_store(announce.host + bucket, n[0] | (uint64_t)n[1] << 17 | (uint64_t)n[2] << 34 | (uint64_t)announce.tag << 51, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+template <bool ALLOW16, bool ASIDE>
+__global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits, uint32_t *pos_all,
+                                                          uint32_t *counts_all, dq::Announce announce) {
+  __shared__ SearchSpace S;
+  const uint32_t T = search_block<ALLOW16, ASIDE>(F_all + (uint64_t)blockIdx.x * J, J, max_code_bits, S);
+  if (threadIdx.x >= 64) return;
+  const RowPlaces p = row_places(J, S);
+  const uint32_t from = threadIdx.x * kAllocThreads;
+  uint32_t *pos = pos_all + (uint64_t)blockIdx.x * J;
+  if (from + kAllocThreads < J) {  // not the last row
 #pragma unroll
-      for (int c = 0; c < 4; ++c) gst<uint32_t>(pos + from + c, first[c]);
-    }
-    if (lane == 0) {
-      uint32_t *cnt = counts_all + 5ull * blockIdx.x;
+    for (int c = 0; c < 4; ++c) gst<uint32_t>(pos + from + c, p.first[c]);
+  }
+  if (threadIdx.x == 0) {
+    uint32_t *cnt = counts_all + 5ull * blockIdx.x;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) gst<uint32_t>(cnt + c, n_class[c]);
-      gst<uint32_t>(cnt + 4, hi);
-      if (announce.host)  // one store, so that nothing needs to be ordered; the fourth class is the rest
-        __hip_atomic_store(announce.host + blockIdx.x, n_class[0] | (uint64_t)n_class[1] << 17 | (uint64_t)n_class[2] << 34 | (uint64_t)announce.tag << 51,
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    for (int c = 0; c < 4; ++c) gst<uint32_t>(cnt + c, p.n_class[c]);
+    gst<uint32_t>(cnt + 4, T);
+    tell(p.n_class, announce, blockIdx.x);
   }
 }
 
@@ -745,41 +775,55 @@ struct TableSpace {
   uint32_t total[4], cost[4];
   double wave_sum[kAllocWaves];
 };
-__device__ __forceinline__ void make_tables(const dq::Tables &T, const uint32_t *counts_all, uint32_t part, TableSpace &L) {
+// Path p's super-groups by width; count(b, w): of bucket b.
+template <typename C>
+__device__ __forceinline__ dq::WalkPath path_of(const dq::Tables &T, uint32_t p, C count) {
+  const uint32_t b = T.by_chunk ? p % T.n_buckets : p / T.n_chunks, c = T.by_chunk ? p / T.n_buckets : p % T.n_chunks;
+  const uint32_t lo = c * T.chunk_sgs, hi = lo + T.chunk_sgs;
+  const uint64_t sg = (uint64_t)b * T.bucket_sgs + lo;
+  dq::WalkPath x = {};
+  x.job.local = reinterpret_cast<const void *>((uintptr_t)((uint64_t)b * T.bucket_sgs * kSG * T.entry_bytes));
+  x.job.mu = T.mu ? T.mu + sg : nullptr;
+  x.job.src = T.origin + sg;
+  x.job.out = T.out + (uint64_t)b * T.bucket_sgs * kSG;
+  x.job.dest = T.origin + sg;
+  x.job.back = x.job.mu;
+  x.job.first_sg = sg;
+  x.chunk = c;
+  uint32_t edge = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const uint32_t end = edge + count(b, w), from = max(lo, edge), to = min(hi, end);
+    x.job.n_sg[w] = to > from ? to - from : 0u;
+    edge = end;
+  }
+  return x;
+}
+template <typename C>
+__device__ __forceinline__ void make_tables(const dq::Tables &T, C count, uint32_t part, TableSpace &L) {
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t n_paths = T.n_chunks * T.n_buckets;
+  if (T.slots) {  // every path has so many waves, a tile or none for each: nothing to be weighed, no barrier
+    const uint32_t v = part * kAllocThreads + tid, p = v / T.slots, t = v - p * T.slots;
+    const dq::WalkPath x = path_of(T, min(p, n_paths - 1), count);
+    uint32_t tiles = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) tiles += (x.job.n_sg[w] + (1u << T.tile_log) - 1u) >> T.tile_log;
+    if (p < n_paths && t == 0) T.paths[p] = x;
+    if (v <= T.waves) T.shares[v] = p >= n_paths ? dq::WalkShare{n_paths, 0} : t < tiles ? dq::WalkShare{p, t} : dq::WalkShare{p + 1, 0};
+    return;
+  }
   if (tid < 4) L.total[tid] = 0;
   __syncthreads();
   uint32_t t[4] = {0, 0, 0, 0};
   if (wave * 64 < n_paths) {
-    const uint32_t p = min(tid, n_paths - 1);
-    const uint32_t b = T.by_chunk ? p % T.n_buckets : p / T.n_chunks, c = T.by_chunk ? p / T.n_buckets : p % T.n_chunks;
-    const uint32_t *cnt = counts_all + 5ull * b;
-    const uint32_t lo = c * T.chunk_sgs, hi = lo + T.chunk_sgs;
-    uint32_t n_sg[4], edge = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const uint32_t end = edge + gld<uint32_t>(cnt + w), from = max(lo, edge), to = min(hi, end);
-      n_sg[w] = to > from ? to - from : 0u;
-      edge = end;
-    }
+    const dq::WalkPath x = path_of(T, min(tid, n_paths - 1), count);
     if (tid < n_paths) {
-      const uint64_t sg = (uint64_t)b * T.bucket_sgs + lo;
-      dq::WalkPath x = {};
-      x.job.local = reinterpret_cast<const void *>((uintptr_t)((uint64_t)b * T.bucket_sgs * kSG * T.entry_bytes));
-      x.job.mu = T.mu ? T.mu + sg : nullptr;
-      x.job.src = T.origin + sg;
-      x.job.out = T.out + (uint64_t)b * T.bucket_sgs * kSG;
-      x.job.dest = T.origin + sg;
-      x.job.back = x.job.mu;
-      x.job.first_sg = sg;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        x.job.n_sg[w] = n_sg[w];
-        t[w] = (n_sg[w] + (1u << T.tile_log) - 1u) >> T.tile_log;
+        t[w] = (x.job.n_sg[w] + (1u << T.tile_log) - 1u) >> T.tile_log;
         L.tiles[tid][w] = t[w];
       }
-      x.chunk = c;
       if (part == 0) T.paths[tid] = x;
     }
 #pragma unroll
@@ -863,7 +907,7 @@ __global__ void __launch_bounds__(kAllocThreads) k_arrange(const float *F_all, c
   __shared__ TableSpace space;
   const uint32_t parts = table_parts(T);
   if (blockIdx.x < parts) {
-    if (blockIdx.y == 0) make_tables(T, counts_all, blockIdx.x, space);
+    if (blockIdx.y == 0) make_tables(T, [&](uint32_t b, int w) { return gld<uint32_t>(counts_all + 5ull * b + w); }, blockIdx.x, space);
     return;
   }
   const uint32_t row = blockIdx.x - parts;
@@ -875,6 +919,47 @@ __global__ void __launch_bounds__(kAllocThreads) k_arrange(const float *F_all, c
     if (mu_all) gst<float>(mu_main + first + x.at, x.k == 3 ? 0.0f : m);
     gst<uint32_t>(origin + first + x.at, j);
   }
+}
+
+// The search and k_arrange in one launch, for one bucket of up to 16 rows: every block searches for itself, which costs nothing but a CU that has
+// nothing else to do, and goes on with what it has in LDS.  Against two launches, a launch's start and the trips of places and counts to memory and back
+// are fewer: 8 workers' 8,192 super-groups 8.2 and 5.2 us -> 9.6, 6 workers' 48 6.9 and 5.1 -> 7.8 (all-reduces 36.1 -> 31.9, 23.2 -> 21.9; 16 workers' halving
+// of 1,312 31.5 -> 27.9, 3 workers' 15,000 30.6 -> 27.4).  What bounds it is the search's chain, whose every piece of code is fetched and run once.
+template <bool ALLOW16>
+__global__ void __launch_bounds__(kAllocThreads) k_search_arrange(const float *F, const float *mu, uint32_t J, uint64_t max_code_bits, float *mu_main,
+                                                                  uint32_t *origin, dq::Announce announce, dq::Tables T) {
+  __shared__ SearchSpace S;
+  __shared__ uint32_t mine_w[kAllocWaves][4];
+  __shared__ TableSpace space;
+  const uint32_t parts = table_parts(T), tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool tables = blockIdx.x < parts;
+  const uint32_t row = tables ? 0u : blockIdx.x - parts, j = row * kAllocThreads + tid;
+  const float f = gld<float>(F + min(j, J - 1)), m = mu ? gld<float>(mu + min(j, J - 1)) : 0.0f;
+  const uint32_t pattern = search_block<ALLOW16, false>(F, J, max_code_bits, S);
+  const RowPlaces p = row_places(J, S);
+  uint32_t first[4];  // of the block's row; by all lanes, as lane `row` says it
+#pragma unroll
+  for (int c = 0; c < 4; ++c) first[c] = (uint32_t)__builtin_amdgcn_readlane((int)p.first[c], (int)row);
+  if (tables) {
+    if (blockIdx.x == 0 && tid == 0) tell(p.n_class, announce, 0);
+    make_tables(T, [&](uint32_t, int w) { return p.n_class[w]; }, blockIdx.x, space);
+    return;
+  }
+  const int32_t p8 = (int32_t)pattern, p4 = p4_from(pattern), p16 = p16_from(pattern, ALLOW16);
+  const uint32_t k = j < J ? class_of(pattern_of(f), p4, p8, p16) : 4u;
+  const uint64_t b[4] = {__ballot(k == 0), __ballot(k == 1), __ballot(k == 2), __ballot(k == 3)};
+  if (lane == 0) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) mine_w[wave][c] = (uint32_t)__builtin_popcountll(b[c]);
+  }
+  uint32_t at = k == 0 ? first[0] : k == 1 ? first[1] : k == 2 ? first[2] : first[3];
+  __syncthreads();
+  if (k == 4) return;
+  for (uint32_t w = 0; w < wave; ++w) at += mine_w[w][k];
+  const uint64_t mine = k == 0 ? b[0] : (k == 1 ? b[1] : (k == 2 ? b[2] : b[3]));
+  at += __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
+  if (mu) gst<float>(mu_main + at, k == 3 ? 0.0f : m);
+  gst<uint32_t>(origin + at, j);
 }
 
 // Buckets of more than 65,536 super-groups: the norms are read again in every round of a bisection, widths and positions
@@ -1147,6 +1232,15 @@ dq_status search(const float *F, uint32_t J, uint32_t n_buckets, uint64_t max_co
   const bool allow16 = max_width == 16, aside = J > 16u * kAllocThreads;
   const auto kernel = aside ? (allow16 ? k_search<true, true> : k_search<false, true>) : (allow16 ? k_search<true, false> : k_search<false, false>);
   hipLaunchKernelGGL(kernel, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, places, counts, announce);
+  return launched();
+}
+
+bool takes_search_arrange(uint32_t J, uint32_t n_buckets) { return n_buckets == 1 && J <= 16u * kAllocThreads; }
+dq_status search_arrange(const float *F, const float *mu, uint32_t J, uint64_t max_code_bits, uint32_t max_width, float *mu_main, uint32_t *origin,
+                         Announce announce, const Tables &tables, hipStream_t s) {
+  const auto kernel = max_width == 16 ? k_search_arrange<true> : k_search_arrange<false>;
+  hipLaunchKernelGGL(kernel, dim3((J + kAllocThreads - 1) / kAllocThreads + table_parts(tables)), dim3(kAllocThreads), 0, s, F, mu, J, max_code_bits, mu_main,
+                     origin, announce, tables);
   return launched();
 }
 
