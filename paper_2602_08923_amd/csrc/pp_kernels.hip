@@ -268,8 +268,8 @@ __global__ void __launch_bounds__(kAllocThreads) k_alloc_positions(const float *
 // factor of two 28.7 instead of 27.2, of equal ones 62 instead of 109).
 constexpr uint32_t kCopies = 8;
 constexpr uint32_t kKept = 15;  // of a thread's up to 64 norms; up to 16 always fit
-constexpr uint32_t kPlaces = 4096, kLastPlaces = 1024;  // bins of the second and third level
-static_assert(kPlaces == 4 * kAllocThreads && kLastPlaces == kAllocThreads, "four and one per thread");
+constexpr uint32_t kPlaces = 4096, kLastPlaces = 2048;  // bins of the second and third level
+static_assert(kPlaces == 4 * kAllocThreads && kLastPlaces == 2 * kAllocThreads, "four and two per thread");
 
 // Inclusive sum over the lanes of a row of 16, and over the wave
 __device__ __forceinline__ uint32_t row_scan(uint32_t x) {
@@ -323,17 +323,181 @@ struct SearchSpace {
   alignas(16) uint32_t places[kPlaces + 4], last_places[kLastPlaces];  // places[kPlaces]: beyond the bracket
   uint32_t wsum[2][kAllocWaves], wfit[kAllocWaves], row_n[kRegs][3], crossing[2][2], exact[2][3][kAllocWaves];
 };
+// h[b] for b < BINS becomes the sum of h[b], h[b + 1], ..., the thread's own bins in x between the two halves, which a
+// barrier separates
+template <typename X>
+__device__ __forceinline__ void sums_begin(X &x, uint32_t *wsum) {
+  uint32_t sum = 0;
+  for (uint32_t one : x.n) sum += one;
+  const uint32_t upto = wave_scan(sum);
+  x.before = upto - sum;  // in the wave, before the thread's own bins
+  if ((threadIdx.x & 63u) == 63) wsum[threadIdx.x >> 6] = upto;
+}
+template <typename X>
+__device__ __forceinline__ void sums_end(const X &x, const uint32_t *wsum, uint32_t *h) {
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t upto = row_scan(wsum[threadIdx.x & 15u]), all = __builtin_amdgcn_readlane(upto, 15);
+  uint32_t left = all - (wave ? __builtin_amdgcn_readlane(upto, wave - 1) : 0u) - x.before;
+  uint32_t *own = h + threadIdx.x * (sizeof(x.n) / 4);
+  for (uint32_t one : x.n) {
+    *own++ = left;
+    left -= one;
+  }
+}
+// The last of the bin boundaries 0 .. n-1 that surely does not fit and the last that may not (boundary 0 is the
+// bracket's lower end): every PER-th first, then, by every wave for itself, those between.  fails(bin, over, may) says it of one.
+template <uint32_t PER, typename F>
+__device__ __forceinline__ void last_failing(uint32_t n, F cost_fails, uint32_t *wfit, uint32_t &surely, uint32_t &perhaps) {
+  const uint32_t lane = threadIdx.x & 63u;
+  auto fails = [&](uint32_t bin, bool &over, bool &may) {
+    over = may = true;
+    if (bin) cost_fails(min(bin, n - 1), over, may);
+    over = over && bin < n;
+    may = may && bin < n;
+  };
+  bool over, may;
+  fails(threadIdx.x * PER, over, may);
+  const uint32_t both = (uint32_t)__builtin_popcountll(__ballot(over)) + ((uint32_t)__builtin_popcountll(__ballot(may)) << 16);
+  if (lane == 0) wfit[threadIdx.x >> 6] = both;
+  __syncthreads();
+  const uint32_t all = __builtin_amdgcn_readlane(row_scan(wfit[lane & 15u]), 15);
+  surely = ((all & 0xFFFFu) - 1) * PER;
+  perhaps = ((all >> 16) - 1) * PER;
+  const bool between = (lane & 31u) < PER - 1;
+  fails((lane < 32 ? surely : perhaps) + 1 + (lane & 31u), over, may);
+  surely += (uint32_t)__builtin_popcountll(__ballot(between && lane < 32 && over));
+  perhaps += (uint32_t)__builtin_popcountll(__ballot(between && lane >= 32 && may));
+}
+
+// What is left of a search: T lies above lo, which does not fit (or is 0), and at most at hi, which does; lo4 .. hi16: around their tied ones.
+struct Bracket {
+  uint32_t lo, hi, lo4, hi4, lo16, hi16;
+  uint32_t base;    // cost at hi, but for tied norms that the first level puts beyond it
+  uint32_t n_kept;  // norms inside that the thread has set aside
+};
+// An event: a norm costs `weight` more up to a threshold; of what kind, and how far above the bracket's lower end that is.
+constexpr uint32_t kMostAbove = 1u << 30;
+__device__ __forceinline__ uint32_t event_of(uint32_t kind, uint32_t upto) { return kind << 30 | upto; }  // 0, 1, 2: T_{4,8}, T_{2,4}, T_{8,16}
+__device__ __forceinline__ uint32_t kind_of(uint32_t event) { return event >> 30; }
+__device__ __forceinline__ uint32_t upto_of(uint32_t event) { return event & (kMostAbove - 1u); }
+__device__ __forceinline__ uint32_t weight_of(uint32_t event) { return 0x824u >> (4 * (event >> 30)) & 15u; }
+__device__ __forceinline__ uint32_t tied4_of(uint32_t pattern) { return f2u(u2f(pattern) * (17.0f / 512.0f)); }
+__device__ __forceinline__ uint32_t tied16_of(uint32_t pattern) { return f2u(u2f(pattern) * (131072.0f / 257.0f)); }
+
+// Down to a width of one pattern: hi is T.  The norms set aside lie in S.room, thread by thread; each_event(body) has what others cost and up to where
+// (event_of).
+struct NoEvents {};
+template <bool ALLOW16, typename Events>
+__device__ __forceinline__ void to_one_pattern(Bracket &bracket, uint32_t budget, SearchSpace &S, Events each_event) {
+  auto &places = S.places;
+  auto &last_places = S.last_places;
+  auto &wsum = S.wsum;
+  auto &crossing = S.crossing;
+  using std::integral_constant;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_kept = bracket.n_kept;
+  uint32_t(*const kept)[kAllocThreads] = reinterpret_cast<uint32_t(*)[kAllocThreads]>(S.room);
+  uint32_t lo = bracket.lo, hi = bracket.hi, lo4 = bracket.lo4, hi4 = bracket.hi4, lo16 = bracket.lo16, hi16 = bracket.hi16, base = bracket.base;
+  [[maybe_unused]] const uint32_t start = lo;
+  // One level: of the boundaries lo + (b << s) the last that does not fit (the first, if none: lo) and the one behind it are the new bracket.
+  auto level = [&](uint32_t *h, auto per_thread, uint32_t s, uint32_t turn) {
+    constexpr uint32_t kOwn = decltype(per_thread)::value;
+    const uint32_t width = hi - lo, width4 = hi4 - lo4, width16 = hi16 - lo16;
+    // a norm of a tied bracket: beyond the bracket, or in the bin of the last pattern whose tied one is at most v, which v divided by the
+    // ratio misses by two patterns at most
+    auto fall = [&](uint32_t v, float by, float back, uint32_t from, uint32_t end, uint32_t weight) {
+      if (v >= end) {
+        atomicAdd(&places[kPlaces], weight);
+      } else if (v >= from) {
+        uint32_t b;
+        if (kOwn > 2 && s >= 2 && v >= 0x06000000u) {  // nothing denormal: a bin before or behind, at most
+          auto at_most = [&](uint32_t T) { return f2u(u2f(T) * by) <= v; };
+          b = (min(max(f2u(u2f(v) * back), lo), hi - 1) - lo) >> s;
+          const uint32_t T = lo + (b << s);
+          b = at_most(T + (1u << s)) ? b + 1 : at_most(T) ? b : b - 1;
+        } else {
+          b = (last_tied(v, by, back, lo, hi) - lo) >> s;
+        }
+        atomicAdd(&h[b], weight);
+      }
+    };
+    const uint32_t from4 = tied4_of(lo), end4 = tied4_of(hi), from16 = ALLOW16 ? tied16_of(lo) : 0u, end16 = ALLOW16 ? tied16_of(hi) : 0u;
+    auto count = [&](uint32_t v) {
+      if (v - lo < width) atomicAdd(&h[(v - lo) >> s], 4u);
+      if (v - lo4 < width4) fall(v, 17.0f / 512.0f, 512.0f / 17.0f, from4, end4, 2u);
+      if (ALLOW16 && v - lo16 < width16) fall(v, 131072.0f / 257.0f, 257.0f / 131072.0f, from16, end16, 8u);
+    };
+    for (uint32_t i = 0; i < n_kept; ++i) count(kept[i][tid]);
+    if constexpr (!__is_same(Events, NoEvents))
+      each_event([&](uint32_t event) {
+        const uint32_t at = start + upto_of(event) - lo;
+        if (at < width) atomicAdd(&h[at >> s], weight_of(event));
+      });
+    __syncthreads();
+    uint32_t own[kOwn], sum = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kOwn; ++i) {
+      own[i] = h[tid * kOwn + i];
+      sum += own[i];
+    }
+    const uint32_t beyond = kOwn > 2 ? places[kPlaces] : 0u;
+    const uint32_t upto = wave_scan(sum);
+    if (lane == 63) wsum[turn][wave] = upto;
+    __syncthreads();
+    const uint32_t waves_upto = row_scan(wsum[turn][lane & 15u]), all = __builtin_amdgcn_readlane(waves_upto, 15);
+    uint32_t behind = base + beyond + all - (wave ? __builtin_amdgcn_readlane(waves_upto, wave - 1) : 0u) - upto;  // cost behind the thread's bins
+    if (behind <= budget && (behind + sum > budget || tid == 0)) {
+      uint32_t b = kOwn - 1;  // of the thread's bins
+#pragma unroll
+      for (uint32_t i = kOwn - 1; i > 0; --i)
+        if (b == i && behind + own[i] <= budget) {
+          behind += own[i];
+          b = i - 1;
+        }
+      crossing[turn][0] = tid * kOwn + b;
+      crossing[turn][1] = behind;
+    }
+    __syncthreads();
+    const bool none = base + beyond > budget;  // infinite norms: not even +inf fits
+    const uint32_t bin = none ? (width - 1) >> s : crossing[turn][0];
+    base = none ? base + beyond : crossing[turn][1];
+    lo += bin << s;
+    hi = min(hi, lo + (1u << s));
+    lo4 = tied4_of(lo);
+    hi4 = tied4_of(hi);
+    if (ALLOW16) {
+      lo16 = tied16_of(lo);
+      hi16 = tied16_of(hi);
+    }
+  };
+  if (hi - lo > 1) level(places, integral_constant<uint32_t, 4>{}, shift_to(hi - lo - 1, kPlaces), 0);
+  while (hi - lo > kLastPlaces) {  // a first bracket of more than four bins
+    places[4 * tid] = places[4 * tid + 1] = places[4 * tid + 2] = places[4 * tid + 3] = 0;
+    if (tid == 0) places[kPlaces] = 0;
+    __syncthreads();
+    level(places, integral_constant<uint32_t, 4>{}, shift_to(hi - lo - 1, kPlaces), 0);
+    __syncthreads();
+  }
+  if (hi - lo > 1) level(last_places, integral_constant<uint32_t, 2>{}, 0, 1);
+  bracket.hi = hi;
+}
+
 // The threshold's pattern; S.row_n holds, for every row, how many norms are at or above the three thresholds.
 // ASIDE: buckets of more than 16 rows, whose threads hold up to 64 norms each, so that those inside the brackets may be more than the kKept that have room.
-template <bool ALLOW16, bool ASIDE>
-__device__ __forceinline__ uint32_t search_block(const float *F, uint32_t J, uint64_t max_code_bits, SearchSpace &S) {
+// given: a bracket to go on from instead of the first level's (for 2, 4 and 8 bits), with the norms at or above its ends and the costs there.
+struct NoBracket {};
+struct Given {
+  uint32_t lo, hi, at_lo, at_hi, cost_lo, base;
+};
+template <bool ALLOW16, bool ASIDE, typename G = NoBracket>
+__device__ __forceinline__ uint32_t search_block(const float *F, uint32_t J, uint64_t max_code_bits, SearchSpace &S, const G &given = G()) {
+  constexpr bool kGiven = !__is_same(G, NoBracket);
+  static_assert(!kGiven || !ALLOW16, "");
   auto &room = S.room;
   auto &places = S.places;
   auto &last_places = S.last_places;
   auto &wsum = S.wsum;
   auto &wfit = S.wfit;
   auto &row_n = S.row_n;
-  auto &crossing = S.crossing;
   auto &exact = S.exact;
   uint32_t *const h8 = room;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -364,7 +528,7 @@ __device__ __forceinline__ uint32_t search_block(const float *F, uint32_t J, uin
   });
   for (uint32_t b = tid; b < kFirstWords / 4; b += kAllocThreads) reinterpret_cast<uint4 *>(room)[b] = make_uint4(0, 0, 0, 0);
   reinterpret_cast<uint4 *>(places)[tid] = make_uint4(0, 0, 0, 0);
-  last_places[tid] = 0;
+  last_places[tid] = last_places[tid + kAllocThreads] = 0;
   if (tid == 0) places[kPlaces] = 0;
   if (tid < kRegs * 3) (&row_n[0][0])[tid] = 0;
   each_group([&](int g) {
@@ -376,90 +540,75 @@ __device__ __forceinline__ uint32_t search_block(const float *F, uint32_t J, uin
       fr[4 * g + q] = J >= 4 ? ((uint32_t)q >= skip ? v : -1) : (e + q < J ? v : -1);
     }
   });
-  auto p16_of = [&](uint32_t pattern) { return f2u(u2f(pattern) * (131072.0f / 257.0f)); };
-  auto p4_of = [](uint32_t pattern) { return f2u(u2f(pattern) * (17.0f / 512.0f)); };
-  // h[b] for b < BINS becomes the sum of h[b], h[b + 1], ..., the thread's own bins in x between the two halves, which a
-  // barrier separates
-  auto sums_begin = [&](int which, auto &x) {
-    uint32_t sum = 0;
-    for (uint32_t one : x.n) sum += one;
-    const uint32_t upto = wave_scan(sum);
-    x.before = upto - sum;  // in the wave, before the thread's own bins
-    if (lane == 63) wsum[which][wave] = upto;
-  };
-  auto sums_end = [&](int which, auto &x, uint32_t *h) {
-    const uint32_t upto = row_scan(wsum[which][lane & 15u]), all = __builtin_amdgcn_readlane(upto, 15);
-    uint32_t left = all - (wave ? __builtin_amdgcn_readlane(upto, wave - 1) : 0u) - x.before;
-    uint32_t *own = h + tid * (sizeof(x.n) / 4);
-    for (uint32_t one : x.n) {
-      *own++ = left;
-      left -= one;
-    }
-  };
-  // The last of the bin boundaries 0 .. n-1 that surely does not fit and the last that may not (boundary 0 is the
-  // bracket's lower end): every PER-th first, then, by every wave for itself, those between.
-  auto bracket = [&](uint32_t n, auto bins, auto cost_bounds, uint32_t &surely, uint32_t &perhaps) {
-    constexpr uint32_t per = decltype(bins)::value / kAllocThreads;
-    auto fails = [&](uint32_t bin, bool &over, bool &may) {
-      uint64_t c_min = ~0ull, c_max = ~0ull;
-      if (bin) cost_bounds(min(bin, n - 1), c_min, c_max);
-      over = bin < n && c_min > max_code_bits;
-      may = bin < n && c_max > max_code_bits;
-    };
-    bool over, may;
-    fails(tid * per, over, may);
-    const uint32_t both = (uint32_t)__builtin_popcountll(__ballot(over)) + ((uint32_t)__builtin_popcountll(__ballot(may)) << 16);
-    if (lane == 0) wfit[wave] = both;
-    __syncthreads();
-    const uint32_t all = __builtin_amdgcn_readlane(row_scan(wfit[lane & 15u]), 15);
-    surely = ((all & 0xFFFFu) - 1) * per;
-    perhaps = ((all >> 16) - 1) * per;
-    const bool between = (lane & 31u) < per - 1;
-    fails((lane < 32 ? surely : perhaps) + 1 + (lane & 31u), over, may);
-    surely += (uint32_t)__builtin_popcountll(__ballot(between && lane < 32 && over));
-    perhaps += (uint32_t)__builtin_popcountll(__ballot(between && lane >= 32 && may));
-  };
   using std::integral_constant;
 
   // level 1: bins of 2^20 patterns, 2040 << 20 is +infinity.  The norms of a bucket share a few dozen bins: kCopies
   // counters of each, in banks next to each other, keep the lanes of a wave from queueing for one word.  The bin before
   // the first takes the threads beyond the bucket's end.
-  __syncthreads();
-  uint32_t *mine = room + kCopies + (lane & (kCopies - 1));
-  each_norm([&](int k) { atomicAdd(mine + (fr[k] >> 20) * (int)kCopies, 1u); });
-  __syncthreads();
-  OwnBins<kBins> first;
-  for (uint32_t i = 0; i < kBins / kAllocThreads; ++i) {
-    first.n[i] = 0;
+  uint32_t lo, hi, lo4, hi4, lo16 = 0, hi16 = 0;
+  uint32_t base;            // cost at hi, but for the tied norms between its tied thresholds and the bins' ends
+  uint32_t at_lo, at_hi;    // norms at or above the brackets' ends, in all
+  uint32_t cost_lo;         // at most
+  if constexpr (kGiven) {
+    lo = given.lo;
+    hi = given.hi;
+    lo4 = tied4_of(lo);
+    hi4 = tied4_of(hi);
+    base = given.base;
+    at_lo = given.at_lo;
+    at_hi = given.at_hi;
+    cost_lo = given.cost_lo;
+    __syncthreads();
+  } else {
+    __syncthreads();
+    uint32_t *mine = room + kCopies + (lane & (kCopies - 1));
+    each_norm([&](int k) { atomicAdd(mine + (fr[k] >> 20) * (int)kCopies, 1u); });
+    __syncthreads();
+    OwnBins<kBins> first;
+    for (uint32_t i = 0; i < kBins / kAllocThreads; ++i) {
+      first.n[i] = 0;
 #pragma unroll
-    for (uint32_t c = 0; c < kCopies; ++c) first.n[i] += room[(kBins / kAllocThreads * tid + i + 1) * kCopies + c];
-  }
-  sums_begin(0, first);
-  __syncthreads();
-  sums_end(0, first, h8);
-  if (tid < 2) h8[kBins + tid] = 0;
-  __syncthreads();
-  uint32_t surely, perhaps;
-  bracket(kBins - 8, integral_constant<int, kBins>{}, [&](uint32_t b, uint64_t &c_min, uint64_t &c_max) {
-    const uint32_t b4 = p4_of(b << 20) >> 20;
-    c_min = 2ull * J + 4ull * h8[b] + 2ull * h8[b4 + 1];
-    c_max = 2ull * J + 4ull * h8[b] + 2ull * h8[b4];
-    if (ALLOW16) {
-      const uint32_t b16 = p16_of(b << 20) >> 20;
-      c_min += 8ull * h8[b16 + 1];
-      c_max += 8ull * h8[b16];
+      for (uint32_t c = 0; c < kCopies; ++c) first.n[i] += room[(kBins / kAllocThreads * tid + i + 1) * kCopies + c];
     }
-  }, surely, perhaps);
-  uint32_t lo = surely << 20, hi = (perhaps + 1) << 20;
-  uint32_t lo4 = p4_of(lo) >> 20 << 20, hi4 = ((p4_of(hi) >> 20) + 1) << 20, lo16 = 0, hi16 = 0;
-  uint32_t base8 = h8[hi >> 20], base4 = h8[hi4 >> 20], base16 = 0;  // norms at or above the brackets
-  if (ALLOW16) {
-    lo16 = p16_of(lo) >> 20 << 20;
-    hi16 = ((p16_of(hi) >> 20) + 1) << 20;
-    base16 = h8[hi16 >> 20];
-  }
+    sums_begin(first, wsum[0]);
+    __syncthreads();
+    sums_end(first, wsum[0], h8);
+    if (tid < 2) h8[kBins + tid] = 0;
+    __syncthreads();
+    uint32_t surely, perhaps;
+    last_failing<kBins / kAllocThreads>(kBins - 8, [&](uint32_t b, bool &over, bool &may) {
+      const uint32_t b4 = tied4_of(b << 20) >> 20;
+      uint64_t c_min = 2ull * J + 4ull * h8[b] + 2ull * h8[b4 + 1], c_max = 2ull * J + 4ull * h8[b] + 2ull * h8[b4];
+      if (ALLOW16) {
+        const uint32_t b16 = tied16_of(b << 20) >> 20;
+        c_min += 8ull * h8[b16 + 1];
+        c_max += 8ull * h8[b16];
+      }
+      over = c_min > max_code_bits;
+      may = c_max > max_code_bits;
+    }, wfit, surely, perhaps);
+    lo = surely << 20;
+    hi = (perhaps + 1) << 20;
+    lo4 = tied4_of(lo) >> 20 << 20;
+    hi4 = ((tied4_of(hi) >> 20) + 1) << 20;
+    uint32_t base8 = h8[hi >> 20], base4 = h8[hi4 >> 20], base16 = 0;  // norms at or above the brackets
+    if (ALLOW16) {
+      lo16 = tied16_of(lo) >> 20 << 20;
+      hi16 = ((tied16_of(hi) >> 20) + 1) << 20;
+      base16 = h8[hi16 >> 20];
+    }
 
-  uint32_t base = 2 * J + 4 * base8 + 2 * base4 + 8 * base16;  // cost at hi, but for the tied norms between its tied thresholds and the bins' ends
+    base = 2 * J + 4 * base8 + 2 * base4 + 8 * base16;  // cost at hi, but for the tied norms between its tied thresholds and the bins' ends
+    at_lo = h8[lo >> 20] + h8[lo4 >> 20];
+    at_hi = base8 + base4;
+    cost_lo = 2 * J + 4 * h8[lo >> 20] + 2 * h8[lo4 >> 20];
+    if (ALLOW16) {
+      at_lo += h8[lo16 >> 20];
+      cost_lo += 8 * h8[lo16 >> 20];
+      at_hi += base16;
+    }
+    __syncthreads();  // everybody has read the counts
+  }
   // Looking at every norm takes a level some 4 us for 51,200, though few of them lie in the brackets: the threads set theirs aside first and the levels
   // look at those.  Where more than a tenth are inside (norms within a factor of two of each other, masses of equal ones), or one thread has more of its
   // up to 64 inside than fit, the bracket is halved by exact counts: until a tenth is left, or to its end.  Up to 16 norms per thread always fit, and the levels take up
@@ -467,14 +616,6 @@ __device__ __forceinline__ uint32_t search_block(const float *F, uint32_t J, uin
   // ones 11.4 and 20.3, of 8,192 24.9 and 24.1, of 16,384 (the other way here) 41 and 30.  More: three per thread are as good as a tenth or better.
   uint32_t n_kept = 0;
   const uint32_t budget = (uint32_t)min(max_code_bits, (uint64_t)0xFFFFFFFFu);
-  uint32_t at_lo = h8[lo >> 20] + h8[lo4 >> 20], at_hi = base8 + base4;  // norms at or above the brackets' ends, in all
-  uint32_t cost_lo = 2 * J + 4 * h8[lo >> 20] + 2 * h8[lo4 >> 20];       // at most
-  if (ALLOW16) {
-    at_lo += h8[lo16 >> 20];
-    cost_lo += 8 * h8[lo16 >> 20];
-    at_hi += base16;
-  }
-  __syncthreads();  // everybody has read the counts
   bool fits = true, last_fit = false;
   for (uint32_t probe = 0; hi - lo > 1; ++probe) {
     const uint32_t turn = probe & 1u;
@@ -500,7 +641,7 @@ __device__ __forceinline__ uint32_t search_block(const float *F, uint32_t J, uin
       const int32_t even = (int32_t)((float)width * ((float)(cost_lo - budget) / (float)(cost_lo - base))), off = (int32_t)(width >> (probe == 1 ? 5 : 4));
       mid = lo + (uint32_t)min(max(probe == 0 ? even : last_fit ? even - off : even + off, 1), (int32_t)width - 1);
     }
-    const uint32_t p4 = p4_of(mid), p16 = ALLOW16 ? p16_of(mid) : 0u;
+    const uint32_t p4 = tied4_of(mid), p16 = ALLOW16 ? tied16_of(mid) : 0u;
     uint32_t n8 = 0, n4 = 0, n16 = 0;
     each_norm([&](int k) {  // per lane: ballots, whose bits the scalar unit counts, take twice as long
       n8 += fr[k] >= (int32_t)mid ? 1u : 0u;
@@ -535,81 +676,9 @@ __device__ __forceinline__ uint32_t search_block(const float *F, uint32_t J, uin
       cost_lo = cost;
     }
   }
-  // One level: of the boundaries lo + (b << s) the last that does not fit (the first, if none: lo) and the one behind it are the new bracket.
-  auto level = [&](uint32_t *h, auto per_thread, uint32_t s, uint32_t turn) {
-    constexpr uint32_t kOwn = decltype(per_thread)::value;
-    const uint32_t width = hi - lo, width4 = hi4 - lo4, width16 = hi16 - lo16;
-    // a norm of a tied bracket: beyond the bracket, or in the bin of the last pattern whose tied one is at most v, which v divided by the
-    // ratio misses by two patterns at most
-    auto fall = [&](uint32_t v, float by, float back, uint32_t from, uint32_t end, uint32_t weight) {
-      if (v >= end) {
-        atomicAdd(&places[kPlaces], weight);
-      } else if (v >= from) {
-        uint32_t b;
-        if (kOwn > 1 && s >= 2 && v >= 0x06000000u) {  // nothing denormal: a bin before or behind, at most
-          auto at_most = [&](uint32_t T) { return f2u(u2f(T) * by) <= v; };
-          b = (min(max(f2u(u2f(v) * back), lo), hi - 1) - lo) >> s;
-          const uint32_t T = lo + (b << s);
-          b = at_most(T + (1u << s)) ? b + 1 : at_most(T) ? b : b - 1;
-        } else {
-          b = (last_tied(v, by, back, lo, hi) - lo) >> s;
-        }
-        atomicAdd(&h[b], weight);
-      }
-    };
-    const uint32_t from4 = p4_of(lo), end4 = p4_of(hi), from16 = ALLOW16 ? p16_of(lo) : 0u, end16 = ALLOW16 ? p16_of(hi) : 0u;
-    auto count = [&](uint32_t v) {
-      if (v - lo < width) atomicAdd(&h[(v - lo) >> s], 4u);
-      if (v - lo4 < width4) fall(v, 17.0f / 512.0f, 512.0f / 17.0f, from4, end4, 2u);
-      if (ALLOW16 && v - lo16 < width16) fall(v, 131072.0f / 257.0f, 257.0f / 131072.0f, from16, end16, 8u);
-    };
-    for (uint32_t i = 0; i < n_kept; ++i) count(kept[i][tid]);
-    __syncthreads();
-    uint32_t own[kOwn], sum = 0;
-#pragma unroll
-    for (uint32_t i = 0; i < kOwn; ++i) {
-      own[i] = h[tid * kOwn + i];
-      sum += own[i];
-    }
-    const uint32_t beyond = kOwn > 1 ? places[kPlaces] : 0u;
-    const uint32_t upto = wave_scan(sum);
-    if (lane == 63) wsum[turn][wave] = upto;
-    __syncthreads();
-    const uint32_t waves_upto = row_scan(wsum[turn][lane & 15u]), all = __builtin_amdgcn_readlane(waves_upto, 15);
-    uint32_t behind = base + beyond + all - (wave ? __builtin_amdgcn_readlane(waves_upto, wave - 1) : 0u) - upto;  // cost behind the thread's bins
-    if (behind <= budget && (behind + sum > budget || tid == 0)) {
-      uint32_t b = kOwn - 1;  // of the thread's bins
-#pragma unroll
-      for (uint32_t i = kOwn - 1; i > 0; --i)
-        if (b == i && behind + own[i] <= budget) {
-          behind += own[i];
-          b = i - 1;
-        }
-      crossing[turn][0] = tid * kOwn + b;
-      crossing[turn][1] = behind;
-    }
-    __syncthreads();
-    const bool none = base + beyond > budget;  // infinite norms: not even +inf fits
-    const uint32_t bin = none ? (width - 1) >> s : crossing[turn][0];
-    base = none ? base + beyond : crossing[turn][1];
-    lo += bin << s;
-    hi = min(hi, lo + (1u << s));
-    lo4 = p4_of(lo);
-    hi4 = p4_of(hi);
-    if (ALLOW16) {
-      lo16 = p16_of(lo);
-      hi16 = p16_of(hi);
-    }
-  };
-  if (hi - lo > 1) level(places, integral_constant<uint32_t, 4>{}, shift_to(hi - lo - 1, kPlaces), 0);
-  while (hi - lo > kLastPlaces) {  // a first bracket of more than four bins
-    places[4 * tid] = places[4 * tid + 1] = places[4 * tid + 2] = places[4 * tid + 3] = 0;
-    if (tid == 0) places[kPlaces] = 0;
-    __syncthreads();
-    level(places, integral_constant<uint32_t, 4>{}, shift_to(hi - lo - 1, kPlaces), 0);
-    __syncthreads();
-  }
-  if (hi - lo > 1) level(last_places, integral_constant<uint32_t, 1>{}, 0, 1);
+  Bracket bracket = {lo, hi, lo4, hi4, lo16, hi16, base, n_kept};
+  to_one_pattern<ALLOW16>(bracket, budget, S, NoEvents());
+  hi = bracket.hi;
   // How many norms of each row are at or above the thresholds; the first wave turns that into the rows' first places.
   const int32_t p8 = (int32_t)hi, p4 = p4_from(hi), p16 = p16_from(hi, ALLOW16);
   uint32_t n4 = 0, n8 = 0, n16 = 0;  // lane g: of the wave's norms in group g
@@ -660,26 +729,285 @@ __device__ __forceinline__ void tell(const uint32_t (&n)[4], const dq::Announce 
                        __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-template <bool ALLOW16, bool ASIDE>
-__global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits, uint32_t *pos_all,
-                                                          uint32_t *counts_all, dq::Announce announce) {
-  __shared__ SearchSpace S;
-  const uint32_t T = search_block<ALLOW16, ASIDE>(F_all + (uint64_t)blockIdx.x * J, J, max_code_bits, S);
-  if (threadIdx.x >= 64) return;
+// A search's results, by its first wave: every row's first places where the row's own positions go, the counts, the threshold.
+__device__ __forceinline__ void put_search(uint32_t J, uint32_t T, const SearchSpace &S, uint32_t *pos, uint32_t *cnt, const dq::Announce &announce) {
   const RowPlaces p = row_places(J, S);
   const uint32_t from = threadIdx.x * kAllocThreads;
-  uint32_t *pos = pos_all + (uint64_t)blockIdx.x * J;
   if (from + kAllocThreads < J) {  // not the last row
 #pragma unroll
     for (int c = 0; c < 4; ++c) gst<uint32_t>(pos + from + c, p.first[c]);
   }
   if (threadIdx.x == 0) {
-    uint32_t *cnt = counts_all + 5ull * blockIdx.x;
 #pragma unroll
     for (int c = 0; c < 4; ++c) gst<uint32_t>(cnt + c, p.n_class[c]);
     gst<uint32_t>(cnt + 4, T);
     tell(p.n_class, announce, blockIdx.x);
   }
+}
+
+template <bool ALLOW16, bool ASIDE>
+__global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, uint32_t J, uint64_t max_code_bits, uint32_t *pos_all,
+                                                          uint32_t *counts_all, dq::Announce announce) {
+  __shared__ SearchSpace S;
+  const uint32_t T = search_block<ALLOW16, ASIDE>(F_all + (uint64_t)blockIdx.x * J, J, max_code_bits, S);
+  if (threadIdx.x < 64) put_search(J, T, S, pos_all + (uint64_t)blockIdx.x * J, counts_all + 5ull * blockIdx.x, announce);
+}
+
+// ---------------------------------------------------------------------------------------
+// Buckets of 32 rows and more at 2, 4 and 8 bits, few enough that a block for each of their rows finds a CU: what takes the search above most of its time, looking at every
+// norm to find the tenth of them that matters, in a launch of its own on as many CUs as there are rows (k_list), the rest by one block behind it
+// (k_search_listed).  Every block of k_list brackets the threshold by itself, from the same sample of 8,192 norms and bins of 2^18 patterns, four standard
+// deviations of the sampled cost to either side, and lists what its own 1,024 norms cost up to where inside the bracket, with how many lie above.  A list
+// goes where the row's positions go (the last whole row's block also has what follows it, up to 1,023 norms).  Sums over the lists' heads are exact: where the
+// threshold is not inside the bracket (norms in an order that the sample's steps meet) the one block searches as before.  Rows with more inside than their list holds
+// it looks at itself, up to 16; where there are more, it goes on as before from the bracket, whose costs are known.
+// What bounds both is their chains, some 5 and 6 us.  Kernels' time for 51,200 norms, one search -> both: lognormal 18.6 -> 12.5, sorted 20.2 -> 20.7, rows of
+// like norms 18.8 -> 17.6, within a factor of two of each other 22.4 -> 20.3, within a tenth 27.2 -> 27.6, equal 56.8 -> 51.8 (a bucket's statistics and
+// allocation 76.1 -> 70.4).  Not with 16-bit widths, whose brackets are wider (20.9 -> 21.2), nor below some 32,000 norms (20,000: 11.4 -> 12.2).
+constexpr uint32_t kSample = 8192, kFine = 18, kFineBins = 8192;  // bins of 2^18 patterns: 0x7F8 << 2 of them are finite
+struct ListHead {
+  uint32_t n;                        // events, or kTooLong: more than the list holds
+  uint32_t above8, above4, in8, in4;  // norms at or above the brackets' ends, and inside
+  uint32_t lo, hi;
+};
+constexpr uint32_t kListHead = 8, kListMost = kAllocThreads - kListHead, kTooLong = 0xFFFFFFFFu;
+static_assert(sizeof(ListHead) <= 4 * kListHead, "");
+
+__global__ void __launch_bounds__(kAllocThreads) k_list(const float *F_all, uint32_t J, uint64_t max_code_bits, uint32_t *lists_all) {
+  __shared__ alignas(16) uint32_t counters[kFineBins + 4];
+  __shared__ uint32_t wsum[kAllocWaves], wfit[kAllocWaves], found[kAllocWaves][4];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float *F = F_all + (uint64_t)blockIdx.y * J;
+  uint32_t *list = lists_all + (uint64_t)blockIdx.y * J + (uint64_t)blockIdx.x * kAllocThreads;
+  float sample[kSample / kAllocThreads], own[2];
+#pragma unroll
+  for (uint32_t i = 0; i < kSample / kAllocThreads; ++i) sample[i] = gld<float>(F + (uint32_t)(((uint64_t)(i * kAllocThreads + tid) * J) / kSample));
+  const uint32_t j0 = blockIdx.x * kAllocThreads + tid, j1 = blockIdx.x + 1 == gridDim.x ? j0 + kAllocThreads : J;
+  own[0] = gld<float>(F + j0);
+  own[1] = j1 < J ? gld<float>(F + j1) : 0.0f;
+  for (uint32_t b = tid; b < kFineBins / 4; b += kAllocThreads) reinterpret_cast<uint4 *>(counters)[b] = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < kSample / kAllocThreads; ++i) {
+    const uint32_t bin = (uint32_t)pattern_of(sample[i]) >> kFine, one = __builtin_amdgcn_readfirstlane(bin);
+    const bool all = __ballot(bin == one) == ~0ull;  // norms that are equal do not queue
+    if (!all || lane == 0) atomicAdd(counters + bin, all ? 64u : 1u);
+  }
+  __syncthreads();
+  OwnBins<kFineBins> first;
+#pragma unroll
+  for (uint32_t i = 0; i < kFineBins / kAllocThreads; ++i) first.n[i] = counters[kFineBins / kAllocThreads * tid + i];
+  sums_begin(first, wsum);
+  __syncthreads();
+  sums_end(first, wsum, counters);
+  if (tid < 4) counters[kFineBins + tid] = 0;
+  __syncthreads();
+  // the budget above 2 bits a norm, for the sample, and what the sample's cost may be off: its variance is at most (mean)(most - mean) per norm
+  constexpr float kMost = 6.0f;
+  const float mean = min((float)(max_code_bits - 2ull * J) / (float)J, kMost), budget = mean * (float)kSample;
+  const float off = 4.0f * __builtin_sqrtf(mean * (kMost - mean) * (float)kSample) + kMost;
+  uint32_t surely, perhaps;
+  last_failing<kFineBins / kAllocThreads>(0x7F800000u >> kFine, [&](uint32_t b, bool &over, bool &may) {
+    const uint32_t b4 = tied4_of(b << kFine) >> kFine;
+    over = (float)(4 * counters[b] + 2 * counters[b4 + 1]) > budget + off;
+    may = (float)(4 * counters[b] + 2 * counters[b4]) > budget - off;
+  }, wfit, surely, perhaps);
+  const uint32_t lo = surely << kFine, hi = (perhaps + 1) << kFine, lo4 = tied4_of(lo), hi4 = tied4_of(hi);
+  uint32_t event[2][2], at[2][2], n_in[2] = {0, 0}, above[2] = {0, 0};
+  bool in[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const bool there = i == 0 || j1 < J;
+    const uint32_t v = (uint32_t)pattern_of(own[i]);
+#pragma unroll
+    for (int kind = 0; kind < 2; ++kind) {
+      const uint32_t from = kind == 0 ? lo : lo4, to = kind == 0 ? hi : hi4;
+      in[i][kind] = there && v - from < to - from;
+      uint32_t upto = v;
+      if (kind == 1 && in[i][kind]) upto = last_tied(v, 17.0f / 512.0f, 512.0f / 17.0f, lo, hi);
+      event[i][kind] = event_of(kind, upto - lo);
+      const uint64_t inside = __ballot(in[i][kind]);
+      at[i][kind] = n_in[0] + n_in[1] + __builtin_amdgcn_mbcnt_hi((uint32_t)(inside >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)inside, 0u));
+      n_in[kind] += (uint32_t)__builtin_popcountll(inside);
+      above[kind] += (uint32_t)__builtin_popcountll(__ballot(there && v >= to));
+    }
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int kind = 0; kind < 2; ++kind) {
+      found[wave][kind] = n_in[kind];
+      found[wave][2 + kind] = above[kind];
+    }
+  }
+  __syncthreads();
+  uint32_t all[4], before = 0;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const uint32_t upto = row_scan(found[lane & 15u][c]);
+    all[c] = __builtin_amdgcn_readlane(upto, 15);
+    if (c < 2) before += (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)wave) - n_in[c];
+  }
+  const bool too_long = all[0] + all[1] > kListMost || hi - lo > kMostAbove;
+  if (tid == 0) {
+    const ListHead head = {too_long ? kTooLong : all[0] + all[1], all[2], all[3], all[0], all[1], lo, hi};
+    struct Words { uint32_t w[sizeof(ListHead) / 4]; };
+    const Words words = __builtin_bit_cast(Words, head);
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(ListHead) / 4; ++i) gst<uint32_t>(list + i, words.w[i]);
+  }
+  if (too_long) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int kind = 0; kind < 2; ++kind)
+      if (in[i][kind]) gst<uint32_t>(list + kListHead + before + at[i][kind], event[i][kind]);
+}
+
+// From the lists: T, and how many norms of each row are at or above the thresholds, in S.row_n.
+__device__ __forceinline__ uint32_t search_lists(const float *F, const uint32_t *lists, uint32_t J, uint64_t max_code_bits, SearchSpace &S) {
+  constexpr uint32_t kPerWave = kRegs / kAllocWaves, kAtOnce = 128;  // lists per wave; of each, events asked for before its length is known
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_lists = J / kAllocThreads;
+  struct Words { uint32_t w[sizeof(ListHead) / 4]; } words;
+#pragma unroll
+  for (uint32_t i = 0; i < sizeof(ListHead) / 4; ++i) words.w[i] = gld<uint32_t>(lists + min(lane, n_lists - 1) * kAllocThreads + i);
+  const ListHead head = __builtin_bit_cast(ListHead, words);
+  uint32_t ahead[kPerWave][kAtOnce / 64];
+#pragma unroll
+  for (uint32_t i = 0; i < kPerWave; ++i) {
+    const uint32_t *list = lists + min(wave + i * kAllocWaves, n_lists - 1) * kAllocThreads + kListHead;
+#pragma unroll
+    for (uint32_t k = 0; k < kAtOnce / 64; ++k) ahead[i][k] = gld<uint32_t>(list + k * 64 + lane);
+  }
+  reinterpret_cast<uint4 *>(S.places)[tid] = make_uint4(0, 0, 0, 0);
+  S.last_places[tid] = S.last_places[tid + kAllocThreads] = 0;
+  if (tid == 0) S.places[kPlaces] = 0;
+  const bool there = lane < n_lists;
+  auto sum = [&](uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(there ? x : 0u), 63); };
+  const uint32_t all8 = sum(head.above8), all4 = sum(head.above4), all_in8 = sum(head.in8), all_in4 = sum(head.in4);
+  Bracket bracket = {};
+  bracket.lo = __builtin_amdgcn_readfirstlane(head.lo);
+  bracket.hi = __builtin_amdgcn_readfirstlane(head.hi);
+  bracket.lo4 = tied4_of(bracket.lo);
+  bracket.hi4 = tied4_of(bracket.hi);
+  bracket.base = 2 * J + 4 * all8 + 2 * all4;
+  const uint32_t budget = (uint32_t)min(max_code_bits, (uint64_t)0xFFFFFFFFu), cost_lo = bracket.base + 4 * all_in8 + 2 * all_in4;
+  if (bracket.base > budget || (bracket.lo && cost_lo <= budget)) {  // not inside
+    __syncthreads();
+    return search_block<false, true>(F, J, max_code_bits, S);
+  }
+  const uint64_t dense = __ballot(there && head.n == kTooLong);  // rows whose norms are looked at themselves
+  const bool tail = J % kAllocThreads != 0 && dense >> (n_lists - 1) & 1u;  // what follows the last of them is a row more
+  const uint32_t n_dense = (uint32_t)__builtin_popcountll(dense) + (tail ? 1u : 0u);
+  // what a list has beyond the first kAtOnce goes to S.room
+  const uint32_t n_in = there && head.n != kTooLong ? head.n : 0u, longer = n_in > kAtOnce ? n_in - kAtOnce : 0u;
+  const uint32_t upto = wave_scan(longer), all = __builtin_amdgcn_readlane(upto, 63);
+  if (all + n_dense * kAllocThreads > 16u * kAllocThreads) {
+    const Given given = {bracket.lo, bracket.hi, all8 + all4 + all_in8 + all_in4, all8 + all4, cost_lo, bracket.base};
+    __syncthreads();
+    return search_block<false, true>(F, J, max_code_bits, S, given);
+  }
+  uint32_t n[kPerWave];  // of the wave's lists
+#pragma unroll
+  for (uint32_t i = 0; i < kPerWave; ++i) {
+    const uint32_t l = wave + i * kAllocWaves, len = (uint32_t)__builtin_amdgcn_readlane((int)n_in, (int)(l & 63u));
+    n[i] = l < n_lists ? len : 0u;
+  }
+  for (uint64_t more = __ballot(longer != 0); more;) {  // by all threads, four lists at a time
+    uint32_t to[4], event[4];
+    bool in[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t l = (uint32_t)__builtin_ctzll(more | 1ull << 63), len = more ? (uint32_t)__builtin_amdgcn_readlane((int)longer, (int)l) : 0u;
+      to[i] = n_dense * kAllocThreads + (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)l) - len + tid;
+      in[i] = tid < len;
+      event[i] = in[i] ? gld<uint32_t>(lists + l * kAllocThreads + kListHead + kAtOnce + tid) : 0u;
+      more &= more - 1;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (in[i]) S.room[to[i]] = event[i];
+  }
+  uint32_t n_rows = 0;
+  for (uint64_t more = dense; more;) {
+    float f[4];
+    uint32_t some = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t l = (uint32_t)__builtin_ctzll(more | 1ull << 63);
+      f[i] = more ? gld<float>(F + l * kAllocThreads + tid) : 0.0f;
+      some += more ? 1u : 0u;
+      more &= more - 1;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i)
+      if (i < some) S.room[(n_rows + i) * kAllocThreads + tid] = (uint32_t)pattern_of(f[i]);
+    n_rows += some;
+  }
+  if (tail) {
+    const uint32_t j = n_lists * kAllocThreads + tid;
+    S.room[n_rows * kAllocThreads + tid] = j < J ? (uint32_t)pattern_of(gld<float>(F + j)) : 0xFFFFFFFFu;
+  }
+  __syncthreads();
+  const uint32_t *const longer_lists = S.room + n_dense * kAllocThreads;
+  const uint32_t n_longer = all > tid ? (all - tid + kAllocThreads - 1) / kAllocThreads : 0u;
+  bracket.n_kept = n_dense;
+  const Bracket whole = bracket;
+  to_one_pattern<false>(bracket, budget, S, [&](auto body) {
+#pragma unroll
+    for (uint32_t i = 0; i < kPerWave; ++i)
+#pragma unroll
+      for (uint32_t k = 0; k < kAtOnce / 64; ++k)
+        if (k * 64 + lane < n[i]) body(ahead[i][k]);
+    for (uint32_t i = 0; i < n_longer; ++i) body(longer_lists[i * kAllocThreads + tid]);
+  });
+  const uint32_t T = bracket.hi, p4 = tied4_of(T);
+  uint32_t n4 = head.above4, n8 = head.above8;  // lane l: norms of row l at or above
+#pragma unroll
+  for (uint32_t i = 0; i < kPerWave; ++i) {
+    uint32_t a4 = 0, a8 = 0;
+    auto count = [&](bool valid, uint32_t event) {
+      const bool reached = valid && whole.lo + upto_of(event) >= T;
+      a8 += (uint32_t)__builtin_popcountll(__ballot(reached && kind_of(event) == 0));
+      a4 += (uint32_t)__builtin_popcountll(__ballot(reached && kind_of(event) == 1));
+    };
+#pragma unroll
+    for (uint32_t k = 0; k < kAtOnce / 64; ++k) count(k * 64 + lane < n[i], ahead[i][k]);
+    if (n[i] > kAtOnce) {
+      const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)((wave + i * kAllocWaves) & 63u));
+      for (uint32_t k = end - (n[i] - kAtOnce); k < end; k += 64) count(k + lane < end, longer_lists[min(k + lane, end - 1)]);
+    }
+    const bool mine = lane == wave + i * kAllocWaves;
+    n4 += mine ? a4 : 0u;
+    n8 += mine ? a8 : 0u;
+  }
+  if ((lane & (kAllocWaves - 1)) == wave) {  // the wave's rows; beyond the lists there is none
+    S.row_n[lane][0] = there ? n4 : 0u;
+    S.row_n[lane][1] = there ? n8 : 0u;
+    S.row_n[lane][2] = 0;
+  }
+  __syncthreads();
+  if (dense) {
+    uint64_t more = dense;
+    for (uint32_t i = 0; i < n_dense; ++i) {
+      const uint32_t l = i < n_rows ? (uint32_t)__builtin_ctzll(more) : n_lists - 1, v = S.room[i * kAllocThreads + tid];
+      more &= more - 1;
+      const uint32_t a4 = (uint32_t)__builtin_popcountll(__ballot(v < whole.hi4 && v >= p4)), a8 = (uint32_t)__builtin_popcountll(__ballot(v < whole.hi && v >= T));
+      if (lane == 0) {
+        atomicAdd(&S.row_n[l][0], a4);
+        atomicAdd(&S.row_n[l][1], a8);
+      }
+    }
+    __syncthreads();
+  }
+  return T;  // (the last list's row has what follows it, too: of the row after it nobody reads the first places, and sums over all are the same)
+}
+
+__global__ void __launch_bounds__(kAllocThreads) k_search_listed(const float *F_all, uint32_t J, uint64_t max_code_bits, uint32_t *pos_all,
+                                                                 uint32_t *counts_all, dq::Announce announce) {
+  __shared__ SearchSpace S;
+  uint32_t *pos = pos_all + (uint64_t)blockIdx.x * J;
+  const uint32_t T = search_lists(F_all + (uint64_t)blockIdx.x * J, pos, J, max_code_bits, S);
+  if (threadIdx.x < 64) put_search(J, T, S, pos, counts_all + 5ull * blockIdx.x, announce);
 }
 
 // Behind the search of an all-reduce that replays on the original tensors: what k_alloc_positions and k_reorder_mean do between them, but for the
@@ -1226,11 +1554,19 @@ dq_status stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dty
   return launched();
 }
 
+constexpr uint32_t kLeastListed = 32 * kAllocThreads, kMostListed = 256;  // blocks that list, a CU each
 static_assert(kMostSearched == (uint32_t)kRegs * kAllocThreads && kMostTablePaths <= (uint32_t)kAllocThreads, "a register per norm, a thread per path");
 dq_status search(const float *F, uint32_t J, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width, uint32_t *places, uint32_t *counts,
                  Announce announce, hipStream_t s) {
   const bool allow16 = max_width == 16, aside = J > 16u * kAllocThreads;
-  const auto kernel = aside ? (allow16 ? k_search<true, true> : k_search<false, true>) : (allow16 ? k_search<true, false> : k_search<false, false>);
+  auto kernel = aside ? (allow16 ? k_search<true, true> : k_search<false, true>) : (allow16 ? k_search<true, false> : k_search<false, false>);
+  const uint32_t lists = J / kAllocThreads;
+  if (!allow16 && J >= kLeastListed && (uint64_t)lists * n_buckets <= kMostListed) {
+    hipLaunchKernelGGL(k_list, dim3(lists, n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, places);
+    const dq_status st = launched();
+    if (st != DQ_OK) return st;
+    kernel = k_search_listed;
+  }
   hipLaunchKernelGGL(kernel, dim3(n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, places, counts, announce);
   return launched();
 }

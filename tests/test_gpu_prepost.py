@@ -234,6 +234,33 @@ def test_allocate_norms_close_together(dev, J, max_width):
             check_allocate(dev, F.astype(f32), J, int(bits * J), max_width=max_width)
 
 
+@pytest.mark.parametrize("J", [32767, 32768, 33791, 40001, 65535, 65536])   # below and from where rows list their norms; whole rows and a rest
+@pytest.mark.parametrize("kind", ["random", "sorted", "dense_end", "clustered", "aliased", "equal", "half"])
+def test_allocate_from_lists(dev, J, kind):
+    """Rows list the norms around a threshold that a sample brackets: lists longer than what is asked for ahead, longer than their place (in the last row
+    with what follows it, too), too many of those, and samples that are beside the mark."""
+    rng = np.random.default_rng(J)
+    F = np.exp(rng.normal(-14, 2.5, 2 * J)).astype(f32)
+    if kind == "sorted":
+        F = np.sort(F)
+    elif kind == "dense_end":         # the norms around the threshold in the last row and behind it
+        F = F.reshape(2, J)
+        F[:, J - 1800:] = np.exp(rng.normal(-12.5, 0.2, (2, 1800)))
+        F = F.reshape(-1)
+    elif kind == "clustered":         # a few rows each hold most of what is near the threshold
+        F = (np.exp(rng.normal(-14, 2.5, 2 * J // 512 + 1)).repeat(512)[:2 * J] * np.exp(rng.normal(0, 0.05, 2 * J))).astype(f32)
+    elif kind == "aliased":           # the sampled norms are unlike the others
+        at = np.arange(8192, dtype=np.int64) * J // 8192
+        F[at] *= f32(1e-6)
+        F[J + at] *= f32(1e6)
+    elif kind == "equal":
+        F = np.full(2 * J, 3.25e-7, f32)
+    elif kind == "half":
+        F[::2] = 0
+    for bits in (2.1, 4.0, 7.5):
+        check_allocate(dev, F, J, int(bits * J))
+
+
 def test_allocate_more_buckets_than_a_grid_dimension(dev):
     """70,000 buckets of 5 super-groups: the positions launch is cut at 65,535 buckets (the grid's second
     dimension); buckets on both sides of the cut must come out right."""
