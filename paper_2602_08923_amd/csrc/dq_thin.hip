@@ -78,19 +78,17 @@ __device__ __forceinline__ uint64_t tensor_of(const Walk &W, uint32_t chunk, uin
 // Maximum over a super-group of which every lane of the wave has its group's maximum.  (As one block, as the compiler makes three instructions of each of the
 // last two maxima.  A maximum reads what the one before it wrote from other lanes: two wait states between them.)
 __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
-  uint32_t top;
   asm("s_nop 1\n\t"
-      "v_max_u32_dpp %1, %1, %1 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_u32_dpp %0, %0, %0 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
       "s_nop 1\n\t"
-      "v_max_u32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_u32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
       "s_nop 1\n\t"
-      "v_max_u32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"  // row 0 into 1, row 2 into 3
+      "v_max_u32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"  // row 0 into 1, row 2 into 3
       "s_nop 1\n\t"
-      "v_max_u32_dpp %1, %1, %1 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"  // row 1 into 2 and 3
-      "s_nop 1\n\t"
-      "v_readlane_b32 %0, %1, 63"
-      : "=s"(top), "+v"(x));
-  return top;
+      "v_max_u32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"  // row 1 into 2 and 3
+      "s_nop 1"
+      : "+v"(x));
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);  // outside: the compiler knows what has to stand between it and a vector instruction's read
 }
 
 // What a wave holds of a tile before it walks it: where it is and the slices of its first hops.
@@ -286,9 +284,6 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
             // Levels: a stored scale above zero implies m > 2^-118 (the super-group's is at least 2^-100, and the dither at least
             // 1/512), so the bound only keeps the quotient finite where the levels do not count.
             const float inv = TREE ? (m >= 0x1p-120f ? 1.0f / m : 0.0f) : reciprocal(u2f(max(mg, f2u(0x1p-120f))));
-            // The scales, as in scale_group.  With one super-group per wave its maximum and what follows from it are scalar, and a
-            // super-group that is encoded as zero finds zeros for its reciprocals.  With two such a one has its groups' maxima taken as zero instead
-            // of its results: as conditional results the compiler puts the chain behind a branch, after the levels' lookups.
             // The scales, as in scale_group.  With one super-group per wave its maximum and what follows from it are scalar, and a
             // super-group that is encoded as zero finds zeros for its reciprocals.  With two such a one has its groups' maxima taken as zero instead
             // of its results: as conditional results the compiler puts the chain behind a branch, after the levels' lookups.
