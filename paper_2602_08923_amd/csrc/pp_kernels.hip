@@ -141,6 +141,44 @@ __global__ void __launch_bounds__(kThreads) k_stats_all(WorkerTensors W, uint32_
   }
 }
 
+// The same where that leaves a worker's tile after the other's trip to memory: a wave takes every `slots`-th worker's, and their numbers meet in LDS, where
+// they are summed in the order of the ranks.  What bounds it are launch and trips.  Taken by more than four workers up to so many waves per CU that memory
+// would be what bounds it, 11 in bf16 and 7 in fp32 (the kernel alone in a graph, us, one wave per tile -> 2, 4, 8, 16): bf16, 32 workers' 64 super-groups 8.0 ->
+// 5.7, 4.0, 3.1, 3.0; 8 of 1,000 3.1 -> 2.7, 2.4, 2.3; 18 of 2,000 5.3 -> 4.1, 3.4, 3.4, 3.5; 64 of 4,000 22.7 -> 20.2, 20.6, 22.0, 21.3; 18 of 6,000 9.8 ->
+// 10.0, 10.1; 4 of 3,000 2.4 -> 2.5, 2.5; fp32, 12 of 3,000 6.8 -> 6.1, 5.6, 5.5; 12 of 4,000 8.6 -> 9.2, 9.5.  30 workers' all-reduce of 210 31.2 -> 26.1.
+constexpr uint32_t kMostSlots = 16;  // waves for one tile
+template <typename LT>
+__global__ void __launch_bounds__(64 * kMostSlots) k_stats_split(WorkerTensors W, uint32_t n, uint32_t slots, uint32_t tiles, uint64_t n_sg, float *mu,
+                                                                 float *F, const void **grads) {
+  extern __shared__ float2 part[];  // tile of the block, worker, super-group
+  if (grads && blockIdx.x == 0)
+    for (uint32_t i = threadIdx.x; i < 2 * n; i += blockDim.x) grads[i] = W.x[i < n ? i : i - n];
+  const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t tile = wave / slots, slot = wave - tile * slots;
+  const uint64_t t0 = (uint64_t)blockIdx.x * tiles, first = min((t0 + tile) * 4 + (lane >> 4), n_sg - 1) * kSG + (lane & 15u) * 16;
+  Entries<LT> e = load_entries<LT>(W.x[slot], first);
+  for (uint32_t w = slot; w < n; w += slots) {
+    Entries<LT> next = e;
+    if (w + slots < n) next = load_entries<LT>(W.x[w + slots], first);
+    float s, f;
+    row_sums<LT>(e, s, f);
+    if ((lane & 15u) == 0) part[(tile * n + w) * 4 + (lane >> 4)] = float2{u2f(bf16_rne(s * (1.0f / kSG)) << 16), u2f(bf16_rne(f) << 16)};
+    e = next;
+  }
+  __syncthreads();
+  const uint64_t sg = t0 * 4 + threadIdx.x;
+  if (threadIdx.x >= 4 * tiles || sg >= n_sg) return;
+  const float2 *p = part + (threadIdx.x >> 2) * n * 4 + (threadIdx.x & 3u);
+  float sm = 0.0f, sf = 0.0f;
+#pragma unroll 8
+  for (uint32_t w = 0; w < n; ++w) {
+    sm = sm + p[4 * w].x;
+    sf = sf + p[4 * w].y;
+  }
+  gst<float>(mu + sg, sm / (float)n);
+  gst<float>(F + sg, sf);
+}
+
 // Combination over workers: contributions rounded to bf16 (what is exchanged), summed in rank
 // order in fp32; the mean of the means by one division.  A thread per super-group, eight workers' numbers requested at a time: what
 // bounds it are the trips to memory (8 workers, 51,200 super-groups: 3.2 us with one, 4.8 with one per worker).
@@ -1520,10 +1558,15 @@ __global__ void __launch_bounds__(kThreads) k_restore(const float *sum_all, cons
 
 bool aligned(const void *p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
-// blocks per grid row: enough for the units of one row, at most the GPU's resident share
-uint32_t stream_blocks(uint64_t units_per_block_round, uint64_t units, uint32_t rows = 1) {
+uint32_t compute_units() {
   int dev = 0, n_cu = 256;
   if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+  return (uint32_t)n_cu;
+}
+
+// blocks per grid row: enough for the units of one row, at most the GPU's resident share
+uint32_t stream_blocks(uint64_t units_per_block_round, uint64_t units, uint32_t rows = 1) {
+  const uint32_t n_cu = compute_units();
   const uint64_t need = (units + units_per_block_round - 1) / units_per_block_round;
   const uint64_t cap = ((uint64_t)n_cu * 8 + rows - 1) / rows;  // 8 blocks of 256 threads per CU in all
   return (uint32_t)(need < 1 ? 1 : (need < cap ? need : cap));
@@ -1548,9 +1591,21 @@ dq_status stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dty
     if (!aligned(tensors[w], 16)) return DQ_EALIGN;
     W.x[w] = tensors[w];
   }
+  const uint64_t n_tiles = (n_sg + 3) / 4, waves = compute_units() * (dtype == DQ_F32 ? 7ull : 11ull);  // as many as pay (k_stats_split)
+  if (n_workers > 4 && n_tiles * 2 <= waves) {
+    uint32_t slots = (uint32_t)(waves / n_tiles < kMostSlots ? waves / n_tiles : kMostSlots);
+    slots = slots < n_workers ? slots : n_workers;
+    const uint32_t rounds = (n_workers + slots - 1) / slots;
+    slots = (n_workers + rounds - 1) / rounds;
+    const uint32_t tiles = slots < 4 ? 2 : 1;
+    const auto split = dtype == DQ_F32 ? k_stats_split<float> : k_stats_split<uint16_t>;
+    hipLaunchKernelGGL(split, dim3((uint32_t)((n_tiles + tiles - 1) / tiles)), dim3(64 * slots * tiles), tiles * n_workers * 4 * sizeof(float2), s, W,
+                       n_workers, slots, tiles, n_sg, mu, F, grads);
+    return launched();
+  }
   const uint32_t blocks = stream_blocks(4 * (kThreads / 64), n_sg);
-  if (dtype == DQ_F32) hipLaunchKernelGGL(k_stats_all<float>, dim3(blocks), dim3(kThreads), 0, s, W, n_workers, n_sg, mu, F, grads);
-  else hipLaunchKernelGGL(k_stats_all<uint16_t>, dim3(blocks), dim3(kThreads), 0, s, W, n_workers, n_sg, mu, F, grads);
+  const auto kernel = dtype == DQ_F32 ? k_stats_all<float> : k_stats_all<uint16_t>;
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, s, W, n_workers, n_sg, mu, F, grads);
   return launched();
 }
 

@@ -72,6 +72,18 @@ def test_sg_stats_exact_cases(dev):
     assert mu.numel() == 0 and F.numel() == 0
 
 
+@pytest.mark.parametrize("dtype,n,J", [("bf16", 5, 1), ("bf16", 6, 3), ("bf16", 16, 4093), ("bf16", 17, 1027), ("bf16", 21, 2815), ("bf16", 256, 6),
+                                       ("bf16", 40, 5633), ("f32", 5, 1789), ("f32", 19, 3585), ("f32", 33, 18), ("f32", 3, 500)])
+def test_stats_of_workers_is_stats_and_combination(dev, dtype, n, J):
+    """A wave per worker and tile, per several workers, or per tile: the same bits as every worker's statistics, then their combination."""
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n * 10007 + J)
+    x = torch.randn(n, J * 256, generator=gen, device=dev).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    want = B.dq_stats_combine(*(torch.stack(t) for t in zip(*(B.dq_sg_stats(w) for w in x))))
+    for g, w in zip(B.stats_of_workers(x.unbind(0)), want):
+        assert torch.equal(g, w)
+
+
 def test_stats_combine(dev):
     n, J = 8, 3001
     xs = [draw(2, w, J * 256) for w in range(n)]
