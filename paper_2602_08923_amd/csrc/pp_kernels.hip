@@ -761,10 +761,38 @@ __device__ __forceinline__ RowPlaces row_places(uint32_t J, const SearchSpace &S
   }
   return p;
 }
+// Widths and positions by a block that has searched for itself: its row's super-group of norm f, one per thread.
+__device__ __forceinline__ Placed place_searched(float f, bool there, uint32_t row, uint32_t pattern, bool allow16, const RowPlaces &p,
+                                                 uint32_t (*mine_w)[4]) {
+  const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t first[4];  // as lane `row` says it
+#pragma unroll
+  for (int c = 0; c < 4; ++c) first[c] = (uint32_t)__builtin_amdgcn_readlane((int)p.first[c], (int)row);
+  const int32_t p8 = (int32_t)pattern, p4 = p4_from(pattern), p16 = p16_from(pattern, allow16);
+  const uint32_t k = there ? class_of(pattern_of(f), p4, p8, p16) : 4u;
+  const uint64_t b[4] = {__ballot(k == 0), __ballot(k == 1), __ballot(k == 2), __ballot(k == 3)};
+  if (lane == 0) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) mine_w[wave][c] = (uint32_t)__builtin_popcountll(b[c]);
+  }
+  uint32_t at = k == 0 ? first[0] : k == 1 ? first[1] : k == 2 ? first[2] : first[3];
+  __syncthreads();
+  if (k == 4) return Placed{4u, 0u};
+  for (uint32_t w = 0; w < wave; ++w) at += mine_w[w][k];
+  const uint64_t mine = k == 0 ? b[0] : (k == 1 ? b[1] : (k == 2 ? b[2] : b[3]));
+  return Placed{k, at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u))};
+}
 __device__ __forceinline__ void tell(const uint32_t (&n)[4], const dq::Announce &announce, uint32_t bucket) {
   if (announce.host)  // one store, so that nothing needs to be ordered; the fourth class is the rest
     __hip_atomic_store(announce.host + bucket, n[0] | (uint64_t)n[1] << 17 | (uint64_t)n[2] << 34 | (uint64_t)announce.tag << 51, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__device__ __forceinline__ void put_counts(const uint32_t (&n)[4], uint32_t T, uint32_t *cnt, const dq::Announce &announce, uint32_t bucket) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) gst<uint32_t>(cnt + c, n[c]);
+  gst<uint32_t>(cnt + 4, T);
+  tell(n, announce, bucket);
 }
 
 // A search's results, by its first wave: every row's first places where the row's own positions go, the counts, the threshold.
@@ -775,12 +803,7 @@ __device__ __forceinline__ void put_search(uint32_t J, uint32_t T, const SearchS
 #pragma unroll
     for (int c = 0; c < 4; ++c) gst<uint32_t>(pos + from + c, p.first[c]);
   }
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) gst<uint32_t>(cnt + c, p.n_class[c]);
-    gst<uint32_t>(cnt + 4, T);
-    tell(p.n_class, announce, blockIdx.x);
-  }
+  if (threadIdx.x == 0) put_counts(p.n_class, T, cnt, announce, blockIdx.x);
 }
 
 template <bool ALLOW16, bool ASIDE>
@@ -791,8 +814,31 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
   if (threadIdx.x < 64) put_search(J, T, S, pos_all + (uint64_t)blockIdx.x * J, counts_all + 5ull * blockIdx.x, announce);
 }
 
+// A whole allocation in one launch: grid (rows, buckets), every block searches for itself, on a CU that has nothing else to do, and then places its row.  Against a
+// search in one block and the positions behind it, a launch and the places' trip to memory and back are fewer; the device's time and the
+// host's are both less (statistics and allocation: 2 workers' 17,000 28.7 -> 26.4 us, 8 workers' 30,000 56.3 -> 53.7, of two buckets of 9,000 61.5 -> 59.3, 12 workers'
+// 60,000 up to 16 bits 113.4 -> 111.7).  While there is a CU for every row: more would search one after the other.  (Buckets of one row keep the two launches that
+// tests/test_launch_limits.py describes.)
+template <bool ALLOW16, bool ASIDE>
+__global__ void __launch_bounds__(kAllocThreads) k_search_positions(const float *F_all, uint32_t J, uint64_t max_code_bits, uint8_t *widths_all,
+                                                                    uint32_t *pos_all, uint32_t *counts_all, dq::Announce announce) {
+  __shared__ SearchSpace S;
+  __shared__ uint32_t mine_w[kAllocWaves][4];
+  const uint64_t first = (uint64_t)blockIdx.y * J;
+  const uint32_t row = blockIdx.x, j = row * kAllocThreads + threadIdx.x;
+  const float f = gld<float>(F_all + first + min(j, J - 1));
+  const uint32_t T = search_block<ALLOW16, ASIDE>(F_all + first, J, max_code_bits, S);
+  const RowPlaces p = row_places(J, S);
+  if (row == 0 && threadIdx.x == 0) put_counts(p.n_class, T, counts_all + 5ull * blockIdx.y, announce, blockIdx.y);
+  const Placed x = place_searched(f, j < J, row, T, ALLOW16, p, mine_w);
+  if (x.k < 4) {
+    gst<uint8_t>(widths_all + first + j, (uint8_t)(2u << x.k));
+    gst<uint32_t>(pos_all + first + j, x.at);
+  }
+}
+
 // ---------------------------------------------------------------------------------------
-// Buckets of 32 rows and more at 2, 4 and 8 bits, few enough that a block for each of their rows finds a CU: what takes the search above most of its time, looking at every
+// Buckets of 40 rows and more at 2, 4 and 8 bits, few enough that a block for each of their rows finds a CU: what takes the search above most of its time, looking at every
 // norm to find the tenth of them that matters, in a launch of its own on as many CUs as there are rows (k_list), the rest by one block behind it
 // (k_search_listed).  Every block of k_list brackets the threshold by itself, from the same sample of 8,192 norms and bins of 2^18 patterns, four standard
 // deviations of the sampled cost to either side, and lists what its own 1,024 norms cost up to where inside the bracket, with how many lie above.  A list
@@ -801,7 +847,9 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
 // it looks at itself, up to 16; where there are more, it goes on as before from the bracket, whose costs are known.
 // What bounds both is their chains, some 5 and 6 us.  Kernels' time for 51,200 norms, one search -> both: lognormal 18.6 -> 12.5, sorted 20.2 -> 20.7, rows of
 // like norms 18.8 -> 17.6, within a factor of two of each other 22.4 -> 20.3, within a tenth 27.2 -> 27.6, equal 56.8 -> 51.8 (a bucket's statistics and
-// allocation 76.1 -> 70.4).  Not with 16-bit widths, whose brackets are wider (20.9 -> 21.2), nor below some 32,000 norms (20,000: 11.4 -> 12.2).
+// allocation 76.1 -> 70.4).  Not with 16-bit widths, whose brackets are wider (20.9 -> 21.2), nor below some 41,000 norms, where all in one launch, which the host enqueues
+// sooner, is the better (statistics and allocation, one launch and listed: 2 workers' 33,000 28.2 and 31.0, 40,000 30.6 and 30.7, 4 workers' 50,000 44.9 and 41.4; all-reduces
+// over 6 of 30,000 62.5 and 64.2, over 8 of 42,664 88.9 and 86.9).
 constexpr uint32_t kSample = 8192, kFine = 18, kFineBins = 8192;  // bins of 2^18 patterns: 0x7F8 << 2 of them are finite
 struct ListHead {
   uint32_t n;                        // events, or kTooLong: more than the list holds
@@ -1287,45 +1335,31 @@ __global__ void __launch_bounds__(kAllocThreads) k_arrange(const float *F_all, c
   }
 }
 
-// The search and k_arrange in one launch, for one bucket of up to 16 rows: every block searches for itself, which costs nothing but a CU that has
+// The search and k_arrange in one launch, for one bucket that is not listed: every block searches for itself, which costs nothing but a CU that has
 // nothing else to do, and goes on with what it has in LDS.  Against two launches, a launch's start and the trips of places and counts to memory and back
 // are fewer: 8 workers' 8,192 super-groups 8.2 and 5.2 us -> 9.6, 6 workers' 48 6.9 and 5.1 -> 7.8 (all-reduces 36.1 -> 31.9, 23.2 -> 21.9; 16 workers' halving
-// of 1,312 31.5 -> 27.9, 3 workers' 15,000 30.6 -> 27.4).  What bounds it is the search's chain, whose every piece of code is fetched and run once.
-template <bool ALLOW16>
+// of 1,312 31.5 -> 27.9, 3 workers' 15,000 30.6 -> 27.4, 4 workers' 17,980 36.5 -> 32.5).  What bounds it is the search's chain, whose every piece of code is fetched and run once.
+template <bool ALLOW16, bool ASIDE>
 __global__ void __launch_bounds__(kAllocThreads) k_search_arrange(const float *F, const float *mu, uint32_t J, uint64_t max_code_bits, float *mu_main,
                                                                   uint32_t *origin, dq::Announce announce, dq::Tables T) {
   __shared__ SearchSpace S;
   __shared__ uint32_t mine_w[kAllocWaves][4];
   __shared__ TableSpace space;
-  const uint32_t parts = table_parts(T), tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t parts = table_parts(T), tid = threadIdx.x;
   const bool tables = blockIdx.x < parts;
   const uint32_t row = tables ? 0u : blockIdx.x - parts, j = row * kAllocThreads + tid;
   const float f = gld<float>(F + min(j, J - 1)), m = mu ? gld<float>(mu + min(j, J - 1)) : 0.0f;
-  const uint32_t pattern = search_block<ALLOW16, false>(F, J, max_code_bits, S);
+  const uint32_t pattern = search_block<ALLOW16, ASIDE>(F, J, max_code_bits, S);
   const RowPlaces p = row_places(J, S);
-  uint32_t first[4];  // of the block's row; by all lanes, as lane `row` says it
-#pragma unroll
-  for (int c = 0; c < 4; ++c) first[c] = (uint32_t)__builtin_amdgcn_readlane((int)p.first[c], (int)row);
   if (tables) {
     if (blockIdx.x == 0 && tid == 0) tell(p.n_class, announce, 0);
     make_tables(T, [&](uint32_t, int w) { return p.n_class[w]; }, blockIdx.x, space);
     return;
   }
-  const int32_t p8 = (int32_t)pattern, p4 = p4_from(pattern), p16 = p16_from(pattern, ALLOW16);
-  const uint32_t k = j < J ? class_of(pattern_of(f), p4, p8, p16) : 4u;
-  const uint64_t b[4] = {__ballot(k == 0), __ballot(k == 1), __ballot(k == 2), __ballot(k == 3)};
-  if (lane == 0) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) mine_w[wave][c] = (uint32_t)__builtin_popcountll(b[c]);
-  }
-  uint32_t at = k == 0 ? first[0] : k == 1 ? first[1] : k == 2 ? first[2] : first[3];
-  __syncthreads();
-  if (k == 4) return;
-  for (uint32_t w = 0; w < wave; ++w) at += mine_w[w][k];
-  const uint64_t mine = k == 0 ? b[0] : (k == 1 ? b[1] : (k == 2 ? b[2] : b[3]));
-  at += __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
-  if (mu) gst<float>(mu_main + at, k == 3 ? 0.0f : m);
-  gst<uint32_t>(origin + at, j);
+  const Placed x = place_searched(f, j < J, row, pattern, ALLOW16, p, mine_w);
+  if (x.k == 4) return;
+  if (mu) gst<float>(mu_main + x.at, x.k == 3 ? 0.0f : m);
+  gst<uint32_t>(origin + x.at, j);
 }
 
 // Buckets of more than 65,536 super-groups: the norms are read again in every round of a bisection, widths and positions
@@ -1591,8 +1625,8 @@ dq_status stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dty
     if (!aligned(tensors[w], 16)) return DQ_EALIGN;
     W.x[w] = tensors[w];
   }
-  const uint64_t n_tiles = (n_sg + 3) / 4, waves = compute_units() * (dtype == DQ_F32 ? 7ull : 11ull);  // as many as pay (k_stats_split)
-  if (n_workers > 4 && n_tiles * 2 <= waves) {
+  const uint64_t n_tiles = (n_sg + 3) / 4, waves = n_workers > 4 ? compute_units() * (dtype == DQ_F32 ? 7ull : 11ull) : 0;  // as many as pay (k_stats_split)
+  if (n_tiles * 2 <= waves) {
     uint32_t slots = (uint32_t)(waves / n_tiles < kMostSlots ? waves / n_tiles : kMostSlots);
     slots = slots < n_workers ? slots : n_workers;
     const uint32_t rounds = (n_workers + slots - 1) / slots;
@@ -1609,15 +1643,18 @@ dq_status stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dty
   return launched();
 }
 
-constexpr uint32_t kLeastListed = 32 * kAllocThreads, kMostListed = 256;  // blocks that list, a CU each
+// Whether the rows of a bucket list their norms first (the threshold is where that pays against k_search_positions and k_search_arrange)
+constexpr uint32_t kLeastListed = 40 * kAllocThreads, kMostListed = 256;  // blocks that list, a CU each
+static bool takes_lists(uint32_t J, uint32_t n_buckets, uint32_t max_width) {
+  return max_width == 8 && J >= kLeastListed && J <= kMostSearched && (uint64_t)(J / kAllocThreads) * n_buckets <= kMostListed;
+}
 static_assert(kMostSearched == (uint32_t)kRegs * kAllocThreads && kMostTablePaths <= (uint32_t)kAllocThreads, "a register per norm, a thread per path");
 dq_status search(const float *F, uint32_t J, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width, uint32_t *places, uint32_t *counts,
                  Announce announce, hipStream_t s) {
   const bool allow16 = max_width == 16, aside = J > 16u * kAllocThreads;
   auto kernel = aside ? (allow16 ? k_search<true, true> : k_search<false, true>) : (allow16 ? k_search<true, false> : k_search<false, false>);
-  const uint32_t lists = J / kAllocThreads;
-  if (!allow16 && J >= kLeastListed && (uint64_t)lists * n_buckets <= kMostListed) {
-    hipLaunchKernelGGL(k_list, dim3(lists, n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, places);
+  if (takes_lists(J, n_buckets, max_width)) {
+    hipLaunchKernelGGL(k_list, dim3(J / kAllocThreads, n_buckets), dim3(kAllocThreads), 0, s, F, J, max_code_bits, places);
     const dq_status st = launched();
     if (st != DQ_OK) return st;
     kernel = k_search_listed;
@@ -1626,10 +1663,13 @@ dq_status search(const float *F, uint32_t J, uint32_t n_buckets, uint64_t max_co
   return launched();
 }
 
-bool takes_search_arrange(uint32_t J, uint32_t n_buckets) { return n_buckets == 1 && J <= 16u * kAllocThreads; }
+bool takes_search_arrange(uint32_t J, uint32_t n_buckets, uint32_t max_width) {
+  return n_buckets == 1 && J <= kMostSearched && !takes_lists(J, 1, max_width);
+}
 dq_status search_arrange(const float *F, const float *mu, uint32_t J, uint64_t max_code_bits, uint32_t max_width, float *mu_main, uint32_t *origin,
                          Announce announce, const Tables &tables, hipStream_t s) {
-  const auto kernel = max_width == 16 ? k_search_arrange<true> : k_search_arrange<false>;
+  const auto kernel = J > 16u * kAllocThreads ? (max_width == 16 ? k_search_arrange<true, true> : k_search_arrange<false, true>)
+                                              : (max_width == 16 ? k_search_arrange<true, false> : k_search_arrange<false, false>);
   hipLaunchKernelGGL(kernel, dim3((J + kAllocThreads - 1) / kAllocThreads + table_parts(tables)), dim3(kAllocThreads), 0, s, F, mu, J, max_code_bits, mu_main,
                      origin, announce, tables);
   return launched();
@@ -1699,7 +1739,11 @@ static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_b
     const uint32_t nb = n_buckets - b0 < 65535u ? n_buckets - b0 : 65535u;
     const uint64_t off = (uint64_t)b0 * J;
     uint32_t *const cnt = counts + 5ull * b0;
-    if (rows <= (uint32_t)kRegs) {
+    if (rows > 1 && rows <= (uint32_t)kRegs && (uint64_t)rows * n_buckets <= compute_units() && !dq::takes_lists(J, nb, max_width)) {
+      const auto kernel = rows > 16 ? (allow16 ? k_search_positions<true, true> : k_search_positions<false, true>)
+                                    : (allow16 ? k_search_positions<true, false> : k_search_positions<false, false>);
+      hipLaunchKernelGGL(kernel, dim3(rows, nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, widths + off, pos + off, cnt, announce);
+    } else if (rows <= (uint32_t)kRegs) {
       const dq_status st = dq::search(F + off, J, nb, max_code_bits, max_width, pos + off, cnt, announce, s);
       if (st != DQ_OK) return st;
       hipLaunchKernelGGL(k_alloc_positions, dim3(rows, nb), dim3(kAllocThreads), 0, s, F + off, J, allow16, cnt, widths + off, pos + off);

@@ -176,6 +176,14 @@ def test_allocate_narrow_value_ranges(dev):
     check_allocate(dev, F3, 4097, int(math.floor(prep.code_bits(4.0) * 4097)))   # 3 buckets, 5 rows each, ragged
 
 
+@pytest.mark.parametrize("J,nb", [(1, 3), (1024, 300), (1025, 128), (1025, 129), (16384, 16), (16384, 17), (15361, 2), (40000, 6), (65536, 4)])
+@pytest.mark.parametrize("max_width", [8, 16])
+def test_allocate_where_every_row_searches(dev, J, nb, max_width):
+    """One launch while there is a CU for every row of every bucket, or a row is a bucket; a search and its positions beyond."""
+    F = np.concatenate([lognormal_F(J + b, J, ties=min(J // 7, 40)) for b in range(nb)])
+    check_allocate(dev, F, J, int(math.floor(prep.code_bits(4.0 if max_width == 8 else 7.0) * J)), max_width=max_width)
+
+
 @pytest.mark.parametrize("J", [16384, 16385, 51200, 65536])       # from 16,385 on the search sets norms aside, up to 15 per thread
 @pytest.mark.parametrize("max_width", [8, 16])
 def test_allocate_at_the_edges_of_what_is_set_aside(dev, J, max_width):
@@ -246,7 +254,7 @@ def test_allocate_norms_close_together(dev, J, max_width):
             check_allocate(dev, F.astype(f32), J, int(bits * J), max_width=max_width)
 
 
-@pytest.mark.parametrize("J", [32767, 32768, 33791, 40001, 65535, 65536])   # below and from where rows list their norms; whole rows and a rest
+@pytest.mark.parametrize("J", [32767, 32768, 33791, 40959, 40960, 41983, 65535, 65536])   # below and from where rows list their norms; whole rows and a rest
 @pytest.mark.parametrize("kind", ["random", "sorted", "dense_end", "clustered", "aliased", "equal", "half"])
 def test_allocate_from_lists(dev, J, kind):
     """Rows list the norms around a threshold that a sample brackets: lists longer than what is asked for ahead, longer than their place (in the last row
