@@ -162,6 +162,24 @@ std::mutex g_tables_mutex;
 std::vector<Tables *> g_tables;
 uint64_t g_tables_clock = 0;
 
+// A copy behind the blob (the first `size` words) with entries {T[r], T[r+1]} of 8 bytes for the 8-bit levels, or for both sets, from the same places on, and
+// search tables that lead there.  At the top level, where nothing rounds up, the next one is infinite.
+void append_short_levels(std::vector<uint32_t> &blob, size_t size, bool both) {
+  std::vector<uint32_t> part(blob.begin(), blob.begin() + size);
+  auto shorten = [&](uint32_t tab, uint32_t pairs, uint32_t below) {
+    for (uint32_t e = 0; e < 2 * pairs; ++e) {
+      const uint32_t *entry = &blob[tab + 4 * e];
+      part[tab + 2 * e] = entry[0];
+      part[tab + 2 * e + 1] = entry[1] == 0x7F800000u ? entry[1] : entry[2];
+    }
+    for (size_t q = dq::kOffLut4 + 1; q < size; q += 2)  // (padding is zero)
+      if (blob[q] >= 4 * tab && blob[q] < 4 * below) part[q] = 4 * tab + (blob[q] - 4 * tab) / 2;
+  };
+  shorten(dq::kOffTab8, 127, dq::kOffLut4);
+  if (both) shorten(dq::kOffTab4, 7, dq::kOffDec8);
+  blob.insert(blob.end(), part.begin(), part.end());
+}
+
 // Builds the table blob and fills the fields of P that describe it.
 dq_status build_tables(double g4, double g8, dq::Params &P, std::vector<uint32_t> &blob) {
   memset(&P, 0, sizeof(P));
@@ -243,6 +261,8 @@ dq_status build_tables(double g4, double g8, dq::Params &P, std::vector<uint32_t
   // 64 KB of LDS with the parked draws, less the 3,200 bytes by which the level entries outgrew plain {T, D} pairs
   if (blob.size() * 4 > 60 * 1024 + 3200) return DQ_EUNSUPPORTED;
   P.blob_dwords = (uint32_t)blob.size();
+  append_short_levels(blob, P.blob_dwords, false);
+  append_short_levels(blob, P.blob_dwords, true);
   return DQ_OK;
 }
 

@@ -57,6 +57,8 @@ constexpr uint32_t kOffDec8 = 1848;    // 8-bit decode: 256 signed levels
 constexpr uint32_t kOffTab8 = 2104;    // 8-bit levels: 127 pairs of entries {T[r], D[r], T[r+1], r << 24}
 constexpr uint32_t kOffLut4 = 3120;    // search table of the 4-bit set: (2^m + 1) pairs {next level, address of the candidate's pair}
 
+// Behind the blob lie two more of the same layout for dq_thin.hip, with level entries {T[r], T[r+1]} of 8 bytes: of the 8-bit set, and of both.
+
 // Everything the kernels need besides the job: PRNG key, worker count, table blob.
 struct Params {
   const uint32_t *guard; // null, or a word the single-chunk kernels read first: if it is guard_call they do nothing (dq_bounds.hip)
@@ -95,9 +97,13 @@ struct Walk {
   uint32_t tile_sgs;         // super-groups of a wave's tile: 4 (dq_walk.hip), 2 or 1 (dq_thin.hip)
   uint32_t n_paths;
   uint32_t blocks, waves;    // grid, waves per block
-  uint32_t most_blocks;      // of such a grid
   uint32_t order;            // which share a wave takes (share_of): 0, kReversed, or the CUs that the shares are spread over
   uint32_t raw_beside;       // spread: CUs with a block more have the last shares in it, raw ones, not the first
+};
+// With what only the host needs.  (In the kernels' arguments two words more in front of Params cost a small replay 0.2 us of 5.3.)
+struct WalkGrid : Walk {
+  uint32_t most_blocks;      // of such a grid
+  bool full;                 // whether SIMDs have more than two waves
 };
 constexpr uint32_t kReversed = 0xFFFFFFFFu;
 struct WalkShare {
@@ -106,14 +112,14 @@ struct WalkShare {
 constexpr uint32_t kStackCoded = 1280, kStackRaw = 2048;  // bytes of a pending message per wave: codes and scale, or raw bf16
 uint32_t thin_lds(const Params &P, uint32_t stack_bytes);           // per block
 uint32_t thin_stack(uint32_t tile_sgs, uint32_t levels);            // per wave
-hipError_t launch_thin(dq_dtype dtype, bool tree, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W, const Params &P,
+hipError_t launch_thin(dq_dtype dtype, bool tree, const WalkPath *paths_dev, const WalkShare *shares_dev, const WalkGrid &W, const Params &P,
                        hipStream_t stream);
 // tiles: of one, two and four super-groups.  False: no launch fits
-bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const uint64_t tiles[3], Walk *W);
+bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const uint64_t tiles[3], WalkGrid *W);
 struct Costs { uint32_t of[4]; };
 Costs costs_of(dq_dtype dtype, bool tree, uint32_t n, uint32_t tile_sgs);  // of a tile, by width
 void split_walk(const WalkPath *paths_host, dq_dtype dtype, bool tree, const Walk &W, std::vector<WalkShare> *shares);
-hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths_dev, const WalkShare *shares_dev, const Walk &W,
+hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths_dev, const WalkShare *shares_dev, const WalkGrid &W,
                        const Params &P, hipStream_t stream);
 
 // Class counts that a search tells the host as soon as it has them (dq_bounds.hip): per bucket one word in pinned memory, counts of

@@ -61,7 +61,7 @@ struct Plan {
   uint32_t ring_message_steps = 0;  // steps 0 .. this-1 write messages
   // the whole schedule as one launch (dq_walk.hip): one path per (bucket, chunk), the workers' tensors
   bool walk = false, tree = false;
-  dq::Walk w = {};
+  dq::WalkGrid w = {};
   dq::MxWalk mx = {};
   std::vector<dq::WalkPath> paths;  // freed once they are on the device
   std::vector<dq::WalkShare> shares;
@@ -122,7 +122,7 @@ void plan_walk(const dq_ctx *ctx, const dq_replay_desc *d, const ChunkInfo *ci, 
   const uint32_t n = ctx->cfg.n_workers;
   const size_t es = elt_size(d->dtype);
   const uint64_t bucket_bytes = d->n_sg_bucket * 256 * es;
-  dq::Walk &w = plan->w;
+  dq::WalkGrid &w = plan->w;
   describe(n, d->topology, d->all_gather != 0, &w);
   plan->tree = d->topology == DQ_BUTTERFLY;
   bool raw = false;
@@ -898,7 +898,7 @@ void dq_replay_destroy(dq_replay *plan) {
 // recursive halving over 2 of 30,416 61.4 -> 42.2.
 namespace {
 struct WholePlan {
-  dq::Walk w = {};
+  dq::WalkGrid w = {};
   dq::Tables t = {};
   size_t paths = 0, shares = 0, grads = 0, mu = 0, F = 0, places = 0, counts = 0, mu_main = 0, origin = 0, bytes = 0;
 };
@@ -911,7 +911,7 @@ bool plan_whole(const dq_ctx *ctx, const dqx_whole *d, WholePlan *p) {
       d->max_code_bits < 2ull * J)
     return false;
   const uint32_t m = J / n;
-  dq::Walk &w = p->w;
+  dq::WalkGrid &w = p->w;
   describe(n, d->topology, d->all_gather != 0, &w);
   w.first_kept = n - 1;  // nobody asks for messages
   w.raw = d->max_width == 16;

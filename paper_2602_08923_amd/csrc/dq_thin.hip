@@ -91,6 +91,34 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);  // outside: the compiler knows what has to stand between it and a vector instruction's read
 }
 
+// What the search leads to: a level, the next one, and the step between them.  As 16 bytes, or as 8, T and the next T, with the step a subtraction.
+template <bool SHORT>
+struct Level {
+  u32x4 w;  // T, step, next T, index << (32 - width)
+  __device__ __forceinline__ void load(uint32_t sign, uint32_t pair) { w = lds_ld4(or_and(sign, 16u, pair)); }
+  __device__ __forceinline__ uint32_t here() const { return w.x; }
+  __device__ __forceinline__ uint32_t next() const { return w.z; }
+  __device__ __forceinline__ float step() const { return u2f(w.y); }
+  template <int B>
+  __device__ __forceinline__ uint32_t index() const { return w.w >> (32 - B); }
+};
+template <>
+struct Level<true> {
+  u32x2 w;
+  uint32_t at;
+  __device__ __forceinline__ void load(uint32_t sign, uint32_t pair) {
+    at = or_and(sign >> 1, 8u, pair);
+    w = lds_ld2(at);
+  }
+  __device__ __forceinline__ uint32_t here() const { return w.x; }
+  __device__ __forceinline__ uint32_t next() const { return w.y; }
+  __device__ __forceinline__ float step() const { return u2f(w.y) - u2f(w.x); }
+  template <int B>
+  __device__ __forceinline__ uint32_t index() const {  // pair r has the entries of r + 1 and r
+    return ((at - (B == 4 ? kOffTab4 : kOffTab8) * 4) >> 4) + 1 - (at >> 3 & 1u);
+  }
+};
+
 // What a wave holds of a tile before it walks it: where it is and the slices of its first hops.
 template <typename LT, int E>
 struct Start {
@@ -146,7 +174,7 @@ __device__ __forceinline__ TileBase<B> tile_base_here(const Job &job, const Tile
 }
 
 // B: 2, 4, 8, or 16 (raw: the message is the partial sum rounded to bf16)
-template <int B, typename LT, bool TREE, int E>
+template <int B, typename LT, bool TREE, int E, int SHORT>
 __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P, const Vec &V, const Walk &W, uint32_t park, uint32_t draws,
                                           uint32_t stack0, Start<LT, E> &x) {
   constexpr uint32_t kLanes = 16 / E, kSgs = E / 4, kHops = 32 / kSgs;  // lanes per group, super-groups per tile, hops per park
@@ -301,7 +329,8 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
             if constexpr (!kEarly) look_up_scale();
             float xs[E], u[E];
             u32x2 e[E];
-            u32x4 t[E];
+            constexpr bool kShort = B == 8 ? SHORT >= 1 : SHORT == 2;
+            Level<kShort> t[E];
 #pragma unroll
             for (int k = 0; k < E; ++k) {
               xs[k] = v[k] * inv;
@@ -314,7 +343,7 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
             }
             if constexpr (B != 2) {
 #pragma unroll
-              for (int k = 0; k < E; ++k) t[k] = lds_ld4(or_and(f2u(fabsf(xs[k]) - u2f(e[k].x)) >> 27, 16u, e[k].y));
+              for (int k = 0; k < E; ++k) t[k].load(f2u(fabsf(xs[k]) - u2f(e[k].x)) >> 27, e[k].y);
             }
             __builtin_amdgcn_sched_barrier(0);
             auto uniform = [&](int k) { return __builtin_fmaf((float)((gam[k >> 2] >> (8 * (k & 3))) & 0xFFu), V.s_n, u2f(offset.x)); };
@@ -336,16 +365,16 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
                 up[k] = u[k] < ax;
                 level[k] = u2f(or_and(f2u(xs[k]), V.top, f2u(up[k] ? 1.0f : 0.0f)));
               } else {
-                up[k] = __builtin_fmaf(u[k], u2f(t[k].y), u2f(t[k].x)) < ax;
-                level[k] = u2f(or_and(f2u(xs[k]), V.top, up[k] ? t[k].z : t[k].x));
+                up[k] = __builtin_fmaf(u[k], t[k].step(), u2f(t[k].here())) < ax;
+                level[k] = u2f(or_and(f2u(xs[k]), V.top, up[k] ? t[k].next() : t[k].here()));
               }
             }
             // A level's fourth word counts as read here: the compiler would take its register for another purpose while the read is under way, and wait
             // for the first entry's level before it asks for the others' (ring of 16, 496 super-groups, 10.0 us instead of 9.5; a chain of 100 of 600 in fp32
             // 43.4 and 39.9).  With eight entries per lane there are no registers for that: halving over 8 of 5,600 in fp32 14.8 instead of 13.1.
-            if constexpr (B != 2 && E == 4) {
+            if constexpr (B != 2 && !kShort && E == 4) {
 #pragma unroll
-              for (int k = 0; k < E; ++k) asm volatile("" ::"v"(t[k].w));
+              for (int k = 0; k < E; ++k) asm volatile("" ::"v"(t[k].w.w));
             }
             if (keep) {
               const TileBase<B> tb = tile_base_here<B>(job, pos);
@@ -354,7 +383,7 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
               uint64_t word = 0;
 #pragma unroll
               for (int k = E - 1; k >= 0; --k) {
-                const uint32_t index = B == 2 ? 0u : t[k].w >> (32 - B);
+                const uint32_t index = B == 2 ? 0u : t[k].template index<B>();
                 word = (word << B) | (f2u(xs[k]) >> 31 << (B - 1)) | (rg != 0.0f ? index + (up[k] ? 1u : 0u) : 0u);
               }
               uint8_t *cp = out + tb.code_off + lg * (2 * B) + q * (E * B / 8);
@@ -397,7 +426,14 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
   for (int h = 0; h < E / 4; ++h) gst_once<f32x4>(out + 4 * h, f32x4{v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]});
 }
 
-template <typename LT, bool TREE, int E>
+// SHORT: which levels are 8 bytes, by the number of the tables behind the blob: 1 the 8-bit ones, 2 both.
+//   8-bit : a wave's lanes read as many of the set's 254 entries at a time as the LDS has room for; with four waves per SIMD it was busy two thirds of the time
+//           (256 workers, 4,096 super-groups of 2 to 16 bits 164.5 -> 159.4 us; 32 of 8,000 at 6 bits 39.6 -> 38.9, in fp32 64 of 4,992 65.9 ->
+//           64.4).  Not in bf16 rings and chains of up to two waves per SIMD, where the subtraction is on the one wave's way (100 of 2,000 41.0 -> 41.7).
+//   4-bit : 14 entries, read by many lanes at once whatever their size; but halvings with tiles of two need no scratch memory so (over 16 of 5,600 23.1 -> 19.5, over
+//           32 of 4,096 27.0 -> 23.5, over 64 62.0 -> 56.5), and bf16 rings with tiles of two less of it (100 of 6,000 at 5 bits 86.5, with the 8-bit ones alone 87.8).
+//   fp32 rings with tiles of two have neither (16 of 4,992 20.0; 20.3 with any).
+template <typename LT, bool TREE, int E, int SHORT>
 __global__ __launch_bounds__(kThinWaves * 64) __attribute__((amdgpu_waves_per_eu((E == 4 || sizeof(LT) == 2 ? 4 : 3)))) void k_thin(
     const WalkPath *paths, const WalkShare *shares, Walk W, Params P) {
   extern __shared__ uint4 lds_raw[];
@@ -413,7 +449,7 @@ __global__ __launch_bounds__(kThinWaves * 64) __attribute__((amdgpu_waves_per_eu
     path = table_entry(paths, at.path);
     x = start_tile<LT, TREE, E>(path, W, at.tile);
   }
-  copy_tables(lds, P, kOffTab4);  // nothing is decoded from codes
+  copy_tables(lds, P.blob + SHORT * P.blob_dwords, P, kOffTab4);  // nothing is decoded from codes
   __syncthreads();
   if (!any) return;
   const uint32_t draws = kOffDec2 * 4 + wave * kThinDraws, park = P.blob_dwords * 4 + wave * kThinPark;
@@ -421,10 +457,10 @@ __global__ __launch_bounds__(kThinWaves * 64) __attribute__((amdgpu_waves_per_eu
   lds_st4(park + 640, u32x4{0, 0, 0, 0});
   const Vec V(P);
   for (;;) {
-    if (x.pos.wi == 0) walk_thin<2, LT, TREE, E>(path, P, V, W, park, draws, stack, x);
-    else if (x.pos.wi == 1) walk_thin<4, LT, TREE, E>(path, P, V, W, park, draws, stack, x);
-    else if (x.pos.wi == 2) walk_thin<8, LT, TREE, E>(path, P, V, W, park, draws, stack, x);
-    else walk_thin<16, LT, TREE, E>(path, P, V, W, park, draws, stack, x);
+    if (x.pos.wi == 0) walk_thin<2, LT, TREE, E, SHORT>(path, P, V, W, park, draws, stack, x);
+    else if (x.pos.wi == 1) walk_thin<4, LT, TREE, E, SHORT>(path, P, V, W, park, draws, stack, x);
+    else if (x.pos.wi == 2) walk_thin<8, LT, TREE, E, SHORT>(path, P, V, W, park, draws, stack, x);
+    else walk_thin<16, LT, TREE, E, SHORT>(path, P, V, W, park, draws, stack, x);
     ++at.tile;
     uint32_t tiles = 0;
 #pragma unroll
@@ -437,19 +473,28 @@ __global__ __launch_bounds__(kThinWaves * 64) __attribute__((amdgpu_waves_per_eu
 }
 
 template <typename LT, bool TREE>
-hipError_t go_thin(const WalkPath *paths, const WalkShare *shares, const Walk &W, const Params &P, hipStream_t s) {
+constexpr int kShortPairs = TREE || sizeof(LT) == 2 ? 2 : 0;  // tiles of two
+template <bool TREE>
+constexpr int kShortSingles = TREE ? 2 : 1;
+template <typename LT, bool TREE>
+hipError_t go_thin(const WalkPath *paths, const WalkShare *shares, const WalkGrid &W, const Params &P, hipStream_t s) {
   const uint32_t lds = thin_lds(P, W.stack_bytes);
-  if (W.tile_sgs == 1) hipLaunchKernelGGL((k_thin<LT, TREE, 4>), dim3(W.blocks), dim3(kThinWaves * 64), lds, s, paths, shares, W, P);
-  else hipLaunchKernelGGL((k_thin<LT, TREE, 8>), dim3(W.blocks), dim3(kThinWaves * 64), lds, s, paths, shares, W, P);
+  auto kernel = k_thin<LT, TREE, 8, kShortPairs<LT, TREE>>;
+  if (W.tile_sgs == 1) kernel = k_thin<LT, TREE, 4, kShortSingles<TREE>>;
+  if constexpr (!TREE && sizeof(LT) == 2)
+    if (W.tile_sgs == 1 && !W.full) kernel = k_thin<LT, TREE, 4, 0>;
+  hipLaunchKernelGGL(kernel, dim3(W.blocks), dim3(kThinWaves * 64), lds, s, paths, shares, W, P);
   return hipGetLastError();
 }
 
 template <typename LT>
 hipError_t static_lds_of(size_t *bytes) {
-  hipError_t e = add_static_lds(k_thin<LT, false, 4>, bytes);
-  if (e == hipSuccess) e = add_static_lds(k_thin<LT, false, 8>, bytes);
-  if (e == hipSuccess) e = add_static_lds(k_thin<LT, true, 4>, bytes);
-  return e != hipSuccess ? e : add_static_lds(k_thin<LT, true, 8>, bytes);
+  hipError_t e = add_static_lds(k_thin<LT, false, 4, kShortSingles<false>>, bytes);
+  if constexpr (sizeof(LT) == 2)
+    if (e == hipSuccess) e = add_static_lds(k_thin<LT, false, 4, 0>, bytes);
+  if (e == hipSuccess) e = add_static_lds(k_thin<LT, false, 8, kShortPairs<LT, false>>, bytes);
+  if (e == hipSuccess) e = add_static_lds(k_thin<LT, true, 4, kShortSingles<true>>, bytes);
+  return e != hipSuccess ? e : add_static_lds(k_thin<LT, true, 8, kShortPairs<LT, true>>, bytes);
 }
 
 }  // namespace
@@ -462,7 +507,7 @@ hipError_t thin_static_lds(size_t *bytes) {
 uint32_t thin_lds(const Params &P, uint32_t stack_bytes) { return P.blob_dwords * 4 + kThinWaves * (kThinPark + stack_bytes); }
 uint32_t thin_stack(uint32_t tile_sgs, uint32_t levels) { return levels * (tile_sgs == 1 ? kThinStack<4> : kThinStack<8>); }
 
-hipError_t launch_thin(dq_dtype dtype, bool tree, const WalkPath *paths, const WalkShare *shares, const Walk &W, const Params &P, hipStream_t s) {
+hipError_t launch_thin(dq_dtype dtype, bool tree, const WalkPath *paths, const WalkShare *shares, const WalkGrid &W, const Params &P, hipStream_t s) {
   if (dtype == DQ_F32) return tree ? go_thin<float, true>(paths, shares, W, P, s) : go_thin<float, false>(paths, shares, W, P, s);
   return tree ? go_thin<uint16_t, true>(paths, shares, W, P, s) : go_thin<uint16_t, false>(paths, shares, W, P, s);
 }

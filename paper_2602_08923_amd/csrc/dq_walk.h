@@ -67,17 +67,17 @@ __device__ __forceinline__ T table_entry(const T *table, uint32_t i) {
 // The tables from dword `first` on, and the reciprocals in front, to their places in LDS, in one trip to memory: whatever widths the
 // chunks have.  (Range by range, those of widths that some chunk has, it was a trip each: 8 workers' ring of 8,192 super-groups 19.2 us
 // instead of 17.4, 4 workers' fp32 ring of 4,096 9.1 instead of 8.3, 25 MB through a ring of eight 53 instead of 52.)
-__device__ __forceinline__ void copy_tables(uint32_t *lds, const Params &P, uint32_t first) {
+__device__ __forceinline__ void copy_tables(uint32_t *lds, const uint32_t *blob, const Params &P, uint32_t first) {
   constexpr uint32_t kTogether = 4, kRec = kOffDec2 / 4;  // 16-byte words per thread requested at once; of the reciprocals
   const uint32_t words = P.blob_dwords / 4, lo = first / 4 + threadIdx.x;
   uint4 rec, part[kTogether];
-  if (threadIdx.x < kRec) rec = gld16(&P.blob[threadIdx.x * 4]);
+  if (threadIdx.x < kRec) rec = gld16(&blob[threadIdx.x * 4]);
 #pragma unroll
-  for (uint32_t k = 0; k < kTogether; ++k) part[k] = gld16(&P.blob[min(lo + k * blockDim.x, words - 1) * 4]);
+  for (uint32_t k = 0; k < kTogether; ++k) part[k] = gld16(&blob[min(lo + k * blockDim.x, words - 1) * 4]);
   if (threadIdx.x < kRec) *reinterpret_cast<uint4 *>(&lds[threadIdx.x * 4]) = rec;
 #pragma unroll
   for (uint32_t k = 0; k < kTogether; ++k) *reinterpret_cast<uint4 *>(&lds[min(lo + k * blockDim.x, words - 1) * 4]) = part[k];
-  for (uint32_t i = lo + kTogether * blockDim.x; i < words; i += blockDim.x) *reinterpret_cast<uint4 *>(&lds[i * 4]) = gld16(&P.blob[i * 4]);
+  for (uint32_t i = lo + kTogether * blockDim.x; i < words; i += blockDim.x) *reinterpret_cast<uint4 *>(&lds[i * 4]) = gld16(&blob[i * 4]);
 }
 
 }  // namespace

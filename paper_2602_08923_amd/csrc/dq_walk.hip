@@ -323,7 +323,7 @@ __global__ __launch_bounds__((TREE ? 512 : 256)) __attribute__((amdgpu_waves_per
   const uint32_t waves = blockDim.x / 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t v = __builtin_amdgcn_readfirstlane(share_of<TREE>(W, wave, waves));
   const WalkShare from = table_entry(shares, v), to = table_entry(shares, v + 1);
-  copy_tables(lds, P, TREE ? kOffDec2 : kOffTab4);  // a ring or chain never decodes from codes
+  copy_tables(lds, P.blob, P, TREE ? kOffDec2 : kOffTab4);  // a ring or chain never decodes from codes
   __syncthreads();
   Areas A;
   const uint32_t end = P.blob_dwords * 4;
@@ -370,7 +370,7 @@ hipError_t walk_static_lds(size_t *bytes) {
 }
 
 // The launch of W's schedule with tiles of W->tile_sgs super-groups.  *resident: waves that a CU holds at once.  False: no block fits.
-static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, uint64_t tiles, Walk *W, uint32_t *resident) {
+static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, uint64_t tiles, WalkGrid *W, uint32_t *resident) {
   constexpr uint32_t kLds = 160u * 1024, kGranule = 1280;  // LDS is given out in 128 pieces
   uint32_t lds, most;  // most: waves that fit a CU's registers
   if (W->tile_sgs < kWaveSGs) {
@@ -398,6 +398,7 @@ static bool grid_of_tiles(const Params &P, bool f32, bool tree, uint32_t n_cu, u
   const uint64_t needed = (tiles + W->waves - 1) / W->waves, blocks = (uint64_t)n_cu * per_cu;
   W->blocks = (uint32_t)(needed < blocks ? needed : blocks);
   W->most_blocks = (uint32_t)blocks;
+  W->full = W->blocks * W->waves > 8 * n_cu;
   return true;
 }
 
@@ -449,16 +450,16 @@ static uint32_t tile_for(uint32_t n, bool f32, bool tree, bool all_gather, uint3
   return per_cu <= one ? 1 : per_cu <= two ? 2 : kWaveSGs;
 }
 
-bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const uint64_t tiles_of[3], Walk *W) {
+bool grid_walk(const Params &P, dq_dtype dtype, bool tree, uint32_t n_cu, const uint64_t tiles_of[3], WalkGrid *W) {
   const bool f32 = dtype == DQ_F32;
   const uint64_t super_groups = tiles_of[0];
   if (super_groups == 0) return false;
   const uint32_t wanted = tile_for(W->n, f32, tree, W->encodes == W->n, n_cu, super_groups);
-  Walk best = *W;
+  WalkGrid best = *W;
   uint64_t best_time = 0;
   bool found = false;
   for (uint32_t sgs = kWaveSGs; sgs >= (wanted ? wanted : 1); sgs /= 2) {  // the wanted one, or the next wider that fits
-    Walk w = *W;
+    WalkGrid w = *W;
     w.tile_sgs = sgs;
     uint32_t resident = 0;
     const uint64_t tiles = tiles_of[sgs / 2];
@@ -625,7 +626,7 @@ void split_walk(const WalkPath *paths, dq_dtype dtype, bool tree, const Walk &W,
   while (share != end + 1) *share++ = WalkShare{W.n_paths, 0};
 }
 
-hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths, const WalkShare *shares, const Walk &W,
+hipError_t launch_walk(dq_dtype dtype, bool tree, bool means, const WalkPath *paths, const WalkShare *shares, const WalkGrid &W,
                        const Params &P, hipStream_t s) {
   if (W.tile_sgs < kWaveSGs) return launch_thin(dtype, tree, paths, shares, W, P, s);
   const bool f32 = dtype == DQ_F32;
@@ -642,7 +643,7 @@ extern "C" void dqx_split(const uint32_t *n_sg, uint32_t n_paths, uint32_t n_wor
                           uint32_t waves, uint32_t *shares) {
   std::vector<dq::WalkPath> paths(n_paths, dq::WalkPath{});
   for (uint32_t p = 0; p < n_paths; ++p) memcpy(paths[p].job.n_sg, n_sg + 4 * (size_t)p, 16);
-  dq::Walk W = {};
+  dq::WalkGrid W = {};
   W.n = n_workers;
   W.n_paths = n_paths;
   W.tile_sgs = tile_sgs;

@@ -119,6 +119,15 @@ def test_whole_replay_of_few_super_groups_per_cu_equals_its_steps(dev, topology,
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("all_gather", [False, True])
+@pytest.mark.parametrize("topology,n,J", [("ring", 4, 2044), ("ring", 4, 2048), ("ring", 4, 2052), ("chain", 5, 2049), ("ring", 12, 5160), ("butterfly", 16, 2048),
+                                          ("butterfly", 16, 5632), ("butterfly", 32, 4096)])
+def test_whole_replay_with_short_and_long_level_entries_equals_its_steps(dev, topology, n, J, all_gather, dtype):
+    """Rings and chains on both sides of two waves per SIMD, tiles of one and of two, all four widths."""
+    test_whole_replay_equals_its_steps(dev, topology, n, [[J // 4, J // 4, J - J // 4 * 2 - 77, 77]], all_gather, True, dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("topology,J", [("ring", 64), ("butterfly", 64), ("ring", 8192), ("butterfly", 8192)])   # one and four super-groups per tile
 def test_whole_replay_of_extreme_magnitudes_equals_its_steps(dev, topology, J, dtype):
     """Groups whose maximum's reciprocal is denormal, groups too small for a scale beside ones that are not, super-groups encoded as zero."""
