@@ -394,7 +394,7 @@ def allocate_ahead(F, n_sg_per_bucket, max_code_bits, max_width=8):
 
 
 def allreduce_whole(ctx, tensors, n_sg_per_bucket, topology, max_code_bits, max_width, all_gather, subtract_mean):
-    """The statistics, allocation and replay of a simulated all-reduce on the workers' original tensors, enqueued as three launches (four or five for several or large buckets) without a wait:
+    """The statistics, allocation and replay of a simulated all-reduce on the workers' original tensors, enqueued as three to five launches without a wait:
     (the sum in the original order, a function that waits for widths_of_buckets), or None for calls that it is not made for."""
     got = _native().whole(ctx.h, tensors, n_sg_per_bucket, topology, int(max_code_bits), int(max_width), int(bool(all_gather)), int(bool(subtract_mean)))
     if got is None:

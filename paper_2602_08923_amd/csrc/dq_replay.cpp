@@ -993,11 +993,11 @@ dq_status dqx_whole_run(const dq_ctx *ctx, const dqx_whole *desc, const void *co
   p.w.grads = grads;
   bool searched = false;
   dq_status st = *ticket ? dq::stats_all(tensors, ctx->cfg.n_workers, desc->dtype, (uint64_t)J * nb, floats(p.mu), floats(p.F), grads, s) : DQ_EINVAL;
-  const bool both = dq::takes_search_arrange(J, nb, desc->max_width);
+  const bool both = dq::takes_search_arrange(J, nb);
   if (st == DQ_OK && both) {
     searched = true;
-    st = dq::search_arrange(floats(p.F), means ? floats(p.mu) : nullptr, J, desc->max_code_bits, desc->max_width, means ? floats(p.mu_main) : nullptr,
-                            words(p.origin), announce, p.t, s);
+    st = dq::search_arrange(floats(p.F), means ? floats(p.mu) : nullptr, J, desc->max_code_bits, desc->max_width, words(p.places),
+                            means ? floats(p.mu_main) : nullptr, words(p.origin), announce, p.t, s);
   } else if (st == DQ_OK) {
     searched = true;
     st = dq::search(floats(p.F), J, nb, desc->max_code_bits, desc->max_width, words(p.places), words(p.counts), announce, s);

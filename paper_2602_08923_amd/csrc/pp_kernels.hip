@@ -762,8 +762,9 @@ __device__ __forceinline__ RowPlaces row_places(uint32_t J, const SearchSpace &S
   return p;
 }
 // Widths and positions by a block that has searched for itself: its row's super-group of norm f, one per thread.
+// from_end: the last row, whose places end where the classes do (search_lists does not count it by itself).
 __device__ __forceinline__ Placed place_searched(float f, bool there, uint32_t row, uint32_t pattern, bool allow16, const RowPlaces &p,
-                                                 uint32_t (*mine_w)[4]) {
+                                                 uint32_t (*mine_w)[4], bool from_end = false) {
   const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t first[4];  // as lane `row` says it
 #pragma unroll
@@ -778,6 +779,11 @@ __device__ __forceinline__ Placed place_searched(float f, bool there, uint32_t r
   uint32_t at = k == 0 ? first[0] : k == 1 ? first[1] : k == 2 ? first[2] : first[3];
   __syncthreads();
   if (k == 4) return Placed{4u, 0u};
+  if (from_end) {
+    at = 0;
+    for (uint32_t c = 0; c < 4; ++c) at += c <= k ? p.n_class[c] : 0u;
+    for (uint32_t w = 0; w < kAllocWaves; ++w) at -= mine_w[w][k];
+  }
   for (uint32_t w = 0; w < wave; ++w) at += mine_w[w][k];
   const uint64_t mine = k == 0 ? b[0] : (k == 1 ? b[1] : (k == 2 ? b[2] : b[3]));
   return Placed{k, at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u))};
@@ -849,7 +855,8 @@ __global__ void __launch_bounds__(kAllocThreads) k_search_positions(const float 
 // like norms 18.8 -> 17.6, within a factor of two of each other 22.4 -> 20.3, within a tenth 27.2 -> 27.6, equal 56.8 -> 51.8 (a bucket's statistics and
 // allocation 76.1 -> 70.4).  Not with 16-bit widths, whose brackets are wider (20.9 -> 21.2), nor below some 41,000 norms, where all in one launch, which the host enqueues
 // sooner, is the better (statistics and allocation, one launch and listed: 2 workers' 33,000 28.2 and 31.0, 40,000 30.6 and 30.7, 4 workers' 50,000 44.9 and 41.4; all-reduces
-// over 6 of 30,000 62.5 and 64.2, over 8 of 42,664 88.9 and 86.9).
+// over 6 of 30,000 62.5 and 64.2, over 8 of 42,664 88.9 and 86.9, the listed ones with k_arrange apart, 1.5 more than now).  An all-reduce of one bucket has
+// the second part in every block of its next launch (k_search_arrange).
 constexpr uint32_t kSample = 8192, kFine = 18, kFineBins = 8192;  // bins of 2^18 patterns: 0x7F8 << 2 of them are finite
 struct ListHead {
   uint32_t n;                        // events, or kTooLong: more than the list holds
@@ -1335,13 +1342,16 @@ __global__ void __launch_bounds__(kAllocThreads) k_arrange(const float *F_all, c
   }
 }
 
-// The search and k_arrange in one launch, for one bucket that is not listed: every block searches for itself, which costs nothing but a CU that has
+// The search and k_arrange in one launch, for one bucket: every block searches for itself, which costs nothing but a CU that has
 // nothing else to do, and goes on with what it has in LDS.  Against two launches, a launch's start and the trips of places and counts to memory and back
 // are fewer: 8 workers' 8,192 super-groups 8.2 and 5.2 us -> 9.6, 6 workers' 48 6.9 and 5.1 -> 7.8 (all-reduces 36.1 -> 31.9, 23.2 -> 21.9; 16 workers' halving
 // of 1,312 31.5 -> 27.9, 3 workers' 15,000 30.6 -> 27.4, 4 workers' 17,980 36.5 -> 32.5).  What bounds it is the search's chain, whose every piece of code is fetched and run once.
-template <bool ALLOW16, bool ASIDE>
-__global__ void __launch_bounds__(kAllocThreads) k_search_arrange(const float *F, const float *mu, uint32_t J, uint64_t max_code_bits, float *mu_main,
-                                                                  uint32_t *origin, dq::Announce announce, dq::Tables T) {
+// LISTED: behind k_list, against k_search_listed and k_arrange as launches of their own (all-reduces over 8 of 42,664 94.1 -> 92.6 us, 6 of 48,000 82.1 -> 80.5,
+// halving over 4 of 65,536 86.1 -> 84.5, 2 of 40,960 44.8 -> 43.4).
+template <bool ALLOW16, bool ASIDE, bool LISTED>
+__global__ void __launch_bounds__(kAllocThreads) k_search_arrange(const float *F, const float *mu, const uint32_t *lists, uint32_t J, uint64_t max_code_bits,
+                                                                  float *mu_main, uint32_t *origin, dq::Announce announce, dq::Tables T) {
+  static_assert(!LISTED || (ASIDE && !ALLOW16), "");
   __shared__ SearchSpace S;
   __shared__ uint32_t mine_w[kAllocWaves][4];
   __shared__ TableSpace space;
@@ -1349,14 +1359,16 @@ __global__ void __launch_bounds__(kAllocThreads) k_search_arrange(const float *F
   const bool tables = blockIdx.x < parts;
   const uint32_t row = tables ? 0u : blockIdx.x - parts, j = row * kAllocThreads + tid;
   const float f = gld<float>(F + min(j, J - 1)), m = mu ? gld<float>(mu + min(j, J - 1)) : 0.0f;
-  const uint32_t pattern = search_block<ALLOW16, ASIDE>(F, J, max_code_bits, S);
+  uint32_t pattern;
+  if constexpr (LISTED) pattern = search_lists(F, lists, J, max_code_bits, S);
+  else pattern = search_block<ALLOW16, ASIDE>(F, J, max_code_bits, S);
   const RowPlaces p = row_places(J, S);
   if (tables) {
     if (blockIdx.x == 0 && tid == 0) tell(p.n_class, announce, 0);
     make_tables(T, [&](uint32_t, int w) { return p.n_class[w]; }, blockIdx.x, space);
     return;
   }
-  const Placed x = place_searched(f, j < J, row, pattern, ALLOW16, p, mine_w);
+  const Placed x = place_searched(f, j < J, row, pattern, ALLOW16, p, mine_w, LISTED && row == J / kAllocThreads);
   if (x.k == 4) return;
   if (mu) gst<float>(mu_main + x.at, x.k == 3 ? 0.0f : m);
   gst<uint32_t>(origin + x.at, j);
@@ -1663,15 +1675,21 @@ dq_status search(const float *F, uint32_t J, uint32_t n_buckets, uint64_t max_co
   return launched();
 }
 
-bool takes_search_arrange(uint32_t J, uint32_t n_buckets, uint32_t max_width) {
-  return n_buckets == 1 && J <= kMostSearched && !takes_lists(J, 1, max_width);
+bool takes_search_arrange(uint32_t J, uint32_t n_buckets) {
+  return n_buckets == 1 && J <= kMostSearched;
 }
-dq_status search_arrange(const float *F, const float *mu, uint32_t J, uint64_t max_code_bits, uint32_t max_width, float *mu_main, uint32_t *origin,
-                         Announce announce, const Tables &tables, hipStream_t s) {
-  const auto kernel = J > 16u * kAllocThreads ? (max_width == 16 ? k_search_arrange<true, true> : k_search_arrange<false, true>)
-                                              : (max_width == 16 ? k_search_arrange<true, false> : k_search_arrange<false, false>);
-  hipLaunchKernelGGL(kernel, dim3((J + kAllocThreads - 1) / kAllocThreads + table_parts(tables)), dim3(kAllocThreads), 0, s, F, mu, J, max_code_bits, mu_main,
-                     origin, announce, tables);
+dq_status search_arrange(const float *F, const float *mu, uint32_t J, uint64_t max_code_bits, uint32_t max_width, uint32_t *places, float *mu_main,
+                         uint32_t *origin, Announce announce, const Tables &tables, hipStream_t s) {
+  auto kernel = J > 16u * kAllocThreads ? (max_width == 16 ? k_search_arrange<true, true, false> : k_search_arrange<false, true, false>)
+                                        : (max_width == 16 ? k_search_arrange<true, false, false> : k_search_arrange<false, false, false>);
+  if (takes_lists(J, 1, max_width)) {
+    hipLaunchKernelGGL(k_list, dim3(J / kAllocThreads), dim3(kAllocThreads), 0, s, F, J, max_code_bits, places);
+    const dq_status st = launched();
+    if (st != DQ_OK) return st;
+    kernel = k_search_arrange<false, true, true>;
+  }
+  hipLaunchKernelGGL(kernel, dim3((J + kAllocThreads - 1) / kAllocThreads + table_parts(tables)), dim3(kAllocThreads), 0, s, F, mu, places, J, max_code_bits,
+                     mu_main, origin, announce, tables);
   return launched();
 }
 

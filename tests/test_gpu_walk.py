@@ -404,6 +404,12 @@ def test_an_allreduce_enqueued_whole_equals_its_steps(dev, monkeypatch, topology
     assert enqueued == [n <= 256 and n * nb <= 1024 and J <= 65536 and nb <= 511] * 4
 
 
+@pytest.mark.parametrize("topology,n,J", [("ring", 8, 42664), ("ring", 3, 45057), ("butterfly", 2, 40960), ("ring", 7, 65534)])
+def test_an_allreduce_of_listed_norms_enqueued_whole_equals_its_steps(dev, monkeypatch, topology, n, J):
+    """Every block goes on from the rows' lists: a last row of one, of many and none behind the last list; norms alike and all equal."""
+    test_an_allreduce_enqueued_whole_equals_its_steps(dev, monkeypatch, topology, n, J, 1, 4.2, 8, torch.bfloat16)
+
+
 class Miscounted(list):
     """A list that another thread makes longer or shorter once its length has been asked for."""
     def __init__(self, items, count):
