@@ -857,6 +857,8 @@ __global__ void __launch_bounds__(kAllocThreads) k_search_positions(const float 
 // sooner, is the better (statistics and allocation, one launch and listed: 2 workers' 33,000 28.2 and 31.0, 40,000 30.6 and 30.7, 4 workers' 50,000 44.9 and 41.4; all-reduces
 // over 6 of 30,000 62.5 and 64.2, over 8 of 42,664 88.9 and 86.9, the listed ones with k_arrange apart, 1.5 more than now).  An all-reduce of one bucket has
 // the second part in every block of its next launch (k_search_arrange).
+// What it costs: on a second stream beside a replay that fills the chip, blocks on 50 CUs hold up more of the replay's waves than one does (8 workers' 25 MB: 53 us
+// alone, 65.4 with a search by one block beside it, 70 to 74 so).
 constexpr uint32_t kSample = 8192, kFine = 18, kFineBins = 8192;  // bins of 2^18 patterns: 0x7F8 << 2 of them are finite
 struct ListHead {
   uint32_t n;                        // events, or kTooLong: more than the list holds
