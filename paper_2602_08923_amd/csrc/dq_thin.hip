@@ -429,7 +429,10 @@ __device__ __forceinline__ void walk_thin(const WalkPath &path, const Params &P,
 // SHORT: which levels are 8 bytes, by the number of the tables behind the blob: 1 the 8-bit ones, 2 both.
 //   8-bit : a wave's lanes read as many of the set's 254 entries at a time as the LDS has room for; with four waves per SIMD it was busy two thirds of the time
 //           (256 workers, 4,096 super-groups of 2 to 16 bits 164.5 -> 159.4 us; 32 of 8,000 at 6 bits 39.6 -> 38.9, in fp32 64 of 4,992 65.9 ->
-//           64.4).  Not in bf16 rings and chains of up to two waves per SIMD, where the subtraction is on the one wave's way (100 of 2,000 41.0 -> 41.7).
+//           64.4).  Not in bf16 rings and chains of up to two waves per SIMD, where the subtraction is on the one wave's way (100 of 2,000 41.0 -> 41.7), nor in
+//           any of up to eight workers, which have too few hops for the fewer conflicts to count (us of a ring, long -> short: bf16, 4 of 3,584 8.2 -> 8.3, 8 of them
+//           10.6 -> 10.8; fp32, 3 of 1,024 5.27 -> 5.36.  Means over three mixtures and up to 16 super-groups per CU, over 4, 8, 12 and 16 workers: bf16 with more than two
+//           waves per SIMD 1.5 and 0.8 % longer, 0.2 and 1.1 % less; fp32 0.6 and 0.3 longer, 0.3 and 0.8 less).
 //   4-bit : 14 entries, read by many lanes at once whatever their size; but halvings with tiles of two need no scratch memory so (over 16 of 5,600 23.1 -> 19.5, over
 //           32 of 4,096 27.0 -> 23.5, over 64 62.0 -> 56.5), and bf16 rings with tiles of two less of it (100 of 6,000 at 5 bits 86.5, with the 8-bit ones alone 87.8).
 //   fp32 rings with tiles of two have neither (16 of 4,992 20.0; 20.3 with any).
@@ -476,13 +479,14 @@ template <typename LT, bool TREE>
 constexpr int kShortPairs = TREE || sizeof(LT) == 2 ? 2 : 0;  // tiles of two
 template <bool TREE>
 constexpr int kShortSingles = TREE ? 2 : 1;
+constexpr uint32_t kFewHops = 8;  // of a ring or chain whose levels all have 16 bytes
 template <typename LT, bool TREE>
 hipError_t go_thin(const WalkPath *paths, const WalkShare *shares, const WalkGrid &W, const Params &P, hipStream_t s) {
   const uint32_t lds = thin_lds(P, W.stack_bytes);
   auto kernel = k_thin<LT, TREE, 8, kShortPairs<LT, TREE>>;
   if (W.tile_sgs == 1) kernel = k_thin<LT, TREE, 4, kShortSingles<TREE>>;
-  if constexpr (!TREE && sizeof(LT) == 2)
-    if (W.tile_sgs == 1 && !W.full) kernel = k_thin<LT, TREE, 4, 0>;
+  if constexpr (!TREE)
+    if (W.tile_sgs == 1 && (W.n <= kFewHops || (sizeof(LT) == 2 && !W.full))) kernel = k_thin<LT, TREE, 4, 0>;
   hipLaunchKernelGGL(kernel, dim3(W.blocks), dim3(kThinWaves * 64), lds, s, paths, shares, W, P);
   return hipGetLastError();
 }
@@ -490,8 +494,7 @@ hipError_t go_thin(const WalkPath *paths, const WalkShare *shares, const WalkGri
 template <typename LT>
 hipError_t static_lds_of(size_t *bytes) {
   hipError_t e = add_static_lds(k_thin<LT, false, 4, kShortSingles<false>>, bytes);
-  if constexpr (sizeof(LT) == 2)
-    if (e == hipSuccess) e = add_static_lds(k_thin<LT, false, 4, 0>, bytes);
+  if (e == hipSuccess) e = add_static_lds(k_thin<LT, false, 4, 0>, bytes);
   if (e == hipSuccess) e = add_static_lds(k_thin<LT, false, 8, kShortPairs<LT, false>>, bytes);
   if (e == hipSuccess) e = add_static_lds(k_thin<LT, true, 4, kShortSingles<true>>, bytes);
   return e != hipSuccess ? e : add_static_lds(k_thin<LT, true, 8, kShortPairs<LT, true>>, bytes);

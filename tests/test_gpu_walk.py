@@ -128,6 +128,13 @@ def test_whole_replay_with_short_and_long_level_entries_equals_its_steps(dev, to
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("topology,n,J", [("ring", 8, 2056), ("ring", 9, 2043), ("ring", 9, 2052), ("chain", 8, 2100), ("chain", 9, 2100)])
+def test_whole_replay_on_both_sides_of_eight_workers_equals_its_steps(dev, topology, n, J, dtype):
+    """Level entries of 16 bytes up to eight workers, of 8 from nine on where SIMDs have more than two waves, in fp32 always."""
+    test_whole_replay_equals_its_steps(dev, topology, n, [[J // 4, J // 4, J - J // 4 * 2 - 77, 77]], True, True, dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("topology,J", [("ring", 64), ("butterfly", 64), ("ring", 8192), ("butterfly", 8192)])   # one and four super-groups per tile
 def test_whole_replay_of_extreme_magnitudes_equals_its_steps(dev, topology, J, dtype):
     """Groups whose maximum's reciprocal is denormal, groups too small for a scale beside ones that are not, super-groups encoded as zero."""
