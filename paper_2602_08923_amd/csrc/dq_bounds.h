@@ -71,6 +71,8 @@ struct dqx_tables {
   uint32_t blocks, waves, tile_sgs, by_chunk;  // by_chunk: paths of the same chunk next to each other, not of the same bucket
 };
 dq_status dqx_whole_tables(const dq_ctx *ctx, const dqx_whole *desc, dqx_tables *tables);
+// Whether its search and what the replay needs of it are one launch, on this device, for a replay of so many waves; for the tests.
+int dqx_searches_and_arranges(uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32_t waves);
 // Adds to *wrong (device) how many results of the codec's reciprocal differ from the division's.
 dq_status dqx_reciprocals(uint32_t *wrong, void *hip_stream);
 // Where the waves of a replay of n_paths paths begin (dq_walk.hip), {path, tile} each and an end.

@@ -152,7 +152,7 @@ constexpr uint32_t kMostSearched = 65536;
 dq_status search(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width, uint32_t *places,
                  uint32_t *counts, Announce announce, hipStream_t stream);
 // Both in one launch, for one bucket; the places hold the rows' lists, where it takes them, and are not results.
-bool takes_search_arrange(uint32_t n_sg_per_bucket, uint32_t n_buckets);
+bool takes_search_arrange(uint32_t n_sg_per_bucket, uint32_t n_buckets, const Tables &tables);
 dq_status search_arrange(const float *F, const float *mu, uint32_t n_sg, uint64_t max_code_bits, uint32_t max_width, uint32_t *places, float *mu_main,
                          uint32_t *origin, Announce announce, const Tables &tables, hipStream_t stream);
 // Behind it: the means in reordered order (mu and mu_main, or both null), the origins, and the tables.

@@ -998,7 +998,7 @@ dq_status dqx_whole_run(const dq_ctx *ctx, const dqx_whole *desc, const void *co
   p.w.grads = grads;
   bool searched = false;
   dq_status st = *ticket ? dq::stats_all(tensors, ctx->cfg.n_workers, desc->dtype, (uint64_t)J * nb, floats(p.mu), floats(p.F), grads, s) : DQ_EINVAL;
-  const bool both = dq::takes_search_arrange(J, nb);
+  const bool both = dq::takes_search_arrange(J, nb, p.t);
   if (st == DQ_OK && both) {
     searched = true;
     st = dq::search_arrange(floats(p.F), means ? floats(p.mu) : nullptr, J, desc->max_code_bits, desc->max_width, words(p.places),

@@ -1658,9 +1658,9 @@ dq_status stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dty
 }
 
 // Whether the rows of a bucket list their norms first (the threshold is where that pays against k_search_positions and k_search_arrange)
-constexpr uint32_t kLeastListed = 40 * kAllocThreads, kMostListed = 256;  // blocks that list, a CU each
+constexpr uint32_t kLeastListed = 40 * kAllocThreads;
 static bool takes_lists(uint32_t J, uint32_t n_buckets, uint32_t max_width) {
-  return max_width == 8 && J >= kLeastListed && J <= kMostSearched && (uint64_t)(J / kAllocThreads) * n_buckets <= kMostListed;
+  return max_width == 8 && J >= kLeastListed && J <= kMostSearched && (uint64_t)(J / kAllocThreads) * n_buckets <= compute_units();  // a CU for each list
 }
 static_assert(kMostSearched == (uint32_t)kRegs * kAllocThreads && kMostTablePaths <= (uint32_t)kAllocThreads, "a register per norm, a thread per path");
 dq_status search(const float *F, uint32_t J, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width, uint32_t *places, uint32_t *counts,
@@ -1677,8 +1677,9 @@ dq_status search(const float *F, uint32_t J, uint32_t n_buckets, uint64_t max_co
   return launched();
 }
 
-bool takes_search_arrange(uint32_t J, uint32_t n_buckets) {
-  return n_buckets == 1 && J <= kMostSearched;
+// While there is a CU for every block (up to 64 rows and a few of tables): more would search one after the other, as a block's LDS leaves room for no other.
+bool takes_search_arrange(uint32_t J, uint32_t n_buckets, const Tables &tables) {
+  return n_buckets == 1 && J <= kMostSearched && (J + kAllocThreads - 1) / kAllocThreads + table_parts(tables) <= compute_units();
 }
 dq_status search_arrange(const float *F, const float *mu, uint32_t J, uint64_t max_code_bits, uint32_t max_width, uint32_t *places, float *mu_main,
                          uint32_t *origin, Announce announce, const Tables &tables, hipStream_t s) {
@@ -1739,6 +1740,12 @@ dq_status dq_stats_combine(const float *mu_all, const float *F_all, uint32_t n_w
     if (st != DQ_OK) return st;
   }
   return DQ_OK;
+}
+
+int dqx_searches_and_arranges(uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32_t waves) {
+  dq::Tables tables = {};
+  tables.waves = waves;
+  return dq::takes_search_arrange(n_sg_per_bucket, n_buckets, tables);
 }
 
 dq_status dqx_stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype dtype, uint64_t n_sg, float *mu, float *F,

@@ -179,7 +179,8 @@ def test_allocate_narrow_value_ranges(dev):
 @pytest.mark.parametrize("J,nb", [(1, 3), (1024, 300), (1025, 128), (1025, 129), (16384, 16), (16384, 17), (15361, 2), (40000, 6), (65536, 4)])
 @pytest.mark.parametrize("max_width", [8, 16])
 def test_allocate_where_every_row_searches(dev, J, nb, max_width):
-    """One launch while there is a CU for every row of every bucket, or a row is a bucket; a search and its positions beyond."""
+    """One launch for two rows and more while there is a CU for every row of every bucket; a search and its positions for one row, and beyond; at 40,960 and more
+    and up to 8 bits lists (which launches these are: test_allocation_launches.py)."""
     F = np.concatenate([lognormal_F(J + b, J, ties=min(J // 7, 40)) for b in range(nb)])
     check_allocate(dev, F, J, int(math.floor(prep.code_bits(4.0 if max_width == 8 else 7.0) * J)), max_width=max_width)
 
