@@ -44,9 +44,11 @@ dq_status dqx_bounds_end(void *hip_stream, int *out_of_bounds);
 dq_status dqx_fetch(const uint32_t *src, uint32_t n, uint32_t *dst_host, void *hip_stream);
 // dq_allocate, with the class counts sent to the host as soon as the search has them, while the rest of the call and what is enqueued after
 // it run (not under capture); dqx_allocate_end waits for them: rows of four.  A null ticket: not so (buckets above 65,536 super-groups,
-// more than 500 of them); dqx_fetch of the counts then.
+// more than 500 of them); dqx_fetch of the counts then.  No place for a ticket: they are not asked for.
+// lists: dqx_allocate_lists words of memory that the call's kernels may write to (0: it needs none), or null, which costs some large buckets a launch more.
+uint64_t dqx_allocate_lists(uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32_t max_width);
 dq_status dqx_allocate_begin(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width,
-                             uint8_t *widths, uint32_t *pos, uint32_t *counts, void *hip_stream, void **ticket);
+                             uint8_t *widths, uint32_t *pos, uint32_t *counts, uint32_t *lists, void *hip_stream, void **ticket);
 dq_status dqx_allocate_end(void *ticket, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32_t *rows, void *hip_stream);
 // dq_replay_create for a scratch that belongs to a stream (memory that its earlier work may still be using): the tables are
 // uploaded as work of that stream, nothing is waited for.  Not while the stream is captured.

@@ -22,7 +22,7 @@ PyObject *g_error = nullptr;  // binding.DqError
 #define DQ_SYMBOLS(X)                                                                                                    \
   X(dq_packed_bytes) X(dq_compress) X(dq_dar_hop) X(dq_decompress) X(dq_decompress_restore) X(dq_mx_packed_bytes)       \
   X(dq_mx_compress) X(dq_mx_dar_hop) X(dq_mx_decompress) X(dq_replay_run) X(dq_replay_run_steps) X(dq_sg_stats) X(dq_stats_combine) \
-  X(dq_allocate) X(dq_reorder) X(dq_reorder_mean) X(dq_restore) X(dq_status_str) X(dq_last_hip_error) X(dqx_bounds_begin) \
+  X(dqx_allocate_lists) X(dq_reorder) X(dq_reorder_mean) X(dq_restore) X(dq_status_str) X(dq_last_hip_error) X(dqx_bounds_begin) \
   X(dqx_bounds_end) X(dqx_fetch) X(dqx_allocate_begin) X(dqx_allocate_end) X(dqx_stats_all) \
   X(dqx_whole_scratch_bytes) X(dqx_whole_run)
 struct Lib {
@@ -381,8 +381,11 @@ PyObject *allocate(PyObject *const *a, bool ahead) {
   void *f = ptr(F), *w = ptr(widths), *p = ptr(pos), *c = ptr(counts), *s = stream(), *ticket = nullptr;
   const unsigned long long budget = number(a[2]);
   const uint32_t max_width = (uint32_t)number(a[3]);
-  if (ahead) CALL(dqx_allocate_begin(as<float>(f), (uint32_t)J, (uint32_t)nb, budget, max_width, as<uint8_t>(w), as<uint32_t>(p), as<uint32_t>(c), s, &ticket));
-  else CALL(dq_allocate(as<float>(f), (uint32_t)J, (uint32_t)nb, budget, max_width, as<uint8_t>(w), as<uint32_t>(p), as<uint32_t>(c), s));
+  at::Tensor lists;  // free again when the call returns: what is enqueued on its stream next may have the memory
+  if (const uint64_t words = L.dqx_allocate_lists((uint32_t)J, (uint32_t)nb, max_width)) lists = make((int64_t)words, at::kInt, F);
+  uint32_t *l = lists.defined() ? as<uint32_t>(lists.data_ptr()) : nullptr;
+  CALL(dqx_allocate_begin(as<float>(f), (uint32_t)J, (uint32_t)nb, budget, max_width, as<uint8_t>(w), as<uint32_t>(p), as<uint32_t>(c), l, s,
+                          ahead ? &ticket : nullptr));
   PyObject *t = PyTuple_New(ahead ? 4 : 3);
   PyTuple_SET_ITEM(t, 0, wrap(widths));
   PyTuple_SET_ITEM(t, 1, wrap(pos));

@@ -820,29 +820,6 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
   if (threadIdx.x < 64) put_search(J, T, S, pos_all + (uint64_t)blockIdx.x * J, counts_all + 5ull * blockIdx.x, announce);
 }
 
-// A whole allocation in one launch: grid (rows, buckets), every block searches for itself, on a CU that has nothing else to do, and then places its row.  Against a
-// search in one block and the positions behind it, a launch and the places' trip to memory and back are fewer; the device's time and the
-// host's are both less (statistics and allocation: 2 workers' 17,000 28.7 -> 26.4 us, 8 workers' 30,000 56.3 -> 53.7, of two buckets of 9,000 61.5 -> 59.3, 12 workers'
-// 60,000 up to 16 bits 113.4 -> 111.7).  While there is a CU for every row: more would search one after the other.  (Buckets of one row keep the two launches that
-// tests/test_launch_limits.py describes.)
-template <bool ALLOW16, bool ASIDE>
-__global__ void __launch_bounds__(kAllocThreads) k_search_positions(const float *F_all, uint32_t J, uint64_t max_code_bits, uint8_t *widths_all,
-                                                                    uint32_t *pos_all, uint32_t *counts_all, dq::Announce announce) {
-  __shared__ SearchSpace S;
-  __shared__ uint32_t mine_w[kAllocWaves][4];
-  const uint64_t first = (uint64_t)blockIdx.y * J;
-  const uint32_t row = blockIdx.x, j = row * kAllocThreads + threadIdx.x;
-  const float f = gld<float>(F_all + first + min(j, J - 1));
-  const uint32_t T = search_block<ALLOW16, ASIDE>(F_all + first, J, max_code_bits, S);
-  const RowPlaces p = row_places(J, S);
-  if (row == 0 && threadIdx.x == 0) put_counts(p.n_class, T, counts_all + 5ull * blockIdx.y, announce, blockIdx.y);
-  const Placed x = place_searched(f, j < J, row, T, ALLOW16, p, mine_w);
-  if (x.k < 4) {
-    gst<uint8_t>(widths_all + first + j, (uint8_t)(2u << x.k));
-    gst<uint32_t>(pos_all + first + j, x.at);
-  }
-}
-
 // ---------------------------------------------------------------------------------------
 // Buckets of 40 rows and more at 2, 4 and 8 bits, few enough that a block for each of their rows finds a CU: what takes the search above most of its time, looking at every
 // norm to find the tenth of them that matters, in a launch of its own on as many CUs as there are rows (k_list), the rest by one block behind it
@@ -1103,6 +1080,35 @@ __global__ void __launch_bounds__(kAllocThreads) k_search_listed(const float *F_
   uint32_t *pos = pos_all + (uint64_t)blockIdx.x * J;
   const uint32_t T = search_lists(F_all + (uint64_t)blockIdx.x * J, pos, J, max_code_bits, S);
   if (threadIdx.x < 64) put_search(J, T, S, pos, counts_all + 5ull * blockIdx.x, announce);
+}
+
+// Widths and positions by the blocks that search: grid (rows, buckets), every block searches for itself, on a CU that has nothing else to do, and then places its row.  Against a
+// search in one block and the positions behind it, a launch and the places' trip to memory and back are fewer; the device's time and the
+// host's are both less (statistics and allocation: 2 workers' 17,000 28.7 -> 26.4 us, 8 workers' 30,000 56.3 -> 53.7, of two buckets of 9,000 61.5 -> 59.3, 12 workers'
+// 60,000 up to 16 bits 113.4 -> 111.7).  While there is a CU for every row: more would search one after the other.  (Buckets of one row keep the two launches that
+// tests/test_launch_limits.py describes, though one is the better there, too: an allocation of 1,000 9.7 -> 8.1 us.)
+// LISTED: behind k_list, the lists in memory of their own (a block writes its positions while another may still be reading).  Against k_search_listed and
+// k_alloc_positions, 51,200 norms in one bucket 15.6 -> 14.7 us, in each of four 16.2 -> 14.6; 8 workers' statistics and allocation 63.7 -> 61.7, waited for
+// 98.1 -> 94.7 (a search by one block 68.7 and 93.8: what is waited for behind eight launches is the host's, and a launch more its 4 us).
+template <bool ALLOW16, bool ASIDE, bool LISTED>
+__global__ void __launch_bounds__(kAllocThreads) k_search_positions(const float *F_all, const uint32_t *lists_all, uint32_t J, uint64_t max_code_bits,
+                                                                    uint8_t *widths_all, uint32_t *pos_all, uint32_t *counts_all, dq::Announce announce) {
+  static_assert(!LISTED || (ASIDE && !ALLOW16), "");
+  __shared__ SearchSpace S;
+  __shared__ uint32_t mine_w[kAllocWaves][4];
+  const uint64_t first = (uint64_t)blockIdx.y * J;
+  const uint32_t row = blockIdx.x, j = row * kAllocThreads + threadIdx.x;
+  const float f = gld<float>(F_all + first + min(j, J - 1));
+  uint32_t T;
+  if constexpr (LISTED) T = search_lists(F_all + first, lists_all + first, J, max_code_bits, S);
+  else T = search_block<ALLOW16, ASIDE>(F_all + first, J, max_code_bits, S);
+  const RowPlaces p = row_places(J, S);
+  if (row == 0 && threadIdx.x == 0) put_counts(p.n_class, T, counts_all + 5ull * blockIdx.y, announce, blockIdx.y);
+  const Placed x = place_searched(f, j < J, row, T, ALLOW16, p, mine_w, LISTED && row == J / kAllocThreads);
+  if (x.k < 4) {
+    gst<uint8_t>(widths_all + first + j, (uint8_t)(2u << x.k));
+    gst<uint32_t>(pos_all + first + j, x.at);
+  }
 }
 
 // Behind the search of an all-reduce that replays on the original tensors: what k_alloc_positions and k_reorder_mean do between them, but for the
@@ -1753,12 +1759,18 @@ dq_status dqx_stats_all(const void *const *tensors, uint32_t n_workers, dq_dtype
   return dq::stats_all(tensors, n_workers, dtype, n_sg, mu, F, nullptr, (hipStream_t)hip_stream);
 }
 
-static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits,
-                          uint32_t max_width, uint8_t *widths, uint32_t *pos, uint32_t *counts, dq::Announce announce, void *hip_stream) {
+// Whether every row's block searches (k_search_positions).
+static bool rows_search(uint32_t J, uint32_t n_buckets) {
+  const uint32_t rows = (J + kAllocThreads - 1) / kAllocThreads;
+  return rows > 1 && rows <= (uint32_t)kRegs && (uint64_t)rows * n_buckets <= compute_units();
+}
+// lists: memory for the rows' lists (dqx_allocate_lists), or null: they lie in `pos`, and a launch of its own overwrites them.
+static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width, uint8_t *widths,
+                          uint32_t *pos, uint32_t *counts, uint32_t *lists, dq::Announce announce, void *hip_stream) {
   if (n_sg_per_bucket == 0 || n_buckets == 0) return DQ_OK;
   if (!F || !widths || !pos || !counts || (max_width != 8 && max_width != 16)) return DQ_EINVAL;
   if (max_code_bits < 2ull * n_sg_per_bucket) return DQ_EINVAL;  // fewer than 2 code bits per coordinate
-  if (!aligned(F, 4) || !aligned(pos, 4) || !aligned(counts, 4)) return DQ_EALIGN;
+  if (!aligned(F, 4) || !aligned(pos, 4) || !aligned(counts, 4) || !aligned(lists, 4)) return DQ_EALIGN;
   hipStream_t s = (hipStream_t)hip_stream;
   const bool allow16 = max_width == 16;
   const uint32_t J = n_sg_per_bucket, rows = (J + kAllocThreads - 1) / kAllocThreads;
@@ -1766,10 +1778,18 @@ static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_b
     const uint32_t nb = n_buckets - b0 < 65535u ? n_buckets - b0 : 65535u;
     const uint64_t off = (uint64_t)b0 * J;
     uint32_t *const cnt = counts + 5ull * b0;
-    if (rows > 1 && rows <= (uint32_t)kRegs && (uint64_t)rows * n_buckets <= compute_units() && !dq::takes_lists(J, nb, max_width)) {
-      const auto kernel = rows > 16 ? (allow16 ? k_search_positions<true, true> : k_search_positions<false, true>)
-                                    : (allow16 ? k_search_positions<true, false> : k_search_positions<false, false>);
-      hipLaunchKernelGGL(kernel, dim3(rows, nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, widths + off, pos + off, cnt, announce);
+    const bool listed = dq::takes_lists(J, nb, max_width);
+    if (rows_search(J, n_buckets) && (lists || !listed)) {
+      if (listed) {
+        hipLaunchKernelGGL(k_list, dim3(J / kAllocThreads, nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, lists + off);
+        const dq_status st = launched();
+        if (st != DQ_OK) return st;
+      }
+      const auto kernel = listed      ? k_search_positions<false, true, true>
+                          : rows > 16 ? (allow16 ? k_search_positions<true, true, false> : k_search_positions<false, true, false>)
+                                      : (allow16 ? k_search_positions<true, false, false> : k_search_positions<false, false, false>);
+      hipLaunchKernelGGL(kernel, dim3(rows, nb), dim3(kAllocThreads), 0, s, F + off, listed ? lists + off : nullptr, J, max_code_bits, widths + off, pos + off,
+                         cnt, announce);
     } else if (rows <= (uint32_t)kRegs) {
       const dq_status st = dq::search(F + off, J, nb, max_code_bits, max_width, pos + off, cnt, announce, s);
       if (st != DQ_OK) return st;
@@ -1785,19 +1805,23 @@ static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_b
 
 dq_status dq_allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits,
                       uint32_t max_width, uint8_t *widths, uint32_t *pos, uint32_t *counts, void *hip_stream) {
-  return allocate(F, n_sg_per_bucket, n_buckets, max_code_bits, max_width, widths, pos, counts, dq::Announce{nullptr, 0}, hip_stream);
+  return allocate(F, n_sg_per_bucket, n_buckets, max_code_bits, max_width, widths, pos, counts, nullptr, dq::Announce{nullptr, 0}, hip_stream);
+}
+
+uint64_t dqx_allocate_lists(uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32_t max_width) {
+  return rows_search(n_sg_per_bucket, n_buckets) && dq::takes_lists(n_sg_per_bucket, n_buckets, max_width) ? (uint64_t)n_sg_per_bucket * n_buckets : 0;
 }
 
 dq_status dqx_allocate_begin(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width,
-                             uint8_t *widths, uint32_t *pos, uint32_t *counts, void *hip_stream, void **ticket) {
-  *ticket = nullptr;
+                             uint8_t *widths, uint32_t *pos, uint32_t *counts, uint32_t *lists, void *hip_stream, void **ticket) {
   dq::Announce announce = {nullptr, 0};
-  if (n_buckets != 0 && n_sg_per_bucket != 0 && n_sg_per_bucket <= (uint32_t)(kRegs * kAllocThreads)) {
+  if (ticket) *ticket = nullptr;
+  if (ticket && n_buckets != 0 && n_sg_per_bucket != 0 && n_sg_per_bucket <= (uint32_t)(kRegs * kAllocThreads)) {
     const hipError_t e = dq::announce_begin(n_buckets, (hipStream_t)hip_stream, &announce, ticket);
     if (e != hipSuccess) return dq::hip_status(e);
   }
-  const dq_status st = allocate(F, n_sg_per_bucket, n_buckets, max_code_bits, max_width, widths, pos, counts, announce, hip_stream);
-  if (st != DQ_OK && *ticket) {
+  const dq_status st = allocate(F, n_sg_per_bucket, n_buckets, max_code_bits, max_width, widths, pos, counts, lists, announce, hip_stream);
+  if (st != DQ_OK && ticket && *ticket) {
     dq::announce_drop(*ticket);
     *ticket = nullptr;
   }

@@ -45,6 +45,26 @@ def test_routes_of_an_allocation(runtime, J, nb, max_width, n_cu, route):
 """)
 
 
+@pytest.mark.parametrize("J,nb,max_width,n_cu,listed", [
+    (40959, 1, 8, 256, 0), (40960, 1, 8, 256, 1), (51200, 5, 8, 256, 1), (51201, 5, 8, 256, 1), (51201, 5, 8, 254, 0), (65536, 4, 8, 256, 1), (65536, 1, 16, 256, 0),
+    (51200, 1, 8, 49, 0), (51201, 1, 8, 50, 0), (65537, 1, 8, 256, 0),
+])
+def test_lists_in_memory_of_their_own_save_a_launch(runtime, J, nb, max_width, n_cu, listed):
+    """With as much as dqx_allocate_lists asks for, a launch of every list's block and one of every row's: as many as a search by one block has."""
+    run(runtime, n_cu, f"""
+        L.dqx_allocate_lists.argtypes, L.dqx_allocate_lists.restype = [W, W, W], U
+        assert L.dqx_allocate_lists({J}, {nb}, {max_width}) == {J * nb * listed}
+        if {listed}:
+            F, widths, pos, counts, lists = 1 << 40, 1 << 50, 1 << 52, 1 << 54, 1 << 55
+            L.dqx_allocate_begin.argtypes = [P, W, W, U, W, P, P, P, P, P, P]
+            assert L.dqx_allocate_begin(F, {J}, {nb}, {4 * J}, {max_width}, widths, pos, counts, lists, None, None) == 0
+            first, second = launches()
+            assert list(first.grid) == [{J // 1024}, {nb}, 1] and first.args[0] == F and first.args[3] == lists
+            assert list(second.grid) == [{-(-J // 1024)}, {nb}, 1] and second.args[:2] == [F, lists]
+            assert L.dqx_allocate_begin(F, {J}, {nb}, {4 * J}, {max_width}, widths, pos, counts, lists + 2, None, None) != 0 and not launches()
+""")
+
+
 @pytest.mark.parametrize("J,nb,waves,n_cu,one", [(65536, 1, 5120, 256, 1), (65536, 1, 5120, 70, 1), (65536, 1, 5120, 69, 0), (8192, 1, 2072, 11, 1), (8192, 1, 2072, 10, 0),
                                                  (65537, 1, 5120, 256, 0), (1024, 2, 512, 256, 0)])
 def test_an_all_reduce_searches_once_per_row_only_where_each_has_a_cu(runtime, J, nb, waves, n_cu, one):

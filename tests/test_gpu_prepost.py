@@ -3,6 +3,7 @@
 before it (never the other way round): statistics within the tolerance of fp32 accumulation
 against the float64 definition, everything that is an integer decision or a single rounded
 operation bit-exactly."""
+import ctypes
 import math
 
 import numpy as np
@@ -280,6 +281,18 @@ def test_allocate_from_lists(dev, J, kind):
         F[::2] = 0
     for bits in (2.1, 4.0, 7.5):
         check_allocate(dev, F, J, int(bits * J))
+
+
+@pytest.mark.parametrize("J,nb", [(40960, 1), (41983, 2), (65536, 4)])
+def test_allocate_without_memory_for_lists(dev, J, nb):
+    """The C entry, whose rows list their norms where the positions go: the same as the binding's, whose lists have memory of their own."""
+    F = torch.from_numpy(lognormal_F(J, J * nb, ties=40)).to(dev)
+    want = B.dq_allocate(F, J, 4 * J)
+    got = [torch.empty_like(w) for w in want]
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert B.lib().dq_allocate(F.data_ptr(), J, nb, 4 * J, 8, *(g.data_ptr() for g in got), stream) == 0
+    for g, w in zip(got, want):
+        assert torch.equal(g, w)
 
 
 def test_allocate_more_buckets_than_a_grid_dimension(dev):
