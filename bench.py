@@ -345,7 +345,8 @@ def prepost_context(W, reps):
     c = state["counts"].cpu().numpy()[0]
 
     # does the allocation of bucket k+1 hide beside the replay of bucket k?  `reps` replays on the current
-    # stream and `reps` allocations on a second stream of the same (default) priority, forked and joined
+    # stream and `reps` allocations on a second stream of the same (default) priority, enqueued in turn (all of one
+    # kind first, and the other waits for the host: 8 to 12 us a call), forked and joined
     # ONCE (a cross-stream dependency costs tens of microseconds: per round it would swamp the answer)
     side = torch.cuda.Stream()
     t_replay = timed(W.rp.run)
@@ -355,11 +356,10 @@ def prepost_context(W, reps):
         a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         a.record()
         side.wait_stream(torch.cuda.current_stream())
-        with torch.cuda.stream(side):
-            for _ in range(reps):
-                f_alloc()
         for _ in range(reps):
             W.rp.run()
+            with torch.cuda.stream(side):
+                B.dq_allocate(state["F"], n_sg, budget, beside=True)
         torch.cuda.current_stream().wait_stream(side)
         b.record()
         b.synchronize()
@@ -399,7 +399,7 @@ def prepost_context(W, reps):
         "allocate_beside_replay_us": {"replay_alone": round(t_replay, 1), "allocate_alone": round(t_alloc, 1),
                                       "both_on_two_streams": round(t_both, 1),
                                       "allocation_hidden_frac": hidden(t_alloc, t_both),
-                                      "note": "per repetition, from one fork and one join around 20 repetitions on each stream"},
+                                      "note": "per repetition, from one fork and one join around 20 repetitions on each stream, enqueued in turn; beside=True"},
         "reorder_replay_restore_us": {"three_passes": round(t_three, 1), "fused_into_the_replay": round(t_fused, 1),
                                       "same_bits": same},
         "note": "all workers per figure (stats and reorder: one launch per worker); GB/s = bytes read + written",

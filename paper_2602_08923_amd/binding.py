@@ -373,16 +373,18 @@ def widths_of_buckets(counts):
     return [v[i:i + 4] for i in range(0, len(v), 5)]
 
 
-def dq_allocate(F, n_sg_per_bucket, max_code_bits, max_width=8):
+def dq_allocate(F, n_sg_per_bucket, max_code_bits, max_width=8, beside=False):
     """F: float32 [n_buckets * n_sg_per_bucket] -> (widths uint8, pos int32 (holds uint32),
-    counts int32 [n_buckets, 5] = #2-bit, #4-bit, #8-bit, #16-bit, threshold pattern)."""
-    return _native().allocate(F, n_sg_per_bucket, int(max_code_bits), int(max_width))
+    counts int32 [n_buckets, 5] = #2-bit, #4-bit, #8-bit, #16-bit, threshold pattern).
+    beside: the call runs on a stream of its own beside work that fills the chip, such as another bucket's replay; it takes few CUs then,
+    holds that work up less, and is itself a little slower.  The same results."""
+    return _native().allocate(F, n_sg_per_bucket, int(max_code_bits), int(max_width), beside)
 
 
-def allocate_ahead(F, n_sg_per_bucket, max_code_bits, max_width=8):
+def allocate_ahead(F, n_sg_per_bucket, max_code_bits, max_width=8, beside=False):
     """dq_allocate, and a function that returns widths_of_buckets(counts).  The search sends the counts to the host as soon as it
     has them: what is enqueued between this call and that one runs while the host waits and plans."""
-    widths, pos, counts, ticket = _native().allocate_begin(F, n_sg_per_bucket, int(max_code_bits), int(max_width))
+    widths, pos, counts, ticket = _native().allocate_begin(F, n_sg_per_bucket, int(max_code_bits), int(max_width), beside)
     known = []
 
     def by_width():

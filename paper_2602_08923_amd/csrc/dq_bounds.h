@@ -46,9 +46,10 @@ dq_status dqx_fetch(const uint32_t *src, uint32_t n, uint32_t *dst_host, void *h
 // it run (not under capture); dqx_allocate_end waits for them: rows of four.  A null ticket: not so (buckets above 65,536 super-groups,
 // more than 500 of them); dqx_fetch of the counts then.  No place for a ticket: they are not asked for.
 // lists: dqx_allocate_lists words of memory that the call's kernels may write to (0: it needs none), or null, which costs some large buckets a launch more.
+// beside: for a call on a stream of its own beside work that has the chip: few blocks rather than a short call.  The same results.
 uint64_t dqx_allocate_lists(uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32_t max_width);
 dq_status dqx_allocate_begin(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width,
-                             uint8_t *widths, uint32_t *pos, uint32_t *counts, uint32_t *lists, void *hip_stream, void **ticket);
+                             uint8_t *widths, uint32_t *pos, uint32_t *counts, uint32_t *lists, int beside, void *hip_stream, void **ticket);
 dq_status dqx_allocate_end(void *ticket, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32_t *rows, void *hip_stream);
 // dq_replay_create for a scratch that belongs to a stream (memory that its earlier work may still be using): the tables are
 // uploaded as work of that stream, nothing is waited for.  Not while the stream is captured.

@@ -381,10 +381,12 @@ PyObject *allocate(PyObject *const *a, bool ahead) {
   void *f = ptr(F), *w = ptr(widths), *p = ptr(pos), *c = ptr(counts), *s = stream(), *ticket = nullptr;
   const unsigned long long budget = number(a[2]);
   const uint32_t max_width = (uint32_t)number(a[3]);
+  const int beside = PyObject_IsTrue(a[4]);
+  if (beside < 0) throw Raised();
   at::Tensor lists;  // free again when the call returns: what is enqueued on its stream next may have the memory
-  if (const uint64_t words = L.dqx_allocate_lists((uint32_t)J, (uint32_t)nb, max_width)) lists = make((int64_t)words, at::kInt, F);
+  if (const uint64_t words = beside ? 0 : L.dqx_allocate_lists((uint32_t)J, (uint32_t)nb, max_width)) lists = make((int64_t)words, at::kInt, F);
   uint32_t *l = lists.defined() ? as<uint32_t>(lists.data_ptr()) : nullptr;
-  CALL(dqx_allocate_begin(as<float>(f), (uint32_t)J, (uint32_t)nb, budget, max_width, as<uint8_t>(w), as<uint32_t>(p), as<uint32_t>(c), l, s,
+  CALL(dqx_allocate_begin(as<float>(f), (uint32_t)J, (uint32_t)nb, budget, max_width, as<uint8_t>(w), as<uint32_t>(p), as<uint32_t>(c), l, beside, s,
                           ahead ? &ticket : nullptr));
   PyObject *t = PyTuple_New(ahead ? 4 : 3);
   PyTuple_SET_ITEM(t, 0, wrap(widths));
@@ -398,12 +400,12 @@ PyObject *allocate(PyObject *const *a, bool ahead) {
   }
   return t;
 }
-PyObject *py_allocate(PyObject *const *a, Py_ssize_t nargs) {  // F, n_sg_per_bucket, max_code_bits, max_width
-  DQ_ARGS(4)
+PyObject *py_allocate(PyObject *const *a, Py_ssize_t nargs) {  // F, n_sg_per_bucket, max_code_bits, max_width, beside
+  DQ_ARGS(5)
   return allocate(a, false);
 }
 PyObject *py_allocate_begin(PyObject *const *a, Py_ssize_t nargs) {  // the same; also a ticket for the counts on the host, or None
-  DQ_ARGS(4)
+  DQ_ARGS(5)
   return allocate(a, true);
 }
 PyObject *py_allocate_end(PyObject *const *a, Py_ssize_t nargs) {  // ticket -> rows of four counts

@@ -828,14 +828,14 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
 // goes where the row's positions go (the last whole row's block also has what follows it, up to 1,023 norms).  Sums over the lists' heads are exact: where the
 // threshold is not inside the bracket (norms in an order that the sample's steps meet) the one block searches as before.  Rows with more inside than their list holds
 // it looks at itself, up to 16; where there are more, it goes on as before from the bracket, whose costs are known.
-// What bounds both is their chains, some 5 and 6 us.  Kernels' time for 51,200 norms, one search -> both: lognormal 18.6 -> 12.5, sorted 20.2 -> 20.7, rows of
+// What bounds both is their chains, 6 to 8 us each.  Kernels' time for 51,200 norms, one search -> both: lognormal 18.6 -> 12.5, sorted 20.2 -> 20.7, rows of
 // like norms 18.8 -> 17.6, within a factor of two of each other 22.4 -> 20.3, within a tenth 27.2 -> 27.6, equal 56.8 -> 51.8 (a bucket's statistics and
 // allocation 76.1 -> 70.4).  Not with 16-bit widths, whose brackets are wider (20.9 -> 21.2), nor below some 41,000 norms, where all in one launch, which the host enqueues
 // sooner, is the better (statistics and allocation, one launch and listed: 2 workers' 33,000 28.2 and 31.0, 40,000 30.6 and 30.7, 4 workers' 50,000 44.9 and 41.4; all-reduces
 // over 6 of 30,000 62.5 and 64.2, over 8 of 42,664 88.9 and 86.9, the listed ones with k_arrange apart, 1.5 more than now).  An all-reduce of one bucket has
 // the second part in every block of its next launch (k_search_arrange).
-// What it costs: on a second stream beside a replay that fills the chip, blocks on 50 CUs hold up more of the replay's waves than one does (8 workers' 25 MB: 53 us
-// alone, 65.4 with a search by one block beside it, 70 to 74 so).
+// Beside a replay the short blocks of k_list and one block behind them hold up less than the search by one block (51,200 norms and a 25 MB replay, enqueued in turn, 51.9 us
+// a pair and 53.2; the replay alone 50.4).
 constexpr uint32_t kSample = 8192, kFine = 18, kFineBins = 8192;  // bins of 2^18 patterns: 0x7F8 << 2 of them are finite
 struct ListHead {
   uint32_t n;                        // events, or kTooLong: more than the list holds
@@ -1765,8 +1765,12 @@ static bool rows_search(uint32_t J, uint32_t n_buckets) {
   return rows > 1 && rows <= (uint32_t)kRegs && (uint64_t)rows * n_buckets <= compute_units();
 }
 // lists: memory for the rows' lists (dqx_allocate_lists), or null: they lie in `pos`, and a launch of its own overwrites them.
+// beside: another stream's work has the chip, and no more than a CU of each bucket is taken for the search (lists of large buckets aside, whose blocks are short).
+// Beside replays of 25 MB over 8 workers (50.3 us alone), one of each enqueued in turn, us a pair, every row's block searching -> so: 8,192 norms 52.6 -> 51.5,
+// 16,384 53.9 -> 51.0, 30,000 56.2 -> 51.7, five buckets of them 59.1 -> 51.8, 51,200 (lists either way) 53.4 -> 52.7, in each of four buckets 58.5 -> 53.2, up to 16
+// bits 61.0 -> 55.3; alone 9.7 and 12.0, 11.8 and 14.2, 16.0 and 18.8, 16.1 and 18.9, 15.0 and 16.8, 15.1 and 17.4, 23.2 and 25.2.
 static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width, uint8_t *widths,
-                          uint32_t *pos, uint32_t *counts, uint32_t *lists, dq::Announce announce, void *hip_stream) {
+                          uint32_t *pos, uint32_t *counts, uint32_t *lists, bool beside, dq::Announce announce, void *hip_stream) {
   if (n_sg_per_bucket == 0 || n_buckets == 0) return DQ_OK;
   if (!F || !widths || !pos || !counts || (max_width != 8 && max_width != 16)) return DQ_EINVAL;
   if (max_code_bits < 2ull * n_sg_per_bucket) return DQ_EINVAL;  // fewer than 2 code bits per coordinate
@@ -1779,7 +1783,7 @@ static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_b
     const uint64_t off = (uint64_t)b0 * J;
     uint32_t *const cnt = counts + 5ull * b0;
     const bool listed = dq::takes_lists(J, nb, max_width);
-    if (rows_search(J, n_buckets) && (lists || !listed)) {
+    if (!beside && rows_search(J, n_buckets) && (lists || !listed)) {
       if (listed) {
         hipLaunchKernelGGL(k_list, dim3(J / kAllocThreads, nb), dim3(kAllocThreads), 0, s, F + off, J, max_code_bits, lists + off);
         const dq_status st = launched();
@@ -1805,7 +1809,7 @@ static dq_status allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_b
 
 dq_status dq_allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits,
                       uint32_t max_width, uint8_t *widths, uint32_t *pos, uint32_t *counts, void *hip_stream) {
-  return allocate(F, n_sg_per_bucket, n_buckets, max_code_bits, max_width, widths, pos, counts, nullptr, dq::Announce{nullptr, 0}, hip_stream);
+  return allocate(F, n_sg_per_bucket, n_buckets, max_code_bits, max_width, widths, pos, counts, nullptr, false, dq::Announce{nullptr, 0}, hip_stream);
 }
 
 uint64_t dqx_allocate_lists(uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32_t max_width) {
@@ -1813,14 +1817,14 @@ uint64_t dqx_allocate_lists(uint32_t n_sg_per_bucket, uint32_t n_buckets, uint32
 }
 
 dq_status dqx_allocate_begin(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits, uint32_t max_width,
-                             uint8_t *widths, uint32_t *pos, uint32_t *counts, uint32_t *lists, void *hip_stream, void **ticket) {
+                             uint8_t *widths, uint32_t *pos, uint32_t *counts, uint32_t *lists, int beside, void *hip_stream, void **ticket) {
   dq::Announce announce = {nullptr, 0};
   if (ticket) *ticket = nullptr;
   if (ticket && n_buckets != 0 && n_sg_per_bucket != 0 && n_sg_per_bucket <= (uint32_t)(kRegs * kAllocThreads)) {
     const hipError_t e = dq::announce_begin(n_buckets, (hipStream_t)hip_stream, &announce, ticket);
     if (e != hipSuccess) return dq::hip_status(e);
   }
-  const dq_status st = allocate(F, n_sg_per_bucket, n_buckets, max_code_bits, max_width, widths, pos, counts, lists, announce, hip_stream);
+  const dq_status st = allocate(F, n_sg_per_bucket, n_buckets, max_code_bits, max_width, widths, pos, counts, lists, beside != 0, announce, hip_stream);
   if (st != DQ_OK && ticket && *ticket) {
     dq::announce_drop(*ticket);
     *ticket = nullptr;

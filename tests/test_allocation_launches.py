@@ -56,12 +56,25 @@ def test_lists_in_memory_of_their_own_save_a_launch(runtime, J, nb, max_width, n
         assert L.dqx_allocate_lists({J}, {nb}, {max_width}) == {J * nb * listed}
         if {listed}:
             F, widths, pos, counts, lists = 1 << 40, 1 << 50, 1 << 52, 1 << 54, 1 << 55
-            L.dqx_allocate_begin.argtypes = [P, W, W, U, W, P, P, P, P, P, P]
-            assert L.dqx_allocate_begin(F, {J}, {nb}, {4 * J}, {max_width}, widths, pos, counts, lists, None, None) == 0
+            L.dqx_allocate_begin.argtypes = [P, W, W, U, W, P, P, P, P, C.c_int, P, P]
+            assert L.dqx_allocate_begin(F, {J}, {nb}, {4 * J}, {max_width}, widths, pos, counts, lists, 0, None, None) == 0
             first, second = launches()
             assert list(first.grid) == [{J // 1024}, {nb}, 1] and first.args[0] == F and first.args[3] == lists
             assert list(second.grid) == [{-(-J // 1024)}, {nb}, 1] and second.args[:2] == [F, lists]
-            assert L.dqx_allocate_begin(F, {J}, {nb}, {4 * J}, {max_width}, widths, pos, counts, lists + 2, None, None) != 0 and not launches()
+            assert L.dqx_allocate_begin(F, {J}, {nb}, {4 * J}, {max_width}, widths, pos, counts, lists + 2, 0, None, None) != 0 and not launches()
+""")
+
+
+@pytest.mark.parametrize("J,nb,max_width,listed", [(1, 1, 8, 0), (1025, 1, 8, 0), (16384, 16, 16, 0), (30000, 2, 8, 0), (40959, 1, 8, 0), (40960, 1, 8, 1), (51200, 1, 16, 0),
+                                                   (65536, 4, 8, 1), (65536, 5, 8, 0)])
+def test_an_allocation_beside_other_work_searches_on_a_cu_for_each_bucket(runtime, J, nb, max_width, listed):
+    """Whether it is given memory for lists or not."""
+    grids = [[J // 1024, nb, 1]] * listed + [[nb, 1, 1], [-(-J // 1024), nb, 1]]
+    run(runtime, 256, f"""
+        L.dqx_allocate_begin.argtypes = [P, W, W, U, W, P, P, P, P, C.c_int, P, P]
+        for lists in (None, 1 << 55):
+            assert L.dqx_allocate_begin(1 << 40, {J}, {nb}, {4 * J}, {max_width}, 1 << 50, 1 << 52, 1 << 54, lists, 1, None, None) == 0
+            assert [list(l.grid) for l in launches()] == {grids}
 """)
 
 

@@ -295,6 +295,23 @@ def test_allocate_without_memory_for_lists(dev, J, nb):
         assert torch.equal(g, w)
 
 
+@pytest.mark.parametrize("J,nb,max_width", [(1, 1, 8), (1025, 2, 8), (16385, 3, 16), (30000, 1, 8), (41983, 2, 8), (65537, 1, 8)])
+def test_allocate_beside_other_work(dev, J, nb, max_width):
+    """Fewer blocks, the same bits; the counts that are sent ahead, too."""
+    F = torch.from_numpy(lognormal_F(J, J * nb, ties=min(J // 7, 40))).to(dev)
+    want = B.dq_allocate(F, J, 4 * J, max_width=max_width)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        plain = B.dq_allocate(F, J, 4 * J, max_width=max_width, beside=True)
+        *ahead, by_width = B.allocate_ahead(F, J, 4 * J, max_width=max_width, beside=True)
+        assert by_width() == [row[:4] for row in want[2].cpu().tolist()]
+    side.synchronize()
+    for got in (plain, ahead):
+        for g, w in zip(got, want):
+            assert torch.equal(g, w)
+
+
 def test_allocate_more_buckets_than_a_grid_dimension(dev):
     """70,000 buckets of 5 super-groups: the positions launch is cut at 65,535 buckets (the grid's second
     dimension); buckets on both sides of the cut must come out right."""
