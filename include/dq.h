@@ -257,8 +257,9 @@ dq_status dq_stats_combine(const float *mu_all, const float *F_all, uint32_t n_w
  *   pos[j]     its index inside the reordered bucket: all 2-bit super-groups first, then the
  *              4-bit, 8-bit and 16-bit ones, each class in original order (Section 3.5)
  *   counts[5b .. 5b+4] = {#2-bit, #4-bit, #8-bit, #16-bit, bit pattern of T48} of bucket b
- * The search runs in one thread block per bucket; for buckets of up to 65,536 super-groups the widths
- * and positions are written by a second launch spread over the GPU. */
+ * For buckets of up to 65,536 super-groups every row of 1,024 searches in a block of its own while the GPU has a
+ * CU for each, and writes its widths and positions; otherwise, and for buckets of one row, the search is one
+ * block per bucket, with a second launch for widths and positions.  pos holds scratch data in between. */
 dq_status dq_allocate(const float *F, uint32_t n_sg_per_bucket, uint32_t n_buckets, uint64_t max_code_bits,
                       uint32_t max_width, uint8_t *widths, uint32_t *pos, uint32_t *counts, void *hip_stream);
 

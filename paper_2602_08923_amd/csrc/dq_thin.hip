@@ -10,10 +10,10 @@
 // schedules come here.
 //
 // What bounds it is how much of a hop's chain four waves per SIMD cover: two vector instructions can go per four cycles, from two waves,
-// and about half of that is reached (256 workers, 4,096 super-groups: 93 instructions per hop, 169 to 175 us; 88 would be their issue).  So all
-// instructions count, on the path or beside it, scalar ones and waits too: both super-group draws made by one generator call, the next four tensors
-// by one scalar load and the group scale left in fp32 took 188 us there to 184, four workers' fp32 ring of 4,096 with all-gather from 9.9 to 9.1;
-// the super-group's maximum and scale in scalar registers and the rounding of the group scale in two instructions 185 to 177.
+// and about half of that is reached (256 workers, 4,096 super-groups: 93 instructions per hop, 159 to 169 us from card to card; 88 would be their issue).  So all
+// instructions count, on the path or beside it, scalar ones and waits too.  Earlier states against each other, in turn on one card, as are the pairs further down: both super-group
+// draws made by one generator call, the next four tensors by one scalar load and the group scale left in fp32 took 188 us there to 184, four workers' fp32 ring of 4,096 with
+// all-gather from 9.9 to 9.1; the super-group's maximum and scale in scalar registers and the rounding of the group scale in two instructions 185 to 177.
 // (All comparisons of a hop before its selections, which saves the waits between them: 192.)
 //
 // What differs from the wide tile:

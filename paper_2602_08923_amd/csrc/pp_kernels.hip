@@ -207,11 +207,11 @@ __global__ void __launch_bounds__(kThreads) k_combine(const float *mu_all, const
 }
 
 // ---------------------------------------------------------------------------------------
-// Allocation: the search in one block of 1024 threads per bucket.  Super-group j = 1024*k + t sits in slot k
-// of thread t (a register when the bucket has at most 64 rows of 1024), so every global access
-// is coalesced.  Values are handled as int32 bit patterns: non-negative floats order like their
+// Allocation: a search is one block of 1024 threads (of which a bucket has one, or one for each of its rows of 1024 super-groups).  In buckets of at most
+// 64 rows the threads hold all norms in registers, four neighbours each, so every global access
+// is coalesced; larger ones are read again in every pass.  Values are handled as int32 bit patterns: non-negative floats order like their
 // patterns, and the difference of two patterns below 2^31 has the sign of the comparison,
-// F >= theta  <=>  bits(F) - bits(theta) >= 0.  Negative values and NaN count as +0; slots past
+// F >= theta  <=>  bits(F) - bits(theta) >= 0.  Negative values and NaN count as +0; places past
 // the bucket's end hold -1, which is below every threshold.
 constexpr int kAllocThreads = 1024;
 constexpr int kAllocWaves = kAllocThreads / 64;
@@ -297,7 +297,7 @@ __global__ void __launch_bounds__(kAllocThreads) k_alloc_positions(const float *
 // suffix counts give at the bins' boundaries a lower and an upper bound of the cost (c8 is exact there, c4 and c16 lie between the counts of two
 // bins), which leave 1 to 3 bins of 2^20 patterns.  The next two look at the places where the cost falls: a norm v costs 4 bits less beyond the threshold v,
 // 2 less beyond the last threshold T whose tied one is at most v, 8 less beyond the last whose other tied one is.  One histogram of those places,
-// weighted, has the cost at every boundary as a suffix sum: up to 4096 bins, then 1024 of single patterns.
+// weighted, has the cost at every boundary as a suffix sum: up to 4096 bins, then up to 2048 of single patterns.
 //
 // What bounds it: one CU's vector ALU and LDS (51,200 norms are 800 wave instructions for every instruction of a pass,
 // and an LDS atomic of a wave takes 12 cycles) and, for small buckets, the barriers and scans of the levels.
@@ -351,8 +351,10 @@ __device__ __forceinline__ uint32_t last_tied(uint32_t v, float by, float back, 
   return below;
 }
 
-// A block's LDS: the first level's counters, over which the threads then lay their norms that the other levels look at, and those levels' counters: 86 KB.  A search that runs beside a whole replay waits for a CU that has that much in one piece, and registers for sixteen waves; two blocks
-// of k_walk (29 KB, 96 registers) may stay beside it.
+// A block's LDS: the first level's counters, over which the threads then lay their norms that the other levels look at, and those levels' counters: 91,520 bytes.  A search that
+// runs beside a whole replay waits for a CU that has that much in one piece, and registers for sixteen waves; two blocks
+// of k_walk (29 KB, 96 registers) may stay beside k_search, k_search_listed and k_search_positions (91,520 to 92,032 bytes), one beside k_search_arrange (116,768), whose first
+// blocks make the replay's tables.
 constexpr uint32_t kFirstWords = (kBins + 1) * kCopies;
 static_assert((kKept + 1) * kAllocThreads <= kFirstWords, "the norms set aside");
 
@@ -361,6 +363,7 @@ struct SearchSpace {
   alignas(16) uint32_t places[kPlaces + 4], last_places[kLastPlaces];  // places[kPlaces]: beyond the bracket
   uint32_t wsum[2][kAllocWaves], wfit[kAllocWaves], row_n[kRegs][3], crossing[2][2], exact[2][3][kAllocWaves];
 };
+static_assert(sizeof(SearchSpace) == 91520, "two blocks of k_walk beside one that searches");
 // h[b] for b < BINS becomes the sum of h[b], h[b + 1], ..., the thread's own bins in x between the two halves, which a
 // barrier separates
 template <typename X>
@@ -830,7 +833,7 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
 // it looks at itself, up to 16; where there are more, it goes on as before from the bracket, whose costs are known.
 // What bounds both is their chains, 6 to 8 us each.  Kernels' time for 51,200 norms, one search -> both: lognormal 18.6 -> 12.5, sorted 20.2 -> 20.7, rows of
 // like norms 18.8 -> 17.6, within a factor of two of each other 22.4 -> 20.3, within a tenth 27.2 -> 27.6, equal 56.8 -> 51.8 (a bucket's statistics and
-// allocation 76.1 -> 70.4).  Not with 16-bit widths, whose brackets are wider (20.9 -> 21.2), nor below some 41,000 norms, where all in one launch, which the host enqueues
+// allocation 76.1 -> 69.6, search and positions in one launch).  Not with 16-bit widths, whose brackets are wider (20.9 -> 21.2), nor below some 41,000 norms, where all in one launch, which the host enqueues
 // sooner, is the better (statistics and allocation, one launch and listed: 2 workers' 33,000 28.2 and 31.0, 40,000 30.6 and 30.7, 4 workers' 50,000 44.9 and 41.4; all-reduces
 // over 6 of 30,000 62.5 and 64.2, over 8 of 42,664 88.9 and 86.9, the listed ones with k_arrange apart, 1.5 more than now).  An all-reduce of one bucket has
 // the second part in every block of its next launch (k_search_arrange).
