@@ -927,13 +927,14 @@ bool plan_whole(const dq_ctx *ctx, const dqx_whole *d, WholePlan *p) {
   t.by_chunk = by_chunk_number(w, nb, J);
   t.entry_bytes = (uint32_t)elt_size(d->dtype);
   // A tile per wave at most, found by counting, which takes the arrange launch or the search before it 1 to 3 us less than weighing the tiles.  Not where the waves that a
-  // path's one to three tiles fewer leave without one are more than a 16th, nor where they give some CU a block more than the fullest has without them, or
-  // fill the last round of CUs: the fullest CU is what a replay waits for.  All-reduces, us, weighed and counted: tiles of one super-group 6 % faster counted on
-  // average of 3,618; of two and four, inside this line 7 % (931, three of them 2 to 5 % slower), outside 2 % slower to 18 % slower where a CU gets a block more
-  // (fp32 ring of 57, 2 x 5,529: 714 blocks, counted 798, 227 and 269; bf16 of 16 by halves, 5 x 1,664 at up to 16 bits: 262 and 290 blocks, 55.2 and 58.2).
+  // path's one to three tiles fewer leave without one are more than a 16th; nor, over more than eight workers and unless they are less than a 96th, where they give some CU a
+  // block more than the fullest has without them, or fill the last round of CUs: the fullest CU is what a replay waits for, hop by hop.  All-reduces, us, weighed and counted:
+  // tiles of one super-group 6 % faster counted on average of 3,618; of two and four, without a block more 7 % (931, three of them 2 to 5 % slower), with one 6 % inside this line
+  // (828, 20 of them 2 to 5 % slower) and outside, of 2,633, 10 % faster to 18 % slower (fp32 ring of 57, 2 x 5,529: 714 blocks, counted 798, 227 and 269; of 37, 12,062 up
+  // to 16 bits 760, 787, 165 and 199; bf16 of 16 by halves, 5 x 1,664 up to 16 bits: 262 and 290 blocks, 55.2 and 58.2; but of 8, 8,160 511 and 516, 35.1 and 31.8).
   const uint64_t each = (m + w.tile_sgs - 1) / w.tile_sgs, slots = w.tile_sgs == 1 ? each : each + 3, slot_blocks = (slots * w.n_paths + w.waves - 1) / w.waves;
   const bool fuller = (slot_blocks - 1) / ctx->n_cu != (w.blocks - 1) / ctx->n_cu || slot_blocks / ctx->n_cu != w.blocks / ctx->n_cu;
-  if (slot_blocks <= w.most_blocks && slots <= each + each / 16 && !fuller) {
+  if (slot_blocks <= w.most_blocks && slots <= each + each / (fuller && n > 8 ? 96 : 16)) {
     t.slots = (uint32_t)slots;
     w.blocks = (uint32_t)slot_blocks;
   }
