@@ -824,17 +824,17 @@ __global__ void __launch_bounds__(kAllocThreads) k_search(const float *F_all, ui
 }
 
 // ---------------------------------------------------------------------------------------
-// Buckets of 40 rows and more at 2, 4 and 8 bits, few enough that a block for each of their rows finds a CU: what takes the search above most of its time, looking at every
-// norm to find the tenth of them that matters, in a launch of its own on as many CUs as there are rows (k_list), the rest by one block behind it
-// (k_search_listed).  Every block of k_list brackets the threshold by itself, from the same sample of 8,192 norms and bins of 2^18 patterns, four standard
+// Buckets of 40 rows and more at 2, 4 and 8 bits, few enough that a block for each of their rows has a CU: what takes the search above most of its time, looking at every
+// norm to find the tenth of them that matters, in a launch of its own on as many CUs as there are rows (k_list), the rest by every row's block behind it
+// (k_search_positions) or by one (k_search_listed).  Every block of k_list brackets the threshold by itself, from the same sample of 8,192 norms and bins of 2^18 patterns, four standard
 // deviations of the sampled cost to either side, and lists what its own 1,024 norms cost up to where inside the bracket, with how many lie above.  A list
-// goes where the row's positions go (the last whole row's block also has what follows it, up to 1,023 norms).  Sums over the lists' heads are exact: where the
-// threshold is not inside the bracket (norms in an order that the sample's steps meet) the one block searches as before.  Rows with more inside than their list holds
+// goes to memory of its own, or where the row's positions go (the last whole row's block also has what follows it, up to 1,023 norms).  Sums over the lists' heads are exact: where the
+// threshold is not inside the bracket (norms in an order that the sample's steps meet) a block searches as without lists.  Rows with more inside than their list holds
 // it looks at itself, up to 16; where there are more, it goes on as before from the bracket, whose costs are known.
 // What bounds both is their chains, 6 to 8 us each.  Kernels' time for 51,200 norms, one search -> both: lognormal 18.6 -> 12.5, sorted 20.2 -> 20.7, rows of
 // like norms 18.8 -> 17.6, within a factor of two of each other 22.4 -> 20.3, within a tenth 27.2 -> 27.6, equal 56.8 -> 51.8 (a bucket's statistics and
 // allocation 76.1 -> 69.6, search and positions in one launch).  Not with 16-bit widths, whose brackets are wider (20.9 -> 21.2), nor below some 41,000 norms, where all in one launch, which the host enqueues
-// sooner, is the better (statistics and allocation, one launch and listed: 2 workers' 33,000 28.2 and 31.0, 40,000 30.6 and 30.7, 4 workers' 50,000 44.9 and 41.4; all-reduces
+// sooner, is the better (statistics and allocation, one launch and listed in three: 2 workers' 33,000 28.2 and 31.0, 40,000 30.6 and 30.7, 4 workers' 50,000 44.9 and 41.4; all-reduces
 // over 6 of 30,000 62.5 and 64.2, over 8 of 42,664 88.9 and 86.9, the listed ones with k_arrange apart, 1.5 more than now).  An all-reduce of one bucket has
 // the second part in every block of its next launch (k_search_arrange).
 // Beside a replay the short blocks of k_list and one block behind them hold up less than the search by one block (51,200 norms and a 25 MB replay, enqueued in turn, 51.9 us
@@ -1077,6 +1077,7 @@ __device__ __forceinline__ uint32_t search_lists(const float *F, const uint32_t 
   return T;  // (the last list's row has what follows it, too: of the row after it nobody reads the first places, and sums over all are the same)
 }
 
+// The lists lie in `pos`: for callers without other memory for them, beside other work, and for several buckets of an all-reduce (whose k_arrange is behind it).
 __global__ void __launch_bounds__(kAllocThreads) k_search_listed(const float *F_all, uint32_t J, uint64_t max_code_bits, uint32_t *pos_all,
                                                                  uint32_t *counts_all, dq::Announce announce) {
   __shared__ SearchSpace S;
