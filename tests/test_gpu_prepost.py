@@ -312,6 +312,26 @@ def test_allocate_beside_other_work(dev, J, nb, max_width):
             assert torch.equal(g, w)
 
 
+def test_allocate_from_lists_in_a_graph(dev):
+    """The lists' memory is free again within the capture, and what is captured next takes it: every replay, with the program's own work in between, is as the call itself."""
+    J, nb = 41983, 2
+    F = torch.from_numpy(lognormal_F(J, J * nb, ties=40)).to(dev)
+    B.dq_allocate(F, J, 4 * J)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = B.dq_allocate(F, J, 4 * J)
+        filled = torch.full((J * nb,), -1, dtype=torch.int32, device=dev)
+        beside = B.dq_allocate(F, J, 4 * J, beside=True)
+    for replay in range(3):
+        F.copy_(torch.from_numpy(lognormal_F(J + replay, J * nb, ties=7)))
+        graph.replay()
+        want = B.dq_allocate(F, J, 4 * J)
+        torch.cuda.synchronize()
+        assert bool((filled == -1).all())
+        for g, b, w in zip(got, beside, want):
+            assert torch.equal(g, w) and torch.equal(b, w)
+
+
 def test_allocate_more_buckets_than_a_grid_dimension(dev):
     """70,000 buckets of 5 super-groups: the positions launch is cut at 65,535 buckets (the grid's second
     dimension); buckets on both sides of the cut must come out right."""
